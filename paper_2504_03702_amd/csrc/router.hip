@@ -4,11 +4,22 @@
 // peak_i = the largest value, over the next `window` iterations, of instance i's look-ahead map with
 // the request virtually added (P + t tokens at iteration t < D).  Decisions are sequential by
 // definition (a dispatched request changes its instance's queue and map for the next one), so one
-// workgroup walks the micro-batch with all state on chip (in the registers of the instances' threads where the
-// windows are short enough, else in LDS): TPI threads per instance scan its window, the
-// scores are reduced to the minimum (lowest index on ties) with wavefront shuffles and one exchange
-// through LDS, and the winner's threads add the request to its window.  Integer arithmetic
-// throughout: the decisions are exact.
+// workgroup walks the micro-batch with all state on chip.  Integer arithmetic throughout: the
+// decisions are exact.
+//
+// The walk is a chain of dependent decisions, so what counts is the latency of one of them.  Scanning an
+// instance's window for every request is most of that, and is not needed: with D' = min(D, window),
+//     peak = max(P + max_{t < D'} (w[t] + t),  max_{t >= D'} w[t]),
+// a prefix maximum and a suffix maximum that change only for the instance a request is dispatched to.
+// They are kept per block of the window (at most 32 blocks: at window 100 the blocks are 4 slots), so a score
+// reads one prefix, one suffix and the one block that D' falls into.  One thread per instance scores it; the
+// wavefront that owns the chosen instance adds the request to its window with one lane per block and rebuilds
+// both rows of maxima with one scan (prefixes in lanes 0..31, suffixes, in reverse order, in lanes 32..63),
+// while the other wavefronts are already at the next request.  An instance's state is touched by its own
+// wavefront only, so the exchange of the wavefronts' minima is the one barrier of a request; up to 64
+// instances need none.
+// 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
+// window in registers for every request, 3.14 ms this way.
 #include "device_util.h"
 #include "internal.h"
 
@@ -16,214 +27,273 @@ namespace {
 
 const int kRouteThreads = 1024;
 const int kRouteLdsBytes = 160 * 1024;       // all of a compute unit's LDS
+const int kRouteMaxBlocks = 32;              // blocks of a window: one lane each in either half of the update's scan
 
-__global__ __launch_bounds__(kRouteThreads) void route_kernel(
-    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
-    int window, int tpi, int32_t* __restrict__ window_tokens, const int32_t* __restrict__ capacity,
-    int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct, int beta,
-    int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    long long* s_qp = (long long*)lds_raw;                       // [n_inst]
-    long long* s_cd = s_qp + n_inst;                             // [n_inst]
-    long long* s_best = s_cd + n_inst;                           // [2][16] per-wavefront minimum score
-    int* s_best_i = (int*)(s_best + 32);                         // [2][16] and its instance
-    int* s_cap = s_best_i + 32;                                  // [n_inst]
-    int2* s_req = (int2*)(s_cap + n_inst + (n_inst & 1));         // [1024] (P, D) of the requests being walked
-    long long* s_out_s = (long long*)(s_req + kRouteThreads);    // [1024] their scores
-    int* s_out_i = (int*)(s_out_s + kRouteThreads);              // [1024] and instances, written out per chunk: a
-                                                                 // global store per request would be waited for at
-                                                                 // every barrier
-    int* s_win = s_out_i + kRouteThreads;                        // [n_inst][window]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < n_inst; i += kRouteThreads) { s_qp[i] = queued_p[i]; s_cd[i] = current_d[i]; s_cap[i] = capacity[i]; }
-    for (int i = tid; i < n_inst * window; i += kRouteThreads) s_win[i] = window_tokens[i];
-    __syncthreads();
-    const int inst = tid / tpi, sub = tid % tpi;
-    const bool mine = inst < n_inst;
-    int* row = s_win + (mine ? inst : 0) * window;
-    const long long kNone = 0x7fffffffffffffffll;
-    bool range_fault = false;
-    for (int r = 0; r < n_req; ++r) {
-        if ((r & (kRouteThreads - 1)) == 0) {
-            // results of the last 1024 requests out, the next 1024 requests in
-            __syncthreads();
-            if (r > 0) { assigned[r - kRouteThreads + tid] = s_out_i[tid]; score100[r - kRouteThreads + tid] = s_out_s[tid]; }
-            if (r + tid < n_req) s_req[tid] = make_int2(prompt_tokens[r + tid], pred_tokens[r + tid]);
-            __syncthreads();
+// How the windows lie in LDS: 16-byte pieces of four consecutive slots, [piece][instance], `pitch` instances apart
+// (odd where that fits, so that one instance's pieces fall in different banks); behind them the two tables of
+// block maxima, [block][instance].
+struct RoutePlan {
+    int block;                               // slots per block, a multiple of 4
+    int n_blocks, pitch;
+    size_t lds_bytes;
+};
+
+RoutePlan plan_route(int n_inst, int window) {
+    RoutePlan p;
+    const int whole = (window + 3) / 4 * 4;
+    for (int block = 4 * ((window + 4 * kRouteMaxBlocks - 1) / (4 * kRouteMaxBlocks));; block *= 2) {
+        if (block > whole) block = whole;
+        p.block = block;
+        p.n_blocks = window > 0 ? (window + block - 1) / block : 0;
+        // small blocks make the cheapest scores; larger ones, and at last the plain pitch and a single block, are
+        // for maps that fill the LDS
+        for (int odd = 1; odd >= 0; --odd) {
+            p.pitch = odd ? n_inst | 1 : n_inst;
+            p.lds_bytes = 512 + (size_t)p.pitch * 4 * ((size_t)p.n_blocks * block + 2 * (size_t)(p.n_blocks + 1));
+            if (p.lds_bytes <= (size_t)kRouteLdsBytes) return p;
         }
-        const int slot = r & (kRouteThreads - 1);
-        const int2 pd = s_req[slot];
-        const int P = pd.x, D = pd.y;                           // uniform
-        if (P < 0 || D < 0) {
-            if (tid == 0) { s_out_i[slot] = -1; s_out_s[slot] = 0; report_fault(st, PS_ST_BAD_RECORD, r); }
-            __syncthreads();                                    // keeps the one-barrier-per-request rhythm of the exchange slots
-            continue;
-        }
-        long long peak = -kNone;
-        if (mine)
-            for (int t = sub; t < window; t += tpi) peak = max(peak, (long long)row[t] + (t < D ? (long long)P + t : 0ll));
-        for (int o = tpi >> 1; o > 0; o >>= 1) peak = max(peak, __shfl_xor(peak, o, 64));
-        long long L = kNone;
-        if (mine && sub == 0) {
-            const long long pen = window > 0 ? max(0ll, 100 * peak - (long long)t_mem_pct * s_cap[inst]) : 0ll;
-            L = 100 * (s_qp[inst] + P + s_cd[inst] + D) + (long long)beta * pen;
-        }
-        int bi = mine ? inst : 0x7fffffff;
-        // minimum over the wavefront, lowest instance on ties
-        for (int o = 32; o > 0; o >>= 1) {
-            const long long oL = __shfl_xor(L, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (oL < L || (oL == L && oi < bi)) { L = oL; bi = oi; }
-        }
-        // the exchange slots alternate between requests, so one barrier per request is enough: a slot
-        // is rewritten two requests later, after the barrier of the request in between
-        const int par = (r & 1) * 16;
-        if (lane == 0) { s_best[par + wave] = L; s_best_i[par + wave] = bi; }
-        __syncthreads();
-        long long bL = s_best[par];
-        int bI = s_best_i[par];
-        for (int w = 1; w < kRouteThreads / 64; ++w) {
-            const long long oL = s_best[par + w];
-            const int oi = s_best_i[par + w];
-            if (oL < bL || (oL == bL && oi < bI)) { bL = oL; bI = oi; }
-        }
-        if (tid == 0) { s_out_i[slot] = bI; s_out_s[slot] = bL; }
-        if (mine && inst == bI) {
-            const int stop = min(D, window);
-            for (int t = sub; t < stop; t += tpi) {
-                const long long v = (long long)row[t] + P + t;
-                if (v > 2147483647ll) range_fault = true;
-                row[t] = (int)v;
-            }
-            if (sub == 0) { s_qp[inst] += P; s_cd[inst] += D; }
-        }
-        // no barrier here: an instance's window and counters are only ever touched by its own threads
+        if (block == whole) return p;
     }
-    __syncthreads();
-    {   // results of the last, possibly partial, chunk
-        const int done = n_req & ~(kRouteThreads - 1), first = done == n_req ? n_req - kRouteThreads : done;
-        if (first + tid < n_req) { assigned[first + tid] = s_out_i[tid]; score100[first + tid] = s_out_s[tid]; }
-    }
-    if (range_fault) report_fault(st, PS_ST_RANGE, -1);
-    for (int i = tid; i < n_inst; i += kRouteThreads) { queued_p[i] = s_qp[i]; current_d[i] = s_cd[i]; }
-    for (int i = tid; i < n_inst * window; i += kRouteThreads) window_tokens[i] = s_win[i];
 }
 
-// The same walk with every instance's window in the registers of its TPI threads (thread `sub` of an instance
-// owns iterations sub, sub + TPI, ...; at most kRegSlots each).  32-bit arithmetic: a running bound B on every
-// window value is kept, and a request that could take a sum to 2^31 (B + P + window) is reported as a range
-// fault before it is scored.  The sixteen wavefronts' minima are combined by every wavefront in parallel (one
-// entry per lane, shuffles) instead of a serial scan.
-const int kRegSlots = 32;
-
-__global__ __launch_bounds__(kRouteThreads) void route_reg_kernel(
-    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
-    int window, int tpi, int32_t* __restrict__ window_tokens, const int32_t* __restrict__ capacity,
-    int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct, int beta,
-    int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
-    __shared__ long long s_best[2][16];
-    __shared__ int s_best_i[2][16];
-    __shared__ int2 s_req[kRouteThreads];
-    __shared__ long long s_out_s[kRouteThreads];
-    __shared__ int s_out_i[kRouteThreads];
-    __shared__ int s_max[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int inst = tid / tpi, sub = tid % tpi;
-    const bool mine = inst < n_inst;
-    const int kMin = (int)0x80000000;
-    int r[kRegSlots];                            // dead slots (beyond the window, or no instance) hold the minimum
-    int top = kMin;
-#pragma unroll
-    for (int i = 0; i < kRegSlots; ++i) {
-        const int t = sub + tpi * i;
-        r[i] = mine && t < window ? window_tokens[(int64_t)inst * window + t] : kMin;
-        top = max(top, r[i]);
+// DPP moves with the operation's identity where no lane is read, so that they fold into the operation.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_max(int v) {
+    return max(v, __builtin_amdgcn_update_dpp((int)0x80000000, v, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_min(int v) {
+    return min(v, __builtin_amdgcn_update_dpp(0x7fffffff, v, CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_min64(long long v) {
+    const int lo = (int)v, hi = (int)(v >> 32);
+    const int olo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const int ohi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    const long long o = ((long long)ohi << 32) | (unsigned)olo;
+    return o < v ? o : v;
+}
+// Minimum of v over the wavefront (lanes that take no part hold 2^63 - 1) and the lowest lane that has it.  Scores
+// hardly ever leave 32 bits (that takes 2^31 / 100 tokens on one instance): then the minimum is taken in one
+// register, else in two.
+__device__ __forceinline__ long long wave_min(long long v, bool part, int& src) {
+    const int lo = (int)v;
+    if (!__any(part && (int)(v >> 32) != (lo >> 31))) {
+        const int x = part ? lo : 0x7fffffff;
+        int m = dpp_min<0x111, 0xf>(x);          // row_shr 1, 2, 4, 8: lane 15 of a row has the row's minimum
+        m = dpp_min<0x112, 0xf>(m);
+        m = dpp_min<0x114, 0xf>(m);
+        m = dpp_min<0x118, 0xf>(m);
+        m = dpp_min<0x142, 0xa>(m);              // row_bcast 15 into rows 1 and 3
+        m = dpp_min<0x143, 0xc>(m);              // row_bcast 31 into rows 2 and 3: lane 63 has it
+        m = __builtin_amdgcn_readlane(m, 63);
+        src = __builtin_ctzll(__ballot(x == m)); // (some lane holds it)
+        return m;
     }
-    long long qp = 0, cd = 0, cap = 0;
-    if (mine && sub == 0) { qp = queued_p[inst]; cd = current_d[inst]; cap = capacity[inst]; }
-    // B: an upper bound on every window value, uniform over the workgroup
-    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
-    if (lane == 0) s_max[wave] = top;
+    long long m = dpp_min64<0x111, 0xf>(v);
+    m = dpp_min64<0x112, 0xf>(m);
+    m = dpp_min64<0x114, 0xf>(m);
+    m = dpp_min64<0x118, 0xf>(m);
+    m = dpp_min64<0x142, 0xa>(m);
+    m = dpp_min64<0x143, 0xc>(m);
+    const unsigned mlo = (unsigned)__builtin_amdgcn_readlane((int)m, 63);
+    m = ((long long)__builtin_amdgcn_readlane((int)(m >> 32), 63) << 32) | mlo;
+    src = __builtin_ctzll(__ballot(v == m));
+    return m;
+}
+
+// Launched with 1024 threads: all of them bring the windows in, then the wavefronts without instances leave.
+// SMALL: a block is one 16-byte piece (windows of 1 to 128 slots whose tables fit).
+template <bool SMALL>
+__global__ __launch_bounds__(kRouteThreads) void route_kernel(
+    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
+    int window, int block, int n_blocks, int pitch, int32_t* __restrict__ window_tokens,
+    const int32_t* __restrict__ capacity, int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct,
+    int beta, int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    int4* s_best = (int4*)lds_raw;                               // [2][16] a wavefront's minimum: score, instance, peak
+    int4* s_win = (int4*)(lds_raw + 512);                        // [pieces][pitch]
+    const int pieces = n_blocks * (block >> 2);
+    // maxima by block, with a row of minima for "no block": row b of s_pre is over the blocks below b, of w[t] + t;
+    // row b of s_suf over the blocks from b on, of w[t]
+    int* s_pre = (int*)(s_win + (size_t)pieces * pitch);         // [n_blocks + 1][pitch]
+    int* s_suf = s_pre + (n_blocks + 1) * pitch;                 // [n_blocks + 1][pitch]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kMin = (int)0x80000000;
+    const int nw = (n_inst + 63) >> 6;                           // wavefronts that own instances
+    // windows in: a wavefront takes whole rows; the slots that fill the last piece hold the minimum, to which
+    // nothing is ever added
+    for (int t0 = 0; t0 < 4 * pieces; t0 += 64) {
+        const int t = t0 + lane;
+        for (int i0 = wave; i0 < n_inst; i0 += 16 * 8) {
+            int v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + 16 * u;
+                v[u] = i < n_inst && t < window ? window_tokens[(int64_t)i * window + t] : kMin;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + 16 * u;
+                if (i < n_inst && t < 4 * pieces) ((int*)(s_win + (t >> 2) * pitch + i))[t & 3] = v[u];
+            }
+        }
+    }
+    const int inst = tid;
+    const bool mine = inst < n_inst;
+    long long qp = 0, s100 = 0, thr = 0;
+    if (mine) {
+        qp = queued_p[inst];
+        s100 = 100 * (qp + current_d[inst]);
+        thr = (long long)t_mem_pct * capacity[inst];
+        s_pre[inst] = kMin;
+        s_suf[n_blocks * pitch + inst] = kMin;
+    }
     __syncthreads();
-    long long B = kMin;
-    for (int w = 0; w < 16; ++w) B = max(B, (long long)s_max[w]);
+    if (wave >= nw) return;
+
+    // One instance's window with a request's ramp added on its first Dc slots, and its two rows of block maxima:
+    // all lanes of its wavefront, lane j and lane 32 + n_blocks - 1 - j for block j.
+    const int chunks = SMALL ? 1 : block >> 2;
+    const bool u_low = lane < 32, u_live = (lane & 31) < n_blocks;
+    const int u_blk = u_live ? (u_low ? lane & 31 : n_blocks - 1 - (lane & 31)) : 0;
+    int4* const u_win = s_win + u_blk * chunks * pitch;
+    int* const u_out = u_low ? s_pre + (u_blk + 1) * pitch : s_suf + u_blk * pitch;
+    auto update = [&](int i, int P, int Dc) {
+        int m = kMin;
+        for (int c = 0; c < chunks; ++c) {
+            int4* at = u_win + c * pitch + i;
+            const int4 v4 = *at;
+            int v[4] = {v4.x, v4.y, v4.z, v4.w};
+            const int t0 = u_blk * (SMALL ? 4 : block) + 4 * c;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int t = t0 + e;
+                v[e] = (int)((unsigned)v[e] + (t < Dc ? (unsigned)(P + t) : 0u));
+                m = max(m, (int)((unsigned)v[e] + (u_low && t < window ? (unsigned)t : 0u)));
+            }
+            if (u_low && u_live) *at = make_int4(v[0], v[1], v[2], v[3]);
+        }
+        m = u_live ? m : kMin;
+        m = dpp_max<0x111, 0xf>(m);
+        m = dpp_max<0x112, 0xf>(m);
+        m = dpp_max<0x114, 0xf>(m);
+        m = dpp_max<0x118, 0xf>(m);
+        m = dpp_max<0x142, 0xa>(m);                              // the halves stay apart: lane 15 to row 1, 47 to row 3
+        if (u_live) u_out[i] = m;
+        // the next score reads what other lanes have written: LDS serves a wavefront in order, the compiler has to
+        // keep that order
+        asm volatile("" ::: "memory");
+    };
+    if (SMALL) {
+        // every thread its own instance's rows
+        if (mine) {
+            int m = kMin;
+            for (int b = 0; b < n_blocks; ++b) {
+                const int4 v = s_win[b * pitch + inst];
+                const int t = 4 * b;
+                m = max(m, (int)((unsigned)v.x + (unsigned)t));
+                if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
+                if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
+                if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
+                s_pre[(b + 1) * pitch + inst] = m;
+            }
+            m = kMin;
+            for (int b = n_blocks - 1; b >= 0; --b) {
+                const int4 v = s_win[b * pitch + inst];
+                m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
+                s_suf[b * pitch + inst] = m;
+            }
+        }
+        asm volatile("" ::: "memory");
+    } else if (n_blocks > 0) {
+        for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(i, 0, 0);
+    }
+    // top: the largest window value of all instances, uniform
+    int top = mine ? s_suf[inst] : kMin;
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+    if (nw > 1) {
+        if (lane == 0) s_best[16 + wave].x = top;
+        __syncthreads();
+        for (int w = 0; w < nw; ++w) top = max(top, s_best[16 + w].x);
+    }
+    top = __builtin_amdgcn_readfirstlane(top);
+
     const long long kNone = 0x7fffffffffffffffll;
     bool range_fault = false;
-    for (int q = 0; q < n_req; ++q) {
-        if ((q & (kRouteThreads - 1)) == 0) {
-            // results of the last 1024 requests out, the next 1024 requests in
-            __syncthreads();
-            if (q > 0) { assigned[q - kRouteThreads + tid] = s_out_i[tid]; score100[q - kRouteThreads + tid] = s_out_s[tid]; }
-            if (q + tid < n_req) s_req[tid] = make_int2(prompt_tokens[q + tid], pred_tokens[q + tid]);
-            __syncthreads();
-        }
-        const int slot = q & (kRouteThreads - 1);
-        const int2 pd = s_req[slot];
-        const int P = pd.x, D = pd.y;                           // uniform
-        if (P < 0 || D < 0) {
-            if (tid == 0) { s_out_i[slot] = -1; s_out_s[slot] = 0; report_fault(st, PS_ST_BAD_RECORD, q); }
-            __syncthreads();                                    // keeps the one-barrier-per-request rhythm of the exchange slots
-            continue;
-        }
-        if (B + P + window >= 2147483647ll) range_fault = true; // a sum below may leave the int32 range
-        int pk = kMin;
-        const int Pt = P + sub;                                 // P + t of this thread's first iteration
-#pragma unroll
-        for (int i = 0; i < kRegSlots; ++i) {
-            const int t = sub + tpi * i;
-            const unsigned add = t < D ? (unsigned)(Pt + tpi * i) : 0u;
-            pk = max(pk, (int)((unsigned)r[i] + add));          // (a dead slot stays far below any live one)
-        }
-        for (int o = tpi >> 1; o > 0; o >>= 1) pk = max(pk, __shfl_xor(pk, o, 64));
-        long long L = kNone;
-        if (mine && sub == 0) {
-            const long long pen = max(0ll, 100 * (long long)pk - (long long)t_mem_pct * cap);
-            L = 100 * (qp + P + cd + D) + (long long)beta * pen;
-        }
-        int bi = mine ? inst : 0x7fffffff;
-        // minimum over the wavefront, lowest instance on ties
-        for (int o = 32; o > 0; o >>= 1) {
-            const long long oL = __shfl_xor(L, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (oL < L || (oL == L && oi < bi)) { L = oL; bi = oi; }
-        }
-        // the exchange slots alternate between requests, so one barrier per request is enough: a slot
-        // is rewritten two requests later, after the barrier of the request in between
-        const int par = q & 1;
-        if (lane == 0) { s_best[par][wave] = L; s_best_i[par][wave] = bi; }
-        __syncthreads();
-        long long bL = lane < 16 ? s_best[par][lane] : kNone;
-        int bI = lane < 16 ? s_best_i[par][lane] : 0x7fffffff;
-        for (int o = 8; o > 0; o >>= 1) {
-            const long long oL = __shfl_xor(bL, o, 64);
-            const int oi = __shfl_xor(bI, o, 64);
-            if (oL < bL || (oL == bL && oi < bI)) { bL = oL; bI = oi; }
-        }
-        bL = __shfl(bL, 0, 64);
-        bI = __shfl(bI, 0, 64);
-        if (tid == 0) { s_out_i[slot] = bI; s_out_s[slot] = bL; }
-        if (mine && inst == bI) {
-#pragma unroll
-            for (int i = 0; i < kRegSlots; ++i) {
-                const int t = sub + tpi * i;
-                if (t < D && t < window) r[i] = (int)((unsigned)r[i] + (unsigned)(Pt + tpi * i));
+    const int ic = mine ? inst : 0;
+    const int row4 = pitch * 4, row16 = pitch * 16;              // bytes from a row of the tables to the next
+    int nP = 0, nD = 0;                                          // lane l: request l of the next 64
+    if (lane < n_req) { nP = prompt_tokens[lane]; nD = pred_tokens[lane]; }
+    for (int base = 0; base < n_req; base += 64) {
+        const int cnt = min(64, n_req - base);
+        const int vP = nP, vD = nD;
+        // blocks below b lie under the request's ramp whole, block b is looked at slot by slot (where the ramp ends on
+        // a block boundary that only repeats what the tables say), blocks from the next one on keep their values
+        const int vDc = min(max(vD, 0), window), vb = n_blocks > 0 ? vDc / block : 0;
+        const int vs = n_blocks > 0 ? (vDc + block - 1) / block : 0;
+        const int v_pre = vb * row4, v_suf = vs * row4, v_win = max(min(vb, n_blocks - 1), 0);
+        if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
+        int out_i = -1, out_lo = 0, out_hi = 0;
+        for (int q = 0; q < cnt; ++q) {
+            const int P = __builtin_amdgcn_readlane(vP, q), D = __builtin_amdgcn_readlane(vD, q);
+            // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
+            const int par = (q & 1) * 16;
+            if (P < 0 || D < 0) {
+                if (tid == 0) report_fault(st, PS_ST_BAD_RECORD, base + q);
+                if (nw > 1) __builtin_amdgcn_s_barrier();
+                continue;
             }
-            if (sub == 0) { qp += P; cd += D; }
+            const int Dc = __builtin_amdgcn_readlane(vDc, q), blk = __builtin_amdgcn_readlane(v_win, q);
+            const int pre = *(const int*)((const char*)(s_pre + ic) + __builtin_amdgcn_readlane(v_pre, q));
+            const int suf = *(const int*)((const char*)(s_suf + ic) + __builtin_amdgcn_readlane(v_suf, q));
+            int pk = kMin;
+            for (int c = 0; c < chunks; ++c) {
+                const int4 v = *(const int4*)((const char*)(s_win + ic) + (blk * chunks + c) * row16);
+                const int t = blk * (SMALL ? 4 : block) + 4 * c;
+                pk = max(max(pk, (int)((unsigned)v.x + (t < Dc ? (unsigned)(P + t) : 0u))),
+                         (int)((unsigned)v.y + (t + 1 < Dc ? (unsigned)(P + t + 1) : 0u)));
+                pk = max(max(pk, (int)((unsigned)v.z + (t + 2 < Dc ? (unsigned)(P + t + 2) : 0u))),
+                         (int)((unsigned)v.w + (t + 3 < Dc ? (unsigned)(P + t + 3) : 0u)));
+            }
+            pk = max(max(pk, (int)((unsigned)pre + (unsigned)P)), suf);
+            long long pen = 100 * (long long)pk - thr;
+            pen = pen > 0 && (SMALL || window > 0) ? pen : 0;
+            if (beta != 1) pen *= beta;
+            const long long add100 = 100 * ((long long)P + D);
+            const long long L = mine ? s100 + (pen + add100) : kNone;
+            // minimum over the wavefront, lowest instance on ties
+            int src;
+            long long best = wave_min(L, mine, src);
+            int best_i = 64 * wave + src, best_pk = __builtin_amdgcn_readlane(pk, src);
+            if (nw > 1) {
+                if (lane == 0) s_best[par + wave] = make_int4((int)best, (int)(best >> 32), best_i, best_pk);
+                // (LDS only: __syncthreads would also wait for the results' global stores)
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                const int4 o = s_best[par + (lane & 15)];        // (slots no wavefront writes are not looked at)
+                const int o_lo = o.x, o_hi = o.y, o_i = o.z, o_pk = o.w;
+                // (wavefronts are in the order of their instances)
+                best = wave_min(lane < nw ? ((long long)o_hi << 32) | (unsigned)o_lo : kNone, lane < nw, src);
+                best_i = __builtin_amdgcn_readlane(o_i, src);
+                best_pk = __builtin_amdgcn_readlane(o_pk, src);
+            }
+            if (lane == q) { out_i = best_i; out_lo = (int)best; out_hi = (int)(best >> 32); }
+            if (inst == best_i) { qp += P; s100 += add100; }
+            if (SMALL || window > 0) {
+                if ((long long)top + P + window >= 2147483647ll) range_fault = true;   // a sum may have left int32
+                top = max(top, best_pk);                         // the chosen instance's largest value from now on
+                if ((best_i >> 6) == wave && Dc > 0) update(best_i, P, Dc);
+            }
         }
-        B += (long long)P + window;                             // every new value is at most an old one + P + window
-    }
-    __syncthreads();
-    {   // results of the last, possibly partial, chunk
-        const int done = n_req & ~(kRouteThreads - 1), first = done == n_req ? n_req - kRouteThreads : done;
-        if (first + tid < n_req) { assigned[first + tid] = s_out_i[tid]; score100[first + tid] = s_out_s[tid]; }
+        if (wave == 0 && lane < cnt) {
+            assigned[base + lane] = out_i;
+            score100[base + lane] = ((long long)out_hi << 32) | (unsigned)out_lo;
+        }
     }
     if (range_fault && tid == 0) report_fault(st, PS_ST_RANGE, -1);
-    if (mine && sub == 0) { queued_p[inst] = qp; current_d[inst] = cd; }
-#pragma unroll
-    for (int i = 0; i < kRegSlots; ++i) {
-        const int t = sub + tpi * i;
-        if (mine && t < window) window_tokens[(int64_t)inst * window + t] = r[i];
-    }
+    if (mine) { queued_p[inst] = qp; current_d[inst] = s100 / 100 - qp; }
+    for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i)
+        for (int t = lane; t < window; t += 64) window_tokens[(int64_t)i * window + t] = ((const int*)(s_win + (t >> 2) * pitch + i))[t & 3];
 }
 
 }  // namespace
@@ -237,26 +307,28 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     if (n_req == 0) return PS_OK;
     if (!prompt_tokens || !pred_tokens || !assigned || !score100) return PS_EINVAL;
     if (n_inst > kRouteThreads) return PS_EUNSUPPORTED;
-    const size_t lds = (size_t)n_inst * 20 + 32 * 12 + 20 * (size_t)kRouteThreads + (size_t)n_inst * window * 4 + 64;
-    if (lds > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
-    int tpi = 64;                                               // threads per instance: a power of two, <= 64
-    while (tpi > 1 && (int64_t)tpi * n_inst > kRouteThreads) tpi >>= 1;
+    // the limit the header states; every map within it has a plan that fits (plan_route's last one, a single block
+    // per window, takes less)
+    if ((size_t)n_inst * 20 + (size_t)n_inst * window * 4 + 20928 > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
+    const RoutePlan p = plan_route(n_inst, window);
+    if (p.lds_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
     static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
     if (!lds_attr_set) {
-        if (hipFuncSetAttribute((const void*)route_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void*)route_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess)
             return PS_EHIP;
         lds_attr_set = true;
     }
-    if (window >= 1 && (window + tpi - 1) / tpi <= kRegSlots)
-        hipLaunchKernelGGL(route_reg_kernel, dim3(1), dim3(kRouteThreads), 0, s, prompt_tokens, pred_tokens, n_req, n_inst,
-                           window, tpi, window_tokens, capacity, queued_p, current_d, t_mem_pct, beta, assigned,
-                           score100, status);
-    else
-        hipLaunchKernelGGL(route_kernel, dim3(1), dim3(kRouteThreads), lds, s, prompt_tokens, pred_tokens, n_req, n_inst,
-                           window, tpi, window_tokens, capacity, queued_p, current_d, t_mem_pct, beta, assigned, score100,
-                           status);
+#define PS_ROUTE(SMALL)                                                                                             \
+    hipLaunchKernelGGL(route_kernel<SMALL>, dim3(1), dim3(kRouteThreads), p.lds_bytes, s, prompt_tokens, pred_tokens, \
+                       n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens, capacity, queued_p,      \
+                       current_d, t_mem_pct, beta, assigned, score100, status)
+    if (p.block == 4) PS_ROUTE(true);
+    else PS_ROUTE(false);
+#undef PS_ROUTE
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }

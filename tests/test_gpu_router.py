@@ -76,3 +76,23 @@ def test_missing_predictions_and_limits():
     with pytest.raises(ps.PsError) as e:                    # windows that do not fit the LDS
         ps.ps_route(z32[:1], z32[:1], 256, 200, big, z32[:256], z64[:256], z64[:256], z32[:1], z64[:1])
     assert e.value.code == -6
+
+
+@pytest.mark.parametrize("K,l,n", [(64, 128, 150), (65, 129, 150), (2, 4, 200), (3, 5, 200), (63, 1, 130), (128, 127, 64),
+                                   (1024, 29, 70),        # fills the LDS: one block per window
+                                   (256, 134, 66),        # larger blocks than the smallest, to fit
+                                   (7, 1000, 40), (1, 8000, 12), (2, 17000, 5)])
+def test_block_edges_and_full_lds(K, l, n):
+    """The kernel keeps maxima per block of a window: predictions on, beside and beyond the block boundaries, maps of one
+    wavefront and of several, and the largest maps the call accepts.  Integers: everything must match."""
+    print(f"route blocks K={K} l={l} n={n}", flush=True)
+    rng = np.random.default_rng(K * 7919 + l)
+    P, D, win, cap, qp, cd = random_case(rng, K, l, n, True)
+    edges = np.array([0, 1, 3, 4, 5, 8, l // 2, max(l - 4, 0), max(l - 1, 0), l, l + 1, 4096])
+    D = np.where(rng.random(n) < 0.7, edges[rng.integers(0, len(edges), n)], D)
+    win[0, :] = -5                                              # (values below zero keep their place in the maxima)
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd)
+    assert flags == 0
+    assert np.array_equal(a, ra) and np.array_equal(s, rs)
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
