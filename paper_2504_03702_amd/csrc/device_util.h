@@ -85,3 +85,43 @@ __device__ __forceinline__ void report_fault(ps_status* st, int flag, int64_t in
     atomicOr(&st->flags, flag);
     atomicMax((long long*)&st->first_bad, (long long)(((int64_t)1 << 62) - index));
 }
+
+// ---- LayerNorm pieces that several kernels must compute alike, to the last bit ----------------------------
+// (mean, 1 / std) from a row's sum and sum of squares (biased variance).
+__device__ __forceinline__ float2 ln_moments(float sum, float sq, float inv_n, float eps) {
+    const float mean = sum * inv_n;
+    const float var = fmaxf(fmaf(sq, inv_n, -(mean * mean)), 0.f);
+    return make_float2(mean, 1.0f / sqrtf(var + eps));
+}
+
+// LayerNorm of the stream value hi + lo.
+__device__ __forceinline__ float ln_apply(float hi, float lo, float2 st, float gamma, float beta) {
+    return fmaf(((hi + lo) - st.x) * st.y, gamma, beta);
+}
+
+// (mean, 1 / std) of one row of the sums hi + lo by one wavefront, in two passes.
+__device__ __forceinline__ float2 row_moments(const uint16_t* yh, const uint16_t* yl, int H, float eps, int lane) {
+    float sum = 0.f;
+#pragma unroll 4
+    for (int i = lane; i < H; i += 64) sum += bf16_to_f32(yh[i]) + bf16_to_f32(yl[i]);
+    const float mean = wave_sum(sum) / (float)H;
+    float sq = 0.f;
+#pragma unroll 4
+    for (int i = lane; i < H; i += 64) {
+        const float d = (bf16_to_f32(yh[i]) + bf16_to_f32(yl[i])) - mean;
+        sq = fmaf(d, d, sq);
+    }
+    return make_float2(mean, 1.0f / sqrtf(wave_sum(sq) / (float)H + eps));
+}
+
+// Sum over 8 consecutive lanes (lanes 8 r .. 8 r + 7) with DPP moves; every one of them gets the total.
+// The order of the additions is fixed, so the result does not change from run to run.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row8_sum(float v) {
+    v = dpp_add<0xB1>(v);      // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);      // quad_perm [2, 3, 0, 1]
+    return dpp_add<0x141>(v);  // row_half_mirror: lane i of each group of 8 takes lane 7 - i
+}

@@ -28,9 +28,7 @@ __global__ __launch_bounds__(256) void ln_stats_kernel(const float2* __restrict_
         sm += __shfl_xor(sm, o, 16);
         sq += __shfl_xor(sq, o, 16);
     }
-    const float mean = sm * inv_n;
-    const float var = fmaxf(sq * inv_n - mean * mean, 0.f);
-    if (p == 0) stats[row] = make_float2(mean, 1.0f / sqrtf(var + eps));
+    if (p == 0) stats[row] = ln_moments(sm, sq, inv_n, eps);
 }
 
 }  // namespace
@@ -40,6 +38,11 @@ void launch_ln_stats(const float2* pstats, float2* stats, float eps, int hidden,
     hipLaunchKernelGGL(ln_stats_kernel, dim3((unsigned)(max_rows / 16)), dim3(256), 0, s, pstats, stats, hidden / 64,
                        1.0f / (float)hidden, eps, total_rows);
 }
+
+// Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
+// Six-layer encoder, hidden 768: 253 rows 805 -> 435 us, 907 rows 869 -> 518 us; at 3200 rows the large tiles' better
+// reuse wins (993 us against 1036), so the line lies below that.
+#define PS_FUSED_ROWS 2560
 
 void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hipStream_t s) {
     const ps_model_info& f = m->info;
@@ -54,15 +57,24 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     // the stream entering layer 0 is the embedding LayerNorm of the sums the embed kernel left in (x, la)
     const float *sg = m->lne_g, *sbeta = m->lne_b;
 #define PS_TIMED(FAM, CALL) do { ProfScope p_(m, FAM, s); CALL; } while (0)
-    // the per-request side maps: the tiled kernel, or for calls of a few requests the streaming one
-    const bool skinny = n_req <= PS_SKINNY_ROWS;
-    // (K = the map's contraction length; the hi | lo forms hold 2 K columns per row of A and of the repeated W)
+    // the per-request side maps of calls of more than 16 requests (k_cols: columns per row of A and W; the hi | lo
+    // forms hold twice the map's contraction length)
     auto side_gemm = [&](GemmEpilogue epi, const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C,
-                         int N, int K) {
-        const int k_cols = epi == EPI_Q_MAPPED ? K : 2 * K;
-        if (skinny) launch_skinny_gemm_bf16(epi, A, (const bf16_t*)W, bias, r, C, N, K, H, n_req_dev, s);
-        else launch_gemm_bf16(epi, A, (const bf16_t*)W, bias, r, C, nullptr, ws.cls_rows, N, k_cols, H, n_req_dev, nullptr, s);
+                         int N, int k_cols) {
+        SmallGemm p = {};
+        p.A = A; p.W = (const bf16_t*)W; p.bias = bias; p.res = r; p.C = C;
+        p.max_rows = ws.cls_rows; p.N = N; p.K = k_cols; p.hidden = H; p.rows = n_req_dev;
+        launch_small_gemm_bf16(epi, p, nullptr, s);
     };
+    const bool skinny = n_req <= PS_SKINNY_ROWS;
+    auto skinny_args = [&](const void* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K, int ldw,
+                           int stats_from, float2* stats_out) {
+        return SkinnyArgs{(const bf16_t*)A, (const bf16_t*)W, bias, r, C, N, K, ldw, H, n_req,
+                          stats_from, ws.ps, stats_out, 1.0f / (float)H, m->ln_eps};
+    };
+    // Calls of a few requests over few rows: a layer is five launches, each map's launch doing the per-request map
+    // beside it and making the row statistics it needs from the previous launch's pieces.
+    const bool fused = skinny && ws.max_rows <= PS_FUSED_ROWS;
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
         // After the last layer only the first row of every request goes on (to the head), and within
@@ -79,47 +91,95 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
         // operands of the maps with a folded LayerNorm: row statistics and column sums
         const ResidualSrc fold_qkv = {nullptr, nullptr, ws.sa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.c_qkv};
         const ResidualSrc fold_1 = {nullptr, nullptr, ws.sb, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.c_1};
+        const float2* stats_in = l > 0 ? ws.ps : nullptr;   // (fused) pieces of the sums entering the layer; the embedding leaves statistics
+        auto small = [&](const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K,
+                         const int32_t* n_rows, const float2* pieces, float2* stats_out) {
+            return SmallGemm{A, (const bf16_t*)W, bias, r, C, vt, ws.max_rows, N, K, H, n_rows, rows, pieces, stats_out,
+                             1.0f / (float)H, m->ln_eps, n_req, ws.row_start, ws.seq_len};
+        };
         if (!last) {
-            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_QKV, x, (const bf16_t*)w.w_qkv, w.b_qkv, fold_qkv, qk, vt,
-                                                   ws.max_rows, 3 * H, H, H, qkv_rows, clk, s));
+            if (fused)
+                PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_QKV, small(x, w.w_qkv, w.b_qkv, fold_qkv, qk, 3 * H, H, qkv_rows,
+                                                                            stats_in, ws.sa), nullptr, s));
+            else
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_QKV, x, (const bf16_t*)w.w_qkv, w.b_qkv, fold_qkv, qk, vt,
+                                                       ws.max_rows, 3 * H, H, H, qkv_rows, clk, s));
         } else {
             // keys and values of all rows; queries of the requests' first rows only, by a side GEMM on
             // those rows gathered into the (not yet used) first-row buffer
+            const ResidualSrc first_rows = {x, ws.la, ws.sa, nullptr, nullptr, ws.row_start, ws.seq_len, nullptr, nullptr, w.c_qkv};
             const ResidualSrc fold_kv = {nullptr, nullptr, ws.sa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.c_qkv + H};
-            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_KV, x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv,
-                                                   qk, vt, ws.max_rows, 2 * H, H, H, qkv_rows, clk, s));
-            const ResidualSrc first_rows = {nullptr, nullptr, ws.sa, nullptr, nullptr, ws.row_start, ws.seq_len, nullptr, nullptr, w.c_qkv};
-            PS_TIMED(PS_FAM_REFINE, launch_cls_rows(m, n_req, ws, x, (bf16_t*)ws.cls_a, s));
-            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_Q_MAPPED, (const bf16_t*)ws.cls_a, w.w_qkv, w.b_qkv, first_rows, qk, H, H));
+            if (fused) {
+                const SkinnyArgs q = skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H, H, stats_in ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN, nullptr);
+                PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_KV, small(x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv, qk,
+                                                                           2 * H, H, qkv_rows, stats_in, ws.sa), &q, s));
+            } else {
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_KV, x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv,
+                                                       qk, vt, ws.max_rows, 2 * H, H, H, qkv_rows, clk, s));
+                if (skinny) {
+                    PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_Q_MAPPED, skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H, H,
+                                                                                              SKINNY_STATS_GIVEN, nullptr), s));
+                } else {
+                    PS_TIMED(PS_FAM_REFINE, launch_cls_rows(m, n_req, ws, x, (bf16_t*)ws.cls_a, s));
+                    PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_Q_MAPPED, (const bf16_t*)ws.cls_a, w.w_qkv, w.b_qkv, first_rows, qk, H, H));
+                }
+            }
         }
         PS_TIMED(PS_FAM_ATTENTION, launch_attention_bf16(m, n_req, ws, last, s));
-        if (!last)
-            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
-                                                   nullptr, ws.max_rows, H, H, H, rows, clk, s));
-        // output projection again for each request's first row from the hi | lo pairs the attention
-        // kernel left in cls_a (see the feed-forward refinement below)
+        // Output projection of all rows, and again for each request's first row from the hi | lo pairs the attention
+        // kernel left in cls_a.  The feed-forward block again for those rows, the ones the head reads, with its input and
+        // its GELU output carried as two bf16 values per element (contraction length doubled, weights repeated): bf16
+        // rounding of these two tensors is the dominant error of the prediction and acts row by row, so the pass
+        // removes it where it matters at < 1 % of the block's cost.
         const ResidualSrc in_cls = {x, ws.la, ws.sa, sg, sbeta, ws.row_start, ws.seq_len, x1, ps, nullptr};
-        PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H));
-        if (!last) {
-            PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
-            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
-                                                   ws.max_rows, F, H, H, rows, clk, s));
-            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
-                                                   nullptr, ws.max_rows, H, F, H, rows, clk, s));
+        const ResidualSrc ffn_cls = {x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, ws.row_start, ws.seq_len, nullptr, nullptr, nullptr};
+        if (skinny) {
+            const SkinnyArgs so = skinny_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H, 2 * H, 0, nullptr);
+            const SkinnyArgs s1 = skinny_args(nullptr, w.w_1d, w.b_1, ffn_cls, ws.cls_g, F, H, 2 * H,
+                                              last ? SKINNY_STATS_ROWS : fused ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN,
+                                              last ? ws.sb : nullptr);
+            const SkinnyArgs s2 = skinny_args(ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F, 2 * F, 0, nullptr);
+            if (fused && !last) {
+                PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(att, w.w_o, w.b_o, in, ws.lb, H, H, rows, nullptr, nullptr), &so, s));
+                PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_GELU, small(x1, w.w_1, w.d_1, fold_1, g, F, H, rows, ws.ps, ws.sb), &s1, s));
+                PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(g, w.w_2, w.b_2, mid, ws.la, H, F, rows, nullptr, nullptr), &s2, s));
+            } else {
+                if (!last)
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
+                                                           nullptr, ws.max_rows, H, H, H, rows, clk, s));
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
+                if (!last) {
+                    PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
+                                                           ws.max_rows, F, H, H, rows, clk, s));
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
+                                                           nullptr, ws.max_rows, H, F, H, rows, clk, s));
+                }
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
+            }
         } else {
-            PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x1, ws.lb, ws.sb, s));
+            if (!last)
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
+                                                       nullptr, ws.max_rows, H, H, H, rows, clk, s));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, 2 * H));
+            if (!last) {
+                PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
+                                                       ws.max_rows, F, H, H, rows, clk, s));
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
+                                                       nullptr, ws.max_rows, H, F, H, rows, clk, s));
+            } else {
+                PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x1, ws.lb, ws.sb, s));
+            }
+            PS_TIMED(PS_FAM_REFINE, launch_cls_gather(m, n_req, ws, x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, s));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, 2 * H));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, 2 * F));
         }
-        // The feed-forward block again for each request's first row, the one the head reads, with its
-        // input and its GELU output carried as two bf16 values per element (contraction length doubled,
-        // weights repeated): bf16 rounding of these two tensors is the dominant error of the prediction
-        // and acts row by row, so the pass removes it where it matters at < 1 % of the block's cost.
-        PS_TIMED(PS_FAM_REFINE, launch_cls_gather(m, n_req, ws, x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, s));
-        PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
-        PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F));
-        if (!last)
-            PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sa, m->ln_eps, H, ws.max_rows, rows, s));
-        else
+        if (last)
             PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x, ws.la, ws.sa, s));   // what the head reads
+        else if (!fused)
+            PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sa, m->ln_eps, H, ws.max_rows, rows, s));
         sg = w.ln2_g;
         sbeta = w.ln2_b;
     }

@@ -39,18 +39,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 #define GLOBAL_AS __attribute__((address_space(1)))
 #define LDS_AS __attribute__((address_space(3)))
 
-// Sum over 8 consecutive lanes (lanes 8 r .. 8 r + 7) with DPP moves; every one of them gets the total.
-// The order of the additions is fixed, so the result does not change from run to run.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row8_sum(float v) {
-    v = dpp_add<0xB1>(v);      // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);      // quad_perm [2, 3, 0, 1]
-    return dpp_add<0x141>(v);  // row_half_mirror: lane i of each group of 8 takes lane 7 - i
-}
-
 template <int BM, int BN, int WM, int WN>
 struct Tile {
     static constexpr int NW = WM * WN;               // wavefronts per workgroup
@@ -343,7 +331,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
                 for (int t = 0; t < 4; ++t) stg[(4 * fhalf + t) * SW + 32 * j + frow] = acc[i][j][4 * e4 + t];
         };
 
-        if (EPI == EPI_BIAS_RESIDUAL || EPI == EPI_RESIDUAL_MAPPED) {
+        if (EPI == EPI_BIAS_RESIDUAL) {
             // New sums of the residual stream: v = acc + bias + LayerNorm(y_prev) recomputed from the
             // previous sums (kept as two bf16, hi + lo) and the row statistics, so the stream is never
             // rounded to 8 bits.  v goes out as hi + lo again: hi is what the next map reads.  A lane
@@ -400,46 +388,30 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
                     if (res.pstats && cg == 0) res.pstats[row * pieces + piece] = make_float2(sm, sq);
                 }
             };
-            if (EPI == EPI_BIAS_RESIDUAL) {
-                // The previous sums and statistics of strip s + D are requested before strip s is worked
-                // on, so the strips do not each wait out a trip to memory.  Strip s covers rows
-                // 8 s .. 8 s + 7 of the wavefront's tile.
-                constexpr int D = 3;
-                const int64_t row0 = m_base + r_in;
-                const bf16_t* yh = res.y_hi + row0 * N + col;
-                const bf16_t* yl = res.y_lo + row0 * N + col;
-                const float2* sb = res.stats + row0;
-                uint4 ph[D + 1], pl[D + 1];
-                float2 st[D + 1];
-                auto fetch = [&](int s) {
-                    ph[s % (D + 1)] = *(const uint4*)(yh + (int64_t)(8 * s) * N);
-                    pl[s % (D + 1)] = *(const uint4*)(yl + (int64_t)(8 * s) * N);
-                    st[s % (D + 1)] = sb[8 * s];
-                };
+            // The previous sums and statistics of strip s + D are requested before strip s is worked
+            // on, so the strips do not each wait out a trip to memory.  Strip s covers rows
+            // 8 s .. 8 s + 7 of the wavefront's tile.
+            constexpr int D = 3;
+            const int64_t row0 = m_base + r_in;
+            const bf16_t* yh = res.y_hi + row0 * N + col;
+            const bf16_t* yl = res.y_lo + row0 * N + col;
+            const float2* sb = res.stats + row0;
+            uint4 ph[D + 1], pl[D + 1];
+            float2 st[D + 1];
+            auto fetch = [&](int s) {
+                ph[s % (D + 1)] = *(const uint4*)(yh + (int64_t)(8 * s) * N);
+                pl[s % (D + 1)] = *(const uint4*)(yl + (int64_t)(8 * s) * N);
+                st[s % (D + 1)] = sb[8 * s];
+            };
 #pragma unroll
-                for (int s = 0; s < D; ++s) fetch(s);
+            for (int s = 0; s < D; ++s) fetch(s);
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    if (s + D < NS) fetch(s + D);
-                    stage_strip(s / 4, s % 4);
-                    const int64_t row = row0 + 8 * s;
-                    finish_row(r_in, ph[s % (D + 1)], pl[s % (D + 1)], st[s % (D + 1)], row, row < rows);
-                }
-                continue;
+            for (int s = 0; s < NS; ++s) {
+                if (s + D < NS) fetch(s + D);
+                stage_strip(s / 4, s % 4);
+                const int64_t row = row0 + 8 * s;
+                finish_row(r_in, ph[s % (D + 1)], pl[s % (D + 1)], st[s % (D + 1)], row, row < rows);
             }
-            // rows mapped through the request table (a small side problem: no prefetch)
-#pragma unroll
-            for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    stage_strip(i, e4);
-                    int64_t row = m_base + 32 * i + 8 * e4 + r_in;
-                    // GEMM row = request; its stream row is the request's first row
-                    if (row >= rows || res.seq_len[row] <= 0) continue;
-                    row = res.row_map[row];
-                    finish_row(r_in, *(const uint4*)(res.y_hi + row * N + col), *(const uint4*)(res.y_lo + row * N + col),
-                               res.stats[row], row, true);
-                }
             continue;
         }
 
@@ -451,7 +423,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
             const float4 b0 = *(const float4*)(bias + col), b1 = *(const float4*)(bias + col + 4);
             // maps with a LayerNorm folded in: column sums, and the statistics of every row this lane
             // will touch, requested before the first strip
-            constexpr bool FOLD = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_Q_MAPPED || EPI == EPI_BIAS_GELU;
+            constexpr bool FOLD = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_BIAS_GELU;
             float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
             float2 rst[FOLD ? T::TM * 4 * NIT : 1];
             if (FOLD) {
@@ -461,13 +433,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
                 for (int s = 0; s < T::TM * 4; ++s)
 #pragma unroll
                     for (int it = 0; it < NIT; ++it) {
-                        int64_t row = m_base + 8 * s + r_in + RPI * it;
-                        if (EPI == EPI_Q_MAPPED) row = (row < rows && res.seq_len[row] > 0) ? res.row_map[row] : 0;
+                        const int64_t row = m_base + 8 * s + r_in + RPI * it;
                         rst[s * NIT + it] = res.stats[row];
                     }
             }
-            const int64_t ldc = (EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_Q_MAPPED) ? 2 * (int64_t)hidden
-                                : EPI == EPI_GELU_SPLIT ? 2 * (int64_t)N : (int64_t)N;
+            const int64_t ldc = (EPI == EPI_QKV || EPI == EPI_KV) ? 2 * (int64_t)hidden
+                                : (int64_t)N;
             const int c_col = col + (EPI == EPI_KV ? hidden : 0);   // key columns sit after the query columns
             bf16_t* C = (bf16_t*)Cv;
 #pragma unroll
@@ -478,12 +449,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
 #pragma unroll
                     for (int it = 0; it < NIT; ++it) {
                         const int r = r_in + RPI * it;
-                        int64_t row = m_base + 32 * i + 8 * e4 + r;
-                        if (EPI == EPI_Q_MAPPED) {
-                            // GEMM row = request; its queries belong to the request's first row
-                            if (row >= rows || res.seq_len[row] <= 0) continue;
-                            row = res.row_map[row];
-                        }
+                        const int64_t row = m_base + 32 * i + 8 * e4 + r;
                         const float4 lo = *(const float4*)(stg + r * SW + 8 * cg);
                         const float4 hi = *(const float4*)(stg + r * SW + 8 * cg + 4);
                         float v[8];
@@ -498,23 +464,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
                             v[0] = lo.x + b0.x; v[1] = lo.y + b0.y; v[2] = lo.z + b0.z; v[3] = lo.w + b0.w;
                             v[4] = hi.x + b1.x; v[5] = hi.y + b1.y; v[6] = hi.z + b1.z; v[7] = hi.w + b1.w;
                         }
-                        if (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_SPLIT) {
+                        if (EPI == EPI_BIAS_GELU) {
 #pragma unroll
                             for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
                         }
                         const uint4 o = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]),
                                                    cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
                         *(uint4*)(C + row * ldc + c_col) = o;
-                        if (EPI == EPI_GELU_SPLIT) {
-                            // second half of the row: what the first rounding lost, as bf16 again
-                            const uint32_t h[4] = {o.x, o.y, o.z, o.w};
-                            uint32_t l[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                l[t] = cvt_pk_bf16(v[2 * t] - __uint_as_float(h[t] << 16),
-                                                   v[2 * t + 1] - __uint_as_float(h[t] & 0xffff0000u));
-                            *(uint4*)(C + row * ldc + N + c_col) = make_uint4(l[0], l[1], l[2], l[3]);
-                        }
                     }
                 }
         }
@@ -545,10 +501,8 @@ void launch_cfg(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float*
         case EPI_BIAS_GELU: PS_LAUNCH(EPI_BIAS_GELU); break;
         case EPI_BIAS_RESIDUAL: PS_LAUNCH(EPI_BIAS_RESIDUAL); break;
         case EPI_QKV: PS_LAUNCH(EPI_QKV); break;
-        case EPI_GELU_SPLIT: PS_LAUNCH(EPI_GELU_SPLIT); break;
-        case EPI_RESIDUAL_MAPPED: PS_LAUNCH(EPI_RESIDUAL_MAPPED); break;
         case EPI_KV: PS_LAUNCH(EPI_KV); break;
-        case EPI_Q_MAPPED: PS_LAUNCH(EPI_Q_MAPPED); break;
+        default: break;                                  // the per-request forms are small_gemm.hip's and skinny_gemm.hip's
     }
 #undef PS_LAUNCH
 }
@@ -564,7 +518,7 @@ void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const 
     // micro-batch of a few requests) would leave most compute units idle: 128 x 128 tiles give four times as
     // many workgroups to spread them over.
     const int64_t big_tiles = (max_rows + 255) / 256 * (N / 256);
-    if (epi == EPI_RESIDUAL_MAPPED || epi == EPI_Q_MAPPED || big_tiles < 128)
+    if (big_tiles < 128)
         launch_cfg<128, 128, 2, 2>(epi, A, W, bias, residual, C, vt, max_rows, N, K, hidden, total_rows, clk, s);
     else
         launch_cfg<256, 256, 2, 4>(epi, A, W, bias, residual, C, vt, max_rows, N, K, hidden, total_rows, clk, s);

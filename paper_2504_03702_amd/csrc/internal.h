@@ -136,8 +136,42 @@ void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const 
 // The per-request forms (EPI_GELU_SPLIT, EPI_RESIDUAL_MAPPED, EPI_Q_MAPPED) for calls of at most PS_SKINNY_ROWS
 // requests: a stream over W with the contraction split among a workgroup's wavefronts.
 #define PS_SKINNY_ROWS 16
-void launch_skinny_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias, ResidualSrc residual,
-                             void* C, int N, int K, int hidden, const int32_t* n_rows, hipStream_t s);
+enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
+struct SkinnyArgs {
+    const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)
+    const float* bias;
+    ResidualSrc res;
+    void* C;
+    int N, K, ldw, hidden, n_req;
+    // EPI_GELU_SPLIT, EPI_Q_MAPPED: where the first rows' LayerNorm statistics come from: res.stats, the 64-column
+    // pieces in pstats_in, or two passes over the rows; stats_out (may be null) gets them
+    int stats_from;
+    const float2* pstats_in;
+    float2* stats_out;
+    float inv_n, eps;
+};
+void launch_skinny_gemm_bf16(GemmEpilogue epi, const SkinnyArgs& p, hipStream_t s);
+// The maps of calls with few activation rows (64 x 64 tiles, one workgroup each).  `side`, if not null, is the
+// per-request map of the same layer, done by further workgroups of the launch; rows of the residual stream that it
+// writes are left to it.  pstats_in, if not null: the statistics of the operand's rows are made from these pieces
+// and left in stats_out (res.stats otherwise).
+struct SmallGemm {
+    const bf16_t *A, *W;
+    const float* bias;
+    ResidualSrc res;
+    void* C;
+    bf16_t* vt;
+    int64_t max_rows;            // rows the buffers hold; also the row stride of vt
+    int N, K, hidden;
+    const int32_t* rows;         // rows to compute
+    const int32_t* live_rows;    // rows that belong to requests (the others take statistics of zero)
+    const float2* pstats_in;
+    float2* stats_out;
+    float inv_n, eps;
+    int n_side;                  // requests whose first rows the side map writes (0 without one)
+    const int32_t *row_start, *seq_len;
+};
+void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
 void launch_cls_gather(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* y_hi, const bf16_t* y_lo,
                        const float2* stats, const float* gamma, const float* beta, hipStream_t s);
 // out[r][0:hidden] = x[first row of request r] for every request (zeros for faulty ones and padding rows).

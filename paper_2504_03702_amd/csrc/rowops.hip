@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void cls_gather_kernel(const bf16_t* __restric
     const int64_t row = row_start[r];
     const float2 st = stats[row];
     for (int i = lane; i < H; i += 64) {
-        const float x = ((bf16_to_f32(y_hi[row * H + i]) + bf16_to_f32(y_lo[row * H + i])) - st.x) * st.y * gamma[i] + beta[i];
+        const float x = ln_apply(bf16_to_f32(y_hi[row * H + i]), bf16_to_f32(y_lo[row * H + i]), st, gamma[i], beta[i]);
         const bf16_t hi = f32_to_bf16(x);
         o[i] = hi;
         o[H + i] = f32_to_bf16(x - bf16_to_f32(hi));
@@ -378,17 +378,8 @@ __global__ __launch_bounds__(256) void cls_stats_kernel(const bf16_t* __restrict
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= n_req || seq_len[r] <= 0) return;
     const int64_t row = row_start[r];
-    const bf16_t *yh = y_hi + row * H, *yl = y_lo + row * H;
-    float sum = 0.f;
-    for (int i = lane; i < H; i += 64) sum += bf16_to_f32(yh[i]) + bf16_to_f32(yl[i]);
-    const float mean = wave_sum(sum) / (float)H;
-    float sq = 0.f;
-    for (int i = lane; i < H; i += 64) {
-        const float d = (bf16_to_f32(yh[i]) + bf16_to_f32(yl[i])) - mean;
-        sq = fmaf(d, d, sq);
-    }
-    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)H + eps);
-    if (lane == 0) stats[row] = make_float2(mean, rstd);
+    const float2 v = row_moments(y_hi + row * H, y_lo + row * H, H, eps, lane);
+    if (lane == 0) stats[row] = v;
 }
 
 // The bf16 input rows of each request's first token, one per request, for the side GEMM that computes
