@@ -7,9 +7,17 @@
 // The second step applies the model to the history extended by the first forecast: while that
 // forecast lies inside the history's range the normalisation is unchanged and the recurrence simply
 // goes on by one input; otherwise the k + 1 values are normalised afresh and the recurrence is run
-// again from the start.  One wavefront per service, lane j owning hidden unit j (hidden <= 64); h and
-// m are exchanged through the wavefront's LDS slots; fp32 arithmetic.  Matrices are stored input-major
-// ([in][out]: element (out j, in i) at i * H + j), so the lanes of a wavefront read consecutive words.
+// again from the start.
+//
+// The recurrence is a chain of k + 1 steps, each two products with H x H matrices (H <= 64) and two rounds of
+// elementwise functions; a wavefront per service that read its matrices anew at every step (L2, 82 KB a step and
+// model) took 33 us a step.  Here a workgroup is one service: four wavefronts per model, both models side by side.
+// Lane j owns hidden unit j; wavefront g keeps column j of gate g's matrix and a quarter of W_mh's rows in registers
+// (read once: the weights' bytes are what the call cannot do without), so a step is 64 + 16 multiply-adds, two
+// exchanges through LDS and two barriers (512 services of 64 units over 24 windows: 824 -> 89 us; one service 511 -> 53).
+// c and h are kept by all four wavefronts alike.  fp32 arithmetic, four
+// partial sums per product.  Matrices are stored input-major ([in][out]: element (out j, in i) at i * H + j), so the
+// lanes of a wavefront read consecutive words.
 // A model is packed as
 //   w_mx[H] W_mh[H][H] w_hx[H] W_hm[H][H] b_h[H] w_ix[H] W_im[H][H] b_i[H] w_ox[H] W_om[H][H] b_o[H]
 //   w_fx[H] W_fm[H][H] b_f[H] w_out[H] b_out
@@ -20,109 +28,115 @@ namespace {
 
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 
-__global__ __launch_bounds__(256) void forecast_kernel(const float* __restrict__ weights, int hidden,
+// HB: hidden rounded up to 32 or 64 (weights beyond `hidden` are zeros).
+template <int HB>
+__global__ __launch_bounds__(512) void forecast_kernel(const float* __restrict__ weights, int hidden,
                                                        const float* __restrict__ hist_p,
-                                                       const float* __restrict__ hist_d, int n_services, int k,
+                                                       const float* __restrict__ hist_d, int k,
                                                        const float* __restrict__ mu, float* __restrict__ out) {
-    __shared__ float s_h[4][64], s_m[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int s = blockIdx.x * 4 + wave;
-    const bool live = s < n_services;                       // whole wavefront; dead ones still meet the barriers
-    const bool unit = lane < hidden;
-    const int H = hidden;
+    constexpr int Q = HB / 4;                               // rows of W_mh per wavefront
+    __shared__ __align__(16) float s_v[8][64];              // a wavefront's own copy of h, then of m
+    __shared__ float s_a[2][4][64], s_g[2][4][64];          // partial products with W_mh; gate values
+    __shared__ float s_y[2][2];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kind = wave >> 2, gate = wave & 3;            // gates in storage order: hh, i, o, f
+    const int s = blockIdx.x, H = hidden;
+    const bool unit = lane < H;
     const size_t model_floats = (size_t)5 * H * H + 10 * H + 1;
-    float y[2][2] = {{0.f, 0.f}, {0.f, 0.f}};               // [kind][step]
-    for (int kind = 0; kind < 2; ++kind) {
-        const float* w = weights + (size_t)(2 * (live ? s : 0) + kind) * model_floats;
-        const float* w_mx = w;
-        const float* W_mh = w_mx + H;
-        const float* w_hx = W_mh + H * H;
-        const float* W_hm = w_hx + H;
-        const float* b_h = W_hm + H * H;
-        const float* w_ix = b_h + H;
-        const float* W_im = w_ix + H;
-        const float* b_i = W_im + H * H;
-        const float* w_ox = b_i + H;
-        const float* W_om = w_ox + H;
-        const float* b_o = W_om + H * H;
-        const float* w_fx = b_o + H;
-        const float* W_fm = w_fx + H;
-        const float* b_f = W_fm + H * H;
-        const float* w_out = b_f + H;
-        const float b_out = w_out[H];
-        const float* hist = (kind == 0 ? hist_p : hist_d) + (size_t)(live ? s : 0) * k;
-        // minimum and maximum of the history (every lane scans it: the values are wave-uniform)
-        float lo = hist[0], hi = hist[0];
-        for (int t = 1; t < k; ++t) {
-            lo = fminf(lo, hist[t]);
-            hi = fmaxf(hi, hist[t]);
-        }
-        float span = hi > lo ? hi - lo : 1.0f;
-        // pass 0: the k past windows, then (first forecast inside [lo, hi]) one more input.  pass 1, only if the
-        // first forecast left that range: the k + 1 values again under their own normalisation.
-        // The barriers below are met by all four wavefronts of the workgroup the same number of times whatever
-        // their passes: if one of them needs the second pass, the others run it on their data all the same and
-        // discard the result (needs_second false: y is not overwritten).
-        bool needs_second = false;
-        for (int pass = 0; pass < 2; ++pass) {
-            float h = 0.f, c = 0.f;
-            s_h[wave][lane] = 0.f;
+    const float* w = weights + (size_t)(2 * s + kind) * model_floats;
+    const float* W_mh = w + H;
+    const float* gates = W_mh + H * H;                      // per gate: input weights [H], matrix [H][H], bias [H]
+    const float* gw = gates + (size_t)gate * (H * H + 2 * H);
+    const float* w_out = gates + (size_t)4 * (H * H + 2 * H);
+    float wm[Q], wg[HB];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) wm[i] = unit && gate * Q + i < H ? W_mh[(gate * Q + i) * H + lane] : 0.f;
+#pragma unroll
+    for (int i = 0; i < HB; ++i) wg[i] = unit && i < H ? gw[H + i * H + lane] : 0.f;
+    const float w_mx = unit ? w[lane] : 0.f, w_x = unit ? gw[lane] : 0.f, b_x = unit ? gw[H + H * H + lane] : 0.f;
+    const float w_o = unit ? w_out[lane] : 0.f, b_out = w_out[H];
+    const float* hist = (kind == 0 ? hist_p : hist_d) + (size_t)s * k;
+    float lo = hist[min(lane, k - 1)], hi = lo;
+    for (int t = lane + 64; t < k; t += 64) {
+        lo = fminf(lo, hist[t]);
+        hi = fmaxf(hi, hist[t]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, o, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+    }
+    float span = hi > lo ? hi - lo : 1.0f;
+    float y0 = 0.f, y1 = 0.f;                               // this model's forecasts
+    // pass 0: the k past windows, then (first forecast inside [lo, hi]) one more input.  pass 1, only if the
+    // first forecast left that range: the k + 1 values again under their own normalisation.  Both models of the
+    // workgroup meet its barriers the same number of times: if one needs the second pass, the other runs it on
+    // its data all the same and discards the result.
+    bool needs_second = false;
+    for (int pass = 0; pass < 2; ++pass) {
+        float h = 0.f, c = 0.f;
+        float v = hist[0];
+        for (int t = 0; t <= k; ++t) {
+            const float v_next = hist[min(t + 1, k - 1)];   // requested a step ahead
+            const float x = ((t < k ? v : y0) - lo) / span;
+            v = v_next;
+            // m = (w_mx x) * (W_mh h): this wavefront's rows
+            s_v[wave][lane] = h;
+            __builtin_amdgcn_wave_barrier();
+            float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < Q; i += 4) {
+                const float4 hv = *(const float4*)&s_v[wave][gate * Q + i];
+                a[0] = fmaf(wm[i], hv.x, a[0]); a[1] = fmaf(wm[i + 1], hv.y, a[1]);
+                a[2] = fmaf(wm[i + 2], hv.z, a[2]); a[3] = fmaf(wm[i + 3], hv.w, a[3]);
+            }
+            s_a[kind][gate][lane] = (a[0] + a[1]) + (a[2] + a[3]);
             __syncthreads();
-            for (int t = 0; t <= k; ++t) {
-                const float v = t < k ? hist[t] : y[kind][0];
-                const float x = (v - lo) / span;
-                float a = 0.f;
-                if (unit) {
-#pragma unroll 16
-                    for (int j = 0; j < H; ++j) a = fmaf(W_mh[j * H + lane], s_h[wave][j], a);
-                }
-                s_m[wave][lane] = unit ? (w_mx[lane] * x) * a : 0.f;
-                __syncthreads();
-                if (unit) {
-                    float hh = fmaf(w_hx[lane], x, b_h[lane]), gi = fmaf(w_ix[lane], x, b_i[lane]);
-                    float go = fmaf(w_ox[lane], x, b_o[lane]), gf = fmaf(w_fx[lane], x, b_f[lane]);
-#pragma unroll 8
-                    for (int j = 0; j < H; ++j) {
-                        const float mj = s_m[wave][j];
-                        hh = fmaf(W_hm[j * H + lane], mj, hh);
-                        gi = fmaf(W_im[j * H + lane], mj, gi);
-                        go = fmaf(W_om[j * H + lane], mj, go);
-                        gf = fmaf(W_fm[j * H + lane], mj, gf);
+            const float am = (s_a[kind][0][lane] + s_a[kind][1][lane]) + (s_a[kind][2][lane] + s_a[kind][3][lane]);
+            s_v[wave][lane] = unit ? (w_mx * x) * am : 0.f;
+            __builtin_amdgcn_wave_barrier();
+            float z[4] = {fmaf(w_x, x, b_x), 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < HB; i += 4) {
+                const float4 mv = *(const float4*)&s_v[wave][i];
+                z[0] = fmaf(wg[i], mv.x, z[0]); z[1] = fmaf(wg[i + 1], mv.y, z[1]);
+                z[2] = fmaf(wg[i + 2], mv.z, z[2]); z[3] = fmaf(wg[i + 3], mv.w, z[3]);
+            }
+            const float zs = (z[0] + z[1]) + (z[2] + z[3]);
+            s_g[kind][gate][lane] = gate == 0 ? tanhf(zs) : sigmoid_f(zs);
+            __syncthreads();
+            c = s_g[kind][3][lane] * c + s_g[kind][1][lane] * s_g[kind][0][lane];
+            h = unit ? tanhf(c) * s_g[kind][2][lane] : 0.f;
+            if (t >= k - 1) {                               // after the k-th input and after the extension
+                const float dot = wave_sum(w_o * h);
+                const float f = fmaxf(0.f, fmaf(span, dot + b_out, lo));
+                if (pass == 0) {
+                    if (t == k - 1) {
+                        y0 = f;
+                        needs_second = f < lo || f > hi;
+                    } else {
+                        y1 = f;
                     }
-                    c = sigmoid_f(gf) * c + sigmoid_f(gi) * tanhf(hh);
-                    h = tanhf(c) * sigmoid_f(go);
-                }
-                s_h[wave][lane] = unit ? h : 0.f;
-                __syncthreads();
-                if (t >= k - 1) {                           // after the k-th input and after the extension
-                    const float dot = wave_sum(unit ? w_out[lane] * h : 0.f);
-                    const float f = fmaxf(0.f, fmaf(span, dot + b_out, lo));
-                    if (pass == 0) {
-                        y[kind][t - (k - 1)] = f;
-                        if (t == k - 1) {
-                            needs_second = f < lo || f > hi;
-                        }
-                    } else if (needs_second && t == k) {
-                        y[kind][1] = f;
-                    }
+                } else if (needs_second && t == k) {
+                    y1 = f;
                 }
             }
-            // no wavefront of this workgroup needs the second pass (decided by all its threads together, so
-            // every one of them leaves or stays)
-            if (pass == 0 && !__syncthreads_or((int)needs_second)) break;
-            // normalisation of the extended history for the second pass
-            const float f1 = y[kind][0];
-            if (needs_second) {
-                lo = fminf(lo, f1);
-                hi = fmaxf(hi, f1);
-                span = hi > lo ? hi - lo : 1.0f;
-            }
+        }
+        // neither model needs the second pass (decided by all threads together, so every one leaves or stays)
+        if (pass == 0 && !__syncthreads_or((int)needs_second)) break;
+        // normalisation of the extended history for the second pass
+        if (needs_second) {
+            lo = fminf(lo, y0);
+            hi = fmaxf(hi, y0);
+            span = hi > lo ? hi - lo : 1.0f;
         }
     }
-    if (live && lane == 0) {
-        const float p2 = y[0][1], d2 = y[1][1];
+    if (gate == 0 && lane == 0) { s_y[kind][0] = y0; s_y[kind][1] = y1; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float p2 = s_y[0][1], d2 = s_y[1][1];
         float* o = out + (size_t)s * 5;
-        o[0] = y[0][0]; o[1] = y[1][0]; o[2] = p2; o[3] = d2;
+        o[0] = s_y[0][0]; o[1] = s_y[1][0]; o[2] = p2; o[3] = d2;
         o[4] = fmaxf(fmaxf(p2 / mu[3 * s], d2 / mu[3 * s + 1]), (p2 + d2) / mu[3 * s + 2]);
     }
 }
@@ -135,7 +149,16 @@ extern "C" int ps_forecast(const float* weights, int32_t hidden, const float* hi
     if (hidden < 1 || hidden > 64) return PS_EUNSUPPORTED;
     if (n_services == 0) return PS_OK;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(forecast_kernel, dim3((unsigned)((n_services + 3) / 4)), dim3(256), 0, (hipStream_t)hip_stream,
-                       weights, hidden, hist_p, hist_d, n_services, k, mu, out);
+    const size_t model_floats = (size_t)5 * hidden * hidden + 10 * hidden + 1;
+    const int32_t most = 1 << 22;                            // services per launch (a grid holds fewer than 2^32 threads)
+    for (int32_t s0 = 0, n; s0 < n_services; s0 += n) {
+        n = n_services - s0 < most ? n_services - s0 : most;
+        const dim3 grid((unsigned)n), block(512);
+        const float *w = weights + (size_t)2 * s0 * model_floats, *hp = hist_p + (size_t)s0 * k, *hd = hist_d + (size_t)s0 * k;
+        if (hidden <= 32)
+            hipLaunchKernelGGL(forecast_kernel<32>, grid, block, 0, (hipStream_t)hip_stream, w, hidden, hp, hd, k, mu + (size_t)3 * s0, out + (size_t)5 * s0);
+        else
+            hipLaunchKernelGGL(forecast_kernel<64>, grid, block, 0, (hipStream_t)hip_stream, w, hidden, hp, hd, k, mu + (size_t)3 * s0, out + (size_t)5 * s0);
+    }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }

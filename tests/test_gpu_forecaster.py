@@ -49,3 +49,18 @@ def test_argument_checks():
         ps._check(load.ps_forecast(z.data_ptr(), 65, z.data_ptr(), z.data_ptr(), 1, 1, z.data_ptr(), z.data_ptr(), None),
                   "ps_forecast")
     assert e.value.code == -6
+
+
+@pytest.mark.parametrize("S,H,k", [(2, 2, 70), (4, 31, 5), (9, 32, 1), (3, 33, 65), (2, 63, 48), (600, 64, 3)])
+def test_register_tile_edges(S, H, k):
+    """Hidden sizes around the register tiles (32, 64; a wavefront holds a quarter of W_mh's rows), histories shorter
+    and longer than a wavefront, more services than the chip holds at once."""
+    x = wl.make_forecaster_inputs(seed=S + H, n_services=S, hidden=H, k=k)
+    got = run_forecast(x)
+    ref = of.forecast_services([x.model(s, 0) for s in range(S)], [x.model(s, 1) for s in range(S)],
+                               x.hist_p.astype(np.float64), x.hist_d.astype(np.float64),
+                               x.mu[:, 0].astype(np.float64), x.mu[:, 1].astype(np.float64), x.mu[:, 2].astype(np.float64))
+    scale = np.maximum(np.abs(ref), np.sqrt(np.mean(ref ** 2, axis=1, keepdims=True)))
+    err = np.abs(got - ref) / scale
+    print(f"forecast S={S} H={H} k={k} max rel err {err.max():.2e}", flush=True)
+    assert err.max() < TOL
