@@ -44,18 +44,25 @@ __global__ __launch_bounds__(256) void scaler_rows_kernel(const int32_t* __restr
     }
 }
 
-// one wavefront for the totals; the sum of the peak fractions is taken in instance order in fp64
-__global__ __launch_bounds__(64) void scaler_summary_kernel(const int32_t* __restrict__ capacity,
-                                                            const int32_t* __restrict__ peak_tokens,
-                                                            const int32_t* __restrict__ overloaded, int n_inst,
-                                                            int window, int idle_pct, int32_t* __restrict__ summary,
-                                                            double* __restrict__ scale_down) {
-    const int lane = threadIdx.x;
+// Totals by one wavefront, or by the first wavefront of the single-launch form.  The sum of the peak fractions is taken
+// in instance order in fp64: the quotients of 64 instances at a time are made by the lanes and added one by one from
+// their registers (a loop over memory with a division per instance took 27 us for 256 instances).
+__device__ __forceinline__ void scaler_totals(const int32_t* capacity, const int32_t* peak_tokens, const int32_t* overloaded,
+                                              int n_inst, int window, int idle_pct, int lane, int32_t* summary, double* scale_down) {
     int n_over = 0, idle = 1;
-    for (int k = lane; k < n_inst; k += 64) {
-        const long long M = capacity[k];
-        n_over += overloaded[k];
-        if (M < 1 || window < 1 || !((long long)peak_tokens[k] * 100 < (long long)idle_pct * M)) idle = 0;
+    double total = 0.0;
+    for (int k0 = 0; k0 < n_inst; k0 += 64) {
+        const int k = k0 + lane;
+        double q = 0.0;                                    // (adding 0 for instances left out leaves the sum as it is)
+        if (k < n_inst) {
+            const int M = capacity[k], pk = peak_tokens[k];
+            n_over += overloaded[k];
+            if (M < 1 || window < 1 || !((long long)pk * 100 < (long long)idle_pct * M)) idle = 0;
+            if (M >= 1 && window >= 1) q = (double)pk / (double)M;
+        }
+        const int lo = __double2loint(q), hi = __double2hiint(q);
+#pragma unroll
+        for (int l = 0; l < 64; ++l) total += __hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l));
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -63,14 +70,81 @@ __global__ __launch_bounds__(64) void scaler_summary_kernel(const int32_t* __res
         idle &= __shfl_xor(idle, o, 64);
     }
     if (lane == 0) {
-        double total = 0.0;
-        if (window >= 1)
-            for (int k = 0; k < n_inst; ++k)
-                if (capacity[k] >= 1) total += (double)peak_tokens[k] / (double)capacity[k];
         summary[0] = n_over;
         summary[1] = idle;
         scale_down[0] = (double)n_inst - total / ((double)idle_pct / 100.0);
     }
+}
+
+__global__ __launch_bounds__(64) void scaler_summary_kernel(const int32_t* __restrict__ capacity,
+                                                            const int32_t* __restrict__ peak_tokens,
+                                                            const int32_t* __restrict__ overloaded, int n_inst,
+                                                            int window, int idle_pct, int32_t* __restrict__ summary,
+                                                            double* __restrict__ scale_down) {
+    scaler_totals(capacity, peak_tokens, overloaded, n_inst, window, idle_pct, threadIdx.x, summary, scale_down);
+}
+
+// Both parts in one launch by one workgroup, 16 lanes per instance and eight slots of a lane requested at a time: for
+// clusters whose windows one compute unit reads in a few microseconds, the second launch costs more than it saves.
+constexpr int kOneMostInst = 512;
+constexpr int kOneMostSlots = 65536;                       // n_inst * window
+__global__ __launch_bounds__(1024) void scaler_one_kernel(const int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
+                                                          int n_inst, int map_len, int w, int over_pct, int share_pct, int idle_pct,
+                                                          int32_t* __restrict__ over_count, int32_t* __restrict__ peak_tokens,
+                                                          int32_t* __restrict__ overloaded, int32_t* __restrict__ summary,
+                                                          double* __restrict__ scale_down) {
+    __shared__ int32_t s_cap[kOneMostInst], s_peak[kOneMostInst], s_over[kOneMostInst];
+    const int l = threadIdx.x & 15;
+    constexpr int UK = 4;                                  // instances of a group of 16 lanes whose slots are requested together
+    for (int k0 = threadIdx.x >> 4; k0 < n_inst; k0 += 64 * UK) {
+        int M[UK], cnt[UK], pk[UK];
+#pragma unroll
+        for (int i = 0; i < UK; ++i) {
+            M[i] = capacity[min(k0 + 64 * i, n_inst - 1)];
+            cnt[i] = 0;
+            pk[i] = (int)0x80000000;
+        }
+        for (int t0 = l; t0 < w; t0 += 128) {
+            int v[UK][8];
+#pragma unroll
+            for (int i = 0; i < UK; ++i) {
+                const int32_t* row = kv_tokens + (int64_t)min(k0 + 64 * i, n_inst - 1) * map_len;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[i][u] = row[min(t0 + 16 * u, w - 1)];
+            }
+#pragma unroll
+            for (int i = 0; i < UK; ++i)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (t0 + 16 * u < w) {
+                        cnt[i] += (long long)v[i][u] * 100 > (long long)over_pct * M[i] ? 1 : 0;
+                        pk[i] = max(pk[i], v[i][u]);
+                    }
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < UK; ++i) {
+            const int k = k0 + 64 * i;
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) {
+                cnt[i] += __shfl_xor(cnt[i], o, 16);
+                pk[i] = max(pk[i], __shfl_xor(pk[i], o, 16));
+            }
+            if (M[i] < 1) { cnt[i] = 0; pk[i] = 0; }
+            if (w < 1) pk[i] = 0;
+            if (l == 0 && k < n_inst) {
+                const int over = (long long)cnt[i] * 100 > (long long)share_pct * w ? 1 : 0;
+                over_count[k] = cnt[i];
+                peak_tokens[k] = pk[i];
+                overloaded[k] = over;
+                s_cap[k] = M[i];
+                s_peak[k] = pk[i];
+                s_over[k] = over;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) scaler_totals(s_cap, s_peak, s_over, n_inst, w, idle_pct, threadIdx.x, summary, scale_down);
 }
 
 }  // namespace
@@ -83,6 +157,12 @@ extern "C" int ps_scaler_scan(const int32_t* kv_tokens, const int32_t* capacity,
     if (n_inst < 1 || map_len < 1 || window < 0 || over_pct < 0 || share_pct < 0 || idle_pct < 1) return PS_EINVAL;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
+    const int w = min(window, map_len);
+    if (n_inst <= kOneMostInst && (int64_t)n_inst * w <= kOneMostSlots) {
+        hipLaunchKernelGGL(scaler_one_kernel, dim3(1), dim3(1024), 0, s, kv_tokens, capacity, n_inst, map_len, w, over_pct,
+                           share_pct, idle_pct, over_count, peak_tokens, overloaded, summary, scale_down);
+        return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
+    }
     hipLaunchKernelGGL(scaler_rows_kernel, dim3((unsigned)((n_inst + 3) / 4)), dim3(256), 0, s, kv_tokens, capacity,
                        n_inst, map_len, window, over_pct, share_pct, over_count, peak_tokens, overloaded);
     hipLaunchKernelGGL(scaler_summary_kernel, dim3(1), dim3(64), 0, s, capacity, peak_tokens, overloaded, n_inst,

@@ -234,3 +234,22 @@ def test_binned_route_on_unaligned_arrays():
     assert ps.ps_status_read(st)[0] == 0
     rkv, rovf, _, _ = ol.lookahead_update(*cols, K, map_len)
     assert np.array_equal(kv.cpu().numpy().reshape(K, map_len), rkv) and np.array_equal(ovf.cpu().numpy(), rovf)
+
+
+@pytest.mark.parametrize("K,L,window", [(1, 1, 1), (64, 300, 128), (65, 300, 129), (512, 140, 127), (512, 129, 129),
+                                        (513, 200, 16), (3, 50, 0), (130, 90, 400)])
+def test_scaler_sizes_around_the_single_launch(K, L, window):
+    """Instance counts around the totals' groups of 64 and the single launch's limits (512 instances, 65536 slots),
+    windows around a lane's batch of slots; instances without capacity and negative maps among them."""
+    from oracle import scaler as osc
+    print(f"scaler K={K} L={L} window={window}", flush=True)
+    rng = np.random.default_rng(K + window)
+    cap = rng.integers(1, 2000, K).astype(np.int32)
+    kv = (rng.uniform(-0.1, 1.2, (K, L)) * cap[:, None]).astype(np.int32)
+    cap[:: 7] -= cap[:: 7] if K > 7 else 0
+    got = run_scaler(kv, cap, window)
+    ref = osc.scaler_scan(kv, cap, window)
+    for g, r in zip(got[:5], ref[:5]):
+        assert np.array_equal(g, r)
+    # the same fp64 operations in the same order, but for a fused multiply-add in the last one
+    assert abs(got[5] - ref[5]) <= 4e-16 * (K + abs(ref[5]))
