@@ -249,12 +249,94 @@ __global__ __launch_bounds__(kBinThreads) void lookahead_bin_kernel(
             if (s_ovf[i] != 0) atomicAdd((unsigned long long*)(overflow + i), (unsigned long long)s_ovf[i]);
 }
 
+// The scan of an LDS row of differences into the caller's map by a workgroup of 1024 threads (the same arithmetic as
+// lookahead_scan_kernel); VEC: rows are whole 16-byte pieces; PACKED: s_off holds offset * 2^24 + slope words.
+template <bool VEC, bool PACKED>
+__device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* s_slp, long long* s_w0, long long* s_w1, int k,
+                                             int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
+                                             float* __restrict__ fraction, ps_status* st) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int32_t* out = kv_tokens + (int64_t)k * map_len;
+    float* frow = fraction ? fraction + (int64_t)k * map_len : nullptr;
+    const int cap = fraction ? capacity[k] : 1;
+    const float cap_f = cap >= 1 ? (float)cap : __builtin_nanf("");      // no capacity: fractions are NaN
+    long long carry0 = 0, carry1 = 0;
+    for (int t0 = 0; t0 < map_len; t0 += 4096) {
+        const int t = t0 + 4 * tid;
+        long long a0[4], a1[4];
+        int was[4] = {0, 0, 0, 0};                              // the map's row, requested ahead of the scan
+        if (VEC) {
+            if (t < map_len) {
+                const int4 v = *(const int4*)(out + t);
+                was[0] = v.x; was[1] = v.y; was[2] = v.z; was[3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) if (t + c < map_len) was[c] = out[t + c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const long long v = t + c < map_len ? s_off[t + c] : 0;
+            if (PACKED) {
+                a1[c] = (long long)((unsigned long long)v << 40) >> 40;
+                a0[c] = (v - a1[c]) >> 24;
+            } else {
+                a0[c] = v;
+                a1[c] = t + c < map_len ? (long long)s_slp[t + c] : 0;
+            }
+        }
+#pragma unroll
+        for (int c = 1; c < 4; ++c) { a0[c] += a0[c - 1]; a1[c] += a1[c - 1]; }
+        long long i0 = a0[3], i1 = a1[3];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long u0 = __shfl_up(i0, o, 64), u1 = __shfl_up(i1, o, 64);
+            if (lane >= o) { i0 += u0; i1 += u1; }
+        }
+        if (lane == 63) { s_w0[wave] = i0; s_w1[wave] = i1; }
+        __syncthreads();
+        long long before0 = carry0 + i0 - a0[3], before1 = carry1 + i1 - a1[3];
+        long long tot0 = 0, tot1 = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) { before0 += s_w0[w]; before1 += s_w1[w]; }
+            tot0 += s_w0[w];
+            tot1 += s_w1[w];
+        }
+        int now[4];
+        float part[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const long long nv = (long long)was[c] + (before0 + a0[c]) + (long long)(t + c) * (before1 + a1[c]);
+            if (t + c < map_len && (nv > 2147483647ll || nv < -2147483648ll)) report_fault(st, PS_ST_RANGE, -1);
+            now[c] = (int32_t)(uint32_t)(unsigned long long)nv;
+            part[c] = frow ? (float)nv / cap_f : 0.f;
+        }
+        if (VEC) {
+            if (t < map_len) {
+                *(int4*)(out + t) = make_int4(now[0], now[1], now[2], now[3]);
+                if (frow) *(float4*)(frow + t) = make_float4(part[0], part[1], part[2], part[3]);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (t + c < map_len) {
+                    out[t + c] = now[c];
+                    if (frow) frow[t + c] = part[c];
+                }
+            }
+        }
+        carry0 += tot0;
+        carry1 += tot1;
+        __syncthreads();
+    }
+}
+
 // One workgroup per instance: its entries from every chunk into an LDS row, then the scan of that row
 // into the caller's map (same arithmetic as lookahead_scan_kernel).
 __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
     const unsigned long long* __restrict__ entries, const int32_t* __restrict__ table, int64_t n_chunks, int n_inst,
     int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity, float* __restrict__ fraction,
-    ps_status* st) {
+    int vec, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     long long* s_off = (long long*)lds_raw;                               // [map_len] offset differences
     int* s_slp = (int*)(s_off + map_len);                                 // [map_len] slope differences
@@ -305,49 +387,67 @@ __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
         }
     }
     __syncthreads();
-    int32_t* out = kv_tokens + (int64_t)k * map_len;
-    float* frow = fraction ? fraction + (int64_t)k * map_len : nullptr;
-    const int cap = fraction ? capacity[k] : 1;
-    const float cap_f = cap >= 1 ? (float)cap : __builtin_nanf("");      // no capacity: fractions are NaN
-    long long carry0 = 0, carry1 = 0;
-    for (int t0 = 0; t0 < map_len; t0 += 4096) {
-        const int t = t0 + 4 * tid;
-        long long a0[4], a1[4];
+    if (vec) scan_lds_row<true, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
+    else scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
+}
+
+// ---- short lists ------------------------------------------------------------------------------------
+// One launch and no scratch: a workgroup per instance looks through the whole list's instances (from its XCD's L2; eight
+// ids a thread requested together), applies its own records to an LDS row as above and scans the row into the map.  The
+// atomic route clears, updates and reads back a map-sized difference array: 4096 records over 256 instances of 4096 slots
+// took it 20 us in three launches, 11.5 here.
+const int64_t kDirectMaxRecords = 16384;
+const int64_t kDirectMaxLooks = (int64_t)1 << 23;        // records * instances
+__global__ __launch_bounds__(1024) void lookahead_direct_kernel(
+    const int32_t* __restrict__ instance_id, const int32_t* __restrict__ start_iter,
+    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ i_begin,
+    const int32_t* __restrict__ i_end, const int32_t* __restrict__ sign, int n, int n_inst, int map_len,
+    int32_t* __restrict__ kv_tokens, int64_t* __restrict__ overflow, const int32_t* __restrict__ capacity,
+    float* __restrict__ fraction, int vec, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    unsigned long long* s_row = (unsigned long long*)lds_raw;             // [map_len] packed differences (at most 2^14 records)
+    __shared__ long long s_w0[16], s_w1[16];
+    __shared__ unsigned long long s_ovf;
+    const int k = blockIdx.x, tid = threadIdx.x;
+    for (int i = tid; i < map_len; i += 1024) s_row[i] = 0;
+    if (tid == 0) s_ovf = 0;
+    __syncthreads();
+    constexpr int U = 8;
+    for (int r0 = tid; r0 < n; r0 += 1024 * U) {
+        int kk[U];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            a0[c] = t + c < map_len ? s_off[t + c] : 0;
-            a1[c] = t + c < map_len ? (long long)s_slp[t + c] : 0;
-        }
+        for (int u = 0; u < U; ++u) kk[u] = instance_id[min(r0 + 1024 * u, n - 1)];
 #pragma unroll
-        for (int c = 1; c < 4; ++c) { a0[c] += a0[c - 1]; a1[c] += a1[c - 1]; }
-        long long i0 = a0[3], i1 = a1[3];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const long long u0 = __shfl_up(i0, o, 64), u1 = __shfl_up(i1, o, 64);
-            if (lane >= o) { i0 += u0; i1 += u1; }
-        }
-        if (lane == 63) { s_w0[wave] = i0; s_w1[wave] = i1; }
-        __syncthreads();
-        long long before0 = carry0 + i0 - a0[3], before1 = carry1 + i1 - a1[3];
-        long long tot0 = 0, tot1 = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wave) { before0 += s_w0[w]; before1 += s_w1[w]; }
-            tot0 += s_w0[w];
-            tot1 += s_w1[w];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (t + c < map_len) {
-                const long long nv = (long long)out[t + c] + (before0 + a0[c]) + (long long)(t + c) * (before1 + a1[c]);
-                if (nv > 2147483647ll || nv < -2147483648ll) report_fault(st, PS_ST_RANGE, -1);
-                out[t + c] = (int32_t)(uint32_t)(unsigned long long)nv;
-                if (frow) frow[t + c] = (float)nv / cap_f;
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + 1024 * u;
+            if (r >= n) continue;
+            // an instance outside the map is nobody's: reported by the first workgroup
+            if ((unsigned)kk[u] >= (unsigned)n_inst && k == 0) report_fault(st, PS_ST_BAD_RECORD, r);
+            if (kk[u] != k) continue;
+            const int s = start_iter[r], P = prompt_tokens[r], b = i_begin[r], e = i_end[r], sg = sign[r];
+            if ((unsigned)s >= (unsigned)map_len || (unsigned)P >= (unsigned)PS_MAX_PROMPT || b < 0 || e < b || e > PS_MAX_ITER ||
+                (sg != 1 && sg != -1)) {
+                report_fault(st, PS_ST_BAD_RECORD, r);
+                continue;
             }
+            if (b == e) continue;
+            const int lo = s + b, hi = s + e;                             // both below 2^17
+            const unsigned long long word = (unsigned long long)((long long)sg * (P - s) * (1ll << 24) + sg);
+            if (hi > map_len && overflow) {
+                // iterations io .. e - 1 fall beyond the map: c of them, sum of (P + i) in closed form
+                const long long io = max(b, map_len - s), c = e - io;
+                const long long sum = c * P + (io + e - 1) * c / 2;
+                atomicAdd(&s_ovf, (unsigned long long)((long long)sg * sum));
+            }
+            if (lo < map_len) atomicAdd(&s_row[lo], word);
+            if (hi < map_len) atomicAdd(&s_row[hi], 0ull - word);
         }
-        carry0 += tot0;
-        carry1 += tot1;
-        __syncthreads();
     }
+    __syncthreads();
+    if (tid == 0 && overflow && s_ovf) overflow[k] += (int64_t)s_ovf;
+    const long long* words = (const long long*)s_row;
+    if (vec) scan_lds_row<true, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
+    else scan_lds_row<false, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
 }
 
 // Layout of the workspace: the difference array of the atomic route, then the binned route's entries and table.
@@ -398,6 +498,21 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
     (void)hipGetLastError();
     const int64_t n16 = (int64_t)(plan.diff_bytes / 16);
     const unsigned clear_blocks = (unsigned)((n16 + 255) / 256 < 2048 ? (n16 + 255) / 256 : 2048);
+    // rows of the map (and of the fractions) are whole, aligned 16-byte pieces
+    const int vec_rows = (map_len & 3) == 0 && (((uintptr_t)kv_tokens | (uintptr_t)fraction) & 15) == 0;
+    if (n_rec <= kDirectMaxRecords && n_rec * n_inst <= kDirectMaxLooks && (int64_t)map_len * 8 <= kRowLdsBytes) {
+        static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
+        if (!lds_attr_set) {
+            if (hipFuncSetAttribute((const void*)lookahead_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kRowLdsBytes) != hipSuccess)
+                return PS_EHIP;
+            lds_attr_set = true;
+        }
+        hipLaunchKernelGGL(lookahead_direct_kernel, dim3((unsigned)n_inst), dim3(1024), (size_t)map_len * 8, s, instance_id,
+                           start_iter, prompt_tokens, i_begin, i_end, sign, (int)n_rec, n_inst, map_len, kv_tokens, overflow,
+                           capacity, fraction, vec_rows, status);
+        return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
+    }
     if (plan.binned) {
         static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
         if (!lds_attr_set) {
@@ -427,7 +542,7 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
                                    instance_id + at, start_iter + at, prompt_tokens + at, i_begin + at, i_end + at, sign + at,
                                    n_part, at, n_inst, map_len, entries, table, chunks, overflow, status);
             hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)n_inst), dim3(1024), (size_t)map_len * 12, s, entries,
-                               table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, status);
+                               table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, vec_rows, status);
         }
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }

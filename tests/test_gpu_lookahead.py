@@ -253,3 +253,26 @@ def test_scaler_sizes_around_the_single_launch(K, L, window):
         assert np.array_equal(g, r)
     # the same fp64 operations in the same order, but for a fused multiply-add in the last one
     assert abs(got[5] - ref[5]) <= 4e-16 * (K + abs(ref[5]))
+
+
+@pytest.mark.parametrize("n,K,L", [(1, 1, 1), (7, 3, 5), (1024, 2, 4096), (8193, 5, 1023), (16384, 512, 64), (16385, 3, 300),
+                                   (16384, 513, 64), (5000, 4, 12800), (5000, 4, 12801)])
+def test_short_lists_around_the_direct_route(n, K, L):
+    """List lengths around a thread's batch and the route's limits (16384 records, 2^23 records x instances, rows of
+    12800 slots), rows that are whole 16-byte pieces and not, faulty records, tokens past the map, a map in use."""
+    print(f"look-ahead direct n={n} K={K} L={L}", flush=True)
+    rng = np.random.default_rng(n + L)
+    sign = rng.choice([-1, 1], n)
+    b = rng.integers(0, 300, n)
+    cols = [rng.integers(0, K, n), rng.integers(0, L, n), rng.integers(0, 3000, n), b, b + rng.integers(0, 2 * L + 2, n), sign]
+    cols = [c.astype(np.int32) for c in cols]
+    if n > 4:
+        cols[0][1], cols[0][2], cols[1][3], cols[5][4] = K, -1, L, 0
+    cap = rng.integers(1, 5000, K).astype(np.int32)
+    kv = rng.integers(-1000, 1000, (K, L)).astype(np.int32)
+    ovf = rng.integers(0, 1000, K).astype(np.int64)
+    got = run_lookahead(cols, K, L, kv=kv, overflow=ovf, capacity=cap, want_fraction=True)
+    ref_kv, ref_ovf, _, ref_bad = ol.lookahead_update(*cols, K, L, kv.copy(), ovf.copy())
+    assert np.array_equal(got[0], ref_kv) and np.array_equal(got[1], ref_ovf)
+    assert np.array_equal(got[2], (ref_kv.astype(np.float32) / cap.astype(np.float32)[:, None]))
+    assert got[4] == ref_bad == (1 if n > 4 else -1)
