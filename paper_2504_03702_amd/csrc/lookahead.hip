@@ -27,7 +27,7 @@
 // beyond the map are summed per instance in LDS and added to overflow[] at the end), ranks the chunk's
 // entries per instance with an LDS counter each, and writes them to its own region of the workspace
 // grouped by instance, with the region's per-instance boundaries in a table.  Then one workgroup per
-// instance walks the table, applies its entries to an LDS row (offset differences in 64 bits, slope
+// instance (several where there are few instances, whose rows a last kernel adds up) walks the table, applies its entries to an LDS row (offset differences in 64 bits, slope
 // differences in 32: nothing can overflow) and scans the row into the caller's map itself.  Every record
 // is read once (24 bytes), written once as an entry and read once more (8 bytes each).
 #include "device_util.h"
@@ -128,6 +128,7 @@ const int kBinPerThread = 16;
 const int kBinChunk = kBinThreads * kBinPerThread;       // records per binning workgroup
 const int kBinMaxInst = 4096;                            // instance counters of a chunk live in LDS
 const int kRowLdsBytes = 150 * 1024;                     // LDS a map row may take (12 bytes per slot)
+const int kConsumeWorkgroups = 256;                      // one per compute unit
 const int64_t kBinMinRecords = 65536;                    // shorter lists do not pay for the extra pass
 const int64_t kBinPart = (int64_t)1 << 26;               // records per part (bounds the workspace)
 
@@ -251,10 +252,11 @@ __global__ __launch_bounds__(kBinThreads) void lookahead_bin_kernel(
 
 // The scan of an LDS row of differences into the caller's map by a workgroup of 1024 threads (the same arithmetic as
 // lookahead_scan_kernel); VEC: rows are whole 16-byte pieces; PACKED: s_off holds offset * 2^24 + slope words.
+// prow, if not null: the sums go there and the map is left alone.
 template <bool VEC, bool PACKED>
 __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* s_slp, long long* s_w0, long long* s_w1, int k,
                                              int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
-                                             float* __restrict__ fraction, ps_status* st) {
+                                             float* __restrict__ fraction, long long* __restrict__ prow, ps_status* st) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int32_t* out = kv_tokens + (int64_t)k * map_len;
     float* frow = fraction ? fraction + (int64_t)k * map_len : nullptr;
@@ -272,7 +274,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
             }
         } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) if (t + c < map_len) was[c] = out[t + c];
+            for (int c = 0; c < 4; ++c) if (t + c < map_len && !prow) was[c] = out[t + c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -307,6 +309,10 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const long long nv = (long long)was[c] + (before0 + a0[c]) + (long long)(t + c) * (before1 + a1[c]);
+            if (prow) {
+                if (t + c < map_len) prow[t + c] = nv;
+                continue;
+            }
             if (t + c < map_len && (nv > 2147483647ll || nv < -2147483648ll)) report_fault(st, PS_ST_RANGE, -1);
             now[c] = (int32_t)(uint32_t)(unsigned long long)nv;
             part[c] = frow ? (float)nv / cap_f : 0.f;
@@ -319,7 +325,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (t + c < map_len) {
+                if (t + c < map_len && !prow) {
                     out[t + c] = now[c];
                     if (frow) frow[t + c] = part[c];
                 }
@@ -331,17 +337,24 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
     }
 }
 
-// One workgroup per instance: its entries from every chunk into an LDS row, then the scan of that row
-// into the caller's map (same arithmetic as lookahead_scan_kernel).
+// A workgroup per instance, or `parts` of them where there are too few instances to fill the chip: an even share of the
+// chunks each, dealt evenly to the wavefronts; the entries go into an LDS row.  One part: the row is scanned into the
+// caller's map.  Several: its scan is left in partial[part][instance][slot] for lookahead_combine_kernel.
+// What bounds it is the latency of the entries' loads (segments of 8192 / instances entries): eight segments of a
+// wavefront are requested before the first is applied (long segments: eight loads of one; sixteen of either were slower).
 __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
     const unsigned long long* __restrict__ entries, const int32_t* __restrict__ table, int64_t n_chunks, int n_inst,
     int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity, float* __restrict__ fraction,
-    int vec, ps_status* st) {
+    int vec, int parts, long long* __restrict__ partial, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     long long* s_off = (long long*)lds_raw;                               // [map_len] offset differences
     int* s_slp = (int*)(s_off + map_len);                                 // [map_len] slope differences
     __shared__ long long s_w0[16], s_w1[16];
-    const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // XCD x (workgroups x, x + 8, ...) takes a run of neighbouring instances: their segments share lines at both ends
+    const int per_xcd = (n_inst + 7) >> 3, in_part = blockIdx.x % (8 * per_xcd), part = blockIdx.x / (8 * per_xcd);
+    const int k = (in_part & 7) * per_xcd + (in_part >> 3);
+    if (k >= n_inst) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int i = tid; i < map_len; i += 1024) { s_off[i] = 0; s_slp[i] = 0; }
     __syncthreads();
     auto apply = [&](unsigned long long v) {
@@ -357,24 +370,40 @@ __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
             atomicAdd(&s_slp[hi], -sl);
         }
     };
-    // wavefront w takes chunks 64 w .. 64 w + 63, then 1024 further on; their bounds are fetched together (one chunk
-    // per lane), and the first 64 entries of eight chunks are requested before any is applied
-    for (int64_t c0 = (int64_t)wave * 64; c0 < n_chunks; c0 += 16 * 64) {
+    constexpr int UC = 8;
+    const bool long_segments = n_inst <= 32;                              // on average 256 entries or more
+    const int share = part * 16 + wave, shares = parts * 16;
+    const int64_t c_begin = n_chunks * share / shares, c_end = n_chunks * (share + 1) / shares;
+    for (int64_t c0 = c_begin; c0 < c_end; c0 += 64) {                    // the bounds of 64 chunks, one per lane
         const int64_t mine = c0 + lane;
         int seg_b = 0, seg_e = 0;
-        if (mine < n_chunks) {
+        if (mine < c_end) {
             seg_b = table[(int64_t)k * n_chunks + mine];
             seg_e = table[(int64_t)(k + 1) * n_chunks + mine];
         }
-        constexpr int UC = 8;
-        for (int j0 = 0; j0 < 64; j0 += UC) {
-            if (c0 + j0 >= n_chunks) break;                               // uniform
+        const int here = (int)min((int64_t)64, c_end - c0);
+        if (long_segments) {
+            for (int j = 0; j < here; ++j) {
+                const int b = __builtin_amdgcn_readlane(seg_b, j), e = __builtin_amdgcn_readlane(seg_e, j);
+                const unsigned long long* src = entries + (c0 + j) * kBinChunk;
+                for (int i0 = b; i0 < e; i0 += 64 * UC) {
+                    unsigned long long v[UC];
+#pragma unroll
+                    for (int u = 0; u < UC; ++u) v[u] = src[min(i0 + 64 * u + lane, e - 1)];
+#pragma unroll
+                    for (int u = 0; u < UC; ++u)
+                        if (i0 + 64 * u + lane < e) apply(v[u]);
+                }
+            }
+            continue;
+        }
+        for (int j0 = 0; j0 < here; j0 += UC) {
             int b[UC], e[UC];
             unsigned long long first[UC];
 #pragma unroll
             for (int u = 0; u < UC; ++u) {
-                b[u] = __shfl(seg_b, j0 + u, 64);                          // (chunks past the end: empty segments)
-                e[u] = __shfl(seg_e, j0 + u, 64);
+                b[u] = __builtin_amdgcn_readlane(seg_b, j0 + u);          // (chunks past the end: empty segments)
+                e[u] = __builtin_amdgcn_readlane(seg_e, j0 + u);
                 const unsigned long long* src = entries + (c0 + j0 + u) * kBinChunk;
                 first[u] = b[u] + lane < e[u] ? src[b[u] + lane] : 0ull;
             }
@@ -387,8 +416,28 @@ __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
         }
     }
     __syncthreads();
-    if (vec) scan_lds_row<true, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
-    else scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
+    long long* prow = parts > 1 ? partial + ((int64_t)part * n_inst + k) * map_len : nullptr;
+    if (prow) scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, prow, st);
+    else if (vec) scan_lds_row<true, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+    else scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+}
+
+// The parts' rows added into the caller's map.
+__global__ __launch_bounds__(256) void lookahead_combine_kernel(const long long* __restrict__ partial, int parts, int n_inst,
+                                                                int map_len, int32_t* __restrict__ kv_tokens,
+                                                                const int32_t* __restrict__ capacity,
+                                                                float* __restrict__ fraction, ps_status* st) {
+    const int64_t cells = (int64_t)n_inst * map_len, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= cells) return;
+    long long nv = kv_tokens[i];
+#pragma unroll 8
+    for (int p = 0; p < parts; ++p) nv += partial[p * cells + i];
+    if (nv > 2147483647ll || nv < -2147483648ll) report_fault(st, PS_ST_RANGE, -1);
+    kv_tokens[i] = (int32_t)(uint32_t)(unsigned long long)nv;
+    if (fraction) {
+        const int cap = capacity[i / map_len];
+        fraction[i] = (float)nv / (cap >= 1 ? (float)cap : __builtin_nanf(""));
+    }
 }
 
 // ---- short lists ------------------------------------------------------------------------------------
@@ -446,14 +495,15 @@ __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     __syncthreads();
     if (tid == 0 && overflow && s_ovf) overflow[k] += (int64_t)s_ovf;
     const long long* words = (const long long*)s_row;
-    if (vec) scan_lds_row<true, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
-    else scan_lds_row<false, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, st);
+    if (vec) scan_lds_row<true, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+    else scan_lds_row<false, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
 }
 
 // Layout of the workspace: the difference array of the atomic route, then the binned route's entries and table.
 struct LookaheadPlan {
     bool binned;                 // the call qualifies for the binned route
-    size_t diff_bytes, entries_at, entries_bytes, table_at, table_bytes, total_bytes;
+    size_t diff_bytes, entries_at, entries_bytes, table_at, table_bytes, partial_at, total_bytes;
+    int consumers;               // binned: workgroups that share an instance's entries
     int64_t part;                // records per part of the route taken
 };
 
@@ -471,7 +521,18 @@ LookaheadPlan plan_lookahead(int64_t n_rec, int n_inst, int map_len) {
         p.table_bytes = align_up((size_t)chunks * (size_t)(n_inst + 1) * 4, 256);
     }
     p.table_at = p.entries_at + p.entries_bytes;
-    p.total_bytes = p.table_at + p.table_bytes;
+    p.partial_at = p.table_at + p.table_bytes;
+    p.total_bytes = p.partial_at;
+    p.consumers = 1;
+    if (p.binned) {
+        // few instances: enough workgroups to fill the chip, 8 chunks (65536 records) each at the least
+        const int64_t chunks = ((n_rec < kBinPart ? n_rec : kBinPart) + kBinChunk - 1) / kBinChunk;
+        const int64_t most = chunks / 8 < kConsumeWorkgroups / n_inst ? chunks / 8 : kConsumeWorkgroups / n_inst;
+        if (most > 1) {
+            p.consumers = (int)most;
+            p.total_bytes += align_up((size_t)p.consumers * n_inst * map_len * 8, 256);
+        }
+    }
     return p;
 }
 }  // namespace
@@ -541,8 +602,13 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
                 hipLaunchKernelGGL(lookahead_bin_kernel<false>, dim3((unsigned)chunks), dim3(kBinThreads), (size_t)kBinChunk * 8 + (size_t)n_inst * 12, s,
                                    instance_id + at, start_iter + at, prompt_tokens + at, i_begin + at, i_end + at, sign + at,
                                    n_part, at, n_inst, map_len, entries, table, chunks, overflow, status);
-            hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)n_inst), dim3(1024), (size_t)map_len * 12, s, entries,
-                               table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, vec_rows, status);
+            long long* partial = (long long*)((uint8_t*)workspace + plan.partial_at);
+            hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)((n_inst + 7) / 8 * 8 * plan.consumers)), dim3(1024), (size_t)map_len * 12, s,
+                               entries, table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, vec_rows,
+                               plan.consumers, partial, status);
+            if (plan.consumers > 1)
+                hipLaunchKernelGGL(lookahead_combine_kernel, dim3((unsigned)(((int64_t)n_inst * map_len + 255) / 256)), dim3(256), 0, s,
+                                   partial, plan.consumers, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, status);
         }
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }

@@ -276,3 +276,23 @@ def test_short_lists_around_the_direct_route(n, K, L):
     assert np.array_equal(got[0], ref_kv) and np.array_equal(got[1], ref_ovf)
     assert np.array_equal(got[2], (ref_kv.astype(np.float32) / cap.astype(np.float32)[:, None]))
     assert got[4] == ref_bad == (1 if n > 4 else -1)
+
+
+@pytest.mark.parametrize("n,K,L", [(65536, 1, 64), (131072, 2, 4096), (140_001, 1, 12800), (600_011, 33, 1021), (600_011, 32, 1024),
+                                   (1_100_000, 127, 37), (300_000, 129, 256)])
+def test_few_instances_share_their_entries(n, K, L):
+    """Binned lists over few instances: several workgroups fold one instance's entries (8 chunks each at the least),
+    long and short segments (the line lies at 32 instances), fractions and a map in use."""
+    print(f"look-ahead few instances n={n} K={K} L={L}", flush=True)
+    rng = np.random.default_rng(n + L)
+    b = rng.integers(0, 300, n)
+    cols = [rng.integers(0, K, n), rng.integers(0, L, n), rng.integers(0, 3000, n), b, b + rng.integers(0, 2 * L + 2, n),
+            rng.choice([-1, 1], n)]
+    cols = [c.astype(np.int32) for c in cols]
+    cols[0][n // 2], cols[5][n - 1] = K, 0
+    cap = rng.integers(1, 5000, K).astype(np.int32)
+    kv = rng.integers(-1000, 1000, (K, L)).astype(np.int32)
+    got = run_lookahead(cols, K, L, kv=kv, capacity=cap, want_fraction=True)
+    ref_kv, ref_ovf, _, ref_bad = ol.lookahead_update(*cols, K, L, kv.copy())
+    assert np.array_equal(got[0], ref_kv) and np.array_equal(got[1], ref_ovf) and got[4] == ref_bad == n // 2
+    assert np.array_equal(got[2], ref_kv.astype(np.float32) / cap.astype(np.float32)[:, None])
