@@ -203,3 +203,21 @@ def test_host_side_argument_errors():
     with pytest.raises(ps.PsError) as e:      # workspace too small
         ps.ps_anticipate(z, z, z, None, 2, 4, load, None, ws[:256].contiguous()[:16])
     assert e.value.code == -5
+
+
+@pytest.mark.parametrize("n,K,T,with_rate", [(1, 1, 1, True), (8192, 3, 1023, True), (8193, 2, 1024, False), (16384, 512, 65, True),
+                                             (16384, 513, 65, True), (16385, 4, 600, True), (3000, 2, 16000, True),
+                                             (3000, 2, 16001, False), (64, 5000, 30, True)])
+def test_short_calls_around_the_direct_route(n, K, T, with_rate):
+    """Batch sizes around a thread's batch of records and the route's limits (16384 records, 2^23 records x instances,
+    horizons of 16000 buckets), long predictions that run past the horizon, a map and overflow in use."""
+    print(f"anticipate direct n={n} K={K} T={T} rate={with_rate}", flush=True)
+    rng = np.random.default_rng(n + T)
+    pred = rng.integers(0, 4097, n).astype(np.int32)
+    pred[:: 50] = 65535
+    inp = wl.AnticipatorInputs(pred, rng.integers(0, K, n).astype(np.int32), rng.integers(0, T, n).astype(np.int32),
+                               rng.integers(1, 90, K).astype(np.int32) if with_rate else None, K, T)
+    load0 = rng.integers(0, 1000, (K, T)).astype(np.int32)
+    ovf0 = rng.integers(0, 1000, K).astype(np.int64)
+    _, _, flags = check(inp, load0, ovf0)
+    assert flags == 0
