@@ -1,4 +1,4 @@
-// fp32 encoder path (models stored in fp32): plain LDS-tiled kernels in full single precision.
+// fp32 encoder path (models stored in fp32): kernels in full single precision.
 // It exists for small models whose results must track the fp64 definition to 1e-4; the bf16
 // MFMA path in encoder_bf16.hip is the one built for throughput.
 #include "device_util.h"
@@ -8,52 +8,81 @@ namespace {
 
 enum { F32_NONE = 0, F32_GELU = 1, F32_RESIDUAL = 2 };
 
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
 // C[m, n] = sum_k A[m, k] W[k, n] + bias[n], then GELU or + residual[m, n].
-// 64 x 64 output tile, 16-deep k slices staged in LDS, 4 x 4 outputs per thread.
-template <int EPI>
+//
+// v_mfma_f32_32x32x2_f32 (fp32 products and sums) on fragments straight from global memory: the matrices are small and
+// sit in L2, and what a staged 64 x 64 tile cost was a trip to memory per 16-deep slice (23 us for K = 128, 75 us for
+// K = 512 at 600 rows).  A workgroup owns TM x 32 rows and 32 columns; its four wavefronts split the contraction and
+// their sums are added through LDS in order.  In a group of eight k lane l holds four consecutive ones of its row of A
+// (one 16-byte load; lanes 32.. the upper four) and the same four rows of its column of W, a whole 128-byte line per
+// row; eight groups are requested before the first is used.  VEC: K a multiple of 8 and N of 32, so nothing is ragged.
+template <int EPI, int TM, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        const float* __restrict__ bias,
                                                        const float* __restrict__ residual, float* __restrict__ C,
                                                        int N, int K, const BatchMeta* meta) {
-    __shared__ float sA[16][64 + 1];
-    __shared__ float sW[16][64 + 1];
-    const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+    __shared__ float s_part[4][TM * 32][33];
+    const int m0 = blockIdx.x * 32 * TM, n0 = blockIdx.y * 32;
     if (m0 >= meta->total_rows) return;
-    const int tid = threadIdx.x;
-    const int tm = (tid / 16) * 4, tn = (tid % 16) * 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int i = tid; i < 64 * 16; i += 256) {
-            const int r = i / 16, kk = i % 16;          // A: rows are always inside the padded buffer
-            sA[kk][r] = (k0 + kk < K) ? A[(int64_t)(m0 + r) * K + k0 + kk] : 0.f;
-            const int wk = i / 64, wn = i % 64;
-            sW[wk][wn] = (k0 + wk < K && n0 + wn < N) ? W[(int64_t)(k0 + wk) * N + n0 + wn] : 0.f;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 31, half = lane >> 5, n = n0 + row;
+    const int groups = (K + 7) / 8, g0 = groups * wave / 4, g1 = groups * (wave + 1) / 4;
+    const float* ap = A + (int64_t)(m0 + row) * K + 4 * half;    // rows are always inside the padded buffer
+    const float* wp = W + (int64_t)(4 * half) * N + (VEC ? n : min(n, N - 1));
+    f32x16 acc[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    constexpr int U = 8 / TM;
+    for (int g = g0; g < g1; g += U) {
+        float a[U][TM][4], w[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = 8 * min(g + u, g1 - 1);               // (past the end: the last group again, not used)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (VEC) {
+                    const float4 v = *(const float4*)(ap + (int64_t)(32 * i) * K + k);
+                    a[u][i][0] = v.x; a[u][i][1] = v.y; a[u][i][2] = v.z; a[u][i][3] = v.w;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) a[u][i][t] = k + 4 * half + t < K ? ap[(int64_t)(32 * i) * K + k + t] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                w[u][t] = VEC || k + 4 * half + t < K ? wp[(int64_t)(k + t) * N] : 0.f;
         }
-        __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], w[4];
+        for (int u = 0; u < U; ++u) {
+            if (g + u < g1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[kk][tm + i]; w[i] = sW[kk][tn + i]; }
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
+                    for (int i = 0; i < TM; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i][t], w[u][t], acc[i], 0, 0, 0);
+            }
         }
-        __syncthreads();
     }
+    // element e of a lane is row 8 (e / 4) + 4 half + e % 4, column lane % 32
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tn + j;
-            if (n >= N) continue;
-            const int64_t at = (int64_t)(m0 + tm + i) * N + n;
-            float v = acc[i][j] + bias[n];
-            if (EPI == F32_GELU) v = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-            if (EPI == F32_RESIDUAL) v += residual[at];
-            C[at] = v;
-        }
+        for (int e = 0; e < 16; ++e) s_part[wave][32 * i + 8 * (e >> 2) + 4 * half + (e & 3)][row] = acc[i][e];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4 * TM; ++i) {
+        const int r = 8 * i + (threadIdx.x >> 5), c = threadIdx.x & 31;
+        if (!VEC && n0 + c >= N) continue;
+        const int64_t at = (int64_t)(m0 + r) * N + n0 + c;
+        float v = ((s_part[0][r][c] + s_part[1][r][c]) + (s_part[2][r][c] + s_part[3][r][c])) + bias[n0 + c];
+        if (EPI == F32_GELU) v = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+        if (EPI == F32_RESIDUAL) v += residual[at];
+        C[at] = v;
+    }
 }
 
 // One wavefront per (row, head): scores of the row against its request's keys go to LDS, then
@@ -124,15 +153,22 @@ __global__ __launch_bounds__(256) void layernorm_f32_kernel(const float* __restr
     for (int i = lane; i < H; i += 64) out[row * H + i] = (x[i] - mean) * rstd * gamma[i] + beta[i];
 }
 
-void gemm_f32(int epi, const float* A, const float* W, const float* bias, const float* res, float* C,
-              int64_t max_rows, int N, int K, const BatchMeta* meta, hipStream_t s) {
-    dim3 grid((unsigned)(max_rows / 64), (unsigned)((N + 63) / 64));
-    if (epi == F32_NONE)
-        hipLaunchKernelGGL(gemm_f32_kernel<F32_NONE>, grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
-    else if (epi == F32_GELU)
-        hipLaunchKernelGGL(gemm_f32_kernel<F32_GELU>, grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
+template <int EPI, int TM>
+void gemm_f32_rows(const float* A, const float* W, const float* bias, const float* res, float* C, int64_t max_rows, int N, int K,
+                   const BatchMeta* meta, hipStream_t s) {
+    const dim3 grid((unsigned)(max_rows / (32 * TM)), (unsigned)((N + 31) / 32));
+    if (N % 32 == 0 && K % 8 == 0)
+        hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, true>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
     else
-        hipLaunchKernelGGL(gemm_f32_kernel<F32_RESIDUAL>, grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
+        hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, false>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
+}
+
+template <int EPI>
+void gemm_f32(const float* A, const float* W, const float* bias, const float* res, float* C, int64_t max_rows, int N, int K,
+              const BatchMeta* meta, hipStream_t s) {
+    // enough workgroups to fill the chip twice: a tile of 64 rows reads W half as often
+    if (max_rows / 64 * ((N + 31) / 32) >= 512) gemm_f32_rows<EPI, 2>(A, W, bias, res, C, max_rows, N, K, meta, s);
+    else gemm_f32_rows<EPI, 1>(A, W, bias, res, C, max_rows, N, K, meta, s);
 }
 
 }  // namespace
@@ -146,14 +182,14 @@ void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipS
     const size_t att_lds = sizeof(float) * 4 * (size_t)(f.max_pos + d);
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
-        gemm_f32(F32_NONE, x, (const float*)w.w_qkv, w.b_qkv, nullptr, qkv, ws.max_rows, 3 * H, H, ws.meta, s);
+        gemm_f32<F32_NONE>(x, (const float*)w.w_qkv, w.b_qkv, nullptr, qkv, ws.max_rows, 3 * H, H, ws.meta, s);
         hipLaunchKernelGGL(attention_f32_kernel, dim3(row_blocks, (unsigned)f.heads), dim3(256), att_lds, s,
                            qkv, att, H, d, n_req, f.max_pos, ws.meta, ws.seq_len, ws.row_start);
-        gemm_f32(F32_RESIDUAL, att, (const float*)w.w_o, w.b_o, x, y, ws.max_rows, H, H, ws.meta, s);
+        gemm_f32<F32_RESIDUAL>(att, (const float*)w.w_o, w.b_o, x, y, ws.max_rows, H, H, ws.meta, s);
         hipLaunchKernelGGL(layernorm_f32_kernel, dim3(row_blocks), dim3(256), 0, s, y, x1, w.ln1_g, w.ln1_b,
                            m->ln_eps, H, ws.meta);
-        gemm_f32(F32_GELU, x1, (const float*)w.w_1, w.b_1, nullptr, g, ws.max_rows, F, H, ws.meta, s);
-        gemm_f32(F32_RESIDUAL, g, (const float*)w.w_2, w.b_2, x1, y, ws.max_rows, H, F, ws.meta, s);
+        gemm_f32<F32_GELU>(x1, (const float*)w.w_1, w.b_1, nullptr, g, ws.max_rows, F, H, ws.meta, s);
+        gemm_f32<F32_RESIDUAL>(g, (const float*)w.w_2, w.b_2, x1, y, ws.max_rows, H, F, ws.meta, s);
         hipLaunchKernelGGL(layernorm_f32_kernel, dim3(row_blocks), dim3(256), 0, s, y, x, w.ln2_g, w.ln2_b,
                            m->ln_eps, H, ws.meta);
     }

@@ -167,3 +167,20 @@ def test_host_side_argument_errors(tmp_models):
     assert ps.ps_workspace_bytes(model, -1, 4) == 0
     info = model.info
     assert (info.layers, info.hidden, info.heads, info.ffn, info.vocab, info.dtype) == (2, 128, 2, 512, 8192, 0)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,n", [(8, 1, 8, 3), (24, 2, 40, 5), (96, 3, 32, 40), (32, 4, 264, 600), (65, 5, 33, 20)])
+def test_matrix_tiles_at_their_edges(tmp_models, hidden, heads, ffn, n):
+    """Contractions of fewer groups of eight than wavefronts, columns that do not fill a tile of 32, rows enough for the
+    64-row tiles."""
+    cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=300, max_pos=70, head_hidden=17, dtype=wl.DTYPE_FP32)
+    print(f"predict fp32 hidden={hidden} ffn={ffn} n={n}", flush=True)
+    model, ref = make(tmp_models, f"edges_{hidden}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(hidden)
+    lengths = rng.integers(1, 65, n).astype(np.int32)
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got_f, got_t, flags, _ = run_predict(model, batch)
+    ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
+    assert flags == 0
+    assert rel_err(got_f, ref_f).max() < TOL_FP32
+    check_tokens(got_f, got_t, ref_t, cfg.d_max)
