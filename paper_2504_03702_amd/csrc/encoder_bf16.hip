@@ -134,11 +134,11 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
         const ResidualSrc in_cls = {x, ws.la, ws.sa, sg, sbeta, ws.row_start, ws.seq_len, x1, ps, nullptr};
         const ResidualSrc ffn_cls = {x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, ws.row_start, ws.seq_len, nullptr, nullptr, nullptr};
         if (skinny) {
-            const SkinnyArgs so = skinny_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H, 2 * H, 0, nullptr);
+            const SkinnyArgs so = skinny_args(ws.cls_a, w.w_o, w.b_o, in_cls, ws.lb, H, H, H, 0, nullptr);
             const SkinnyArgs s1 = skinny_args(nullptr, w.w_1d, w.b_1, ffn_cls, ws.cls_g, F, H, 2 * H,
                                               last ? SKINNY_STATS_ROWS : fused ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN,
                                               last ? ws.sb : nullptr);
-            const SkinnyArgs s2 = skinny_args(ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F, 2 * F, 0, nullptr);
+            const SkinnyArgs s2 = skinny_args(ws.cls_g, w.w_2, w.b_2, mid_cls, ws.la, H, F, F, 0, nullptr);
             if (fused && !last) {
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(att, w.w_o, w.b_o, in, ws.lb, H, H, rows, nullptr, nullptr), &so, s));
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_GELU, small(x1, w.w_1, w.d_1, fold_1, g, F, H, rows, ws.ps, ws.sb), &s1, s));

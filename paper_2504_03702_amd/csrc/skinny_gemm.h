@@ -141,6 +141,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     const int total_rounds = K / 64;                    // dealt to the shares as evenly as whole rounds allow
     const int lda = DUAL && !NORM ? 2 * K : K;
     const int64_t wg = (int64_t)16 * ldw;               // next column group: 16 rows of W further
+    const bool on = frow < n_req;
     constexpr int U = NORM ? 2 : DUAL ? 3 : 4;          // rounds whose loads are in flight together
     for (int sh = 0; sh < SH; ++sh) {
         const int share = wave * SH + sh;
@@ -153,15 +154,17 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};
         for (int t0 = 0; t0 < max(rounds, 1); t0 += U) {
-            sk_bf16x8 fa[U][2], fl[DUAL ? U : 1][2], fw[U][4][2];
+            sk_bf16x8 fa[U][2] = {}, fl[DUAL ? U : 1][2] = {}, fw[U][4][2];
             float4 gv[NORM ? U : 1][4], bb[NORM ? U : 1][4];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int t = min(t0 + u, max(rounds, 1) - 1);   // (past the end: the last round again, not used)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    fa[u][h] = *(const sk_bf16x8*)(ap + 64 * t + 8 * h);
-                    if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
+                    if (on) {                           // (the other lanes' rows are nobody's)
+                        fa[u][h] = *(const sk_bf16x8*)(ap + 64 * t + 8 * h);
+                        if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
+                    }
 #pragma unroll
                     for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg + 64 * t + 8 * h);
                 }
