@@ -31,6 +31,8 @@ Workspace plan_workspace(const ps_model_info& info, int64_t n_tokens, int32_t n_
     ws.row_start = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.qtile_start = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.bad_req = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
+    ws.head_done = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
+    ws.head_sum = (float*)take(sizeof(float) * 32 * (size_t)(n_req < 256 ? n_req + 1 : 256));   // (several workgroups a request: at most 128)
     ws.x = take(es * rows * H);
     ws.qkv = take(es * rows * 3 * H);
     ws.vt = info.dtype == 1 ? take(es * rows * H + 1024) : nullptr;   // + slack: the last key tile may read past a row end

@@ -176,9 +176,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, 2 * H));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, 2 * F));
         }
-        if (last)
-            PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x, ws.la, ws.sa, s));   // what the head reads
-        else if (!fused)
+        if (!last && !fused)                             // (the head makes the last LayerNorm's statistics itself)
             PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sa, m->ln_eps, H, ws.max_rows, rows, s));
         sg = w.ln2_g;
         sbeta = w.ln2_b;

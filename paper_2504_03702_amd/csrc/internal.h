@@ -74,6 +74,8 @@ struct Workspace {
     int32_t *row_start;          // [B+1] first activation row of request r
     int32_t *qtile_start;        // [B+1] first attention query tile of request r
     int32_t *bad_req;            // [B]   set when a request's text holds an invalid token id
+    int32_t *head_done;          // [B]   workgroups of the head that have left their sum
+    float *head_sum;             // [B][32] the sums of their rounds of 64 hidden units
     void *x, *qkv, *vt, *att, *y, *x1, *g;
     // bf16 path: the residual stream is kept as the pre-LayerNorm sums of the last two sublayers,
     // each sum as two bf16 values hi + lo (16 significant bits), plus each row's (mean, 1/std); its

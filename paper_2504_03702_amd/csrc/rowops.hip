@@ -19,7 +19,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
                                                     long long row_capacity, BatchMeta* meta,
                                                     int32_t* seq_len, int32_t* row_start,
                                                     int32_t* qtile_start, int32_t* bad_req,
-                                                    ps_status* st) {
+                                                    int32_t* head_done, ps_status* st) {
     __shared__ long long s_rows[1024];
     __shared__ long long s_tiles[1024];
     __shared__ long long s_cut_rows, s_cut_tiles;     // rows / query tiles in front of the first request that does not fit
@@ -37,6 +37,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
         if (bad) report_fault(st, PS_ST_BAD_LENGTH, r);
         seq_len[r] = S;
         bad_req[r] = 0;
+        head_done[r] = 0;
         rows += (S + PS_ROW_ALIGN - 1) / PS_ROW_ALIGN * PS_ROW_ALIGN;
         tiles += (S + PS_ATT_BQ - 1) / PS_ATT_BQ;
     }
@@ -234,68 +235,98 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
 }
 
 // ------------------------------------------------------------------------------------------
-// head: one workgroup of 16 wavefronts per request.  c = final state of the request's first row
-// (bf16 path: the last LayerNorm recomputed in fp32 from the row's sums and statistics); wavefront w
-// takes hidden units j = w, w + 16, ..., four of them at a time (their loads are all requested before
-// the first is used: with few requests the kernel's time is the latency of these loads): 64-lane dot
-// products of c with rows of W_h1^T reduced across the wavefront, ReLU, times w_h2[j]; the sixteen
-// partial sums are added in a fixed order.  pred_tokens = clamp(rint(y), 0, d_max) with rint
-// rounding half to even.
+// head: workgroups of 16 wavefronts, `parts` of them per request.  c = final state of the request's first row
+// (bf16 path: the last LayerNorm in fp32 from the row's sums, statistics in two passes); of a part's hidden units
+// wavefront w takes j = w, w + 16, ..., four of them at a time (their loads are all requested before the first is used,
+// the first four units' before the row itself): 64-lane dot products of c with rows of W_h1^T reduced across the
+// wavefront, ReLU, times w_h2[j]; the sixteen partial sums are added in a fixed order.  With few requests the kernel's
+// time is one compute unit's rate on W_h1 (2.4 MB: 37 us), so several workgroups share a request: each leaves its rounds'
+// sums in the workspace and the last to arrive (a counter per request, cleared by prep) adds them in order.
+// pred_tokens = clamp(rint(y), 0, d_max) with rint rounding half to even.
 // ------------------------------------------------------------------------------------------
 const int kHeadWaves = 16;
+const int kHeadUnits = 4 * kHeadWaves;    // units of one round
+const int kHeadParts = 32;                // most workgroups per request
+
+__device__ __forceinline__ float head_block_sum(float v, float* s_red) {
+    v = wave_sum(v);
+    __syncthreads();                                     // s_red's previous use is over
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < kHeadWaves; ++w) t += s_red[w];
+    return t;
+}
 
 template <typename T>
 __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restrict__ x, const int32_t* __restrict__ seq_len,
                                                    const int32_t* __restrict__ row_start,
                                                    const int32_t* __restrict__ bad_req,
-                                                   const bf16_t* __restrict__ y_lo, const float2* __restrict__ stats,
-                                                   const float* __restrict__ ln_g, const float* __restrict__ ln_b,
+                                                   const bf16_t* __restrict__ y_lo,
+                                                   const float* __restrict__ ln_g, const float* __restrict__ ln_b, float eps,
                                                    int H, int Hh,
                                                    const float* __restrict__ w_h1t, const float* __restrict__ b_h1,
                                                    const float* __restrict__ w_h2, float b_h2, int d_max,
+                                                   int parts, float* __restrict__ part_sum, int32_t* __restrict__ part_done,
                                                    float* __restrict__ pred_f, int32_t* __restrict__ pred_tokens,
                                                    ps_status* st) {
-    extern __shared__ float s_c[];           // [H] + kHeadWaves partial sums
-    const int r = blockIdx.x;
+    extern __shared__ float s_c[];           // [H], kHeadWaves partial sums, the rounds' sums
+    const int r = blockIdx.x / parts, part = blockIdx.x - r * parts;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (seq_len[r] <= 0 || bad_req[r]) {
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0 && part == 0) {
             pred_f[r] = __builtin_nanf("");
             pred_tokens[r] = -1;
         }
         return;
     }
+    const int rounds = (Hh + kHeadUnits - 1) / kHeadUnits;
+    const int rd0 = rounds * part / parts, rd1 = rounds * (part + 1) / parts;
+    const int u0 = rd0 * kHeadUnits;
+    // every round's sum is kept apart (those from the 32nd on together), so the result does not depend on `parts`
+    float* s_round = s_c + H + kHeadWaves;               // [wavefront][kHeadParts]
+    const bool wide = (H & 255) == 0 && H <= 2048;       // rows of whole 16-byte pieces per lane (all bf16 models)
+    const int nch = H >> 8;
+    float4 wv[4][4];
+    // lane l holds the 4-element pieces l, l + 64, ... of a row, four pieces (1024 elements) at a time
+    auto load_w = [&](int j0, int c0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = min(j0 + u * kHeadWaves, Hh - 1);      // (a unit past the end re-reads the last row)
+            const float4* w = (const float4*)(w_h1t + (int64_t)j * H);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                wv[u][c] = c0 + c < nch ? w[lane + 64 * (c0 + c)] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    if (wide) load_w(u0 + wave, 0);
+    asm volatile("" ::: "memory");
     const int64_t crow = row_start[r];
     if (y_lo) {
-        // bf16 models: x holds the hi parts of the last sums
-        const float2 st2 = stats[crow];
+        // bf16 models (H at most 2048: two elements a thread): x holds the hi parts of the last sums
         const bf16_t* hi = (const bf16_t*)x + crow * H;
         const bf16_t* lo = y_lo + crow * H;
-        for (int i = threadIdx.x; i < H; i += kHeadWaves * 64)
-            s_c[i] = ((bf16_to_f32(hi[i]) + bf16_to_f32(lo[i])) - st2.x) * st2.y * ln_g[i] + ln_b[i];
+        const int i0 = threadIdx.x, i1 = threadIdx.x + kHeadWaves * 64;
+        const float v0 = i0 < H ? bf16_to_f32(hi[i0]) + bf16_to_f32(lo[i0]) : 0.f;
+        const float v1 = i1 < H ? bf16_to_f32(hi[i1]) + bf16_to_f32(lo[i1]) : 0.f;
+        const float mean = head_block_sum(v0 + v1, s_c + H) / (float)H;
+        const float d0 = i0 < H ? v0 - mean : 0.f, d1 = i1 < H ? v1 - mean : 0.f;
+        const float rstd = 1.0f / sqrtf(head_block_sum(fmaf(d0, d0, d1 * d1), s_c + H) / (float)H + eps);
+        if (i0 < H) s_c[i0] = fmaf(d0 * rstd, ln_g[i0], ln_b[i0]);
+        if (i1 < H) s_c[i1] = fmaf(d1 * rstd, ln_g[i1], ln_b[i1]);
     } else {
         const T* c = x + crow * H;
         for (int i = threadIdx.x; i < H; i += kHeadWaves * 64) s_c[i] = load_elem<T>(c, i);
     }
     __syncthreads();
-    float acc = 0.f;
-    const bool wide = (H & 255) == 0 && H <= 2048;       // rows of whole 16-byte pieces per lane (all bf16 models)
-    for (int j0 = wave; j0 < Hh; j0 += 4 * kHeadWaves) {
+    for (int rd = rd0; rd < rd1; ++rd) {
+        const int j0 = rd * kHeadUnits + wave;
+        float acc = 0.f;
         float dot[4] = {0.f, 0.f, 0.f, 0.f};
         if (wide) {
-            // lane l holds the 4-element pieces l, l + 64, ... of a row; the loads of four units' rows are all
-            // requested before the first product is taken, four pieces (1024 elements) at a time
-            const int nch = H >> 8;
             for (int c0 = 0; c0 < nch; c0 += 4) {
-                float4 wv[4][4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int j = min(j0 + u * kHeadWaves, Hh - 1);      // (a unit past the end re-reads the last row)
-                    const float4* w = (const float4*)(w_h1t + (int64_t)j * H);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        wv[u][c] = c0 + c < nch ? w[lane + 64 * (c0 + c)] : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                if (rd != rd0 || c0) load_w(j0, c0);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     if (c0 + c < nch) {
@@ -324,12 +355,24 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
                 acc += (d < 0.f ? 0.f : d) * w_h2[j];   // ReLU that lets a NaN through to the check below
             }
         }
+        float* slot = s_round + wave * kHeadParts + min(rd, kHeadParts - 1);
+        if (lane == 0) *slot = rd < kHeadParts ? acc : *slot + acc;
     }
-    if (lane == 0) s_c[H + wave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         float y = 0.f;
-        for (int w = 0; w < kHeadWaves; ++w) y += s_c[H + w];
+        for (int i = min(rd0, kHeadParts); i < min(rd1, kHeadParts); ++i) {
+            float t = 0.f;
+            for (int w = 0; w < kHeadWaves; ++w) t += s_round[w * kHeadParts + i];
+            if (parts > 1) __hip_atomic_store(part_sum + (int64_t)r * kHeadParts + i, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            y += t;
+        }
+        if (parts > 1) {
+            if (__hip_atomic_fetch_add(part_done + r, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != parts - 1) return;
+            y = 0.f;
+            for (int i = 0; i < rounds; ++i)
+                y += __hip_atomic_load(part_sum + (int64_t)r * kHeadParts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         y += b_h2;
         pred_f[r] = y;
         if (y != y) {
@@ -418,7 +461,7 @@ void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengt
                  const Workspace& ws, ps_status* st, hipStream_t s) {
     hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft,
                        m->info.max_pos, (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), ws.meta, ws.seq_len,
-                       ws.row_start, ws.qtile_start, ws.bad_req, st);
+                       ws.row_start, ws.qtile_start, ws.bad_req, ws.head_done, st);
 }
 
 void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* offsets, int32_t n_req,
@@ -440,15 +483,20 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
 void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* pred_f, int32_t* pred_tokens,
                  ps_status* st, hipStream_t s) {
     const ps_model_info& f = m->info;
-    const size_t lds = sizeof(float) * (size_t)(f.hidden + kHeadWaves);
+    const size_t lds = sizeof(float) * (size_t)(f.hidden + kHeadWaves + kHeadWaves * kHeadParts);
+    // enough workgroups to fill the chip, a round of 64 units each at the least
+    const int rounds = (f.head_hidden + kHeadUnits - 1) / kHeadUnits;
+    int parts = 256 / n_req < rounds ? 256 / n_req : rounds;
+    if (parts < 1 || rounds > kHeadParts) parts = 1;
+    const dim3 grid((unsigned)n_req * (unsigned)parts);
     if (f.dtype == 1)
-        hipLaunchKernelGGL(head_kernel<bf16_t>, dim3(n_req), dim3(kHeadWaves * 64), lds, s, (const bf16_t*)ws.x,
-                           ws.seq_len, ws.row_start, ws.bad_req, (const bf16_t*)ws.la, (const float2*)ws.sa,
-                           (const float*)m->layers.back().ln2_g, (const float*)m->layers.back().ln2_b, f.hidden, f.head_hidden, m->w_h1t, m->b_h1, m->w_h2,
-                           m->b_h2, f.d_max, pred_f, pred_tokens, st);
+        hipLaunchKernelGGL(head_kernel<bf16_t>, grid, dim3(kHeadWaves * 64), lds, s, (const bf16_t*)ws.x, ws.seq_len, ws.row_start,
+                           ws.bad_req, (const bf16_t*)ws.la, (const float*)m->layers.back().ln2_g,
+                           (const float*)m->layers.back().ln2_b, m->ln_eps, f.hidden, f.head_hidden, m->w_h1t, m->b_h1, m->w_h2,
+                           m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f, pred_tokens, st);
     else
-        hipLaunchKernelGGL(head_kernel<float>, dim3(n_req), dim3(kHeadWaves * 64), lds, s, (const float*)ws.x,
-                           ws.seq_len, ws.row_start, ws.bad_req, (const bf16_t*)nullptr, (const float2*)nullptr,
-                           (const float*)nullptr, (const float*)nullptr, f.hidden, f.head_hidden, m->w_h1t, m->b_h1, m->w_h2,
-                           m->b_h2, f.d_max, pred_f, pred_tokens, st);
+        hipLaunchKernelGGL(head_kernel<float>, grid, dim3(kHeadWaves * 64), lds, s, (const float*)ws.x, ws.seq_len, ws.row_start,
+                           ws.bad_req, (const bf16_t*)nullptr, (const float*)nullptr, (const float*)nullptr, 0.f, f.hidden,
+                           f.head_hidden, m->w_h1t, m->b_h1, m->w_h2, m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f,
+                           pred_tokens, st);
 }

@@ -1,6 +1,8 @@
 """Calls of few requests or few rows: 64 x 64 tiles with the per-request maps in the same launches.  Their
 accumulation order is that of the large tiles, so the same requests in a layout with many padding slots (which
 takes the large tiles) must give the same bits; the fp64 oracle bounds both."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -53,3 +55,18 @@ def test_faulty_request_leaves_the_others(tmp_models):
     assert flags != 0 and bad == 1
     assert np.isnan(got[[1, 3]]).all() and (tokens[[1, 3]] == -1).all()
     assert np.array_equal(got[good], want)
+
+
+@pytest.mark.parametrize("head_hidden", [1, 63, 64, 65, 129, 2048, 2100])
+def test_head_rounds(tmp_models, head_hidden):
+    """Hidden units of the head around its rounds of 64 and beyond the 32 rounds that are kept apart: a request's value
+    must not depend on how many workgroups share it (one at 256 requests, several below 129)."""
+    print(f"predict head_hidden={head_hidden}", flush=True)
+    cfg = dataclasses.replace(SMALL, layers=1, head_hidden=head_hidden)
+    model, ref = make(tmp_models, f"head_{head_hidden}.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    lengths = np.random.default_rng(3).integers(1, 20, 256).astype(np.int32)
+    ids = np.random.default_rng(4).integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32)
+    batch = wl.pack_prompts(lengths, ids)
+    got = check(model, ref, batch)
+    few = wl.pack_prompts(lengths[:17], ids[:batch.offsets[17]])
+    assert np.array_equal(check(model, ref, few), got[:17])
