@@ -40,9 +40,9 @@ void launch_ln_stats(const float2* pstats, float2* stats, float eps, int hidden,
 }
 
 // Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
-// Six-layer encoder, hidden 768: 253 rows 805 -> 435 us, 907 rows 869 -> 518 us; at 3200 rows the large tiles' better
-// reuse wins (993 us against 1036), so the line lies below that.
-#define PS_FUSED_ROWS 2560
+// Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
+// 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
+#define PS_FUSED_ROWS 3584
 
 void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hipStream_t s) {
     const ps_model_info& f = m->info;
