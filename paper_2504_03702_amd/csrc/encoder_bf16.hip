@@ -57,19 +57,18 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     // the stream entering layer 0 is the embedding LayerNorm of the sums the embed kernel left in (x, la)
     const float *sg = m->lne_g, *sbeta = m->lne_b;
 #define PS_TIMED(FAM, CALL) do { ProfScope p_(m, FAM, s); CALL; } while (0)
-    // the per-request side maps of calls of more than 16 requests (k_cols: columns per row of A and W; the hi | lo
-    // forms hold twice the map's contraction length)
+    // the per-request side maps of calls of more than 16 requests
     auto side_gemm = [&](GemmEpilogue epi, const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C,
-                         int N, int k_cols) {
+                         int N, int K) {
         SmallGemm p = {};
         p.A = A; p.W = (const bf16_t*)W; p.bias = bias; p.res = r; p.C = C;
-        p.max_rows = ws.cls_rows; p.N = N; p.K = k_cols; p.hidden = H; p.rows = n_req_dev;
+        p.max_rows = ws.cls_rows; p.N = N; p.K = K; p.hidden = H; p.rows = n_req_dev;
         launch_small_gemm_bf16(epi, p, nullptr, s);
     };
     const bool skinny = n_req <= PS_SKINNY_ROWS;
-    auto skinny_args = [&](const void* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K, int ldw,
+    auto skinny_args = [&](const void* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K,
                            int stats_from, float2* stats_out) {
-        return SkinnyArgs{(const bf16_t*)A, (const bf16_t*)W, bias, r, C, N, K, ldw, H, n_req,
+        return SkinnyArgs{(const bf16_t*)A, (const bf16_t*)W, bias, r, C, N, K, H, n_req,
                           stats_from, ws.ps, stats_out, 1.0f / (float)H, m->ln_eps};
     };
     // Calls of a few requests over few rows: a layer is five launches, each map's launch doing the per-request map
@@ -110,14 +109,14 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
             const ResidualSrc first_rows = {x, ws.la, ws.sa, nullptr, nullptr, ws.row_start, ws.seq_len, nullptr, nullptr, w.c_qkv};
             const ResidualSrc fold_kv = {nullptr, nullptr, ws.sa, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, w.c_qkv + H};
             if (fused) {
-                const SkinnyArgs q = skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H, H, stats_in ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN, nullptr);
+                const SkinnyArgs q = skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H, stats_in ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN, nullptr);
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_KV, small(x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv, qk,
                                                                            2 * H, H, qkv_rows, stats_in, ws.sa), &q, s));
             } else {
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_KV, x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv,
                                                        qk, vt, ws.max_rows, 2 * H, H, H, qkv_rows, clk, s));
                 if (skinny) {
-                    PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_Q_MAPPED, skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H, H,
+                    PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_Q_MAPPED, skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H,
                                                                                               SKINNY_STATS_GIVEN, nullptr), s));
                 } else {
                     PS_TIMED(PS_FAM_REFINE, launch_cls_rows(m, n_req, ws, x, (bf16_t*)ws.cls_a, s));
@@ -128,17 +127,17 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
         PS_TIMED(PS_FAM_ATTENTION, launch_attention_bf16(m, n_req, ws, last, s));
         // Output projection of all rows, and again for each request's first row from the hi | lo pairs the attention
         // kernel left in cls_a.  The feed-forward block again for those rows, the ones the head reads, with its input and
-        // its GELU output carried as two bf16 values per element (contraction length doubled, weights repeated): bf16
+        // its GELU output carried as two bf16 values per element: bf16
         // rounding of these two tensors is the dominant error of the prediction and acts row by row, so the pass
         // removes it where it matters at < 1 % of the block's cost.
         const ResidualSrc in_cls = {x, ws.la, ws.sa, sg, sbeta, ws.row_start, ws.seq_len, x1, ps, nullptr};
         const ResidualSrc ffn_cls = {x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, ws.row_start, ws.seq_len, nullptr, nullptr, nullptr};
         if (skinny) {
-            const SkinnyArgs so = skinny_args(ws.cls_a, w.w_o, w.b_o, in_cls, ws.lb, H, H, H, 0, nullptr);
-            const SkinnyArgs s1 = skinny_args(nullptr, w.w_1d, w.b_1, ffn_cls, ws.cls_g, F, H, 2 * H,
+            const SkinnyArgs so = skinny_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H, 0, nullptr);
+            const SkinnyArgs s1 = skinny_args(nullptr, w.w_1d, w.b_1, ffn_cls, ws.cls_g, F, H,
                                               last ? SKINNY_STATS_ROWS : fused ? SKINNY_STATS_PIECES : SKINNY_STATS_GIVEN,
                                               last ? ws.sb : nullptr);
-            const SkinnyArgs s2 = skinny_args(ws.cls_g, w.w_2, w.b_2, mid_cls, ws.la, H, F, F, 0, nullptr);
+            const SkinnyArgs s2 = skinny_args(ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F, 0, nullptr);
             if (fused && !last) {
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(att, w.w_o, w.b_o, in, ws.lb, H, H, rows, nullptr, nullptr), &so, s));
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_GELU, small(x1, w.w_1, w.d_1, fold_1, g, F, H, rows, ws.ps, ws.sb), &s1, s));
@@ -162,7 +161,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
             if (!last)
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
                                                        nullptr, ws.max_rows, H, H, H, rows, clk, s));
-            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, 2 * H));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H));
             if (!last) {
                 PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
@@ -173,8 +172,8 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x1, ws.lb, ws.sb, s));
             }
             PS_TIMED(PS_FAM_REFINE, launch_cls_gather(m, n_req, ws, x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, s));
-            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, 2 * H));
-            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, 2 * F));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
+            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F));
         }
         if (!last && !fused)                             // (the head makes the last LayerNorm's statistics itself)
             PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sa, m->ln_eps, H, ws.max_rows, rows, s));

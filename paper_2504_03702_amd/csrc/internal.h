@@ -23,7 +23,7 @@ typedef uint16_t bf16_t;   // raw bf16 bit pattern
 // (the contraction index contiguous) for the MFMA kernels; fp32 models: float, [in][out].
 struct LayerWeights {
     void *w_qkv, *w_o, *w_1, *w_2;
-    void *w_od, *w_1d, *w_2d;    // bf16 models: W_o, W_1, W_2 with the contraction index repeated ([out][2 in])
+    void *w_od, *w_1d, *w_2d;    // bf16 models: the plain W_o, W_1, W_2 of the per-request pass (w_1 has a LayerNorm folded in)
     float *b_qkv, *b_o, *b_1, *b_2;
     // bf16 models: the LayerNorm in front of the QKV and the first feed-forward map is folded into them.
     // With x = (y - mean) * rstd * gamma + beta:  x W + b = rstd * (y (gamma W) - mean * c) + d,
@@ -144,7 +144,7 @@ struct SkinnyArgs {
     const float* bias;
     ResidualSrc res;
     void* C;
-    int N, K, ldw, hidden, n_req;
+    int N, K, hidden, n_req;
     // EPI_GELU_SPLIT, EPI_Q_MAPPED: where the first rows' LayerNorm statistics come from: res.stats, the 64-column
     // pieces in pstats_in, or two passes over the rows; stats_out (may be null) gets them
     int stats_from;

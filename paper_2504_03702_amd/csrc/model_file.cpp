@@ -217,35 +217,27 @@ int ps_build_model_image(const uint8_t* raw, size_t raw_bytes, ModelImage* out) 
                 }
                 return at;
             };
-            auto put_doubled = [&](size_t src_at, int64_t K, int64_t N) {   // [N][K] -> [N][2K], each row twice
-                if (info.dtype != 1) return (size_t)0;
-                size_t at = c.take((size_t)2 * K * N * 2);
-                if (pass) {
-                    const bf16_t* src = (const bf16_t*)(stage.data() + src_at);
-                    bf16_t* dst = (bf16_t*)(stage.data() + at);
-                    for (int64_t n = 0; n < N; ++n) {
-                        memcpy(dst + n * 2 * K, src + n * K, (size_t)K * 2);
-                        memcpy(dst + n * 2 * K + K, src + n * K, (size_t)K * 2);
-                    }
-                }
-                return at;
-            };
             t.wo = put_matrix(H, H);
-            t.wod = put_doubled(t.wo, H, H);
+            t.wod = t.wo;
             t.bo = put_f32(H);
             t.g1 = put_f32(H);
             t.be1 = put_f32(H);
             t.w1 = put_matrix(H, F);
-            t.w1d = put_doubled(t.w1, H, F);
+            t.w1d = t.w1;
+            if (info.dtype == 1) {
+                // the per-request pass reads W_1 as it is, without the LayerNorm that is folded into the other copy below
+                t.w1d = c.take((size_t)H * F * 2);
+                if (pass) memcpy(stage.data() + t.w1d, stage.data() + t.w1, (size_t)H * F * 2);
+            }
             t.b1 = put_f32(F);
             if (info.dtype == 1) {
-                // the first LayerNorm goes into W_1 (after the plain copy for the first-row pass was taken)
+                // the first LayerNorm goes into W_1 (after the plain copy for the per-request pass was taken)
                 t.c1 = c.take((size_t)F * 4);
                 t.d1 = c.take((size_t)F * 4);
                 if (pass) fold_layernorm(t.w1, F, H, t.g1, t.be1, t.b1, t.c1, t.d1);
             }
             t.w2 = put_matrix(F, H);
-            t.w2d = put_doubled(t.w2, F, H);
+            t.w2d = t.w2;
             t.b2 = put_f32(H);
             t.g2 = put_f32(H);
             t.be2 = put_f32(H);

@@ -59,8 +59,7 @@ struct SkinnyPieces {
 };
 
 // One block of 64 output columns by NW wavefronts; smem: kSkinnyLds bytes.  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED
-// take hi | lo rows (each W fragment serves two MFMAs; W's rows are read over their first K columns only, row stride
-// ldw).  GATHER: the rows of A are taken from the stream itself, at each request's first row: for EPI_Q_MAPPED the hi
+// take hi | lo rows (each W fragment serves two MFMAs).  GATHER: the rows of A are taken from the stream itself, at each request's first row: for EPI_Q_MAPPED the hi
 // parts, for EPI_GELU_SPLIT the LayerNorm of hi + lo, split again.
 template <int EPI, int NW, bool GATHER>
 __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem) {
@@ -68,7 +67,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     constexpr bool NORM = GATHER && EPI == EPI_GELU_SPLIT;
     constexpr int SH = kSkinnyShares / NW;
     const ResidualSrc& res = p.res;
-    const int N = p.N, K = p.K, ldw = p.ldw;
+    const int N = p.N, K = p.K;
     sk_f32x4(*s_part)[4][64] = (sk_f32x4(*)[4][64])smem;    // [share][column group][lane]: 16 rows x 16 columns each
     sk_f32x4(*s_sum)[64] = (sk_f32x4(*)[64])(smem + kSkinnyShares * 4 * 64 * 16);
     float2* s_st = (float2*)(smem + (kSkinnyShares + 1) * 4 * 64 * 16);
@@ -140,7 +139,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     // row, the four lanes of a row one whole 128-byte line ----------------------------------------------------
     const int total_rounds = K / 64;                    // dealt to the shares as evenly as whole rounds allow
     const int lda = DUAL && !NORM ? 2 * K : K;
-    const int64_t wg = (int64_t)16 * ldw;               // next column group: 16 rows of W further
+    const int64_t wg = (int64_t)16 * K;                 // next column group: 16 rows of W further
     const bool on = frow < n_req;
     constexpr int U = NORM ? 2 : DUAL ? 3 : 4;          // rounds whose loads are in flight together
     for (int sh = 0; sh < SH; ++sh) {
@@ -149,7 +148,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
         const int k0 = 64 * r_begin + 16 * fq;
         const bf16_t* ap = (NORM ? res.y_hi : p.A) + arow * lda + k0;
         const bf16_t* lp = NORM ? res.y_lo + arow * lda + k0 : ap + K;
-        const bf16_t* wp = p.W + (int64_t)(n0 + frow) * ldw + k0;
+        const bf16_t* wp = p.W + (int64_t)(n0 + frow) * K + k0;
         sk_f32x4 acc[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};

@@ -8,7 +8,7 @@
 // accumulation order over k is that of the larger tiles and the epilogues are the same expressions, so the results are
 // equal to theirs to the last bit and the choice between the kernels is free.
 //
-// Per-request maps of 64 requests (hidden 768 / 3072, hi | lo rows): 76 us a launch on the 128 x 128 tiles, 23 here.
+// Per-request maps of 64 requests (hidden 768 / 3072, hi | lo rows): 76 us a launch on the 128 x 128 tiles, 10.7 here.
 //
 // A launch can carry the layer's per-request side map (skinny_gemm.h) in further workgroups, and makes the row
 // statistics of its operand from the 64-column pieces in its prologue: with few rows a layer's time is made of
@@ -42,10 +42,14 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// TM, TN: 32 x 32 blocks of a wavefront; the four wavefronts' tile is 64 TM x 64 TN.
+// TM, TN: 32 x 32 blocks of a wavefront; the four wavefronts' tile is 64 TM x 64 TN.  The per-request maps whose operand
+// carries each value as hi + lo (columns [0, K) and [K, 2K) of a row) put a request's hi part in the tile's upper half
+// and its lo part in the lower: one slice of W serves both and the two results are added in the epilogue: half as many
+// steps as a contraction over 2K (64 requests of hidden 768: 23 -> 10.7 us a launch).
 template <int EPI, int TM, int TN, int STAGES, int SIDE>
 __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs side, int side_blocks) {
-    constexpr int BM = 64 * TM, BN = 64 * TN, NIT = 2 * TM;
+    constexpr bool DUAL = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED;
+    constexpr int BM = 64 * TM, BN = 64 * TN, ROWS = DUAL ? BM / 2 : BM, NIT = ROWS / 32;   // ROWS: of the result
     constexpr int kStage = (BM + BN) * 128;   // a 64-deep slice: the rows of A, then those of W, 128 bytes each
     constexpr int kOutLd = BN + 8;            // floats per row of the staged tile (spreads the half-waves' writes)
     constexpr int NDMA = 2 * (TM + TN);       // DMAs of a wavefront per slice
@@ -66,27 +70,32 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
     // ---- tile: XCD x (workgroups x, x + 8, ...) takes a contiguous run, row tiles fastest: a column of W is read
     // by one or two XCDs, the few rows of A by all of them
     const int rows = *p.rows;
-    const int m_tiles = (rows + BM - 1) / BM, tiles = m_tiles * (N / BN);
+    const int m_tiles = (rows + ROWS - 1) / ROWS, tiles = m_tiles * (N / BN);
     const int b = blockIdx.x - side_blocks, per_xcd = (tiles + 7) >> 3, slot = b >> 3;
     const int tile = (b & 7) * per_xcd + slot;
     if (slot >= per_xcd || tile >= tiles) return;
     const int tn = tile / m_tiles, tm = tile - tn * m_tiles;
-    const int m0 = tm * BM, n0 = tn * BN;
+    const int m0 = tm * ROWS, n0 = tn * BN;
 
     // ---- slices: DMA j of wavefront w brings rows 8 (4 j + w) .. + 7 of the slice's (A's, then W's) ------------
-    const unsigned lane_off = (unsigned)((lane >> 3) * K + (((lane & 7) ^ (lane >> 3) ^ (wave & 1)) * 8)) * 2u;
+    const int lda = DUAL ? 2 * K : K;
+    const unsigned chunk = (unsigned)((lane & 7) ^ (lane >> 3) ^ (wave & 1)) * 16u;
+    const unsigned a_off = (unsigned)((lane >> 3) * lda) * 2u + chunk, w_off = (unsigned)((lane >> 3) * K) * 2u + chunk;
     const unsigned char* src[NDMA];
 #pragma unroll
-    for (int j = 0; j < NDMA; ++j)
-        src[j] = (const unsigned char*)(j < 2 * TM ? p.A + (int64_t)(m0 + 8 * (4 * j + wave)) * K
-                                                   : p.W + (int64_t)(n0 + 8 * (4 * (j - 2 * TM) + wave)) * K);
+    for (int j = 0; j < NDMA; ++j) {
+        const int r = 8 * (4 * (j < 2 * TM ? j : j - 2 * TM) + wave);
+        const bool lo = DUAL && r >= ROWS;
+        src[j] = (const unsigned char*)(j < 2 * TM ? p.A + (int64_t)(m0 + r - (lo ? ROWS : 0)) * lda + (lo ? K : 0)
+                                                   : p.W + (int64_t)(n0 + r) * K);
+    }
     int wr = 0;                                          // stage of the next slice to bring
     auto dma = [&](int kt) {
         unsigned char* at = smem + wr * kStage;
         wr = wr + 1 == STAGES ? 0 : wr + 1;
 #pragma unroll
         for (int j = 0; j < NDMA; ++j)
-            __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(src[j] + (int64_t)kt * 128 + lane_off),
+            __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(src[j] + (int64_t)kt * 128 + (j < 2 * TM ? a_off : w_off)),
                                              (LDS_AS void*)(at + (4 * j + wave) * 1024), 16, 0, 0);
     };
     const int nk = K / 64;
@@ -257,6 +266,11 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
         for (int it = 0; it < NIT; ++it) {
             float a[8], v[8];
             load8(out + (r0 + 32 * it) * kOutLd + 64 * pc + 8 * cg, a);
+            if (DUAL) {
+                load8(out + (ROWS + r0 + 32 * it) * kOutLd + 64 * pc + 8 * cg, v);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) a[t] += v[t];
+            }
             if (RESID) {
                 const uint32_t hw[4] = {yh[pc][it].x, yh[pc][it].y, yh[pc][it].z, yh[pc][it].w}, lw[4] = {yl[pc][it].x, yl[pc][it].y, yl[pc][it].z, yl[pc][it].w};
 #pragma unroll
@@ -317,7 +331,8 @@ template <int EPI, int SIDE>
 void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     const int side_blocks = side ? (int)align_up((size_t)(side->N / kSkinnyCols), 8) : 0;
     const SkinnyArgs sd = side ? *side : SkinnyArgs{};
-    auto tiles = [&](int bm, int bn) { return (p.max_rows + bm - 1) / bm * (p.N / bn); };
+    constexpr int kParts = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED ? 2 : 1;   // rows of the tile per row of the result
+    auto tiles = [&](int bm, int bn) { return (p.max_rows * kParts + bm - 1) / bm * (p.N / bn); };
     auto grid = [&](int bm, int bn) { return dim3((unsigned)(side_blocks + (tiles(bm, bn) + 7) / 8 * 8)); };
 #define PS_SMALL(TM, TN, STAGES) \
     hipLaunchKernelGGL((small_gemm_kernel<EPI, TM, TN, STAGES, SIDE>), grid(64 * TM, 64 * TN), dim3(256), 0, s, p, sd, side_blocks)
@@ -344,7 +359,7 @@ void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
 }  // namespace
 
 // Requirements: N % 64 == 0, K % 128 == 0; every buffer holds max_rows rows with max_rows % 64 == 0 (whole tiles are
-// in bounds).  The side map, where there is one: EPI_RESIDUAL_MAPPED beside EPI_BIAS_RESIDUAL, EPI_GELU_SPLIT beside
+// in bounds).  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED take A as [rows][2K] (hi | lo).  The side map, where there is one: EPI_RESIDUAL_MAPPED beside EPI_BIAS_RESIDUAL, EPI_GELU_SPLIT beside
 // EPI_BIAS_GELU, EPI_Q_MAPPED beside EPI_KV.
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     switch (epi) {
