@@ -8,36 +8,82 @@
 
 namespace {
 
-// Row statistics from the partial sums the residual epilogues leave: 16 lanes per row, lane p taking
-// the pieces p, p + 16, ...; the 16 partial results are added in a fixed order.  Biased variance as
-// E[v^2] - mean^2 (the rows are residual-stream sums, whose mean is small against their spread).
-__global__ __launch_bounds__(256) void ln_stats_kernel(const float2* __restrict__ pstats, float2* __restrict__ stats,
-                                                       int pieces, float inv_n, float eps,
-                                                       const int32_t* __restrict__ total_rows) {
-    const int p = threadIdx.x & 15;
-    const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    if (row >= *total_rows) return;                     // whole 16-lane groups leave together
+// The sum of 16 consecutive lanes, in every one of them; fixed order.
+__device__ __forceinline__ float lanes16_sum(float v) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 16);
+    return v;
+}
+
+// Statistics of one row from the partial sums the residual epilogues leave, by 16 lanes: lane p takes the pieces p,
+// p + 16, ...; the 16 partial results are added in a fixed order.  Biased variance as E[v^2] - mean^2 (the rows are
+// residual-stream sums, whose mean is small against their spread).
+__device__ __forceinline__ float2 piece_stats(const float2* __restrict__ row, int pieces, int p, float inv_n, float eps) {
     float sm = 0.f, sq = 0.f;
     for (int c = p; c < pieces; c += 16) {
-        const float2 v = pstats[row * pieces + c];
+        const float2 v = row[c];
         sm += v.x;
         sq += v.y;
     }
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-        sm += __shfl_xor(sm, o, 16);
-        sq += __shfl_xor(sq, o, 16);
+    sm = lanes16_sum(sm);
+    sq = lanes16_sum(sq);
+    return ln_moments(sm, sq, inv_n, eps);
+}
+
+// Two things the maps after a residual one need, in one launch (they depend on the same sums, and in small calls a
+// launch is what they cost: 5 + 7 us apart).  The first gather_blocks workgroups, a wavefront per request, make the
+// operand of the per-request feed-forward map: row r is the fp32 LayerNorm of request r's first row of the stream, split
+// into two bf16 values per element (x ~ hi + lo, |x - hi - lo| <= 2^-17 |x|), hi in columns [0, H), lo in [H, 2H); zeros
+// for faulty requests and padding rows.  The others, 16 lanes per row, make the row statistics of the stream.
+// TWO_PASS (the last layer, where the epilogues leave no pieces): a first row's statistics from the row itself, and they
+// are left in stats.
+template <bool TWO_PASS>
+__global__ __launch_bounds__(256) void ln_stats_gather_kernel(const float2* __restrict__ pstats, float2* __restrict__ stats,
+                                                              int H, float inv_n, float eps,
+                                                              const int32_t* __restrict__ total_rows, int gather_blocks,
+                                                              const bf16_t* __restrict__ y_hi, const bf16_t* __restrict__ y_lo,
+                                                              const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                              int n_req, const int32_t* __restrict__ seq_len,
+                                                              const int32_t* __restrict__ row_start, bf16_t* __restrict__ out) {
+    const int pieces = H >> 6, lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= gather_blocks) {
+        const int64_t row = (int64_t)(blockIdx.x - gather_blocks) * 16 + (threadIdx.x >> 4);
+        if (row >= *total_rows) return;                 // whole 16-lane groups leave together
+        const float2 st = piece_stats(pstats + row * pieces, pieces, lane & 15, inv_n, eps);
+        if ((lane & 15) == 0) stats[row] = st;
+        return;
     }
-    if (p == 0) stats[row] = ln_moments(sm, sq, inv_n, eps);
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    uint2* oh = (uint2*)(out + (int64_t)r * 2 * H);
+    uint2* ol = oh + H / 4;
+    if (r >= n_req || seq_len[r] <= 0) {
+        for (int i = lane; i < H / 4; i += 64) oh[i] = ol[i] = make_uint2(0u, 0u);
+        return;
+    }
+    const int64_t row = row_start[r];
+    float2 st;
+    if (TWO_PASS) {
+        st = row_moments(y_hi + row * H, y_lo + row * H, H, eps, lane);
+        if (lane == 0) stats[row] = st;
+    } else {
+        st = piece_stats(pstats + row * pieces, pieces, lane & 15, inv_n, eps);
+    }
+    const uint2 *yh = (const uint2*)(y_hi + row * H), *yl = (const uint2*)(y_lo + row * H);
+    for (int i = lane; i < H / 4; i += 64) {
+        const uint2 h = yh[i], l = yl[i];
+        const float4 g = ((const float4*)gamma)[i], b = ((const float4*)beta)[i];
+        const float x0 = ln_apply(__uint_as_float(h.x << 16), __uint_as_float(l.x << 16), st, g.x, b.x);
+        const float x1 = ln_apply(__uint_as_float(h.x & 0xffff0000u), __uint_as_float(l.x & 0xffff0000u), st, g.y, b.y);
+        const float x2 = ln_apply(__uint_as_float(h.y << 16), __uint_as_float(l.y << 16), st, g.z, b.z);
+        const float x3 = ln_apply(__uint_as_float(h.y & 0xffff0000u), __uint_as_float(l.y & 0xffff0000u), st, g.w, b.w);
+        const uint2 o = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+        oh[i] = o;
+        ol[i] = make_uint2(pack_bf16x2(x0 - __uint_as_float(o.x << 16), x1 - __uint_as_float(o.x & 0xffff0000u)),
+                           pack_bf16x2(x2 - __uint_as_float(o.y << 16), x3 - __uint_as_float(o.y & 0xffff0000u)));
+    }
 }
 
 }  // namespace
-
-void launch_ln_stats(const float2* pstats, float2* stats, float eps, int hidden, int64_t max_rows,
-                     const int32_t* total_rows, hipStream_t s) {
-    hipLaunchKernelGGL(ln_stats_kernel, dim3((unsigned)(max_rows / 16)), dim3(256), 0, s, pstats, stats, hidden / 64,
-                       1.0f / (float)hidden, eps, total_rows);
-}
 
 // Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
 // Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
@@ -56,6 +102,19 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     int64_t* clk = m->profiling ? m->clk_slot : nullptr;   // clock probe of the large GEMMs
     // the stream entering layer 0 is the embedding LayerNorm of the sums the embed kernel left in (x, la)
     const float *sg = m->lne_g, *sbeta = m->lne_b;
+    // row statistics of the stream (`rows_too`), and the per-request feed-forward operand (`res`, if not null)
+    auto ln_stats = [&](float2* stats, bool rows_too, const ResidualSrc* res) {
+        const unsigned gather = res ? (unsigned)(ws.cls_rows / 4) : 0, blocks = gather + (rows_too ? (unsigned)(ws.max_rows / 16) : 0);
+        const ResidualSrc q = res ? *res : none;
+        if (rows_too)
+            hipLaunchKernelGGL(ln_stats_gather_kernel<false>, dim3(blocks), dim3(256), 0, s, ws.ps, stats, H, 1.0f / (float)H,
+                               m->ln_eps, rows, (int)gather, q.y_hi, q.y_lo, q.gamma, q.beta, n_req, ws.seq_len, ws.row_start,
+                               (bf16_t*)ws.cls_a);
+        else
+            hipLaunchKernelGGL(ln_stats_gather_kernel<true>, dim3(blocks), dim3(256), 0, s, ws.ps, stats, H, 1.0f / (float)H,
+                               m->ln_eps, rows, (int)gather, q.y_hi, q.y_lo, q.gamma, q.beta, n_req, ws.seq_len, ws.row_start,
+                               (bf16_t*)ws.cls_a);
+    };
 #define PS_TIMED(FAM, CALL) do { ProfScope p_(m, FAM, s); CALL; } while (0)
     // the per-request side maps of calls of more than 16 requests
     auto side_gemm = [&](GemmEpilogue epi, const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C,
@@ -148,7 +207,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                                                            nullptr, ws.max_rows, H, H, H, rows, clk, s));
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
                 if (!last) {
-                    PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
+                    PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, nullptr));
                     PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
                                                            ws.max_rows, F, H, H, rows, clk, s));
                     PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
@@ -162,21 +221,18 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
                                                        nullptr, ws.max_rows, H, H, H, rows, clk, s));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H));
+            PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, !last, &ffn_cls));
             if (!last) {
-                PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sb, m->ln_eps, H, ws.max_rows, rows, s));
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
                                                        ws.max_rows, F, H, H, rows, clk, s));
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
                                                        nullptr, ws.max_rows, H, F, H, rows, clk, s));
-            } else {
-                PS_TIMED(PS_FAM_LAYERNORM, launch_cls_stats(m, n_req, ws, x1, ws.lb, ws.sb, s));
             }
-            PS_TIMED(PS_FAM_REFINE, launch_cls_gather(m, n_req, ws, x1, ws.lb, ws.sb, w.ln1_g, w.ln1_b, s));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F));
         }
         if (!last && !fused)                             // (the head makes the last LayerNorm's statistics itself)
-            PS_TIMED(PS_FAM_LAYERNORM, launch_ln_stats(ws.ps, ws.sa, m->ln_eps, H, ws.max_rows, rows, s));
+            PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sa, true, nullptr));
         sg = w.ln2_g;
         sbeta = w.ln2_b;
     }

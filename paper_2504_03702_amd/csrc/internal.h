@@ -174,20 +174,11 @@ struct SmallGemm {
     const int32_t *row_start, *seq_len;
 };
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
-void launch_cls_gather(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* y_hi, const bf16_t* y_lo,
-                       const float2* stats, const float* gamma, const float* beta, hipStream_t s);
 // out[r][0:hidden] = x[first row of request r] for every request (zeros for faulty ones and padding rows).
 void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* x, bf16_t* out, hipStream_t s);
-// stats[first row of request r] = LayerNorm statistics of that row of the sums hi + lo, for every request.
-void launch_cls_stats(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* y_hi, const bf16_t* y_lo,
-                      float2* stats, hipStream_t s);
 // first_rows_only: compute (at least) the first query row of every request and nothing beyond its
 // first 32 rows; the rest of the output buffer keeps its old contents.
 void launch_attention_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, bool first_rows_only, hipStream_t s);
-// stats[row] = (mean, 1/std) of every live row from the partial sums the residual epilogues left.
-void launch_ln_stats(const float2* pstats, float2* stats, float eps, int hidden, int64_t max_rows,
-                     const int32_t* total_rows, hipStream_t s);
-
 // Brackets the launches made during its lifetime with two events when profiling is on.
 struct ProfScope {
     const ps_model* m;

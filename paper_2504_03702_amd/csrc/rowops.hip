@@ -385,46 +385,6 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
     }
 }
 
-// Gather for the [CLS] refinement: row r of the side matrix is the fp32 LayerNorm output of request
-// r's first row, split into two bf16 values per element (x ~ hi + lo, |x - hi - lo| <= 2^-17 |x|),
-// hi in columns [0, H), lo in [H, 2H).  Rows of faulty requests and padding rows are zero.
-__global__ __launch_bounds__(256) void cls_gather_kernel(const bf16_t* __restrict__ y_hi, const bf16_t* __restrict__ y_lo,
-                                                         const float2* __restrict__ stats,
-                                                         const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                         int H, int n_req, const int32_t* __restrict__ seq_len,
-                                                         const int32_t* __restrict__ row_start, bf16_t* __restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    bf16_t* o = out + (int64_t)r * 2 * H;
-    if (r >= n_req || seq_len[r] <= 0) {
-        for (int i = lane; i < 2 * H; i += 64) o[i] = 0;
-        return;
-    }
-    const int64_t row = row_start[r];
-    const float2 st = stats[row];
-    for (int i = lane; i < H; i += 64) {
-        const float x = ln_apply(bf16_to_f32(y_hi[row * H + i]), bf16_to_f32(y_lo[row * H + i]), st, gamma[i], beta[i]);
-        const bf16_t hi = f32_to_bf16(x);
-        o[i] = hi;
-        o[H + i] = f32_to_bf16(x - bf16_to_f32(hi));
-    }
-}
-
-// LayerNorm statistics (mean, 1 / std; biased variance) of each request's first row of the sums hi + lo:
-// one wavefront per request.  Used where only those rows go on (the last layer), in place of the
-// LayerNorm over all rows.
-__global__ __launch_bounds__(256) void cls_stats_kernel(const bf16_t* __restrict__ y_hi, const bf16_t* __restrict__ y_lo,
-                                                        float2* __restrict__ stats, float eps,
-                                                        int H, int n_req, const int32_t* __restrict__ seq_len,
-                                                        const int32_t* __restrict__ row_start) {
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= n_req || seq_len[r] <= 0) return;
-    const int64_t row = row_start[r];
-    const float2 v = row_moments(y_hi + row * H, y_lo + row * H, H, eps, lane);
-    if (lane == 0) stats[row] = v;
-}
-
 // The bf16 input rows of each request's first token, one per request, for the side GEMM that computes
 // only those rows' queries (last layer).  Rows of faulty requests and padding rows are zero.
 __global__ __launch_bounds__(256) void cls_rows_kernel(const bf16_t* __restrict__ x, int H, int n_req,
@@ -443,18 +403,6 @@ __global__ __launch_bounds__(256) void cls_rows_kernel(const bf16_t* __restrict_
 void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* x, bf16_t* out, hipStream_t s) {
     hipLaunchKernelGGL(cls_rows_kernel, dim3((unsigned)(ws.cls_rows / 4)), dim3(256), 0, s, x, m->info.hidden, n_req,
                        ws.seq_len, ws.row_start, out);
-}
-
-void launch_cls_stats(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* y_hi, const bf16_t* y_lo,
-                      float2* stats, hipStream_t s) {
-    hipLaunchKernelGGL(cls_stats_kernel, dim3((unsigned)(ws.cls_rows / 4)), dim3(256), 0, s, y_hi, y_lo, stats, m->ln_eps,
-                       m->info.hidden, n_req, ws.seq_len, ws.row_start);
-}
-
-void launch_cls_gather(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* y_hi, const bf16_t* y_lo,
-                       const float2* stats, const float* gamma, const float* beta, hipStream_t s) {
-    hipLaunchKernelGGL(cls_gather_kernel, dim3((unsigned)(ws.cls_rows / 4)), dim3(256), 0, s, y_hi, y_lo, stats, gamma, beta,
-                       m->info.hidden, n_req, ws.seq_len, ws.row_start, (bf16_t*)ws.cls_a);
 }
 
 void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengths, int32_t n_req, int64_t n_tokens,
