@@ -131,12 +131,13 @@ size_t ps_anticipate_workspace_bytes(int64_t n_req, int32_t n_inst, int32_t hori
  *             is persistent, the caller zeroes it to start afresh.
  *   overflow  [n_inst] int64, accumulated: tokens that fall at or after `horizon`.  May be NULL
  *             only if rate == NULL (nothing can overflow then).
- *   Records may come in any order and the result does not depend on it.  Long streams (262144 records
+ *   Records may come in any order and the result does not depend on it.  Calls of at most 16384 records (with
+ *   n_req * n_inst <= 2^23, horizon <= 16000) are folded by a workgroup per instance in one launch.  Long streams (262144 records
  *   or more, rate given, horizon <= 4096) whose records are in arrival order (non-decreasing
  *   arrival_bucket, as in a request log) are folded by a cheaper kernel; if a record turns out to lie
  *   outside the bucket window of its part of the stream, the general kernel redoes the call.
  *   workspace at least ps_anticipate_workspace_bytes(n_req, n_inst, horizon) bytes, 256-byte
- *             aligned.
+ *             aligned (required of every call, whichever kernels it takes).
  *   status    device ps_status or NULL.  Faulty records are skipped (PS_ST_BAD_RECORD).
  * Integer arithmetic throughout: the result does not depend on record order and is bit-exact.
  * pred_tokens, instance_id and arrival_bucket must be 16-byte aligned (PS_EINVAL otherwise).
@@ -188,9 +189,10 @@ int ps_anticipate_static(const int32_t* pred_tokens, const int32_t* instance_id,
  *              i_end > PS_MAX_ITER or sign not +1 / -1 is skipped (PS_ST_BAD_RECORD); a slot that
  *              leaves the int32 range keeps its low 32 bits (PS_ST_RANGE).
  * Integer arithmetic throughout: the result does not depend on record order and is bit-exact, however many
- * records start or end in one slot (lists of 65536 records or more over maps of at most 12800 slots and 4096
- * instances are binned by instance and folded in LDS with wide counters; other calls use packed global counters
- * and are folded in parts of 2^22 records, within which no intermediate sum can leave its field).
+ * records start or end in one slot (lists of at most 16384 records are folded by a workgroup per instance in LDS, where
+ * n_rec * n_inst <= 2^23 and the map has at most 19200 slots; lists of 65536 records or more over maps of at most 12800
+ * slots and 4096 instances are binned by instance and folded in LDS with wide counters; other calls use packed global
+ * counters and are folded in parts of 2^22 records, within which no intermediate sum can leave its field).
  * n_rec == 0 is allowed (with `fraction` it recomputes the fractions of the map as it stands).
  * Errors: PS_EINVAL, PS_EWORKSPACE, PS_EUNSUPPORTED (map_len above PS_MAX_ITER + 1), PS_EHIP. */
 #define PS_MAX_ITER  65535       /* largest i_end ps_lookahead_update accepts                 */
