@@ -183,7 +183,9 @@ int ps_anticipate_static(const int32_t* pred_tokens, const int32_t* instance_id,
  *   fraction   [n_inst * map_len] float or NULL, out: kv_tokens / capacity after the update (NaN for
  *              an instance whose capacity is < 1)
  *   workspace  device scratch of at least ps_lookahead_workspace_bytes(n_rec, n_inst, map_len) bytes,
- *              256-byte aligned; contents undefined before and after
+ *              256-byte aligned; contents undefined before and after.  For long lists over
+ *              fewer than 129 instances the query asks for more, which makes them faster; what it asks for with
+ *              more instances (up to 4096; same records and map_len) serves as well.
  *   status     device ps_status or NULL.  A record with instance outside [0, n_inst), start_iter
  *              outside [0, map_len), prompt_tokens outside [0, PS_MAX_PROMPT), i_begin < 0, i_end < i_begin,
  *              i_end > PS_MAX_ITER or sign not +1 / -1 is skipped (PS_ST_BAD_RECORD); a slot that

@@ -499,47 +499,50 @@ __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     else scan_lds_row<false, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
 }
 
-// Layout of the workspace: the difference array of the atomic route, then the binned route's entries and table.
+// Layout of the workspace.  Atomic route: the difference array.  Binned route: entries, table, and from there to the end
+// of what the caller handed over the rows of the workgroups that share an instance's entries.  A call needs
+// `need_bytes` (difference array, entries and table: more instances never need less, so a workspace sized for a cluster
+// also serves it once it is scaled down); the query's `full_bytes` has room for all the sharing that pays, and a call
+// with less room shares less (consumers_in).
 struct LookaheadPlan {
     bool binned;                 // the call qualifies for the binned route
-    size_t diff_bytes, entries_at, entries_bytes, table_at, table_bytes, partial_at, total_bytes;
-    int consumers;               // binned: workgroups that share an instance's entries
+    size_t table_at, partial_at, row_bytes, need_bytes, full_bytes;
+    int64_t diff_bytes;
+    int consumers;               // binned: workgroups that share an instance's entries, given the room
     int64_t part;                // records per part of the route taken
+    int consumers_in(size_t workspace_bytes) const {
+        const size_t rows = (workspace_bytes - partial_at) / row_bytes;
+        return rows < (size_t)consumers ? (rows > 1 ? (int)rows : 1) : consumers;
+    }
 };
 
 LookaheadPlan plan_lookahead(int64_t n_rec, int n_inst, int map_len) {
     LookaheadPlan p;
-    p.diff_bytes = align_up((size_t)n_inst * (size_t)map_len * 8, 256);
+    p.row_bytes = (size_t)n_inst * (size_t)map_len * 8;          // a row of sums for every instance
+    p.diff_bytes = (int64_t)align_up(p.row_bytes, 256);
     p.binned = n_rec >= kBinMinRecords && n_inst <= kBinMaxInst && (int64_t)map_len * 12 <= kRowLdsBytes;
     p.part = p.binned ? kBinPart : (int64_t)1 << 22;
-    p.entries_at = p.diff_bytes;
-    p.entries_bytes = p.table_bytes = 0;
+    p.table_at = p.partial_at = 0;
+    p.consumers = 1;
     if (p.binned) {
         const int64_t most = n_rec < kBinPart ? n_rec : kBinPart;
         const int64_t chunks = (most + kBinChunk - 1) / kBinChunk;
-        p.entries_bytes = align_up((size_t)chunks * kBinChunk * 8, 256);
-        p.table_bytes = align_up((size_t)chunks * (size_t)(n_inst + 1) * 4, 256);
-    }
-    p.table_at = p.entries_at + p.entries_bytes;
-    p.partial_at = p.table_at + p.table_bytes;
-    p.total_bytes = p.partial_at;
-    p.consumers = 1;
-    if (p.binned) {
+        p.table_at = align_up((size_t)chunks * kBinChunk * 8, 256);
+        p.partial_at = p.table_at + align_up((size_t)chunks * (size_t)(n_inst + 1) * 4, 256);
         // few instances: enough workgroups to fill the chip, 8 chunks (65536 records) each at the least
-        const int64_t chunks = ((n_rec < kBinPart ? n_rec : kBinPart) + kBinChunk - 1) / kBinChunk;
-        const int64_t most = chunks / 8 < kConsumeWorkgroups / n_inst ? chunks / 8 : kConsumeWorkgroups / n_inst;
-        if (most > 1) {
-            p.consumers = (int)most;
-            p.total_bytes += align_up((size_t)p.consumers * n_inst * map_len * 8, 256);
-        }
+        const int64_t share = chunks / 8 < kConsumeWorkgroups / n_inst ? chunks / 8 : kConsumeWorkgroups / n_inst;
+        if (share > 1) p.consumers = (int)share;
     }
+    p.need_bytes = p.partial_at + (size_t)p.diff_bytes;
+    const size_t shared = p.partial_at + align_up(p.row_bytes * (size_t)p.consumers, 256);
+    p.full_bytes = shared > p.need_bytes ? shared : p.need_bytes;
     return p;
 }
 }  // namespace
 
 extern "C" size_t ps_lookahead_workspace_bytes(int64_t n_rec, int32_t n_inst, int32_t map_len) {
     if (n_rec < 0 || n_inst < 1 || map_len < 1 || map_len > PS_MAX_ITER + 1) return 0;
-    return plan_lookahead(n_rec, n_inst, map_len).total_bytes;
+    return plan_lookahead(n_rec, n_inst, map_len).full_bytes;
 }
 
 extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* start_iter,
@@ -553,11 +556,10 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
     if (n_rec > 0 && (!instance_id || !start_iter || !prompt_tokens || !i_begin || !i_end || !sign)) return PS_EINVAL;
     if (n_rec == 0 && !fraction) return PS_OK;
     const LookaheadPlan plan = plan_lookahead(n_rec, n_inst, map_len);
-    const size_t need = plan.total_bytes;
-    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return PS_EWORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < plan.need_bytes) return PS_EWORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
-    const int64_t n16 = (int64_t)(plan.diff_bytes / 16);
+    const int64_t n16 = plan.diff_bytes / 16;
     const unsigned clear_blocks = (unsigned)((n16 + 255) / 256 < 2048 ? (n16 + 255) / 256 : 2048);
     // rows of the map (and of the fractions) are whole, aligned 16-byte pieces
     const int vec_rows = (map_len & 3) == 0 && (((uintptr_t)kv_tokens | (uintptr_t)fraction) & 15) == 0;
@@ -586,8 +588,9 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
                 return PS_EHIP;
             lds_attr_set = true;
         }
-        unsigned long long* entries = (unsigned long long*)((uint8_t*)workspace + plan.entries_at);
+        unsigned long long* entries = (unsigned long long*)workspace;
         int32_t* table = (int32_t*)((uint8_t*)workspace + plan.table_at);
+        const int consumers = plan.consumers_in(workspace_bytes);
         const bool vec = (((uintptr_t)instance_id | (uintptr_t)start_iter | (uintptr_t)prompt_tokens | (uintptr_t)i_begin |
                            (uintptr_t)i_end | (uintptr_t)sign) & 15) == 0;       // (parts start at multiples of 2^26 records)
         for (int64_t at = 0; at < n_rec; at += plan.part) {
@@ -603,12 +606,12 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
                                    instance_id + at, start_iter + at, prompt_tokens + at, i_begin + at, i_end + at, sign + at,
                                    n_part, at, n_inst, map_len, entries, table, chunks, overflow, status);
             long long* partial = (long long*)((uint8_t*)workspace + plan.partial_at);
-            hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)((n_inst + 7) / 8 * 8 * plan.consumers)), dim3(1024), (size_t)map_len * 12, s,
+            hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)((n_inst + 7) / 8 * 8 * consumers)), dim3(1024), (size_t)map_len * 12, s,
                                entries, table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, vec_rows,
-                               plan.consumers, partial, status);
-            if (plan.consumers > 1)
+                               consumers, partial, status);
+            if (consumers > 1)
                 hipLaunchKernelGGL(lookahead_combine_kernel, dim3((unsigned)(((int64_t)n_inst * map_len + 255) / 256)), dim3(256), 0, s,
-                                   partial, plan.consumers, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, status);
+                                   partial, consumers, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, status);
         }
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }

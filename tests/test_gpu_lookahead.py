@@ -296,3 +296,24 @@ def test_few_instances_share_their_entries(n, K, L):
     ref_kv, ref_ovf, _, ref_bad = ol.lookahead_update(*cols, K, L, kv.copy())
     assert np.array_equal(got[0], ref_kv) and np.array_equal(got[1], ref_ovf) and got[4] == ref_bad == n // 2
     assert np.array_equal(got[2], ref_kv.astype(np.float32) / cap.astype(np.float32)[:, None])
+
+
+@pytest.mark.parametrize("n,sized_for,K,L", [(1_000_000, 256, 128, 4096), (1_000_000, 256, 1, 4096), (1_000_000, 129, 33, 700),
+                                             (600_011, 200, 100, 1021), (70_001, 4096, 20, 5)])
+def test_workspace_of_a_larger_cluster(n, sized_for, K, L):
+    """A cluster that is scaled down keeps its workspace: fewer instances with the size the query gave for more, whether
+    or not that has room for all the workgroups that would share an instance's entries."""
+    print(f"look-ahead workspace for {sized_for} instances, {K} there, n={n} L={L}", flush=True)
+    dev = "cuda:0"
+    rng = np.random.default_rng(n + K)
+    b = rng.integers(0, 300, n)
+    cols = [rng.integers(0, K, n), rng.integers(0, L, n), rng.integers(0, 3000, n), b, b + rng.integers(0, 2 * L + 2, n),
+            rng.choice([-1, 1], n)]
+    cols = [c.astype(np.int32) for c in cols]
+    ws = ps.alloc_workspace(ps.ps_lookahead_workspace_bytes(n, sized_for, L), dev)
+    ws.fill_(0xA5)
+    kv, ovf = torch.zeros(K * L, dtype=torch.int32, device=dev), torch.zeros(K, dtype=torch.int64, device=dev)
+    st = ps.new_status(dev)
+    ps.ps_lookahead_update(*[torch.from_numpy(c).to(dev) for c in cols], K, L, kv, ovf, ws, status=st)
+    ref_kv, ref_ovf, _, _ = ol.lookahead_update(*cols, K, L)
+    assert np.array_equal(kv.cpu().numpy().reshape(K, L), ref_kv) and np.array_equal(ovf.cpu().numpy(), ref_ovf)
