@@ -191,8 +191,8 @@ int ps_anticipate_static(const int32_t* pred_tokens, const int32_t* instance_id,
  *              i_end > PS_MAX_ITER or sign not +1 / -1 is skipped (PS_ST_BAD_RECORD); a slot that
  *              leaves the int32 range keeps its low 32 bits (PS_ST_RANGE).
  * Integer arithmetic throughout: the result does not depend on record order and is bit-exact, however many
- * records start or end in one slot (lists of at most 16384 records are folded by a workgroup per instance in LDS, where
- * n_rec * n_inst <= 2^23 and the map has at most 19200 slots; lists of 65536 records or more over maps of at most 12800
+ * records start or end in one slot (lists of at most 16384 records over a few hundred instances and maps of at most 19200
+ * slots are folded by a workgroup per instance in LDS; lists of 65536 records or more over maps of at most 12800
  * slots and 4096 instances are binned by instance and folded in LDS with wide counters; other calls use packed global
  * counters and are folded in parts of 2^22 records, within which no intermediate sum can leave its field).
  * n_rec == 0 is allowed (with `fraction` it recomputes the fractions of the map as it stands).

@@ -445,8 +445,27 @@ __global__ __launch_bounds__(256) void lookahead_combine_kernel(const long long*
 // ids a thread requested together), applies its own records to an LDS row as above and scans the row into the map.  The
 // atomic route clears, updates and reads back a map-sized difference array: 4096 records over 256 instances of 4096 slots
 // took it 20 us in three launches, 11.5 here.
+//
+// Where it pays (microseconds, atomic route / this one).  Every instance is a workgroup of 1024 threads that looks through
+// the list, so its time grows with instances beyond two a compute unit and with records times instances; the atomic
+// route's with the map it clears and scans:
+//   256 instances, 1024 / 4096 slots:      4096 records 16 / 12, 19 / 12;  16384 records 17 / 14, 19 / 15
+//   512 instances, 1024 slots:             4096 records 17 / 16,  8192 17 / 18,  16384 17 / 22
+//   640 to 768 instances, 1024 records:    1024 slots 17 / 19,  4096 slots 27 / 20,  12800 slots 52 / 52
+//   1024 and 2048 instances, 1024 records: 1024 slots 16 / 24 and 22 / 45,  4096 slots 30 / 26 and 44 / 50
+//   1536, 2048, 4096 instances x 19200, 12800, 8192 slots, 1024 records (the difference array is 200 MB and more):
+//                                          176 / 124, 178 / 132, 200 / 154
+//   8192 instances, 64 slots:              19 / 149
+//   8 instances, 16384 records (the lanes' own records come one by one, but the atomic route's collide in short rows):
+//                                          64 slots 65 / 27,  1024 slots 17 / 19,  12800 slots 32 / 28
 const int64_t kDirectMaxRecords = 16384;
-const int64_t kDirectMaxLooks = (int64_t)1 << 23;        // records * instances
+const int64_t kDirectMaxLooks = (int64_t)1 << 22;        // records * instances
+bool direct_pays(int64_t n_rec, int n_inst, int map_len) {
+    if (n_rec > kDirectMaxRecords || n_rec * n_inst > kDirectMaxLooks || (int64_t)map_len * 8 > kRowLdsBytes) return false;
+    if (n_rec > 8192 && n_inst < 64 && map_len >= 1024 && map_len < 8192) return false;
+    if (n_inst <= 512 || (n_inst <= 768 && map_len >= 4096)) return true;
+    return map_len >= 8192 && n_inst <= 65536 && (int64_t)n_inst * map_len >= 25000000;
+}
 __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     const int32_t* __restrict__ instance_id, const int32_t* __restrict__ start_iter,
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ i_begin,
@@ -563,7 +582,7 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
     const unsigned clear_blocks = (unsigned)((n16 + 255) / 256 < 2048 ? (n16 + 255) / 256 : 2048);
     // rows of the map (and of the fractions) are whole, aligned 16-byte pieces
     const int vec_rows = (map_len & 3) == 0 && (((uintptr_t)kv_tokens | (uintptr_t)fraction) & 15) == 0;
-    if (n_rec <= kDirectMaxRecords && n_rec * n_inst <= kDirectMaxLooks && (int64_t)map_len * 8 <= kRowLdsBytes) {
+    if (direct_pays(n_rec, n_inst, map_len)) {
         static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
         if (!lds_attr_set) {
             if (hipFuncSetAttribute((const void*)lookahead_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,

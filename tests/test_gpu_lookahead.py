@@ -256,10 +256,14 @@ def test_scaler_sizes_around_the_single_launch(K, L, window):
 
 
 @pytest.mark.parametrize("n,K,L", [(1, 1, 1), (7, 3, 5), (1024, 2, 4096), (8193, 5, 1023), (16384, 512, 64), (16385, 3, 300),
-                                   (16384, 513, 64), (5000, 4, 12800), (5000, 4, 12801)])
+                                   (16384, 513, 64), (5000, 4, 12800), (5000, 4, 12801), (5000, 4, 19200), (5000, 4, 19201),
+                                   (16384, 256, 64), (16384, 257, 64), (8192, 512, 64), (300, 513, 70), (300, 768, 4096),
+                                   (300, 769, 4096), (50, 3000, 8334), (50, 2999, 8334), (8193, 63, 1024), (8193, 64, 1024),
+                                   (8193, 63, 8192)])
 def test_short_lists_around_the_direct_route(n, K, L):
-    """List lengths around a thread's batch and the route's limits (16384 records, 2^23 records x instances, rows of
-    12800 slots), rows that are whole 16-byte pieces and not, faulty records, tokens past the map, a map in use."""
+    """List lengths around a thread's batch and the route's limits (16384 records, 2^22 records x instances, 512 and, for
+    4096 slots, 768 instances, maps of 25 M cells and more, rows of 19200 slots), rows that are whole 16-byte pieces and
+    not, faulty records, tokens past the map, a map in use."""
     print(f"look-ahead direct n={n} K={K} L={L}", flush=True)
     rng = np.random.default_rng(n + L)
     sign = rng.choice([-1, 1], n)
@@ -317,3 +321,19 @@ def test_workspace_of_a_larger_cluster(n, sized_for, K, L):
     ps.ps_lookahead_update(*[torch.from_numpy(c).to(dev) for c in cols], K, L, kv, ovf, ws, status=st)
     ref_kv, ref_ovf, _, _ = ol.lookahead_update(*cols, K, L)
     assert np.array_equal(kv.cpu().numpy().reshape(K, L), ref_kv) and np.array_equal(ovf.cpu().numpy(), ref_ovf)
+
+
+@pytest.mark.parametrize("n", [0, 1])
+def test_millions_of_instances(n):
+    """The fractions of 2^22 short maps are refreshed, and a record lands in the last of them."""
+    print(f"look-ahead 2^22 instances, {n} records", flush=True)
+    dev, K = "cuda:0", 1 << 22
+    kv = torch.arange(K, dtype=torch.int32, device=dev)
+    cap = torch.full((K,), 3, dtype=torch.int32, device=dev)
+    frac = torch.zeros(K, device=dev)
+    ws = ps.alloc_workspace(ps.ps_lookahead_workspace_bytes(n, K, 1), dev)
+    cols = [torch.tensor([v][:n], dtype=torch.int32, device=dev) for v in (K - 1, 0, 40, 0, 1, 1)]
+    ps.ps_lookahead_update(*cols, K, 1, kv, None, ws, cap, frac)
+    want = torch.arange(K, dtype=torch.int32, device=dev)
+    want[K - 1] += 40 * n
+    assert torch.equal(kv, want) and torch.equal(frac, want.float() / cap.float())
