@@ -252,8 +252,8 @@ __global__ __launch_bounds__(kBinThreads) void lookahead_bin_kernel(
 
 // The scan of an LDS row of differences into the caller's map by a workgroup of 1024 threads (the same arithmetic as
 // lookahead_scan_kernel); VEC: rows are whole 16-byte pieces; PACKED: s_off holds offset * 2^24 + slope words.
-// prow, if not null: the sums go there and the map is left alone.
-template <bool VEC, bool PACKED>
+// SHARED: the sums go to prow and the map is left alone.
+template <bool VEC, bool PACKED, bool SHARED>
 __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* s_slp, long long* s_w0, long long* s_w1, int k,
                                              int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
                                              float* __restrict__ fraction, long long* __restrict__ prow, ps_status* st) {
@@ -274,7 +274,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
             }
         } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) if (t + c < map_len && !prow) was[c] = out[t + c];
+            for (int c = 0; c < 4; ++c) if (!SHARED && t + c < map_len) was[c] = out[t + c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -309,7 +309,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const long long nv = (long long)was[c] + (before0 + a0[c]) + (long long)(t + c) * (before1 + a1[c]);
-            if (prow) {
+            if (SHARED) {
                 if (t + c < map_len) prow[t + c] = nv;
                 continue;
             }
@@ -325,7 +325,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (t + c < map_len && !prow) {
+                if (!SHARED && t + c < map_len) {
                     out[t + c] = now[c];
                     if (frow) frow[t + c] = part[c];
                 }
@@ -342,16 +342,19 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
 // caller's map.  Several: its scan is left in partial[part][instance][slot] for lookahead_combine_kernel.
 // What bounds it is the latency of the entries' loads (segments of 8192 / instances entries): eight segments of a
 // wavefront are requested before the first is applied (long segments: eight loads of one; sixteen of either were slower).
+// A kernel for each form of the scan: with all three in one its code doubled, and short lists over many instances, whose
+// time is the start and end of the workgroups, lost a fifth (65536 records, 4096 instances of 64 slots: 100 us, 88 so).
+template <bool VEC, bool SHARED>
 __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
-    const unsigned long long* __restrict__ entries, const int32_t* __restrict__ table, int64_t n_chunks, int n_inst,
+    const unsigned long long* __restrict__ entries, const int32_t* __restrict__ table, int n_chunks, int n_inst,
     int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity, float* __restrict__ fraction,
-    int vec, int parts, long long* __restrict__ partial, ps_status* st) {
+    int parts, long long* __restrict__ partial, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     long long* s_off = (long long*)lds_raw;                               // [map_len] offset differences
     int* s_slp = (int*)(s_off + map_len);                                 // [map_len] slope differences
     __shared__ long long s_w0[16], s_w1[16];
     // XCD x (workgroups x, x + 8, ...) takes a run of neighbouring instances: their segments share lines at both ends
-    const int per_xcd = (n_inst + 7) >> 3, in_part = blockIdx.x % (8 * per_xcd), part = blockIdx.x / (8 * per_xcd);
+    const int per_xcd = (n_inst + 7) >> 3, part = SHARED ? blockIdx.x / (8 * per_xcd) : 0, in_part = blockIdx.x - part * 8 * per_xcd;
     const int k = (in_part & 7) * per_xcd + (in_part >> 3);
     if (k >= n_inst) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -372,20 +375,21 @@ __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
     };
     constexpr int UC = 8;
     const bool long_segments = n_inst <= 32;                              // on average 256 entries or more
-    const int share = part * 16 + wave, shares = parts * 16;
-    const int64_t c_begin = n_chunks * share / shares, c_end = n_chunks * (share + 1) / shares;
-    for (int64_t c0 = c_begin; c0 < c_end; c0 += 64) {                    // the bounds of 64 chunks, one per lane
-        const int64_t mine = c0 + lane;
+    // (at most 8192 chunks a part, dealt to at most 256 x 16 wavefronts)
+    const int share = part * 16 + wave, shares = SHARED ? parts * 16 : 16;
+    const int c_begin = n_chunks * share / shares, c_end = n_chunks * (share + 1) / shares;
+    for (int c0 = c_begin; c0 < c_end; c0 += 64) {                        // the bounds of 64 chunks, one per lane
+        const int mine = c0 + lane;
         int seg_b = 0, seg_e = 0;
         if (mine < c_end) {
             seg_b = table[(int64_t)k * n_chunks + mine];
             seg_e = table[(int64_t)(k + 1) * n_chunks + mine];
         }
-        const int here = (int)min((int64_t)64, c_end - c0);
+        const int here = min(64, c_end - c0);
         if (long_segments) {
             for (int j = 0; j < here; ++j) {
                 const int b = __builtin_amdgcn_readlane(seg_b, j), e = __builtin_amdgcn_readlane(seg_e, j);
-                const unsigned long long* src = entries + (c0 + j) * kBinChunk;
+                const unsigned long long* src = entries + (int64_t)(c0 + j) * kBinChunk;
                 for (int i0 = b; i0 < e; i0 += 64 * UC) {
                     unsigned long long v[UC];
 #pragma unroll
@@ -404,22 +408,20 @@ __global__ __launch_bounds__(1024) void lookahead_consume_kernel(
             for (int u = 0; u < UC; ++u) {
                 b[u] = __builtin_amdgcn_readlane(seg_b, j0 + u);          // (chunks past the end: empty segments)
                 e[u] = __builtin_amdgcn_readlane(seg_e, j0 + u);
-                const unsigned long long* src = entries + (c0 + j0 + u) * kBinChunk;
+                const unsigned long long* src = entries + (int64_t)(c0 + j0 + u) * kBinChunk;
                 first[u] = b[u] + lane < e[u] ? src[b[u] + lane] : 0ull;
             }
 #pragma unroll
             for (int u = 0; u < UC; ++u) {
                 if (b[u] + lane < e[u]) apply(first[u]);
-                const unsigned long long* src = entries + (c0 + j0 + u) * kBinChunk;
+                const unsigned long long* src = entries + (int64_t)(c0 + j0 + u) * kBinChunk;
                 for (int i = b[u] + 64 + lane; i < e[u]; i += 64) apply(src[i]);
             }
         }
     }
     __syncthreads();
-    long long* prow = parts > 1 ? partial + ((int64_t)part * n_inst + k) * map_len : nullptr;
-    if (prow) scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, prow, st);
-    else if (vec) scan_lds_row<true, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
-    else scan_lds_row<false, false>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+    long long* prow = SHARED ? partial + ((int64_t)part * n_inst + k) * map_len : nullptr;
+    scan_lds_row<VEC, false, SHARED>(s_off, s_slp, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, prow, st);
 }
 
 // The parts' rows added into the caller's map.
@@ -466,12 +468,13 @@ bool direct_pays(int64_t n_rec, int n_inst, int map_len) {
     if (n_inst <= 512 || (n_inst <= 768 && map_len >= 4096)) return true;
     return map_len >= 8192 && n_inst <= 65536 && (int64_t)n_inst * map_len >= 25000000;
 }
+template <bool VEC>
 __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     const int32_t* __restrict__ instance_id, const int32_t* __restrict__ start_iter,
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ i_begin,
     const int32_t* __restrict__ i_end, const int32_t* __restrict__ sign, int n, int n_inst, int map_len,
     int32_t* __restrict__ kv_tokens, int64_t* __restrict__ overflow, const int32_t* __restrict__ capacity,
-    float* __restrict__ fraction, int vec, ps_status* st) {
+    float* __restrict__ fraction, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     unsigned long long* s_row = (unsigned long long*)lds_raw;             // [map_len] packed differences (at most 2^14 records)
     __shared__ long long s_w0[16], s_w1[16];
@@ -513,9 +516,7 @@ __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     }
     __syncthreads();
     if (tid == 0 && overflow && s_ovf) overflow[k] += (int64_t)s_ovf;
-    const long long* words = (const long long*)s_row;
-    if (vec) scan_lds_row<true, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
-    else scan_lds_row<false, true>(words, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+    scan_lds_row<VEC, true, false>((const long long*)s_row, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
 }
 
 // Layout of the workspace.  Atomic route: the difference array.  Binned route: entries, table, and from there to the end
@@ -585,20 +586,30 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
     if (direct_pays(n_rec, n_inst, map_len)) {
         static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
         if (!lds_attr_set) {
-            if (hipFuncSetAttribute((const void*)lookahead_direct_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+            if (hipFuncSetAttribute((const void*)lookahead_direct_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kRowLdsBytes) != hipSuccess ||
+                hipFuncSetAttribute((const void*)lookahead_direct_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     kRowLdsBytes) != hipSuccess)
                 return PS_EHIP;
             lds_attr_set = true;
         }
-        hipLaunchKernelGGL(lookahead_direct_kernel, dim3((unsigned)n_inst), dim3(1024), (size_t)map_len * 8, s, instance_id,
-                           start_iter, prompt_tokens, i_begin, i_end, sign, (int)n_rec, n_inst, map_len, kv_tokens, overflow,
-                           capacity, fraction, vec_rows, status);
+#define PS_DIRECT(VEC)                                                                                                    \
+    hipLaunchKernelGGL(lookahead_direct_kernel<VEC>, dim3((unsigned)n_inst), dim3(1024), (size_t)map_len * 8, s, instance_id, \
+                       start_iter, prompt_tokens, i_begin, i_end, sign, (int)n_rec, n_inst, map_len, kv_tokens, overflow,    \
+                       capacity, fraction, status)
+        if (vec_rows) PS_DIRECT(true);
+        else PS_DIRECT(false);
+#undef PS_DIRECT
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }
     if (plan.binned) {
         static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
         if (!lds_attr_set) {
-            if (hipFuncSetAttribute((const void*)lookahead_consume_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+            if (hipFuncSetAttribute((const void*)lookahead_consume_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kRowLdsBytes) != hipSuccess ||
+                hipFuncSetAttribute((const void*)lookahead_consume_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kRowLdsBytes) != hipSuccess ||
+                hipFuncSetAttribute((const void*)lookahead_consume_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     kRowLdsBytes) != hipSuccess ||
                 hipFuncSetAttribute((const void*)lookahead_bin_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     kBinChunk * 8 + kBinMaxInst * 12) != hipSuccess ||
@@ -625,9 +636,14 @@ extern "C" int ps_lookahead_update(const int32_t* instance_id, const int32_t* st
                                    instance_id + at, start_iter + at, prompt_tokens + at, i_begin + at, i_end + at, sign + at,
                                    n_part, at, n_inst, map_len, entries, table, chunks, overflow, status);
             long long* partial = (long long*)((uint8_t*)workspace + plan.partial_at);
-            hipLaunchKernelGGL(lookahead_consume_kernel, dim3((unsigned)((n_inst + 7) / 8 * 8 * consumers)), dim3(1024), (size_t)map_len * 12, s,
-                               entries, table, chunks, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, vec_rows,
-                               consumers, partial, status);
+#define PS_CONSUME(VEC, SHARED)                                                                                              \
+    hipLaunchKernelGGL((lookahead_consume_kernel<VEC, SHARED>), dim3((unsigned)((n_inst + 7) / 8 * 8 * consumers)), dim3(1024), \
+                       (size_t)map_len * 12, s, entries, table, (int)chunks, n_inst, map_len, kv_tokens, capacity,            \
+                       last ? fraction : nullptr, consumers, partial, status)
+            if (consumers > 1) PS_CONSUME(false, true);
+            else if (vec_rows) PS_CONSUME(true, false);
+            else PS_CONSUME(false, false);
+#undef PS_CONSUME
             if (consumers > 1)
                 hipLaunchKernelGGL(lookahead_combine_kernel, dim3((unsigned)(((int64_t)n_inst * map_len + 255) / 256)), dim3(256), 0, s,
                                    partial, consumers, n_inst, map_len, kv_tokens, capacity, last ? fraction : nullptr, status);
