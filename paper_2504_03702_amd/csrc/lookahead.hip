@@ -549,9 +549,18 @@ LookaheadPlan plan_lookahead(int64_t n_rec, int n_inst, int map_len) {
         const int64_t chunks = (most + kBinChunk - 1) / kBinChunk;
         p.table_at = align_up((size_t)chunks * kBinChunk * 8, 256);
         p.partial_at = p.table_at + align_up((size_t)chunks * (size_t)(n_inst + 1) * 4, 256);
-        // few instances: enough workgroups to fill the chip, 8 chunks (65536 records) each at the least
-        const int64_t share = chunks / 8 < kConsumeWorkgroups / n_inst ? chunks / 8 : kConsumeWorkgroups / n_inst;
-        if (share > 1) p.consumers = (int)share;
+        // Few instances: enough workgroups to fill the chip (a workgroup to a compute unit, 32 to an XCD), 8 chunks
+        // (65536 records) each at the least, where an instance's entries are many against the rows that are written and
+        // added up for it.  Microseconds, one workgroup an instance / shared:
+        //   8 instances, 4096 slots:     131072 records 24 / 25,  300000 32 / 26,  1 M 64 / 33,  10 M 464 / 91
+        //   9 instances, 12800 slots:    300000 records 41 / 36
+        //   64 instances, 1024 slots:    500000 records 23 / 24,  1 M 30 / 30,  4 M 66 / 48
+        //   64 instances, 12800 slots:   500000 records 35 / 45,  1 M 41 / 46,  4 M 76 / 64
+        //   128 instances, 4096 slots:   1 M records 27 / 33,  2 M 38 / 39,  10 M 110 / 97
+        const int per_xcd = (n_inst + 7) / 8;
+        const int64_t fill = n_inst > 8 ? kConsumeWorkgroups / 8 / per_xcd : kConsumeWorkgroups / n_inst;
+        const int64_t share = chunks / 8 < fill ? chunks / 8 : fill;
+        if (share > 1 && most / n_inst >= 8192 + (int64_t)map_len * (n_inst < 32 ? n_inst : 32) / 16) p.consumers = (int)share;
     }
     p.need_bytes = p.partial_at + (size_t)p.diff_bytes;
     const size_t shared = p.partial_at + align_up(p.row_bytes * (size_t)p.consumers, 256);

@@ -283,10 +283,11 @@ def test_short_lists_around_the_direct_route(n, K, L):
 
 
 @pytest.mark.parametrize("n,K,L", [(65536, 1, 64), (131072, 2, 4096), (140_001, 1, 12800), (600_011, 33, 1021), (600_011, 32, 1024),
-                                   (1_100_000, 127, 37), (300_000, 129, 256)])
+                                   (1_100_000, 127, 37), (300_000, 129, 256), (131_072, 8, 12800), (131_072, 16, 100), (131_072, 16, 12800),
+                                   (2_200_000, 85, 100)])
 def test_few_instances_share_their_entries(n, K, L):
-    """Binned lists over few instances: several workgroups fold one instance's entries (8 chunks each at the least),
-    long and short segments (the line lies at 32 instances), fractions and a map in use."""
+    """Binned lists over few instances: several workgroups fold one instance's entries (8 chunks each and 8192 entries
+    and up to two for every slot of a row at the least), long and short segments (the line lies at 32 instances), fractions and a map in use."""
     print(f"look-ahead few instances n={n} K={K} L={L}", flush=True)
     rng = np.random.default_rng(n + L)
     b = rng.integers(0, 300, n)
@@ -302,8 +303,8 @@ def test_few_instances_share_their_entries(n, K, L):
     assert np.array_equal(got[2], ref_kv.astype(np.float32) / cap.astype(np.float32)[:, None])
 
 
-@pytest.mark.parametrize("n,sized_for,K,L", [(1_000_000, 256, 128, 4096), (1_000_000, 256, 1, 4096), (1_000_000, 129, 33, 700),
-                                             (600_011, 200, 100, 1021), (70_001, 4096, 20, 5)])
+@pytest.mark.parametrize("n,sized_for,K,L", [(2_200_000, 256, 128, 1024), (1_000_000, 256, 1, 4096), (1_000_000, 129, 33, 700),
+                                             (1_200_000, 200, 100, 1021), (70_001, 4096, 20, 5)])
 def test_workspace_of_a_larger_cluster(n, sized_for, K, L):
     """A cluster that is scaled down keeps its workspace: fewer instances with the size the query gave for more, whether
     or not that has room for all the workgroups that would share an instance's entries."""
