@@ -131,8 +131,8 @@ size_t ps_anticipate_workspace_bytes(int64_t n_req, int32_t n_inst, int32_t hori
  *             is persistent, the caller zeroes it to start afresh.
  *   overflow  [n_inst] int64, accumulated: tokens that fall at or after `horizon`.  May be NULL
  *             only if rate == NULL (nothing can overflow then).
- *   Records may come in any order and the result does not depend on it.  Calls of at most 16384 records (with
- *   n_req * n_inst <= 2^23, horizon <= 16000) are folded by a workgroup per instance in one launch.  Long streams (262144 records
+ *   Records may come in any order and the result does not depend on it.  Calls of at most 16384 records over up to
+ *   2^23 / n_req instances are folded by a workgroup per instance in one launch.  Long streams (262144 records
  *   or more, rate given, horizon <= 4096) whose records are in arrival order (non-decreasing
  *   arrival_bucket, as in a request log) are folded by a cheaper kernel; if a record turns out to lie
  *   outside the bucket window of its part of the stream, the general kernel redoes the call.

@@ -207,10 +207,11 @@ def test_host_side_argument_errors():
 
 @pytest.mark.parametrize("n,K,T,with_rate", [(1, 1, 1, True), (8192, 3, 1023, True), (8193, 2, 1024, False), (16384, 512, 65, True),
                                              (16384, 513, 65, True), (16385, 4, 600, True), (3000, 2, 16000, True),
-                                             (3000, 2, 16001, False), (64, 5000, 30, True)])
+                                             (3000, 2, 16001, False), (64, 5000, 30, True), (4096, 1, 16, True),
+                                             (4097, 1, 16, True)])
 def test_short_calls_around_the_direct_route(n, K, T, with_rate):
     """Batch sizes around a thread's batch of records and the route's limits (16384 records, 2^23 records x instances,
-    horizons of 16000 buckets), long predictions that run past the horizon, a map and overflow in use."""
+    horizons of 16000 buckets, 256 records a cell), long predictions that run past the horizon, a map and overflow in use."""
     print(f"anticipate direct n={n} K={K} T={T} rate={with_rate}", flush=True)
     rng = np.random.default_rng(n + T)
     pred = rng.integers(0, 4097, n).astype(np.int32)
