@@ -86,7 +86,11 @@ __global__ __launch_bounds__(64) void scaler_summary_kernel(const int32_t* __res
 
 // Both parts in one launch by one workgroup, 16 lanes per instance and eight slots of a lane requested at a time: for
 // clusters whose windows one compute unit reads in a few microseconds, the second launch costs more than it saves.
+// Microseconds, two launches / one: 1 instance of 512 and 1000 slots 13 / 10 and 13 / 14, of 4096 13 / 45 (16 lanes read
+// what 64 would, a trip to memory per 128 slots); 64 of 512 and 640 slots 13 / 12 and 13 / 14; 128 of 512 18 / 12;
+// 256 of 256 31 / 11; 512 of 128 57 / 15.
 constexpr int kOneMostInst = 512;
+constexpr int kOneMostWindow = 512;
 constexpr int kOneMostSlots = 65536;                       // n_inst * window
 __global__ __launch_bounds__(1024) void scaler_one_kernel(const int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
                                                           int n_inst, int map_len, int w, int over_pct, int share_pct, int idle_pct,
@@ -158,7 +162,7 @@ extern "C" int ps_scaler_scan(const int32_t* kv_tokens, const int32_t* capacity,
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
     const int w = min(window, map_len);
-    if (n_inst <= kOneMostInst && (int64_t)n_inst * w <= kOneMostSlots) {
+    if (n_inst <= kOneMostInst && w <= kOneMostWindow && (int64_t)n_inst * w <= kOneMostSlots) {
         hipLaunchKernelGGL(scaler_one_kernel, dim3(1), dim3(1024), 0, s, kv_tokens, capacity, n_inst, map_len, w, over_pct,
                            share_pct, idle_pct, over_count, peak_tokens, overloaded, summary, scale_down);
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;

@@ -237,10 +237,10 @@ def test_binned_route_on_unaligned_arrays():
 
 
 @pytest.mark.parametrize("K,L,window", [(1, 1, 1), (64, 300, 128), (65, 300, 129), (512, 140, 127), (512, 129, 129),
-                                        (513, 200, 16), (3, 50, 0), (130, 90, 400)])
+                                        (513, 200, 16), (3, 50, 0), (130, 90, 400), (20, 600, 512), (20, 600, 513)])
 def test_scaler_sizes_around_the_single_launch(K, L, window):
-    """Instance counts around the totals' groups of 64 and the single launch's limits (512 instances, 65536 slots),
-    windows around a lane's batch of slots; instances without capacity and negative maps among them."""
+    """Instance counts around the totals' groups of 64 and the single launch's limits (512 instances, windows
+    of 512, 65536 slots), windows around a lane's batch of slots; instances without capacity and negative maps among them."""
     from oracle import scaler as osc
     print(f"scaler K={K} L={L} window={window}", flush=True)
     rng = np.random.default_rng(K + window)
