@@ -51,10 +51,11 @@ def test_argument_checks():
     assert e.value.code == -6
 
 
-@pytest.mark.parametrize("S,H,k", [(2, 2, 70), (4, 31, 5), (9, 32, 1), (3, 33, 65), (2, 63, 48), (600, 64, 3)])
+@pytest.mark.parametrize("S,H,k", [(2, 2, 70), (4, 31, 5), (9, 32, 1), (3, 33, 65), (2, 63, 48), (600, 64, 3),
+                                   (1025, 1, 3), (2047, 4, 3), (2048, 4, 4), (3073, 16, 2), (3074, 32, 1)])
 def test_register_tile_edges(S, H, k):
     """Hidden sizes around the register tiles (32, 64; a wavefront holds a quarter of W_mh's rows), histories shorter
-    and longer than a wavefront, more services than the chip holds at once."""
+    and longer than a wavefront, more services than the chip holds at once, and so many that a wavefront takes a service."""
     x = wl.make_forecaster_inputs(seed=S + H, n_services=S, hidden=H, k=k)
     got = run_forecast(x)
     ref = of.forecast_services([x.model(s, 0) for s in range(S)], [x.model(s, 1) for s in range(S)],
