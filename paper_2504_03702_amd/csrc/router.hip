@@ -141,10 +141,11 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     }
     const int inst = tid;
     const bool mine = inst < n_inst;
-    long long qp = 0, s100 = 0, thr = 0;
+    long long qp = 0, cd = 0, s100 = 0, thr = 0;
     if (mine) {
         qp = queued_p[inst];
-        s100 = 100 * (qp + current_d[inst]);
+        cd = current_d[inst];
+        s100 = 100 * (qp + cd);
         thr = (long long)t_mem_pct * capacity[inst];
         s_pre[inst] = kMin;
         s_suf[n_blocks * pitch + inst] = kMin;
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 best_pk = __builtin_amdgcn_readlane(o_pk, src);
             }
             if (lane == q) { out_i = best_i; out_lo = (int)best; out_hi = (int)(best >> 32); }
-            if (inst == best_i) { qp += P; s100 += add100; }
+            if (inst == best_i) { qp += P; cd += D; s100 += add100; }
             if (SMALL || window > 0) {
                 if ((long long)top + P + window >= 2147483647ll) range_fault = true;   // a sum may have left int32
                 top = max(top, best_pk);                         // the chosen instance's largest value from now on
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         }
     }
     if (range_fault && tid == 0) report_fault(st, PS_ST_RANGE, -1);
-    if (mine) { queued_p[inst] = qp; current_d[inst] = s100 / 100 - qp; }
+    if (mine) { queued_p[inst] = qp; current_d[inst] = cd; }
     for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i)
         for (int t = lane; t < window; t += 64) window_tokens[(int64_t)i * window + t] = ((const int*)(s_win + (t >> 2) * pitch + i))[t & 3];
 }

@@ -96,3 +96,12 @@ def test_block_edges_and_full_lds(K, l, n):
     assert flags == 0
     assert np.array_equal(a, ra) and np.array_equal(s, rs)
     assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
+def test_state_of_an_instance_with_huge_queues():
+    """The state is carried exactly in int64 also where a hundredfold no longer fits (10^17 tokens as a mark of an
+    instance that is out of use)."""
+    mark = 10**17
+    a, s, w, qp, cd, flags, _ = run_route([10, 20, 30], [3, 1, 2], np.zeros((1, 4), np.int64), [1000], [mark], [mark + 7])
+    assert flags == 0 and a.tolist() == [0, 0, 0]
+    assert qp.tolist() == [mark + 60] and cd.tolist() == [mark + 7 + 6] and w[0].tolist() == [60, 42, 12, 0]
