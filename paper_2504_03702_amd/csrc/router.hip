@@ -20,6 +20,8 @@
 // instances need none.
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
 // window in registers for every request, 3.14 ms this way.
+#include <type_traits>
+
 #include "device_util.h"
 #include "internal.h"
 
@@ -111,7 +113,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int32_t* __restrict__ capacity, int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct,
     int beta, int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    int4* s_best = (int4*)lds_raw;                               // [2][16] a wavefront's minimum: score, instance, peak
+    int4* s_best = (int4*)lds_raw;                               // [2][16] a wavefront's minimum: score, instance
     int4* s_win = (int4*)(lds_raw + 512);                        // [pieces][pitch]
     const int pieces = n_blocks * (block >> 2);
     // maxima by block, with a row of minima for "no block": row b of s_pre is over the blocks below b, of w[t] + t;
@@ -160,7 +162,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int u_blk = u_live ? (u_low ? lane & 31 : n_blocks - 1 - (lane & 31)) : 0;
     int4* const u_win = s_win + u_blk * chunks * pitch;
     int* const u_out = u_low ? s_pre + (u_blk + 1) * pitch : s_suf + u_blk * pitch;
-    auto update = [&](int i, int P, int Dc) {
+    bool range_fault = false;                                    // a stored value has left int32
+    auto update = [&](auto far, int i, int P, int Dc) {
         int m = kMin;
         for (int c = 0; c < chunks; ++c) {
             int4* at = u_win + c * pitch + i;
@@ -170,7 +173,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int t = t0 + e;
-                v[e] = (int)((unsigned)v[e] + (t < Dc ? (unsigned)(P + t) : 0u));
+                if (far.value && t < Dc && (long long)v[e] + P + t > 2147483647ll) range_fault = true;
+                v[e] = (int)((unsigned)v[e] + (t < Dc ? (unsigned)P + (unsigned)t : 0u));
                 m = max(m, (int)((unsigned)v[e] + (u_low && t < window ? (unsigned)t : 0u)));
             }
             if (u_low && u_live) *at = make_int4(v[0], v[1], v[2], v[3]);
@@ -208,33 +212,34 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         }
         asm volatile("" ::: "memory");
     } else if (n_blocks > 0) {
-        for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(i, 0, 0);
+        for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(std::false_type{}, i, 0, 0);
     }
-    // top: the largest window value of all instances, uniform
-    int top = mine ? s_suf[inst] : kMin;
-    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
-    if (nw > 1) {
-        if (lane == 0) s_best[16 + wave].x = top;
-        __syncthreads();
-        for (int w = 0; w < nw; ++w) top = max(top, s_best[16 + w].x);
-    }
-    top = __builtin_amdgcn_readfirstlane(top);
+    // The largest window value of all instances (2^30 at the least), uniform.
+    auto largest = [&]() {
+        int top = mine ? s_suf[inst] : kMin;
+        for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+        if (nw > 1) {
+            if (lane == 0) s_best[wave].x = top;                 // (last read two requests ago)
+            __syncthreads();
+            for (int w = 0; w < nw; ++w) top = max(top, s_best[w].x);
+            __syncthreads();
+        }
+        return __builtin_amdgcn_readfirstlane(max(top, 1 << 30));
+    };
 
     const long long kNone = 0x7fffffffffffffffll;
-    bool range_fault = false;
     const int ic = mine ? inst : 0;
     const int row4 = pitch * 4, row16 = pitch * 16;              // bytes from a row of the tables to the next
     int nP = 0, nD = 0;                                          // lane l: request l of the next 64
     if (lane < n_req) { nP = prompt_tokens[lane]; nD = pred_tokens[lane]; }
-    for (int base = 0; base < n_req; base += 64) {
-        const int cnt = min(64, n_req - base);
-        const int vP = nP, vD = nD;
+    // The requests of one group of 64.  FAR: their tokens could take a sum, or one of the tables' w[t] + t, to 2^31, so
+    // they are scored slot by slot in 64 bits.
+    auto walk = [&](auto far, int base, int cnt, int vP, int vD) {
         // blocks below b lie under the request's ramp whole, block b is looked at slot by slot (where the ramp ends on
         // a block boundary that only repeats what the tables say), blocks from the next one on keep their values
         const int vDc = min(max(vD, 0), window), vb = n_blocks > 0 ? vDc / block : 0;
         const int vs = n_blocks > 0 ? (vDc + block - 1) / block : 0;
         const int v_pre = vb * row4, v_suf = vs * row4, v_win = max(min(vb, n_blocks - 1), 0);
-        if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
         int out_i = -1, out_lo = 0, out_hi = 0;
         for (int q = 0; q < cnt; ++q) {
             const int P = __builtin_amdgcn_readlane(vP, q), D = __builtin_amdgcn_readlane(vD, q);
@@ -246,19 +251,24 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 continue;
             }
             const int Dc = __builtin_amdgcn_readlane(vDc, q), blk = __builtin_amdgcn_readlane(v_win, q);
-            const int pre = *(const int*)((const char*)(s_pre + ic) + __builtin_amdgcn_readlane(v_pre, q));
-            const int suf = *(const int*)((const char*)(s_suf + ic) + __builtin_amdgcn_readlane(v_suf, q));
-            int pk = kMin;
-            for (int c = 0; c < chunks; ++c) {
-                const int4 v = *(const int4*)((const char*)(s_win + ic) + (blk * chunks + c) * row16);
-                const int t = blk * (SMALL ? 4 : block) + 4 * c;
-                pk = max(max(pk, (int)((unsigned)v.x + (t < Dc ? (unsigned)(P + t) : 0u))),
-                         (int)((unsigned)v.y + (t + 1 < Dc ? (unsigned)(P + t + 1) : 0u)));
-                pk = max(max(pk, (int)((unsigned)v.z + (t + 2 < Dc ? (unsigned)(P + t + 2) : 0u))),
-                         (int)((unsigned)v.w + (t + 3 < Dc ? (unsigned)(P + t + 3) : 0u)));
+            long long pen = -thr;
+            if (far.value) {
+                long long pk = kMin;
+                for (int t = 0; t < window; ++t)
+                    pk = max(pk, (long long)((const int*)(s_win + (t >> 2) * pitch + ic))[t & 3] + (t < Dc ? (long long)P + t : 0ll));
+                pen += 100 * pk;
+            } else {
+                const int pre = *(const int*)((const char*)(s_pre + ic) + __builtin_amdgcn_readlane(v_pre, q));
+                const int suf = *(const int*)((const char*)(s_suf + ic) + __builtin_amdgcn_readlane(v_suf, q));
+                int pk = kMin;
+                for (int c = 0; c < chunks; ++c) {
+                    const int4 v = *(const int4*)((const char*)(s_win + ic) + (blk * chunks + c) * row16);
+                    const int t = blk * (SMALL ? 4 : block) + 4 * c;
+                    pk = max(max(pk, v.x + (t < Dc ? P + t : 0)), v.y + (t + 1 < Dc ? P + t + 1 : 0));
+                    pk = max(max(pk, v.z + (t + 2 < Dc ? P + t + 2 : 0)), v.w + (t + 3 < Dc ? P + t + 3 : 0));
+                }
+                pen += 100 * (long long)max(max(pk, pre + P), suf);
             }
-            pk = max(max(pk, (int)((unsigned)pre + (unsigned)P)), suf);
-            long long pen = 100 * (long long)pk - thr;
             pen = pen > 0 && (SMALL || window > 0) ? pen : 0;
             if (beta != 1) pen *= beta;
             const long long add100 = 100 * ((long long)P + D);
@@ -266,32 +276,41 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
             // minimum over the wavefront, lowest instance on ties
             int src;
             long long best = wave_min(L, mine, src);
-            int best_i = 64 * wave + src, best_pk = __builtin_amdgcn_readlane(pk, src);
+            int best_i = 64 * wave + src;
             if (nw > 1) {
-                if (lane == 0) s_best[par + wave] = make_int4((int)best, (int)(best >> 32), best_i, best_pk);
+                if (lane == 0) s_best[par + wave] = make_int4((int)best, (int)(best >> 32), best_i, 0);
                 // (LDS only: __syncthreads would also wait for the results' global stores)
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
                 const int4 o = s_best[par + (lane & 15)];        // (slots no wavefront writes are not looked at)
-                const int o_lo = o.x, o_hi = o.y, o_i = o.z, o_pk = o.w;
+                const int o_lo = o.x, o_hi = o.y, o_i = o.z;
                 // (wavefronts are in the order of their instances)
                 best = wave_min(lane < nw ? ((long long)o_hi << 32) | (unsigned)o_lo : kNone, lane < nw, src);
                 best_i = __builtin_amdgcn_readlane(o_i, src);
-                best_pk = __builtin_amdgcn_readlane(o_pk, src);
             }
             if (lane == q) { out_i = best_i; out_lo = (int)best; out_hi = (int)(best >> 32); }
             if (inst == best_i) { qp += P; cd += D; s100 += add100; }
-            if (SMALL || window > 0) {
-                if ((long long)top + P + window >= 2147483647ll) range_fault = true;   // a sum may have left int32
-                top = max(top, best_pk);                         // the chosen instance's largest value from now on
-                if ((best_i >> 6) == wave && Dc > 0) update(best_i, P, Dc);
-            }
+            if ((best_i >> 6) == wave && Dc > 0) update(far, best_i, P, Dc);
         }
         if (wave == 0 && lane < cnt) {
             assigned[base + lane] = out_i;
             score100[base + lane] = ((long long)out_hi << 32) | (unsigned)out_lo;
         }
+    };
+    // bound: no window value is above it (a request raises it by its tokens and the window; taken afresh when that has
+    // added up)
+    long long bound = largest();
+    for (int base = 0; base < n_req; base += 64) {
+        const int cnt = min(64, n_req - base), vP = nP, vD = nD;
+        if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
+        int most = lane < cnt ? vP : 0;                          // largest prompt of the group
+        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+        const long long rise = 64ll * ((long long)__builtin_amdgcn_readfirstlane(most) + window);
+        if (bound + rise >= 2147483647ll) bound = largest();
+        if (bound + rise >= 2147483647ll) walk(std::true_type{}, base, cnt, vP, vD);
+        else walk(std::false_type{}, base, cnt, vP, vD);
+        bound += rise;
     }
-    if (range_fault && tid == 0) report_fault(st, PS_ST_RANGE, -1);
+    if (range_fault) report_fault(st, PS_ST_RANGE, -1);
     if (mine) { queued_p[inst] = qp; current_d[inst] = cd; }
     for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i)
         for (int t = lane; t < window; t += 64) window_tokens[(int64_t)i * window + t] = ((const int*)(s_win + (t >> 2) * pitch + i))[t & 3];

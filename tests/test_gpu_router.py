@@ -105,3 +105,68 @@ def test_state_of_an_instance_with_huge_queues():
     a, s, w, qp, cd, flags, _ = run_route([10, 20, 30], [3, 1, 2], np.zeros((1, 4), np.int64), [1000], [mark], [mark + 7])
     assert flags == 0 and a.tolist() == [0, 0, 0]
     assert qp.tolist() == [mark + 60] and cd.tolist() == [mark + 7 + 6] and w[0].tolist() == [60, 42, 12, 0]
+
+
+# one wavefront and several, blocks of one 16-byte piece and longer ones, more slots than a thread's registers
+SHAPES = [(3, 8, 12), (70, 20, 40), (64, 129, 40), (256, 134, 12), (8, 3000, 6), (5, 2000, 6), (1, 100, 5)]
+
+
+@pytest.mark.parametrize("K,l,n", SHAPES)
+def test_peaks_beyond_int32(K, l, n):
+    """Instances whose windows lie so high that a request's tokens would take them past 2^31: nothing is stored out of
+    range as long as they are not chosen (their peak is the largest of all), so nothing is flagged and all results
+    are exact.  Values just below, at and above the line at which 32 bits would still do."""
+    print(f"route near 2^31 K={K} l={l} n={n}", flush=True)
+    rng = np.random.default_rng(K + l)
+    P, D, win, cap, qp, cd = random_case(rng, K, l, n, False)
+    hot = rng.permutation(K)[: (K + 1) // 2] if K > 1 else np.array([], int)
+    for k in hot:
+        win[k, rng.integers(0, l, 3)] = 2**31 - 1 - rng.integers(0, 4000, 3)
+    if K == 1:
+        win[0, :] = 2**31 - 1 - 5000 - rng.integers(0, 100, l)
+        P = np.array([200, 300, 150, 400, 7][:n])
+        D = np.minimum(D, l)
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd)
+    assert rw.max() < 2**31 and flags == 0
+    assert np.array_equal(a, ra) and np.array_equal(s, rs)
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
+@pytest.mark.parametrize("K,l", [(k, l) for k, l, _ in SHAPES])
+def test_stored_values_beyond_int32_are_flagged(K, l):
+    """Every instance is full to the brim, so the request that is dispatched takes slots out of the int32 range: flagged,
+    low 32 bits kept, score and queues exact."""
+    print(f"route past 2^31 K={K} l={l}", flush=True)
+    rng = np.random.default_rng(K * l)
+    _, _, win, cap, qp, cd = random_case(rng, K, l, 1, False)
+    win[:, :] = 2**31 - 1 - rng.integers(0, 50, (K, l))
+    P, D = np.array([100]), np.array([l - l // 3])
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd)
+    assert flags == ps.PS_ST_RANGE and rw.max() >= 2**31
+    assert np.array_equal(a, ra) and np.array_equal(s, rs) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+    assert np.array_equal(w.astype(np.int64) & 0xffffffff, rw & 0xffffffff)
+
+
+@pytest.mark.parametrize("where", ["everywhere", "one wavefront", "ties"])
+@pytest.mark.parametrize("K,l,n", [(64, 12, 50), (200, 16, 60), (130, 140, 40), (6, 3000, 5)])
+def test_scores_beyond_32_bits(K, l, n, where):
+    """Queues so long that scores need 64 bits: on all instances, on those of one wavefront only (the exchange then mixes
+    minima found either way), and equal ones, which go to the lowest instance."""
+    print(f"route 64-bit scores K={K} l={l} n={n} {where}", flush=True)
+    rng = np.random.default_rng(K + n)
+    P, D, win, cap, qp, cd = random_case(rng, K, l, n, True)
+    big = rng.integers(2**25, 2**40, K)
+    if where == "everywhere":
+        qp, cd = big, rng.integers(2**25, 2**40, K)
+    elif where == "one wavefront":
+        qp = np.where(np.arange(K) // 64 == (K - 1) // 64, big, qp)
+    else:
+        win[:, :], cap[:], cd[:] = 0, 10**6, 0
+        qp = np.full(K, 2**33)
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd)
+    assert flags == 0
+    assert np.array_equal(a, ra) and np.array_equal(s, rs)
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
