@@ -19,7 +19,7 @@
 // wavefront only, so the exchange of the wavefronts' minima is the one barrier of a request; up to 64
 // instances need none.
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
-// window in registers for every request, 3.14 ms this way.
+// window in registers for every request, 3.09 ms this way.
 #include <type_traits>
 
 #include "device_util.h"
@@ -316,6 +316,242 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         for (int t = lane; t < window; t += 64) window_tokens[(int64_t)i * window + t] = ((const int*)(s_win + (t >> 2) * pitch + i))[t & 3];
 }
 
+// ---- a few requests, or long windows ----------------------------------------------------------------------
+// The tables have to be made before the first request is scored, and long blocks make dear scores.  Where that costs more
+// than it saves, TPI threads per instance scan its whole window for every request.  The windows lie in LDS:
+__device__ __forceinline__ void scan_walk(
+    unsigned char* lds_raw, const int32_t* prompt_tokens, const int32_t* pred_tokens, int first_index, int n_req, int n_inst,
+    int window, int tpi, int32_t* window_tokens, const int32_t* capacity, int64_t* queued_p, int64_t* current_d,
+    int t_mem_pct, int beta, int32_t* assigned, int64_t* score100, ps_status* st) {
+    long long* s_qp = (long long*)lds_raw;                       // [n_inst]
+    long long* s_cd = s_qp + n_inst;                             // [n_inst]
+    long long* s_best = s_cd + n_inst;                           // [2][16] per-wavefront minimum score
+    int* s_best_i = (int*)(s_best + 32);                         // [2][16] and its instance
+    int* s_cap = s_best_i + 32;                                  // [n_inst]
+    int2* s_req = (int2*)(s_cap + n_inst + (n_inst & 1));         // [1024] (P, D) of the requests being walked
+    long long* s_out_s = (long long*)(s_req + kRouteThreads);    // [1024] their scores
+    int* s_out_i = (int*)(s_out_s + kRouteThreads);              // [1024] and instances, written out per chunk: a
+                                                                 // global store per request would be waited for at
+                                                                 // every barrier
+    int* s_win = s_out_i + kRouteThreads;                        // [n_inst][window]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < n_inst; i += kRouteThreads) { s_qp[i] = queued_p[i]; s_cd[i] = current_d[i]; s_cap[i] = capacity[i]; }
+    for (int i = tid; i < n_inst * window; i += kRouteThreads) s_win[i] = window_tokens[i];
+    __syncthreads();
+    const int inst = tid / tpi, sub = tid % tpi;
+    const bool mine = inst < n_inst;
+    int* row = s_win + (mine ? inst : 0) * window;
+    const long long kNone = 0x7fffffffffffffffll;
+    bool range_fault = false;
+    for (int r = 0; r < n_req; ++r) {
+        if ((r & (kRouteThreads - 1)) == 0) {
+            // results of the last 1024 requests out, the next 1024 requests in
+            __syncthreads();
+            if (r > 0) { assigned[r - kRouteThreads + tid] = s_out_i[tid]; score100[r - kRouteThreads + tid] = s_out_s[tid]; }
+            if (r + tid < n_req) s_req[tid] = make_int2(prompt_tokens[r + tid], pred_tokens[r + tid]);
+            __syncthreads();
+        }
+        const int slot = r & (kRouteThreads - 1);
+        const int2 pd = s_req[slot];
+        const int P = pd.x, D = pd.y;                           // uniform
+        if (P < 0 || D < 0) {
+            if (tid == 0) { s_out_i[slot] = -1; s_out_s[slot] = 0; report_fault(st, PS_ST_BAD_RECORD, first_index + r); }
+            __syncthreads();                                    // keeps the one-barrier-per-request rhythm of the exchange slots
+            continue;
+        }
+        long long peak = -kNone;
+        if (mine)
+            for (int t = sub; t < window; t += tpi) peak = max(peak, (long long)row[t] + (t < D ? (long long)P + t : 0ll));
+        for (int o = tpi >> 1; o > 0; o >>= 1) peak = max(peak, __shfl_xor(peak, o, 64));
+        long long L = kNone;
+        if (mine && sub == 0) {
+            const long long pen = window > 0 ? max(0ll, 100 * peak - (long long)t_mem_pct * s_cap[inst]) : 0ll;
+            L = 100 * (s_qp[inst] + P + s_cd[inst] + D) + (long long)beta * pen;
+        }
+        int bi = mine ? inst : 0x7fffffff;
+        // minimum over the wavefront, lowest instance on ties
+        for (int o = 32; o > 0; o >>= 1) {
+            const long long oL = __shfl_xor(L, o, 64);
+            const int oi = __shfl_xor(bi, o, 64);
+            if (oL < L || (oL == L && oi < bi)) { L = oL; bi = oi; }
+        }
+        // the exchange slots alternate between requests, so one barrier per request is enough: a slot
+        // is rewritten two requests later, after the barrier of the request in between
+        const int par = (r & 1) * 16;
+        if (lane == 0) { s_best[par + wave] = L; s_best_i[par + wave] = bi; }
+        __syncthreads();
+        long long bL = s_best[par];
+        int bI = s_best_i[par];
+        for (int w = 1; w < kRouteThreads / 64; ++w) {
+            const long long oL = s_best[par + w];
+            const int oi = s_best_i[par + w];
+            if (oL < bL || (oL == bL && oi < bI)) { bL = oL; bI = oi; }
+        }
+        if (tid == 0) { s_out_i[slot] = bI; s_out_s[slot] = bL; }
+        if (mine && inst == bI) {
+            const int stop = min(D, window);
+            for (int t = sub; t < stop; t += tpi) {
+                const long long v = (long long)row[t] + P + t;
+                if (v > 2147483647ll) range_fault = true;
+                row[t] = (int)v;
+            }
+            if (sub == 0) { s_qp[inst] += P; s_cd[inst] += D; }
+        }
+        // no barrier here: an instance's window and counters are only ever touched by its own threads
+    }
+    __syncthreads();
+    {   // results of the last, possibly partial, chunk
+        const int done = n_req & ~(kRouteThreads - 1), first = done == n_req ? n_req - kRouteThreads : done;
+        if (first + tid < n_req) { assigned[first + tid] = s_out_i[tid]; score100[first + tid] = s_out_s[tid]; }
+    }
+    if (range_fault) report_fault(st, PS_ST_RANGE, -1);
+    for (int i = tid; i < n_inst; i += kRouteThreads) { queued_p[i] = s_qp[i]; current_d[i] = s_cd[i]; }
+    for (int i = tid; i < n_inst * window; i += kRouteThreads) window_tokens[i] = s_win[i];
+}
+
+__global__ __launch_bounds__(kRouteThreads) void route_scan_kernel(
+    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
+    int window, int tpi, int32_t* __restrict__ window_tokens, const int32_t* __restrict__ capacity,
+    int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct, int beta,
+    int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    scan_walk(lds_raw, prompt_tokens, pred_tokens, 0, n_req, n_inst, window, tpi, window_tokens, capacity, queued_p, current_d,
+              t_mem_pct, beta, assigned, score100, st);
+}
+
+// The same walk with every instance's window in the registers of its TPI threads (thread `sub` of an instance
+// owns iterations sub, sub + TPI, ...; at most kRegSlots each).  32-bit arithmetic: a running bound B on every
+// window value is kept, and from the first request on that could take a sum to 2^31 (B + P + window) the walk goes on
+// in LDS with 64-bit peaks (the registers have no room for them).  The sixteen wavefronts' minima are combined by every wavefront in parallel (one
+// entry per lane, shuffles) instead of a serial scan.
+const int kRegSlots = 32;
+
+__global__ __launch_bounds__(kRouteThreads) void route_reg_kernel(
+    const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
+    int window, int tpi, int32_t* __restrict__ window_tokens, const int32_t* __restrict__ capacity,
+    int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct, int beta,
+    int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    long long(*s_best)[16] = (long long(*)[16])lds_raw;         // [2]
+    long long* s_out_s = (long long*)lds_raw + 32;              // [1024]
+    int2* s_req = (int2*)(s_out_s + kRouteThreads);             // [1024]
+    int* s_out_i = (int*)(s_req + kRouteThreads);               // [1024]
+    int(*s_best_i)[16] = (int(*)[16])(s_out_i + kRouteThreads); // [2]
+    int* s_max = s_out_i + kRouteThreads + 32;                  // [16]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int inst = tid / tpi, sub = tid % tpi;
+    const bool mine = inst < n_inst;
+    const int kMin = (int)0x80000000;
+    int r[kRegSlots];                            // dead slots (beyond the window, or no instance) hold the minimum
+    int top = kMin;
+#pragma unroll
+    for (int i = 0; i < kRegSlots; ++i) {
+        const int t = sub + tpi * i;
+        r[i] = mine && t < window ? window_tokens[(int64_t)inst * window + t] : kMin;
+        top = max(top, r[i]);
+    }
+    long long qp = 0, cd = 0, cap = 0;
+    if (mine && sub == 0) { qp = queued_p[inst]; cd = current_d[inst]; cap = capacity[inst]; }
+    // B: an upper bound on every window value, uniform over the workgroup
+    for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+    if (lane == 0) s_max[wave] = top;
+    __syncthreads();
+    long long B = 1 << 30;
+    for (int w = 0; w < 16; ++w) B = max(B, (long long)s_max[w]);
+    const long long kNone = 0x7fffffffffffffffll;
+    int done = n_req;                                           // requests walked here
+    for (int q = 0; q < n_req; ++q) {
+        if ((q & (kRouteThreads - 1)) == 0) {
+            // results of the last 1024 requests out, the next 1024 requests in
+            __syncthreads();
+            if (q > 0) { assigned[q - kRouteThreads + tid] = s_out_i[tid]; score100[q - kRouteThreads + tid] = s_out_s[tid]; }
+            if (q + tid < n_req) s_req[tid] = make_int2(prompt_tokens[q + tid], pred_tokens[q + tid]);
+            __syncthreads();
+        }
+        const int slot = q & (kRouteThreads - 1);
+        const int2 pd = s_req[slot];
+        const int P = pd.x, D = pd.y;                           // uniform
+        if (P < 0 || D < 0) {
+            if (tid == 0) { s_out_i[slot] = -1; s_out_s[slot] = 0; report_fault(st, PS_ST_BAD_RECORD, q); }
+            __syncthreads();                                    // keeps the one-barrier-per-request rhythm of the exchange slots
+            continue;
+        }
+        if (B + P + window >= 2147483647ll) { done = q; break; }    // a sum below may leave the int32 range
+        int pk = kMin;
+        const int Pt = P + sub;                                 // P + t of this thread's first iteration
+#pragma unroll
+        for (int i = 0; i < kRegSlots; ++i) {
+            const int t = sub + tpi * i;
+            const unsigned add = t < D ? (unsigned)(Pt + tpi * i) : 0u;
+            pk = max(pk, (int)((unsigned)r[i] + add));          // (a dead slot stays far below any live one)
+        }
+        for (int o = tpi >> 1; o > 0; o >>= 1) pk = max(pk, __shfl_xor(pk, o, 64));
+        long long L = kNone;
+        if (mine && sub == 0) {
+            const long long pen = max(0ll, 100 * (long long)pk - (long long)t_mem_pct * cap);
+            L = 100 * (qp + P + cd + D) + (long long)beta * pen;
+        }
+        int bi = mine ? inst : 0x7fffffff;
+        // minimum over the wavefront, lowest instance on ties
+        for (int o = 32; o > 0; o >>= 1) {
+            const long long oL = __shfl_xor(L, o, 64);
+            const int oi = __shfl_xor(bi, o, 64);
+            if (oL < L || (oL == L && oi < bi)) { L = oL; bi = oi; }
+        }
+        // the exchange slots alternate between requests, so one barrier per request is enough: a slot
+        // is rewritten two requests later, after the barrier of the request in between
+        const int par = q & 1;
+        if (lane == 0) { s_best[par][wave] = L; s_best_i[par][wave] = bi; }
+        __syncthreads();
+        long long bL = lane < 16 ? s_best[par][lane] : kNone;
+        int bI = lane < 16 ? s_best_i[par][lane] : 0x7fffffff;
+        for (int o = 8; o > 0; o >>= 1) {
+            const long long oL = __shfl_xor(bL, o, 64);
+            const int oi = __shfl_xor(bI, o, 64);
+            if (oL < bL || (oL == bL && oi < bI)) { bL = oL; bI = oi; }
+        }
+        bL = __shfl(bL, 0, 64);
+        bI = __shfl(bI, 0, 64);
+        if (tid == 0) { s_out_i[slot] = bI; s_out_s[slot] = bL; }
+        if (mine && inst == bI) {
+#pragma unroll
+            for (int i = 0; i < kRegSlots; ++i) {
+                const int t = sub + tpi * i;
+                if (t < D && t < window) r[i] = (int)((unsigned)r[i] + (unsigned)(Pt + tpi * i));
+            }
+            if (sub == 0) { qp += P; cd += D; }
+        }
+        B += (long long)P + window;                             // every new value is at most an old one + P + window
+    }
+    __syncthreads();
+    for (int q = (max(done, 1) - 1) / kRouteThreads * kRouteThreads + tid; q < done; q += kRouteThreads) {   // the last chunk
+        assigned[q] = s_out_i[q & (kRouteThreads - 1)];
+        score100[q] = s_out_s[q & (kRouteThreads - 1)];
+    }
+    if (mine && sub == 0) { queued_p[inst] = qp; current_d[inst] = cd; }
+#pragma unroll
+    for (int i = 0; i < kRegSlots; ++i) {
+        const int t = sub + tpi * i;
+        if (mine && t < window) window_tokens[(int64_t)inst * window + t] = r[i];
+    }
+    if (done == n_req) return;
+    __threadfence_block();                                      // the state as it stands is the scan's input
+    __syncthreads();
+    scan_walk(lds_raw, prompt_tokens + done, pred_tokens + done, done, n_req - done, n_inst, window, tpi, window_tokens, capacity,
+              queued_p, current_d, t_mem_pct, beta, assigned + done, score100 + done, st);
+}
+
+// Microseconds for n requests, scanned / with the tables (the tables take 5 us to make where a block is one piece of 4
+// slots, 30 to 60 where the wavefronts make them block by block):
+//   blocks of 4: 64 instances of 100 slots, n = 1 11 / 15, 64 221 / 47;  256 of 100, n = 1 14 / 18, 2048 6553 / 1585
+//   blocks of 8 and 16: 256 of 128, n = 1 16 / 54, 64 219 / 151;  64 of 500, n = 1 12 / 71, 64 221 / 152, 2048 6802 / 2706
+//   blocks of 32 and 48: 1024 of 29, n = 64 225 / 187;  16 of 1500, n = 64 227 / 253, 2048 6984 / 6053
+//   longer ones: 1 of 2000, n = 2048 6281 / 8372;  8 of 3000 11499 / 11415;  256 of 134 (one block each) 13979 / 15951
+bool tables_pay(int n_req, int window, int block) {
+    if (window == 0) return true;
+    return block == 4 ? n_req >= 3 : block <= 16 ? n_req >= 32 : block <= 48 && n_req >= 128;
+}
+
 }  // namespace
 
 extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens, int32_t n_req, int32_t n_inst,
@@ -327,16 +563,21 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     if (n_req == 0) return PS_OK;
     if (!prompt_tokens || !pred_tokens || !assigned || !score100) return PS_EINVAL;
     if (n_inst > kRouteThreads) return PS_EUNSUPPORTED;
-    // the limit the header states; every map within it has a plan that fits (plan_route's last one, a single block
-    // per window, takes less)
-    if ((size_t)n_inst * 20 + (size_t)n_inst * window * 4 + 20928 > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
+    // the limit the header states (what the scan keeps in LDS); every map within it has a plan that fits (plan_route's
+    // last one, a single block per window, takes less)
+    const size_t map_bytes = (size_t)n_inst * 20 + (size_t)n_inst * window * 4 + 20928;
+    if (map_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
     const RoutePlan p = plan_route(n_inst, window);
     if (p.lds_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
     static bool lds_attr_set = false;     // raising the limit twice is harmless, so no lock
     if (!lds_attr_set) {
-        if (hipFuncSetAttribute((const void*)route_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void*)route_scan_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_reg_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void*)route_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess)
@@ -347,8 +588,21 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     hipLaunchKernelGGL(route_kernel<SMALL>, dim3(1), dim3(kRouteThreads), p.lds_bytes, s, prompt_tokens, pred_tokens, \
                        n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens, capacity, queued_p,      \
                        current_d, t_mem_pct, beta, assigned, score100, status)
-    if (p.block == 4) PS_ROUTE(true);
-    else PS_ROUTE(false);
+    if (tables_pay(n_req, window, p.block)) {
+        if (p.block == 4) PS_ROUTE(true);
+        else PS_ROUTE(false);
+        return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
+    }
 #undef PS_ROUTE
+    int tpi = 64;                                               // threads per instance: a power of two, <= 64
+    while (tpi > 1 && (int64_t)tpi * n_inst > kRouteThreads) tpi >>= 1;
+    if ((window + tpi - 1) / tpi <= kRegSlots)
+        hipLaunchKernelGGL(route_reg_kernel, dim3(1), dim3(kRouteThreads), map_bytes, s, prompt_tokens, pred_tokens, n_req, n_inst,
+                           window, tpi, window_tokens, capacity, queued_p, current_d, t_mem_pct, beta, assigned,
+                           score100, status);
+    else
+        hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(kRouteThreads), map_bytes, s, prompt_tokens, pred_tokens, n_req,
+                           n_inst, window, tpi, window_tokens, capacity, queued_p, current_d, t_mem_pct, beta, assigned,
+                           score100, status);
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }

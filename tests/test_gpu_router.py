@@ -81,7 +81,10 @@ def test_missing_predictions_and_limits():
 @pytest.mark.parametrize("K,l,n", [(64, 128, 150), (65, 129, 150), (2, 4, 200), (3, 5, 200), (63, 1, 130), (128, 127, 64),
                                    (1024, 29, 70),        # fills the LDS: one block per window
                                    (256, 134, 66),        # larger blocks than the smallest, to fit
-                                   (7, 1000, 40), (1, 8000, 12), (2, 17000, 5)])
+                                   (7, 1000, 40), (1, 8000, 12), (2, 17000, 5),
+                                   # requests and blocks at which the scan of whole windows takes over
+                                   (64, 100, 1), (64, 100, 2), (64, 100, 3), (64, 500, 31), (64, 500, 32), (16, 1500, 127),
+                                   (16, 1500, 128), (2, 1536, 130), (2, 1537, 130), (1024, 29, 2), (33, 600, 33), (9, 0, 1)])
 def test_block_edges_and_full_lds(K, l, n):
     """The kernel keeps maxima per block of a window: predictions on, beside and beyond the block boundaries, maps of one
     wavefront and of several, and the largest maps the call accepts.  Integers: everything must match."""
