@@ -17,8 +17,13 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // K = 512 at 600 rows).  A workgroup owns TM x 32 rows and 32 columns; its four wavefronts split the contraction and
 // their sums are added through LDS in order.  In a group of eight k lane l holds four consecutive ones of its row of A
 // (one 16-byte load; lanes 32.. the upper four) and the same four rows of its column of W, a whole 128-byte line per
-// row; eight groups are requested before the first is used.  VEC: K a multiple of 8 and N of 32, so nothing is ragged.
-template <int EPI, int TM, bool VEC>
+// row; eight groups are requested before the first is used.  Where K is no multiple of 4 the 16-byte loads are aligned to
+// 4 bytes only (rows of A begin anywhere), which global loads may be.  TAIL: K is no multiple of 8; only the last group is
+// looked at element by element (testing all of them, and columns beyond N in the same way, cost 512 prompts of a model with
+// hidden 1000 26.3 ms, 13.4 so).
+struct __attribute__((packed, aligned(4))) Float4Any { float x, y, z, w; };
+
+template <int EPI, int TM, bool TAIL>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        const float* __restrict__ bias,
                                                        const float* __restrict__ residual, float* __restrict__ C,
@@ -29,42 +34,48 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 31, half = lane >> 5, n = n0 + row;
     const int groups = (K + 7) / 8, g0 = groups * wave / 4, g1 = groups * (wave + 1) / 4;
+    const int g1_whole = TAIL ? min(g1, K / 8) : g1;
     const float* ap = A + (int64_t)(m0 + row) * K + 4 * half;    // rows are always inside the padded buffer
-    const float* wp = W + (int64_t)(4 * half) * N + (VEC ? n : min(n, N - 1));
+    const float* wp = W + (int64_t)(4 * half) * N + min(n, N - 1);
     f32x16 acc[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
     constexpr int U = 8 / TM;
-    for (int g = g0; g < g1; g += U) {
+    for (int g = g0; g < g1_whole; g += U) {
         float a[U][TM][4], w[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = 8 * min(g + u, g1 - 1);               // (past the end: the last group again, not used)
+            const int k = 8 * min(g + u, g1_whole - 1);         // (past the end: the last group again, not used)
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                if (VEC) {
-                    const float4 v = *(const float4*)(ap + (int64_t)(32 * i) * K + k);
-                    a[u][i][0] = v.x; a[u][i][1] = v.y; a[u][i][2] = v.z; a[u][i][3] = v.w;
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) a[u][i][t] = k + 4 * half + t < K ? ap[(int64_t)(32 * i) * K + k + t] : 0.f;
-                }
+                const Float4Any v = *(const Float4Any*)(ap + (int64_t)(32 * i) * K + k);
+                a[u][i][0] = v.x; a[u][i][1] = v.y; a[u][i][2] = v.z; a[u][i][3] = v.w;
             }
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                w[u][t] = VEC || k + 4 * half + t < K ? wp[(int64_t)(k + t) * N] : 0.f;
+            for (int t = 0; t < 4; ++t) w[u][t] = wp[(int64_t)(k + t) * N];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (g + u < g1) {
+            if (g + u < g1_whole) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
                         acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i][t], w[u][t], acc[i], 0, 0, 0);
             }
+        }
+    }
+    if (TAIL && g1 > K / 8) {                                   // the last wavefront
+        const int k = K / 8 * 8;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool in = k + 4 * half + t < K;
+            const float w = in ? wp[(int64_t)(k + t) * N] : 0.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? ap[(int64_t)(32 * i) * K + k + t] : 0.f, w, acc[i], 0, 0, 0);
         }
     }
     // element e of a lane is row 8 (e / 4) + 4 half + e % 4, column lane % 32
@@ -76,7 +87,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int i = 0; i < 4 * TM; ++i) {
         const int r = 8 * i + (threadIdx.x >> 5), c = threadIdx.x & 31;
-        if (!VEC && n0 + c >= N) continue;
+        if (n0 + c >= N) continue;
         const int64_t at = (int64_t)(m0 + r) * N + n0 + c;
         float v = ((s_part[0][r][c] + s_part[1][r][c]) + (s_part[2][r][c] + s_part[3][r][c])) + bias[n0 + c];
         if (EPI == F32_GELU) v = 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
@@ -157,7 +168,7 @@ template <int EPI, int TM>
 void gemm_f32_rows(const float* A, const float* W, const float* bias, const float* res, float* C, int64_t max_rows, int N, int K,
                    const BatchMeta* meta, hipStream_t s) {
     const dim3 grid((unsigned)(max_rows / (32 * TM)), (unsigned)((N + 31) / 32));
-    if (N % 32 == 0 && K % 8 == 0)
+    if (K % 8 != 0)
         hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, true>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
     else
         hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, false>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);

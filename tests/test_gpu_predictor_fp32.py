@@ -169,7 +169,8 @@ def test_host_side_argument_errors(tmp_models):
     assert (info.layers, info.hidden, info.heads, info.ffn, info.vocab, info.dtype) == (2, 128, 2, 512, 8192, 0)
 
 
-@pytest.mark.parametrize("hidden,heads,ffn,n", [(8, 1, 8, 3), (24, 2, 40, 5), (96, 3, 32, 40), (32, 4, 264, 600), (65, 5, 33, 20)])
+@pytest.mark.parametrize("hidden,heads,ffn,n", [(8, 1, 8, 3), (24, 2, 40, 5), (96, 3, 32, 40), (32, 4, 264, 600), (65, 5, 33, 20), (66, 3, 70, 300), (33, 3, 36, 7),
+                                                (5, 1, 3, 9)])
 def test_matrix_tiles_at_their_edges(tmp_models, hidden, heads, ffn, n):
     """Contractions of fewer groups of eight than wavefronts, columns that do not fill a tile of 32, rows enough for the
     64-row tiles."""
