@@ -27,9 +27,9 @@ template <int EPI, int TM, bool TAIL>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        const float* __restrict__ bias,
                                                        const float* __restrict__ residual, float* __restrict__ C,
-                                                       int N, int K, const BatchMeta* meta) {
+                                                       int N, int K, int n_first, const BatchMeta* meta) {
     __shared__ float s_part[4][TM * 32][33];
-    const int m0 = blockIdx.x * 32 * TM, n0 = blockIdx.y * 32;
+    const int m0 = blockIdx.x * 32 * TM, n0 = n_first + blockIdx.y * 32;
     if (m0 >= meta->total_rows) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 31, half = lane >> 5, n = n0 + row;
@@ -167,11 +167,14 @@ __global__ __launch_bounds__(256) void layernorm_f32_kernel(const float* __restr
 template <int EPI, int TM>
 void gemm_f32_rows(const float* A, const float* W, const float* bias, const float* res, float* C, int64_t max_rows, int N, int K,
                    const BatchMeta* meta, hipStream_t s) {
-    const dim3 grid((unsigned)(max_rows / (32 * TM)), (unsigned)((N + 31) / 32));
-    if (K % 8 != 0)
-        hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, true>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
-    else
-        hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, false>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, meta);
+    const int most = 65535 * 32;                                 // columns a grid holds
+    for (int n_first = 0; n_first < N; n_first += most) {
+        const dim3 grid((unsigned)(max_rows / (32 * TM)), (unsigned)(((N - n_first < most ? N - n_first : most) + 31) / 32));
+        if (K % 8 != 0)
+            hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, true>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, n_first, meta);
+        else
+            hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, false>), grid, dim3(256), 0, s, A, W, bias, res, C, N, K, n_first, meta);
+    }
 }
 
 template <int EPI>

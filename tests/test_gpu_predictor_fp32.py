@@ -185,3 +185,15 @@ def test_matrix_tiles_at_their_edges(tmp_models, hidden, heads, ffn, n):
     assert flags == 0
     assert rel_err(got_f, ref_f).max() < TOL_FP32
     check_tokens(got_f, got_t, ref_t, cfg.d_max)
+
+
+def test_more_feed_forward_units_than_a_grid_has_tiles(tmp_models):
+    """2097152 + 100 feed-forward units: more tiles of 32 columns than one launch may have in a dimension."""
+    cfg = wl.ModelConfig(layers=1, hidden=2, heads=1, ffn=2097152 + 100, vocab=10, max_pos=8, head_hidden=3, dtype=wl.DTYPE_FP32)
+    model, ref = make(tmp_models, "wide.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    batch = wl.pack_prompts(np.array([3, 1], np.int32), np.array([1, 9, 4, 7], np.int32))
+    got_f, got_t, flags, _ = run_predict(model, batch)
+    ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
+    assert flags == 0
+    assert rel_err(got_f, ref_f).max() < TOL_FP32
+    check_tokens(got_f, got_t, ref_t, cfg.d_max)
