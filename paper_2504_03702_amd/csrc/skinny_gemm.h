@@ -146,9 +146,13 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
         const int share = wave * SH + sh;
         const int r_begin = share * total_rounds / kSkinnyShares, rounds = (share + 1) * total_rounds / kSkinnyShares - r_begin;
         const int k0 = 64 * r_begin + 16 * fq;
-        const bf16_t* ap = (NORM ? res.y_hi : p.A) + arow * lda + k0;
-        const bf16_t* lp = NORM ? res.y_lo + arow * lda + k0 : ap + K;
-        const bf16_t* wp = p.W + (int64_t)(n0 + frow) * K + k0;
+        // A share of no rounds (K below 512) makes its loads all the same, which keeps the schedule of the others, but all
+        // lanes from one place: a round's worth of W through the cache for nothing held a map of hidden 256 12 us, not 8.
+        const bool some = rounds > 0;
+        const int64_t a_at = some ? arow * lda + k0 : 0, wg_at = some ? wg : 0;
+        const bf16_t* ap = (NORM ? res.y_hi : p.A) + a_at;
+        const bf16_t* lp = NORM ? res.y_lo + a_at : ap + K;
+        const bf16_t* wp = p.W + (some ? (int64_t)(n0 + frow) * K + k0 : 0);
         sk_f32x4 acc[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -165,7 +169,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
                         if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
                     }
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg + 64 * t + 8 * h);
+                    for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg_at + 64 * t + 8 * h);
                 }
                 if (NORM) {
 #pragma unroll
