@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
 // ------------------------------------------------------------------------------------------
 const int kHeadWaves = 16;
 const int kHeadUnits = 4 * kHeadWaves;    // units of one round
-const int kHeadParts = 32;                // most workgroups per request
+const int kHeadSlots = 32;                // rounds whose sums are kept apart, so also the most workgroups per request
 
 __device__ __forceinline__ float head_block_sum(float v, float* s_red) {
     v = wave_sum(v);
@@ -268,10 +268,10 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
                                                    int H, int Hh,
                                                    const float* __restrict__ w_h1t, const float* __restrict__ b_h1,
                                                    const float* __restrict__ w_h2, float b_h2, int d_max,
-                                                   int parts, int slots, float* __restrict__ part_sum, int32_t* __restrict__ part_done,
+                                                   int parts, float* __restrict__ part_sum, int32_t* __restrict__ part_done,
                                                    float* __restrict__ pred_f, int32_t* __restrict__ pred_tokens,
                                                    ps_status* st) {
-    extern __shared__ float s_c[];           // [H], kHeadWaves partial sums, the rounds' sums
+    extern __shared__ float s_c[];           // [H], kHeadWaves partial sums, [kHeadWaves][kHeadSlots] the rounds' sums
     const int r = blockIdx.x / parts, part = blockIdx.x - r * parts;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (seq_len[r] <= 0 || bad_req[r]) {
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
     const int rd0 = rounds * part / parts, rd1 = rounds * (part + 1) / parts;
     const int u0 = rd0 * kHeadUnits;
     // every round's sum is kept apart (those from the last slot on together), so the result does not depend on `parts`
-    float* s_round = slots == 1 ? s_c + H : s_c + H + kHeadWaves;   // [wavefront][slots]
+    float* s_round = s_c + H + kHeadWaves;
     const bool wide = (H & 255) == 0 && H <= 2048;       // rows of whole 16-byte pieces per lane (all bf16 models)
     const int nch = H >> 8;
     float4 wv[4][4];
@@ -355,23 +355,23 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
                 acc += (d < 0.f ? 0.f : d) * w_h2[j];   // ReLU that lets a NaN through to the check below
             }
         }
-        float* slot = s_round + wave * slots + min(rd, slots - 1);
-        if (lane == 0) *slot = rd < slots ? acc : *slot + acc;
+        float* slot = s_round + wave * kHeadSlots + min(rd, kHeadSlots - 1);
+        if (lane == 0) *slot = rd < kHeadSlots ? acc : *slot + acc;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         float y = 0.f;
-        for (int i = min(rd0, slots); i < min(rd1, slots); ++i) {
+        for (int i = min(rd0, kHeadSlots); i < min(rd1, kHeadSlots); ++i) {
             float t = 0.f;
-            for (int w = 0; w < kHeadWaves; ++w) t += s_round[w * slots + i];
-            if (parts > 1) __hip_atomic_store(part_sum + (int64_t)r * kHeadParts + i, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int w = 0; w < kHeadWaves; ++w) t += s_round[w * kHeadSlots + i];
+            if (parts > 1) __hip_atomic_store(part_sum + (int64_t)r * kHeadSlots + i, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             y += t;
         }
         if (parts > 1) {
             if (__hip_atomic_fetch_add(part_done + r, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != parts - 1) return;
             y = 0.f;
             for (int i = 0; i < rounds; ++i)
-                y += __hip_atomic_load(part_sum + (int64_t)r * kHeadParts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                y += __hip_atomic_load(part_sum + (int64_t)r * kHeadSlots + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         y += b_h2;
         pred_f[r] = y;
@@ -431,22 +431,20 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
 void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* pred_f, int32_t* pred_tokens,
                  ps_status* st, hipStream_t s) {
     const ps_model_info& f = m->info;
-    // (fp32 models whose row nearly fills a workgroup's LDS keep one sum per wavefront, in the room of the reduction)
-    const int slots = f.hidden > 8192 ? 1 : kHeadParts;
-    const size_t lds = sizeof(float) * (size_t)(f.hidden + kHeadWaves + (slots > 1 ? kHeadWaves * slots : 0));
+    const size_t lds = sizeof(float) * (size_t)(f.hidden + kHeadWaves + kHeadWaves * kHeadSlots);   // (hidden <= 8192: 35 KB)
     // enough workgroups to fill the chip, a round of 64 units each at the least
     const int rounds = (f.head_hidden + kHeadUnits - 1) / kHeadUnits;
     int parts = 256 / n_req < rounds ? 256 / n_req : rounds;
-    if (parts < 1 || rounds > slots) parts = 1;
+    if (parts < 1 || rounds > kHeadSlots) parts = 1;
     const dim3 grid((unsigned)n_req * (unsigned)parts);
     if (f.dtype == 1)
         hipLaunchKernelGGL(head_kernel<bf16_t>, grid, dim3(kHeadWaves * 64), lds, s, (const bf16_t*)ws.x, ws.seq_len, ws.row_start,
                            ws.bad_req, (const bf16_t*)ws.la, (const float*)m->layers.back().ln2_g,
                            (const float*)m->layers.back().ln2_b, m->ln_eps, f.hidden, f.head_hidden, m->w_h1t, m->b_h1, m->w_h2,
-                           m->b_h2, f.d_max, parts, slots, ws.head_sum, ws.head_done, pred_f, pred_tokens, st);
+                           m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f, pred_tokens, st);
     else
         hipLaunchKernelGGL(head_kernel<float>, grid, dim3(kHeadWaves * 64), lds, s, (const float*)ws.x, ws.seq_len, ws.row_start,
                            ws.bad_req, (const bf16_t*)nullptr, (const float*)nullptr, (const float*)nullptr, 0.f, f.hidden,
-                           f.head_hidden, m->w_h1t, m->b_h1, m->w_h2, m->b_h2, f.d_max, parts, slots, ws.head_sum, ws.head_done, pred_f,
+                           f.head_hidden, m->w_h1t, m->b_h1, m->w_h2, m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f,
                            pred_tokens, st);
 }
