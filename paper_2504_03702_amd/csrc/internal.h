@@ -153,9 +153,9 @@ struct SkinnyArgs {
     float inv_n, eps;
 };
 void launch_skinny_gemm_bf16(GemmEpilogue epi, const SkinnyArgs& p, hipStream_t s);
-// The maps of calls with few activation rows (64 x 64 tiles, one workgroup each).  `side`, if not null, is the
-// per-request map of the same layer, done by further workgroups of the launch; rows of the residual stream that it
-// writes are left to it.  pstats_in, if not null: the statistics of the operand's rows are made from these pieces
+// The maps of calls with few activation rows (tiles of 64 x 64 to 128 x 128, one workgroup each).  `side`: for
+// EPI_BIAS_RESIDUAL, EPI_BIAS_GELU and EPI_KV the per-request map of the same layer, done by further workgroups of the
+// launch (null for the others); rows of the residual stream that it writes are left to it.  pstats_in, if not null: the statistics of the operand's rows are made from these pieces
 // and left in stats_out (res.stats otherwise).
 struct SmallGemm {
     const bf16_t *A, *W;

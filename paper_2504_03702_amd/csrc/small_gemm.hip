@@ -6,7 +6,8 @@
 // STAGES - 1 slices on their way to LDS (global_load_lds), so a slice costs its share of the unit's LDS and L2 rate and
 // not a trip to memory; a wavefront reads the fragments of the next slice while its MFMAs of the current one run.  The
 // accumulation order over k is that of the larger tiles and the epilogues are the same expressions, so the results are
-// equal to theirs to the last bit and the choice between the kernels is free.
+// equal to theirs to the last bit and the choice between the kernels is free.  (Not so for hi | lo rows, below: the two
+// parts' sums are formed apart and added, where one chain over 2K used to form them; the last digits differ.)
 //
 // Per-request maps of 64 requests (hidden 768 / 3072, hi | lo rows): 76 us a launch on the 128 x 128 tiles, 10.7 here.
 //
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
                 if (tn == 0 && cg == 0 && p.stats_out) p.stats_out[r] = st[it];
             }
         }
-        if (EPI == EPI_BIAS_RESIDUAL && SIDE != kNoSide) {
+        if (EPI == EPI_BIAS_RESIDUAL) {
             for (int q = 0; q < p.n_side; ++q)           // a request's first row is the side map's
                 if (p.row_start[q] == r && p.seq_len[q] > 0) live[it] = false;
         }
@@ -329,8 +330,8 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
 
 template <int EPI, int SIDE>
 void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
-    const int side_blocks = side ? (int)align_up((size_t)(side->N / kSkinnyCols), 8) : 0;
-    const SkinnyArgs sd = side ? *side : SkinnyArgs{};
+    const int side_blocks = SIDE != kNoSide ? (int)align_up((size_t)(side->N / kSkinnyCols), 8) : 0;
+    const SkinnyArgs sd = SIDE != kNoSide ? *side : SkinnyArgs{};
     constexpr int kParts = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED ? 2 : 1;   // rows of the tile per row of the result
     auto tiles = [&](int bm, int bn) { return (p.max_rows * kParts + bm - 1) / bm * (p.N / bn); };
     auto grid = [&](int bm, int bn) { return dim3((unsigned)(side_blocks + (tiles(bm, bn) + 7) / 8 * 8)); };
@@ -359,23 +360,15 @@ void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
 }  // namespace
 
 // Requirements: N % 64 == 0, K % 128 == 0; every buffer holds max_rows rows with max_rows % 64 == 0 (whole tiles are
-// in bounds).  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED take A as [rows][2K] (hi | lo).  The side map, where there is one: EPI_RESIDUAL_MAPPED beside EPI_BIAS_RESIDUAL, EPI_GELU_SPLIT beside
-// EPI_BIAS_GELU, EPI_Q_MAPPED beside EPI_KV.
+// in bounds).  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED take A as [rows][2K] (hi | lo).  Three maps come with a side map:
+// EPI_BIAS_RESIDUAL with EPI_RESIDUAL_MAPPED, EPI_BIAS_GELU with EPI_GELU_SPLIT, EPI_KV with EPI_Q_MAPPED; the others with
+// none.
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     switch (epi) {
         case EPI_QKV: launch<EPI_QKV, kNoSide>(p, nullptr, s); break;
-        case EPI_BIAS_RESIDUAL:
-            if (side) launch<EPI_BIAS_RESIDUAL, EPI_RESIDUAL_MAPPED>(p, side, s);
-            else launch<EPI_BIAS_RESIDUAL, kNoSide>(p, nullptr, s);
-            break;
-        case EPI_BIAS_GELU:
-            if (side) launch<EPI_BIAS_GELU, EPI_GELU_SPLIT>(p, side, s);
-            else launch<EPI_BIAS_GELU, kNoSide>(p, nullptr, s);
-            break;
-        case EPI_KV:
-            if (side) launch<EPI_KV, EPI_Q_MAPPED>(p, side, s);
-            else launch<EPI_KV, kNoSide>(p, nullptr, s);
-            break;
+        case EPI_BIAS_RESIDUAL: launch<EPI_BIAS_RESIDUAL, EPI_RESIDUAL_MAPPED>(p, side, s); break;
+        case EPI_BIAS_GELU: launch<EPI_BIAS_GELU, EPI_GELU_SPLIT>(p, side, s); break;
+        case EPI_KV: launch<EPI_KV, EPI_Q_MAPPED>(p, side, s); break;
         case EPI_GELU_SPLIT: launch<EPI_GELU_SPLIT, kNoSide>(p, nullptr, s); break;
         case EPI_RESIDUAL_MAPPED: launch<EPI_RESIDUAL_MAPPED, kNoSide>(p, nullptr, s); break;
         case EPI_Q_MAPPED: launch<EPI_Q_MAPPED, kNoSide>(p, nullptr, s); break;
