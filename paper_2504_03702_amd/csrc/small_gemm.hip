@@ -339,7 +339,8 @@ void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     hipLaunchKernelGGL((small_gemm_kernel<EPI, TM, TN, STAGES, SIDE>), grid(64 * TM, 64 * TN), dim3(256), 0, s, p, sd, side_blocks)
     // At most one 64 x 64 tile per compute unit: a unit to itself, seven slices on their way.  Beyond that what the unit
     // reads from LDS and L2 per product counts: 128 x 64 tiles, two to a unit (1536 rows of hidden 768, the query-key-value
-    // map 18.5 -> 16.0 us, the second feed-forward map 31.7 -> 26.0).  The maps back to the hidden width have few columns
+    // map, 468 tiles for 512 places, 18.5 -> 16.0 us, the second feed-forward map 31.7 -> 26.0; where the tiles just pass the
+    // places, 540 at 1782 rows, the second wave shows: 22 us).  The maps back to the hidden width have few columns
     // and a long contraction: 128 x 128 with three slices on their way once that still gives every other unit a tile
     // (1922 rows of hidden 1024: 54.5 -> 44.5 us).
     constexpr bool kResid = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_RESIDUAL_MAPPED;
