@@ -90,6 +90,13 @@ __global__ __launch_bounds__(256) void ln_stats_gather_kernel(const float2* __re
 // 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
 #define PS_FUSED_ROWS 3584
 
+// The first feed-forward map of the per-request pass: the small tiles read W once for both halves of the operand but
+// take two passes' worth of places; beyond 1024 of their 128 x 64 tiles (two waves of the chip's 512 places) the large
+// kernel's 128 x 128 tiles are faster, with the same bits.  Small against large: hidden 768 (ffn 3072) 1280 requests, 960
+// tiles, 24.6 / 24.8 us, 1536 30.4 / 28.1, 4096 90 / 57, 20000 409 / 234; hidden 1024 (ffn 4096) 1024 requests, 1024
+// tiles, 29.3 / 30.7, 1280 36.0 / 35.6, 4096 150 / 81.
+#define PS_SPLIT_TILES 1024
+
 void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hipStream_t s) {
     const ps_model_info& f = m->info;
     const int H = f.hidden, F = f.ffn;
@@ -228,7 +235,11 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
                                                        nullptr, ws.max_rows, H, F, H, rows, clk, s));
             }
-            PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
+            if (ws.cls_rows / 64 * (F / 64) > PS_SPLIT_TILES)
+                PS_TIMED(PS_FAM_REFINE, launch_gemm_bf16(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, (const bf16_t*)w.w_1d, w.b_1, none,
+                                                         ws.cls_g, nullptr, ws.cls_rows, F, 2 * H, H, n_req_dev, nullptr, s));
+            else
+                PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F));
         }
         if (!last && !fused)                             // (the head makes the last LayerNorm's statistics itself)

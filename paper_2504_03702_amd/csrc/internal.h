@@ -129,7 +129,7 @@ struct ResidualSrc {
     // `stats` are the statistics of the operand's rows, colsum is c above and the bias argument is d
     const float* colsum;
 };
-// C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K]; rows = *total_rows (device).
+// C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
 // The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,
 // may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,

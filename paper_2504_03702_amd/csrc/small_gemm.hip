@@ -6,8 +6,8 @@
 // STAGES - 1 slices on their way to LDS (global_load_lds), so a slice costs its share of the unit's LDS and L2 rate and
 // not a trip to memory; a wavefront reads the fragments of the next slice while its MFMAs of the current one run.  The
 // accumulation order over k is that of the larger tiles and the epilogues are the same expressions, so the results are
-// equal to theirs to the last bit and the choice between the kernels is free.  (Not so for hi | lo rows, below: the two
-// parts' sums are formed apart and added, where one chain over 2K used to form them; the last digits differ.)
+// equal to theirs to the last bit and the choice between the kernels is free.  (Of hi | lo rows, below, both form the two
+// parts' sums apart and add them; one chain over 2K would differ in the last digits.)
 //
 // Per-request maps of 64 requests (hidden 768 / 3072, hi | lo rows): 76 us a launch on the 128 x 128 tiles, 10.7 here.
 //

@@ -8,7 +8,7 @@ import pytest
 
 from paper_2504_03702_amd import workloads as wl
 from tests.gpu_util import run_predict
-from tests.test_gpu_predictor_bf16 import SMALL, check, make
+from tests.test_gpu_predictor_bf16 import SMALL, check, chunks_bit_equal, make
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,19 @@ def test_head_rounds(tmp_models, head_hidden):
     got = check(model, ref, batch)
     few = wl.pack_prompts(lengths[:17], ids[:batch.offsets[17]])
     assert np.array_equal(check(model, ref, few), got[:17])
+
+
+@pytest.mark.parametrize("n_req", [1024, 1025, 1281, 2100])
+def test_many_requests_take_large_tiles(tmp_models, n_req):
+    """4096 feed-forward units: above 1024 requests the per-request map goes to the large kernel's 128 x 128 tiles.  The
+    requests' bits must be those of calls of 500, and the oracle bounds them."""
+    print(f"predict many requests n={n_req}", flush=True)
+    cfg = dataclasses.replace(SMALL, ffn=4096)
+    model, ref = make(tmp_models, "many_requests.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(n_req)
+    lengths = rng.integers(1, 6, n_req).astype(np.int32)
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    check(model, ref, batch)
+    got, tokens, flags, _ = run_predict(model, batch)
+    assert flags == 0
+    chunks_bit_equal(model, batch, got, tokens, chunk=500)
