@@ -168,7 +168,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                                                                             stats_in, ws.sa), nullptr, s));
             else
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_QKV, x, (const bf16_t*)w.w_qkv, w.b_qkv, fold_qkv, qk, vt,
-                                                       ws.max_rows, 3 * H, H, H, qkv_rows, clk, s));
+                                                       ws.max_rows, 3 * H, H, H, qkv_rows, &ws.meta->plan[PS_PLAN_QKV], clk, s));
         } else {
             // keys and values of all rows; queries of the requests' first rows only, by a side GEMM on
             // those rows gathered into the (not yet used) first-row buffer
@@ -180,7 +180,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                                                                            2 * H, H, qkv_rows, stats_in, ws.sa), &q, s));
             } else {
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_KV, x, (const bf16_t*)w.w_qkv + (size_t)H * H, w.b_qkv + H, fold_kv,
-                                                       qk, vt, ws.max_rows, 2 * H, H, H, qkv_rows, clk, s));
+                                                       qk, vt, ws.max_rows, 2 * H, H, H, qkv_rows, &ws.meta->plan[PS_PLAN_KV], clk, s));
                 if (skinny) {
                     PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_Q_MAPPED, skinny_args(x, w.w_qkv, w.b_qkv, first_rows, qk, H, H,
                                                                                               SKINNY_STATS_GIVEN, nullptr), s));
@@ -211,14 +211,14 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
             } else {
                 if (!last)
                     PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
-                                                           nullptr, ws.max_rows, H, H, H, rows, clk, s));
+                                                           nullptr, ws.max_rows, H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
                 if (!last) {
                     PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, nullptr));
                     PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
-                                                           ws.max_rows, F, H, H, rows, clk, s));
+                                                           ws.max_rows, F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s));
                     PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
-                                                           nullptr, ws.max_rows, H, F, H, rows, clk, s));
+                                                           nullptr, ws.max_rows, H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
                 }
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
@@ -226,18 +226,18 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
         } else {
             if (!last)
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
-                                                       nullptr, ws.max_rows, H, H, H, rows, clk, s));
+                                                       nullptr, ws.max_rows, H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H));
             PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, !last, &ffn_cls));
             if (!last) {
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
-                                                       ws.max_rows, F, H, H, rows, clk, s));
+                                                       ws.max_rows, F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s));
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
-                                                       nullptr, ws.max_rows, H, F, H, rows, clk, s));
+                                                       nullptr, ws.max_rows, H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
             }
             if (ws.cls_rows / 64 * (F / 64) > PS_SPLIT_TILES)
                 PS_TIMED(PS_FAM_REFINE, launch_gemm_bf16(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, (const bf16_t*)w.w_1d, w.b_1, none,
-                                                         ws.cls_g, nullptr, ws.cls_rows, F, 2 * H, H, n_req_dev, nullptr, s));
+                                                         ws.cls_g, nullptr, ws.cls_rows, F, 2 * H, H, n_req_dev, nullptr, nullptr, s));
             else
                 PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_GELU_SPLIT, (const bf16_t*)ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H));
             PS_TIMED(PS_FAM_REFINE, side_gemm(EPI_RESIDUAL_MAPPED, (const bf16_t*)ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F));

@@ -41,80 +41,107 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 template <int BM, int BN, int WM, int WN>
 struct Tile {
+    static_assert(WM == 2, "two rows of wavefronts: the lower one may have fewer blocks");
     static constexpr int NW = WM * WN;               // wavefronts per workgroup
     static constexpr int THREADS = NW * 64;
-    static constexpr int TM = BM / WM / 32;          // 32 x 32 accumulator tiles per wavefront
+    static constexpr int TM = BM / WM / 32;          // 32 x 32 accumulator blocks of a wavefront, at most
     static constexpr int TN = BN / WN / 32;
     static constexpr int A_BYTES = BM * 128;         // one 64-deep slice
     static constexpr int B_BYTES = BN * 128;
+    static constexpr int STAGE = A_BYTES + B_BYTES;  // an A slice followed by a W slice
+    static constexpr int EPI_BYTES = 4096;           // per-wavefront transpose region of the epilogue
+    static constexpr int LDS = 2 * STAGE + NW * EPI_BYTES;
     static_assert(NW % 2 == 0 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile / wave split");
+    static_assert(LDS <= 160 * 1024, "LDS budget");
 };
 
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const float* __restrict__ bias,
-    ResidualSrc res, void* __restrict__ Cv, bf16_t* __restrict__ Vt, int64_t vt_ld,
-    int N, int K, int hidden, const int32_t* __restrict__ total_rows, int64_t* __restrict__ clk) {
-    using T = Tile<BM, BN, WM, WN>;
-    constexpr int STAGE = T::A_BYTES + T::B_BYTES;      // an A slice followed by a W slice
-    constexpr int EPI_BYTES = 4096;                     // per-wavefront transpose region of the epilogue
-    static_assert(2 * STAGE + T::NW * EPI_BYTES <= 160 * 1024, "LDS budget");
-    __shared__ __align__(1024) unsigned char smem[2 * STAGE + T::NW * EPI_BYTES];
+// Every DMA of this wavefront has landed, and every wavefront is past its LDS reads.
+__device__ __forceinline__ void dma_barrier() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
-    // the wavefront index is uniform; saying so keeps everything derived from it in scalar registers
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+struct GemmArgs {
+    const bf16_t *A, *W;
+    const float* bias;
+    ResidualSrc res;
+    void* C;
+    bf16_t* Vt;
+    int64_t max_rows;            // rows of every activation buffer; also the row stride of Vt
+    int N, K, hidden;
+};
 
-    // ---- this workgroup's tiles --------------------------------------------------------------
-    // The grid is persistent (one workgroup per compute unit).  The hardware deals workgroups to the 8
-    // XCDs round-robin, so workgroup b runs on XCD b % 8 as its slot b / 8.  Each XCD has its own L2:
-    // the tiles in flight on one XCD should share operand panels, and panels should stay there.
-    // A workgroup walks its tiles (tm, tn) by one rule: tn += step_n, tm += step_m, and when tn passes
-    // the last tile column it wraps and tm += wrap_m.  Three walks use it:
-    //  * large problems whose tile columns come in P groups of 4: the 32 workgroups of an XCD form an
-    //    8 x 4 block of tiles, the fewest distinct panels for 32 tiles.
-    //      - P divides 8: XCD x keeps column group x % P for the whole launch, so that group's weights
-    //        (4 x 256 rows of W) stay in its L2, and walks down the row blocks x / P, x / P + 8 / P, ...;
-    //        the P XCDs that need a row block work on it at the same time, so it comes from HBM once
-    //        and from the memory-side cache for the others.
-    //      - otherwise: XCD x takes row blocks x, x + 8, ... and visits the P column groups of each in
-    //        turn (the row block is re-read from the memory-side cache, the weights rotate).
-    //  * anything else (few tile rows, odd column counts, small grids): XCD x works through the contiguous
-    //    run of tiles [x * per_xcd, (x + 1) * per_xcd), n fastest, its workgroups taking every slots-th.
-    const int rows = *total_rows;
-    const int n_tiles = N / BN, m_tiles = (rows + BM - 1) / BM;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
-    int tm, tn, step_m, step_n, wrap_m, n_my;                // first tile, walk, number of tiles of this workgroup
-    if (slots == 32 && m_tiles >= 64 && (n_tiles & 3) == 0) {
-        const int P = n_tiles >> 2;
-        if ((8 % P) == 0) {
-            tm = (xcd / P) * 8 + (slot >> 2);
-            tn = (xcd % P) * 4 + (slot & 3);
-            step_m = 64 / P; step_n = 0; wrap_m = 0;
-            n_my = tm < m_tiles ? (m_tiles - tm + step_m - 1) / step_m : 0;
-        } else {
-            tm = xcd * 8 + (slot >> 2);
-            tn = slot & 3;
-            step_m = 0; step_n = 4; wrap_m = 64;
-            n_my = tm < m_tiles ? P * ((m_tiles - tm + 63) / 64) : 0;
-        }
-    } else {
-        const int tiles = m_tiles * n_tiles;
-        const int per_xcd = (tiles + 7) >> 3;
-        const int first = xcd * per_xcd + slot, end = min((xcd + 1) * per_xcd, tiles);
-        tm = first / n_tiles; tn = first % n_tiles;
-        step_m = slots / n_tiles; step_n = slots % n_tiles; wrap_m = 1;
-        n_my = first < end ? (end - first + slots - 1) / slots : 0;
+// One region of the output: the rows from row_begin on, in tiles of bm rows (32 for each of the 2 x TM blocks of the two
+// rows of wavefronts; wavefront row 0 has tm0 of them, this wavefront TM).
+struct Region {
+    int row_begin, bm, tm0, m_tiles;
+    int rows;                    // rows of the whole problem
+};
+
+// The tiles of a region that this workgroup computes.  The grid is persistent.  The hardware deals workgroups to the 8 XCDs
+// round-robin, so workgroup b runs on XCD b % 8 as its slot b / 8.  Each XCD has its own L2: the tiles in flight on one XCD
+// should share operand panels.  Tiles are numbered in bands of 8 tile rows, column by column within a band (up to 3 columns
+// row by row), and in every round of the grid an XCD takes a run of `slots` consecutive numbers.  Columns in P groups of 4
+// make a run of 32 an 8 x 4 block, the fewest distinct panels for 32 tiles.  Which run:
+//  * P divides 8: the XCDs' runs follow each other, so an XCD keeps its column group for the whole region (4 x 256 rows of
+//    W stay in its L2) and the P XCDs that need a band work on it at the same time: it comes from HBM once and from the
+//    memory-side cache for the others.
+//  * P does not: an XCD takes bands x, x + 8, ... and the P column groups of each in turn.
+//  * other column counts: every XCD goes through a range of its own (hidden 768, query-key-value map, 250 k rows: 895 us,
+//    row by row 935).
+// The tiles of the last round are dealt to the XCDs evenly, so every workgroup gets the same number of tiles to one (P = 3
+// in whole bands per XCD, as it used to be: the first feed-forward map of 100 k rows of hidden 768 549 us, 523 so).
+struct Walk {
+    int n_tiles, m_tiles, slots, xcd, slot, full, rest, n_my;
+    __device__ __forceinline__ Walk(int m, int n) : n_tiles(n), m_tiles(m) {
+        xcd = blockIdx.x & 7; slot = blockIdx.x >> 3; slots = gridDim.x >> 3;
+        const int tiles = m * n;
+        full = tiles / (int)gridDim.x;
+        rest = tiles - full * (int)gridDim.x;
+        const int per = (rest + 7) >> 3;
+        n_my = full + (slot < per && xcd * per + slot < rest ? 1 : 0);
     }
+    // row and column of this workgroup's tile `round`
+    __device__ __forceinline__ void tile(int round, int& tm, int& tn) const {
+        int run = xcd * full + round;
+        if ((n_tiles & 3) == 0) {
+            const int P = n_tiles >> 2, done = 8 % P == 0 ? 0 : full / P * P;
+            run = round < done ? (round / P * 8 + xcd) * P + round % P : round * 8 + xcd;
+        }
+        const int id = round < full ? run * slots + slot : full * (int)gridDim.x + xcd * ((rest + 7) >> 3) + slot;
+        const int high = n_tiles < 4 ? 1 : 8;
+        const int band = id / (high * n_tiles), in = id - band * high * n_tiles, rb = min(high, m_tiles - high * band);
+        tn = in / rb;
+        tm = high * band + in - tn * rb;
+    }
+};
+
+// All tiles of a region that belong to this workgroup, by one of its wavefronts; TM: the wavefront's 32-row blocks.
+template <typename T, int WN, int TM, int EPI>
+__device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                             const float* __restrict__ bias, void* __restrict__ Cv, bf16_t* __restrict__ Vt,
+                                             const Region& rg_, unsigned char* smem) {
+    constexpr int STAGE = T::STAGE, EPI_BYTES = T::EPI_BYTES, BN = 32 * T::TN * WN;
+    const ResidualSrc& res = g.res;
+    const int64_t vt_ld = g.max_rows;
+    const int N = g.N, K = g.K, hidden = g.hidden, rows = rg_.rows;
+
+    // (a copy the compiler takes for new: nothing derived from it is kept across the regions)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    // the wavefront index is uniform; saying so keeps everything derived from it in scalar registers
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int wave_row = wm * rg_.tm0 * 32;                  // the wavefront's first row in a tile
+
+    const Walk walk(rg_.m_tiles, N / BN);
+    const int n_my = walk.n_my;
     if (n_my == 0) return;
-    auto walk = [&](int& m, int& n) {
-        n += step_n; m += step_m;
-        const bool wrap = n >= n_tiles;
-        n -= wrap ? n_tiles : 0;
-        m += wrap ? wrap_m : 0;
-    };
-    // clock probe (profiling only): core cycles and constant-rate ticks over this workgroup's life
-    const int64_t clk_c0 = clk ? (int64_t)clock64() : 0, clk_w0 = clk ? (int64_t)wall_clock64() : 0;
+    // first row of a tile; the last tile is moved up where it would pass the end of the buffers (rows of two tiles are
+    // written twice with the same values)
+    const int last_m0 = (int)g.max_rows - rg_.bm;
+    auto row_of = [&](int tm) { return min(rg_.row_begin + tm * rg_.bm, last_m0); };
 
     // ---- DMA sources: lane i of a wavefront fetches chunk (i%8)^swz of row i/8 of its group ----
     const int dma_row = wave * 8 + (lane >> 3);
@@ -131,16 +158,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
 
     // ---- fragment addresses: row (lane%32) of a 32-row tile, chunks 2*ks + lane/32 ----------
     const int frow = lane & 31, fhalf = lane >> 5;
-    const int a_off = (wm * (BM / WM) + frow) * 128;
+    const int a_off = (wave_row + frow) * 128;
     const int b_off = (wn * (BN / WN) + frow) * 128;
     int koff[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) koff[ks] = ((2 * ks + fhalf) ^ lds_swz(frow)) * 16;
 
-    f32x16 acc[T::TM][T::TN];
+    f32x16 acc[TM][T::TN];
     auto clear_acc = [&]() {
 #pragma unroll
-        for (int i = 0; i < T::TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < T::TN; ++j)
 #pragma unroll
@@ -158,23 +185,25 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
     // Slices g+1 and g+2 may belong to the next tile: its first two slices land while this tile
     // finishes and runs its epilogue (which has an LDS region of its own), so a tile starts with
     // its operands already in LDS.
-    bf16x8 fa0[T::TM], fb0[T::TN], fa1[T::TM], fb1[T::TN];
+    bf16x8 fa0[TM], fb0[T::TN], fa1[TM], fb1[T::TN];
     auto read_frags = [&](bf16x8* fa, bf16x8* fb, const unsigned char* stage, int ks) {
         const unsigned char* sA = stage + a_off + koff[ks];
         const unsigned char* sB = stage + T::A_BYTES + b_off + koff[ks];
 #pragma unroll
-        for (int i = 0; i < T::TM; ++i) fa[i] = *(const bf16x8*)(sA + i * 4096);
+        for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8*)(sA + i * 4096);
 #pragma unroll
         for (int j = 0; j < T::TN; ++j) fb[j] = *(const bf16x8*)(sB + j * 4096);
     };
     const int nk = K / 64;
-    // Prefetch cursor: the next slice to fetch is slice pf_kt of tile (pf_m, pf_n), the pf_it-th of this
-    // workgroup.  Once its tiles are used up the cursor parks on the first tile of the problem: the
-    // DMAs stay unconditional (straight-line code the scheduler can interleave with the MFMAs) and the
-    // parked ones refill LDS stages nobody reads any more.
-    int pf_it = 0, pf_m = tm, pf_n = tn, pf_kt = 0, pf_stage = 0;
-    const unsigned char* pf_a = (const unsigned char*)(A + (int64_t)pf_m * BM * K);
-    const unsigned char* pf_w = (const unsigned char*)(W + (int64_t)pf_n * BN * ldw);
+    // Prefetch cursor: the next slice to fetch is slice pf_kt of the tile at (pf_a, pf_w).  It runs up to two slices ahead of
+    // the products, so it enters the next tile, at (nx_a, nx_w), while they finish this one.  Once the workgroup's tiles are
+    // used up it parks on the region's first tile: the DMAs stay unconditional (straight-line code the scheduler can
+    // interleave with the MFMAs) and the parked ones refill LDS stages nobody reads any more.
+    int pf_kt = 0, pf_stage = 0, tm, tn;
+    walk.tile(0, tm, tn);
+    auto a_of = [&](int m) { return (const unsigned char*)(A + (int64_t)row_of(m) * K); };
+    auto w_of = [&](int n) { return (const unsigned char*)(W + (int64_t)n * BN * ldw); };
+    const unsigned char *pf_a = a_of(tm), *pf_w = w_of(tn), *nx_a = pf_a, *nx_w = pf_w;
     // The DMA of a slice is issued in two halves, A rows then W rows, each spread among the MFMAs of
     // one k-step: a wavefront that queues all of a slice's DMA instructions at once waits at the
     // memory pipeline's issue queue and issues no MFMA meanwhile.
@@ -194,16 +223,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
         pf_stage ^= 1;
         const bool last = ++pf_kt == nk;
         pf_kt = last ? 0 : pf_kt;
-        pf_it += last ? 1 : 0;
-        int nm = pf_m, nn = pf_n;
-        walk(nm, nn);
-        const bool parked = pf_it >= n_my;
-        pf_m = parked ? 0 : last ? nm : pf_m;
-        pf_n = parked ? 0 : last ? nn : pf_n;
-        pf_a = (const unsigned char*)(A + (int64_t)pf_m * BM * K);
-        pf_w = (const unsigned char*)(W + (int64_t)pf_n * BN * ldw);
+        pf_a = last ? nx_a : pf_a;
+        pf_w = last ? nx_w : pf_w;
     };
-    constexpr int NDMA_A = BM / 8 / T::NW, NDMA_W = BN / 8 / T::NW;
+    // wavefronts of the upper row move as many 8-row groups more as they have blocks more
+    constexpr int NDMA_A = TM * 8 / T::NW, NDMA_W = BN / 8 / T::NW;
 
     // One k-step in exact issue order (the scheduler may not move anything across the fences): in
     // each of TM + TN rounds one fragment read for the next step, at most one DMA, and a share of this
@@ -211,14 +235,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
     auto k_step = [&](const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb, const unsigned char* rd_stage,
                       int rd_ks, auto dma_tag) {
         constexpr int DMA = decltype(dma_tag)::value;
-        constexpr int nR = T::TM + T::TN, nM = T::TM * T::TN;
+        constexpr int nR = TM + T::TN, nM = TM * T::TN;
         static_assert(NDMA_A <= nR && NDMA_W <= nR, "one DMA per round");
         const unsigned char* sA = rd_stage + a_off + koff[rd_ks];
         const unsigned char* sB = rd_stage + T::A_BYTES + b_off + koff[rd_ks];
 #pragma unroll
         for (int r = 0; r < nR; ++r) {
-            if (r < T::TM) na[r] = *(const bf16x8*)(sA + r * 4096);
-            else nb[r - T::TM] = *(const bf16x8*)(sB + (r - T::TM) * 4096);
+            if (r < TM) na[r] = *(const bf16x8*)(sA + r * 4096);
+            else nb[r - TM] = *(const bf16x8*)(sB + (r - TM) * 4096);
             if (DMA == 1 && r < NDMA_A) prefetch_a(r);
             if (DMA == 2 && r < NDMA_W) prefetch_w(r);
             // MFMAs [r * nM / nR, (r + 1) * nM / nR) of the step, in row-major order of the wavefront's tiles
@@ -238,16 +262,22 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
 #pragma unroll
     for (int j = 0; j < NDMA_W; ++j) prefetch_w(j);
     advance_cursor();
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
+    dma_barrier();
 #pragma unroll
     for (int j = 0; j < NDMA_A; ++j) prefetch_a(j);
     read_frags(fa0, fb0, smem, 0);
     int stage = 0;
     float* stg = (float*)(smem + 2 * STAGE + wave * EPI_BYTES);
-    constexpr int WTM = BM / WM, WTN = BN / WN;
+    constexpr int WTN = BN / WN;
 
-    for (int it = 0; it < n_my; ++it, walk(tm, tn)) {
+    for (int it = 0; it < n_my; ++it) {
+        const int m_base = row_of(tm) + wave_row, n0 = tn * BN, n_base = n0 + wn * WTN;
+        int tm2, tn2;
+        walk.tile(it + 1 < n_my ? it + 1 : 0, tm2, tn2);
+        nx_a = a_of(tm2);
+        nx_w = w_of(tn2);
+        tm = tm2;
+        tn = tn2;
         auto contract = [&](int slices) {
             clear_acc();
             for (int kt = 0; kt < slices; ++kt) {
@@ -258,23 +288,22 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
                 advance_cursor();
                 k_step(fa1, fb1, fa0, fb0, cur, 2, NoDma{});
                 k_step(fa0, fb0, fa1, fb1, cur, 3, NoDma{});
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
+                dma_barrier();
                 // reads the step-0 fragments of the next slice, of this tile or of the next one (after the
                 // last slice of all: of a stage nobody needs); + A half of the slice two after this one
                 k_step(fa1, fb1, fa0, fb0, nxt, 0, ADma{});
             }
         };
         if constexpr (SPLIT) {
-            f32x16 hi[T::TM][T::TN];
+            f32x16 hi[TM][T::TN];
             contract(nk / 2);
 #pragma unroll
-            for (int i = 0; i < T::TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) hi[i][j] = acc[i][j];
             contract(nk / 2);
 #pragma unroll
-            for (int i = 0; i < T::TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) acc[i][j] = hi[i][j] + acc[i][j];
         } else {
@@ -286,8 +315,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
         // + e % 4, col = 32 j + lane % 32: a lane holds one column.  Each wavefront transposes through
         // its private 4 KB of LDS: it writes a strip of accumulators, reads it back with 16 bytes of
         // consecutive output per lane, applies the epilogue there and issues 16-byte global accesses.
-        const int m0 = tm * BM, n0 = tn * BN;
-        const int m_base = m0 + wm * WTM, n_base = n0 + wn * WTN;
+
+        // (a copy of the lane index that the compiler takes for new: what is derived from it is worked out here for every
+        // tile, and no register holds it through the contraction)
+        int el = lane;
+        asm volatile("" : "+v"(el));
+        const int ecol = el & 31, ehalf = el >> 5;
 
         // first value column of this launch's W: after the query and key columns, or after the key columns
         const int v_col0 = EPI == EPI_KV ? hidden : 2 * hidden;
@@ -296,42 +329,42 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
             // [32 features][32 rows]; the 16-byte chunks of a feature's rows are XOR-swizzled with the
             // feature index so the 128-byte-strided writes of the 32 lanes spread over the banks.  Read
             // back, a lane holds 8 consecutive rows of one feature: the folded LayerNorm is finished there.
-            const int rg = lane & 3;
+            const int rg = el & 3;
             float cc[T::TN][2], dd[T::TN][2];
 #pragma unroll
             for (int j = 0; j < T::TN; ++j)
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
-                    const int c = n_base + 32 * j + (lane >> 2) + 16 * it;
+                    const int c = n_base + 32 * j + (el >> 2) + 16 * it;
                     cc[j][it] = res.colsum[c];
                     dd[j][it] = bias[c];
                 }
-            float2 sv[2][8];                         // statistics of the lane's 8 rows, tile row i and i + 1
+            float2 sv[8];                            // statistics of the lane's 8 rows of block i
             auto fetch_sv = [&](int i) {
 #pragma unroll
-                for (int r = 0; r < 8; ++r) sv[i & 1][r] = res.stats[m_base + 32 * i + 8 * rg + r];
+                for (int r = 0; r < 8; ++r) sv[r] = res.stats[m_base + 32 * i + 8 * rg + r];
             };
             fetch_sv(0);
 #pragma unroll
-            for (int i = 0; i < T::TM; ++i) {
-                if (i + 1 < T::TM) fetch_sv(i + 1);
+            for (int i = 0; i < TM; ++i) {
                 float rs[8], nm[8];
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    rs[r] = sv[i & 1][r].y;
-                    nm[r] = -sv[i & 1][r].x * sv[i & 1][r].y;
+                    rs[r] = sv[r].y;
+                    nm[r] = -sv[r].x * sv[r].y;
                 }
+                if (i + 1 < TM) fetch_sv(i + 1);
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) {
 #pragma unroll
                     for (int e4 = 0; e4 < 4; ++e4) {
                         const f32x16& a = acc[i][j];
-                        *(float4*)(stg + frow * 32 + 4 * ((2 * e4 + fhalf) ^ (frow & 7))) =
+                        *(float4*)(stg + ecol * 32 + 4 * ((2 * e4 + ehalf) ^ (ecol & 7))) =
                             make_float4(a[4 * e4], a[4 * e4 + 1], a[4 * e4 + 2], a[4 * e4 + 3]);
                     }
 #pragma unroll
                     for (int it = 0; it < 2; ++it) {
-                        const int c = (lane >> 2) + 16 * it;
+                        const int c = (el >> 2) + 16 * it;
                         const float4 lo = *(const float4*)(stg + c * 32 + 4 * ((2 * rg) ^ (c & 7)));
                         const float4 hi = *(const float4*)(stg + c * 32 + 4 * ((2 * rg + 1) ^ (c & 7)));
                         const float a8[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -354,7 +387,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
 #pragma unroll
             for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) stg[(4 * fhalf + t) * SW + 32 * j + frow] = acc[i][j][4 * e4 + t];
+                for (int t = 0; t < 4; ++t) stg[(4 * ehalf + t) * SW + 32 * j + ecol] = acc[i][j][4 * e4 + t];
         };
 
         if (EPI == EPI_BIAS_RESIDUAL) {
@@ -362,9 +395,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
             // previous sums (kept as two bf16, hi + lo) and the row statistics, so the stream is never
             // rounded to 8 bits.  v goes out as hi + lo again: hi is what the next map reads.  A lane
             // handles 8 consecutive columns (16-byte accesses), 8 lanes a row of the strip.
-            constexpr int LPR = WTN / 8, RPI = 64 / LPR, NIT = 8 / RPI, NS = 4 * T::TM;
+            constexpr int LPR = WTN / 8, RPI = 64 / LPR, NIT = 8 / RPI, NS = 4 * TM;
             static_assert(LPR == 8 && NIT == 1, "8 lanes per 64-column row piece");
-            const int cg = lane % LPR, r_in = lane / LPR;
+            const int cg = el % LPR, r_in = el / LPR;
             const int col = n_base + 8 * cg;
             float bv[8], rg[8], rb[8];
 #pragma unroll
@@ -444,19 +477,19 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
         {
             // bf16 out (plain, GELU, or the query / key columns of the QKV projection): 8 columns per lane
             constexpr int LPR = WTN / 8, RPI = 64 / LPR, NIT = 8 / RPI;
-            const int cg = lane % LPR, r_in = lane / LPR;
+            const int cg = el % LPR, r_in = el / LPR;
             const int col = n_base + 8 * cg;
             const float4 b0 = *(const float4*)(bias + col), b1 = *(const float4*)(bias + col + 4);
             // maps with a LayerNorm folded in: column sums, and the statistics of every row this lane
             // will touch, requested before the first strip
             constexpr bool FOLD = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_BIAS_GELU;
             float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
-            float2 rst[FOLD ? T::TM * 4 * NIT : 1];
+            float2 rst[FOLD ? TM * 4 * NIT : 1];
             if (FOLD) {
                 c0 = *(const float4*)(res.colsum + col);
                 c1 = *(const float4*)(res.colsum + col + 4);
 #pragma unroll
-                for (int s = 0; s < T::TM * 4; ++s)
+                for (int s = 0; s < TM * 4; ++s)
 #pragma unroll
                     for (int it = 0; it < NIT; ++it) {
                         const int64_t row = m_base + 8 * s + r_in + RPI * it;
@@ -468,7 +501,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
             const int c_col = col + (EPI == EPI_KV ? hidden : 0);   // key columns sit after the query columns
             bf16_t* C = (bf16_t*)Cv;
 #pragma unroll
-            for (int i = 0; i < T::TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int e4 = 0; e4 < 4; ++e4) {
                     stage_strip(i, e4);
@@ -513,25 +546,55 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(
     }
     // parked DMAs may still be in flight: they must land before the workgroup gives up its LDS
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Rows in two regions: plan->m_tiles tiles of BM rows, then the others in tiles of 32 (tm0 + tm1) rows, as prep chose them
+// (PLANNED); without a plan all in tiles of BM rows.
+template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
+                                                                 const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk) {
+    using T = Tile<BM, BN, WM, WN>;
+    __shared__ __align__(1024) unsigned char smem[T::LDS];
+    // clock probe (profiling only): core cycles and constant-rate ticks over this workgroup's life
+    const int64_t clk_c0 = clk ? (int64_t)clock64() : 0, clk_w0 = clk ? (int64_t)wall_clock64() : 0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Region rg;
+    rg.rows = *total_rows;
+    if constexpr (!PLANNED) {
+        rg.row_begin = 0; rg.bm = BM; rg.tm0 = T::TM;
+        rg.m_tiles = (rg.rows + BM - 1) / BM;
+        region_tiles<T, WN, T::TM, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+    } else {
+        static_assert(T::TM == 4, "regions of 2 to 4 blocks a wavefront");
+        const GemmPlan pl = *plan;
+        for (int r = pl.m_tiles > 0 ? 0 : 1; r < 2; ++r) {
+            const int tm0 = r == 0 ? T::TM : pl.tm0, tm1 = r == 0 ? T::TM : pl.tm1;
+            rg.row_begin = r == 0 ? 0 : pl.m_tiles * BM;
+            rg.bm = 32 * (tm0 + tm1); rg.tm0 = tm0;
+            rg.m_tiles = r == 0 ? pl.m_tiles : (rg.rows - rg.row_begin + rg.bm - 1) / rg.bm;
+            if (rg.m_tiles <= 0) break;
+            if (r == 1 && pl.m_tiles > 0) dma_barrier();     // every wavefront's parked DMAs have landed
+            const int tm = wave / WN == 0 ? tm0 : tm1;       // both paths meet the same barriers
+            if (tm == 4) region_tiles<T, WN, 4, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else if (tm == 3) region_tiles<T, WN, 3, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else region_tiles<T, WN, 2, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+        }
+    }
     if (clk && blockIdx.x == 0 && threadIdx.x == 0) {
         clk[0] = (int64_t)clock64() - clk_c0;
         clk[1] = (int64_t)wall_clock64() - clk_w0;
     }
 }
 
-template <int BM, int BN, int WM, int WN>
-void launch_cfg(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias, ResidualSrc residual,
-                void* C, bf16_t* vt, int64_t max_rows, int N, int K, int hidden, const int32_t* total_rows,
-                int64_t* clk, hipStream_t s) {
-    // persistent: one workgroup per compute unit (fewer if there cannot be that many tiles); the small tiles
-    // leave room for two workgroups per unit (LDS and registers), which then hide each other's waits
-    const int64_t tiles = (max_rows + BM - 1) / BM * (N / BN);
-    const int64_t most = BM * BN <= 128 * 128 ? 512 : 256;
-    const int64_t wgs = tiles < most ? (tiles + 7) / 8 * 8 : most;
+template <int BM, int BN, int WM, int WN, bool PLANNED>
+void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk,
+                hipStream_t s) {
+    // persistent: one workgroup per compute unit; the small tiles leave room for two (LDS and registers), which then hide
+    // each other's waits, and take fewer workgroups if there cannot be that many tiles
+    const int64_t tiles = (g.max_rows + BM - 1) / BM * (g.N / BN);
+    const int64_t wgs = PLANNED ? 256 : tiles < 512 ? (tiles + 7) / 8 * 8 : 512;
     const dim3 grid((unsigned)wgs), block(WM * WN * 64);
-#define PS_LAUNCH(E)                                                                                       \
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E>), grid, block, 0, s, A, W, bias, residual, C, vt, \
-                       max_rows, N, K, hidden, total_rows, clk)
+#define PS_LAUNCH(E) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED>), grid, block, 0, s, g, total_rows, plan, clk)
     switch (epi) {
         case EPI_BIAS: PS_LAUNCH(EPI_BIAS); break;
         case EPI_BIAS_GELU: PS_LAUNCH(EPI_BIAS_GELU); break;
@@ -539,7 +602,7 @@ void launch_cfg(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float*
         case EPI_QKV: PS_LAUNCH(EPI_QKV); break;
         case EPI_KV: PS_LAUNCH(EPI_KV); break;
         case EPI_GELU_SPLIT:
-            if constexpr (BM * BN <= 128 * 128) PS_LAUNCH(EPI_GELU_SPLIT);
+            if constexpr (!PLANNED) PS_LAUNCH(EPI_GELU_SPLIT);
             break;
         default: break;                                  // the mapped forms are small_gemm.hip's and skinny_gemm.hip's
     }
@@ -552,13 +615,14 @@ void launch_cfg(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float*
 // max_rows rows with max_rows % 256 == 0, so whole tiles are always in bounds.
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc residual, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
-                      int hidden, const int32_t* total_rows, int64_t* clk, hipStream_t s) {
+                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s) {
     // Problems with few 256 x 256 tiles (whole calls on a micro-batch of a few requests) would leave most compute
     // units idle: 128 x 128 tiles give four times as many workgroups to spread them over.  EPI_GELU_SPLIT has only these
     // (its second set of accumulators): 4096 requests of hidden 768 in 57 us, 20000 in 234.
     const int64_t big_tiles = (max_rows + 255) / 256 * (N / 256);
+    const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden};
     if (epi == EPI_GELU_SPLIT || big_tiles < 128)
-        launch_cfg<128, 128, 2, 2>(epi, A, W, bias, residual, C, vt, max_rows, N, K, hidden, total_rows, clk, s);
+        launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, s);
     else
-        launch_cfg<256, 256, 2, 4>(epi, A, W, bias, residual, C, vt, max_rows, N, K, hidden, total_rows, clk, s);
+        launch_cfg<256, 256, 2, 4, true>(epi, g, total_rows, plan, clk, s);
 }

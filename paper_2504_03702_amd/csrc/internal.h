@@ -59,12 +59,19 @@ struct ps_model {
     float b_h2;
 };
 
+// How a map's rows are cut into tiles (gemm_bf16.hip): m_tiles tiles of 256 rows, then tiles of 32 (tm0 + tm1) rows.
+struct GemmPlan {
+    int32_t m_tiles, tm0, tm1;
+};
+enum { PS_PLAN_QKV = 0, PS_PLAN_KV = 1, PS_PLAN_H = 2, PS_PLAN_F = 3, PS_PLANS = 4 };
+
 // Per-call bookkeeping the prep kernel writes at the start of the workspace.
 struct BatchMeta {
     int32_t total_rows;          // activation rows in use (padded request starts included)
     int32_t total_qtiles;        // attention query tiles over all requests
     int32_t n_req;               // requests in this call (row count of the per-request side GEMMs)
     int32_t qkv_rows;            // total_rows + PS_KEY_SLACK: rows the QKV projection covers
+    GemmPlan plan[PS_PLANS];     // tiles of the maps of all rows
 };
 
 // Carved-up workspace of one ps_predict_load call.
@@ -134,7 +141,7 @@ struct ResidualSrc {
 // may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc res, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
-                      int hidden, const int32_t* total_rows, int64_t* clk, hipStream_t s);
+                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s);
 // The per-request forms (EPI_GELU_SPLIT, EPI_RESIDUAL_MAPPED, EPI_Q_MAPPED) for calls of at most PS_SKINNY_ROWS
 // requests: a stream over W with the contraction split among a workgroup's wavefronts.
 #define PS_SKINNY_ROWS 16

@@ -5,6 +5,34 @@
 
 namespace {
 
+// How a map of `rows` rows and n tile columns is cut into tiles for 256 workgroups (the whole wavefront calls, every lane
+// weighs one candidate): all rows in tiles of one height, or as many whole rounds of 256-row tiles as there are (or one
+// fewer) and the rest in tiles of one height.  Costs in thousandths of a full round of 256-row tiles.  A full round of
+// lower tiles costs more than its share of rows (measured on 250 k and 440 k rows, the four maps of hidden 768 and 1024:
+// 224 rows 1.00-1.02 per row, 192 1.03-1.08, 160 1.06-1.13, 128 1.11-1.26); a round that leaves units idle runs
+// faster, the chip's power being shared by fewer, down to 0.68 of a full one (153 tiles of 256 rows, contraction 3072:
+// 70 us against 103).
+__device__ GemmPlan plan_gemm(int rows, int n) {
+    const int lane = threadIdx.x & 63;
+    const int heights[5] = {8, 7, 6, 5, 4}, costs[5] = {1000, 888, 780, 690, 600};   // heights in blocks of 32 rows
+    const int tiles = (rows + 255) / 256 * n, pick = min(lane / 5, 2);
+    int h = 8, c = 1000;
+#pragma unroll
+    for (int i = 1; i < 5; ++i)
+        if (lane % 5 == i) { h = heights[i]; c = costs[i]; }
+    const int rounds = max(pick == 0 ? 0 : tiles / 256 - (pick - 1), 0), m = rounds * 256 / n;
+    const int left = max(rows - 256 * m, 0), rest = (left + 32 * h - 1) / (32 * h) * n;
+    int64_t cost = (int64_t)rounds * 1000 + (int64_t)(rest / 256) * c + (rounds > 0 ? 50 : 0);
+    if (rest % 256) cost += (int64_t)c * max(680, (rest % 256) * 1000 / 256) / 1000;
+    int64_t best = lane < 15 ? cost * 64 + lane : INT64_MAX;
+    for (int o = 8; o > 0; o >>= 1) {
+        const int64_t other = __shfl_xor(best, o, 16);
+        best = other < best ? other : best;
+    }
+    const int at = (int)(__shfl(best, 0, 64) & 63);
+    return GemmPlan{__shfl(m, at, 64), (__shfl(h, at, 64) + 1) / 2, __shfl(h, at, 64) / 2};
+}
+
 // ------------------------------------------------------------------------------------------
 // prep: one workgroup turns (offsets, lengths) into the packed row layout of this call.
 // Request r occupies activation rows [row_start[r], row_start[r] + seq_len[r]); row_start is a
@@ -16,7 +44,7 @@ namespace {
 __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ offsets,
                                                     const int32_t* __restrict__ lengths, int n_req,
                                                     int n_soft, int max_pos, long long n_tokens,
-                                                    long long row_capacity, BatchMeta* meta,
+                                                    long long row_capacity, int4 plan_cols, BatchMeta* meta,
                                                     int32_t* seq_len, int32_t* row_start,
                                                     int32_t* qtile_start, int32_t* bad_req,
                                                     int32_t* head_done, ps_status* st) {
@@ -98,6 +126,12 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
         meta->total_qtiles = (int32_t)cut_tiles;
         meta->n_req = n_req;
         meta->qkv_rows = (int32_t)cut_rows + PS_KEY_SLACK;
+    }
+    const int plan = tid >> 6;                       // a wavefront each; tile columns of the maps, none for fp32 models
+    if (plan < PS_PLANS && plan_cols.x > 0) {
+        const int n = plan == PS_PLAN_QKV ? plan_cols.x : plan == PS_PLAN_KV ? plan_cols.y : plan == PS_PLAN_H ? plan_cols.z : plan_cols.w;
+        const GemmPlan p = plan_gemm((int)cut_rows + (plan == PS_PLAN_QKV || plan == PS_PLAN_KV ? PS_KEY_SLACK : 0), n);
+        if ((tid & 63) == 0) meta->plan[plan] = p;
     }
 }
 
@@ -412,8 +446,10 @@ void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, cons
 
 void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengths, int32_t n_req, int64_t n_tokens,
                  const Workspace& ws, ps_status* st, hipStream_t s) {
-    hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft,
-                       m->info.max_pos, (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), ws.meta, ws.seq_len,
+    const int h = m->info.hidden / 256, f = m->info.ffn / 256;
+    const int4 plan_cols = m->info.dtype == 1 ? make_int4(3 * h, 2 * h, h, f) : make_int4(0, 0, 0, 0);
+    hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft, m->info.max_pos,
+                       (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), plan_cols, ws.meta, ws.seq_len,
                        ws.row_start, ws.qtile_start, ws.bad_req, ws.head_done, st);
 }
 

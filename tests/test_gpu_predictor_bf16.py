@@ -267,3 +267,21 @@ def test_production_stratified_sample_against_oracle(production):
     picks = np.unique(np.concatenate([rest, [0, p["batch"].n_req - 1, int(np.argmax(lengths))]]))
     picks = picks[lengths[picks] > 48]
     check_against_pool("stratified", p["path"], p["batch"], p["got_f"], p["got_t"], picks, p["model"].info.d_max)
+
+
+@pytest.mark.parametrize("rows", [2700, 5600, 6600, 9200, 12500, 16500, 19650, 24250, 28900, 34600, 50900])
+def test_tile_heights(tmp_models, rows):
+    """Row counts at which the maps of all rows take tiles of 256, 224, 192, 160 and 128 rows, alone and behind whole rounds
+    of 256-row tiles (12 tile columns in the first feed-forward map, 3 and 1 in the others), with last tiles that reach
+    past the buffers: the bits are those of the same requests in calls of 20."""
+    print(f"predict tile heights rows={rows}", flush=True)
+    cfg = dataclasses.replace(SMALL, ffn=3072)
+    model, _ = make(tmp_models, "tile_heights.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(rows)
+    n = 40 if rows < 20000 else 120
+    lengths = (rows // n // 8 * 8 + rng.integers(-4, 5, n // 2) * 8).astype(np.int32)
+    lengths = np.concatenate([lengths, 2 * (rows // n) - lengths]).astype(np.int32)
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got, tokens, flags, _ = run_predict(model, batch)
+    assert flags == 0 and np.isfinite(got).all()
+    chunks_bit_equal(model, batch, got, tokens, chunk=20)
