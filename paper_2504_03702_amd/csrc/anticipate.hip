@@ -24,9 +24,10 @@
 // keeps a window of buckets for ALL instances in LDS (256 x 152 counters) instead of all buckets for a
 // quarter of them.  Every record then belongs to the one workgroup that reads it: no second, third
 // and fourth inspection by other groups, no compaction queue.  A workgroup that meets a record
-// outside its window says so in place of its result; that makes the general kernel run after it
+// outside its window says so in place of its result; that makes a kernel for any order run after it
 // (otherwise its workgroups leave at once) and tells the reduction which partial results to use, so
-// the outcome is the same for any order.
+// the outcome is the same for any order.  That kernel is the general one or, for long streams of many rows, one with
+// 16-bit counters (anticipate_halves_kernel).
 #include <string.h>
 
 #include <mutex>
@@ -46,6 +47,10 @@ const int64_t kMinSlice = 16384;         // records per slice below which more s
 const int kTargetWorkgroups = 256;       // one scatter workgroup per compute unit
 
 const int64_t kWindowMinRecords = 262144;   // shorter streams do not pay for the extra launches
+// Looks at records (records x groups) that the halves kernel must save to pay for its prefix sums.  Microseconds a call, general / halves: 256 instances of 600 buckets (4 groups / 2) 0.26 M records 26.2 / 29.6,
+// 1 M 35.5 / 36.1, 2 M 38.1 / 38.3, 5 M 51.4 / 47.4, 15 M 90 / 72, 44 M 215 / 157; 100 of 600 (2 / 1) 1 M 32.3 / 34.0, 2 M
+// 37.9 / 36.4, 44 M 156 / 139; 200 of 1100 (6 / 3) 0.3 M 30.8 / 32.8, 1 M 46.4 / 38.8; 200 of 1200 20 M 272 / 107.
+const int64_t kHalvesMinSaved = 3000000;
 const int kWindowMaxHorizon = 4096;         // the reduction keeps one 64-bit row of the map in LDS
 const int kGaveUp = -2;                     // a windowed workgroup's origin when a record fell outside its window
 
@@ -57,6 +62,10 @@ struct AntPlan {
     int w_slices, w_buckets;
     int64_t w_slice_len;
     size_t w_lds_bytes, w_partial_bytes, w_ovf_bytes, w_origin_bytes, w_partial_at, w_ovf_at, w_origin_at;
+    // halves kernel (records in any order, twice as many rows a workgroup); h_slices == 0: not used
+    int h_rows, h_groups, h_slices, h_stride;
+    int64_t h_slice_len;
+    size_t h_lds_bytes, h_high_at, h_ovf_at, h_flag_at;
     bool ok;
 };
 
@@ -108,6 +117,34 @@ void plan_window(AntPlan& p, int64_t n, int n_inst, int horizon, bool with_rate)
     p.w_ovf_at = p.w_partial_at + p.w_partial_bytes;
     p.w_origin_at = p.w_ovf_at + p.w_ovf_bytes;
     p.total_bytes = p.w_origin_at + p.w_origin_bytes;
+}
+
+// Lays the halves kernel's results over the general and the windowed buffers (they are needed only where the windowed
+// kernel gave up), as many slices as fit; not used where a workgroup would not hold more rows than the general one's.
+void plan_halves(AntPlan& p, int64_t n, int n_inst, int horizon) {
+    p.h_slices = 0;
+    if (p.w_slices == 0) return;
+    const int64_t per_pair = 4 * (int64_t)horizon + 2 * (8 + 4);  // counters, overflow and 1/rate of two rows
+    int64_t fit = (kLdsBytes - kQueueBytes - 64) / per_pair * 2;
+    if (fit > 256) fit = 256;                                     // a queued record names its row in 8 bits
+    p.h_groups = fit > 0 ? (int)((n_inst + fit - 1) / fit) : p.groups;
+    if (p.h_groups >= p.groups || n * (p.groups - p.h_groups) < kHalvesMinSaved) return;
+    p.h_rows = ((n_inst + p.h_groups - 1) / p.h_groups + 1) / 2 * 2;
+    p.h_stride = (horizon + 7) / 8 * 8;
+    const int64_t slice_bytes = (int64_t)n_inst * (4 * (int64_t)p.h_stride + 8) + 4 * (int64_t)p.h_groups;
+    int64_t s = (n + kMinSlice / 2 - 1) / (kMinSlice / 2);
+    const int64_t cap = kTargetWorkgroups / p.h_groups, room = ((int64_t)p.w_origin_at - 1024) / slice_bytes;
+    s = s < cap ? s : cap;
+    s = s < room ? s : room;
+    if (s < 1) return;
+    // (beyond some hundred records a cell, of some hundred tokens each, loads would leave 16 bits as a rule)
+    if (n / s > 128 * (int64_t)n_inst * horizon) return;
+    p.h_slices = (int)s;
+    p.h_slice_len = ((n + s - 1) / s + 3) / 4 * 4;
+    p.h_lds_bytes = (size_t)(p.h_rows / 2 * per_pair + kQueueBytes + 64);
+    p.h_high_at = align_up((size_t)s * n_inst * p.h_stride * 2, 256);
+    p.h_ovf_at = 2 * p.h_high_at;
+    p.h_flag_at = align_up(p.h_ovf_at + (size_t)s * n_inst * 8, 256);
 }
 
 // Exact integer division by float reciprocals.  All numerators here are below 2^20
@@ -315,6 +352,240 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(
     for (int i = tid; i < rows; i += kScatterThreads) partial_ovf[(int64_t)slice * n_inst + k0 + i] = (int64_t)s_ovf[i];
 }
 
+// Scatter for long streams in any order: 16-bit counters, two rows to a word, so that a workgroup holds twice the rows
+// and a record is looked at by half as many workgroups.  The general kernel is bound by instruction issue, most of it
+// looking at records of other groups (118 wavefront instructions per 64 records over four groups of 64 rows).
+//
+// Word [w][b] holds the difference of row w in its low half and of row w + R in its high half: adding signed amounts,
+// shifted for the high half, keeps word = low + 2^16 high modulo 2^32, and the same holds for the prefix sums over b, whose
+// halves are the two rows' loads.  Loads are never negative, so if both are below 2^16 the halves are exactly they; a load
+// that is not makes the halves add up to less than the true loads (65535 less for every wrap of the low half, which
+// carries into the high one, 65536 for the high half).  Compared over the whole workgroup, what the halves add up to is
+// therefore equal to the tokens put in exactly if no load has wrapped.  Where one has, the workgroup goes through its slice
+// twice more, half of its rows at a time with 32-bit counters, and leaves the loads' upper halves in a second plane.
+// Results are loads, not differences: the reduction adds them up and needs no scan.
+//
+// 44.1 M records over 256 instances of 600 buckets: 200 us in the general kernel, 146 here, of which about 105 are vector
+// instructions (19 a look, 48 a record); a queue entry names row, bucket and tokens in fields, so neither side multiplies
+// or divides by the row length.
+struct HalvesArgs {
+    const int32_t *pred, *inst, *arrival, *rate;
+    int64_t n, slice_len;
+    int n_inst, horizon, rows, groups, slices, stride;
+    uint16_t *low, *high;                // [instance][slice][stride]: the reduction of an instance reads one block
+    int64_t* ovf;                        // [slice][instance]
+    int32_t* wide;                       // [slice][group]: the upper halves are there too
+};
+
+template <bool WIDE>
+__device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int rows, unsigned char* lds_raw, bool report,
+                            unsigned long long* s_sum, ps_status* st) {
+    const int horizon = p.horizon, R = p.rows / 2;
+    uint32_t* s_queue = (uint32_t*)lds_raw;                                    // [kWaves][kQueue]
+    int* s_flag = (int*)(lds_raw + kQueueBytes);                               // some row has rate < 1
+    unsigned long long* s_ovf = (unsigned long long*)(lds_raw + kQueueBytes + 64);  // [p.rows]
+    float* s_rcp = (float*)(s_ovf + p.rows);                                   // biased 1 / rate; 0: no usable rate
+    int* s_word = (int*)(s_rcp + p.rows);                                      // [R][horizon]
+    // (the wavefront index is uniform: what is derived from it stays in scalar registers)
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __syncthreads();
+    if (tid == 0) *s_flag = 0;
+    __syncthreads();
+    for (int i = tid; i < R * horizon; i += kScatterThreads) s_word[i] = 0;
+    for (int i = tid; i < rows; i += kScatterThreads) {
+        s_ovf[i] = 0;
+        const int r = min(p.rate[k0 + i], PS_MAX_PRED);
+        if (r < 1) *s_flag = 1;
+        s_rcp[i] = r > 0 ? (1.0f / (float)r) * (1.0f + 0x1p-21f) : 0.f;
+    }
+    __syncthreads();
+    const bool bad_rate_rows = *s_flag != 0;                  // uniform; rare
+
+    uint32_t* q = s_queue + wave * kQueue;
+    unsigned head = 0, tail = 0;                                // wave-uniform ring indices
+    unsigned long long inside_sum = 0;                          // tokens this lane has put into buckets
+    unsigned long long mass = 0;                                // WIDE: bound on what any counter can have reached
+
+    // one record of row `row`: D1 = its tokens less one
+    auto apply = [&](unsigned row, unsigned a, unsigned D1) {
+        const bool upper = !WIDE && row >= (unsigned)R;
+        const unsigned D = D1 + 1u, w = WIDE ? row : min(row, row - (unsigned)R), sh = upper ? 16u : 0u;
+        const unsigned dur = div_by_row(D1, s_rcp[row]) + 1u;                   // ceil(D / rate)
+        const unsigned qq = div_exact(D, dur);
+        const unsigned rem = D - __umul24(qq, dur);
+        const unsigned room = (unsigned)horizon - a;            // buckets from a to the end of the row
+        int* cell = s_word + __umul24(w, (unsigned)horizon) + a;
+        atomicAdd(cell, (int)((qq + (rem != 0)) << sh));        // rem == 0: the +1 and the -1 fall on the same cell
+        if (rem != 0 && rem < room) atomicAdd(cell + rem, (int)(0xffffffffu << sh));
+        if (dur < room) atomicAdd(cell + dur, (int)(0u - (qq << sh)));
+        inside_sum += D;
+        if (WIDE) mass += qq + 1;
+        if (dur > room) {
+            const unsigned long long over = (unsigned long long)D - ((unsigned long long)room * qq + min(room, rem));
+            atomicAdd(&s_ovf[row], over);
+            inside_sum -= over;
+        }
+    };
+    // up to 64 queued records, lane i entry head + i: row (8 bits) | arrival bucket (12 bits) | prediction less one (12 bits)
+    auto consume = [&](unsigned count) {
+        if ((unsigned)lane < count) {
+            const uint32_t e = q[(head + lane) & (kQueue - 1)];
+            apply(e >> 24, (e >> 12) & 0xfffu, e & 0xfffu);
+        }
+    };
+
+    const int64_t begin = (int64_t)slice * p.slice_len, end = min(begin + p.slice_len, p.n);
+    // four consecutive records per lane, 256 per wavefront and block, loads two blocks ahead (plain loads: the groups
+    // of a slice share it through their XCD's L2)
+    struct Block { int k[4], d[4], a[4]; };
+    const int64_t n_full = max(end - begin, (int64_t)0) / 256;
+    const int64_t last_full = begin + (n_full - 1) * 256;
+    auto load_full = [&](int64_t blk) {
+        Block b;
+        const int64_t at = min(blk, last_full);                // uniform: scalar addresses
+        const int4 kv = ((const int4*)(p.inst + at))[lane];
+        const int4 dv = ((const int4*)(p.pred + at))[lane];
+        const int4 av = ((const int4*)(p.arrival + at))[lane];
+        b.k[0] = kv.x; b.k[1] = kv.y; b.k[2] = kv.z; b.k[3] = kv.w;
+        b.d[0] = dv.x; b.d[1] = dv.y; b.d[2] = dv.z; b.d[3] = dv.w;
+        b.a[0] = av.x; b.a[1] = av.y; b.a[2] = av.z; b.a[3] = av.w;
+        return b;
+    };
+    auto process = [&](const Block& b, int64_t blk, bool ragged) {
+        const int64_t idx = blk + lane * 4;
+        // validity of all four records at once; a block with a faulty record, one of more tokens than the queue takes, or
+        // the ragged tail is taken record by record, past the queue
+        const unsigned dmax = max(max((unsigned)b.d[0], (unsigned)b.d[1]), max((unsigned)b.d[2], (unsigned)b.d[3]));
+        const unsigned amax = max(max((unsigned)b.a[0], (unsigned)b.a[1]), max((unsigned)b.a[2], (unsigned)b.a[3]));
+        const unsigned kmax = max(max((unsigned)b.k[0], (unsigned)b.k[1]), max((unsigned)b.k[2], (unsigned)b.k[3]));
+        const bool suspect = ragged || dmax > 4096u || amax >= (unsigned)horizon || kmax >= (unsigned)p.n_inst;
+        if (__any(suspect) || bad_rate_rows) {                 // uniform
+#pragma unroll 1
+            for (int c = 0; c < 4; ++c) {
+                const int kc = c == 0 ? b.k[0] : c == 1 ? b.k[1] : c == 2 ? b.k[2] : b.k[3];
+                const int dc = c == 0 ? b.d[0] : c == 1 ? b.d[1] : c == 2 ? b.d[2] : b.d[3];
+                const int ac = c == 0 ? b.a[0] : c == 1 ? b.a[1] : c == 2 ? b.a[2] : b.a[3];
+                const unsigned kk = (unsigned)(kc - k0);
+                const bool in = idx + c < end, k_ok = (unsigned)kc < (unsigned)p.n_inst, mine = k_ok && kk < (unsigned)rows;
+                bool ok = (unsigned)dc <= (unsigned)PS_MAX_PRED && (unsigned)ac < (unsigned)horizon;
+                if (mine && ok && s_rcp[kk] == 0.f) ok = false;
+                // a record outside every group is reported by group 0, others by their own group
+                if (report && in && ((!k_ok && g == 0) || (mine && !ok))) report_fault(st, PS_ST_BAD_RECORD, idx + c);
+                if (in && mine && ok && dc != 0) apply(kk, (unsigned)ac, (unsigned)dc - 1u);
+            }
+            return;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const unsigned kk = (unsigned)(b.k[c] - k0), d1 = (unsigned)b.d[c] - 1u;
+            const bool m = (kk | (d1 & 0x80000000u)) < (unsigned)rows;          // (no tokens: d1 wraps)
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(m);
+            const unsigned pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, tail));
+            if (m) q[pos & (kQueue - 1)] = (kk << 24) | ((unsigned)b.a[c] << 12) | d1;
+            tail += (unsigned)__popcll(mask);
+            if (tail - head >= 64u) {
+                consume(64u);
+                head += 64u;
+            }
+        }
+    };
+    const int64_t stride = (int64_t)kWaves * 256;
+    const int64_t blk0 = begin + (int64_t)wave * 256;
+    const int64_t full_end = begin + n_full * 256;
+    if (blk0 < full_end) {
+        Block b0 = load_full(blk0);
+        Block b1 = load_full(blk0 + stride);
+        Block b2 = load_full(blk0 + 2 * stride);
+        for (int64_t blk = blk0;;) {
+            process(b0, blk, false);
+            b0 = load_full(blk + 3 * stride);
+            if ((blk += stride) >= full_end) break;
+            process(b1, blk, false);
+            b1 = load_full(blk + 3 * stride);
+            if ((blk += stride) >= full_end) break;
+            process(b2, blk, false);
+            b2 = load_full(blk + 3 * stride);
+            if ((blk += stride) >= full_end) break;
+        }
+    }
+    if (full_end < end && wave == (int)(n_full % kWaves)) {
+        Block b;
+        const int64_t idx = full_end + lane * 4;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool in = idx + c < end;
+            b.k[c] = in ? p.inst[idx + c] : -1;                // -1 matches no row
+            b.d[c] = in ? p.pred[idx + c] : 0;
+            b.a[c] = in ? p.arrival[idx + c] : 0;
+        }
+        process(b, full_end, true);
+    }
+    if (tail != head) consume(tail - head);
+    if (WIDE) {
+        for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
+        if (lane == 0 && mass >= (1ull << 31) / kWaves) report_fault(st, PS_ST_RANGE, begin);
+    }
+    __syncthreads();
+
+    // prefix sums, a wavefront per row of words, two words a lane; the loads of both rows go out as they are
+    unsigned long long halves_sum = 0;
+    for (int w = wave; w < (WIDE ? rows : min(R, rows)); w += kWaves) {
+        const int64_t at = ((int64_t)(k0 + w) * p.slices + slice) * p.stride;
+        const bool two = !WIDE && w + R < rows;
+        unsigned carry = 0;
+        for (int b0 = 0; b0 < horizon; b0 += 128) {
+            const int b = b0 + 2 * lane;
+            const unsigned x = b < horizon ? (unsigned)s_word[w * horizon + b] : 0u;
+            const unsigned y = b + 1 < horizon ? (unsigned)s_word[w * horizon + b + 1] : 0u;
+            unsigned incl = x + y;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned t = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += t;
+            }
+            const unsigned s1 = carry + incl, s0 = s1 - y;     // loads of buckets b and b + 1
+            if (b < p.stride) {                                 // (stride is even; cells beyond the horizon are not read)
+                *(uint32_t*)(p.low + at + b) = (s0 & 0xffffu) | (s1 << 16);
+                if (WIDE) *(uint32_t*)(p.high + at + b) = (s0 >> 16) | (s1 & 0xffff0000u);
+                else if (two) *(uint32_t*)(p.low + at + (int64_t)R * p.slices * p.stride + b) = (s0 >> 16) | (s1 & 0xffff0000u);
+            }
+            if (!WIDE) {
+                if (b < horizon) halves_sum += (s0 & 0xffffu) + (s0 >> 16);
+                if (b + 1 < horizon) halves_sum += (s1 & 0xffffu) + (s1 >> 16);
+            }
+            carry += __shfl(incl, 63, 64);
+        }
+    }
+    for (int i = tid; i < rows; i += kScatterThreads) p.ovf[(int64_t)slice * p.n_inst + k0 + i] = (int64_t)s_ovf[i];
+    if (!WIDE) {
+        unsigned long long diff = inside_sum - halves_sum;
+        for (int o = 32; o > 0; o >>= 1) diff += __shfl_xor(diff, o, 64);
+        if (lane == 0) atomicAdd(s_sum, diff);
+    }
+}
+
+__global__ __launch_bounds__(kScatterThreads) void anticipate_halves_kernel(HalvesArgs p, const int32_t* __restrict__ worigin,
+                                                                            int w_slices, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    unsigned long long* s_sum = (unsigned long long*)(lds_raw + kQueueBytes + 8);   // tokens put in less what the halves show
+    if (!window_gave_up(worigin, w_slices)) return;            // launched behind the windowed kernel
+    // blocks are dealt to the 8 XCDs round-robin: keep the groups of one slice on one XCD
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int g = j % p.groups, slice = (j / p.groups) * 8 + xcd;
+    if (slice >= p.slices) return;
+    const int k0 = g * p.rows, rows = min(p.rows, p.n_inst - k0);
+    if (rows <= 0) return;
+    if (threadIdx.x == 0) *s_sum = 0;
+    halves_pass<false>(p, slice, g, k0, rows, lds_raw, true, s_sum, st);
+    __syncthreads();
+    const bool wrapped = *s_sum != 0;                          // uniform
+    if (threadIdx.x == 0) p.wide[slice * p.groups + g] = wrapped;
+    if (!wrapped) return;
+    const int R = p.rows / 2;
+    halves_pass<true>(p, slice, g, k0, min(R, rows), lds_raw, false, nullptr, st);
+    if (rows > R) halves_pass<true>(p, slice, g, k0 + R, rows - R, lds_raw, false, nullptr, st);
+}
+
 // Windowed scatter for records in arrival order: workgroup = slice of the records; LDS holds, for
 // every instance, the difference counters of the buckets [a0, a0 + w_buckets), a0 = the arrival bucket
 // of the slice's first record.  Each lane takes its own records straight through the two divisions and
@@ -516,7 +787,7 @@ const int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
     const int32_t* __restrict__ partial, const int64_t* __restrict__ partial_ovf, int slices, int n_inst, int horizon,
     const int32_t* __restrict__ wpartial, const int64_t* __restrict__ wovf, const int32_t* __restrict__ worigin,
-    int w_slices, int w_buckets, int32_t* __restrict__ load, int64_t* __restrict__ overflow, ps_status* st) {
+    int w_slices, int w_buckets, HalvesArgs hv, int32_t* __restrict__ load, int64_t* __restrict__ overflow, ps_status* st) {
     __shared__ long long s_wave[4];
     __shared__ unsigned long long s_over;
     __shared__ int s_origin[kTargetWorkgroups];              // first bucket of every slice's row
@@ -526,6 +797,59 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
     const bool windowed = worigin && !window_gave_up(worigin, w_slices);
     const bool in_lds = horizon <= kWindowMaxHorizon;         // (the windowed kernel is only used then)
     if (tid == 0) s_over = 0;                                 // (a barrier follows before its first use)
+    if (worigin && !windowed && hv.slices > 0) {
+        // the halves kernel's loads: a thread adds up eight neighbouring buckets of every T-th slice
+        for (int i = tid; i < horizon; i += kReduceThreads) s_row[i] = 0;
+        const int wg = k / hv.rows;
+        bool some = false;
+        for (int i = tid; i < hv.slices; i += kReduceThreads) some |= hv.wide[i * hv.groups + wg] != 0;
+        const bool wide = __syncthreads_or(some) != 0;        // rare
+        const int groups = hv.stride >> 3, T = kReduceThreads / groups;       // (at most 512 groups)
+        const int sl0 = tid / groups, g8 = tid - sl0 * groups;
+        const int64_t step = hv.stride, at0 = (int64_t)k * hv.slices * hv.stride + 8 * g8;
+        if (sl0 < T) {
+            unsigned sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};       // at most 256 slices of 16 bits
+            constexpr int NB = 10;
+            for (int s0 = sl0; s0 < hv.slices; s0 += T * NB) {
+                uint4 v[NB];
+#pragma unroll
+                for (int u = 0; u < NB; ++u) v[u] = *(const uint4*)(hv.low + min(s0 + T * u, hv.slices - 1) * step + at0);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int sl = s0 + T * u;
+                    if (sl >= hv.slices) continue;
+                    const unsigned x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) { sum[2 * c] += x[c] & 0xffffu; sum[2 * c + 1] += x[c] >> 16; }
+                    if (wide && hv.wide[sl * hv.groups + wg]) {
+                        for (int c = 0; c < 8 && 8 * g8 + c < horizon; ++c) {
+                            const unsigned long long hi = hv.high[sl * step + at0 + c];
+                            if (hi) atomicAdd(&s_row[8 * g8 + c], hi << 16);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (8 * g8 + c < horizon && sum[c]) atomicAdd(&s_row[8 * g8 + c], (unsigned long long)sum[c]);
+        }
+        __syncthreads();
+        for (int b = tid; b < horizon; b += kReduceThreads) {
+            int32_t* cell = load + (int64_t)k * horizon + b;
+            const long long nv = (long long)*cell + (long long)s_row[b];
+            if (nv > 2147483647ll || nv < -2147483648ll) report_fault(st, PS_ST_RANGE, -1);
+            *cell = (int32_t)(uint32_t)(unsigned long long)nv;
+        }
+        if (overflow) {
+            for (int s2 = tid; s2 < hv.slices; s2 += kReduceThreads) {
+                const long long o = hv.ovf[(int64_t)s2 * n_inst + k];
+                if (o) atomicAdd(&s_over, (unsigned long long)o);
+            }
+            __syncthreads();
+            if (tid == 0 && s_over) overflow[k] += (long long)s_over;
+        }
+        return;
+    }
     if (in_lds) {
         const int n_rows = windowed ? w_slices : slices, row_len = windowed ? w_buckets : horizon;
         for (int s = tid; s < n_rows; s += kReduceThreads) s_origin[s] = windowed ? worigin[s] : 0;
@@ -795,6 +1119,8 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
     if (!lds_attr_set) {
         if (hipFuncSetAttribute((const void*)anticipate_scatter_kernel,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)anticipate_halves_kernel,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void*)anticipate_window_kernel,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
             return PS_EHIP;
@@ -814,12 +1140,22 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
                            pred_tokens, instance_id, arrival_bucket, rate, n_req, n_inst, horizon, p.w_buckets,
                            p.w_slice_len, wpartial, wovf, worigin, status);
     }
-    const unsigned blocks = 8u * (unsigned)p.groups * (unsigned)((p.slices + 7) / 8);
-    hipLaunchKernelGGL(anticipate_scatter_kernel, dim3(blocks), dim3(kScatterThreads), p.lds_bytes, s,
-                       pred_tokens, instance_id, arrival_bucket, rate, n_req, n_inst, horizon,
-                       p.rows_per_group, p.groups, p.slices, p.slice_len, partial, partial_ovf, worigin, p.w_slices, status);
+    plan_halves(p, n_req, n_inst, horizon);
+    HalvesArgs hv = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.h_slice_len, n_inst, horizon, p.h_rows, p.h_groups,
+                     p.h_slices, p.h_stride, (uint16_t*)wsb, (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at),
+                     (int32_t*)(wsb + p.h_flag_at)};
+    if (p.h_slices > 0) {
+        const unsigned blocks = 8u * (unsigned)p.h_groups * (unsigned)((p.h_slices + 7) / 8);
+        hipLaunchKernelGGL(anticipate_halves_kernel, dim3(blocks), dim3(kScatterThreads), p.h_lds_bytes, s, hv, worigin,
+                           p.w_slices, status);
+    } else {
+        const unsigned blocks = 8u * (unsigned)p.groups * (unsigned)((p.slices + 7) / 8);
+        hipLaunchKernelGGL(anticipate_scatter_kernel, dim3(blocks), dim3(kScatterThreads), p.lds_bytes, s,
+                           pred_tokens, instance_id, arrival_bucket, rate, n_req, n_inst, horizon,
+                           p.rows_per_group, p.groups, p.slices, p.slice_len, partial, partial_ovf, worigin, p.w_slices, status);
+    }
     hipLaunchKernelGGL(anticipate_reduce_kernel, dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, partial, partial_ovf, p.slices, n_inst, horizon,
-                       wpartial, wovf, worigin, p.w_slices, p.w_buckets, load, overflow, status);
+                       wpartial, wovf, worigin, p.w_slices, p.w_buckets, hv, load, overflow, status);
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }
 

@@ -123,6 +123,31 @@ def test_long_streams_in_any_order_with_exceptions():
         check(inp)
 
 
+@pytest.mark.parametrize("n_inst,horizon,hot", [(256, 600, [7]), (256, 600, [71, 199]), (256, 601, [0, 64, 255]), (130, 597, [65, 129]),
+                                                (200, 1100, [33]), (66, 1023, [65])])
+def test_any_order_loads_beyond_sixteen_bits(n_inst, horizon, hot):
+    """Long streams in any order whose loads leave 16 bits within a slice, on rows of either half of a word, the last
+    row and the last bucket, beside rows that stay inside, and at exactly 65535 and 65536 tokens."""
+    rng = np.random.default_rng(n_inst + horizon)
+    n = 3_000_001
+    print(f"anticipator wide loads K={n_inst} Hz={horizon} hot={hot}", flush=True)
+    k = rng.integers(0, n_inst, n, dtype=np.int32)
+    d = rng.integers(0, 50, n, dtype=np.int32)
+    a = rng.integers(0, horizon, n, dtype=np.int32)
+    rate = rng.integers(20, 200, n_inst, dtype=np.int32)
+    for h, bucket in zip(hot, [horizon - 1, 5, 300]):
+        pick = rng.random(n) < 0.005
+        k[pick], d[pick], a[pick] = h, 4000, bucket
+        rate[h] = 5000
+    check(wl.AnticipatorInputs(d, k, a, rate, n_inst, horizon))
+    for top in (65535, 65536):                         # one cell of an otherwise empty row, at the edge of the counter
+        k2, d2 = np.where(k == hot[0], (hot[0] + 1) % n_inst, k), d.copy()
+        k2[:2], d2[:2], a[:2] = hot[0], [top - 30_000, 30_000], 17
+        rate2 = rate.copy()
+        rate2[hot[0]] = 65535
+        check(wl.AnticipatorInputs(d2, k2, a, rate2, n_inst, horizon))
+
+
 def test_accumulates_into_existing_map():
     inp = wl.make_anticipator_inputs("medium", seed=2, n=5000)
     rng = np.random.default_rng(0)
