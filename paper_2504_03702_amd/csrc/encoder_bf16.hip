@@ -85,11 +85,6 @@ __global__ __launch_bounds__(256) void ln_stats_gather_kernel(const float2* __re
 
 }  // namespace
 
-// Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
-// Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
-// 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
-#define PS_FUSED_ROWS 3584
-
 // The first feed-forward map of the per-request pass: the small tiles read W once for both halves of the operand but
 // take two passes' worth of places; beyond 1024 of their 128 x 64 tiles (two waves of the chip's 512 places) the large
 // kernel's 128 x 128 tiles are faster, with the same bits.  Small against large: hidden 768 (ffn 3072) 1280 requests, 960

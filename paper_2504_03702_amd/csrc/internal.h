@@ -145,6 +145,10 @@ void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const 
 // The per-request forms (EPI_GELU_SPLIT, EPI_RESIDUAL_MAPPED, EPI_Q_MAPPED) for calls of at most PS_SKINNY_ROWS
 // requests: a stream over W with the contraction split among a workgroup's wavefronts.
 #define PS_SKINNY_ROWS 16
+// Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
+// Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
+// 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
+#define PS_FUSED_ROWS 3584
 enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
 struct SkinnyArgs {
     const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)

@@ -447,7 +447,9 @@ void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, cons
 void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengths, int32_t n_req, int64_t n_tokens,
                  const Workspace& ws, ps_status* st, hipStream_t s) {
     const int h = m->info.hidden / 256, f = m->info.ffn / 256;
-    const int4 plan_cols = m->info.dtype == 1 ? make_int4(3 * h, 2 * h, h, f) : make_int4(0, 0, 0, 0);
+    // (calls that take the small tiles only, run_encoder_bf16, need none; nor do fp32 models)
+    const bool planned = m->info.dtype == 1 && (n_req > PS_SKINNY_ROWS || ws.max_rows > PS_FUSED_ROWS);
+    const int4 plan_cols = planned ? make_int4(3 * h, 2 * h, h, f) : make_int4(0, 0, 0, 0);
     hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft, m->info.max_pos,
                        (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), plan_cols, ws.meta, ws.seq_len,
                        ws.row_start, ws.qtile_start, ws.bad_req, ws.head_done, st);

@@ -141,84 +141,99 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     const int lda = DUAL && !NORM ? 2 * K : K;
     const int64_t wg = (int64_t)16 * K;                 // next column group: 16 rows of W further
     const bool on = frow < n_req;
-    constexpr int U = NORM ? 2 : DUAL ? 3 : 4;          // rounds whose loads are in flight together
-    for (int sh = 0; sh < SH; ++sh) {
-        const int share = wave * SH + sh;
-        const int r_begin = share * total_rounds / kSkinnyShares, rounds = (share + 1) * total_rounds / kSkinnyShares - r_begin;
-        const int k0 = 64 * r_begin + 16 * fq;
-        // A share of no rounds (K below 512) makes its loads all the same, which keeps the schedule of the others, but all
-        // lanes from one place: a round's worth of W through the cache for nothing held a map of hidden 256 12 us, not 8.
-        const bool some = rounds > 0;
-        const int64_t a_at = some ? arow * lda + k0 : 0, wg_at = some ? wg : 0;
-        const bf16_t* ap = (NORM ? res.y_hi : p.A) + a_at;
-        const bf16_t* lp = NORM ? res.y_lo + a_at : ap + K;
-        const bf16_t* wp = p.W + (some ? (int64_t)(n0 + frow) * K + k0 : 0);
-        sk_f32x4 acc[4];
+    // A wavefront's shares are neighbours in k: it goes through their rounds in one run, so the loads in flight together
+    // may belong to two shares.  A share of no rounds (K below 512) leaves zeros.  Two rounds at a time, in a loop that is
+    // not unrolled: what a unit's address path takes for lanes that read a row each (not the trip to memory) and, in code
+    // that runs once, the fetching of instructions are what this costs.  One prompt, hidden 768 / 3072, us a launch, before
+    // (three rounds at a time, share by share, absent ones loaded too) / one / two / three rounds: output projection
+    // 9.4 / 6.9 / 6.9 / 7.3, first feed-forward map 12.7 / 12.4 / 12.4 / 12.4, second 15.7 / 16.0 / 16.1 / 16.4.  Reading 64
+    // bytes of a row per quad of lanes and exchanging the chunks among them costs more than it saves (10.5, 16.7, 24.8).
+    constexpr int U = 2;                                // rounds whose loads are in flight together
+    const int first = wave * SH;
+    const int r0 = first * total_rounds / kSkinnyShares, r1 = (first + SH) * total_rounds / kSkinnyShares;
+    sk_f32x4 acc[4];
+    int share = first, share_end = (first + 1) * total_rounds / kSkinnyShares;
+    auto clear = [&]() {
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int t0 = 0; t0 < max(rounds, 1); t0 += U) {
-            sk_bf16x8 fa[U][2] = {}, fl[DUAL ? U : 1][2] = {}, fw[U][4][2];
-            float4 gv[NORM ? U : 1][4], bb[NORM ? U : 1][4];
+    };
+    auto close_shares = [&](int t) {                    // round t belongs to a later share
+        while (share < first + SH && t >= share_end) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = min(t0 + u, max(rounds, 1) - 1);   // (past the end: the last round again, not used)
+            for (int g = 0; g < 4; ++g) s_part[share][g][lane] = acc[g];
+            clear();
+            ++share;
+            share_end = (share + 1) * total_rounds / kSkinnyShares;
+        }
+    };
+    clear();
+    const bf16_t* ap = (NORM ? res.y_hi : p.A) + arow * lda + 16 * fq;
+    const bf16_t* lp = NORM ? res.y_lo + arow * lda + 16 * fq : ap + K;
+    const bf16_t* wp = p.W + (int64_t)(n0 + frow) * K + 16 * fq;
+    const float *gp = NORM ? res.gamma + 16 * fq : nullptr, *bp = NORM ? res.beta + 16 * fq : nullptr;
+#pragma unroll 1
+    for (int t0 = r0; t0 == r0 || t0 < r1; t0 += U) {
+        sk_bf16x8 fa[U][2] = {}, fl[DUAL ? U : 1][2] = {}, fw[U][4][2];
+        float4 gv[NORM ? U : 1][4], bb[NORM ? U : 1][4];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (on) {                           // (the other lanes' rows are nobody's)
-                        fa[u][h] = *(const sk_bf16x8*)(ap + 64 * t + 8 * h);
-                        if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
-                    }
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u;
+            if (t >= r1) continue;                      // uniform
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg_at + 64 * t + 8 * h);
+            for (int h = 0; h < 2; ++h) {
+                if (on) {                               // (the other lanes' rows are nobody's)
+                    fa[u][h] = *(const sk_bf16x8*)(ap + 64 * t + 8 * h);
+                    if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
                 }
-                if (NORM) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        gv[u][q] = *(const float4*)(res.gamma + k0 + 64 * t + 4 * q);
-                        bb[u][q] = *(const float4*)(res.beta + k0 + 64 * t + 4 * q);
-                    }
-                }
+                for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg + 64 * t + 8 * h);
             }
-            if (sh == 0 && t0 == 0) {
-                asm volatile("" ::: "memory");          // the operands first
-                if (wave == 0) epilogue_loads();
-                if (GATHER && p.stats_from == SKINNY_STATS_PIECES) ast = pieces.stats(p.inv_n, p.eps);
-            }
+            if (NORM) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (t0 + u < rounds) {
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (NORM) {
-                            union { sk_bf16x8 v; uint32_t w[4]; } yh, yl;
-                            yh.v = fa[u][h];
-                            yl.v = fl[u][h];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const float4 ga = gv[u][2 * h + (t >> 1)], be = bb[u][2 * h + (t >> 1)];
-                                const float x0 = ln_apply(__uint_as_float(yh.w[t] << 16), __uint_as_float(yl.w[t] << 16), ast,
-                                                          (t & 1) ? ga.z : ga.x, (t & 1) ? be.z : be.x);
-                                const float x1 = ln_apply(__uint_as_float(yh.w[t] & 0xffff0000u), __uint_as_float(yl.w[t] & 0xffff0000u),
-                                                          ast, (t & 1) ? ga.w : ga.y, (t & 1) ? be.w : be.y);
-                                const uint32_t o = pack_bf16x2(x0, x1);
-                                yh.w[t] = o;
-                                yl.w[t] = pack_bf16x2(x0 - __uint_as_float(o << 16), x1 - __uint_as_float(o & 0xffff0000u));
-                            }
-                            fa[u][h] = yh.v;
-                            fl[u][h] = yl.v;
-                        }
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][h], fw[u][g][h], acc[g], 0, 0, 0);
-                            if (DUAL) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl[u][h], fw[u][g][h], acc[g], 0, 0, 0);
-                        }
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    gv[u][q] = *(const float4*)(gp + 64 * t + 4 * q);
+                    bb[u][q] = *(const float4*)(bp + 64 * t + 4 * q);
                 }
             }
         }
+        if (t0 == r0) {
+            asm volatile("" ::: "memory");              // the operands first
+            if (wave == 0) epilogue_loads();
+            if (GATHER && p.stats_from == SKINNY_STATS_PIECES) ast = pieces.stats(p.inv_n, p.eps);
+        }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) s_part[share][g][lane] = acc[g];
+        for (int u = 0; u < U; ++u) {
+            if (t0 + u >= r1) continue;
+            close_shares(t0 + u);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (NORM) {
+                    union { sk_bf16x8 v; uint32_t w[4]; } yh, yl;
+                    yh.v = fa[u][h];
+                    yl.v = fl[u][h];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float4 ga = gv[u][2 * h + (t >> 1)], be = bb[u][2 * h + (t >> 1)];
+                        const float x0 = ln_apply(__uint_as_float(yh.w[t] << 16), __uint_as_float(yl.w[t] << 16), ast,
+                                                  (t & 1) ? ga.z : ga.x, (t & 1) ? be.z : be.x);
+                        const float x1 = ln_apply(__uint_as_float(yh.w[t] & 0xffff0000u), __uint_as_float(yl.w[t] & 0xffff0000u),
+                                                  ast, (t & 1) ? ga.w : ga.y, (t & 1) ? be.w : be.y);
+                        const uint32_t o = pack_bf16x2(x0, x1);
+                        yh.w[t] = o;
+                        yl.w[t] = pack_bf16x2(x0 - __uint_as_float(o << 16), x1 - __uint_as_float(o & 0xffff0000u));
+                    }
+                    fa[u][h] = yh.v;
+                    fl[u][h] = yl.v;
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][h], fw[u][g][h], acc[g], 0, 0, 0);
+                    if (DUAL) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl[u][h], fw[u][g][h], acc[g], 0, 0, 0);
+                }
+            }
+        }
     }
+    close_shares(total_rounds);
     __syncthreads();
     if (wave < 4) {                                     // column group `wave`: the eight partial results in order
         sk_f32x4 t = s_part[0][wave][lane];
@@ -236,7 +251,6 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
 #pragma unroll
         for (int e = 0; e < 4; ++e) st[e] = make_float2(__shfl(ast.x, 4 * fq + e, 64), __shfl(ast.y, 4 * fq + e, 64));
     }
-    sk_f32x4 acc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = s_sum[g][lane];
     if (EPI == EPI_GELU_SPLIT) {
