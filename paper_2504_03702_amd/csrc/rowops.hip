@@ -48,8 +48,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
                                                     int32_t* seq_len, int32_t* row_start,
                                                     int32_t* qtile_start, int32_t* bad_req,
                                                     int32_t* head_done, ps_status* st) {
-    __shared__ long long s_rows[1024];
-    __shared__ long long s_tiles[1024];
+    __shared__ long long s_rows[16], s_tiles[16];     // totals of the wavefronts
     __shared__ long long s_cut_rows, s_cut_tiles;     // rows / query tiles in front of the first request that does not fit
     const int tid = threadIdx.x;
     const int per = (n_req + 1023) / 1024;
@@ -69,26 +68,32 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
         rows += (S + PS_ROW_ALIGN - 1) / PS_ROW_ALIGN * PS_ROW_ALIGN;
         tiles += (S + PS_ATT_BQ - 1) / PS_ATT_BQ;
     }
-    s_rows[tid] = rows;
-    s_tiles[tid] = tiles;
+    // exclusive prefix sums over the threads: within a wavefront, then the wavefronts in front of it
+    long long row_incl = rows, tile_incl = tiles;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long a = __shfl_up(row_incl, o, 64), b = __shfl_up(tile_incl, o, 64);
+        if ((tid & 63) >= o) { row_incl += a; tile_incl += b; }
+    }
+    if ((tid & 63) == 63) {
+        s_rows[tid >> 6] = row_incl;
+        s_tiles[tid >> 6] = tile_incl;
+    }
     __syncthreads();
-    // inclusive scan over the 1024 per-thread sums
-    for (int d = 1; d < 1024; d <<= 1) {
-        long long a = 0, b = 0;
-        if (tid >= d) { a = s_rows[tid - d]; b = s_tiles[tid - d]; }
-        __syncthreads();
-        s_rows[tid] += a;
-        s_tiles[tid] += b;
-        __syncthreads();
+    long long row = row_incl - rows, tile = tile_incl - tiles, all_rows = 0, all_tiles = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < tid >> 6) { row += s_rows[w]; tile += s_tiles[w]; }
+        all_rows += s_rows[w];
+        all_tiles += s_tiles[w];
     }
     if (tid == 0) {
-        s_cut_rows = s_rows[1023];
-        s_cut_tiles = s_tiles[1023];
+        s_cut_rows = all_rows;
+        s_cut_tiles = all_tiles;
     }
     __syncthreads();
     // Row starts are non-decreasing, so the requests that do not fit the workspace are a suffix: the first of
     // them starts where the last fitting one ends.
-    long long row = s_rows[tid] - rows, tile = s_tiles[tid] - tiles;
     bool cut_here = false;
     long long my_cut_rows = 0, my_cut_tiles = 0;
     for (int r = r0; r < r1; ++r) {
