@@ -18,8 +18,11 @@
 // while the other wavefronts are already at the next request.  An instance's state is touched by its own
 // wavefront only, so the exchange of the wavefronts' minima is the one barrier of a request; up to 64
 // instances need none.
+// A decision is some 150 instructions of one wavefront after the other (no more than one to a SIMD is at work), so their
+// number counts as well: where a bound on queues and windows allows, scores are made in one register (walk_narrow).
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
-// window in registers for every request, 3.09 ms this way.
+// window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.09 in one register; 64
+// instances 2.06 and 1.47.  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
 #include <type_traits>
 
 #include "device_util.h"
@@ -152,6 +155,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         s_pre[inst] = kMin;
         s_suf[n_blocks * pitch + inst] = kMin;
     }
+    if (tid < 32) s_best[tid] = make_int4(0x7fffffff, 0, 0, 0);
     __syncthreads();
     if (wave >= nw) return;
 
@@ -214,17 +218,18 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     } else if (n_blocks > 0) {
         for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(std::false_type{}, i, 0, 0);
     }
-    // The largest window value of all instances (2^30 at the least), uniform.
-    auto largest = [&]() {
-        int top = mine ? s_suf[inst] : kMin;
+    // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
+    int par = 0;
+    // The largest of the lanes' values (0 at the least), uniform over the workgroup.
+    auto largest = [&](int top) {
         for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
         if (nw > 1) {
-            if (lane == 0) s_best[wave].x = top;                 // (last read two requests ago)
+            if (lane == 0) s_best[par + wave].x = top;           // (the slots that are written next)
             __syncthreads();
-            for (int w = 0; w < nw; ++w) top = max(top, s_best[w].x);
+            for (int w = 0; w < nw; ++w) top = max(top, s_best[par + w].x);
             __syncthreads();
         }
-        return __builtin_amdgcn_readfirstlane(max(top, 1 << 30));
+        return __builtin_amdgcn_readfirstlane(max(top, 0));
     };
 
     const long long kNone = 0x7fffffffffffffffll;
@@ -243,11 +248,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         int out_i = -1, out_lo = 0, out_hi = 0;
         for (int q = 0; q < cnt; ++q) {
             const int P = __builtin_amdgcn_readlane(vP, q), D = __builtin_amdgcn_readlane(vD, q);
-            // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
-            const int par = (q & 1) * 16;
             if (P < 0 || D < 0) {
                 if (tid == 0) report_fault(st, PS_ST_BAD_RECORD, base + q);
-                if (nw > 1) __builtin_amdgcn_s_barrier();
                 continue;
             }
             const int Dc = __builtin_amdgcn_readlane(vDc, q), blk = __builtin_amdgcn_readlane(v_win, q);
@@ -286,6 +288,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 // (wavefronts are in the order of their instances)
                 best = wave_min(lane < nw ? ((long long)o_hi << 32) | (unsigned)o_lo : kNone, lane < nw, src);
                 best_i = __builtin_amdgcn_readlane(o_i, src);
+                par ^= 16;
             }
             if (lane == q) { out_i = best_i; out_lo = (int)best; out_hi = (int)(best >> 32); }
             if (inst == best_i) { qp += P; cd += D; s100 += add100; }
@@ -296,19 +299,130 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
             score100[base + lane] = ((long long)out_hi << 32) | (unsigned)out_lo;
         }
     };
-    // bound: no window value is above it (a request raises it by its tokens and the window; taken afresh when that has
-    // added up)
-    long long bound = largest();
+    // The same with less to do for a request: blocks of four slots (SMALL), and scores, peaks and limits that a bound shows
+    // to lie in [0, 2^30), peaks below 2^24, so that one register holds a score and a full-rate multiply makes it.  What a
+    // request's ramp adds to the block it ends in is worked out for 64 requests at once; what it adds to a lane's slots of
+    // the chosen window, while the exchange is under way.
+    auto walk_narrow = [&](auto many, int base, int cnt, int vP, int vD) {
+        const int vDc = min(max(vD, 0), window), vb = vDc >> 2, vw = min(vb, n_blocks - 1);
+        const int v_pre = vb * row4, v_suf = ((vDc + 3) >> 2) * row4, v_win = vw * row16;
+        const int v_add = (int)(100u * ((unsigned)vP + (unsigned)vD));
+        int v_ramp[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v_ramp[e] = 4 * vw + e < vDc ? vP + 4 * vw + e : 0;
+        const bool good = lane < cnt && vP >= 0 && vD >= 0;
+        if (wave == 0 && lane < cnt && !good) report_fault(st, PS_ST_BAD_RECORD, base + lane);
+        int out_i = -1, out_s = 0, dP = 0;
+        // lanes without an instance stay above every score
+        const int lim = mine ? (int)min(thr, 0x7fffffffll) : 0x7fffffff, s0 = mine ? (int)s100 : 1 << 30;
+        int s32 = s0;
+        for (unsigned long long todo = __ballot(good); todo; todo &= todo - 1) {
+            const int q = __builtin_ctzll(todo);
+            const int4 w = *(const int4*)((const char*)(s_win + ic) + __builtin_amdgcn_readlane(v_win, q));
+            const int pre = *(const int*)((const char*)(s_pre + ic) + __builtin_amdgcn_readlane(v_pre, q));
+            const int suf = *(const int*)((const char*)(s_suf + ic) + __builtin_amdgcn_readlane(v_suf, q));
+            const int P = __builtin_amdgcn_readlane(vP, q), Dc = __builtin_amdgcn_readlane(vDc, q);
+            const int add = __builtin_amdgcn_readlane(v_add, q);
+            int pk = max(max(w.x + __builtin_amdgcn_readlane(v_ramp[0], q), w.y + __builtin_amdgcn_readlane(v_ramp[1], q)),
+                         w.z + __builtin_amdgcn_readlane(v_ramp[2], q));
+            pk = max(max(pk, w.w + __builtin_amdgcn_readlane(v_ramp[3], q)), pre + P);
+            pk = max(max(pk, suf), 0);                           // (a peak below 0 is no more over a limit than one of 0)
+            int pen = max((int)__umul24(pk, 100) - lim, 0);
+            if (beta != 1) pen *= beta;
+            const int L = s32 + pen + add;
+            int m = dpp_min<0x111, 0xf>(L);                      // as in wave_min
+            m = dpp_min<0x112, 0xf>(m);
+            m = dpp_min<0x114, 0xf>(m);
+            m = dpp_min<0x118, 0xf>(m);
+            m = dpp_min<0x142, 0xa>(m);
+            m = dpp_min<0x143, 0xc>(m);
+            int best = __builtin_amdgcn_readlane(m, 63);
+            int best_i = 64 * wave + __builtin_ctzll(__ballot(L == best));
+            int2 o = make_int2(0, 0);
+            if (many.value) {
+                if (lane == 0) *(int2*)(s_best + par + wave) = make_int2(best, best_i);
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                o = *(const int2*)(s_best + par + (lane & 15));  // (slots no wavefront writes hold 2^31 - 1)
+                par ^= 16;
+            }
+            int r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = 4 * u_blk + e < Dc ? P + 4 * u_blk + e : 0;
+            if (many.value) {
+                m = dpp_min<0x111, 0xf>(o.x);
+                m = dpp_min<0x112, 0xf>(m);                      // lane 3 has the first four
+                if (nw > 4) {
+                    m = dpp_min<0x114, 0xf>(m);
+                    m = dpp_min<0x118, 0xf>(m);
+                }
+                best = __builtin_amdgcn_readlane(m, nw > 4 ? 15 : 3);
+                best_i = __builtin_amdgcn_readlane(o.y, __builtin_ctzll(__ballot(o.x == best)));
+            }
+            if (lane == q) { out_i = best_i; out_s = best; }
+            if (inst == best_i) { s32 += add; dP += P; }
+            if ((best_i >> 6) == wave && Dc > 0) {               // as in update
+                int4 v = u_win[best_i];
+                v.x += r[0];
+                v.y += r[1];
+                v.z += r[2];
+                v.w += r[3];
+                if (u_low && u_live) u_win[best_i] = v;
+                const int t = 4 * u_blk;
+                m = max(v.x + (u_low && t < window ? t : 0), v.y + (u_low && t + 1 < window ? t + 1 : 0));
+                m = max(max(m, v.z + (u_low && t + 2 < window ? t + 2 : 0)), v.w + (u_low && t + 3 < window ? t + 3 : 0));
+                m = u_live ? m : kMin;
+                m = dpp_max<0x111, 0xf>(m);
+                m = dpp_max<0x112, 0xf>(m);
+                m = dpp_max<0x114, 0xf>(m);
+                m = dpp_max<0x118, 0xf>(m);
+                m = dpp_max<0x142, 0xa>(m);
+                if (u_live) u_out[best_i] = m;
+                asm volatile("" ::: "memory");
+            }
+        }
+        const int rise = s32 - s0;
+        s100 += rise;
+        qp += dP;
+        cd += rise / 100 - dP;
+        if (wave == 0 && lane < cnt) {
+            assigned[base + lane] = out_i;
+            score100[base + lane] = out_s;
+        }
+    };
+    // bound: no window value is above it, score_bound: no instance's queue and penalty are (a request raises them by its
+    // tokens and the window; taken afresh when that has added up).  A queue or limit below 0 counts as one without bound.
+    long long bound = largest(mine ? s_suf[ic] : kMin);
+    auto load100 = [&]() { return mine ? (s100 < 0 || thr < 0 || s100 >= 1 << 30 ? 1 << 30 : (int)s100) : 0; };
+    long long load_bound = SMALL ? largest(load100()) : 0;
+    bool narrow = SMALL;
     for (int base = 0; base < n_req; base += 64) {
         const int cnt = min(64, n_req - base), vP = nP, vD = nD;
         if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
-        int most = lane < cnt ? vP : 0;                          // largest prompt of the group
-        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
-        const long long rise = 64ll * ((long long)__builtin_amdgcn_readfirstlane(most) + window);
-        if (bound + rise >= 2147483647ll) bound = largest();
-        if (bound + rise >= 2147483647ll) walk(std::true_type{}, base, cnt, vP, vD);
+        int most = lane < cnt ? max(vP, 0) : 0, most_d = lane < cnt ? max(vD, 0) : 0;   // largest prompt and prediction of the group
+        for (int o = 32; o > 0; o >>= 1) {
+            most = max(most, __shfl_xor(most, o, 64));
+            if (SMALL) most_d = max(most_d, __shfl_xor(most_d, o, 64));
+        }
+        most = __builtin_amdgcn_readfirstlane(most);
+        const long long rise = 64ll * ((long long)most + window);
+        const long long load_rise = 6400ll * ((long long)most + __builtin_amdgcn_readfirstlane(most_d));
+        // (bounds of walk_narrow)
+        const long long most_peak = min((1ll << 24) - 1, ((1ll << 29) - 1) / (100ll * max(beta, 1)));
+        auto fits = [&]() { return bound + rise <= most_peak && load_bound + load_rise < 1 << 29; };
+        if ((narrow && !fits()) || bound + rise >= 2147483647ll) {
+            bound = largest(mine ? s_suf[ic] : kMin);
+            if (narrow) {
+                load_bound = largest(load100());
+                narrow = bound <= most_peak && load_bound < 1 << 29;     // (neither ever falls)
+            }
+        }
+        if (SMALL && narrow && fits()) {
+            if (nw > 1) walk_narrow(std::true_type{}, base, cnt, vP, vD);
+            else walk_narrow(std::false_type{}, base, cnt, vP, vD);
+        } else if (bound + rise >= 2147483647ll) walk(std::true_type{}, base, cnt, vP, vD);
         else walk(std::false_type{}, base, cnt, vP, vD);
         bound += rise;
+        load_bound += load_rise;
     }
     if (range_fault) report_fault(st, PS_ST_RANGE, -1);
     if (mine) { queued_p[inst] = qp; current_d[inst] = cd; }

@@ -101,6 +101,60 @@ def test_block_edges_and_full_lds(K, l, n):
     assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
 
 
+@pytest.mark.parametrize("K,l,n", [(65, 100, 200), (129, 12, 257), (256, 128, 300), (257, 60, 150), (600, 40, 190),
+                                   (130, 140, 140), (90, 0, 70), (1024, 29, 130)])
+@pytest.mark.parametrize("near", ["spread", "one instance", "last instance", "two wavefronts"])
+def test_choices_that_follow_each_other(K, l, n, near):
+    """Choices that stay with one instance, alternate between wavefronts, or fall on one that is alone in its wavefront;
+    requests without a prediction between them, a whole group of 64 of them, and at both ends.  Integers: everything must
+    match."""
+    print(f"route choices K={K} l={l} n={n} {near}", flush=True)
+    rng = np.random.default_rng(K * 31 + l)
+    P, D, win, cap, qp, cd = random_case(rng, K, l, n, True)
+    few = {"spread": [], "one instance": [min(K - 1, 70)], "last instance": [K - 1], "two wavefronts": [5, K - 1]}[near]
+    if few:
+        qp = qp + 10_000_000                                    # far more than the calls below add to the others
+        qp[few] = 0
+    D[rng.random(n) < 0.2] = 0
+    bad = rng.random(n) < 0.1
+    bad[[0, -1]] = True
+    if n >= 192:
+        bad[64:128] = True
+    D[bad & (rng.random(n) < 0.5)] = -1
+    P[bad & (D >= 0)] = -2
+    a, s, w, q2, c2, flags, first = run_route(P, D, win, cap, qp, cd)
+    ok = ~bad
+    ra, rs, rw, rq, rc = orr.route(P[ok], D[ok], win, cap, qp, cd)
+    assert flags == ps.PS_ST_BAD_RECORD and first == 0
+    assert np.array_equal(a[ok], ra) and np.array_equal(s[ok], rs)
+    assert (a[bad] == -1).all() and (s[bad] == 0).all()
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
+@pytest.mark.parametrize("K", [5, 64, 130, 260])
+@pytest.mark.parametrize("beta,peak,queued", [(1, (1 << 29) // 100, 0), (1, (1 << 24), 0), (3, (1 << 29) // 300, 0),
+                                              (1, 1000, (1 << 29) // 100), (0, 1 << 24, 5000), (700, 4000, 100),
+                                              (1, 1000, -5), (1, -70000, 10)])
+def test_values_that_pass_the_bounds_of_the_short_form(K, beta, peak, queued):
+    """Scores and peaks of a call that start below the bounds for one-register scores and pass them on the way (each
+    bound, with the penalty's factor), or lie outside from the start; limits of 0 and queues below 0 among them."""
+    print(f"route bounds K={K} beta={beta} peak={peak} queued={queued}", flush=True)
+    rng = np.random.default_rng(K + beta)
+    P, D, win, cap, qp, cd = random_case(rng, K, 50, 400, True)
+    win = peak - rng.integers(0, 60_000, (K, 50)) - np.arange(K)[:, None] % 7 * 3000
+    cap[::3] = 0
+    if queued > 1 << 20:
+        qp = queued - rng.integers(0, 90_000, K)
+    elif queued < 0:
+        qp[K // 2] = queued
+        cd[K // 2] = 0
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd, beta=beta)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd, beta=beta)
+    assert flags == 0
+    assert np.array_equal(a, ra) and np.array_equal(s, rs)
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
 def test_state_of_an_instance_with_huge_queues():
     """The state is carried exactly in int64 also where a hundredfold no longer fits (10^17 tokens as a mark of an
     instance that is out of use)."""
