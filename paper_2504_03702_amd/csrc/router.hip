@@ -12,8 +12,10 @@
 //     peak = max(P + max_{t < D'} (w[t] + t),  max_{t >= D'} w[t]),
 // a prefix maximum and a suffix maximum that change only for the instance a request is dispatched to.
 // They are kept per block of the window (at most 32 blocks: at window 100 the blocks are 4 slots), so a score
-// reads one prefix, one suffix and the one block that D' falls into.  One thread per instance scores it; the
-// wavefront that owns the chosen instance adds the request to its window with one lane per block and rebuilds
+// reads one prefix, one suffix and the one block that D' falls into (8 or 16 slots where the tables of smaller ones would
+// not fit).  One thread per instance scores it; the wavefront that owns the chosen instance adds the request to its
+// window with one lane per piece of four slots (per block, where the window has more than 32 pieces: 2048 requests over
+// 256 instances of 128 slots 3.17 ms by blocks and with scores in 64 bits, 1.25 by pieces and in one register) and rebuilds
 // both rows of maxima with one scan (prefixes in lanes 0..31, suffixes, in reverse order, in lanes 32..63),
 // while the other wavefronts are already at the next request.  An instance's state is touched by its own
 // wavefront only, so the exchange of the wavefronts' minima is the one barrier of a request; up to 64
@@ -21,8 +23,8 @@
 // A decision is some 150 instructions of one wavefront after the other (no more than one to a SIMD is at work), so their
 // number counts as well: where a bound on queues and windows allows, scores are made in one register (walk_narrow).
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
-// window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.09 in one register; 64
-// instances 2.06 and 1.47.  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
+// window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.06 in one register; 64
+// instances 2.06 and 1.43.  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
 #include <type_traits>
 
 #include "device_util.h"
@@ -108,8 +110,10 @@ __device__ __forceinline__ long long wave_min(long long v, bool part, int& src) 
 }
 
 // Launched with 1024 threads: all of them bring the windows in, then the wavefronts without instances leave.
-// SMALL: a block is one 16-byte piece (windows of 1 to 128 slots whose tables fit).
-template <bool SMALL>
+// CH: 16-byte pieces of a block (1, 2 or 4: windows of at most 32 pieces, which an update takes a lane each; 0: any
+// plan, a lane takes a block).  NARROW: with walk_narrow, for calls of 12 requests and more; what it needs in front costs the
+// others more than it saves (256 instances of 100 slots, 3 requests 27.8 us without, 29.3 with; 12 34.7 and 33.8).
+template <int CH, bool NARROW>
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
     int window, int block, int n_blocks, int pitch, int32_t* __restrict__ window_tokens,
@@ -160,20 +164,24 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     if (wave >= nw) return;
 
     // One instance's window with a request's ramp added on its first Dc slots, and its two rows of block maxima:
-    // all lanes of its wavefront, lane j and lane 32 + n_blocks - 1 - j for block j.
-    const int chunks = SMALL ? 1 : block >> 2;
-    const bool u_low = lane < 32, u_live = (lane & 31) < n_blocks;
-    const int u_blk = u_live ? (u_low ? lane & 31 : n_blocks - 1 - (lane & 31)) : 0;
-    int4* const u_win = s_win + u_blk * chunks * pitch;
+    // all lanes of its wavefront, lane j and lane 32 + n_parts - 1 - j for part j (a piece or a block) of the window.
+    const int chunks = CH ? CH : block >> 2;                     // pieces of a block
+    const int n_parts = CH ? pieces : n_blocks, part_chunks = CH ? 1 : block >> 2, part_slots = CH ? 4 : block;
+    const bool u_low = lane < 32, u_live = (lane & 31) < n_parts;
+    const int u_part = u_live ? (u_low ? lane & 31 : n_parts - 1 - (lane & 31)) : 0;
+    int4* const u_win = s_win + u_part * part_chunks * pitch;
+    const int u_blk = CH ? u_part / max(CH, 1) : u_part;
     int* const u_out = u_low ? s_pre + (u_blk + 1) * pitch : s_suf + u_blk * pitch;
+    // the last piece of a block has the prefix, the first the suffix
+    const bool u_put = u_live && (CH < 2 || u_part % max(CH, 1) == (u_low ? CH - 1 : 0));
     bool range_fault = false;                                    // a stored value has left int32
     auto update = [&](auto far, int i, int P, int Dc) {
         int m = kMin;
-        for (int c = 0; c < chunks; ++c) {
+        for (int c = 0; c < part_chunks; ++c) {
             int4* at = u_win + c * pitch + i;
             const int4 v4 = *at;
             int v[4] = {v4.x, v4.y, v4.z, v4.w};
-            const int t0 = u_blk * (SMALL ? 4 : block) + 4 * c;
+            const int t0 = u_part * part_slots + 4 * c;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int t = t0 + e;
@@ -189,28 +197,34 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         m = dpp_max<0x114, 0xf>(m);
         m = dpp_max<0x118, 0xf>(m);
         m = dpp_max<0x142, 0xa>(m);                              // the halves stay apart: lane 15 to row 1, 47 to row 3
-        if (u_live) u_out[i] = m;
+        if (u_put) u_out[i] = m;
         // the next score reads what other lanes have written: LDS serves a wavefront in order, the compiler has to
         // keep that order
         asm volatile("" ::: "memory");
     };
-    if (SMALL) {
+    if (CH > 0) {
         // every thread its own instance's rows
         if (mine) {
             int m = kMin;
             for (int b = 0; b < n_blocks; ++b) {
-                const int4 v = s_win[b * pitch + inst];
-                const int t = 4 * b;
-                m = max(m, (int)((unsigned)v.x + (unsigned)t));
-                if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
-                if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
-                if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    const int4 v = s_win[(b * CH + c) * pitch + inst];
+                    const int t = 4 * (b * CH + c);
+                    if (t < window) m = max(m, (int)((unsigned)v.x + (unsigned)t));
+                    if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
+                    if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
+                    if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
+                }
                 s_pre[(b + 1) * pitch + inst] = m;
             }
             m = kMin;
             for (int b = n_blocks - 1; b >= 0; --b) {
-                const int4 v = s_win[b * pitch + inst];
-                m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    const int4 v = s_win[(b * CH + c) * pitch + inst];
+                    m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
+                }
                 s_suf[b * pitch + inst] = m;
             }
         }
@@ -265,13 +279,13 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 int pk = kMin;
                 for (int c = 0; c < chunks; ++c) {
                     const int4 v = *(const int4*)((const char*)(s_win + ic) + (blk * chunks + c) * row16);
-                    const int t = blk * (SMALL ? 4 : block) + 4 * c;
+                    const int t = blk * (CH ? 4 * CH : block) + 4 * c;
                     pk = max(max(pk, v.x + (t < Dc ? P + t : 0)), v.y + (t + 1 < Dc ? P + t + 1 : 0));
                     pk = max(max(pk, v.z + (t + 2 < Dc ? P + t + 2 : 0)), v.w + (t + 3 < Dc ? P + t + 3 : 0));
                 }
                 pen += 100 * (long long)max(max(pk, pre + P), suf);
             }
-            pen = pen > 0 && (SMALL || window > 0) ? pen : 0;
+            pen = pen > 0 && (CH > 0 || window > 0) ? pen : 0;
             if (beta != 1) pen *= beta;
             const long long add100 = 100 * ((long long)P + D);
             const long long L = mine ? s100 + (pen + add100) : kNone;
@@ -299,17 +313,18 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
             score100[base + lane] = ((long long)out_hi << 32) | (unsigned)out_lo;
         }
     };
-    // The same with less to do for a request: blocks of four slots (SMALL), and scores, peaks and limits that a bound shows
+    // The same with less to do for a request: blocks of 4, 8 or 16 slots (CH), and scores, peaks and limits that a bound shows
     // to lie in [0, 2^30), peaks below 2^24, so that one register holds a score and a full-rate multiply makes it.  What a
     // request's ramp adds to the block it ends in is worked out for 64 requests at once; what it adds to a lane's slots of
     // the chosen window, while the exchange is under way.
     auto walk_narrow = [&](auto many, int base, int cnt, int vP, int vD) {
-        const int vDc = min(max(vD, 0), window), vb = vDc >> 2, vw = min(vb, n_blocks - 1);
-        const int v_pre = vb * row4, v_suf = ((vDc + 3) >> 2) * row4, v_win = vw * row16;
+        constexpr int B = CH ? 4 * CH : 4;                       // slots of a block
+        const int vDc = min(max(vD, 0), window), vb = vDc / B, vw = min(vb, n_blocks - 1);
+        const int v_pre = vb * row4, v_suf = (vDc + B - 1) / B * row4, v_win = vw * (B / 4) * row16;
         const int v_add = (int)(100u * ((unsigned)vP + (unsigned)vD));
-        int v_ramp[4];
+        int v_ramp[B];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v_ramp[e] = 4 * vw + e < vDc ? vP + 4 * vw + e : 0;
+        for (int e = 0; e < B; ++e) v_ramp[e] = B * vw + e < vDc ? vP + B * vw + e : 0;
         const bool good = lane < cnt && vP >= 0 && vD >= 0;
         if (wave == 0 && lane < cnt && !good) report_fault(st, PS_ST_BAD_RECORD, base + lane);
         int out_i = -1, out_s = 0, dP = 0;
@@ -318,14 +333,26 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         int s32 = s0;
         for (unsigned long long todo = __ballot(good); todo; todo &= todo - 1) {
             const int q = __builtin_ctzll(todo);
-            const int4 w = *(const int4*)((const char*)(s_win + ic) + __builtin_amdgcn_readlane(v_win, q));
+            const int at = __builtin_amdgcn_readlane(v_win, q);
+            int4 w[B / 4];
+#pragma unroll
+            for (int c = 0; c < B / 4; ++c) w[c] = *(const int4*)((const char*)(s_win + ic) + at + c * row16);
             const int pre = *(const int*)((const char*)(s_pre + ic) + __builtin_amdgcn_readlane(v_pre, q));
             const int suf = *(const int*)((const char*)(s_suf + ic) + __builtin_amdgcn_readlane(v_suf, q));
             const int P = __builtin_amdgcn_readlane(vP, q), Dc = __builtin_amdgcn_readlane(vDc, q);
             const int add = __builtin_amdgcn_readlane(v_add, q);
-            int pk = max(max(w.x + __builtin_amdgcn_readlane(v_ramp[0], q), w.y + __builtin_amdgcn_readlane(v_ramp[1], q)),
-                         w.z + __builtin_amdgcn_readlane(v_ramp[2], q));
-            pk = max(max(pk, w.w + __builtin_amdgcn_readlane(v_ramp[3], q)), pre + P);
+            int e[B];
+#pragma unroll
+            for (int c = 0; c < B / 4; ++c) {
+                e[4 * c] = w[c].x + __builtin_amdgcn_readlane(v_ramp[4 * c], q);
+                e[4 * c + 1] = w[c].y + __builtin_amdgcn_readlane(v_ramp[4 * c + 1], q);
+                e[4 * c + 2] = w[c].z + __builtin_amdgcn_readlane(v_ramp[4 * c + 2], q);
+                e[4 * c + 3] = w[c].w + __builtin_amdgcn_readlane(v_ramp[4 * c + 3], q);
+            }
+            int pk = e[0];
+#pragma unroll
+            for (int c = 1; c + 1 < B; c += 2) pk = max(max(pk, e[c]), e[c + 1]);
+            pk = max(max(pk, e[B - 1]), pre + P);
             pk = max(max(pk, suf), 0);                           // (a peak below 0 is no more over a limit than one of 0)
             int pen = max((int)__umul24(pk, 100) - lim, 0);
             if (beta != 1) pen *= beta;
@@ -347,7 +374,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
             }
             int r[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = 4 * u_blk + e < Dc ? P + 4 * u_blk + e : 0;
+            for (int e = 0; e < 4; ++e) r[e] = 4 * u_part + e < Dc ? P + 4 * u_part + e : 0;
             if (many.value) {
                 m = dpp_min<0x111, 0xf>(o.x);
                 m = dpp_min<0x112, 0xf>(m);                      // lane 3 has the first four
@@ -367,7 +394,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 v.z += r[2];
                 v.w += r[3];
                 if (u_low && u_live) u_win[best_i] = v;
-                const int t = 4 * u_blk;
+                const int t = 4 * u_part;
                 m = max(v.x + (u_low && t < window ? t : 0), v.y + (u_low && t + 1 < window ? t + 1 : 0));
                 m = max(max(m, v.z + (u_low && t + 2 < window ? t + 2 : 0)), v.w + (u_low && t + 3 < window ? t + 3 : 0));
                 m = u_live ? m : kMin;
@@ -376,7 +403,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 m = dpp_max<0x114, 0xf>(m);
                 m = dpp_max<0x118, 0xf>(m);
                 m = dpp_max<0x142, 0xa>(m);
-                if (u_live) u_out[best_i] = m;
+                if (u_put) u_out[best_i] = m;
                 asm volatile("" ::: "memory");
             }
         }
@@ -389,34 +416,35 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
             score100[base + lane] = out_s;
         }
     };
-    // bound: no window value is above it, score_bound: no instance's queue and penalty are (a request raises them by its
+    // bound: no window value is above it, load_bound: no instance's queue, a hundredfold, is (a request raises them by its
     // tokens and the window; taken afresh when that has added up).  A queue or limit below 0 counts as one without bound.
     long long bound = largest(mine ? s_suf[ic] : kMin);
     auto load100 = [&]() { return mine ? (s100 < 0 || thr < 0 || s100 >= 1 << 30 ? 1 << 30 : (int)s100) : 0; };
-    long long load_bound = SMALL ? largest(load100()) : 0;
-    bool narrow = SMALL;
+    bool narrow = NARROW;
+    long long load_bound = narrow ? largest(load100()) : 0;
     for (int base = 0; base < n_req; base += 64) {
         const int cnt = min(64, n_req - base), vP = nP, vD = nD;
         if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
-        int most = lane < cnt ? max(vP, 0) : 0, most_d = lane < cnt ? max(vD, 0) : 0;   // largest prompt and prediction of the group
+        // largest prompt and prediction of the group
+        int most = lane < cnt ? max(vP, 0) : 0, most_d = lane < cnt ? max(vD, 0) : 0;
         for (int o = 32; o > 0; o >>= 1) {
             most = max(most, __shfl_xor(most, o, 64));
-            if (SMALL) most_d = max(most_d, __shfl_xor(most_d, o, 64));
+            if (narrow) most_d = max(most_d, __shfl_xor(most_d, o, 64));
         }
         most = __builtin_amdgcn_readfirstlane(most);
         const long long rise = 64ll * ((long long)most + window);
         const long long load_rise = 6400ll * ((long long)most + __builtin_amdgcn_readfirstlane(most_d));
-        // (bounds of walk_narrow)
-        const long long most_peak = min((1ll << 24) - 1, ((1ll << 29) - 1) / (100ll * max(beta, 1)));
-        auto fits = [&]() { return bound + rise <= most_peak && load_bound + load_rise < 1 << 29; };
+        // what walk_narrow asks for: peaks below 2^24, penalties and the rest of a score below 2^29
+        auto peaks_fit = [&](long long peak) { return peak < 1 << 24 && peak * 100 * max(beta, 1) < 1 << 29; };
+        auto fits = [&]() { return peaks_fit(bound + rise) && load_bound + load_rise < 1 << 29; };
         if ((narrow && !fits()) || bound + rise >= 2147483647ll) {
             bound = largest(mine ? s_suf[ic] : kMin);
             if (narrow) {
                 load_bound = largest(load100());
-                narrow = bound <= most_peak && load_bound < 1 << 29;     // (neither ever falls)
+                narrow = peaks_fit(bound) && load_bound < 1 << 29;     // (neither ever falls)
             }
         }
-        if (SMALL && narrow && fits()) {
+        if (NARROW && narrow && fits()) {
             if (nw > 1) walk_narrow(std::true_type{}, base, cnt, vP, vD);
             else walk_narrow(std::false_type{}, base, cnt, vP, vD);
         } else if (bound + rise >= 2147483647ll) walk(std::true_type{}, base, cnt, vP, vD);
@@ -655,15 +683,22 @@ __global__ __launch_bounds__(kRouteThreads) void route_reg_kernel(
               queued_p, current_d, t_mem_pct, beta, assigned + done, score100 + done, st);
 }
 
-// Microseconds for n requests, scanned / with the tables (the tables take 5 us to make where a block is one piece of 4
-// slots, 30 to 60 where the wavefronts make them block by block):
-//   blocks of 4: 64 instances of 100 slots, n = 1 11 / 15, 64 221 / 47;  256 of 100, n = 1 14 / 18, 2048 6553 / 1585
-//   blocks of 8 and 16: 256 of 128, n = 1 16 / 54, 64 219 / 151;  64 of 500, n = 1 12 / 71, 64 221 / 152, 2048 6802 / 2706
+// An update can take a window's pieces a lane each.
+bool by_piece(const RoutePlan& p) {
+    return (p.block == 4 || p.block == 8 || p.block == 16) && (int64_t)p.n_blocks * p.block <= 4 * kRouteMaxBlocks;
+}
+
+// Microseconds for n requests, scanned / with the tables (the tables take 5 us to make where updates go by pieces, 30 to
+// 60 where the wavefronts make them block by block):
+//   by pieces: 256 instances of 100 slots (blocks of 4), n = 1 24.6 / 27.6, 2 28.3 / 28.1, 64 221 / 60;  256 of 120 (of 8)
+//   1 25.7 / 28.2, 3 32.8 / 28.9, 31 127 / 44;  256 of 128 (of 16) 2 29.3 / 29.0, 4 36.6 / 30.2, 31 127 / 46
+//   blocks of 8 and 16, not by pieces: 90 of 256, n = 8 41 / 59, 24 90 / 75;  64 of 500, n = 1 21 / 81, 24 102 / 109,
+//   31 126 / 118, 2048 6802 / 2671
 //   blocks of 32 and 48: 1024 of 29, n = 64 225 / 187;  16 of 1500, n = 64 227 / 253, 2048 6984 / 6053
 //   longer ones: 1 of 2000, n = 2048 6281 / 8372;  8 of 3000 11499 / 11415;  256 of 134 (one block each) 13979 / 15951
-bool tables_pay(int n_req, int window, int block) {
+bool tables_pay(int n_req, int window, const RoutePlan& p) {
     if (window == 0) return true;
-    return block == 4 ? n_req >= 3 : block <= 16 ? n_req >= 32 : block <= 48 && n_req >= 128;
+    return by_piece(p) ? n_req >= 3 : p.block <= 16 ? n_req >= 32 : p.block <= 48 && n_req >= 128;
 }
 
 }  // namespace
@@ -691,20 +726,36 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
                                 kRouteLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void*)route_reg_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<0, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<4, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess)
             return PS_EHIP;
         lds_attr_set = true;
     }
-#define PS_ROUTE(SMALL)                                                                                             \
-    hipLaunchKernelGGL(route_kernel<SMALL>, dim3(1), dim3(kRouteThreads), p.lds_bytes, s, prompt_tokens, pred_tokens, \
-                       n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens, capacity, queued_p,      \
+#define PS_ROUTE(...)                                                                                                    \
+    hipLaunchKernelGGL((route_kernel<__VA_ARGS__>), dim3(1), dim3(kRouteThreads), p.lds_bytes, s, prompt_tokens, pred_tokens, \
+                       n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens, capacity, queued_p,           \
                        current_d, t_mem_pct, beta, assigned, score100, status)
-    if (tables_pay(n_req, window, p.block)) {
-        if (p.block == 4) PS_ROUTE(true);
-        else PS_ROUTE(false);
+    if (tables_pay(n_req, window, p)) {
+        const bool narrow = n_req >= 12;
+        if (!by_piece(p)) PS_ROUTE(0, false);
+        else if (p.block == 4 && narrow) PS_ROUTE(1, true);
+        else if (p.block == 4) PS_ROUTE(1, false);
+        else if (p.block == 8 && narrow) PS_ROUTE(2, true);
+        else if (p.block == 8) PS_ROUTE(2, false);
+        else if (narrow) PS_ROUTE(4, true);
+        else PS_ROUTE(4, false);
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }
 #undef PS_ROUTE

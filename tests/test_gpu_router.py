@@ -102,7 +102,8 @@ def test_block_edges_and_full_lds(K, l, n):
 
 
 @pytest.mark.parametrize("K,l,n", [(65, 100, 200), (129, 12, 257), (256, 128, 300), (257, 60, 150), (600, 40, 190),
-                                   (130, 140, 140), (90, 0, 70), (1024, 29, 130)])
+                                   (130, 140, 140), (90, 0, 70), (1024, 29, 130), (256, 120, 40),
+                                   (250, 125, 3), (256, 128, 200)])
 @pytest.mark.parametrize("near", ["spread", "one instance", "last instance", "two wavefronts"])
 def test_choices_that_follow_each_other(K, l, n, near):
     """Choices that stay with one instance, alternate between wavefronts, or fall on one that is alone in its wavefront;
@@ -131,17 +132,17 @@ def test_choices_that_follow_each_other(K, l, n, near):
     assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
 
 
-@pytest.mark.parametrize("K", [5, 64, 130, 260])
+@pytest.mark.parametrize("K,l", [(5, 50), (64, 50), (130, 50), (260, 50), (70, 140), (100, 260), (6, 500), (256, 128)])
 @pytest.mark.parametrize("beta,peak,queued", [(1, (1 << 29) // 100, 0), (1, (1 << 24), 0), (3, (1 << 29) // 300, 0),
                                               (1, 1000, (1 << 29) // 100), (0, 1 << 24, 5000), (700, 4000, 100),
                                               (1, 1000, -5), (1, -70000, 10)])
-def test_values_that_pass_the_bounds_of_the_short_form(K, beta, peak, queued):
+def test_values_that_pass_the_bounds_of_the_short_form(K, l, beta, peak, queued):
     """Scores and peaks of a call that start below the bounds for one-register scores and pass them on the way (each
     bound, with the penalty's factor), or lie outside from the start; limits of 0 and queues below 0 among them."""
-    print(f"route bounds K={K} beta={beta} peak={peak} queued={queued}", flush=True)
+    print(f"route bounds K={K} l={l} beta={beta} peak={peak} queued={queued}", flush=True)
     rng = np.random.default_rng(K + beta)
-    P, D, win, cap, qp, cd = random_case(rng, K, 50, 400, True)
-    win = peak - rng.integers(0, 60_000, (K, 50)) - np.arange(K)[:, None] % 7 * 3000
+    P, D, win, cap, qp, cd = random_case(rng, K, l, 300, True)
+    win = peak - rng.integers(0, 60_000, (K, l)) - np.arange(K)[:, None] % 7 * 3000
     cap[::3] = 0
     if queued > 1 << 20:
         qp = queued - rng.integers(0, 90_000, K)
