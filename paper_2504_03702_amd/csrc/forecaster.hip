@@ -37,7 +37,8 @@ __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf
 // rounded; reciprocals get one Newton step.  tanh: below 0.6 z + z^3 P(z^2) (P: degree-5 least-squares fit on Chebyshev
 // nodes, largest relative error 7e-8, rms 2.5e-8), from there 1 - 2 / (1 + e^2|z|).
 __device__ __forceinline__ float one_over_one_plus_exp(float y) {
-    y = y > 87.0f ? 87.0f : y;                              // (the steps below must not meet an infinity; NaN stays)
+    // the steps below must meet no infinity, in e nor in t (as far out as this the result is 1 and 0 already); NaN stays
+    y = y > 87.0f ? 87.0f : y < -87.0f ? -87.0f : y;
     const float t = y * 1.44269504f, e = __builtin_amdgcn_exp2f(t);
     const float d = 1.0f + fmaf(e, fmaf(t, -0.693147182f, y), e), r = __builtin_amdgcn_rcpf(d);
     return fmaf(fmaf(-d, r, 1.0f), r, r);

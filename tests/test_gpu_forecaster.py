@@ -65,3 +65,33 @@ def test_register_tile_edges(S, H, k):
     err = np.abs(got - ref) / scale
     print(f"forecast S={S} H={H} k={k} max rel err {err.max():.2e}", flush=True)
     assert err.max() < TOL
+
+
+def set_field(x, name, unit, value):
+    """Unit `unit` of a vector field of every model of x."""
+    at, H = 0, x.hidden
+    for f in wl.FORECASTER_FIELDS:
+        if f == name:
+            x.weights[:, :, at + unit] = value
+        at += H * H if f.startswith("W_") else 1 if f == "b_out" else H
+
+
+# a workgroup a service, of both register tiles, and a wavefront a service
+@pytest.mark.parametrize("S,H,k", [(3, 8, 4), (5, 64, 24), (2048, 4, 4)])
+def test_gates_held_open_and_shut(S, H, k):
+    """Biases that hold a gate open or shut, infinite or so large that the exponent of their exponential overflows:
+    sigmoid and tanh saturate, forecasts are the definition's."""
+    print(f"forecast saturated S={S} H={H} k={k}", flush=True)
+    x = wl.make_forecaster_inputs(seed=S + H, n_services=S, hidden=H, k=k)
+    for unit, (name, value) in enumerate([("b_f", np.inf), ("b_i", 3e38), ("b_o", np.inf), ("b_h", -np.inf)]):
+        set_field(x, name, unit, value)
+    for unit, (name, value) in enumerate([("b_f", -np.inf), ("b_i", -3e38), ("b_o", -np.inf), ("b_h", 3e38)]):
+        set_field(x, name, H - 1 - unit, value)
+    got = run_forecast(x)
+    with np.errstate(over="ignore"):
+        ref = of.forecast_services([x.model(s, 0) for s in range(S)], [x.model(s, 1) for s in range(S)],
+                                   x.hist_p.astype(np.float64), x.hist_d.astype(np.float64),
+                                   x.mu[:, 0].astype(np.float64), x.mu[:, 1].astype(np.float64), x.mu[:, 2].astype(np.float64))
+    assert np.isfinite(ref).all() and (ref[:4] > 0).any()
+    scale = np.maximum(np.abs(ref), np.sqrt(np.mean(ref ** 2, axis=1, keepdims=True)))
+    assert (np.abs(got - ref) / scale).max() < TOL
