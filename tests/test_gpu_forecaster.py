@@ -95,3 +95,19 @@ def test_gates_held_open_and_shut(S, H, k):
     assert np.isfinite(ref).all() and (ref[:4] > 0).any()
     scale = np.maximum(np.abs(ref), np.sqrt(np.mean(ref ** 2, axis=1, keepdims=True)))
     assert (np.abs(got - ref) / scale).max() < TOL
+
+
+def test_error_of_the_gates_far_out():
+    """A gate's own relative error stays that of an exponential of one unit in the last place however far out the gate is:
+    2^-23 for e^-z, 2^-24 for the quotient's rounding and 2^-25 for the products in between, 2.1e-7 in all.  One unit whose
+    cell has grown to 20 (tanh 1 to the last bit) and an output gate at z: the forecast is the gate's value."""
+    S, k = 1024, 20
+    z = np.linspace(-86.0, 86.0, S).astype(np.float32)
+    x = wl.make_forecaster_inputs(seed=0, n_services=S, hidden=1, k=k)
+    x.weights[:], x.hist_p[:], x.hist_d[:], x.mu[:] = 0, 0, 0, 1
+    for name, value in [("b_h", 20.0), ("b_i", 100.0), ("b_f", 100.0), ("b_o", z[:, None]), ("w_out", 1.0)]:
+        set_field(x, name, 0, value)
+    ref = 1.0 / (1.0 + np.exp(-z.astype(np.float64)))
+    err = np.abs(run_forecast(x)[:2] / ref - 1.0)
+    print(f"gate error {err.max():.2e}, beyond 20 {err[:, np.abs(z) > 20].max():.2e}", flush=True)
+    assert err.max() < 2.1e-7
