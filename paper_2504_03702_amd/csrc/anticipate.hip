@@ -63,7 +63,7 @@ struct AntPlan {
     int64_t w_slice_len;
     size_t w_lds_bytes, w_partial_bytes, w_ovf_bytes, w_origin_bytes, w_partial_at, w_ovf_at, w_origin_at;
     // halves kernel (records in any order, twice as many rows a workgroup); h_slices == 0: not used
-    int h_rows, h_groups, h_slices, h_stride;
+    int h_rows, h_groups, h_slices, h_stride, h_row_bits, h_bucket_bits;
     int64_t h_slice_len;
     size_t h_lds_bytes, h_high_at, h_ovf_at, h_flag_at;
     bool ok;
@@ -119,6 +119,13 @@ void plan_window(AntPlan& p, int64_t n, int n_inst, int horizon, bool with_rate)
     p.total_bytes = p.w_origin_at + p.w_origin_bytes;
 }
 
+// Bits that hold any index below n.
+int bits_for(int n) {
+    int bits = 0;
+    while ((1 << bits) < n) ++bits;
+    return bits;
+}
+
 // Lays the halves kernel's results over the general and the windowed buffers (they are needed only where the windowed
 // kernel gave up), as many slices as fit; not used where a workgroup would not hold more rows than the general one's.
 void plan_halves(AntPlan& p, int64_t n, int n_inst, int horizon) {
@@ -126,10 +133,13 @@ void plan_halves(AntPlan& p, int64_t n, int n_inst, int horizon) {
     if (p.w_slices == 0) return;
     const int64_t per_pair = 4 * (int64_t)horizon + 2 * (8 + 4);  // counters, overflow and 1/rate of two rows
     int64_t fit = (kLdsBytes - kQueueBytes - 64) / per_pair * 2;
-    if (fit > 256) fit = 256;                                     // a queued record names its row in 8 bits
+    if (fit > 256) fit = 256;                                     // (measured up to here)
     p.h_groups = fit > 0 ? (int)((n_inst + fit - 1) / fit) : p.groups;
     if (p.h_groups >= p.groups || n * (p.groups - p.h_groups) < kHalvesMinSaved) return;
     p.h_rows = ((n_inst + p.h_groups - 1) / p.h_groups + 1) / 2 * 2;
+    // fields of a queued record; what LDS holds keeps the two below 19 bits together
+    p.h_row_bits = bits_for(p.h_rows);
+    p.h_bucket_bits = bits_for(horizon);
     p.h_stride = (horizon + 7) / 8 * 8;
     const int64_t slice_bytes = (int64_t)n_inst * (4 * (int64_t)p.h_stride + 8) + 4 * (int64_t)p.h_groups;
     int64_t s = (n + kMinSlice / 2 - 1) / (kMinSlice / 2);
@@ -367,11 +377,13 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(
 //
 // 44.1 M records over 256 instances of 600 buckets: 200 us in the general kernel, 146 here, of which about 105 are vector
 // instructions (19 a look, 48 a record); a queue entry names row, bucket and tokens in fields, so neither side multiplies
-// or divides by the row length.
+// or divides by the row length.  The fields are as wide as the call's rows and buckets ask for, which leaves 14 bits and
+// more to the tokens (12 as a fixed width: with 5 % of the predictions above 4096 284 us, the general kernel 220).
 struct HalvesArgs {
     const int32_t *pred, *inst, *arrival, *rate;
     int64_t n, slice_len;
     int n_inst, horizon, rows, groups, slices, stride;
+    int row_shift, d_bits;               // a queued record: row << row_shift | arrival bucket << d_bits | prediction less one
     uint16_t *low, *high;                // [instance][slice][stride]: the reduction of an instance reads one block
     int64_t* ovf;                        // [slice][instance]
     int32_t* wide;                       // [slice][group]: the upper halves are there too
@@ -407,7 +419,7 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
     unsigned long long mass = 0;                                // WIDE: bound on what any counter can have reached
 
     // one record of row `row`: D1 = its tokens less one
-    auto apply = [&](unsigned row, unsigned a, unsigned D1) {
+    auto apply = [&](unsigned row, unsigned a, unsigned D1) __attribute__((always_inline)) {
         const bool upper = !WIDE && row >= (unsigned)R;
         const unsigned D = D1 + 1u, w = WIDE ? row : min(row, row - (unsigned)R), sh = upper ? 16u : 0u;
         const unsigned dur = div_by_row(D1, s_rcp[row]) + 1u;                   // ceil(D / rate)
@@ -426,14 +438,14 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
             inside_sum -= over;
         }
     };
-    // up to 64 queued records, lane i entry head + i: row (8 bits) | arrival bucket (12 bits) | prediction less one (12 bits)
-    auto consume = [&](unsigned count) {
+    const unsigned d_most = 1u << p.d_bits, a_mask = (1u << (p.row_shift - p.d_bits)) - 1u;
+    // up to 64 queued records, lane i entry head + i
+    auto consume = [&](unsigned count) __attribute__((always_inline)) {
         if ((unsigned)lane < count) {
             const uint32_t e = q[(head + lane) & (kQueue - 1)];
-            apply(e >> 24, (e >> 12) & 0xfffu, e & 0xfffu);
+            apply(e >> p.row_shift, (e >> p.d_bits) & a_mask, e & (d_most - 1u));
         }
     };
-
     const int64_t begin = (int64_t)slice * p.slice_len, end = min(begin + p.slice_len, p.n);
     // four consecutive records per lane, 256 per wavefront and block, loads two blocks ahead (plain loads: the groups
     // of a slice share it through their XCD's L2)
@@ -451,29 +463,39 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
         b.a[0] = av.x; b.a[1] = av.y; b.a[2] = av.z; b.a[3] = av.w;
         return b;
     };
-    auto process = [&](const Block& b, int64_t blk, bool ragged) {
-        const int64_t idx = blk + lane * 4;
-        // validity of all four records at once; a block with a faulty record, one of more tokens than the queue takes, or
-        // the ragged tail is taken record by record, past the queue
+    auto process = [&](Block b, int64_t blk, bool ragged) __attribute__((always_inline)) {
+        // validity of all four records at once; a block with a faulty record, or the ragged tail, is looked at record by
+        // record first: what is not to be queued loses its tokens
         const unsigned dmax = max(max((unsigned)b.d[0], (unsigned)b.d[1]), max((unsigned)b.d[2], (unsigned)b.d[3]));
         const unsigned amax = max(max((unsigned)b.a[0], (unsigned)b.a[1]), max((unsigned)b.a[2], (unsigned)b.a[3]));
         const unsigned kmax = max(max((unsigned)b.k[0], (unsigned)b.k[1]), max((unsigned)b.k[2], (unsigned)b.k[3]));
-        const bool suspect = ragged || dmax > 4096u || amax >= (unsigned)horizon || kmax >= (unsigned)p.n_inst;
+        const bool suspect = ragged || dmax > (unsigned)PS_MAX_PRED || amax >= (unsigned)horizon || kmax >= (unsigned)p.n_inst;
         if (__any(suspect) || bad_rate_rows) {                 // uniform
-#pragma unroll 1
+            const int64_t idx = blk + lane * 4;
+#pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int kc = c == 0 ? b.k[0] : c == 1 ? b.k[1] : c == 2 ? b.k[2] : b.k[3];
-                const int dc = c == 0 ? b.d[0] : c == 1 ? b.d[1] : c == 2 ? b.d[2] : b.d[3];
-                const int ac = c == 0 ? b.a[0] : c == 1 ? b.a[1] : c == 2 ? b.a[2] : b.a[3];
-                const unsigned kk = (unsigned)(kc - k0);
-                const bool in = idx + c < end, k_ok = (unsigned)kc < (unsigned)p.n_inst, mine = k_ok && kk < (unsigned)rows;
-                bool ok = (unsigned)dc <= (unsigned)PS_MAX_PRED && (unsigned)ac < (unsigned)horizon;
+                const unsigned kk = (unsigned)(b.k[c] - k0);
+                const bool in = idx + c < end, k_ok = (unsigned)b.k[c] < (unsigned)p.n_inst, mine = k_ok && kk < (unsigned)rows;
+                bool ok = (unsigned)b.d[c] <= (unsigned)PS_MAX_PRED && (unsigned)b.a[c] < (unsigned)horizon;
                 if (mine && ok && s_rcp[kk] == 0.f) ok = false;
                 // a record outside every group is reported by group 0, others by their own group
                 if (report && in && ((!k_ok && g == 0) || (mine && !ok))) report_fault(st, PS_ST_BAD_RECORD, idx + c);
-                if (in && mine && ok && dc != 0) apply(kk, (unsigned)ac, (unsigned)dc - 1u);
+                if (!(in && mine && ok)) b.d[c] = 0;
             }
-            return;
+        }
+        if (__any(dmax > d_most)) {                            // records that no entry holds: applied at once, one a lane and turn
+            unsigned left = 0;
+            for (int c = 0; c < 4; ++c)
+                if ((unsigned)b.d[c] > d_most && (unsigned)(b.k[c] - k0) < (unsigned)rows) left |= 1u << c;
+            const unsigned taken = left;
+            while (__any(left != 0)) {
+                const int k = left & 1 ? b.k[0] : left & 2 ? b.k[1] : left & 4 ? b.k[2] : b.k[3];
+                const int d = left & 1 ? b.d[0] : left & 2 ? b.d[1] : left & 4 ? b.d[2] : b.d[3];
+                const int a = left & 1 ? b.a[0] : left & 2 ? b.a[1] : left & 4 ? b.a[2] : b.a[3];
+                if (left != 0) apply((unsigned)(k - k0), (unsigned)a, (unsigned)d - 1u);
+                left &= left - 1;
+            }
+            for (int c = 0; c < 4; ++c) b.d[c] = taken >> c & 1 ? 0 : b.d[c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -481,7 +503,7 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
             const bool m = (kk | (d1 & 0x80000000u)) < (unsigned)rows;          // (no tokens: d1 wraps)
             const unsigned long long mask = __builtin_amdgcn_ballot_w64(m);
             const unsigned pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, tail));
-            if (m) q[pos & (kQueue - 1)] = (kk << 24) | ((unsigned)b.a[c] << 12) | d1;
+            if (m) q[pos & (kQueue - 1)] = (kk << p.row_shift) | ((unsigned)b.a[c] << p.d_bits) | d1;
             tail += (unsigned)__popcll(mask);
             if (tail - head >= 64u) {
                 consume(64u);
@@ -582,8 +604,8 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_halves_kernel(Halv
     if (threadIdx.x == 0) p.wide[slice * p.groups + g] = wrapped;
     if (!wrapped) return;
     const int R = p.rows / 2;
-    halves_pass<true>(p, slice, g, k0, min(R, rows), lds_raw, false, nullptr, st);
-    if (rows > R) halves_pass<true>(p, slice, g, k0 + R, rows - R, lds_raw, false, nullptr, st);
+#pragma unroll 1
+    for (int r0 = 0; r0 < rows; r0 += R) halves_pass<true>(p, slice, g, k0 + r0, min(R, rows - r0), lds_raw, false, nullptr, st);
 }
 
 // Windowed scatter for records in arrival order: workgroup = slice of the records; LDS holds, for
@@ -1142,7 +1164,7 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
     }
     plan_halves(p, n_req, n_inst, horizon);
     HalvesArgs hv = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.h_slice_len, n_inst, horizon, p.h_rows, p.h_groups,
-                     p.h_slices, p.h_stride, (uint16_t*)wsb, (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at),
+                     p.h_slices, p.h_stride, 32 - p.h_row_bits, 32 - p.h_row_bits - p.h_bucket_bits, (uint16_t*)wsb, (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at),
                      (int32_t*)(wsb + p.h_flag_at)};
     if (p.h_slices > 0) {
         const unsigned blocks = 8u * (unsigned)p.h_groups * (unsigned)((p.h_slices + 7) / 8);

@@ -148,6 +148,48 @@ def test_any_order_loads_beyond_sixteen_bits(n_inst, horizon, hot):
         check(wl.AnticipatorInputs(d2, k2, a, rate2, n_inst, horizon))
 
 
+@pytest.mark.parametrize("n_inst,horizon", [(256, 600), (66, 1023), (130, 597)])
+def test_any_order_with_exceptions_on_sixteen_bit_counters(n_inst, horizon):
+    """What test_long_streams_in_any_order_with_exceptions does to the general kernel, on streams long enough for the
+    16-bit counters: accumulated, predictions up to the largest in most blocks of 256 records and around the most a
+    queued record's field holds (14 bits where rows and buckets take 18 of 32, 15 where they take 17), faulty records
+    and a row without a usable rate, and the latter two where a busy row makes both halves go through 32-bit counters."""
+    rng = np.random.default_rng(31 + n_inst)
+    n = 3_000_001
+    base = wl.AnticipatorInputs(rng.integers(0, 300, n, dtype=np.int32), rng.integers(0, n_inst, n, dtype=np.int32),
+                                rng.integers(0, horizon, n, dtype=np.int32), rng.integers(20, 200, n_inst, dtype=np.int32),
+                                n_inst, horizon)
+    at = lambda what: print(f"anticipator 16 bits K={n_inst} Hz={horizon}: {what}", flush=True)
+    at("accumulated")
+    load0 = rng.integers(-1000, 1 << 20, (n_inst, horizon), dtype=np.int32)
+    _, _, flags = check(base, load0, rng.integers(0, 1 << 40, n_inst, dtype=np.int64))
+    assert flags == 0
+    at("large predictions")
+    d = base.pred_tokens.copy()
+    big = rng.random(n) < 0.02
+    d[big] = rng.integers(300, 65_536, int(big.sum()))
+    for bits in (12, 14, 15):
+        d[rng.integers(0, n, 3000)] = rng.choice([(1 << bits) - 1, 1 << bits, (1 << bits) + 1], 3000)
+    d[[0, n - 1]] = 65_535
+    _, _, flags = check(dataclasses.replace(base, pred_tokens=d))
+    assert flags == 0
+    at("faulty records")
+    k = base.instance_id.copy(); a = base.arrival_bucket.copy(); d = base.pred_tokens.copy()
+    k[[300_003, 400_000]] = [-1, n_inst]; d[[500_010, 2_500_011]] = [-1, -70_000]; a[[2_000_020, n - 1]] = [horizon, -5]
+    d[700_000] = 65_535
+    check(dataclasses.replace(base, instance_id=k, pred_tokens=d, arrival_bucket=a))
+    at("a row without a rate")
+    r = base.rate.copy(); r[n_inst // 2] = 0
+    check(dataclasses.replace(base, rate=r))
+    at("both, beside loads beyond 16 bits")
+    r[[1, n_inst - 1]] = 5000
+    for row in (1, n_inst - 1):
+        hot = rng.random(n) < 0.005
+        k[hot], a[hot], d[hot] = row, 11, 4000
+    k[300_003] = -1
+    check(dataclasses.replace(base, instance_id=k, pred_tokens=d, arrival_bucket=a, rate=r))
+
+
 def test_accumulates_into_existing_map():
     inp = wl.make_anticipator_inputs("medium", seed=2, n=5000)
     rng = np.random.default_rng(0)
