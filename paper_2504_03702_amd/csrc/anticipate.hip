@@ -26,8 +26,8 @@
 // and fourth inspection by other groups, no compaction queue.  A workgroup that meets a record
 // outside its window says so in place of its result; that makes a kernel for any order run after it
 // (otherwise its workgroups leave at once) and tells the reduction which partial results to use, so
-// the outcome is the same for any order.  That kernel is the general one or, for long streams of many rows, one with
-// 16-bit counters (anticipate_halves_kernel).
+// the outcome is the same for any order.  That kernel works as above or, for long streams of many rows, with 16-bit
+// counters (halves_body), unless a sample that the windowed kernel takes shows loads too crowded for those.
 #include <string.h>
 
 #include <mutex>
@@ -47,12 +47,18 @@ const int64_t kMinSlice = 16384;         // records per slice below which more s
 const int kTargetWorkgroups = 256;       // one scatter workgroup per compute unit
 
 const int64_t kWindowMinRecords = 262144;   // shorter streams do not pay for the extra launches
-// Looks at records (records x groups) that the halves kernel must save to pay for its prefix sums.  Microseconds a call, general / halves: 256 instances of 600 buckets (4 groups / 2) 0.26 M records 26.2 / 29.6,
-// 1 M 35.5 / 36.1, 2 M 38.1 / 38.3, 5 M 51.4 / 47.4, 15 M 90 / 72, 44 M 215 / 157; 100 of 600 (2 / 1) 1 M 32.3 / 34.0, 2 M
-// 37.9 / 36.4, 44 M 156 / 139; 200 of 1100 (6 / 3) 0.3 M 30.8 / 32.8, 1 M 46.4 / 38.8; 200 of 1200 20 M 272 / 107.
-const int64_t kHalvesMinSaved = 3000000;
+// Looks at records (records x groups) that 16-bit counters must save to pay for the sample and the prefix sums: fewer where
+// the general form's workgroups do not fit the chip at once, or a workgroup of its reduction has many words to add up.
+// Microseconds a call, general / halves: 256 instances of 600 buckets (4 groups / 2) 2 M records 39.9 / 44.5, 5 M 53.3 / 52.6,
+// 10 M 72 / 65, 44 M 222 / 175; 100 of 600 (2 / 1) 5 M 48.4 / 50.2, 10 M 61.4 / 58.9; 256 of 1200 (8 / 4) 2 M 45.5 / 47.3, 3 M
+// 53.1 / 50.8, 25 M 201 / 141.  The others: 200 of 1100 (6 / 3) 1 M 47.5 / 44.4, 25 M 302 / 211; 1000 of 200 2 M 75 / 59; 66 of
+// 1023 (2 / 1) 3 M 61 / 47; 30 of 4096 2 M 66 / 54.
+const int64_t kHalvesMinSaved = 8000000, kHalvesMinSavedOthers = 3000000, kHalvesReduceWords = 100000;
 const int kWindowMaxHorizon = 4096;         // the reduction keeps one 64-bit row of the map in LDS
-const int kGaveUp = -2;                     // a windowed workgroup's origin when a record fell outside its window
+// What a windowed workgroup leaves: the first bucket of its window, and
+const int kGaveUp = 1 << 16;                // a record fell outside it
+const int kCrowded = 1 << 17;               // the rows it weighed are too crowded for 16-bit counters
+const int kNothing = 1 << 18;               // no records in its slice
 
 struct AntPlan {
     int rows_per_group, groups, slices;
@@ -63,7 +69,7 @@ struct AntPlan {
     int64_t w_slice_len;
     size_t w_lds_bytes, w_partial_bytes, w_ovf_bytes, w_origin_bytes, w_partial_at, w_ovf_at, w_origin_at;
     // halves kernel (records in any order, twice as many rows a workgroup); h_slices == 0: not used
-    int h_rows, h_groups, h_slices, h_stride, h_row_bits, h_bucket_bits;
+    int h_rows, h_groups, h_slices, h_stride, h_row_bits, h_bucket_bits, h_weighed;
     int64_t h_slice_len;
     size_t h_lds_bytes, h_high_at, h_ovf_at, h_flag_at;
     bool ok;
@@ -135,7 +141,11 @@ void plan_halves(AntPlan& p, int64_t n, int n_inst, int horizon) {
     int64_t fit = (kLdsBytes - kQueueBytes - 64) / per_pair * 2;
     if (fit > 256) fit = 256;                                     // (measured up to here)
     p.h_groups = fit > 0 ? (int)((n_inst + fit - 1) / fit) : p.groups;
-    if (p.h_groups >= p.groups || n * (p.groups - p.h_groups) < kHalvesMinSaved) return;
+    const bool others = 8 * p.groups * ((p.slices + 7) / 8) > kTargetWorkgroups || (int64_t)p.slices * horizon > kHalvesReduceWords;
+    if (p.h_groups >= p.groups || n * (p.groups - p.h_groups) < (others ? kHalvesMinSavedOthers : kHalvesMinSaved)) return;
+    // rows that a windowed workgroup weighs beforehand, a wavefront each
+    p.h_weighed = (n_inst + p.w_slices - 1) / p.w_slices;
+    if (p.h_weighed > kWaves || 64 + (int64_t)n_inst * 16 + 4 * (int64_t)p.h_weighed * horizon > (int64_t)p.w_lds_bytes) return;
     p.h_rows = ((n_inst + p.h_groups - 1) / p.h_groups + 1) / 2 * 2;
     // fields of a queued record; what LDS holds keeps the two below 19 bits together
     p.h_row_bits = bits_for(p.h_rows);
@@ -172,28 +182,32 @@ __device__ __forceinline__ unsigned div_exact(unsigned num, unsigned den) {
     return (unsigned)(((float)num * __builtin_amdgcn_rcpf((float)den)) * (1.0f + 0x1p-20f));
 }
 
-// True if some workgroup of the windowed kernel gave up.  Every wavefront looks through all the origins
-// itself, so the answer is the same across the workgroup without a barrier or LDS.
-__device__ __forceinline__ bool window_gave_up(const int32_t* __restrict__ worigin, int w_slices) {
-    bool mine = false;
-    for (int s = threadIdx.x & 63; s < w_slices; s += 64) mine |= worigin[s] == kGaveUp;
-    return __any(mine) != 0;
+// What the workgroups of the windowed kernel say together.  Every wavefront looks through all of it itself, so the answer
+// is the same across the workgroup without a barrier or LDS.
+__device__ __forceinline__ int origin_bits(const int32_t* __restrict__ worigin, int w_slices) {
+    int mine = 0;
+    for (int s = threadIdx.x & 63; s < w_slices; s += 64) mine |= worigin[s];
+    return (__any(mine & kGaveUp) ? kGaveUp : 0) | (__any(mine & kCrowded) ? kCrowded : 0);
 }
 
-__global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(
-    const int32_t* __restrict__ pred_tokens, const int32_t* __restrict__ instance_id,
-    const int32_t* __restrict__ arrival_bucket, const int32_t* __restrict__ rate, int64_t n, int n_inst,
-    int horizon, int rows_per_group, int groups, int slices, int64_t slice_len,
-    int32_t* __restrict__ partial, int64_t* __restrict__ partial_ovf, const int32_t* __restrict__ worigin,
-    int w_slices, ps_status* st) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    // launched behind the windowed kernel: needed only if that one gave up somewhere
-    if (worigin && !window_gave_up(worigin, w_slices)) return;
+struct GeneralArgs {
+    const int32_t *pred_tokens, *instance_id, *arrival_bucket, *rate;
+    int64_t n, slice_len;
+    int n_inst, horizon, rows_per_group, groups, slices;
+    int32_t* partial;
+    int64_t* partial_ovf;
+};
+
+__device__ __forceinline__ void general_body(const GeneralArgs& p, unsigned char* lds_raw, ps_status* st) {
+    const int32_t *__restrict__ pred_tokens = p.pred_tokens, *__restrict__ instance_id = p.instance_id;
+    const int32_t *__restrict__ arrival_bucket = p.arrival_bucket, *__restrict__ rate = p.rate;
+    const int64_t n = p.n, slice_len = p.slice_len;
+    const int n_inst = p.n_inst, horizon = p.horizon, rows_per_group = p.rows_per_group, groups = p.groups;
     // blocks are dealt to the 8 XCDs round-robin: keep the groups of one slice on one XCD
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int g = j % groups;
     const int slice = (j / groups) * 8 + xcd;
-    if (slice >= slices) return;
+    if (slice >= p.slices) return;
     const int k0 = g * rows_per_group;
     const int rows = min(rows_per_group, n_inst - k0);
     if (rows <= 0) return;
@@ -357,9 +371,9 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(
     for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
     if (lane == 0 && mass >= (1ull << 31) / kWaves) report_fault(st, PS_ST_RANGE, begin);
     __syncthreads();
-    int32_t* out = partial + ((int64_t)slice * n_inst + k0) * horizon;
+    int32_t* out = p.partial + ((int64_t)slice * n_inst + k0) * horizon;
     for (int i = tid; i < rows * horizon; i += kScatterThreads) out[i] = s_diff[i];
-    for (int i = tid; i < rows; i += kScatterThreads) partial_ovf[(int64_t)slice * n_inst + k0 + i] = (int64_t)s_ovf[i];
+    for (int i = tid; i < rows; i += kScatterThreads) p.partial_ovf[(int64_t)slice * n_inst + k0 + i] = (int64_t)s_ovf[i];
 }
 
 // Scatter for long streams in any order: 16-bit counters, two rows to a word, so that a workgroup holds twice the rows
@@ -372,13 +386,20 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(
 // that is not makes the halves add up to less than the true loads (65535 less for every wrap of the low half, which
 // carries into the high one, 65536 for the high half).  Compared over the whole workgroup, what the halves add up to is
 // therefore equal to the tokens put in exactly if no load has wrapped.  Where one has, the workgroup goes through its slice
-// twice more, half of its rows at a time with 32-bit counters, and leaves the loads' upper halves in a second plane.
+// a second time with the rows of a word exchanged: word' = high + 2^16 low.  The low halves of the two are the loads'
+// lower 16 bits; word's upper half less the lower 16 bits of the high row is what the low row carried into it, its upper 16
+// bits, and the other way round.  The upper bits go to a second plane.
 // Results are loads, not differences: the reduction adds them up and needs no scan.
 //
 // 44.1 M records over 256 instances of 600 buckets: 200 us in the general kernel, 146 here, of which about 105 are vector
 // instructions (19 a look, 48 a record); a queue entry names row, bucket and tokens in fields, so neither side multiplies
 // or divides by the row length.  The fields are as wide as the call's rows and buckets ask for, which leaves 14 bits and
 // more to the tokens (12 as a fixed width: with 5 % of the predictions above 4096 284 us, the general kernel 220).
+//
+// A second pass costs what the first does.  Crowds that a sample shows are left to the general form (anticipate_window_kernel
+// takes the sample in 2 us); 5 % of those records in one cell 229 us so, 467 with two more passes in place of a sample,
+// general 221; instances drawn by Zipf's law and a rush hour 296, 501 and 287.  What it does not show: 2756 records for one
+// cell that follow each other in the stream 290 us, general 217.
 struct HalvesArgs {
     const int32_t *pred, *inst, *arrival, *rate;
     int64_t n, slice_len;
@@ -389,9 +410,15 @@ struct HalvesArgs {
     int32_t* wide;                       // [slice][group]: the upper halves are there too
 };
 
-template <bool WIDE>
-__device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int rows, unsigned char* lds_raw, bool report,
-                            unsigned long long* s_sum, ps_status* st) {
+// Difference of both halves, each modulo 2^16.
+__device__ __forceinline__ uint32_t sub_halves(uint32_t a, uint32_t b) {
+    return ((a - b) & 0xffffu) | ((a & 0xffff0000u) - (b & 0xffff0000u));
+}
+
+// One pass over a slice for the group's rows.  SWAP: the second one, with the rows of a word exchanged.
+template <bool SWAP>
+__device__ __forceinline__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int rows, unsigned char* lds_raw,
+                                            unsigned long long* s_sum, ps_status* st) {
     const int horizon = p.horizon, R = p.rows / 2;
     uint32_t* s_queue = (uint32_t*)lds_raw;                                    // [kWaves][kQueue]
     int* s_flag = (int*)(lds_raw + kQueueBytes);                               // some row has rate < 1
@@ -416,12 +443,12 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
     uint32_t* q = s_queue + wave * kQueue;
     unsigned head = 0, tail = 0;                                // wave-uniform ring indices
     unsigned long long inside_sum = 0;                          // tokens this lane has put into buckets
-    unsigned long long mass = 0;                                // WIDE: bound on what any counter can have reached
+    unsigned long long mass = 0;                                // SWAP: bound on what any counter can have reached
 
     // one record of row `row`: D1 = its tokens less one
     auto apply = [&](unsigned row, unsigned a, unsigned D1) __attribute__((always_inline)) {
-        const bool upper = !WIDE && row >= (unsigned)R;
-        const unsigned D = D1 + 1u, w = WIDE ? row : min(row, row - (unsigned)R), sh = upper ? 16u : 0u;
+        const bool upper = row >= (unsigned)R;
+        const unsigned D = D1 + 1u, w = min(row, row - (unsigned)R), sh = upper != SWAP ? 16u : 0u;
         const unsigned dur = div_by_row(D1, s_rcp[row]) + 1u;                   // ceil(D / rate)
         const unsigned qq = div_exact(D, dur);
         const unsigned rem = D - __umul24(qq, dur);
@@ -431,7 +458,7 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
         if (rem != 0 && rem < room) atomicAdd(cell + rem, (int)(0xffffffffu << sh));
         if (dur < room) atomicAdd(cell + dur, (int)(0u - (qq << sh)));
         inside_sum += D;
-        if (WIDE) mass += qq + 1;
+        if (SWAP) mass += qq + 1;
         if (dur > room) {
             const unsigned long long over = (unsigned long long)D - ((unsigned long long)room * qq + min(room, rem));
             atomicAdd(&s_ovf[row], over);
@@ -479,7 +506,7 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
                 bool ok = (unsigned)b.d[c] <= (unsigned)PS_MAX_PRED && (unsigned)b.a[c] < (unsigned)horizon;
                 if (mine && ok && s_rcp[kk] == 0.f) ok = false;
                 // a record outside every group is reported by group 0, others by their own group
-                if (report && in && ((!k_ok && g == 0) || (mine && !ok))) report_fault(st, PS_ST_BAD_RECORD, idx + c);
+                if (in && ((!k_ok && g == 0) || (mine && !ok))) report_fault(st, PS_ST_BAD_RECORD, idx + c);
                 if (!(in && mine && ok)) b.d[c] = 0;
             }
         }
@@ -543,7 +570,7 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
         process(b, full_end, true);
     }
     if (tail != head) consume(tail - head);
-    if (WIDE) {
+    if (SWAP) {
         for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
         if (lane == 0 && mass >= (1ull << 31) / kWaves) report_fault(st, PS_ST_RANGE, begin);
     }
@@ -551,9 +578,10 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
 
     // prefix sums, a wavefront per row of words, two words a lane; the loads of both rows go out as they are
     unsigned long long halves_sum = 0;
-    for (int w = wave; w < (WIDE ? rows : min(R, rows)); w += kWaves) {
-        const int64_t at = ((int64_t)(k0 + w) * p.slices + slice) * p.stride;
-        const bool two = !WIDE && w + R < rows;
+    for (int w = wave; w < min(R, rows); w += kWaves) {
+        const int64_t at = ((int64_t)(k0 + w) * p.slices + slice) * p.stride, at2 = at + (int64_t)R * p.slices * p.stride;
+        const bool two = w + R < rows;
+        if (SWAP && !two) continue;                             // (alone in its words: nothing is missing)
         unsigned carry = 0;
         for (int b0 = 0; b0 < horizon; b0 += 128) {
             const int b = b0 + 2 * lane;
@@ -566,12 +594,19 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
                 if (lane >= o) incl += t;
             }
             const unsigned s1 = carry + incl, s0 = s1 - y;     // loads of buckets b and b + 1
+            const unsigned lo = (s0 & 0xffffu) | (s1 << 16), up = (s0 >> 16) | (s1 & 0xffff0000u);
             if (b < p.stride) {                                 // (stride is even; cells beyond the horizon are not read)
-                *(uint32_t*)(p.low + at + b) = (s0 & 0xffffu) | (s1 << 16);
-                if (WIDE) *(uint32_t*)(p.high + at + b) = (s0 >> 16) | (s1 & 0xffff0000u);
-                else if (two) *(uint32_t*)(p.low + at + (int64_t)R * p.slices * p.stride + b) = (s0 >> 16) | (s1 & 0xffff0000u);
+                if (SWAP) {
+                    const unsigned lo1 = *(const uint32_t*)(p.low + at + b), up1 = *(const uint32_t*)(p.low + at2 + b);
+                    *(uint32_t*)(p.high + at + b) = sub_halves(up1, lo);
+                    *(uint32_t*)(p.low + at2 + b) = lo;
+                    *(uint32_t*)(p.high + at2 + b) = sub_halves(up, lo1);
+                } else {
+                    *(uint32_t*)(p.low + at + b) = lo;
+                    *(uint32_t*)((two ? p.low + at2 : p.high + at) + b) = up;
+                }
             }
-            if (!WIDE) {
+            if (!SWAP) {
                 if (b < horizon) halves_sum += (s0 & 0xffffu) + (s0 >> 16);
                 if (b + 1 < horizon) halves_sum += (s1 & 0xffffu) + (s1 >> 16);
             }
@@ -579,18 +614,15 @@ __device__ void halves_pass(const HalvesArgs& p, int slice, int g, int k0, int r
         }
     }
     for (int i = tid; i < rows; i += kScatterThreads) p.ovf[(int64_t)slice * p.n_inst + k0 + i] = (int64_t)s_ovf[i];
-    if (!WIDE) {
+    if (!SWAP) {
         unsigned long long diff = inside_sum - halves_sum;
         for (int o = 32; o > 0; o >>= 1) diff += __shfl_xor(diff, o, 64);
         if (lane == 0) atomicAdd(s_sum, diff);
     }
 }
 
-__global__ __launch_bounds__(kScatterThreads) void anticipate_halves_kernel(HalvesArgs p, const int32_t* __restrict__ worigin,
-                                                                            int w_slices, ps_status* st) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
+__device__ __forceinline__ void halves_body(const HalvesArgs& p, unsigned char* lds_raw, ps_status* st) {
     unsigned long long* s_sum = (unsigned long long*)(lds_raw + kQueueBytes + 8);   // tokens put in less what the halves show
-    if (!window_gave_up(worigin, w_slices)) return;            // launched behind the windowed kernel
     // blocks are dealt to the 8 XCDs round-robin: keep the groups of one slice on one XCD
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int g = j % p.groups, slice = (j / p.groups) * 8 + xcd;
@@ -598,25 +630,33 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_halves_kernel(Halv
     const int k0 = g * p.rows, rows = min(p.rows, p.n_inst - k0);
     if (rows <= 0) return;
     if (threadIdx.x == 0) *s_sum = 0;
-    halves_pass<false>(p, slice, g, k0, rows, lds_raw, true, s_sum, st);
+    halves_pass<false>(p, slice, g, k0, rows, lds_raw, s_sum, st);
     __syncthreads();
     const bool wrapped = *s_sum != 0;                          // uniform
     if (threadIdx.x == 0) p.wide[slice * p.groups + g] = wrapped;
-    if (!wrapped) return;
-    const int R = p.rows / 2;
-#pragma unroll 1
-    for (int r0 = 0; r0 < rows; r0 += R) halves_pass<true>(p, slice, g, k0 + r0, min(R, rows - r0), lds_raw, false, nullptr, st);
+    if (wrapped) halves_pass<true>(p, slice, g, k0, rows, lds_raw, s_sum, st);
+}
+
+// The scatter for any order, launched behind the windowed one where that is tried: needed only if it gave up somewhere.
+__global__ __launch_bounds__(kScatterThreads) void anticipate_scatter_kernel(GeneralArgs p, HalvesArgs hv,
+                                                                             const int32_t* __restrict__ worigin,
+                                                                             int w_slices, ps_status* st) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int bits = worigin ? origin_bits(worigin, w_slices) : kGaveUp;
+    if (!(bits & kGaveUp)) return;
+    if (hv.slices > 0 && !(bits & kCrowded)) halves_body(hv, lds_raw, st);
+    else general_body(p, lds_raw, st);
 }
 
 // Windowed scatter for records in arrival order: workgroup = slice of the records; LDS holds, for
 // every instance, the difference counters of the buckets [a0, a0 + w_buckets), a0 = the arrival bucket
 // of the slice's first record.  Each lane takes its own records straight through the two divisions and
 // the three LDS adds.  A record that reaches outside the window (or before it) makes the workgroup
-// leave kGaveUp in place of its origin; the general kernel then redoes the whole call.
+// leave kGaveUp in place of its origin; the scatter for any order then redoes the whole call.
 __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
     const int32_t* __restrict__ pred_tokens, const int32_t* __restrict__ instance_id,
     const int32_t* __restrict__ arrival_bucket, const int32_t* __restrict__ rate, int64_t n, int n_inst,
-    int horizon, int w_buckets, int64_t slice_len, int32_t* __restrict__ wpartial,
+    int horizon, int w_buckets, int64_t slice_len, int weighed, int64_t h_slice_len, int32_t* __restrict__ wpartial,
     int64_t* __restrict__ wovf, int32_t* __restrict__ worigin, ps_status* st) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     int* s_flag = (int*)lds_raw;                                              // [0] a row has rate < 1, [1] gave up
@@ -627,35 +667,95 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
     const int slice = blockIdx.x;
     const int64_t begin = (int64_t)slice * slice_len;
     const int64_t end = min(begin + slice_len, n);
-    if (begin >= end) {
-        if (tid == 0) worigin[slice] = -1;                    // nothing to add from this slice
-        return;
-    }
     // window origin: the slice's first arrival bucket; a faulty (negative) one must not shift the window the
     // slice's valid records are placed in, so the origin is never below bucket 0 (a first bucket at or beyond
-    // the horizon leaves every valid record before the window: the workgroup gives up and the general kernel runs)
-    const int a0 = max(arrival_bucket[begin], 0);
-    if (tid < 2) s_flag[tid] = 0;
+    // the horizon leaves every valid record before the window: the workgroup gives up and the scatter for any order runs)
+    const int a0 = begin < end ? max(arrival_bucket[begin], 0) : 0;
+    const int64_t probe = begin + (int64_t)tid * 4;
+    int4 probed = make_int4(-1, -1, -1, -1);
+    if (probe + 4 <= end) probed = *(const int4*)(arrival_bucket + probe);
+    // sample of the whole stream, looked at if this slice is in no order: 16 records from each of 256 places (four from each
+    // of 1024: 4 us more a call), for `weighed` rows a workgroup
+    const int k0 = slice * weighed, rows = max(min(weighed, n_inst - k0), 0);
+    int4 kv = {}, dv = {}, av = {};
+    int rates = 0;                                             // of row `lane`
+    if (rows > 0) {
+        const int64_t at = (int64_t)(tid >> 2) * (n / 4096 * 16) + 4 * (tid & 3);
+        kv = *(const int4*)(instance_id + at);
+        dv = *(const int4*)(pred_tokens + at);
+        av = *(const int4*)(arrival_bucket + at);
+        rates = rate[min(k0 + (lane & (kWaves - 1)), n_inst - 1)];
+        for (int i = tid; i < rows * horizon; i += kScatterThreads) s_diff[i] = 0;
+    }
+    unsigned* s_top = (unsigned*)(lds_raw + 8);               // of the sample: largest load; tokens; tokens times what a
+    unsigned long long *s_tokens = (unsigned long long*)(lds_raw + 16), *s_weighted = s_tokens + 1;   // bucket gets of them
+    if (tid < 2) { s_flag[tid] = 0; *s_top = 0; s_tokens[tid] = 0; }
+    if (begin >= end) {
+        if (tid == 0) worigin[slice] = kNothing;
+        return;
+    }
     __syncthreads();
     {
         // A look at the slice's first records before anything is set up: a stream in no particular order shows a
         // valid arrival bucket outside the window at once, and the workgroup leaves without clearing its counters.
         // (Invalid buckets are not counted: such records are skipped, not folded.)
-        const int64_t probe = begin + (int64_t)tid * 4;
+        const int aa[4] = {probed.x, probed.y, probed.z, probed.w};
         bool far = false;
-        if (probe + 4 <= end) {
-            const int4 av = *(const int4*)(arrival_bucket + probe);
-            const int aa[4] = {av.x, av.y, av.z, av.w};
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                far |= (unsigned)aa[c] < (unsigned)horizon && (unsigned)(aa[c] - a0) >= (unsigned)w_buckets;
-        }
+        for (int c = 0; c < 4; ++c)
+            far |= (unsigned)aa[c] < (unsigned)horizon && (unsigned)(aa[c] - a0) >= (unsigned)w_buckets;
         if (__any(far) && lane == 0) s_flag[1] = 1;
         __syncthreads();
-        if (s_flag[1]) {                                      // uniform
-            if (tid == 0) worigin[slice] = kGaveUp;
-            return;
+    }
+    if (s_flag[1]) {                                          // uniform
+        // Are its rows too crowded for 16-bit counters?  The sample's largest load, scaled up to a slice of halves_body.  A
+        // load m of records that give a bucket q each varies by sqrt(q m) from sample to sample (q: the mean over
+        // tokens): two of those are taken off, so that a few large records that met by chance are no crowd.
+        const int kk[4] = {kv.x, kv.y, kv.z, kv.w}, dd[4] = {dv.x, dv.y, dv.z, dv.w}, aa[4] = {av.x, av.y, av.z, av.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int row = kk[c] - k0, D = dd[c], r = min(__shfl(rates, row & (kWaves - 1), 64), PS_MAX_PRED);
+            if ((unsigned)kk[c] >= (unsigned)n_inst || (unsigned)row >= (unsigned)rows) continue;
+            if (D < 1 || D > PS_MAX_PRED || (unsigned)aa[c] >= (unsigned)horizon || r < 1) continue;
+            const int dur = (int)div_exact((unsigned)(D + r - 1), (unsigned)r), q = (int)div_exact((unsigned)D, (unsigned)dur);
+            atomicAdd(s_diff + row * horizon + aa[c], q);
+            if (dur < horizon - aa[c]) atomicAdd(s_diff + row * horizon + aa[c] + dur, -q);
+            atomicAdd(s_tokens, (unsigned long long)D);
+            atomicAdd(s_weighted, (unsigned long long)D * q);
         }
+        __syncthreads();
+        if (wave < rows) {                                     // a wavefront a row, sixteen neighbouring buckets a lane
+            int carry = 0, top = 0;
+            for (int b0 = 0; b0 < horizon; b0 += 1024) {
+                const int b = b0 + 16 * lane;
+                int v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = b + i < horizon ? s_diff[wave * horizon + b + i] : 0;
+                int most = v[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) {
+                    v[i] += v[i - 1];
+                    most = max(most, v[i]);
+                }
+                int run = v[15];
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int t = __shfl_up(run, o, 64);
+                    if (lane >= o) run += t;
+                }
+                top = max(top, carry + run - v[15] + most);
+                carry += __shfl(run, 63, 64);
+            }
+            for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+            if (lane == 0) atomicMax(s_top, (unsigned)top);
+        }
+        if (rows > 1) __syncthreads();                         // (one row: its wavefront is the one that goes on)
+        if (tid == 0) {
+            const float m = (float)*s_top, q = (float)*s_weighted / fmaxf((float)*s_tokens, 1.0f);
+            const bool crowded = (m - 2.0f * sqrtf(q * m)) * (float)h_slice_len > 65535.0f * 4096.0f;
+            worigin[slice] = kGaveUp | (crowded ? kCrowded : 0);
+        }
+        return;
     }
     for (int i = tid; i < n_inst * w_buckets; i += kScatterThreads) s_diff[i] = 0;
     for (int i = tid; i < n_inst; i += kScatterThreads) {
@@ -777,7 +877,7 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
     for (int o = 32; o > 0; o >>= 1) mass += __shfl_xor(mass, o, 64);
     if (lane == 0 && mass >= (1ull << 31) / kWaves) report_fault(st, PS_ST_RANGE, begin);
     __syncthreads();
-    if (s_flag[1]) {                                          // uniform: the general kernel takes over
+    if (s_flag[1]) {                                          // uniform: the scatter for any order takes over
         if (tid == 0) worigin[slice] = kGaveUp;
         return;
     }
@@ -816,44 +916,46 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
     __shared__ unsigned long long s_row[kWindowMaxHorizon];  // this instance's difference row, 64-bit
     const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // which first kernel produced the partial results: the windowed one unless it gave up
-    const bool windowed = worigin && !window_gave_up(worigin, w_slices);
+    const int bits = worigin ? origin_bits(worigin, w_slices) : kGaveUp;
+    const bool windowed = !(bits & kGaveUp);
     const bool in_lds = horizon <= kWindowMaxHorizon;         // (the windowed kernel is only used then)
     if (tid == 0) s_over = 0;                                 // (a barrier follows before its first use)
-    if (worigin && !windowed && hv.slices > 0) {
+    if (hv.slices > 0 && bits == kGaveUp) {
         // the halves kernel's loads: a thread adds up eight neighbouring buckets of every T-th slice
         for (int i = tid; i < horizon; i += kReduceThreads) s_row[i] = 0;
         const int wg = k / hv.rows;
         bool some = false;
-        for (int i = tid; i < hv.slices; i += kReduceThreads) some |= hv.wide[i * hv.groups + wg] != 0;
+        for (int i = tid; i < hv.slices; i += kReduceThreads) {
+            s_origin[i] = hv.wide[i * hv.groups + wg];         // (this slice's upper halves are there)
+            some |= s_origin[i] != 0;
+        }
         const bool wide = __syncthreads_or(some) != 0;        // rare
         const int groups = hv.stride >> 3, T = kReduceThreads / groups;       // (at most 512 groups)
         const int sl0 = tid / groups, g8 = tid - sl0 * groups;
         const int64_t step = hv.stride, at0 = (int64_t)k * hv.slices * hv.stride + 8 * g8;
-        if (sl0 < T) {
+        auto add_plane = [&](const uint16_t* plane, bool upper) {
             unsigned sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};       // at most 256 slices of 16 bits
             constexpr int NB = 10;
             for (int s0 = sl0; s0 < hv.slices; s0 += T * NB) {
                 uint4 v[NB];
 #pragma unroll
-                for (int u = 0; u < NB; ++u) v[u] = *(const uint4*)(hv.low + min(s0 + T * u, hv.slices - 1) * step + at0);
+                for (int u = 0; u < NB; ++u) v[u] = *(const uint4*)(plane + min(s0 + T * u, hv.slices - 1) * step + at0);
 #pragma unroll
                 for (int u = 0; u < NB; ++u) {
                     const int sl = s0 + T * u;
-                    if (sl >= hv.slices) continue;
+                    if (sl >= hv.slices || (upper && s_origin[sl] == 0)) continue;
                     const unsigned x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
                     for (int c = 0; c < 4; ++c) { sum[2 * c] += x[c] & 0xffffu; sum[2 * c + 1] += x[c] >> 16; }
-                    if (wide && hv.wide[sl * hv.groups + wg]) {
-                        for (int c = 0; c < 8 && 8 * g8 + c < horizon; ++c) {
-                            const unsigned long long hi = hv.high[sl * step + at0 + c];
-                            if (hi) atomicAdd(&s_row[8 * g8 + c], hi << 16);
-                        }
-                    }
                 }
             }
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                if (8 * g8 + c < horizon && sum[c]) atomicAdd(&s_row[8 * g8 + c], (unsigned long long)sum[c]);
+                if (8 * g8 + c < horizon && sum[c]) atomicAdd(&s_row[8 * g8 + c], (unsigned long long)sum[c] << (upper ? 16 : 0));
+        };
+        if (sl0 < T) {
+            add_plane(hv.low, false);
+            if (wide) add_plane(hv.high, true);
         }
         __syncthreads();
         for (int b = tid; b < horizon; b += kReduceThreads) {
@@ -874,7 +976,7 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
     }
     if (in_lds) {
         const int n_rows = windowed ? w_slices : slices, row_len = windowed ? w_buckets : horizon;
-        for (int s = tid; s < n_rows; s += kReduceThreads) s_origin[s] = windowed ? worigin[s] : 0;
+        for (int s = tid; s < n_rows; s += kReduceThreads) s_origin[s] = !windowed ? 0 : worigin[s] & kNothing ? -1 : worigin[s] & 0xffff;
         for (int i = tid; i < horizon; i += kReduceThreads) s_row[i] = 0;
         __syncthreads();
         // general partials are [slice][instance][bucket], windowed ones [instance][slice][bucket of the window]
@@ -995,7 +1097,7 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
         for (int s2 = tid; s2 < n_rows; s2 += kReduceThreads) {
             long long o = 0;
             if (windowed) {
-                if (worigin[s2] >= 0) o = wovf[(int64_t)s2 * n_inst + k];
+                if (!(worigin[s2] & kNothing)) o = wovf[(int64_t)s2 * n_inst + k];
             } else {
                 o = partial_ovf[(int64_t)s2 * n_inst + k];
             }
@@ -1141,13 +1243,12 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
     if (!lds_attr_set) {
         if (hipFuncSetAttribute((const void*)anticipate_scatter_kernel,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)anticipate_halves_kernel,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void*)anticipate_window_kernel,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) != hipSuccess)
             return PS_EHIP;
         lds_attr_set = true;
     }
+    plan_halves(p, n_req, n_inst, horizon);
     uint8_t* wsb = (uint8_t*)workspace;
     int32_t* partial = (int32_t*)wsb;
     int64_t* partial_ovf = (int64_t*)(wsb + p.partial_bytes);
@@ -1160,22 +1261,19 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
         worigin = (int32_t*)(wsb + p.w_origin_at);
         hipLaunchKernelGGL(anticipate_window_kernel, dim3((unsigned)p.w_slices), dim3(kScatterThreads), p.w_lds_bytes, s,
                            pred_tokens, instance_id, arrival_bucket, rate, n_req, n_inst, horizon, p.w_buckets,
-                           p.w_slice_len, wpartial, wovf, worigin, status);
+                           p.w_slice_len, p.h_slices > 0 ? p.h_weighed : 0, p.h_slice_len, wpartial, wovf, worigin, status);
     }
-    plan_halves(p, n_req, n_inst, horizon);
     HalvesArgs hv = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.h_slice_len, n_inst, horizon, p.h_rows, p.h_groups,
                      p.h_slices, p.h_stride, 32 - p.h_row_bits, 32 - p.h_row_bits - p.h_bucket_bits, (uint16_t*)wsb, (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at),
                      (int32_t*)(wsb + p.h_flag_at)};
-    if (p.h_slices > 0) {
-        const unsigned blocks = 8u * (unsigned)p.h_groups * (unsigned)((p.h_slices + 7) / 8);
-        hipLaunchKernelGGL(anticipate_halves_kernel, dim3(blocks), dim3(kScatterThreads), p.h_lds_bytes, s, hv, worigin,
-                           p.w_slices, status);
-    } else {
-        const unsigned blocks = 8u * (unsigned)p.groups * (unsigned)((p.slices + 7) / 8);
-        hipLaunchKernelGGL(anticipate_scatter_kernel, dim3(blocks), dim3(kScatterThreads), p.lds_bytes, s,
-                           pred_tokens, instance_id, arrival_bucket, rate, n_req, n_inst, horizon,
-                           p.rows_per_group, p.groups, p.slices, p.slice_len, partial, partial_ovf, worigin, p.w_slices, status);
-    }
+    const GeneralArgs ga = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.slice_len, n_inst, horizon,
+                            p.rows_per_group, p.groups, p.slices, partial, partial_ovf};
+    // (which of the two runs is known on the device)
+    const unsigned blocks = 8u * (unsigned)p.groups * (unsigned)((p.slices + 7) / 8);
+    const unsigned h_blocks = 8u * (unsigned)p.h_groups * (unsigned)((p.h_slices + 7) / 8);
+    const bool halves = p.h_slices > 0;
+    hipLaunchKernelGGL(anticipate_scatter_kernel, dim3(halves && h_blocks > blocks ? h_blocks : blocks), dim3(kScatterThreads),
+                       halves && p.h_lds_bytes > p.lds_bytes ? p.h_lds_bytes : p.lds_bytes, s, ga, hv, worigin, p.w_slices, status);
     hipLaunchKernelGGL(anticipate_reduce_kernel, dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, partial, partial_ovf, p.slices, n_inst, horizon,
                        wpartial, wovf, worigin, p.w_slices, p.w_buckets, hv, load, overflow, status);
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;

@@ -148,12 +148,17 @@ def test_any_order_loads_beyond_sixteen_bits(n_inst, horizon, hot):
         check(wl.AnticipatorInputs(d2, k2, a, rate2, n_inst, horizon))
 
 
+def between_places(pick):
+    """Of the picked records those that the sample of a long stream, 16 records from each of 256 places, does not see."""
+    return pick & (np.arange(pick.size) % (pick.size // 4096 * 16) >= 16)
+
+
 @pytest.mark.parametrize("n_inst,horizon", [(256, 600), (66, 1023), (130, 597)])
 def test_any_order_with_exceptions_on_sixteen_bit_counters(n_inst, horizon):
     """What test_long_streams_in_any_order_with_exceptions does to the general kernel, on streams long enough for the
     16-bit counters: accumulated, predictions up to the largest in most blocks of 256 records and around the most a
     queued record's field holds (14 bits where rows and buckets take 18 of 32, 15 where they take 17), faulty records
-    and a row without a usable rate, and the latter two where a busy row makes both halves go through 32-bit counters."""
+    and a row without a usable rate, and the latter two where busy rows need the second pass."""
     rng = np.random.default_rng(31 + n_inst)
     n = 3_000_001
     base = wl.AnticipatorInputs(rng.integers(0, 300, n, dtype=np.int32), rng.integers(0, n_inst, n, dtype=np.int32),
@@ -184,10 +189,30 @@ def test_any_order_with_exceptions_on_sixteen_bit_counters(n_inst, horizon):
     at("both, beside loads beyond 16 bits")
     r[[1, n_inst - 1]] = 5000
     for row in (1, n_inst - 1):
-        hot = rng.random(n) < 0.005
+        hot = between_places(rng.random(n) < 0.005)
         k[hot], a[hot], d[hot] = row, 11, 4000
     k[300_003] = -1
     check(dataclasses.replace(base, instance_id=k, pred_tokens=d, arrival_bucket=a, rate=r))
+
+
+@pytest.mark.parametrize("n_inst,horizon,hot", [(256, 600, [7, 135]), (256, 600, [71]), (256, 601, [0, 64, 255]), (130, 597, [65, 129]),
+                                                (200, 1100, [33, 67]), (66, 1023, [65]), (67, 1021, [0, 32, 33, 66])])
+@pytest.mark.parametrize("share", [0.005, 0.1])
+def test_any_order_crowds_that_the_sample_misses(n_inst, horizon, hot, share):
+    """Loads that leave 16 bits on streams whose sampled records do not show it: the second pass over a slice brings the
+    upper bits, of one row of a word, of both (65536 times and more, up to 28 bits), of a row without a partner."""
+    rng = np.random.default_rng(n_inst * 7 + horizon)
+    n = 3_000_001
+    print(f"anticipator missed crowds K={n_inst} Hz={horizon} hot={hot} share={share}", flush=True)
+    k = rng.integers(0, n_inst, n, dtype=np.int32)
+    d = rng.integers(0, 50, n, dtype=np.int32)
+    a = rng.integers(0, horizon, n, dtype=np.int32)
+    rate = rng.integers(20, 200, n_inst, dtype=np.int32)
+    for i, h in enumerate(hot):
+        pick = between_places(rng.random(n) < share)
+        k[pick], d[pick], a[pick] = h, 60_000 if i == 0 else 4000, [horizon - 1, 5, 300, 5][i]
+        rate[h] = 65_535 if i == 0 else 5000
+    check(wl.AnticipatorInputs(d, k, a, rate, n_inst, horizon))
 
 
 def test_accumulates_into_existing_map():
