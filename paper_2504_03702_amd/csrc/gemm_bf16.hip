@@ -92,6 +92,9 @@ struct Region {
 //    row by row 935).
 // The tiles of the last round are dealt to the XCDs evenly, so every workgroup gets the same number of tiles to one (P = 3
 // in whole bands per XCD, as it used to be: the first feed-forward map of 100 k rows of hidden 768 549 us, 523 so).
+// Without BANDS, row by row and a range to each XCD: small tiles, mostly one to a workgroup, where a launch of 27 us shows the
+// arithmetic (18 to 26 requests, maps of hidden 768 27.4 us with bands, 26.6 so; keys and values 17.6, 17.1).
+template <bool BANDS>
 struct Walk {
     int n_tiles, m_tiles, slots, xcd, slot, full, rest, n_my;
     __device__ __forceinline__ Walk(int m, int n) : n_tiles(n), m_tiles(m) {
@@ -105,20 +108,25 @@ struct Walk {
     // row and column of this workgroup's tile `round`
     __device__ __forceinline__ void tile(int round, int& tm, int& tn) const {
         int run = xcd * full + round;
-        if ((n_tiles & 3) == 0) {
+        if (BANDS && (n_tiles & 3) == 0) {
             const int P = n_tiles >> 2, done = 8 % P == 0 ? 0 : full / P * P;
             run = round < done ? (round / P * 8 + xcd) * P + round % P : round * 8 + xcd;
         }
         const int id = round < full ? run * slots + slot : full * (int)gridDim.x + xcd * ((rest + 7) >> 3) + slot;
-        const int high = n_tiles < 4 ? 1 : 8;
-        const int band = id / (high * n_tiles), in = id - band * high * n_tiles, rb = min(high, m_tiles - high * band);
-        tn = in / rb;
-        tm = high * band + in - tn * rb;
+        if constexpr (BANDS) {
+            const int high = n_tiles < 4 ? 1 : 8;
+            const int band = id / (high * n_tiles), in = id - band * high * n_tiles, rb = min(high, m_tiles - high * band);
+            tn = in / rb;
+            tm = high * band + in - tn * rb;
+        } else {
+            tm = id / n_tiles;
+            tn = id - tm * n_tiles;
+        }
     }
 };
 
 // All tiles of a region that belong to this workgroup, by one of its wavefronts; TM: the wavefront's 32-row blocks.
-template <typename T, int WN, int TM, int EPI>
+template <typename T, int WN, int TM, int EPI, bool PLANNED>
 __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                              const float* __restrict__ bias, void* __restrict__ Cv, bf16_t* __restrict__ Vt,
                                              const Region& rg_, unsigned char* smem) {
@@ -135,7 +143,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     const int wm = wave / WN, wn = wave % WN;
     const int wave_row = wm * rg_.tm0 * 32;                  // the wavefront's first row in a tile
 
-    const Walk walk(rg_.m_tiles, N / BN);
+    const Walk<PLANNED> walk(rg_.m_tiles, N / BN);
     const int n_my = walk.n_my;
     if (n_my == 0) return;
     // first row of a tile; the last tile is moved up where it would pass the end of the buffers (rows of two tiles are
@@ -273,7 +281,12 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     for (int it = 0; it < n_my; ++it) {
         const int m_base = row_of(tm) + wave_row, n0 = tn * BN, n_base = n0 + wn * WTN;
         int tm2, tn2;
-        walk.tile(it + 1 < n_my ? it + 1 : 0, tm2, tn2);
+        if constexpr (PLANNED) {
+            walk.tile(it + 1 < n_my ? it + 1 : 0, tm2, tn2);
+        } else {                                               // mostly the only one
+            tm2 = tm; tn2 = tn;
+            if (it + 1 < n_my) walk.tile(it + 1, tm2, tn2);
+        }
         nx_a = a_of(tm2);
         nx_w = w_of(tn2);
         tm = tm2;
@@ -563,7 +576,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
     if constexpr (!PLANNED) {
         rg.row_begin = 0; rg.bm = BM; rg.tm0 = T::TM;
         rg.m_tiles = (rg.rows + BM - 1) / BM;
-        region_tiles<T, WN, T::TM, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+        region_tiles<T, WN, T::TM, EPI, false>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
     } else {
         static_assert(T::TM == 4, "regions of 2 to 4 blocks a wavefront");
         const GemmPlan pl = *plan;
@@ -575,9 +588,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
             if (rg.m_tiles <= 0) break;
             if (r == 1 && pl.m_tiles > 0) dma_barrier();     // every wavefront's parked DMAs have landed
             const int tm = wave / WN == 0 ? tm0 : tm1;       // both paths meet the same barriers
-            if (tm == 4) region_tiles<T, WN, 4, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else if (tm == 3) region_tiles<T, WN, 3, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else region_tiles<T, WN, 2, EPI>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            if (tm == 4) region_tiles<T, WN, 4, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else if (tm == 3) region_tiles<T, WN, 3, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else region_tiles<T, WN, 2, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
         }
     }
     if (clk && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -611,8 +624,9 @@ void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, 
 
 }  // namespace
 
-// Requirements (checked when the model is loaded): N % 256 == 0, K % 64 == 0; every buffer holds
-// max_rows rows with max_rows % 256 == 0, so whole tiles are always in bounds.
+// Requirements (checked when the model is loaded): N % 256 == 0, K % 64 == 0; every buffer holds max_rows rows with
+// max_rows % 256 == 0.  Tiles of 128 and 256 rows are then always in bounds; those of other heights may reach past the end
+// and are moved up (row_of).
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc residual, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
                       int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s) {

@@ -9,9 +9,11 @@ namespace {
 // weighs one candidate): all rows in tiles of one height, or as many whole rounds of 256-row tiles as there are (or one
 // fewer) and the rest in tiles of one height.  Costs in thousandths of a full round of 256-row tiles.  A full round of
 // lower tiles costs more than its share of rows (measured on 250 k and 440 k rows, the four maps of hidden 768 and 1024:
-// 224 rows 1.00-1.02 per row, 192 1.03-1.08, 160 1.06-1.13, 128 1.11-1.26); a round that leaves units idle runs
+// 224 rows 1.00-1.02 per row, 192 1.03-1.08, 160 1.06-1.13, 128 1.11-1.26); a last round that leaves units idle runs
 // faster, the chip's power being shared by fewer, down to 0.68 of a full one (153 tiles of 256 rows, contraction 3072:
-// 70 us against 103).
+// 70 us against 103).  Where all tiles fit one round, the lowest that do are the fastest however many units that leaves
+// idle: query-key-value map of hidden 768, 4600 rows, 256 to 192 rows 26.9 / 26.3 / 24.9 us; maps back to hidden 1024,
+// 8050 rows, 256 to 128 65.1 / 62.2 / 60.3 / 58.0 / 55.5; hidden 768, 16700 rows, 256 and 224 68.9 / 64.5.
 __device__ GemmPlan plan_gemm(int rows, int n) {
     const int lane = threadIdx.x & 63;
     const int heights[5] = {8, 7, 6, 5, 4}, costs[5] = {1000, 888, 780, 690, 600};   // heights in blocks of 32 rows
@@ -23,7 +25,8 @@ __device__ GemmPlan plan_gemm(int rows, int n) {
     const int rounds = max(pick == 0 ? 0 : tiles / 256 - (pick - 1), 0), m = rounds * 256 / n;
     const int left = max(rows - 256 * m, 0), rest = (left + 32 * h - 1) / (32 * h) * n;
     int64_t cost = (int64_t)rounds * 1000 + (int64_t)(rest / 256) * c + (rounds > 0 ? 50 : 0);
-    if (rest % 256) cost += (int64_t)c * max(680, (rest % 256) * 1000 / 256) / 1000;
+    if (rounds == 0 && rest <= 256) cost = c;
+    else if (rest % 256) cost += (int64_t)c * max(680, (rest % 256) * 1000 / 256) / 1000;
     int64_t best = lane < 15 ? cost * 64 + lane : INT64_MAX;
     for (int o = 8; o > 0; o >>= 1) {
         const int64_t other = __shfl_xor(best, o, 16);
