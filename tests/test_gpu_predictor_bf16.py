@@ -10,6 +10,7 @@ from oracle import predictor as op
 from paper_2504_03702_amd import binding as ps
 from paper_2504_03702_amd import workloads as wl
 from oracle import pool as oracle_pool
+from tests import test_tile_plan as tile_plan
 from tests.gpu_util import TOL_BF16, rel_err, run_predict
 
 pytestmark = pytest.mark.gpu
@@ -272,8 +273,8 @@ def test_production_stratified_sample_against_oracle(production):
 @pytest.mark.parametrize("rows", [2700, 5600, 6600, 9200, 12500, 16500, 19650, 24250, 28900, 34600, 50900])
 def test_tile_heights(tmp_models, rows):
     """Row counts at which the maps of all rows take tiles of 256, 224, 192, 160 and 128 rows, alone and behind whole rounds
-    of 256-row tiles (12 tile columns in the first feed-forward map, 3 and 1 in the others), with last tiles that reach
-    past the buffers: the bits are those of the same requests in calls of 20."""
+    of 256-row tiles (12 tile columns in the first feed-forward map, 3 and 1 in the others): the bits are those of the
+    same requests in calls of 20."""
     print(f"predict tile heights rows={rows}", flush=True)
     cfg = dataclasses.replace(SMALL, ffn=3072)
     model, _ = make(tmp_models, "tile_heights.bin", cfg, ln_jitter=0.1, bias_std=0.05)
@@ -281,6 +282,22 @@ def test_tile_heights(tmp_models, rows):
     n = 40 if rows < 20000 else 120
     lengths = (rows // n // 8 * 8 + rng.integers(-4, 5, n // 2) * 8).astype(np.int32)
     lengths = np.concatenate([lengths, 2 * (rows // n) - lengths]).astype(np.int32)
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got, tokens, flags, _ = run_predict(model, batch)
+    assert flags == 0 and np.isfinite(got).all()
+    chunks_bit_equal(model, batch, got, tokens, chunk=20)
+
+
+@pytest.mark.parametrize("rows", tile_plan.ROWS)
+def test_tiles_up_to_the_end_of_the_buffers(tmp_models, rows):
+    """Every tile height of every map, all rows in one height and behind whole rounds of 256-row tiles, with last tiles
+    that end inside the buffers and such that would reach past them and are moved up (test_tile_plan.py shows that
+    these row counts do): the bits are those of the same requests in calls of 20."""
+    print(f"predict tiles up to the end rows={rows}", flush=True)
+    cfg = dataclasses.replace(SMALL, ffn=3072)
+    model, _ = make(tmp_models, "tile_heights.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(rows)
+    lengths = tile_plan.lengths_of(rows, rng)
     batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
     got, tokens, flags, _ = run_predict(model, batch)
     assert flags == 0 and np.isfinite(got).all()
