@@ -187,6 +187,25 @@ def test_matrix_tiles_at_their_edges(tmp_models, hidden, heads, ffn, n):
     check_tokens(got_f, got_t, ref_t, cfg.d_max)
 
 
+@pytest.mark.parametrize("hidden,heads", [(33, 1), (70, 2), (111, 3), (130, 2), (198, 3), (64, 2)])
+@pytest.mark.parametrize("n", [2, 150])
+def test_head_sizes_off_the_attention_loads(tmp_models, hidden, heads, n):
+    """Head sizes above 32 that are no multiple of 4 (keys are read 16 bytes a load, of which all but one row of a head
+    then start off a 16-byte boundary) and one that is, with one row and with four rows a wavefront."""
+    cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=48, vocab=300, max_pos=133, head_hidden=17, dtype=wl.DTYPE_FP32)
+    print(f"predict fp32 head size {hidden // heads} n={n}", flush=True)
+    model, ref = make(tmp_models, f"heads_{hidden}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(hidden + n)
+    lengths = rng.integers(1, 134, n).astype(np.int32)
+    lengths[-1] = 133
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got_f, got_t, flags, _ = run_predict(model, batch)
+    ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
+    assert flags == 0
+    assert rel_err(got_f, ref_f).max() < TOL_FP32
+    check_tokens(got_f, got_t, ref_t, cfg.d_max)
+
+
 def test_more_feed_forward_units_than_a_grid_has_tiles(tmp_models):
     """2097152 + 100 feed-forward units: more tiles of 32 columns than one launch may have in a dimension."""
     cfg = wl.ModelConfig(layers=1, hidden=2, heads=1, ffn=2097152 + 100, vocab=10, max_pos=8, head_hidden=3, dtype=wl.DTYPE_FP32)
