@@ -14,10 +14,11 @@
 // model) took 33 us a step.  Here a workgroup is one service: four wavefronts per model, both models side by side.
 // Lane j owns hidden unit j; wavefront g keeps column j of gate g's matrix and a quarter of W_mh's rows in registers
 // (read once: the weights' bytes are what the call cannot do without), so a step is 64 + 16 multiply-adds, two
-// exchanges through LDS and two barriers (512 services of 64 units over 24 windows: 82 us with the library's functions and a
-// division a step, 77 so; one service 31 and 28).  Vector ALU (some 140 instructions a step and wavefront, four wavefronts
-// a SIMD) and LDS reads (20 of 16 bytes a lane) take about as long as each other.  Broadcasting h and m by the
-// multiply-adds' own lane selection instead of LDS reads: half-rate multiply-adds, no faster.
+// exchanges through LDS and two barriers (64 units over 24 windows, with the library's functions and a division a step / so:
+// 512 services 92 and 88 us, one 32.4 and 30.4).  What bounds it: vector ALU (some 150 instructions a step and wavefront,
+// four wavefronts a SIMD: busy 53 % of the time before the last of them came in) and the waits of a step's chain, LDS reads
+// (20 of 16 bytes a lane) and two barriers.  Broadcasting h and m by the multiply-adds' own lane selection instead of LDS
+// reads: half-rate multiply-adds, no faster.
 // c and h are kept by all four wavefronts alike.  fp32 arithmetic, four
 // partial sums per product.  Matrices are stored input-major ([in][out]: element (out j, in i) at i * H + j), so the
 // lanes of a wavefront read consecutive words.
@@ -61,6 +62,9 @@ __device__ __forceinline__ float tanh_hw(float z) {
     return fabsf(z) < 0.6f ? fmaf(z * u, q, z) : far;
 }
 
+// A value that all lanes hold alike, in a scalar register (the weights fill the vector registers).
+__device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
 // HB: hidden rounded up to 32 or 64 (weights beyond `hidden` are zeros).
 template <int HB>
 __global__ __launch_bounds__(512, 4) void forecast_kernel(const float* __restrict__ weights, int hidden,
@@ -99,7 +103,9 @@ __global__ __launch_bounds__(512, 4) void forecast_kernel(const float* __restric
         lo = fminf(lo, __shfl_xor(lo, o, 64));
         hi = fmaxf(hi, __shfl_xor(hi, o, 64));
     }
-    float span = hi > lo ? hi - lo : 1.0f;
+    lo = uniform(lo);
+    hi = uniform(hi);
+    float span = uniform(hi > lo ? hi - lo : 1.0f);
     float y0 = 0.f, y1 = 0.f;                               // this model's forecasts
     // pass 0: the k past windows, then (first forecast inside [lo, hi]) one more input.  pass 1, only if the
     // first forecast left that range: the k + 1 values again under their own normalisation.  Both models of the
@@ -142,7 +148,7 @@ __global__ __launch_bounds__(512, 4) void forecast_kernel(const float* __restric
             h = unit ? tanh_hw(c) * s_g[kind][2][lane] : 0.f;
             if (t >= k - 1) {                               // after the k-th input and after the extension
                 const float dot = wave_sum(w_o * h);
-                const float f = fmaxf(0.f, fmaf(span, dot + b_out, lo));
+                const float f = uniform(fmaxf(0.f, fmaf(span, dot + b_out, lo)));
                 if (pass == 0) {
                     if (t == k - 1) {
                         y0 = f;
@@ -159,9 +165,9 @@ __global__ __launch_bounds__(512, 4) void forecast_kernel(const float* __restric
         if (pass == 0 && !__syncthreads_or((int)needs_second)) break;
         // normalisation of the extended history for the second pass
         if (needs_second) {
-            lo = fminf(lo, y0);
-            hi = fmaxf(hi, y0);
-            span = hi > lo ? hi - lo : 1.0f;
+            lo = uniform(fminf(lo, y0));
+            hi = uniform(fmaxf(hi, y0));
+            span = uniform(hi > lo ? hi - lo : 1.0f);
         }
     }
     if (gate == 0 && lane == 0) { s_y[kind][0] = y0; s_y[kind][1] = y1; }
