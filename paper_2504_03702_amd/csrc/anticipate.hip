@@ -16,8 +16,8 @@
 // HBM once and shared through that XCD's L2.
 // Kernel 2 (reduce): one workgroup per instance sums the partial difference rows, takes the prefix
 // sum over buckets and accumulates into load[]; overflow[] likewise.  No global atomics: every
-// global word has exactly one writer; the only atomic operations are the LDS adds of kernel 1.  All arithmetic is integer, so the result is exact and
-// independent of record order.
+// global word has exactly one writer; the only atomic operations are the LDS adds of kernel 1.  All arithmetic is
+// integer, so the result is exact and independent of record order.
 //
 // Records in arrival order (a request log, the order requests are admitted in) allow a cheaper first
 // kernel, tried first on long streams: a slice of such a stream touches few buckets, so its workgroup
@@ -1264,8 +1264,8 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
                            p.w_slice_len, p.h_slices > 0 ? p.h_weighed : 0, p.h_slice_len, wpartial, wovf, worigin, status);
     }
     HalvesArgs hv = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.h_slice_len, n_inst, horizon, p.h_rows, p.h_groups,
-                     p.h_slices, p.h_stride, 32 - p.h_row_bits, 32 - p.h_row_bits - p.h_bucket_bits, (uint16_t*)wsb, (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at),
-                     (int32_t*)(wsb + p.h_flag_at)};
+                     p.h_slices, p.h_stride, 32 - p.h_row_bits, 32 - p.h_row_bits - p.h_bucket_bits, (uint16_t*)wsb,
+                     (uint16_t*)(wsb + p.h_high_at), (int64_t*)(wsb + p.h_ovf_at), (int32_t*)(wsb + p.h_flag_at)};
     const GeneralArgs ga = {pred_tokens, instance_id, arrival_bucket, rate, n_req, p.slice_len, n_inst, horizon,
                             p.rows_per_group, p.groups, p.slices, partial, partial_ovf};
     // (which of the two runs is known on the device)
@@ -1274,8 +1274,8 @@ int anticipate_enqueue(const int32_t* pred_tokens, const int32_t* instance_id, c
     const bool halves = p.h_slices > 0;
     hipLaunchKernelGGL(anticipate_scatter_kernel, dim3(halves && h_blocks > blocks ? h_blocks : blocks), dim3(kScatterThreads),
                        halves && p.h_lds_bytes > p.lds_bytes ? p.h_lds_bytes : p.lds_bytes, s, ga, hv, worigin, p.w_slices, status);
-    hipLaunchKernelGGL(anticipate_reduce_kernel, dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, partial, partial_ovf, p.slices, n_inst, horizon,
-                       wpartial, wovf, worigin, p.w_slices, p.w_buckets, hv, load, overflow, status);
+    hipLaunchKernelGGL(anticipate_reduce_kernel, dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, partial, partial_ovf, p.slices,
+                       n_inst, horizon, wpartial, wovf, worigin, p.w_slices, p.w_buckets, hv, load, overflow, status);
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }
 

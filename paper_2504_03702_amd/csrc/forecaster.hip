@@ -314,12 +314,15 @@ extern "C" int ps_forecast(const float* weights, int32_t hidden, const float* hi
         n = n_services - s0 < most ? n_services - s0 : most;
         const dim3 grid((unsigned)n), block(512);
         const float *w = weights + (size_t)2 * s0 * model_floats, *hp = hist_p + (size_t)s0 * k, *hd = hist_d + (size_t)s0 * k;
+        const float* mu0 = mu + (size_t)3 * s0;
+        float* o = out + (size_t)5 * s0;
+        hipStream_t st = (hipStream_t)hip_stream;
         if (many_pays(n_services, hidden, k))
-            hipLaunchKernelGGL(forecast_many_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, (hipStream_t)hip_stream, w, hidden, hp, hd, n, k, mu + (size_t)3 * s0, out + (size_t)5 * s0);
+            hipLaunchKernelGGL(forecast_many_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, w, hidden, hp, hd, n, k, mu0, o);
         else if (hidden <= 32)
-            hipLaunchKernelGGL(forecast_kernel<32>, grid, block, 0, (hipStream_t)hip_stream, w, hidden, hp, hd, k, mu + (size_t)3 * s0, out + (size_t)5 * s0);
+            hipLaunchKernelGGL(forecast_kernel<32>, grid, block, 0, st, w, hidden, hp, hd, k, mu0, o);
         else
-            hipLaunchKernelGGL(forecast_kernel<64>, grid, block, 0, (hipStream_t)hip_stream, w, hidden, hp, hd, k, mu + (size_t)3 * s0, out + (size_t)5 * s0);
+            hipLaunchKernelGGL(forecast_kernel<64>, grid, block, 0, st, w, hidden, hp, hd, k, mu0, o);
     }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
 }
