@@ -93,7 +93,8 @@ struct Region {
 // The tiles of the last round are dealt to the XCDs evenly, so every workgroup gets the same number of tiles to one (P = 3
 // in whole bands per XCD, as it used to be: the first feed-forward map of 100 k rows of hidden 768 549 us, 523 so).
 // Without BANDS, row by row and a range to each XCD: small tiles, mostly one to a workgroup, where a launch of 27 us shows the
-// arithmetic (18 to 26 requests, maps of hidden 768 27.4 us with bands, 26.6 so; keys and values 17.6, 17.1).
+// arithmetic (18 to 26 requests, maps of hidden 768 27.4 us with bands, 26.6 so; keys and values 17.6, 17.1).  4096 requests'
+// first feed-forward map of hidden 1024, 1024 of those tiles: 90 us with bands, 101 without.
 template <bool BANDS>
 struct Walk {
     int n_tiles, m_tiles, slots, xcd, slot, full, rest, n_my;
@@ -143,7 +144,9 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     const int wm = wave / WN, wn = wave % WN;
     const int wave_row = wm * rg_.tm0 * 32;                  // the wavefront's first row in a tile
 
-    const Walk<PLANNED> walk(rg_.m_tiles, N / BN);
+    // (EPI_GELU_SPLIT: small tiles, but many of them for many requests)
+    constexpr bool BANDS = PLANNED || EPI == EPI_GELU_SPLIT;
+    const Walk<BANDS> walk(rg_.m_tiles, N / BN);
     const int n_my = walk.n_my;
     if (n_my == 0) return;
     // first row of a tile; the last tile is moved up where it would pass the end of the buffers (rows of two tiles are
@@ -281,7 +284,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     for (int it = 0; it < n_my; ++it) {
         const int m_base = row_of(tm) + wave_row, n0 = tn * BN, n_base = n0 + wn * WTN;
         int tm2, tn2;
-        if constexpr (PLANNED) {
+        if constexpr (BANDS) {
             walk.tile(it + 1 < n_my ? it + 1 : 0, tm2, tn2);
         } else {                                               // mostly the only one
             tm2 = tm; tn2 = tn;
