@@ -15,10 +15,10 @@
 // Lane j owns hidden unit j; wavefront g keeps column j of gate g's matrix and a quarter of W_mh's rows in registers
 // (read once: the weights' bytes are what the call cannot do without), so a step is 64 + 16 multiply-adds, two
 // exchanges through LDS and two barriers (64 units over 24 windows, with the library's functions and a division a step / so:
-// 512 services 92 and 88 us, one 32.4 and 30.4).  What bounds it: vector ALU (some 150 instructions a step and wavefront,
-// four wavefronts a SIMD: busy 53 % of the time before the last of them came in) and the waits of a step's chain, LDS reads
-// (20 of 16 bytes a lane) and two barriers.  Broadcasting h and m by the multiply-adds' own lane selection instead of LDS
-// reads: half-rate multiply-adds, no faster.
+// 512 services 92 and 88 us, one 32.4 and 30.4).  What takes the time: vector ALU (some 150 instructions a step and
+// wavefront, four wavefronts a SIMD) 56 % of it, and the waits in a step's chain of LDS reads (20 of 16 bytes a lane) and two
+// barriers.  Broadcasting h and m by the multiply-adds' own lane selection instead of LDS reads: half-rate multiply-adds,
+// no faster.
 // c and h are kept by all four wavefronts alike.  fp32 arithmetic, four
 // partial sums per product.  Matrices are stored input-major ([in][out]: element (out j, in i) at i * H + j), so the
 // lanes of a wavefront read consecutive words.
