@@ -111,8 +111,9 @@ __device__ __forceinline__ long long wave_min(long long v, bool part, int& src) 
 
 // Launched with 1024 threads: all of them bring the windows in, then the wavefronts without instances leave.
 // CH: 16-byte pieces of a block (1, 2 or 4: windows of at most 32 pieces, which an update takes a lane each; 0: any
-// plan, a lane takes a block).  NARROW: with walk_narrow, for calls of 12 requests and more; what it needs in front costs the
-// others more than it saves (256 instances of 100 slots, 3 requests 27.8 us without, 29.3 with; 12 34.7 and 33.8).
+// plan, a lane takes a block).  NARROW: with walk_narrow, for calls of 12 requests and more, where it saves over a
+// microsecond of a call by itself; its bounds cost a call of few (256 instances of 100 slots, 3 requests 27.5 us without,
+// 27.6 with, 8 30.9 and 29.8, 12 34.1 and 31.8; 64 instances 23.7 and 24.2, 26.3 and 25.9, 28.2 and 27.5).
 template <int CH, bool NARROW>
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
@@ -688,14 +689,15 @@ bool by_piece(const RoutePlan& p) {
     return (p.block == 4 || p.block == 8 || p.block == 16) && (int64_t)p.n_blocks * p.block <= 4 * kRouteMaxBlocks;
 }
 
-// Microseconds for n requests, scanned / with the tables (the tables take 5 us to make where updates go by pieces, 30 to
-// 60 where the wavefronts make them block by block):
-//   by pieces: 256 instances of 100 slots (blocks of 4), n = 1 24.6 / 27.6, 2 28.3 / 28.1, 64 221 / 60;  256 of 120 (of 8)
-//   1 25.7 / 28.2, 3 32.8 / 28.9, 31 127 / 44;  256 of 128 (of 16) 2 29.3 / 29.0, 4 36.6 / 30.2, 31 127 / 46
-//   blocks of 8 and 16, not by pieces: 90 of 256, n = 8 41 / 59, 24 90 / 75;  64 of 500, n = 1 21 / 81, 24 102 / 109,
-//   31 126 / 118, 2048 6802 / 2671
-//   blocks of 32 and 48: 1024 of 29, n = 64 225 / 187;  16 of 1500, n = 64 227 / 253, 2048 6984 / 6053
-//   longer ones: 1 of 2000, n = 2048 6281 / 8372;  8 of 3000 11499 / 11415;  256 of 134 (one block each) 13979 / 15951
+// Microseconds a call for n requests, scanned / with the tables, calls back to back (a call by itself takes 10 to 11 more
+// either way); the tables take 4 us to make where updates go by pieces, 20 to 60 where the wavefronts make them block by block:
+//   by pieces: 256 instances of 100 slots (blocks of 4), n = 1 13.5 / 17.4, 2 17.0 / 18.1, 3 20.3 / 18.9, 64 224 / 49;  256 of 120
+//   (of 8) 2 17.6 / 19.5, 3 20.9 / 20.4, 31 115 / 36;  256 of 128 (of 16) 2 18.9 / 19.9, 3 22.2 / 20.8, 31 116 / 37
+//   blocks of 8 and 16, not by pieces: 90 of 256, n = 8 33 / 50, 24 83 / 67, 31 106 / 74, 64 209 / 108;  64 of 500, n = 1
+//   11.5 / 72, 24 91 / 101, 31 116 / 110, 64 230 / 152, 2048 7107 / 2673
+//   blocks of 32 and 48: 1024 of 29 (one block), n = 64 233 / 82, 128 441 / 147, 2048 6624 / 2043;  16 of 1500, n = 64 237 / 252,
+//   128 467 / 439, 2048 7340 / 6033
+//   longer ones: 1 of 2000, n = 2048 6512 / 8457;  8 of 3000 11409 / 11409;  256 of 134 (one block each) 13903 / 15861
 bool tables_pay(int n_req, int window, const RoutePlan& p) {
     if (window == 0) return true;
     return by_piece(p) ? n_req >= 3 : p.block <= 16 ? n_req >= 32 : p.block <= 48 && n_req >= 128;
