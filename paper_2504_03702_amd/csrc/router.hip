@@ -212,7 +212,9 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
                 for (int c = 0; c < CH; ++c) {
                     const int4 v = s_win[(b * CH + c) * pitch + inst];
                     const int t = 4 * (b * CH + c);
-                    if (CH == 1 || t < window) m = max(m, (int)((unsigned)v.x + (unsigned)t));
+                    // (one piece a block: its first slot is inside.  Not said to the NARROW kernel, whose walk comes out
+                    // 0.4 % slower: 4096 requests over 256 instances 2035 us, 2044)
+                    if ((CH == 1 && !NARROW) || t < window) m = max(m, (int)((unsigned)v.x + (unsigned)t));
                     if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
                     if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
                     if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
