@@ -68,7 +68,7 @@ struct AntPlan {
     int w_slices, w_buckets;
     int64_t w_slice_len;
     size_t w_lds_bytes, w_partial_bytes, w_ovf_bytes, w_origin_bytes, w_partial_at, w_ovf_at, w_origin_at;
-    // halves kernel (records in any order, twice as many rows a workgroup); h_slices == 0: not used
+    // halves form (records in any order, twice as many rows a workgroup); h_slices == 0: not used
     int h_rows, h_groups, h_slices, h_stride, h_row_bits, h_bucket_bits, h_weighed;
     int64_t h_slice_len;
     size_t h_lds_bytes, h_high_at, h_ovf_at, h_flag_at;
@@ -132,7 +132,7 @@ int bits_for(int n) {
     return bits;
 }
 
-// Lays the halves kernel's results over the general and the windowed buffers (they are needed only where the windowed
+// Lays the halves form's results over the general and the windowed buffers (they are needed only where the windowed
 // kernel gave up), as many slices as fit; not used where a workgroup would not hold more rows than the general one's.
 void plan_halves(AntPlan& p, int64_t n, int n_inst, int horizon) {
     p.h_slices = 0;
@@ -377,7 +377,7 @@ __device__ __forceinline__ void general_body(const GeneralArgs& p, unsigned char
 }
 
 // Scatter for long streams in any order: 16-bit counters, two rows to a word, so that a workgroup holds twice the rows
-// and a record is looked at by half as many workgroups.  The general kernel is bound by instruction issue, most of it
+// and a record is looked at by half as many workgroups.  The general form is bound by instruction issue, most of it
 // looking at records of other groups (118 wavefront instructions per 64 records over four groups of 64 rows).
 //
 // Word [w][b] holds the difference of row w in its low half and of row w + R in its high half: adding signed amounts,
@@ -391,10 +391,10 @@ __device__ __forceinline__ void general_body(const GeneralArgs& p, unsigned char
 // bits, and the other way round.  The upper bits go to a second plane.
 // Results are loads, not differences: the reduction adds them up and needs no scan.
 //
-// 44.1 M records over 256 instances of 600 buckets: 200 us in the general kernel, 146 here, of which about 105 are vector
+// 44.1 M records over 256 instances of 600 buckets: 200 us in the general form, 148 here, of which about 105 are vector
 // instructions (19 a look, 48 a record); a queue entry names row, bucket and tokens in fields, so neither side multiplies
 // or divides by the row length.  The fields are as wide as the call's rows and buckets ask for, which leaves 14 bits and
-// more to the tokens (12 as a fixed width: with 5 % of the predictions above 4096 284 us, the general kernel 220).
+// more to the tokens (12 as a fixed width: with 5 % of the predictions above 4096 284 us, the general form 220).
 //
 // A second pass costs what the first does.  Crowds that a sample shows are left to the general form (anticipate_window_kernel
 // takes the sample in 2 us); 5 % of those records in one cell 229 us so, 467 with two more passes in place of a sample,
@@ -897,9 +897,9 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
 
 // One workgroup per instance.  Where the horizon is short enough for a 64-bit row of the map in LDS, all
 // 1024 threads first stream this instance's partial rows (one per slice: the whole horizon from the
-// general kernel, a window at its origin from the windowed one) and add them into that row: the
+// general form, a window at its origin from the windowed one) and add them into that row: the
 // (slice, cell) pairs are dealt to the threads in order, so loads are contiguous runs, 16 in flight per
-// thread, and the lanes of an LDS add hit different cells.  Longer horizons sum the general kernel's
+// thread, and the lanes of an LDS add hit different cells.  Longer horizons sum the general form's
 // rows bucket by bucket.  Then buckets are taken 1024 at a time, thread t < 256 owning the four
 // consecutive buckets 4 t .. 4 t + 3: it prefix-sums its four values, the 256 thread totals are scanned
 // with wavefront shuffles, and the curve is accumulated into load[].  64-bit sums, so a bucket leaving
@@ -921,7 +921,7 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
     const bool in_lds = horizon <= kWindowMaxHorizon;         // (the windowed kernel is only used then)
     if (tid == 0) s_over = 0;                                 // (a barrier follows before its first use)
     if (hv.slices > 0 && bits == kGaveUp) {
-        // the halves kernel's loads: a thread adds up eight neighbouring buckets of every T-th slice
+        // the halves form's loads: a thread adds up eight neighbouring buckets of every T-th slice
         for (int i = tid; i < horizon; i += kReduceThreads) s_row[i] = 0;
         const int wg = k / hv.rows;
         bool some = false;
@@ -1112,10 +1112,10 @@ __global__ __launch_bounds__(kReduceThreads) void anticipate_reduce_kernel(
 // A management period's batch is a few thousand records: one launch and no partial curves.  A workgroup per instance
 // looks through the batch's instances (eight ids a thread requested together), applies its own records to an LDS row
 // of differences and adds the row's prefix sums to the map.  At most 2^14 records of at most 2^16 tokens: no cell can
-// leave 32 bits.  The slices of the general kernel keep LDS rows for 65 instances each and hand 256 x 600 counters
+// leave 32 bits.  The slices of the general form keep LDS rows for 65 instances each and hand 256 x 600 counters
 // over through memory: 8 us and 6 us for 4096 records.
 //
-// Microseconds, the general kernels / this one: 16384 records over 8 and 64 instances of 600 buckets 19 / 14 and 21 / 12,
+// Microseconds, the general form / this one: 16384 records over 8 and 64 instances of 600 buckets 19 / 14 and 21 / 12,
 // 4096 over 1024 30 / 12, 64 over 65536 instances of 48 buckets 1105 / 340.  Where hundreds of records meet in one cell
 // the atomics of its only copy queue up: 16384 records over 1 instance of 16, 48 and 100 buckets 21 / 32, 17 / 19 and
 // 17 / 17, over 4 of 4 buckets 20 / 25, over 8 of 48 19 / 16.
