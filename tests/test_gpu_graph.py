@@ -83,3 +83,59 @@ def test_graph_replays_match_eager_calls(tmp_models):
             assert np.array_equal(g, w), f"replay {it} of micro-batch {i}"
         (torch.ones(1000, device=DEV) * 2).sum().item()                   # unrelated eager work between replays
     assert ps.ps_status_read(status)[0] == 0
+
+
+def test_stream_replays_pick_their_form(tmp_models):
+    """One captured call on long streams whose form is decided on the device: in arrival order (window), in any order (16-bit
+    counters), crowded (general form), crowded where the sample does not look (second pass).  Every replay gives the
+    oracle's map, whatever form the replay before it took."""
+    from oracle import anticipator as oa
+    n, n_inst, horizon = 3_000_001, 130, 597
+    rng = np.random.default_rng(8)
+    rate = rng.integers(20, 200, n_inst, dtype=np.int32)
+    rate[[3, 70]] = 5000
+    d, k = rng.integers(0, 50, n, dtype=np.int32), rng.integers(0, n_inst, n, dtype=np.int32)
+    a = rng.integers(0, horizon, n, dtype=np.int32)
+    streams = {"in order": (d, k, np.sort(a)), "any order": (d, k, a)}
+    for name, rows, unseen in (("crowded", [3], False), ("crowded, unseen", [3, 70], True)):
+        d2, k2, a2 = d.copy(), k.copy(), a.copy()
+        for row in rows:
+            hot = rng.random(n) < 0.02
+            if unseen:
+                hot &= np.arange(n) % (n // 4096 * 16) >= 16
+            d2[hot], k2[hot], a2[hot] = 4000, row, 40
+        streams[name] = (d2, k2, a2)
+    want = {}
+    for name, (sd, sk, sa) in streams.items():
+        load, ovf, st, _ = oa.anticipate(sd, sk, sa, rate, n_inst, horizon)
+        assert st == 0
+        want[name] = (load, ovf)
+    dev = {name: [torch.from_numpy(c).to(DEV) for c in cols] for name, cols in streams.items()}
+    stage = [torch.zeros(n, dtype=torch.int32, device=DEV) for _ in range(3)]
+    rate_t = torch.from_numpy(rate).to(DEV)
+    load = torch.zeros(n_inst * horizon, dtype=torch.int32, device=DEV)
+    ovf = torch.zeros(n_inst, dtype=torch.int64, device=DEV)
+    ws = ps.alloc_workspace(ps.ps_anticipate_workspace_bytes(n, n_inst, horizon), DEV)
+    status = ps.new_status(DEV)
+    call = lambda: ps.ps_anticipate(*stage, rate_t, n_inst, horizon, load, ovf, ws, status)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for it, name in enumerate(["any order", "crowded", "any order", "in order", "crowded, unseen", "in order", "crowded",
+                               "crowded, unseen", "any order"]):
+        print(f"graph replay {it}: {name}", flush=True)
+        for s, c in zip(stage, dev[name]):
+            s.copy_(c)
+        load.zero_(); ovf.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        side.synchronize()
+        assert np.array_equal(load.cpu().numpy().reshape(n_inst, horizon), want[name][0]), f"replay {it}, {name}"
+        assert np.array_equal(ovf.cpu().numpy(), want[name][1]), f"replay {it}, {name}"
+        (torch.ones(1000, device=DEV) * 2).sum().item()                   # unrelated eager work between replays
+    assert ps.ps_status_read(status)[0] == 0
