@@ -674,19 +674,6 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
     const int64_t probe = begin + (int64_t)tid * 4;
     int4 probed = make_int4(-1, -1, -1, -1);
     if (probe + 4 <= end) probed = *(const int4*)(arrival_bucket + probe);
-    // sample of the whole stream, looked at if this slice is in no order: 16 records from each of 256 places (four from each
-    // of 1024: 4 us more a call), for `weighed` rows a workgroup
-    const int k0 = slice * weighed, rows = max(min(weighed, n_inst - k0), 0);
-    int4 kv = {}, dv = {}, av = {};
-    int rates = 0;                                             // of row `lane`
-    if (rows > 0) {
-        const int64_t at = (int64_t)(tid >> 2) * (n / 4096 * 16) + 4 * (tid & 3);
-        kv = *(const int4*)(instance_id + at);
-        dv = *(const int4*)(pred_tokens + at);
-        av = *(const int4*)(arrival_bucket + at);
-        rates = rate[min(k0 + (lane & (kWaves - 1)), n_inst - 1)];
-        for (int i = tid; i < rows * horizon; i += kScatterThreads) s_diff[i] = 0;
-    }
     unsigned* s_top = (unsigned*)(lds_raw + 8);               // of the sample: largest load; tokens; tokens times what a
     unsigned long long *s_tokens = (unsigned long long*)(lds_raw + 16), *s_weighted = s_tokens + 1;   // bucket gets of them
     if (tid < 2) { s_flag[tid] = 0; *s_top = 0; s_tokens[tid] = 0; }
@@ -708,6 +695,21 @@ __global__ __launch_bounds__(kScatterThreads) void anticipate_window_kernel(
         __syncthreads();
     }
     if (s_flag[1]) {                                          // uniform
+        // A sample of the whole stream, 16 records from each of 256 places (four from each of 1024: 4 us more a call), for
+        // `weighed` rows a workgroup.  Loaded here and not ahead of the look above: 0.3 us more for streams in any order,
+        // 0.9 less for a log of 44.1 M.
+        const int k0 = slice * weighed, rows = max(min(weighed, n_inst - k0), 0);
+        int4 kv = {}, dv = {}, av = {};
+        int rates = 0;                                         // of row `lane`
+        if (rows > 0) {
+            const int64_t at = (int64_t)(tid >> 2) * (n / 4096 * 16) + 4 * (tid & 3);
+            kv = *(const int4*)(instance_id + at);
+            dv = *(const int4*)(pred_tokens + at);
+            av = *(const int4*)(arrival_bucket + at);
+            rates = rate[min(k0 + (lane & (kWaves - 1)), n_inst - 1)];
+            for (int i = tid; i < rows * horizon; i += kScatterThreads) s_diff[i] = 0;
+        }
+        __syncthreads();
         // Are its rows too crowded for 16-bit counters?  The sample's largest load, scaled up to a slice of halves_body.  A
         // load m of records that give a bucket q each varies by sqrt(q m) from sample to sample (q: the mean over
         // tokens): two of those are taken off, so that a few large records that met by chance are no crowd.
