@@ -86,7 +86,32 @@ __device__ __forceinline__ void report_fault(ps_status* st, int flag, int64_t in
     atomicMax((long long*)&st->first_bad, (long long)(((int64_t)1 << 62) - index));
 }
 
+// ---- The residual stream: 32-bit sums kept as two arrays of 16 bits ------------------------------------------
+// The float's bits plus 0x8000 are cut in two: hi, the upper half, is the sum rounded to bf16 (ties away from zero), the
+// operand of the next map; hi and lo together are the float.  Two instructions an element either way; hi and lo as two
+// bf16 values, which kept 16 significant bits of a sum, took three.
+#define PS_STREAM_ZERO_LO 0x8000u     // lo of a zero (hi is 0)
+__device__ __forceinline__ float stream_join(uint16_t hi, uint16_t lo) {
+    return __uint_as_float((((uint32_t)hi << 16) | lo) - 0x8000u);
+}
+// Two neighbouring elements at a time, of a word of each array.
+__device__ __forceinline__ float2 stream_join2(uint32_t hi, uint32_t lo) {
+    return make_float2(__uint_as_float(__builtin_amdgcn_perm(hi, lo, 0x05040100u) - 0x8000u),
+                       __uint_as_float(__builtin_amdgcn_perm(hi, lo, 0x07060302u) - 0x8000u));
+}
+__device__ __forceinline__ void stream_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+    const uint32_t x = __float_as_uint(a) + 0x8000u, y = __float_as_uint(b) + 0x8000u;
+    hi = __builtin_amdgcn_perm(y, x, 0x07060302u);
+    lo = __builtin_amdgcn_perm(y, x, 0x05040100u);
+}
+
 // ---- LayerNorm pieces that several kernels must compute alike, to the last bit ----------------------------
+// A new sum of the residual stream: a map's product, its bias and the LayerNorm of the sum before it, whose row has
+// st = (mean, 1 / std); shift: beta + bias.
+__device__ __forceinline__ float residual_sum(float product, float y, float2 st, float gamma, float shift) {
+    return product + fmaf(fmaf(y, st.y, -st.x * st.y), gamma, shift);
+}
+
 // (mean, 1 / std) from a row's sum and sum of squares (biased variance).
 __device__ __forceinline__ float2 ln_moments(float sum, float sq, float inv_n, float eps) {
     const float mean = sum * inv_n;
@@ -94,21 +119,21 @@ __device__ __forceinline__ float2 ln_moments(float sum, float sq, float inv_n, f
     return make_float2(mean, 1.0f / sqrtf(var + eps));
 }
 
-// LayerNorm of the stream value hi + lo.
-__device__ __forceinline__ float ln_apply(float hi, float lo, float2 st, float gamma, float beta) {
-    return fmaf(((hi + lo) - st.x) * st.y, gamma, beta);
+// LayerNorm of a value of the stream.
+__device__ __forceinline__ float ln_apply(float y, float2 st, float gamma, float beta) {
+    return fmaf((y - st.x) * st.y, gamma, beta);
 }
 
-// (mean, 1 / std) of one row of the sums hi + lo by one wavefront, in two passes.
+// (mean, 1 / std) of one row of the stream by one wavefront, in two passes.
 __device__ __forceinline__ float2 row_moments(const uint16_t* yh, const uint16_t* yl, int H, float eps, int lane) {
     float sum = 0.f;
 #pragma unroll 4
-    for (int i = lane; i < H; i += 64) sum += bf16_to_f32(yh[i]) + bf16_to_f32(yl[i]);
+    for (int i = lane; i < H; i += 64) sum += stream_join(yh[i], yl[i]);
     const float mean = wave_sum(sum) / (float)H;
     float sq = 0.f;
 #pragma unroll 4
     for (int i = lane; i < H; i += 64) {
-        const float d = (bf16_to_f32(yh[i]) + bf16_to_f32(yl[i])) - mean;
+        const float d = stream_join(yh[i], yl[i]) - mean;
         sq = fmaf(d, d, sq);
     }
     return make_float2(mean, 1.0f / sqrtf(wave_sum(sq) / (float)H + eps));

@@ -1,6 +1,6 @@
 // bf16 encoder path: the per-layer sequence of MFMA GEMMs and attention launches.  There is no
-// LayerNorm kernel: a residual epilogue writes the new sums of the residual stream as two bf16 values
-// hi + lo (hi is the next map's operand) and leaves per-row partial sums; a small kernel turns those into (mean, 1/std),
+// LayerNorm kernel: a residual epilogue writes the new sums of the residual stream in two 16-bit
+// halves hi and lo (hi, the sum rounded to bf16, is the next map's operand) and leaves per-row partial sums; a small kernel turns those into (mean, 1/std),
 // and the next map, which carries the LayerNorm's scale and shift in its weights, finishes the
 // normalisation in its own epilogue.
 #include "device_util.h"
@@ -72,10 +72,9 @@ __global__ __launch_bounds__(256) void ln_stats_gather_kernel(const float2* __re
     for (int i = lane; i < H / 4; i += 64) {
         const uint2 h = yh[i], l = yl[i];
         const float4 g = ((const float4*)gamma)[i], b = ((const float4*)beta)[i];
-        const float x0 = ln_apply(__uint_as_float(h.x << 16), __uint_as_float(l.x << 16), st, g.x, b.x);
-        const float x1 = ln_apply(__uint_as_float(h.x & 0xffff0000u), __uint_as_float(l.x & 0xffff0000u), st, g.y, b.y);
-        const float x2 = ln_apply(__uint_as_float(h.y << 16), __uint_as_float(l.y << 16), st, g.z, b.z);
-        const float x3 = ln_apply(__uint_as_float(h.y & 0xffff0000u), __uint_as_float(l.y & 0xffff0000u), st, g.w, b.w);
+        const float2 ya = stream_join2(h.x, l.x), yb = stream_join2(h.y, l.y);
+        const float x0 = ln_apply(ya.x, st, g.x, b.x), x1 = ln_apply(ya.y, st, g.y, b.y);
+        const float x2 = ln_apply(yb.x, st, g.z, b.z), x3 = ln_apply(yb.y, st, g.w, b.w);
         const uint2 o = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
         oh[i] = o;
         ol[i] = make_uint2(pack_bf16x2(x0 - __uint_as_float(o.x << 16), x1 - __uint_as_float(o.x & 0xffff0000u)),

@@ -2,14 +2,14 @@
 //
 //   C[m, n] = sum_k A[m, k] * W[n, k]   (A: activations [rows][K], W: weights [N][K], both bf16,
 //                                        contraction index contiguous; fp32 accumulation)
-//   epilogue: + bias[n], then one of: store | erf-GELU, store | + residual stream, store as hi + lo |
+//   epilogue: + bias[n], then one of: store | erf-GELU, store | + residual stream, store in two halves |
 //             QKV split (query and key columns to [rows][2H], value columns transposed to
 //             Vt[H][max_rows] so the attention kernel reads keys-contiguous value tiles), also as
 //             keys and values only | erf-GELU, store as hi + lo, for an operand that is hi + lo too.
 //   A LayerNorm in front of a map is folded into it: the operand is the row before normalisation,
 //   W carries the LayerNorm's scale, and the epilogue finishes with the row's (mean, 1/std):
 //   rstd * (acc - mean * colsum[n]) + d[n].  The residual epilogues produce such operands: they write
-//   the new sums as two bf16 values hi + lo (hi is the operand) and leave per-row partial sums for the
+//   the new sums in two halves (hi, rounded to bf16, is the operand) and leave per-row partial sums for the
 //   statistics.
 //
 // One workgroup computes a BM x BN tile.  Per 64-deep k slice the A and W sub-tiles are brought
@@ -26,6 +26,8 @@
 // compacted); each workgroup derives its tile list from it.  Workgroups are dealt to the 8 XCDs
 // round-robin by the hardware; the tile list is built so that the tiles in flight on one XCD are
 // neighbours that share activation row panels and weight column panels through that XCD's L2.
+#include <limits.h>
+
 #include <type_traits>
 
 #include "device_util.h"
@@ -35,6 +37,8 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define GLOBAL_AS __attribute__((address_space(1)))
 #define LDS_AS __attribute__((address_space(3)))
@@ -49,8 +53,12 @@ struct Tile {
     static constexpr int A_BYTES = BM * 128;         // one 64-deep slice
     static constexpr int B_BYTES = BN * 128;
     static constexpr int STAGE = A_BYTES + B_BYTES;  // an A slice followed by a W slice
-    static constexpr int EPI_BYTES = 4096;           // per-wavefront transpose region of the epilogue
-    static constexpr int LDS = 2 * STAGE + NW * EPI_BYTES;
+    // what the epilogue needs of a tile's columns (three arrays of floats) and rows (their statistics)
+    static constexpr int COLS = 2 * STAGE, ROWS = COLS + 3 * BN * 4;
+    static constexpr int STRIPS = ROWS + BM * 8;
+    // residual epilogue: a wavefront's strip of 8 rows x 64 columns of floats, rows padded
+    static constexpr int STRIP_LD = 68, LDS = STRIPS + NW * 8 * STRIP_LD * 4;
+    static_assert(2 * BN <= 512 && BM <= 128 * (NW - 3), "a wavefront fetches an array of the columns, or 128 rows' statistics");
     static_assert(NW % 2 == 0 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile / wave split");
     static_assert(LDS <= 160 * 1024, "LDS budget");
 };
@@ -62,6 +70,34 @@ __device__ __forceinline__ void dma_barrier() {
     asm volatile("" ::: "memory");
 }
 
+// The 16-row groups of both operands are stored in LDS with row bits 2 and 3 exchanged, so that an accumulator's lane and
+// register indexes stand for these rows and columns: see `epilogue`.
+__device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
+
+// Four sets of R registers, each one 16- or 32-byte run of a line (8 positions): in, set (a, b) of lane l holds the run at
+// 32 a + 16 b + 8 (l / 32) of line swap23(l % 32); out, set (a, b) holds the run at 32 (l / 8 % 2) + 16 (l / 16 % 2) +
+// 8 (l / 32) of line 16 b + 8 (l / 4 % 2) + 4 a + l % 4: the 8 lanes that differ in bits 3 to 5 hold a line's 64 positions.
+template <int R>
+__device__ __forceinline__ void gather_runs(uint32_t (&u)[2][2][R]) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            // the second and fourth 16 lanes of b = 0 with the first and third of b = 1
+            const auto x = __builtin_amdgcn_permlane16_swap(u[a][0][r], u[a][1][r], false, false);
+            u[a][0][r] = x[0];
+            u[a][1][r] = x[1];
+        }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            // the upper 8 of every 16 lanes of a = 0 with the lower 8 of a = 1 (row_ror:8, two banks of four)
+            const uint32_t x = u[0][b][r], y = u[1][b][r];
+            u[0][b][r] = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
+            u[1][b][r] = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
+        }
+}
 struct GemmArgs {
     const bf16_t *A, *W;
     const float* bias;
@@ -131,7 +167,7 @@ template <typename T, int WN, int TM, int EPI, bool PLANNED>
 __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                              const float* __restrict__ bias, void* __restrict__ Cv, bf16_t* __restrict__ Vt,
                                              const Region& rg_, unsigned char* smem) {
-    constexpr int STAGE = T::STAGE, EPI_BYTES = T::EPI_BYTES, BN = 32 * T::TN * WN;
+    constexpr int STAGE = T::STAGE, BN = 32 * T::TN * WN;
     const ResidualSrc& res = g.res;
     const int64_t vt_ld = g.max_rows;
     const int N = g.N, K = g.K, hidden = g.hidden, rows = rg_.rows;
@@ -157,14 +193,15 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     // ---- DMA sources: lane i of a wavefront fetches chunk (i%8)^swz of row i/8 of its group ----
     const int dma_row = wave * 8 + (lane >> 3);
     const int dma_chunk = (lane & 7) ^ lds_swz(dma_row);
-    const unsigned lane_off = (unsigned)(dma_row * K + dma_chunk * 8) * 2u;
+    const int src_row = swap23(dma_row);                     // (the DMAs of a slice are multiples of 32 rows apart)
+    const unsigned dma_off = (unsigned)(src_row * K + dma_chunk * 8) * 2u;
     const int64_t ld_bytes = (int64_t)K * 2;
     // EPI_GELU_SPLIT: a row of A is hi | lo, both halves meet the same W, whose rows have K / 2 elements.  The halves'
     // sums are kept apart until the last addition (the bits of the small tiles, so a request's prediction does not
     // depend on how many others are in the call); 64 more accumulators, which the 128 x 128 tiles have room for.
     constexpr bool SPLIT = EPI == EPI_GELU_SPLIT;
     const int ldw = SPLIT ? K / 2 : K;
-    const unsigned lane_off_w = SPLIT ? (unsigned)(dma_row * ldw + dma_chunk * 8) * 2u : lane_off;
+    const unsigned dma_off_w = SPLIT ? (unsigned)(src_row * ldw + dma_chunk * 8) * 2u : dma_off;
     const int64_t ldw_bytes = SPLIT ? (int64_t)ldw * 2 : ld_bytes;
 
     // ---- fragment addresses: row (lane%32) of a 32-row tile, chunks 2*ks + lane/32 ----------
@@ -175,6 +212,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) koff[ks] = ((2 * ks + fhalf) ^ lds_swz(frow)) * 16;
 
+    // SWAP: the product transposed, C^T = W A^T: a lane holds one row and, in its registers, columns
     f32x16 acc[TM][T::TN];
     auto clear_acc = [&]() {
 #pragma unroll
@@ -220,14 +258,14 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     // memory pipeline's issue queue and issues no MFMA meanwhile.
     auto prefetch_a = [&](int j) {        // DMA j of the slice's A rows
         const unsigned char* ub = pf_a + pf_kt * 128 + (int64_t)j * (T::NW * 8) * ld_bytes;    // wave-uniform
-        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(ub + lane_off),
+        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(ub + dma_off),
                                          (LDS_AS void*)(smem + pf_stage * STAGE + (j * T::NW + wave) * 1024), 16, 0, 0);
     };
     auto prefetch_w = [&](int j) {        // DMA j of the slice's W rows
         int kt = pf_kt;
         if constexpr (SPLIT) kt -= pf_kt < nk / 2 ? 0 : nk / 2;
         const unsigned char* ub = pf_w + kt * 128 + (int64_t)j * (T::NW * 8) * ldw_bytes;
-        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(ub + lane_off_w),
+        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(ub + dma_off_w),
                                          (LDS_AS void*)(smem + pf_stage * STAGE + T::A_BYTES + (j * T::NW + wave) * 1024), 16, 0, 0);
     };
     auto advance_cursor = [&]() {         // after the W rows: on to the next slice
@@ -244,8 +282,9 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     // each of TM + TN rounds one fragment read for the next step, at most one DMA, and a share of this
     // step's MFMAs.  dma_tag: 0 none, 1 the slice's A rows, 2 its W rows.
     auto k_step = [&](const bf16x8* fa, const bf16x8* fb, bf16x8* na, bf16x8* nb, const unsigned char* rd_stage,
-                      int rd_ks, auto dma_tag) {
+                      int rd_ks, auto dma_tag, auto swap_tag) {
         constexpr int DMA = decltype(dma_tag)::value;
+        constexpr bool SWAP = decltype(swap_tag)::value;
         constexpr int nR = TM + T::TN, nM = TM * T::TN;
         static_assert(NDMA_A <= nR && NDMA_W <= nR, "one DMA per round");
         const unsigned char* sA = rd_stage + a_off + koff[rd_ks];
@@ -259,8 +298,8 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
             // MFMAs [r * nM / nR, (r + 1) * nM / nR) of the step, in row-major order of the wavefront's tiles
 #pragma unroll
             for (int m = r * nM / nR; m < (r + 1) * nM / nR; ++m)
-                acc[m / T::TN][m % T::TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[m / T::TN], fb[m % T::TN],
-                                                                                   acc[m / T::TN][m % T::TN], 0, 0, 0);
+                acc[m / T::TN][m % T::TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    SWAP ? fb[m % T::TN] : fa[m / T::TN], SWAP ? fa[m / T::TN] : fb[m % T::TN], acc[m / T::TN][m % T::TN], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -278,11 +317,17 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     for (int j = 0; j < NDMA_A; ++j) prefetch_a(j);
     read_frags(fa0, fb0, smem, 0);
     int stage = 0;
-    float* stg = (float*)(smem + 2 * STAGE + wave * EPI_BYTES);
     constexpr int WTN = BN / WN;
+    static_assert(WTN == 64 && T::TN == 2, "64 columns to a wavefront: one piece of the partial row sums");
+    // maps with a LayerNorm folded in: column sums of the weights and statistics of the rows
+    constexpr bool FOLD = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_BIAS_GELU;
+    constexpr bool RESIDUAL = EPI == EPI_BIAS_RESIDUAL;
+    const float* col_bias = (const float*)(smem + T::COLS);
+    const float *col_1 = col_bias + BN, *col_2 = col_bias + 2 * BN;        // column sums, or gamma and beta
+    const float2* row_stats = (const float2*)(smem + T::ROWS);
 
     for (int it = 0; it < n_my; ++it) {
-        const int m_base = row_of(tm) + wave_row, n0 = tn * BN, n_base = n0 + wn * WTN;
+        const int m0 = row_of(tm), m_base = m0 + wave_row, n0 = tn * BN, n_base = n0 + wn * WTN;
         int tm2, tn2;
         if constexpr (BANDS) {
             walk.tile(it + 1 < n_my ? it + 1 : 0, tm2, tn2);
@@ -294,270 +339,280 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
         nx_w = w_of(tn2);
         tm = tm2;
         tn = tn2;
-        auto contract = [&](int slices) {
+        // What the epilogue needs of the tile's columns and rows goes to LDS by DMA behind the tile's first barrier (every
+        // wavefront is past the last tile's epilogue) and has landed at the second one, some ten slices before it is read:
+        // read from memory there it came behind the DMAs of the next tile's slices, which the memory counter keeps in order.
+        auto fetch_params = [&]() {
+            const float* src = wave == 0 ? bias : wave == 1 ? (FOLD ? res.colsum : res.gamma) : res.beta;
+            if (wave == 0 || (wave == 1 && (FOLD || RESIDUAL)) || (wave == 2 && RESIDUAL)) {
+                if (lane < BN / 4)
+                    __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(src + n0 + 4 * lane),
+                                                     (LDS_AS void*)(smem + T::COLS + wave * BN * 4), 16, 0, 0);
+            } else if ((FOLD || RESIDUAL) && wave >= 3 && wave < 3 + (32 * T::TM * 2) / 128) {
+                // two rows a lane; a lower tile's rows end earlier
+                const int r = min((wave - 3) * 128 + 2 * lane, rg_.bm - 2);
+                __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(res.stats + m0 + r),
+                                                 (LDS_AS void*)(smem + T::ROWS + (wave - 3) * 1024), 16, 0, 0);
+            }
+        };
+        // Residual epilogue: strip s covers rows 16 (s / 2) + 4 (s % 2) + {0..3, 8..11} of the wavefront's tile; lane l handles
+        // 8 columns from 8 (l % 8) of row l / 8 of a strip.  The previous sums of the first D strips are requested a slice
+        // ahead of the epilogue, those of strip s + D before strip s is worked on.
+        constexpr int D = RESIDUAL ? 3 : 1, NS = 4 * TM;
+        auto row_in = [](int s) { return 16 * (s >> 1) + 4 * (s & 1); };
+        auto lane_row = [](int l) { return ((l >> 3) & 3) + 8 * (l >> 5); };
+        u32x4 ph[D + 1], pl[D + 1];
+        auto fetch_sums = [&](int s, int in_tile) {               // in_tile: of the lane's first element in the wavefront's tile
+            const int64_t at = (int64_t)(m_base + row_in(s)) * N + n_base;
+            ph[s % (D + 1)] = *(const u32x4*)(res.y_hi + at + in_tile);
+            pl[s % (D + 1)] = *(const u32x4*)(res.y_lo + at + in_tile);
+        };
+        auto contract = [&](int slices, auto swap_tag) {
             clear_acc();
-            for (int kt = 0; kt < slices; ++kt) {
+            auto slice = [&](int kt) {
                 unsigned char* cur = smem + stage * STAGE;
                 unsigned char* nxt = smem + (stage ^ 1) * STAGE;
                 stage ^= 1;
-                k_step(fa0, fb0, fa1, fb1, cur, 1, WDma{});       // + W half of the slice after this one
+                k_step(fa0, fb0, fa1, fb1, cur, 1, WDma{}, swap_tag);       // + W half of the slice after this one
                 advance_cursor();
-                k_step(fa1, fb1, fa0, fb0, cur, 2, NoDma{});
-                k_step(fa0, fb0, fa1, fb1, cur, 3, NoDma{});
+                k_step(fa1, fb1, fa0, fb0, cur, 2, NoDma{}, swap_tag);
+                k_step(fa0, fb0, fa1, fb1, cur, 3, NoDma{}, swap_tag);
                 dma_barrier();
+                if (kt == 0) fetch_params();
+                // (the first groups' sums have landed too: said here, where it costs nothing)
+                if constexpr (RESIDUAL)
+                    if (kt < 0) asm volatile("" : "+v"(ph[0]), "+v"(pl[0]), "+v"(ph[1]), "+v"(pl[1]), "+v"(ph[2]), "+v"(pl[2]));
                 // reads the step-0 fragments of the next slice, of this tile or of the next one (after the
                 // last slice of all: of a stage nobody needs); + A half of the slice two after this one
-                k_step(fa1, fb1, fa0, fb0, nxt, 0, ADma{});
+                k_step(fa1, fb1, fa0, fb0, nxt, 0, ADma{}, swap_tag);
+            };
+            for (int kt = 0; kt < slices - (RESIDUAL ? 1 : 0); ++kt) slice(kt);
+            if constexpr (RESIDUAL) {
+                const int off = lane_row(lane) * N + 8 * (lane & 7);
+#pragma unroll
+                for (int s = 0; s < D; ++s) fetch_sums(s, off);
+                slice(-1);
             }
         };
+        // first value column of this launch's W: after the query and key columns, or after the key columns
+        const int v_col0 = EPI == EPI_KV ? hidden : 2 * hidden;
+        const bool values = (EPI == EPI_QKV || EPI == EPI_KV) && n0 >= v_col0;
         if constexpr (SPLIT) {
             f32x16 hi[TM][T::TN];
-            contract(nk / 2);
+            contract(nk / 2, std::true_type{});
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) hi[i][j] = acc[i][j];
-            contract(nk / 2);
+            contract(nk / 2, std::true_type{});
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) acc[i][j] = hi[i][j] + acc[i][j];
+        } else if (values || RESIDUAL) {
+            contract(nk, std::false_type{});
         } else {
-            contract(nk);
+            contract(nk, std::true_type{});
         }
 
         // ---- epilogue -----------------------------------------------------------------------------
-        // Accumulator element e of tile (i, j) is C[row, col] with row = 32 i + 8 (e / 4) + 4 (lane / 32)
-        // + e % 4, col = 32 j + lane % 32: a lane holds one column.  Each wavefront transposes through
-        // its private 4 KB of LDS: it writes a strip of accumulators, reads it back with 16 bytes of
-        // consecutive output per lane, applies the epilogue there and issues 16-byte global accesses.
+        // The product is transposed: accumulator element e of tile (i, j) is C[row, col] with row = 32 i + swap23(lane % 32),
+        // col = 32 j + 16 (e / 8) + 8 (lane / 32) + e % 8, so a lane holds one row and runs of 8 columns.  Exchanges between
+        // lanes (gather_runs) then give every access whole lines of memory, 8 rows of 128 bytes, with no trip through LDS:
+        // lines written in halves (16 rows of 64 bytes) cost 90 clocks an instruction against 30, and a map's
+        // launch 850 us against 805.  248 k rows of hidden 768, staged through LDS as floats / so: query-key-value map 891 /
+        // 872 us, keys and values 620 / 570, first feed-forward map 1330 / 1284.  Value tiles are contracted
+        // the other way round: a lane holds one feature and runs of 8 rows, and the same exchanges give lines of Vt.
 
         // (a copy of the lane index that the compiler takes for new: what is derived from it is worked out here for every
         // tile, and no register holds it through the contraction)
         int el = lane;
         asm volatile("" : "+v"(el));
-        const int ecol = el & 31, ehalf = el >> 5;
+        const int line = swap23(el & 31), half = el >> 5;
+        const int out_run = 32 * ((el >> 3) & 1) + 16 * ((el >> 4) & 1) + 8 * half;   // after the exchanges
+        const int out_line = 8 * ((el >> 2) & 1) + (el & 3);                          // + 16 b + 4 a of set (a, b)
 
-        // first value column of this launch's W: after the query and key columns, or after the key columns
-        const int v_col0 = EPI == EPI_KV ? hidden : 2 * hidden;
-        if ((EPI == EPI_QKV || EPI == EPI_KV) && n0 >= v_col0) {
-            // Value columns go to Vt[feature][row].  One 32 x 32 accumulator tile at a time is staged as
-            // [32 features][32 rows]; the 16-byte chunks of a feature's rows are XOR-swizzled with the
-            // feature index so the 128-byte-strided writes of the 32 lanes spread over the banks.  Read
-            // back, a lane holds 8 consecutive rows of one feature: the folded LayerNorm is finished there.
-            const int rg = el & 3;
-            float cc[T::TN][2], dd[T::TN][2];
+        if (values) {
+            bf16_t* vrow = Vt + (int64_t)(n_base - v_col0 + out_line) * vt_ld + m_base + out_run;
+            float cc[2], dd[2];
 #pragma unroll
-            for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const int c = n_base + 32 * j + (el >> 2) + 16 * it;
-                    cc[j][it] = res.colsum[c];
-                    dd[j][it] = bias[c];
-                }
-            float2 sv[8];                            // statistics of the lane's 8 rows of block i
-            auto fetch_sv = [&](int i) {
-#pragma unroll
-                for (int r = 0; r < 8; ++r) sv[r] = res.stats[m_base + 32 * i + 8 * rg + r];
-            };
-            fetch_sv(0);
+            for (int j = 0; j < 2; ++j) {
+                cc[j] = col_1[wn * WTN + 32 * j + line];
+                dd[j] = col_bias[wn * WTN + 32 * j + line];
+            }
+            uint32_t u[2][2][2][4];                            // [j][i % 2][e / 8]: 64 rows of a feature in two blocks
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                float rs[8], nm[8];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    rs[r] = sv[r].y;
-                    nm[r] = -sv[r].x * sv[r].y;
+                for (int b = 0; b < 2; ++b) {
+                    float rs[8], nm[8];
+#pragma unroll
+                    for (int t = 0; t < 8; t += 2) {
+                        const float4 s2 = *(const float4*)(row_stats + wave_row + 32 * i + 16 * b + 8 * half + t);
+                        rs[t] = s2.y; nm[t] = -s2.x * s2.y;
+                        rs[t + 1] = s2.w; nm[t + 1] = -s2.z * s2.w;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int t = 0; t < 8; t += 2)
+                            u[j][i & 1][b][t / 2] =
+                                cvt_pk_bf16(fmaf(acc[i][j][8 * b + t], rs[t], fmaf(nm[t], cc[j], dd[j])),
+                                            fmaf(acc[i][j][8 * b + t + 1], rs[t + 1], fmaf(nm[t + 1], cc[j], dd[j])));
                 }
-                if (i + 1 < TM) fetch_sv(i + 1);
+                if ((i & 1) == 0 && i + 1 < TM) continue;
 #pragma unroll
-                for (int j = 0; j < T::TN; ++j) {
+                for (int j = 0; j < 2; ++j) {
+                    if ((i & 1) == 0) {                        // an odd block at the end: lines in halves, as they are
+                        bf16_t* f = Vt + (int64_t)(n_base - v_col0 + 32 * j + line) * vt_ld + m_base + 32 * i + 8 * half;
 #pragma unroll
-                    for (int e4 = 0; e4 < 4; ++e4) {
-                        const f32x16& a = acc[i][j];
-                        *(float4*)(stg + ecol * 32 + 4 * ((2 * e4 + ehalf) ^ (ecol & 7))) =
-                            make_float4(a[4 * e4], a[4 * e4 + 1], a[4 * e4 + 2], a[4 * e4 + 3]);
+                        for (int b = 0; b < 2; ++b)
+                            *(uint4*)(f + 16 * b) = make_uint4(u[j][0][b][0], u[j][0][b][1], u[j][0][b][2], u[j][0][b][3]);
+                        continue;
                     }
+                    gather_runs<4>(u[j]);
 #pragma unroll
-                    for (int it = 0; it < 2; ++it) {
-                        const int c = (el >> 2) + 16 * it;
-                        const float4 lo = *(const float4*)(stg + c * 32 + 4 * ((2 * rg) ^ (c & 7)));
-                        const float4 hi = *(const float4*)(stg + c * 32 + 4 * ((2 * rg + 1) ^ (c & 7)));
-                        const float a8[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                        float v[8];
+                    for (int a = 0; a < 2; ++a)
 #pragma unroll
-                        for (int r = 0; r < 8; ++r) v[r] = fmaf(a8[r], rs[r], fmaf(nm[r], cc[j][it], dd[j][it]));
-                        const uint4 o = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]),
-                                                   cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
-                        *(uint4*)(Vt + (int64_t)(n_base - v_col0 + 32 * j + c) * vt_ld + m_base + 32 * i + 8 * rg) = o;
-                    }
+                        for (int b = 0; b < 2; ++b)
+                            *(uint4*)(vrow + (int64_t)(32 * j + 16 * b + 4 * a) * vt_ld + 32 * (i - 1)) =
+                                make_uint4(u[j][a][b][0], u[j][a][b][1], u[j][a][b][2], u[j][a][b][3]);
                 }
             }
             continue;
         }
 
-        // other epilogues: strips of 8 rows x WTN columns, row-major, padded rows
-        constexpr int SW = WTN + 4;
-        static_assert(8 * SW * 4 <= EPI_BYTES && 32 * 32 * 4 <= EPI_BYTES, "epilogue staging region");
-        auto stage_strip = [&](int i, int e4) {      // rows 32 i + 8 e4 + 0..7 of the wavefront's tile
+        if constexpr (RESIDUAL) {
+            // New sums of the residual stream: acc + bias + LayerNorm(y_prev) recomputed from the previous sums and the row
+            // statistics.  Bound by vector arithmetic, which nothing overlaps (one instruction an element is 1000 clocks a
+            // tile): the product, not transposed, is brought into whole rows through LDS strip by strip, not by exchanges
+            // between lanes, and the stream's two arrays are taken apart and put together by two instructions an element.
+            // 1400 vector instructions a wavefront and tile, 2400 with sums of two bf16 values, exchanges and guarded stores:
+            // output projection of 248 k rows of hidden 768 504 -> 488 us, of 1.8 M rows of hidden 1024 5012 -> 4910 (what
+            // is left is 512 KB in and out a tile, by all units at about the same time), second feed-forward maps even.
+            const int cg = el & 7, in_tile = lane_row(el) * N + 8 * cg;
+            float gm[8], sh[8];
 #pragma unroll
-            for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) stg[(4 * ehalf + t) * SW + 32 * j + ecol] = acc[i][j][4 * e4 + t];
-        };
-
-        if (EPI == EPI_BIAS_RESIDUAL) {
-            // New sums of the residual stream: v = acc + bias + LayerNorm(y_prev) recomputed from the
-            // previous sums (kept as two bf16, hi + lo) and the row statistics, so the stream is never
-            // rounded to 8 bits.  v goes out as hi + lo again: hi is what the next map reads.  A lane
-            // handles 8 consecutive columns (16-byte accesses), 8 lanes a row of the strip.
-            constexpr int LPR = WTN / 8, RPI = 64 / LPR, NIT = 8 / RPI, NS = 4 * TM;
-            static_assert(LPR == 8 && NIT == 1, "8 lanes per 64-column row piece");
-            const int cg = el % LPR, r_in = el / LPR;
-            const int col = n_base + 8 * cg;
-            float bv[8], rg[8], rb[8];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float4 b4 = *(const float4*)(bias + col + 4 * h);
-                const float4 g4 = *(const float4*)(res.gamma + col + 4 * h);
-                const float4 e4 = *(const float4*)(res.beta + col + 4 * h);
-                bv[4 * h] = b4.x; bv[4 * h + 1] = b4.y; bv[4 * h + 2] = b4.z; bv[4 * h + 3] = b4.w;
-                rg[4 * h] = g4.x; rg[4 * h + 1] = g4.y; rg[4 * h + 2] = g4.z; rg[4 * h + 3] = g4.w;
-                rb[4 * h] = e4.x; rb[4 * h + 1] = e4.y; rb[4 * h + 2] = e4.z; rb[4 * h + 3] = e4.w;
+            for (int t = 0; t < 8; t += 4) {
+                const int c = wn * WTN + 8 * cg + t;
+                const float4 b4 = *(const float4*)(col_bias + c), g4 = *(const float4*)(col_1 + c), e4 = *(const float4*)(col_2 + c);
+                gm[t] = g4.x; gm[t + 1] = g4.y; gm[t + 2] = g4.z; gm[t + 3] = g4.w;
+                sh[t] = e4.x + b4.x; sh[t + 1] = e4.y + b4.y; sh[t + 2] = e4.z + b4.z; sh[t + 3] = e4.w + b4.w;
             }
-            bf16_t* Cl = (bf16_t*)Cv;
-            const int piece = n_base >> 6, pieces = N >> 6;
-            // one row of a strip: combine, store hi and lo, and (where asked for) leave the 64-column
-            // piece's sum and sum of squares, added up over the row's 8 lanes
-            auto finish_row = [&](int r, const uint4& h, const uint4& l, const float2& st, int64_t row, bool live) {
-                const float4 a0 = *(const float4*)(stg + r * SW + 8 * cg);
-                const float4 a1 = *(const float4*)(stg + r * SW + 8 * cg + 4);
-                const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                const uint32_t hw[4] = {h.x, h.y, h.z, h.w}, lw[4] = {l.x, l.y, l.z, l.w};
-                float o[8];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float y0 = __uint_as_float(hw[t] << 16) + __uint_as_float(lw[t] << 16);
-                    const float y1 = __uint_as_float(hw[t] & 0xffff0000u) + __uint_as_float(lw[t] & 0xffff0000u);
-                    o[2 * t] = a[2 * t] + bv[2 * t] + ((y0 - st.x) * st.y * rg[2 * t] + rb[2 * t]);
-                    o[2 * t + 1] = a[2 * t + 1] + bv[2 * t + 1] + ((y1 - st.x) * st.y * rg[2 * t + 1] + rb[2 * t + 1]);
-                }
-                float sm = 0.f, sq = 0.f;
-                if (res.pstats) {
-                    sm = ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
-                    sq = (fmaf(o[0], o[0], o[1] * o[1]) + fmaf(o[2], o[2], o[3] * o[3])) +
-                         (fmaf(o[4], o[4], o[5] * o[5]) + fmaf(o[6], o[6], o[7] * o[7]));
-                    sm = row8_sum(sm);
-                    sq = row8_sum(sq);
-                }
-                if (live) {
-                    uint32_t ho[4], lo[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        ho[t] = cvt_pk_bf16(o[2 * t], o[2 * t + 1]);
-                        lo[t] = cvt_pk_bf16(o[2 * t] - __uint_as_float(ho[t] << 16),
-                                            o[2 * t + 1] - __uint_as_float(ho[t] & 0xffff0000u));
-                    }
-                    *(uint4*)(res.x_out + row * N + col) = make_uint4(ho[0], ho[1], ho[2], ho[3]);
-                    *(uint4*)(Cl + row * N + col) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-                    if (res.pstats && cg == 0) res.pstats[row * pieces + piece] = make_float2(sm, sq);
-                }
+            // Stores by buffer instructions whose range ends with the last live row: no lane is masked and no branch taken,
+            // so the compiler counts them and a strip waits for its own sums only (guarded by the row, every strip waited
+            // for the stores before it).
+            const int pieces = N >> 6;
+            const int live = __builtin_amdgcn_readfirstlane(max(0, min(rows - m_base, 32 * TM)));
+            auto range = [&](void* base, int ld, int last) {
+                const uint64_t a = (uint64_t)base;            // (wave-uniform, which the compiler has to be told)
+                const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+                return __builtin_amdgcn_make_buffer_rsrc((void*)u, 0, live > 0 ? (live - 1) * ld + last : 0, 0x27000);
             };
-            // The previous sums and statistics of strip s + D are requested before strip s is worked
-            // on, so the strips do not each wait out a trip to memory.  Strip s covers rows
-            // 8 s .. 8 s + 7 of the wavefront's tile.
-            constexpr int D = 3;
-            const int64_t row0 = m_base + r_in;
-            const bf16_t* yh = res.y_hi + row0 * N + col;
-            const bf16_t* yl = res.y_lo + row0 * N + col;
-            const float2* sb = res.stats + row0;
-            uint4 ph[D + 1], pl[D + 1];
-            float2 st[D + 1];
-            auto fetch = [&](int s) {
-                ph[s % (D + 1)] = *(const uint4*)(yh + (int64_t)(8 * s) * N);
-                pl[s % (D + 1)] = *(const uint4*)(yl + (int64_t)(8 * s) * N);
-                st[s % (D + 1)] = sb[8 * s];
-            };
-#pragma unroll
-            for (int s = 0; s < D; ++s) fetch(s);
+            const int64_t at0 = (int64_t)m_base * N + n_base;
+            const auto hi_out = range(res.x_out + at0, 2 * N, 128), lo_out = range((bf16_t*)Cv + at0, 2 * N, 128);
+            const auto ps_out = range(res.pstats + (int64_t)m_base * pieces + (n_base >> 6), 8 * pieces, 8);
+            const int ps_off = cg == 0 ? lane_row(el) * pieces * 8 : INT_MIN;          // one lane a row, the others out of range
+            float* strip = (float*)(smem + T::STRIPS) + wave * 8 * T::STRIP_LD;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                if (s + D < NS) fetch(s + D);
-                stage_strip(s / 4, s % 4);
-                const int64_t row = row0 + 8 * s;
-                finish_row(r_in, ph[s % (D + 1)], pl[s % (D + 1)], st[s % (D + 1)], row, row < rows);
+                // The next slice's DMAs, while nothing is behind them: with one on its way the compiler takes every wait for
+                // a load as a wait for all memory instructions.
+                if (s == 0) __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0)
+                if (s + D < NS) fetch_sums(s + D, in_tile);
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) strip[(4 * half + t) * T::STRIP_LD + 32 * j + line] = acc[s >> 2][j][4 * (s & 3) + t];
+                const float2 st = row_stats[wave_row + row_in(s) + lane_row(el)];
+                const float4 a0 = *(const float4*)(strip + (el >> 3) * T::STRIP_LD + 8 * cg);
+                const float4 a1 = *(const float4*)(strip + (el >> 3) * T::STRIP_LD + 8 * cg + 4);
+                const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                float o[8];
+                u32x4 ho, lo;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float2 y = stream_join2(ph[s % (D + 1)][t], pl[s % (D + 1)][t]);
+                    o[2 * t] = residual_sum(a[2 * t], y.x, st, gm[2 * t], sh[2 * t]);
+                    o[2 * t + 1] = residual_sum(a[2 * t + 1], y.y, st, gm[2 * t + 1], sh[2 * t + 1]);
+                    uint32_t h, l;
+                    stream_split2(o[2 * t], o[2 * t + 1], h, l);
+                    ho[t] = h;
+                    lo[t] = l;
+                }
+                // the 64-column piece's sum and sum of squares
+                const float sm = row8_sum(((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7])));
+                const float sq = row8_sum((fmaf(o[0], o[0], o[1] * o[1]) + fmaf(o[2], o[2], o[3] * o[3])) +
+                                          (fmaf(o[4], o[4], o[5] * o[5]) + fmaf(o[6], o[6], o[7] * o[7])));
+                const u32x2 ps = {__float_as_uint(sm), __float_as_uint(sq)};
+                // (offsets in the vector operand: the scalar one takes no part in the range check)
+                __builtin_amdgcn_raw_buffer_store_b128(ho, hi_out, 2 * (in_tile + row_in(s) * N), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(lo, lo_out, 2 * (in_tile + row_in(s) * N), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(ps, ps_out, ps_off + 8 * row_in(s) * pieces, 0, 0);
             }
             continue;
         }
 
         {
-            // bf16 out (plain, GELU, or the query / key columns of the QKV projection): 8 columns per lane
-            constexpr int LPR = WTN / 8, RPI = 64 / LPR, NIT = 8 / RPI;
-            const int cg = el % LPR, r_in = el / LPR;
-            const int col = n_base + 8 * cg;
-            const float4 b0 = *(const float4*)(bias + col), b1 = *(const float4*)(bias + col + 4);
-            // maps with a LayerNorm folded in: column sums, and the statistics of every row this lane
-            // will touch, requested before the first strip
-            constexpr bool FOLD = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_BIAS_GELU;
-            float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
-            float2 rst[FOLD ? TM * 4 * NIT : 1];
-            if (FOLD) {
-                c0 = *(const float4*)(res.colsum + col);
-                c1 = *(const float4*)(res.colsum + col + 4);
-#pragma unroll
-                for (int s = 0; s < TM * 4; ++s)
-#pragma unroll
-                    for (int it = 0; it < NIT; ++it) {
-                        const int64_t row = m_base + 8 * s + r_in + RPI * it;
-                        rst[s * NIT + it] = res.stats[row];
-                    }
-            }
+            // bf16 out (plain, GELU, or the query / key columns of the QKV projection): the left 32 columns of all rows are
+            // finished first, then block by block the right ones, the exchanges and the stores
             const int64_t ldc = (EPI == EPI_QKV || EPI == EPI_KV) ? 2 * (int64_t)hidden
                                 : SPLIT ? 2 * (int64_t)N : (int64_t)N;
-            const int c_col = col + (EPI == EPI_KV ? hidden : 0);   // key columns sit after the query columns
-            bf16_t* C = (bf16_t*)Cv;
+            const int c_col = n_base + out_run + (EPI == EPI_KV ? hidden : 0);   // key columns sit after the query columns
+            bf16_t* C = (bf16_t*)Cv + (int64_t)(m_base + out_line) * ldc + c_col;
+            float rs[TM], nm[TM];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i) {
+                const float2 st = FOLD ? row_stats[wave_row + 32 * i + line] : make_float2(0.f, 0.f);
+                rs[i] = st.y; nm[i] = -st.x * st.y;
+            }
+            auto store = [&](uint32_t (&u)[2][2][4], int i, int64_t off) {
+                gather_runs<4>(u);
 #pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    stage_strip(i, e4);
+                for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int it = 0; it < NIT; ++it) {
-                        const int r = r_in + RPI * it;
-                        const int64_t row = m_base + 32 * i + 8 * e4 + r;
-                        const float4 lo = *(const float4*)(stg + r * SW + 8 * cg);
-                        const float4 hi = *(const float4*)(stg + r * SW + 8 * cg + 4);
-                        float v[8];
-                        if (FOLD) {
-                            const float2 st = rst[(4 * i + e4) * NIT + it];
-                            const float nm = -st.x * st.y;
-                            v[0] = fmaf(lo.x, st.y, fmaf(nm, c0.x, b0.x)); v[1] = fmaf(lo.y, st.y, fmaf(nm, c0.y, b0.y));
-                            v[2] = fmaf(lo.z, st.y, fmaf(nm, c0.z, b0.z)); v[3] = fmaf(lo.w, st.y, fmaf(nm, c0.w, b0.w));
-                            v[4] = fmaf(hi.x, st.y, fmaf(nm, c1.x, b1.x)); v[5] = fmaf(hi.y, st.y, fmaf(nm, c1.y, b1.y));
-                            v[6] = fmaf(hi.z, st.y, fmaf(nm, c1.z, b1.z)); v[7] = fmaf(hi.w, st.y, fmaf(nm, c1.w, b1.w));
-                        } else {
-                            v[0] = lo.x + b0.x; v[1] = lo.y + b0.y; v[2] = lo.z + b0.z; v[3] = lo.w + b0.w;
-                            v[4] = hi.x + b1.x; v[5] = hi.y + b1.y; v[6] = hi.z + b1.z; v[7] = hi.w + b1.w;
-                        }
-                        if (EPI == EPI_BIAS_GELU || SPLIT) {
+                    for (int b = 0; b < 2; ++b)
+                        *(uint4*)(C + (int64_t)(32 * i + 16 * b + 4 * a) * ldc + off) =
+                            make_uint4(u[a][b][0], u[a][b][1], u[a][b][2], u[a][b][3]);
+            };
+            uint32_t u[TM][2][2][4], l[SPLIT ? TM : 1][2][2][4];
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
-                        }
-                        const uint4 o = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]),
-                                                   cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
-                        *(uint4*)(C + row * ldc + c_col) = o;
-                        if constexpr (SPLIT) {
-                            // second half of the row: what the first rounding lost, as bf16 again
-                            const uint32_t h[4] = {o.x, o.y, o.z, o.w};
-                            uint32_t l[4];
+            for (int j = 0; j < 2; ++j) {
+                float cc[16], dd[16];                          // of the lane's columns 16 (e / 8) + 8 half + e % 8
 #pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                l[t] = cvt_pk_bf16(v[2 * t] - __uint_as_float(h[t] << 16),
-                                                   v[2 * t + 1] - __uint_as_float(h[t] & 0xffff0000u));
-                            *(uint4*)(C + row * ldc + N + c_col) = make_uint4(l[0], l[1], l[2], l[3]);
-                        }
+                for (int e = 0; e < 16; e += 4) {
+                    const int c = wn * WTN + 32 * j + 16 * (e >> 3) + 8 * half + (e & 7);
+                    const float4 d4 = *(const float4*)(col_bias + c);
+                    dd[e] = d4.x; dd[e + 1] = d4.y; dd[e + 2] = d4.z; dd[e + 3] = d4.w;
+                    if (FOLD) {
+                        const float4 c4 = *(const float4*)(col_1 + c);
+                        cc[e] = c4.x; cc[e + 1] = c4.y; cc[e + 2] = c4.z; cc[e + 3] = c4.w;
                     }
                 }
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                    for (int e = 0; e < 16; e += 2) {
+                        float v[2];
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            const float a = acc[i][j][e + t];
+                            v[t] = FOLD ? fmaf(a, rs[i], fmaf(nm[i], cc[e + t], dd[e + t])) : a + dd[e + t];
+                            if (EPI == EPI_BIAS_GELU || SPLIT) v[t] = gelu_erf(v[t]);
+                        }
+                        const uint32_t h = cvt_pk_bf16(v[0], v[1]);
+                        u[i][j][e >> 3][(e & 7) >> 1] = h;
+                        // second half of the row: what the first rounding lost, as bf16 again
+                        if constexpr (SPLIT)
+                            l[i][j][e >> 3][(e & 7) >> 1] =
+                                cvt_pk_bf16(v[0] - __uint_as_float(h << 16), v[1] - __uint_as_float(h & 0xffff0000u));
+                    }
+                    if (j == 0) continue;
+                    store(u[i], i, 0);
+                    if constexpr (SPLIT) store(l[i], i, N);
+                }
+            }
         }
     }
     // parked DMAs may still be in flight: they must land before the workgroup gives up its LDS
@@ -570,7 +625,7 @@ template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
                                                                  const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk) {
     using T = Tile<BM, BN, WM, WN>;
-    __shared__ __align__(1024) unsigned char smem[T::LDS];
+    __shared__ __align__(1024) unsigned char smem[EPI == EPI_BIAS_RESIDUAL ? T::LDS : T::STRIPS];
     // clock probe (profiling only): core cycles and constant-rate ticks over this workgroup's life
     const int64_t clk_c0 = clk ? (int64_t)clock64() : 0, clk_w0 = clk ? (int64_t)wall_clock64() : 0;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

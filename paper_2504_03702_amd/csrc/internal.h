@@ -85,7 +85,7 @@ struct Workspace {
     float *head_sum;             // [B][32] the sums of their rounds of 64 hidden units
     void *x, *qkv, *vt, *att, *y, *x1, *g;
     // bf16 path: the residual stream is kept as the pre-LayerNorm sums of the last two sublayers,
-    // each sum as two bf16 values hi + lo (16 significant bits), plus each row's (mean, 1/std); its
+    // each sum a float in two 16-bit halves hi and lo (device_util.h, stream_join), plus each row's (mean, 1/std); its
     // LayerNorm is recomputed wherever it is needed.  The hi parts are x (sums entering a layer) and x1
     // (sums after the attention sublayer): exactly the operands of the maps the LayerNorms are folded into.
     bf16_t *la, *lb;             // lo parts belonging to x and x1
@@ -120,7 +120,7 @@ enum GemmEpilogue {
 };
 // The residual stream entering a sublayer: LayerNorm(y) with the row statistics already known.
 struct ResidualSrc {
-    const bf16_t* y_hi;      // [rows][hidden] pre-LayerNorm sums, value = hi + lo
+    const bf16_t* y_hi;      // [rows][hidden] pre-LayerNorm sums, value = stream_join(hi, lo)
     const bf16_t* y_lo;
     const float2* stats;     // [rows] (mean, 1 / sqrt(var + eps))
     const float* gamma;

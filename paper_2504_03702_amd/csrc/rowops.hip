@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
     if (r < 0 || p >= S) {
         for (int i = lane; i < H; i += 64) {
             store_elem<T>(out, i, 0.f);
-            if (yrow) yrow[i] = 0;
+            if (yrow) yrow[i] = (bf16_t)PS_STREAM_ZERO_LO;
         }
         if (yrow && lane == 0) stats_out[row] = make_float2(0.f, 0.f);
         return;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
             }
             for (int i = lane; i < H; i += 64) {
                 store_elem<T>(out, i, 0.f);
-                if (yrow) yrow[i] = 0;
+                if (yrow) yrow[i] = (bf16_t)PS_STREAM_ZERO_LO;
             }
             if (yrow && lane == 0) stats_out[row] = make_float2(0.f, 0.f);
             return;
@@ -245,16 +245,16 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
             }
         }
         const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)H + eps);
-        // the sums as hi + lo; hi, not normalised, is the operand of the first QKV map, which has the
+        // the sums as hi and lo (stream_split2); hi, not normalised, is the operand of the first QKV map, which has the
         // embedding LayerNorm folded into its weights and finishes it from the row statistics
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             if (c < nch) {
-                const uint2 hi = make_uint2(pack_bf16x2(e[c].x, e[c].y), pack_bf16x2(e[c].z, e[c].w));
+                uint2 hi, lo;
+                stream_split2(e[c].x, e[c].y, hi.x, lo.x);
+                stream_split2(e[c].z, e[c].w, hi.y, lo.y);
                 ((uint2*)out)[lane + 64 * c] = hi;
-                ((uint2*)yrow)[lane + 64 * c] =
-                    make_uint2(pack_bf16x2(e[c].x - __uint_as_float(hi.x << 16), e[c].y - __uint_as_float(hi.x & 0xffff0000u)),
-                               pack_bf16x2(e[c].z - __uint_as_float(hi.y << 16), e[c].w - __uint_as_float(hi.y & 0xffff0000u)));
+                ((uint2*)yrow)[lane + 64 * c] = lo;
             }
         }
         if (lane == 0) stats_out[row] = make_float2(mean, rstd);
@@ -350,8 +350,8 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
         const bf16_t* hi = (const bf16_t*)x + crow * H;
         const bf16_t* lo = y_lo + crow * H;
         const int i0 = threadIdx.x, i1 = threadIdx.x + kHeadWaves * 64;
-        const float v0 = i0 < H ? bf16_to_f32(hi[i0]) + bf16_to_f32(lo[i0]) : 0.f;
-        const float v1 = i1 < H ? bf16_to_f32(hi[i1]) + bf16_to_f32(lo[i1]) : 0.f;
+        const float v0 = i0 < H ? stream_join(hi[i0], lo[i0]) : 0.f;
+        const float v1 = i1 < H ? stream_join(hi[i1], lo[i1]) : 0.f;
         const float mean = head_block_sum(v0 + v1, s_c + H) / (float)H;
         const float d0 = i0 < H ? v0 - mean : 0.f, d1 = i1 < H ? v1 - mean : 0.f;
         const float rstd = 1.0f / sqrtf(head_block_sum(fmaf(d0, d0, d1 * d1), s_c + H) / (float)H + eps);

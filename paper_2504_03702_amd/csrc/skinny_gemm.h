@@ -129,7 +129,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int64_t at = srow[e] * N + n0 + 16 * g + frow;
-                    yprev[e][g] = bf16_to_f32(res.y_hi[at]) + bf16_to_f32(res.y_lo[at]);
+                    yprev[e][g] = stream_join(res.y_hi[at], res.y_lo[at]);
                 }
             }
         }
@@ -214,10 +214,9 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const float4 ga = gv[u][2 * h + (t >> 1)], be = bb[u][2 * h + (t >> 1)];
-                        const float x0 = ln_apply(__uint_as_float(yh.w[t] << 16), __uint_as_float(yl.w[t] << 16), ast,
-                                                  (t & 1) ? ga.z : ga.x, (t & 1) ? be.z : be.x);
-                        const float x1 = ln_apply(__uint_as_float(yh.w[t] & 0xffff0000u), __uint_as_float(yl.w[t] & 0xffff0000u),
-                                                  ast, (t & 1) ? ga.w : ga.y, (t & 1) ? be.w : be.y);
+                        const float2 y = stream_join2(yh.w[t], yl.w[t]);
+                        const float x0 = ln_apply(y.x, ast, (t & 1) ? ga.z : ga.x, (t & 1) ? be.z : be.x);
+                        const float x1 = ln_apply(y.y, ast, (t & 1) ? ga.w : ga.y, (t & 1) ? be.w : be.y);
                         const uint32_t o = pack_bf16x2(x0, x1);
                         yh.w[t] = o;
                         yl.w[t] = pack_bf16x2(x0 - __uint_as_float(o << 16), x1 - __uint_as_float(o & 0xffff0000u));
@@ -286,13 +285,13 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int c = n0 + 16 * g + frow;
-                const float o = acc[g][e] + bv[g] + ((yprev[e][g] - st[e].x) * st[e].y * gm[g] + bt[g]);
+                const float o = residual_sum(acc[g][e], yprev[e][g], st[e], gm[g], bt[g] + bv[g]);
                 sm += o;
                 sq = fmaf(o, o, sq);
                 if (live[e]) {
-                    const bf16_t hi = f32_to_bf16(o);
-                    res.x_out[row * N + c] = hi;
-                    Cl[row * N + c] = f32_to_bf16(o - bf16_to_f32(hi));
+                    const uint32_t w = __float_as_uint(o) + 0x8000u;          // see stream_split2
+                    res.x_out[row * N + c] = (bf16_t)(w >> 16);
+                    Cl[row * N + c] = (bf16_t)w;
                 }
             }
             if (res.pstats) {

@@ -276,10 +276,9 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
                 const uint32_t hw[4] = {yh[pc][it].x, yh[pc][it].y, yh[pc][it].z, yh[pc][it].w}, lw[4] = {yl[pc][it].x, yl[pc][it].y, yl[pc][it].z, yl[pc][it].w};
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const float y0 = __uint_as_float(hw[t] << 16) + __uint_as_float(lw[t] << 16);
-                    const float y1 = __uint_as_float(hw[t] & 0xffff0000u) + __uint_as_float(lw[t] & 0xffff0000u);
-                    v[2 * t] = a[2 * t] + bv[2 * t] + ((y0 - st[it].x) * st[it].y * g8[2 * t] + b8[2 * t]);
-                    v[2 * t + 1] = a[2 * t + 1] + bv[2 * t + 1] + ((y1 - st[it].x) * st[it].y * g8[2 * t + 1] + b8[2 * t + 1]);
+                    const float2 y = stream_join2(hw[t], lw[t]);
+                    v[2 * t] = residual_sum(a[2 * t], y.x, st[it], g8[2 * t], b8[2 * t] + bv[2 * t]);
+                    v[2 * t + 1] = residual_sum(a[2 * t + 1], y.y, st[it], g8[2 * t + 1], b8[2 * t + 1] + bv[2 * t + 1]);
                 }
                 float sm = 0.f, sq = 0.f;
                 if (res.pstats) {
@@ -292,10 +291,7 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
                 if (live[it]) {
                     uint32_t ho[4], lo[4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        ho[t] = cvt_pk_bf16(v[2 * t], v[2 * t + 1]);
-                        lo[t] = cvt_pk_bf16(v[2 * t] - __uint_as_float(ho[t] << 16), v[2 * t + 1] - __uint_as_float(ho[t] & 0xffff0000u));
-                    }
+                    for (int t = 0; t < 4; ++t) stream_split2(v[2 * t], v[2 * t + 1], ho[t], lo[t]);
                     *(uint4*)(res.x_out + row[it] * N + col) = make_uint4(ho[0], ho[1], ho[2], ho[3]);
                     *(uint4*)((bf16_t*)p.C + row[it] * N + col) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
                     if (res.pstats && cg == 0) res.pstats[row[it] * (N >> 6) + (n0 >> 6) + pc] = make_float2(sm, sq);

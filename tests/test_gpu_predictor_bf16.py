@@ -5,6 +5,7 @@ import os
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import predictor as op
 from paper_2504_03702_amd import binding as ps
@@ -302,3 +303,27 @@ def test_tiles_up_to_the_end_of_the_buffers(tmp_models, rows):
     got, tokens, flags, _ = run_predict(model, batch)
     assert flags == 0 and np.isfinite(got).all()
     chunks_bit_equal(model, batch, got, tokens, chunk=20)
+
+
+@pytest.mark.parametrize("n,length", [(3, 61), (24, 203), (96, 301)])
+def test_workspace_of_nans(tmp_models, n, length):
+    """Rows behind the last request's are read by its last key tile with weight zero: they are written by every map that
+    has to (and by none that must not), so a workspace full of NaNs gives the bits of a zeroed one, in the launches of a
+    few requests, in 128-row and in 256-row tiles."""
+    print(f"predict workspace of NaNs n={n}", flush=True)
+    cfg = dataclasses.replace(SMALL, ffn=3072)
+    model, _ = make(tmp_models, "tile_heights.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(n)
+    lengths = np.full(n, length, np.int32)
+    ids = torch.from_numpy(rng.integers(0, cfg.vocab, n * length).astype(np.int32)).cuda()
+    offs = torch.arange(n + 1, dtype=torch.int32, device="cuda") * length
+    out = []
+    for fill in (0x00, 0xFF):
+        pred_f, pred_t = torch.zeros(n, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+        ws = ps.alloc_workspace(ps.ps_workspace_bytes(model, ids.numel(), n), "cuda:0")
+        ws.fill_(fill)
+        st = ps.new_status("cuda:0")
+        ps.ps_predict_load(model, ids, offs, None, pred_f, pred_t, ws, st)
+        assert ps.ps_status_read(st)[0] == 0
+        out.append(pred_f.cpu().numpy())
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
