@@ -30,6 +30,7 @@ Workspace plan_workspace(const ps_model_info& info, int64_t n_tokens, int32_t n_
     ws.seq_len = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.row_start = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.qtile_start = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
+    ws.qtiles = info.dtype == 1 ? (int4*)take(sizeof(int4) * (size_t)ws.max_qtiles) : nullptr;
     ws.bad_req = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.head_done = (int32_t*)take(sizeof(int32_t) * (size_t)(n_req + 1));
     ws.head_sum = (float*)take(sizeof(float) * 32 * (size_t)(n_req < 256 ? n_req + 1 : 256));   // (several workgroups a request: at most 128)

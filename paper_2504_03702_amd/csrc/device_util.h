@@ -150,3 +150,30 @@ __device__ __forceinline__ float row8_sum(float v) {
     v = dpp_add<0x4E>(v);      // quad_perm [2, 3, 0, 1]
     return dpp_add<0x141>(v);  // row_half_mirror: lane i of each group of 8 takes lane 7 - i
 }
+
+// Whole lines out of an accumulator tile.  Four sets of R registers, each a run of 8 positions of a line of 64: in, set (a, b)
+// of lane l holds the run at 32 a + 16 b + 8 (l / 32) of the line that belongs to l % 32; out, it holds the run at
+// 32 (l / 8 % 2) + 16 (l / 16 % 2) + 8 (l / 32) of the line that belongs to l % 32 with bit 3 a and bit 4 b: the 8 lanes that
+// differ in bits 3 to 5 hold a line, and an access by 16 bytes a lane covers 8 of them.  A store of 16-byte pieces of 32 lines,
+// or of halves of 16, keeps the memory pipeline busy several times as long.
+template <int R>
+__device__ __forceinline__ void gather_runs(uint32_t (&u)[2][2][R]) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            // the second and fourth 16 lanes of b = 0 with the first and third of b = 1
+            const auto x = __builtin_amdgcn_permlane16_swap(u[a][0][r], u[a][1][r], false, false);
+            u[a][0][r] = x[0];
+            u[a][1][r] = x[1];
+        }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            // the upper 8 of every 16 lanes of a = 0 with the lower 8 of a = 1 (row_ror:8, two banks of four)
+            const uint32_t x = u[0][b][r], y = u[1][b][r];
+            u[0][b][r] = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
+            u[1][b][r] = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
+        }
+}

@@ -184,7 +184,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 }
             }
         }
-        PS_TIMED(PS_FAM_ATTENTION, launch_attention_bf16(m, n_req, ws, last, s));
+        PS_TIMED(PS_FAM_ATTENTION, launch_attention_bf16(m, ws, last, s));
         // Output projection of all rows, and again for each request's first row from the hi | lo pairs the attention
         // kernel left in cls_a.  The feed-forward block again for those rows, the ones the head reads, with its input and
         // its GELU output carried as two bf16 values per element: bf16

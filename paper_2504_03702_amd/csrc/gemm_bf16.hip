@@ -74,30 +74,6 @@ __device__ __forceinline__ void dma_barrier() {
 // register indexes stand for these rows and columns: see `epilogue`.
 __device__ __forceinline__ int swap23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
-// Four sets of R registers, each one 16- or 32-byte run of a line (8 positions): in, set (a, b) of lane l holds the run at
-// 32 a + 16 b + 8 (l / 32) of line swap23(l % 32); out, set (a, b) holds the run at 32 (l / 8 % 2) + 16 (l / 16 % 2) +
-// 8 (l / 32) of line 16 b + 8 (l / 4 % 2) + 4 a + l % 4: the 8 lanes that differ in bits 3 to 5 hold a line's 64 positions.
-template <int R>
-__device__ __forceinline__ void gather_runs(uint32_t (&u)[2][2][R]) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            // the second and fourth 16 lanes of b = 0 with the first and third of b = 1
-            const auto x = __builtin_amdgcn_permlane16_swap(u[a][0][r], u[a][1][r], false, false);
-            u[a][0][r] = x[0];
-            u[a][1][r] = x[1];
-        }
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            // the upper 8 of every 16 lanes of a = 0 with the lower 8 of a = 1 (row_ror:8, two banks of four)
-            const uint32_t x = u[0][b][r], y = u[1][b][r];
-            u[0][b][r] = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
-            u[1][b][r] = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
-        }
-}
 struct GemmArgs {
     const bf16_t *A, *W;
     const float* bias;

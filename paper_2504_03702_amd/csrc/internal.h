@@ -79,7 +79,8 @@ struct Workspace {
     BatchMeta* meta;
     int32_t *seq_len;            // [B]   rows of request r (text + learnable prompts), 0 if faulty
     int32_t *row_start;          // [B+1] first activation row of request r
-    int32_t *qtile_start;        // [B+1] first attention query tile of request r
+    int32_t *qtile_start;        // [B]   first attention query tile of request r (longest requests first in calls of many)
+    int4 *qtiles;                // bf16 path: [query tiles] {first row and rows of the tile's request, its first query, request}
     int32_t *bad_req;            // [B]   set when a request's text holds an invalid token id
     int32_t *head_done;          // [B]   workgroups of the head that have left their sum
     float *head_sum;             // [B][32] the sums of their rounds of 64 hidden units
@@ -189,7 +190,7 @@ void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyAr
 void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* x, bf16_t* out, hipStream_t s);
 // first_rows_only: compute (at least) the first query row of every request and nothing beyond its
 // first 32 rows; the rest of the output buffer keeps its old contents.
-void launch_attention_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, bool first_rows_only, hipStream_t s);
+void launch_attention_bf16(const ps_model* m, const Workspace& ws, bool first_rows_only, hipStream_t s);
 // Brackets the launches made during its lifetime with two events when profiling is on.
 struct ProfScope {
     const ps_model* m;

@@ -47,13 +47,15 @@ __device__ GemmPlan plan_gemm(int rows, int n) {
 __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ offsets,
                                                     const int32_t* __restrict__ lengths, int n_req,
                                                     int n_soft, int max_pos, long long n_tokens,
-                                                    long long row_capacity, int4 plan_cols, BatchMeta* meta,
+                                                    long long row_capacity, int4 plan_cols, int sort_tiles, BatchMeta* meta,
                                                     int32_t* seq_len, int32_t* row_start,
                                                     int32_t* qtile_start, int32_t* bad_req,
                                                     int32_t* head_done, ps_status* st) {
     __shared__ long long s_rows[16], s_tiles[16];     // totals of the wavefronts
     __shared__ long long s_cut_rows, s_cut_tiles;     // rows / query tiles in front of the first request that does not fit
+    __shared__ int s_class[64];                       // query tiles of the requests of one length (in key tiles)
     const int tid = threadIdx.x;
+    if (tid < 64) s_class[tid] = 0;
     const int per = (n_req + 1023) / 1024;
     const int r0 = min(tid * per, n_req);
     const int r1 = min(r0 + per, n_req);
@@ -127,9 +129,30 @@ __global__ __launch_bounds__(1024) void prep_kernel(const int32_t* __restrict__ 
             qtile_start[r] = (int32_t)cut_tiles;
         }
     }
+    if (sort_tiles) {
+        // Query tiles of the longest requests first: a tile takes as long as its request has keys, and the last ones to
+        // start are what the attention kernel ends with.  Requests of one length in any order (no result depends on it).
+        auto length_class = [](int S) { return 63 - min((S + 63) / 64, 63); };
+        for (int r = r0; r < r1; ++r)
+            if (seq_len[r] > 0) atomicAdd(&s_class[length_class(seq_len[r])], (seq_len[r] + PS_ATT_BQ - 1) / PS_ATT_BQ);
+        __syncthreads();
+        if (tid < 64) {
+            const int own = s_class[tid];
+            int incl = own;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int a = __shfl_up(incl, o, 64);
+                if (tid >= o) incl += a;
+            }
+            s_class[tid] = incl - own;
+        }
+        __syncthreads();
+        for (int r = r0; r < r1; ++r)
+            if (seq_len[r] > 0)
+                qtile_start[r] = atomicAdd(&s_class[length_class(seq_len[r])], (seq_len[r] + PS_ATT_BQ - 1) / PS_ATT_BQ);
+    }
     if (tid == 1023) {
         row_start[n_req] = (int32_t)cut_rows;
-        qtile_start[n_req] = (int32_t)cut_tiles;
         meta->total_rows = (int32_t)cut_rows;
         meta->total_qtiles = (int32_t)cut_tiles;
         meta->n_req = n_req;
@@ -169,6 +192,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
                                                     const int32_t* __restrict__ row_start,
                                                     int32_t* bad_req, T* __restrict__ x,
                                                     bf16_t* __restrict__ lo_out, float2* __restrict__ stats_out,
+                                                    const int32_t* __restrict__ qtile_start, int4* __restrict__ qtiles,
                                                     ps_status* st) {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -196,6 +220,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
         if (yrow && lane == 0) stats_out[row] = make_float2(0.f, 0.f);
         return;
     }
+    if (qtiles && lane == 0 && p % PS_ATT_BQ == 0)
+        qtiles[qtile_start[r] + p / PS_ATT_BQ] = make_int4((int)row - p, S, p, r);
     const int n_text = S - n_soft;
     const T* src;
     if (p < n_text) {
@@ -459,7 +485,7 @@ void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengt
     const bool planned = m->info.dtype == 1 && (n_req > PS_SKINNY_ROWS || ws.max_rows > PS_FUSED_ROWS);
     const int4 plan_cols = planned ? make_int4(3 * h, 2 * h, h, f) : make_int4(0, 0, 0, 0);
     hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft, m->info.max_pos,
-                       (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), plan_cols, ws.meta, ws.seq_len,
+                       (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), plan_cols, planned ? 1 : 0, ws.meta, ws.seq_len,
                        ws.row_start, ws.qtile_start, ws.bad_req, ws.head_done, st);
 }
 
@@ -471,12 +497,13 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
         hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const bf16_t*)m->e_tok, (const bf16_t*)m->e_pos, (const bf16_t*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
-                           ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, st);
+                           ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, ws.qtile_start, ws.qtiles, st);
     else
         hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const float*)m->e_tok, (const float*)m->e_pos, (const float*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
-                           ws.row_start, ws.bad_req, (float*)ws.x, (bf16_t*)nullptr, (float2*)nullptr, st);
+                           ws.row_start, ws.bad_req, (float*)ws.x, (bf16_t*)nullptr, (float2*)nullptr, (const int32_t*)nullptr,
+                           (int4*)nullptr, st);
 }
 
 void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* pred_f, int32_t* pred_tokens,
