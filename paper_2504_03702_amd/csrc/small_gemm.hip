@@ -14,6 +14,8 @@
 // A launch can carry the layer's per-request side map (skinny_gemm.h) in further workgroups, and makes the row
 // statistics of its operand from the 64-column pieces in its prologue: with few rows a layer's time is made of
 // launches, and this leaves five of ten.
+#include <type_traits>
+
 #include "skinny_gemm.h"
 
 namespace {
@@ -48,14 +50,14 @@ __device__ __forceinline__ void lds_barrier() {
 // and its lo part in the lower: one slice of W serves both and the two results are added in the epilogue: half as many
 // steps as a contraction over 2K (64 requests of hidden 768: 23 -> 10.7 us a launch).
 template <int EPI, int TM, int TN, int STAGES, int SIDE>
-__global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs side, int side_blocks) {
+__global__ __launch_bounds__(256, TM == 2 && TN == 1 ? 2 : 1) void small_gemm_kernel(SmallGemm p, SkinnyArgs side, int side_blocks) {
     constexpr bool DUAL = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED;
     constexpr int BM = 64 * TM, BN = 64 * TN, ROWS = DUAL ? BM / 2 : BM, NIT = ROWS / 32;   // ROWS: of the result
     constexpr int kStage = (BM + BN) * 128;   // a 64-deep slice: the rows of A, then those of W, 128 bytes each
     constexpr int kOutLd = BN + 8;            // floats per row of the staged tile (spreads the half-waves' writes)
     constexpr int NDMA = 2 * (TM + TN);       // DMAs of a wavefront per slice
     constexpr bool EARLY = TM * TN == 1;      // the previous sums are requested before the contraction (registers allow it)
-    static_assert(STAGES * kStage >= BM * kOutLd * 4 && STAGES * kStage >= kSkinnyLds, "LDS regions");
+    static_assert(STAGES * kStage >= BM * (kOutLd + 1) * 4 && STAGES * kStage >= kSkinnyLds, "LDS regions");
     __shared__ __align__(1024) unsigned char smem[STAGES * kStage];
     __shared__ float2 s_st[BM];
     if (SIDE != kNoSide) {
@@ -91,13 +93,9 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
                                                    : p.W + (int64_t)(n0 + r) * K);
     }
     int wr = 0;                                          // stage of the next slice to bring
-    auto dma = [&](int kt) {
-        unsigned char* at = smem + wr * kStage;
-        wr = wr + 1 == STAGES ? 0 : wr + 1;
-#pragma unroll
-        for (int j = 0; j < NDMA; ++j)
-            __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(src[j] + (int64_t)kt * 128 + (j < 2 * TM ? a_off : w_off)),
-                                             (LDS_AS void*)(at + (4 * j + wave) * 1024), 16, 0, 0);
+    auto dma = [&](int j, int kt, unsigned char* at) {
+        __builtin_amdgcn_global_load_lds((const GLOBAL_AS void*)(src[j] + (int64_t)kt * 128 + (j < 2 * TM ? a_off : w_off)),
+                                         (LDS_AS void*)(at + (4 * j + wave) * 1024), 16, 0, 0);
     };
     const int nk = K / 64;
 
@@ -143,8 +141,12 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
     if (RESID && EARLY) load_previous();
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s)
-        if (s < nk) dma(s);
+    for (int s = 0; s < STAGES - 1; ++s) {
+        if (s >= nk) continue;
+#pragma unroll
+        for (int j = 0; j < NDMA; ++j) dma(j, s, smem + wr * kStage);
+        wr = wr + 1 == STAGES ? 0 : wr + 1;
+    }
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
@@ -182,72 +184,99 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(SmallGemm p, SkinnyArgs
     struct Frags { bf16x8 a[4][TM], w[4][TN]; };
     Frags f0, f1;
     int rd = 0;                                          // stage of the next slice to read
-    // slice kt has landed (everything older than the STAGES - 2 newest slices has), then every wavefront is past its
+    // slice kt has landed (everything older than the STAGES - 2 newest slices has), and every wavefront is past its
     // reads of slice kt - 1, whose stage the next DMA overwrites
-    auto next_slice = [&](int kt, Frags& f) {
+    auto land = [&](int kt) {
         if (kt + STAGES - 2 < nk) wait_vm<NDMA * (STAGES - 2)>();
         else wait_vm<0>();
         lds_barrier();
-        if (kt + STAGES - 1 < nk) dma(kt + STAGES - 1);
-        const int at = rd * kStage;
-        rd = rd + 1 == STAGES ? 0 : rd + 1;
+    };
+    constexpr int NREAD = 4 * (TM + TN), NMFMA = 4 * TM * TN;
+    auto read = [&](int q, Frags& f, int at) {           // fragment q of the slice in stage `at`
+        const int ks = q / (TM + TN), i = q % (TM + TN);
+        if (i < TM) f.a[ks][i] = *(const bf16x8*)(sa + at + i * 4096 + koff[ks]);
+        else f.w[ks][i - TM] = *(const bf16x8*)(sb + at + (i - TM) * 4096 + koff[ks]);
+    };
+    auto multiply = [&](int m, const Frags& f) {
+        const int ks = m / (TM * TN), i = m / TN % TM, j = m % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[ks][i], f.w[ks][j], acc[i][j], 0, 0, 0);
+    };
+    auto next_stage = [&](int& st) {
+        const int at = st * kStage;
+        st = st + 1 == STAGES ? 0 : st + 1;
+        return at;
+    };
+    // The products of slice kt - 1 with the reads of slice kt and the DMAs of slice kt + STAGES - 1 spread among them.  In
+    // one queue behind the other, as the compiler leaves them, a 128 x 64 tile's slice cost the sum of what its DMAs, its reads
+    // and its products take: 1357 rows of hidden 768, second feed-forward map 25.7 -> 23.6 us, first 21.7 -> 20.5,
+    // query-key-value map 16.1 -> 15.5.  (64 x 64 tiles, alone in their units: no change.)
+    auto slice = [&](int kt, const Frags& cur, Frags& nxt) {
+        land(kt);
+        const bool more = kt + STAGES - 1 < nk;
+        unsigned char* to = smem + wr * kStage;
+        const int at = next_stage(rd);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int m = 0; m < NMFMA; ++m) {
+            multiply(m, cur);
+            if (more) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) f.a[ks][i] = *(const bf16x8*)(sa + at + i * 4096 + koff[ks]);
+                for (int j = m * NDMA / NMFMA; j < (m + 1) * NDMA / NMFMA; ++j) dma(j, kt + STAGES - 1, to);
+            }
 #pragma unroll
-            for (int j = 0; j < TN; ++j) f.w[ks][j] = *(const bf16x8*)(sb + at + j * 4096 + koff[ks]);
+            for (int q = m * NREAD / NMFMA; q < (m + 1) * NREAD / NMFMA; ++q) read(q, nxt, at);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        wr = wr + 1 == STAGES ? 0 : wr + 1;
     };
-    auto multiply = [&](const Frags& f) {
+    land(0);
+    if (STAGES - 1 < nk) {
+        unsigned char* to = smem + next_stage(wr);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[ks][i], f.w[ks][j], acc[i][j], 0, 0, 0);
-    };
-    next_slice(0, f0);
-    for (int kt = 0; kt < nk; kt += 2) {                 // (K is a multiple of 256: nk is even)
-        next_slice(kt + 1, f1);
-        multiply(f0);
-        if (kt + 2 < nk) next_slice(kt + 2, f0);
-        multiply(f1);
+        for (int j = 0; j < NDMA; ++j) dma(j, STAGES - 1, to);
     }
+    const int at0 = next_stage(rd);
+#pragma unroll
+    for (int q = 0; q < NREAD; ++q) read(q, f0, at0);
+    for (int kt = 0; kt < nk - 2; kt += 2) {             // (K is a multiple of 256: nk is even)
+        slice(kt + 1, f0, f1);
+        slice(kt + 2, f1, f0);
+    }
+    slice(nk - 1, f0, f1);
+#pragma unroll
+    for (int m = 0; m < NMFMA; ++m) multiply(m, f1);
 
     // ---- epilogue: the tile goes through LDS, then 8 consecutive columns (or rows of a value column) per thread -------
     if (RESID && !EARLY) load_previous();
     __syncthreads();                                     // the last slices have been read
     float* out = (float*)smem;
+    // value columns are read back by rows: another row length keeps those reads off each other's banks
+    const int v_col0 = EPI == EPI_KV ? p.hidden : 2 * p.hidden;
+    const bool values = (EPI == EPI_QKV || EPI == EPI_KV) && n0 >= v_col0;
+    const int out_ld = values ? kOutLd + 1 : kOutLd;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                out[(32 * (TM * wm + i) + 8 * (e >> 2) + 4 * fhalf + (e & 3)) * kOutLd + 32 * (TN * wn + j) + frow] = acc[i][j][e];
+                out[(32 * (TM * wm + i) + 8 * (e >> 2) + 4 * fhalf + (e & 3)) * out_ld + 32 * (TN * wn + j) + frow] = acc[i][j][e];
     __syncthreads();
 
-    const int v_col0 = EPI == EPI_KV ? p.hidden : 2 * p.hidden;
-    if ((EPI == EPI_QKV || EPI == EPI_KV) && n0 >= v_col0) {
-        // value columns, transposed: feature c, 8 consecutive rows per thread
+    if (values) {
+        // transposed: 8 consecutive rows of a feature per thread, whole lines of Vt (64 rows) by 8 neighbouring threads (16
+        // bytes of 64 features an access: query-key-value map of 1357 rows 15.5 us, 13.9 so)
 #pragma unroll
-        for (int pc = 0; pc < TN; ++pc) {
-            const int c = 64 * pc + (threadIdx.x & 63);
+        for (int it = 0; it < BM * BN / 2048; ++it) {
+            const int at = threadIdx.x + 256 * it, c = (at >> 3) % BN, r0 = 64 * ((at >> 3) / BN) + 8 * (at & 7);
             const float cc = res.colsum[n0 + c], dd = p.bias[n0 + c];
+            float v[8];
 #pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int rg = (threadIdx.x >> 6) + 4 * it;
-                float v[8];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float2 sv = s_st[8 * rg + r];
-                    v[r] = fmaf(out[(8 * rg + r) * kOutLd + c], sv.y, fmaf(-sv.x * sv.y, cc, dd));
-                }
-                *(uint4*)(p.vt + (int64_t)(n0 - v_col0 + c) * p.max_rows + m0 + 8 * rg) =
-                    make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
+            for (int r = 0; r < 8; ++r) {
+                const float2 sv = s_st[r0 + r];
+                v[r] = fmaf(out[(r0 + r) * out_ld + c], sv.y, fmaf(-sv.x * sv.y, cc, dd));
             }
+            *(uint4*)(p.vt + (int64_t)(n0 - v_col0 + c) * p.max_rows + m0 + r0) =
+                make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
         }
         return;
     }
