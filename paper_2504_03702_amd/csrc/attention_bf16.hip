@@ -65,10 +65,13 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(
     // request's keys and values through its L2 instead of fetching them once per XCD
     const int heads = H / 64;
     const int head = blockIdx.x % heads, qt = blockIdx.x / heads;
-    if (qt >= meta->total_qtiles) return;
     // The tile's request from a table (the embedding kernel writes it) instead of a search among the requests, and the longest
     // requests' tiles first: 1024 prompts 602 -> 594 us, 582 in that order; 64 padded ones 46.5 us either way, 42.9.
+    // (read before it is known to be one: the table has an entry for every workgroup, and the two loads go out together)
     const int4 tile = qtiles[qt];
+    const int total = meta->total_qtiles;
+    asm volatile("" ::"s"(tile.x), "s"(total));
+    if (qt >= total) return;
     const int base = tile.x, S = tile.y, q0 = tile.z, req = tile.w;
     if (first_rows_only && q0 != 0) return;                 // whole workgroup: nothing to wait for
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
