@@ -207,6 +207,129 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
     }
 }
 
+// The same sums in the same order for heads of whole 16-byte groups, with the keys and values of 64 positions at a time in LDS:
+// a workgroup's rows (of one request) share them, and they come in whole lines.  A row a lane, as above, occupies the
+// address unit for all 64 lanes of every 16 bytes of a key, and the value rows were a trip to memory for every eight of them.
+// The first 64 keys' values are requested with the keys: short requests wait for memory once.  16 prompts of up to 64 tokens,
+// 2 heads of 64: 9.3 -> 7.9 us a launch.
+template <int Q>
+__global__ __launch_bounds__(256) void attention_f32_staged_kernel(const float* __restrict__ qkv, float* __restrict__ out,
+                                                                   int H, int d, int n_req, int max_pos,
+                                                                   const BatchMeta* meta, const int32_t* __restrict__ seq_len,
+                                                                   const int32_t* __restrict__ row_start) {
+    extern __shared__ __align__(16) float lds[];
+    static_assert(4 * Q <= PS_ROW_ALIGN, "a workgroup's rows are of one request");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int first = blockIdx.x * 4 * Q, head = blockIdx.y;
+    if (first >= meta->total_rows) return;
+    int lo = 0, hi = n_req - 1;
+    if (n_req <= 64) {                            // one load and a count of the starts up to this row
+        lo = __popcll(__ballot(lane < n_req && row_start[min(lane, n_req - 1)] <= first)) - 1;
+    } else {
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (row_start[mid] <= first) lo = mid; else hi = mid - 1;
+        }
+    }
+    const int base = row_start[lo], S = seq_len[lo];
+    if (first - base >= S) return;                // the whole workgroup
+    const int row0 = first + wave * Q, rows = min(Q, S - (row0 - base));   // (rows < 1: the wavefront only moves tiles)
+    const int kld = d + 4, pos4 = (max_pos + 3) & ~3;
+    float *kt = lds, *vt = kt + 64 * kld, *q = vt + 64 * d + wave * Q * (d + pos4), *sc = q + Q * d;
+    const int64_t ld = 3 * (int64_t)H;
+    const float scale = 1.0f / sqrtf((float)d);
+    // thread's first 16-byte piece of a tile, and how far on the next one is
+    const int per_row = d / 4, key0 = threadIdx.x / per_row, col0 = threadIdx.x - key0 * per_row;
+    const int key_step = 256 / per_row, col_step = 256 - key_step * per_row;
+    auto stage = [&](float* to, int to_ld, int t0, int part) {               // part: 1 keys, 2 values
+        const int n = min(64, S - t0);
+        const float* from = qkv + (int64_t)(base + t0) * ld + (int64_t)part * H + head * d;
+        for (int key = key0, c = col0; key < n;) {
+            *(float4*)(to + key * to_ld + 4 * c) = *(const float4*)(from + key * ld + 4 * c);
+            key += key_step;
+            c += col_step;
+            if (c >= per_row) { c -= per_row; ++key; }
+        }
+    };
+    stage(kt, kld, 0, 1);
+    stage(vt, d, 0, 2);
+#pragma unroll
+    for (int r = 0; r < Q; ++r)                   // (rows past the request's end: the last one again, not stored)
+        for (int i = lane; i < d; i += 64) q[r * d + i] = qkv[(base + min(row0 - base + r, S - 1)) * ld + head * d + i];
+    float mx[Q];
+#pragma unroll
+    for (int r = 0; r < Q; ++r) mx[r] = -INFINITY;
+    for (int t0 = 0; t0 < S; t0 += 64) {
+        if (t0 > 0) {
+            __syncthreads();
+            stage(kt, kld, t0, 1);
+        }
+        __syncthreads();
+        const int t = t0 + lane;
+        if (t >= S || rows < 1) continue;
+        float s[Q];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) s[r] = 0.f;
+#pragma unroll 4
+        for (int i = 0; i < d; i += 4) {
+            const float4 k = *(const float4*)(kt + lane * kld + i);
+#pragma unroll
+            for (int r = 0; r < Q; ++r) {
+                const float4 qi = *(const float4*)(q + r * d + i);
+                s[r] = fmaf(qi.x, k.x, s[r]);
+                s[r] = fmaf(qi.y, k.y, s[r]);
+                s[r] = fmaf(qi.z, k.z, s[r]);
+                s[r] = fmaf(qi.w, k.w, s[r]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < Q; ++r) {
+            s[r] *= scale;
+            sc[r * pos4 + t] = s[r];
+            mx[r] = fmaxf(mx[r], s[r]);
+        }
+    }
+    float sum[Q];
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+        mx[r] = wave_max(mx[r]);
+        sum[r] = 0.f;
+        for (int t = lane; t < S && rows >= 1; t += 64) {
+            const float e = expf(sc[r * pos4 + t] - mx[r]);
+            sc[r * pos4 + t] = e;
+            sum[r] += e;
+        }
+        sum[r] = wave_sum(sum[r]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // 64 features at a time; the values of the first 64 positions are there the first time round
+    for (int i0 = 0; i0 < d; i0 += 64) {
+        const int i = i0 + lane;
+        float o[Q];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) o[r] = 0.f;
+        for (int t0 = 0; t0 < S; t0 += 64) {
+            if (S > 64 && (t0 > 0 || i0 > 0)) {
+                __syncthreads();
+                stage(vt, d, t0, 2);
+                __syncthreads();
+            }
+            if (i >= d || rows < 1) continue;
+            const int n = min(64, S - t0);
+#pragma unroll 8
+            for (int t = 0; t < n; ++t) {
+                const float x = vt[t * d + i];
+#pragma unroll
+                for (int r = 0; r < Q; ++r) o[r] = fmaf(sc[r * pos4 + t0 + t], x, o[r]);
+            }
+        }
+        if (i < d)
+#pragma unroll
+            for (int r = 0; r < Q; ++r)
+                if (r < rows) out[(int64_t)(row0 + r) * H + head * d + i] = o[r] / sum[r];
+    }
+}
+
 // LayerNorm of one row per wavefront (biased variance, two passes over the row).
 __global__ __launch_bounds__(256) void layernorm_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
                                                             const float* __restrict__ gamma,
@@ -254,6 +377,15 @@ void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipS
     float *x = (float*)ws.x, *qkv = (float*)ws.qkv, *att = (float*)ws.att, *y = (float*)ws.y,
           *x1 = (float*)ws.x1, *g = (float*)ws.g;
     const unsigned row_blocks = (unsigned)(ws.max_rows / 4);
+    // Keys and values through LDS where a head is whole 16-byte groups and they fit: one row a wavefront (us a launch with
+    // hidden 128, 2 heads: 16 prompts, 768 rows, 9.3 without / 7.9 so, 30 prompts 11.9 / 8.5), two from 3072 rows x heads (50
+    // prompts, 2304 rows, 12.5 / 9.9); from 8192 on four rows a wavefront without LDS use the vector units better (150 prompts,
+    // 6400 rows, 16.9 / 20.0; four rows and LDS 27.0).
+    auto staged_lds = [&](int rows) {
+        return sizeof(float) * ((size_t)64 * (2 * d + 4) + (size_t)4 * rows * (d + ((f.max_pos + 3) & ~3)));
+    };
+    const int64_t row_heads = ws.max_rows * f.heads;
+    const int staged = d % 4 != 0 || staged_lds(2) > 64 * 1024 || row_heads >= 8192 ? 0 : row_heads >= 3072 ? 2 : 1;
     // Four rows a wavefront where there are rows enough to fill the chip all the same and their scores leave room for
     // several workgroups to a unit.  Two layers, hidden 128, us a call, one row / four: 16 prompts (768 rows x 2 heads) 90.5 /
     // 93.8, 50 (2048 x 2) 131 / 128, 150 224 / 196, 512 507 / 419.
@@ -263,7 +395,13 @@ void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipS
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
         gemm_f32<F32_NONE>(x, (const float*)w.w_qkv, w.b_qkv, nullptr, qkv, ws.max_rows, 3 * H, H, ws.meta, s);
-        if (att_rows == 4)
+        if (staged == 2)
+            hipLaunchKernelGGL(attention_f32_staged_kernel<2>, dim3(row_blocks / 2, (unsigned)f.heads), dim3(256), staged_lds(2), s,
+                               qkv, att, H, d, n_req, f.max_pos, ws.meta, ws.seq_len, ws.row_start);
+        else if (staged == 1)
+            hipLaunchKernelGGL(attention_f32_staged_kernel<1>, dim3(row_blocks, (unsigned)f.heads), dim3(256), staged_lds(1), s,
+                               qkv, att, H, d, n_req, f.max_pos, ws.meta, ws.seq_len, ws.row_start);
+        else if (att_rows == 4)
             hipLaunchKernelGGL(attention_f32_kernel<4>, dim3(row_blocks / 4, (unsigned)f.heads), dim3(256), att_lds4, s,
                                qkv, att, H, d, n_req, f.max_pos, ws.meta, ws.seq_len, ws.row_start);
         else

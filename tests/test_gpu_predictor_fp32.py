@@ -206,6 +206,27 @@ def test_head_sizes_off_the_attention_loads(tmp_models, hidden, heads, n):
     check_tokens(got_f, got_t, ref_t, cfg.d_max)
 
 
+@pytest.mark.parametrize("hidden,heads", [(8, 2), (64, 1), (128, 2), (136, 2), (200, 2), (124, 1)])
+@pytest.mark.parametrize("n", [2, 25, 70])
+def test_heads_of_whole_groups(tmp_models, hidden, heads, n):
+    """Head sizes that are multiples of 4 (keys and values through LDS, 64 positions at a time): below, at and above 64
+    features, requests of one tile, of exactly 64 and 128 positions and of three tiles, one and two rows a wavefront, more
+    requests than one load finds."""
+    cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=48, vocab=300, max_pos=133, head_hidden=17, dtype=wl.DTYPE_FP32)
+    print(f"predict fp32 whole groups {hidden // heads} n={n}", flush=True)
+    model, ref = make(tmp_models, f"groups_{hidden}_{heads}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(hidden + n)
+    lengths = rng.integers(1, 134, n).astype(np.int32)
+    lengths[:2] = 133, 64
+    lengths[2:6] = np.array([128, 65, 129, 1], np.int32)[:max(n - 2, 0)]
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got_f, got_t, flags, _ = run_predict(model, batch)
+    ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
+    assert flags == 0
+    assert rel_err(got_f, ref_f).max() < TOL_FP32
+    check_tokens(got_f, got_t, ref_t, cfg.d_max)
+
+
 def test_more_feed_forward_units_than_a_grid_has_tiles(tmp_models):
     """2097152 + 100 feed-forward units: more tiles of 32 columns than one launch may have in a dimension."""
     cfg = wl.ModelConfig(layers=1, hidden=2, heads=1, ffn=2097152 + 100, vocab=10, max_pos=8, head_hidden=3, dtype=wl.DTYPE_FP32)
