@@ -129,8 +129,8 @@ struct ResidualSrc {
     const int32_t* row_map;  // EPI_RESIDUAL_MAPPED: stream row of GEMM row r (the request's first row)
     const int32_t* seq_len;  //                       rows with seq_len[r] <= 0 are not stored
     // residual epilogues: the hi parts of the new sums (the lo parts go to the C argument); hi is also
-    // the next map's operand.  Optional: every 64-column piece of a row leaves its (sum, sum of squares)
-    // in pstats[row][N / 64]
+    // the next map's operand.  Every 64-column piece of a row leaves its (sum, sum of squares) in
+    // pstats[row][N / 64] (may be null for the per-request maps)
     bf16_t* x_out;
     float2* pstats;
     // epilogues of the maps a LayerNorm is folded into (EPI_QKV, EPI_KV, EPI_Q_MAPPED, EPI_BIAS_GELU):
