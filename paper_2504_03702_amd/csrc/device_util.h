@@ -89,7 +89,8 @@ __device__ __forceinline__ void report_fault(ps_status* st, int flag, int64_t in
 // ---- The residual stream: 32-bit sums kept as two arrays of 16 bits ------------------------------------------
 // The float's bits plus 0x8000 are cut in two: hi, the upper half, is the sum rounded to bf16 (ties away from zero), the
 // operand of the next map; hi and lo together are the float.  Two instructions an element either way; hi and lo as two
-// bf16 values, which kept 16 significant bits of a sum, took three.
+// bf16 values, which kept 16 significant bits of a sum, took three.  Ties are as rare as one in 2^16 among the sums of
+// products, so where they go does not matter; sums of few bits go through stream_ties_to_even first.
 #define PS_STREAM_ZERO_LO 0x8000u     // lo of a zero (hi is 0)
 __device__ __forceinline__ float stream_join(uint16_t hi, uint16_t lo) {
     return __uint_as_float((((uint32_t)hi << 16) | lo) - 0x8000u);
@@ -103,6 +104,13 @@ __device__ __forceinline__ void stream_split2(float a, float b, uint32_t& hi, ui
     const uint32_t x = __float_as_uint(a) + 0x8000u, y = __float_as_uint(b) + 0x8000u;
     hi = __builtin_amdgcn_perm(y, x, 0x07060302u);
     lo = __builtin_amdgcn_perm(y, x, 0x05040100u);
+}
+// A sum halfway between two bf16 values whose lower one is even, one float step lower, so that stream_split2 rounds ties to
+// even.  A fifth of the sums of a token's and a position's bf16 embedding are ties: all of them away from zero, the first
+// maps' operand was 0.08 % too large throughout, an error that no sum over keys or features averages out.
+__device__ __forceinline__ float stream_ties_to_even(float x) {
+    const uint32_t b = __float_as_uint(x);
+    return __uint_as_float(b - ((b & 0x1ffffu) == 0x8000u ? 1u : 0u));
 }
 
 // ---- LayerNorm pieces that several kernels must compute alike, to the last bit ----------------------------

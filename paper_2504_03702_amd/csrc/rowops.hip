@@ -277,8 +277,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
         for (int c = 0; c < 8; ++c) {
             if (c < nch) {
                 uint2 hi, lo;
-                stream_split2(e[c].x, e[c].y, hi.x, lo.x);
-                stream_split2(e[c].z, e[c].w, hi.y, lo.y);
+                stream_split2(stream_ties_to_even(e[c].x), stream_ties_to_even(e[c].y), hi.x, lo.x);
+                stream_split2(stream_ties_to_even(e[c].z), stream_ties_to_even(e[c].w), hi.y, lo.y);
                 ((uint2*)out)[lane + 64 * c] = hi;
                 ((uint2*)yrow)[lane + 64 * c] = lo;
             }

@@ -327,3 +327,43 @@ def test_workspace_of_nans(tmp_models, n, length):
         assert ps.ps_status_read(st)[0] == 0
         out.append(pred_f.cpu().numpy())
     assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_ties_of_the_embedding_sums(tmp_models, seed):
+    """Sums of a token's and a position's bf16 embedding that lie halfway between two bf16 values, nearly all of them.  The
+    bf16 operand of the first maps has to take them up and down alike (to even): its errors then average out over the 400 keys,
+    to a twentieth of what they come to where every tie goes away from zero.  That is worked out here with the oracle's steps;
+    a quarter of it is allowed, for the other roundings (single predictions are off by a sixth at most, and 24 are averaged)."""
+    cfg = wl.ModelConfig(layers=1, hidden=256, heads=4, ffn=512, vocab=64, max_pos=400, dtype=wl.DTYPE_BF16)
+    print(f"predict bf16 ties seed={seed}", flush=True)
+    w, rng = wl.make_weights(cfg, seed=seed), np.random.default_rng(seed + 1)
+    sign = rng.choice([-1.0, 1.0], cfg.hidden)
+    w["E_tok"] = (sign * (1 + rng.integers(1, 127, (cfg.vocab, cfg.hidden)) / 128)).astype(np.float32)
+    w["E_pos"] = (rng.choice([-1.0, 1.0], (cfg.max_pos, cfg.hidden)) / 256).astype(np.float32)
+    for name in ("layer0.W_v", "layer0.W_o"):
+        w[name] = 4 * w[name]
+    path = os.path.join(tmp_models, f"ties_{seed}.bin")
+    wl.write_model(path, cfg, w)
+    model, ref = ps.ps_model_load(path, 0), op.load_model(path)
+    lengths = np.full(24, cfg.max_pos, np.int32)
+    batch = wl.pack_prompts(lengths, np.random.default_rng(9).integers(0, cfg.vocab, 24 * cfg.max_pos).astype(np.int32))
+    got_f, _, flags, _ = run_predict(model, batch)
+    ref_f, _ = op.predict_load(ref, batch.token_ids, batch.offsets)
+
+    def predict_away(ids):
+        """The prediction with queries, keys and values made from sums rounded away from zero."""
+        e = ref["E_tok"][ids] + ref["E_pos"][:len(ids)]
+        away = ((e.astype(np.float32).view(np.uint32) + 0x8000) & np.uint32(0xFFFF0000)).view(np.float32).astype(np.float64)
+        mean, lay = e.mean(axis=1, keepdims=True), ref["layer"][0]
+        std = np.sqrt(((e - mean) ** 2).mean(axis=1, keepdims=True) + cfg.ln_eps)
+        x, xa = (e - mean) / std, (away - mean) / std              # (LayerNorm scale 1, shift 0)
+        o = op.self_attention(xa, lay, cfg.heads)[0]
+        x1 = op.layer_norm(x[0] + o @ lay["W_o"] + lay["b_o"], *lay["ln_1"], cfg.ln_eps)
+        y = x1 + op.gelu(x1 @ lay["W_1"] + lay["b_1"]) @ lay["W_2"] + lay["b_2"]
+        return op.regression_head(ref, op.layer_norm(y, *lay["ln_2"], cfg.ln_eps))
+
+    shift = np.mean([predict_away(ids) for ids in batch.token_ids.reshape(24, -1)] - ref_f)
+    off = np.mean(got_f - ref_f)
+    print(f"  mean error {off:+.5f}, {shift:+.5f} with ties away from zero", flush=True)
+    assert flags == 0 and abs(shift) > 0.04 and abs(off) < 0.25 * abs(shift)
