@@ -380,12 +380,18 @@ void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipS
     // Keys and values through LDS where a head is whole 16-byte groups and they fit: one row a wavefront (us a launch with
     // hidden 128, 2 heads: 16 prompts, 768 rows, 9.3 without / 7.9 so, 30 prompts 11.9 / 8.5), two from 3072 rows x heads (50
     // prompts, 2304 rows, 12.5 / 9.9); from 8192 on four rows a wavefront without LDS use the vector units better (150 prompts,
-    // 6400 rows, 16.9 / 20.0; four rows and LDS 27.0).
+    // 6400 rows, 16.9 / 20.0; four rows and LDS 27.0).  Heads of 64 features and more only while all workgroups have a place
+    // at once, by the LDS that head size and positions take: a second round costs more than the loads save (two layers, rows x
+    // heads: us a call without / through LDS; 64 features of 640 positions, 512 places, 3072: 166 / 156, 7936: 211 / 267; 64 of
+    // 512, 768 places, 4096: 156 / 153, 7168: 215 / 250; 100 of 256, 512 places, 3328: 170 / 165, 6912: 206 / 264).  Smaller ones
+    // gain there too (32 of 1024, 768 places, 7168: 282 / 179).
     auto staged_lds = [&](int rows) {
         return sizeof(float) * ((size_t)64 * (2 * d + 4) + (size_t)4 * rows * (d + ((f.max_pos + 3) & ~3)));
     };
     const int64_t row_heads = ws.max_rows * f.heads;
-    const int staged = d % 4 != 0 || staged_lds(2) > 64 * 1024 || row_heads >= 8192 ? 0 : row_heads >= 3072 ? 2 : 1;
+    auto one_round = [&](int rows) { return row_heads / (4 * rows) <= 256 * (int64_t)(160 * 1024 / staged_lds(rows)); };
+    const int staged_rows = row_heads >= 3072 ? 2 : 1;
+    const int staged = d % 4 != 0 || staged_lds(2) > 64 * 1024 || row_heads >= 8192 || (d >= 64 && !one_round(staged_rows)) ? 0 : staged_rows;
     // Four rows a wavefront where there are rows enough to fill the chip all the same and their scores leave room for
     // several workgroups to a unit.  Two layers, hidden 128, us a call, one row / four: 16 prompts (768 rows x 2 heads) 90.5 /
     // 93.8, 50 (2048 x 2) 131 / 128, 150 224 / 196, 512 507 / 419.

@@ -209,9 +209,9 @@ def test_head_sizes_off_the_attention_loads(tmp_models, hidden, heads, n):
 @pytest.mark.parametrize("hidden,heads", [(8, 2), (64, 1), (128, 2), (136, 2), (200, 2), (124, 1)])
 @pytest.mark.parametrize("n", [2, 25, 70])
 def test_heads_of_whole_groups(tmp_models, hidden, heads, n):
-    """Head sizes that are multiples of 4 (keys and values through LDS, 64 positions at a time): below, at and above 64
-    features, requests of one tile, of exactly 64 and 128 positions and of three tiles, one and two rows a wavefront, more
-    requests than one load finds."""
+    """Head sizes that are multiples of 4, below, at and above 64 features, the last too large for keys and values through LDS;
+    requests of one tile, of exactly 64 and 128 positions and of three tiles.  The calls of 2 requests and of 25 take the forms
+    with one and two rows a wavefront through LDS, those of 70 with two heads the form without (see attention_form)."""
     cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=48, vocab=300, max_pos=133, head_hidden=17, dtype=wl.DTYPE_FP32)
     print(f"predict fp32 whole groups {hidden // heads} n={n}", flush=True)
     model, ref = make(tmp_models, f"groups_{hidden}_{heads}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
@@ -225,6 +225,43 @@ def test_heads_of_whole_groups(tmp_models, hidden, heads, n):
     assert flags == 0
     assert rel_err(got_f, ref_f).max() < TOL_FP32
     check_tokens(got_f, got_t, ref_t, cfg.d_max)
+
+
+def attention_form(d, heads, max_pos, tokens, n):
+    """The form that the encoder's rule takes: 1 or 2 rows a wavefront with keys and values through LDS, 0 without LDS."""
+    row_heads = -(-(tokens + 7 * n + 64) // 256) * 256 * heads
+    lds = lambda rows: 4 * (64 * (2 * d + 4) + 4 * rows * (d + -(-max_pos // 4) * 4))
+    rows = 2 if row_heads >= 3072 else 1
+    if d % 4 or lds(2) > 65536 or row_heads >= 8192 or (d >= 64 and row_heads // (4 * rows) > 256 * (160 * 1024 // lds(rows))):
+        return 0
+    return rows
+
+
+@pytest.mark.parametrize("hidden,heads,max_pos", [(8, 2, 133), (96, 2, 133), (64, 1, 133), (128, 2, 133), (136, 2, 133),
+                                                  (100, 1, 133), (64, 1, 640)])
+def test_attention_forms_bit_equal(tmp_models, hidden, heads, max_pos):
+    """The same requests by themselves, among so many that two rows go to a wavefront (more than 64, so that a row's request is
+    searched for) and among so many that nothing goes through LDS: the sums are in one order, so the bits are the same."""
+    d = hidden // heads
+    cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=48, vocab=300, max_pos=max_pos, head_hidden=17, dtype=wl.DTYPE_FP32)
+    print(f"predict fp32 attention forms {d} features, {max_pos} positions", flush=True)
+    model, ref = make(tmp_models, f"forms_{hidden}_{heads}_{max_pos}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(hidden + max_pos)
+    lengths = np.full(3000, 21, np.int32)
+    lengths[:6] = max_pos, 64, 128, 65, 129, 1
+    lengths[6:40] = rng.integers(1, 20, 34)
+    ids = rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32)
+    got, forms = [], []
+    for n in ((40, 120, 1200) if heads == 1 else (6, 70, 1200)):
+        tokens = int(lengths[:n].sum())
+        forms.append(attention_form(d, heads, max_pos, tokens, n))
+        f, _, flags, _ = run_predict(model, wl.pack_prompts(lengths[:n], ids[:tokens]))
+        assert flags == 0
+        got.append(f)
+    assert forms == [1, 2, 0]
+    assert np.array_equal(got[0], got[2][:len(got[0])]) and np.array_equal(got[1], got[2][:len(got[1])])
+    ref_f, _ = op.predict_load(ref, ids[:int(lengths[:40].sum())], np.concatenate([[0], np.cumsum(lengths[:40])]))
+    assert rel_err(got[1][:40], ref_f).max() < TOL_FP32
 
 
 def test_more_feed_forward_units_than_a_grid_has_tiles(tmp_models):
