@@ -367,3 +367,44 @@ def test_ties_of_the_embedding_sums(tmp_models, seed):
     off = np.mean(got_f - ref_f)
     print(f"  mean error {off:+.5f}, {shift:+.5f} with ties away from zero", flush=True)
     assert flags == 0 and abs(shift) > 0.04 and abs(off) < 0.25 * abs(shift)
+
+
+def test_faults_among_sorted_tiles(tmp_models):
+    """More than 16 requests: the attention's tiles are dealt longest request first.  Faulty lengths and tokens among them, and
+    offsets that together ask for more rows than the workspace has, leave the others' bits as they are."""
+    print("predict bf16 faults among 40 requests", flush=True)
+    model, _ = make(tmp_models, "small_bf16.bin", SMALL, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(21)
+    lengths = rng.integers(1, 641, 40).astype(np.int32)
+    lengths[:4] = 640, 1, 128, 129
+    batch = wl.pack_prompts(lengths, rng.integers(0, SMALL.vocab, int(lengths.sum())).astype(np.int32))
+    good_f, good_t, flags, _ = run_predict(model, batch)
+    assert flags == 0
+    padded = wl.pad_prompts(lengths, batch.token_ids)
+    lens, ids = padded.lengths.copy(), padded.token_ids.copy()
+    lens[[0, 17, 39]] = 0, 641, -5                             # the longest request among them
+    ids[padded.offsets[5]] = -1
+    ids[padded.offsets[30] + lengths[30] - 1] = SMALL.vocab
+    f, t, flags, first = run_predict(model, dataclasses.replace(padded, lengths=lens, token_ids=ids))
+    assert flags == ps.PS_ST_BAD_LENGTH | ps.PS_ST_BAD_TOKEN and first == 0
+    bad = [0, 5, 17, 30, 39]
+    assert np.isnan(f[bad]).all() and (t[bad] == -1).all()
+    assert np.array_equal(np.delete(f, bad), np.delete(good_f, bad)) and np.array_equal(np.delete(t, bad), np.delete(good_t, bad))
+
+    # every even request claims [0, span), every odd one runs backwards: the spans are valid, but from some request on their
+    # rows pass what the host planned for the 2000 tokens there are
+    n, n_tok = 40, 2000
+    spans = rng.integers(20, 600, n // 2).astype(np.int32)
+    prompt = rng.integers(0, SMALL.vocab, n_tok).astype(np.int32)
+    offs = np.zeros(n + 1, np.int32)
+    offs[1::2] = spans
+    whole = wl.pack_prompts(np.concatenate([spans, spans]), np.concatenate([prompt[:s] for s in spans] * 2))
+    want_f, _, flags, _ = run_predict(model, whole)
+    assert flags == 0
+    f, t, flags, first = run_predict(model, dataclasses.replace(batch, token_ids=prompt, offsets=offs))
+    assert flags == ps.PS_ST_BAD_LENGTH and first == 1
+    assert np.isnan(f[1::2]).all() and (t[1::2] == -1).all()
+    capacity = -(-(n_tok + n * 7 + 64) // 256) * 256 - 64
+    kept = int(np.sum(np.cumsum((spans + 7) // 8 * 8) <= capacity))
+    assert 4 < kept < n // 2
+    assert np.array_equal(f[0::2][:kept], want_f[:kept]) and np.isnan(f[0::2][kept:]).all() and (t[0::2][kept:] == -1).all()
