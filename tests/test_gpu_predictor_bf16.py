@@ -305,11 +305,14 @@ def test_tiles_up_to_the_end_of_the_buffers(tmp_models, rows):
     chunks_bit_equal(model, batch, got, tokens, chunk=20)
 
 
-@pytest.mark.parametrize("n,length", [(3, 61), (24, 203), (96, 301)])
-def test_workspace_of_nans(tmp_models, n, length):
+@pytest.mark.parametrize("n,length,height", [(3, 61, 0), (24, 203, 0), (96, 301, 0), (117, 305, 160), (163, 305, 224)])
+def test_workspace_of_nans(tmp_models, n, length, height):
     """Rows behind the last request's are read by its last key tile with weight zero: they are written by every map that
-    has to (and by none that must not), so a workspace full of NaNs gives the bits of a zeroed one, in the launches of a
-    few requests, in 128-row and in 256-row tiles."""
+    has to (and by none that must not), so a workspace full of NaNs gives the bits of a zeroed one: in the launches of a
+    few requests, in 128-row tiles, with the wide maps only in the tiles of large calls, and with the maps back to the hidden
+    width in those too, of 160 and 224 rows (wavefronts of unequal heights), the last one moved up to the end of the buffers."""
+    met = {k[2:] for k in tile_plan.kinds(n * (length + 7)) if k[0] == "back to hidden"} if length % 8 == 1 else set()
+    assert met == ({(height, True)} if height else set())
     print(f"predict workspace of NaNs n={n}", flush=True)
     cfg = dataclasses.replace(SMALL, ffn=3072)
     model, _ = make(tmp_models, "tile_heights.bin", cfg, ln_jitter=0.1, bias_std=0.05)
