@@ -216,7 +216,7 @@ extern "C" int ps_predict_load(ps_model* m, const int32_t* token_ids, const int3
     if (!m || n_req < 0 || n_tokens < 0) return PS_EINVAL;
     if (n_req == 0) return PS_OK;
     if (!offsets || !pred_f || !pred_tokens || !workspace || (n_tokens > 0 && !token_ids)) return PS_EINVAL;
-    // activation row indices are 32-bit and 8 rows of the transposed values span a 32-bit byte offset
+    // activation row indices are 32-bit and 15 rows of the transposed values span a 32-bit byte offset (attention_bf16.hip)
     if (n_tokens + (int64_t)n_req * (m->info.n_soft + PS_ROW_ALIGN) > PS_MAX_ROWS) return PS_EUNSUPPORTED;
     if (((uintptr_t)workspace & 255) != 0) return PS_EWORKSPACE;
     Workspace ws = plan_workspace(m->info, n_tokens, n_req, workspace);

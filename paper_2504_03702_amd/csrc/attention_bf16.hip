@@ -105,8 +105,9 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(
         // LDS row r holds the key (the feature of V^T) with bits 2 and 3 of r swapped (see below)
         const int kr = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
         const int kb = (grp * 8) & ~8;                        // wave-uniform; kr - kb is in 0..15
+        static_assert(2 * (15 * (PS_MAX_ROWS + PS_KEY_SLACK + PS_ROW_TILE) + 64) <= UINT32_MAX, "v_off: vt_ld as the host admits it");
         k_off[j] = (unsigned)((kr - kb) * (int)ld_qk + c * 8) * 2u;
-        v_off[j] = (unsigned)((kr - kb) * vt_ld + c * 8) * 2u;                 // vt_ld is at most 2^27 and some (checked by the host)
+        v_off[j] = (unsigned)((kr - kb) * vt_ld + c * 8) * 2u;
         k_base[j] = (const unsigned char*)(qk + (int64_t)(base + kb) * ld_qk + H + head * 64);
         v_base[j] = (const unsigned char*)(vt + (int64_t)(head * 64 + kb) * vt_ld + base);
     }

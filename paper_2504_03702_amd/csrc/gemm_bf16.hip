@@ -2,7 +2,7 @@
 //
 //   C[m, n] = sum_k A[m, k] * W[n, k]   (A: activations [rows][K], W: weights [N][K], both bf16,
 //                                        contraction index contiguous; fp32 accumulation)
-//   epilogue: + bias[n], then one of: store | erf-GELU, store | + residual stream, store in two halves |
+//   epilogue: + bias[n], then one of: erf-GELU, store | + residual stream, store in two halves |
 //             QKV split (query and key columns to [rows][2H], value columns transposed to
 //             Vt[H][max_rows] so the attention kernel reads keys-contiguous value tiles), also as
 //             keys and values only | erf-GELU, store as hi + lo, for an operand that is hi + lo too.
@@ -316,8 +316,8 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
         tm = tm2;
         tn = tn2;
         // What the epilogue needs of the tile's columns and rows goes to LDS by DMA behind the tile's first barrier (every
-        // wavefront is past the last tile's epilogue) and has landed at the second one, some ten slices before it is read:
-        // read from memory there it came behind the DMAs of the next tile's slices, which the memory counter keeps in order.
+        // wavefront is past the last tile's epilogue) and has landed at the second one, two slices or more before it is read
+        // (hidden 256 has four): read from memory there it came behind the DMAs of the next tile's slices, which the memory counter keeps in order.
         auto fetch_params = [&]() {
             const float* src = wave == 0 ? bias : wave == 1 ? (FOLD ? res.colsum : res.gamma) : res.beta;
             if (wave == 0 || (wave == 1 && (FOLD || RESIDUAL)) || (wave == 2 && RESIDUAL)) {
@@ -531,7 +531,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
         }
 
         {
-            // bf16 out (plain, GELU, or the query / key columns of the QKV projection): the left 32 columns of all rows are
+            // bf16 out (GELU, or the query / key columns of the QKV projection): the left 32 columns of all rows are
             // finished first, then block by block the right ones, the exchanges and the stores
             const int64_t ldc = (EPI == EPI_QKV || EPI == EPI_KV) ? 2 * (int64_t)hidden
                                 : SPLIT ? 2 * (int64_t)N : (int64_t)N;
@@ -643,7 +643,6 @@ void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, 
     const dim3 grid((unsigned)wgs), block(WM * WN * 64);
 #define PS_LAUNCH(E) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED>), grid, block, 0, s, g, total_rows, plan, clk)
     switch (epi) {
-        case EPI_BIAS: PS_LAUNCH(EPI_BIAS); break;
         case EPI_BIAS_GELU: PS_LAUNCH(EPI_BIAS_GELU); break;
         case EPI_BIAS_RESIDUAL: PS_LAUNCH(EPI_BIAS_RESIDUAL); break;
         case EPI_QKV: PS_LAUNCH(EPI_QKV); break;
@@ -658,7 +657,9 @@ void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, 
 
 }  // namespace
 
-// Requirements (checked when the model is loaded): N % 256 == 0, K % 64 == 0; every buffer holds max_rows rows with
+// Requirements (hidden and feed-forward width are multiples of 256, checked when the model is loaded): N % 256 == 0,
+// K % 64 == 0 and K >= 128, 256 for EPI_GELU_SPLIT's two halves (a tile's biases and statistics are fetched behind the first slice of
+// a contraction, its previous sums ahead of the last); every buffer holds max_rows rows with
 // max_rows % 256 == 0.  Tiles of 128 and 256 rows are then always in bounds; those of other heights may reach past the end
 // and are moved up (row_of).
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,

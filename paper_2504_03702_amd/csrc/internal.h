@@ -113,7 +113,7 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
 
 // bf16 kernels
 enum GemmEpilogue {
-    EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3,
+    EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3,
     EPI_GELU_SPLIT = 4,          // GELU, then the fp32 value stored as two bf16 (value ~ hi + lo) in [rows][2N]
     EPI_RESIDUAL_MAPPED = 5,     // EPI_BIAS_RESIDUAL with GEMM row r living at stream row row_map[r]
     EPI_KV = 6,                  // EPI_QKV without the query columns: W holds the key and value rows only

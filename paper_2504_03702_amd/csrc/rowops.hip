@@ -8,8 +8,8 @@ namespace {
 // How a map of `rows` rows and n tile columns is cut into tiles for 256 workgroups (the whole wavefront calls, every lane
 // weighs one candidate): all rows in tiles of one height, or as many whole rounds of 256-row tiles as there are (or one
 // fewer) and the rest in tiles of one height.  Costs in thousandths of a full round of 256-row tiles.  A full round of
-// lower tiles costs more than its share of rows (measured on 250 k and 440 k rows, the four maps of hidden 768 and 1024:
-// 224 rows 1.00-1.02 per row, 192 1.03-1.08, 160 1.06-1.13, 128 1.11-1.26); a last round that leaves units idle runs
+// lower tiles costs more than its share of rows (measured on 250 k and 440 k rows, the maps of hidden 768 and 1024: 224 rows
+// 1.00-1.05 per row, 1.02 on average, 192 1.02-1.10, 1.04, 160 1.05-1.18, 1.11, 128 1.10-1.28, 1.19); a last round that leaves units idle runs
 // faster, the chip's power being shared by fewer, down to 0.68 of a full one (153 tiles of 256 rows, contraction 3072:
 // 70 us against 103).  Where all tiles fit one round, the lowest that do are the fastest however many units that leaves
 // idle: query-key-value map of hidden 768, 4600 rows, 256 to 192 rows 26.9 / 26.3 / 24.9 us; maps back to hidden 1024,

@@ -60,7 +60,7 @@ struct SkinnyPieces {
 
 // One block of 64 output columns by NW wavefronts; smem: kSkinnyLds bytes.  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED
 // take hi | lo rows (each W fragment serves two MFMAs).  GATHER: the rows of A are taken from the stream itself, at each request's first row: for EPI_Q_MAPPED the hi
-// parts, for EPI_GELU_SPLIT the LayerNorm of hi + lo, split again.
+// parts, for EPI_GELU_SPLIT the LayerNorm of the sums (both parts joined), as hi | lo.
 template <int EPI, int NW, bool GATHER>
 __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem) {
     constexpr bool DUAL = EPI != EPI_Q_MAPPED;
