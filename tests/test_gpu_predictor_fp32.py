@@ -210,8 +210,9 @@ def test_head_sizes_off_the_attention_loads(tmp_models, hidden, heads, n):
 @pytest.mark.parametrize("n", [2, 25, 70])
 def test_heads_of_whole_groups(tmp_models, hidden, heads, n):
     """Head sizes that are multiples of 4, below, at and above 64 features, the last too large for keys and values through LDS;
-    requests of one tile, of exactly 64 and 128 positions and of three tiles.  The calls of 2 requests and of 25 take the forms
-    with one and two rows a wavefront through LDS, those of 70 with two heads the form without (see attention_form)."""
+    requests of one tile, of exactly 64 and 128 positions and of three tiles.  With two heads the calls of 2, 25 and
+    70 requests take the forms with one and two rows a wavefront through LDS and the one without, with one head of 64 the first
+    two only (see attention_form)."""
     cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=48, vocab=300, max_pos=133, head_hidden=17, dtype=wl.DTYPE_FP32)
     print(f"predict fp32 whole groups {hidden // heads} n={n}", flush=True)
     model, ref = make(tmp_models, f"groups_{hidden}_{heads}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
@@ -219,6 +220,8 @@ def test_heads_of_whole_groups(tmp_models, hidden, heads, n):
     lengths = rng.integers(1, 134, n).astype(np.int32)
     lengths[:2] = 133, 64
     lengths[2:6] = np.array([128, 65, 129, 1], np.int32)[:max(n - 2, 0)]
+    form = attention_form(hidden // heads, heads, cfg.max_pos, int(lengths.sum()), n)
+    assert form == (0 if hidden == 124 else {2: 1, 25: 2, 70: 0}[n] if heads == 2 else {2: 1, 25: 1, 70: 2}[n])
     batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
     got_f, got_t, flags, _ = run_predict(model, batch)
     ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
