@@ -24,7 +24,7 @@
 // number counts as well: where a bound on queues and windows allows, scores are made in one register (walk_narrow).
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
 // window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.06 in one register; 64
-// instances 2.06 and 1.43.  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
+// instances 2.06 and 1.43; by one wavefront 1.32 (solo_walk).  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
 #include <type_traits>
 
 #include "device_util.h"
@@ -45,7 +45,7 @@ struct RoutePlan {
     size_t lds_bytes;
 };
 
-RoutePlan plan_route(int n_inst, int window) {
+RoutePlan plan_route(int n_inst, int window, size_t room) {
     RoutePlan p;
     const int whole = (window + 3) / 4 * 4;
     for (int block = 4 * ((window + 4 * kRouteMaxBlocks - 1) / (4 * kRouteMaxBlocks));; block *= 2) {
@@ -57,7 +57,7 @@ RoutePlan plan_route(int n_inst, int window) {
         for (int odd = 1; odd >= 0; --odd) {
             p.pitch = odd ? n_inst | 1 : n_inst;
             p.lds_bytes = 512 + (size_t)p.pitch * 4 * ((size_t)p.n_blocks * block + 2 * (size_t)(p.n_blocks + 1));
-            if (p.lds_bytes <= (size_t)kRouteLdsBytes) return p;
+            if (p.lds_bytes <= room) return p;
         }
         if (block == whole) return p;
     }
@@ -109,18 +109,337 @@ __device__ __forceinline__ long long wave_min(long long v, bool part, int& src) 
     return m;
 }
 
+// ---- one wavefront walks the requests -----------------------------------------------------------------------------
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_umax(unsigned v) {
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ unsigned wave_umax(unsigned m) {
+    m = dpp_umax<0x111, 0xf>(m);
+    m = dpp_umax<0x112, 0xf>(m);
+    m = dpp_umax<0x114, 0xf>(m);
+    m = dpp_umax<0x118, 0xf>(m);
+    m = dpp_umax<0x142, 0xa>(m);
+    m = dpp_umax<0x143, 0xc>(m);
+    return (unsigned)__builtin_amdgcn_readlane((int)m, 63);
+}
+__device__ __forceinline__ int wave_total(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// What the walk needs to know: peaks below 2^24, penalties and the rest of a score below 2^29.
+__device__ __forceinline__ bool peaks_fit(long long peak, int beta) { return peak < 1 << 24 && peak * 100 * max(beta, 1) < 1 << 29; }
+
+// The exchange between wavefronts costs a request as much as its scores do, and the tables are made for requests that end
+// anywhere in any window.  So wavefront 0 walks the requests, R instances a lane, with an instance's window in a few numbers:
+// F = max (w[t] + t), the first slot t* that has it, and the largest w.  A request whose ramp reaches beyond t* has the
+// peak P + F exactly (no slot behind the ramp is above F), and with p = beta (100 F - limit) a score is
+//     s + max(p + 100 beta P, 0),  s the queue a hundredfold.
+// For a ramp that ends before, the largest w gives a lower bound, and where an instance with such a bound has the smallest
+// score its window is read, once, for this request.  The other wavefronts add the requests of a batch to the windows and make
+// the numbers afresh while the next batch is walked; until then an instance's old numbers are a lower bound (windows only grow),
+// and F is less than P + D' above the old one, which keeps most instances below their limit: only where it does not, and the
+// instance is the choice again already, the walk waits for them.  A decision is some 110 instructions of one wavefront and no
+// exchange: 4096 requests over 256 instances of 100 slots 2052 -> 1320 us, 1450 to 2020 as calls fill the windows to their limits;
+// 100 instances 2026 -> 1260 (1690 full), 2048 requests over 128 of 64 slots 1017 -> 612, over 256 of 128 1267 -> 670, over 500
+// of 60 1445 -> 870.  Up to 64 instances a walk with the tables has no exchange either, and waits would be frequent (20 instances
+// 739 -> 820, 64 1470 -> 1280 to 1440): left to it.
+const int kSoloInstances = 512;              // eight a lane
+const int kSoloTokens = 1 << 20;             // prompts and predictions from here on are not walked
+const int kSoloWaves = 8;
+const int kSoloBatch = 16;
+const int kSoloEffort = 96;                  // windows read and, five times each, waits for 64 requests beyond which the tables are the cheaper way
+struct SoloWalk {
+    const int32_t* prompt_tokens;
+    const int32_t* pred_tokens;
+    int n_req, n_inst, window, pitch, beta;
+    int* win;                                // s_win
+    int lanes_log2;                          // of R: instance i is number i % R of lane i / R
+    int4* state;                             // [R][64] p; t*; p with the largest w for F; limit.  At the end, x: s
+    int* added;                              // [n_inst] s, then prompt tokens added
+    unsigned char* lists;                    // [2] of kSoloList: a batch's choices, and whether it was the last
+    int32_t* assigned;
+    int64_t* score100;
+    ps_status* st;
+};
+const int kSoloList = 64 * 8 + 16;           // int2 a request: instance + ramp * 2^16 (or -1), prompt
+size_t solo_lds_bytes(int n_inst) {
+    int lanes = 1;                           // R
+    while (64 * lanes < n_inst) lanes *= 2;
+    return (size_t)lanes * 1024 + 16 + 2 * kSoloList + (size_t)n_inst * 4;
+}
+
+// beta v, from -2^29 on: no request walked makes more than that of it.
+__device__ __forceinline__ int solo_penalty(int v, int beta) { return beta * max(v, -(1 << 29) / max(beta, 1)); }
+
+__device__ __forceinline__ int solo_at_state(const SoloWalk& a, int i) { return (i & ((1 << a.lanes_log2) - 1)) * 64 + (i >> a.lanes_log2); }
+
+// An instance's numbers: the largest w[t] + t, the first t that has it, the largest w; the largest ones from 0 on.
+__device__ __forceinline__ int4 solo_numbers(int f, int t, int most, int lim, int beta) {
+    return make_int4(solo_penalty(100 * f - lim, beta), t, solo_penalty(100 * most - lim, beta), lim);
+}
+
+struct SoloSlots {                           // a lane's two slots of a window
+    int t0, t1;
+    bool live0, live1;
+    int *w0, *w1;
+    __device__ __forceinline__ SoloSlots(const SoloWalk& a, int lane) {
+        t0 = lane;
+        t1 = lane + 64;
+        live0 = t0 < a.window;
+        live1 = t1 < a.window;
+        w0 = a.win + ((live0 ? t0 >> 2 : 0) * a.pitch * 4 + (t0 & 3));
+        w1 = a.win + ((live1 ? t1 >> 2 : 0) * a.pitch * 4 + (t1 & 3));
+    }
+};
+
+// The requests of a list go to their windows, and the instances' numbers are made afresh: wavefronts 1 to 7, an instance always
+// by the same one.
+__device__ __forceinline__ void solo_apply(const SoloWalk& a, const SoloSlots& sl, const unsigned char* list, int wave) {
+    const int lane = threadIdx.x & 63;
+    const int2 d = ((const int2*)list)[lane];
+    for (unsigned long long mask = __ballot(d.x >= 0 && (d.x & 0xffff) % (kSoloWaves - 1) == wave - 1); mask; mask &= mask - 1) {
+        const int q = __builtin_ctzll(mask), x = __builtin_amdgcn_readlane(d.x, q), P = __builtin_amdgcn_readlane(d.y, q);
+        const int i = x & 0xffff, Dc = x >> 16;
+        int4* const state = a.state + solo_at_state(a, i);
+        const int lim = state->w;
+        const int v0 = sl.w0[4 * i] + (sl.t0 < Dc ? P + sl.t0 : 0), v1 = sl.w1[4 * i] + (sl.t1 < Dc ? P + sl.t1 : 0);
+        if (sl.t0 < Dc) sl.w0[4 * i] = v0;
+        if (sl.t1 < Dc) sl.w1[4 * i] = v1;
+        // F * 256 + 255 - t: the largest has the first slot of the largest sum; 0 where all sums are below 0
+        const unsigned k0 = sl.live0 && v0 + sl.t0 >= 0 ? ((unsigned)(v0 + sl.t0) << 8) + 255 - sl.t0 : 0;
+        const unsigned k1 = sl.live1 && v1 + sl.t1 >= 0 ? ((unsigned)(v1 + sl.t1) << 8) + 255 - sl.t1 : 0;
+        const unsigned k = wave_umax(max(k0, k1));
+        const int most = (int)wave_umax((unsigned)max(max(sl.live0 ? v0 : 0, sl.live1 ? v1 : 0), 0));
+        if (lane == 0) *state = solo_numbers((int)(k >> 8), k ? 255 - (int)(k & 255) : a.window, most, lim, a.beta);
+        asm volatile("" ::: "memory");                           // (in order: the next one may be of the same instance)
+    }
+}
+
+// Wavefront 0's part; the others are in solo_follow.  Returns the first request not walked; heavy: it stopped for its effort.
+template <int R>
+__device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long bound, long long load_bound, bool& heavy_out) {
+    const int lane = threadIdx.x, window = a.window, beta = a.beta, beta100 = 100 * beta;
+    const SoloSlots sl(a, lane);
+    // score; its penalty at P = 0; an upper bound of that, above it where the penalty is an old one; t*; as its name
+    int s[R], p[R], u[R], top[R], low[R], id[R];
+    int cur = 0;                             // bit j: the list being made has instance j
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = lane * R + j;
+        id[j] = i;
+        s[j] = 1 << 30;
+        p[j] = u[j] = -(1 << 29);
+        top[j] = low[j] = 0;
+        if (i < a.n_inst) {
+            s[j] = a.added[i];
+            a.added[i] = 0;
+        }
+    }
+    int nP = 0, nD = 0;
+    if (base + lane < a.n_req) { nP = a.prompt_tokens[base + lane]; nD = a.pred_tokens[base + lane]; }
+    bool heavy = false, drain = false, last = false;
+    int vP = 0, vDc = 0, v_add = 0, cnt = 0, most = 0, effort = 0, out_i = -1, out_s = 0, buffer = 0;
+    unsigned long long todo = 0, part = 0;   // of the group: requests to walk; the batch at hand
+    bool open = false;                       // a group is being walked
+    for (;;) {
+        // ---- the numbers as the lists before the last one left them ----
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int i = lane * R + j;
+            if (i < a.n_inst && !drain && !(cur >> j & 1)) {     // (not while it only waits)
+                const int4 v = a.state[64 * j + lane];
+                p[j] = u[j] = v.x;
+                top[j] = v.y;
+                low[j] = v.z;
+            }
+        }
+        cur = 0;
+        // ---- the next group ----
+        if (!open && base < a.n_req && !heavy) {
+            cnt = min(64, a.n_req - base);
+            vP = nP;
+            int vD = nD;
+            if (base + 64 + lane < a.n_req) { nP = a.prompt_tokens[base + 64 + lane]; nD = a.pred_tokens[base + 64 + lane]; }
+            const bool good = lane < cnt && vP >= 0 && vD >= 0;
+            if (!__ballot(good && (vP >= kSoloTokens || vD >= kSoloTokens))) {
+                const int sum_p = wave_total(good ? vP : 0), sum_d = wave_total(good ? vD : 0);
+                const long long rise = sum_p + 64ll * window, load_rise = 100ll * ((long long)sum_p + sum_d);
+                if (peaks_fit(bound + rise, beta) && load_bound + load_rise < 1 << 29) {
+                    bound += rise;
+                    load_bound += load_rise;
+                    if (lane < cnt && !good) report_fault(a.st, PS_ST_BAD_RECORD, base + lane);
+                    vDc = min(vD, window);
+                    v_add = 100 * (vP + vD);
+                    most = (int)wave_umax(good ? (unsigned)vP : 0);
+                    out_i = -1;
+                    out_s = effort = 0;
+                    todo = __ballot(good);
+                    part = (1ull << kSoloBatch) - 1;
+                    open = true;
+                }
+            }
+        }
+        last = !open;
+        const unsigned long long before = todo;
+        if (!drain && todo) {
+            // ramps beyond `reach` pass t* of every instance that may be above its limit
+            int reach = 0;
+#pragma unroll
+            for (int j = 0; j < R; ++j) reach = p[j] + beta100 * most > 0 ? max(reach, top[j]) : reach;
+            reach = (int)wave_umax((unsigned)reach);
+            while (!(todo & part)) part <<= kSoloBatch;
+            unsigned long long now = todo & part;
+            int L[R], best, src, at, sure;                       // smallest score, its lane (the lowest), its place there
+            auto smallest = [&](int pb) {
+                int own = L[0];
+#pragma unroll
+                for (int j = 1; j < R; ++j) own = min(own, L[j]);
+                int m = dpp_min<0x111, 0xf>(own);                // as in wave_min
+                m = dpp_min<0x112, 0xf>(m);
+                m = dpp_min<0x114, 0xf>(m);
+                m = dpp_min<0x118, 0xf>(m);
+                m = dpp_min<0x142, 0xa>(m);
+                m = dpp_min<0x143, 0xc>(m);
+                int place = R - 1, up = u[R - 1], pen = p[R - 1];
+#pragma unroll
+                for (int j = R - 2; j >= 0; --j) {
+                    const bool here = L[j] == own;
+                    place = here ? j : place;
+                    up = here ? u[j] : up;
+                    pen = here ? p[j] : pen;
+                }
+                // an old penalty is a new one as long as neither passes the limit; bit 0: to be trusted, above it: place
+                place = place * 2 + (up == pen || up + pb <= 0);
+                best = __builtin_amdgcn_readlane(m, 63);
+                src = __builtin_ctzll(__ballot(own == best));
+                at = __builtin_amdgcn_readlane(place, src);
+                sure = at & 1;
+                at >>= 1;
+            };
+            auto commit = [&](int q, int add, int lift) {
+                const int i = src * R + at;
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const bool hit = id[j] == i;
+                    s[j] += hit ? add : 0;
+                    u[j] += hit ? lift : 0;
+                }
+                cur |= lane == src ? 1 << at : 0;
+                const bool rec = lane == q;
+                out_i = rec ? i : out_i;
+                out_s = rec ? best + add : out_s;
+            };
+            do {
+                int q;
+                // one way through, with one branch out of it: a taken branch costs as much as five instructions
+                for (;;) {
+                    q = __builtin_ctzll(now);
+                    const int P = __builtin_amdgcn_readlane(vP, q), Dc = __builtin_amdgcn_readlane(vDc, q);
+                    const int add = __builtin_amdgcn_readlane(v_add, q), pb = beta100 * P;
+#pragma unroll
+                    for (int j = 0; j < R; ++j) L[j] = s[j] + max(p[j] + pb, 0);
+                    smallest(pb);
+                    if (__builtin_expect((Dc <= reach) | (sure == 0), 0)) break;
+                    commit(q, add, pb + beta100 * Dc);
+                    now &= now - 1;
+                    if (!now) break;
+                }
+                if (!now) break;
+                // a ramp that ends before some t*, or an instance whose numbers are not made yet
+                const int P = __builtin_amdgcn_readlane(vP, q), Dc = __builtin_amdgcn_readlane(vDc, q);
+                const int add = __builtin_amdgcn_readlane(v_add, q), pb = beta100 * P;
+#pragma unroll
+                for (int j = 0; j < R; ++j) L[j] = s[j] + max(top[j] < Dc ? p[j] + pb : low[j], 0);
+                unsigned seen = 0;                               // the lane's instances whose window has been read
+                for (;;) {
+                    smallest(pb);
+                    const int i = src * R + at;
+                    bool bound_only = false;
+#pragma unroll
+                    for (int j = 0; j < R; ++j)
+                        bound_only |= id[j] == i && top[j] >= Dc && p[j] + pb > 0 && !(seen >> j & 1);
+                    if (!sure || !__ballot(bound_only)) break;
+                    int pk = 0;                                  // (a peak below 0 is no more over a limit than one of 0)
+                    if (sl.live0) pk = max(pk, sl.w0[4 * i] + (sl.t0 < Dc ? P + sl.t0 : 0));
+                    if (sl.live1) pk = max(pk, sl.w1[4 * i] + (sl.t1 < Dc ? P + sl.t1 : 0));
+                    pk = (int)wave_umax((unsigned)pk);
+                    const int over = beta * max(100 * pk - a.state[64 * at + src].w, 0);
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        L[j] = id[j] == i ? s[j] + over : L[j];
+                        seen |= id[j] == i ? 1u << j : 0u;
+                    }
+                    ++effort;
+                }
+                if (!sure) {
+                    drain = true;
+                    effort += 5;
+                    break;
+                }
+                commit(q, add, pb + beta100 * Dc);
+                now &= now - 1;
+            } while (now);
+            todo = (todo & ~part) | now;
+        } else {
+            drain = false;
+        }
+        // ---- the batch's choices to the other wavefronts ----
+        unsigned char* const list = a.lists + buffer * kSoloList;
+        const bool done = (before & ~todo) >> lane & 1;
+        ((int2*)list)[lane] = make_int2(done && vDc > 0 ? out_i | vDc << 16 : -1, vP);
+        if (lane == 0) *(int*)(list + 64 * 8) = last;
+        buffer ^= 1;
+        if (open && !todo) {
+            if (out_i >= 0) atomicAdd(a.added + out_i, vP);
+            if (lane < cnt) {
+                a.assigned[base + lane] = out_i;
+                a.score100[base + lane] = out_s;
+            }
+            base += 64;
+            open = false;
+            heavy = effort > kSoloEffort;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (last) break;
+    }
+    // (the last list is empty, the one before it has been applied)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if (lane * R + j < a.n_inst) a.state[64 * j + lane].x = s[j];
+    heavy_out = heavy;
+    return base;
+}
+__device__ __forceinline__ void solo_follow(const SoloWalk& a, int wave) {
+    const SoloSlots sl(a, threadIdx.x & 63);
+    for (int buffer = 0;; buffer ^= 1) {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const unsigned char* list = a.lists + buffer * kSoloList;
+        if (__builtin_amdgcn_readfirstlane(*(const int*)(list + 64 * 8))) break;
+        solo_apply(a, sl, list, wave);
+    }
+}
+
 // Launched with 1024 threads: all of them bring the windows in, then the wavefronts without instances leave.
 // CH: 16-byte pieces of a block (1, 2 or 4: windows of at most 32 pieces, which an update takes a lane each; 0: any
 // plan, a lane takes a block).  NARROW: with walk_narrow, for calls of 12 requests and more, where it saves over a
 // microsecond of a call by itself; its bounds cost a call of few (256 instances of 100 slots, 3 requests 27.5 us without,
 // 27.6 with, 8 30.9 and 29.8, 12 34.1 and 31.8; 64 instances 23.7 and 24.2, 26.3 and 25.9, 28.2 and 27.5).
-template <int CH, bool NARROW>
-__global__ __launch_bounds__(kRouteThreads) void route_kernel(
+// SOLO: with one wavefront's walk, NARROW too; 512 threads, all of which stay (the walk's registers do not fit sixteen wavefronts).
+template <int CH, bool NARROW, bool SOLO>
+__global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_kernel(
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
     int window, int block, int n_blocks, int pitch, int32_t* __restrict__ window_tokens,
     const int32_t* __restrict__ capacity, int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct,
-    int beta, int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st) {
+    int beta, int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st, int solo_at) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int kWaves = SOLO ? kSoloWaves : 16;
     int4* s_best = (int4*)lds_raw;                               // [2][16] a wavefront's minimum: score, instance
     int4* s_win = (int4*)(lds_raw + 512);                        // [pieces][pitch]
     const int pieces = n_blocks * (block >> 2);
@@ -135,16 +454,16 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     // nothing is ever added
     for (int t0 = 0; t0 < 4 * pieces; t0 += 64) {
         const int t = t0 + lane;
-        for (int i0 = wave; i0 < n_inst; i0 += 16 * 8) {
+        for (int i0 = wave; i0 < n_inst; i0 += kWaves * 8) {
             int v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 16 * u;
+                const int i = i0 + kWaves * u;
                 v[u] = i < n_inst && t < window ? window_tokens[(int64_t)i * window + t] : kMin;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + 16 * u;
+                const int i = i0 + kWaves * u;
                 if (i < n_inst && t < 4 * pieces) ((int*)(s_win + (t >> 2) * pitch + i))[t & 3] = v[u];
             }
         }
@@ -161,8 +480,15 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         s_suf[n_blocks * pitch + inst] = kMin;
     }
     if (tid < 32) s_best[tid] = make_int4(0x7fffffff, 0, 0, 0);
+    // the one wavefront's walk: its share of LDS (there with SOLO)
+    int4* const s_state = (int4*)(lds_raw + solo_at);
+    const int lanes_log2 = nw == 1 ? 0 : 32 - __builtin_clz(nw - 1);
+    int* const s_exit = (int*)(s_state + (64 << lanes_log2));
+    unsigned char* const s_lists = (unsigned char*)(s_exit + 4);
+    int* const s_added = (int*)(s_lists + 2 * kSoloList);
     __syncthreads();
-    if (wave >= nw) return;
+    if (!SOLO && wave >= nw) return;
+    const bool owner = wave < nw;
 
     // One instance's window with a request's ramp added on its first Dc slots, and its two rows of block maxima:
     // all lanes of its wavefront, lane j and lane 32 + n_parts - 1 - j for part j (a piece or a block) of the window.
@@ -203,60 +529,70 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         // keep that order
         asm volatile("" ::: "memory");
     };
-    if (CH > 0) {
-        // every thread its own instance's rows
-        if (mine) {
-            int m = kMin;
-            for (int b = 0; b < n_blocks; ++b) {
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int4 v = s_win[(b * CH + c) * pitch + inst];
-                    const int t = 4 * (b * CH + c);
-                    // (one piece a block: its first slot is inside.  Not said to the NARROW kernel, whose walk comes out
-                    // 0.4 % slower: 4096 requests over 256 instances 2035 us, 2044)
-                    if ((CH == 1 && !NARROW) || t < window) m = max(m, (int)((unsigned)v.x + (unsigned)t));
-                    if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
-                    if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
-                    if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
-                }
-                s_pre[(b + 1) * pitch + inst] = m;
-            }
-            m = kMin;
-            for (int b = n_blocks - 1; b >= 0; --b) {
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int4 v = s_win[(b * CH + c) * pitch + inst];
-                    m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
-                }
-                s_suf[b * pitch + inst] = m;
-            }
-        }
-        asm volatile("" ::: "memory");
-    } else if (n_blocks > 0) {
-        for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(std::false_type{}, i, 0, 0);
-    }
     // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
     int par = 0;
     // The largest of the lanes' values (0 at the least), uniform over the workgroup.
     auto largest = [&](int top) {
         for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
-        if (nw > 1) {
+        if (SOLO || nw > 1) {                                    // (all wavefronts of SOLO)
             if (lane == 0) s_best[par + wave].x = top;           // (the slots that are written next)
             __syncthreads();
-            for (int w = 0; w < nw; ++w) top = max(top, s_best[par + w].x);
+            for (int w = 0; w < (SOLO ? kWaves : nw); ++w) top = max(top, s_best[par + w].x);
             __syncthreads();
+            if (SOLO && lane == 0) s_best[par + wave].x = 0x7fffffff;
         }
         return __builtin_amdgcn_readfirstlane(max(top, 0));
+    };
+
+    auto make_tables = [&]() {
+        if (CH > 0) {
+            // every thread its own instance's rows
+            if (mine) {
+                int m = kMin;
+                for (int b = 0; b < n_blocks; ++b) {
+    #pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        const int4 v = s_win[(b * CH + c) * pitch + inst];
+                        const int t = 4 * (b * CH + c);
+                        // (one piece a block: its first slot is inside.  Not said to the NARROW kernel, whose walk comes out
+                        // 0.4 % slower: 4096 requests over 256 instances 2035 us, 2044)
+                        if ((CH == 1 && !NARROW) || t < window) m = max(m, (int)((unsigned)v.x + (unsigned)t));
+                        if (t + 1 < window) m = max(m, (int)((unsigned)v.y + (unsigned)(t + 1)));
+                        if (t + 2 < window) m = max(m, (int)((unsigned)v.z + (unsigned)(t + 2)));
+                        if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
+                    }
+                    s_pre[(b + 1) * pitch + inst] = m;
+                }
+                m = kMin;
+                for (int b = n_blocks - 1; b >= 0; --b) {
+    #pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        const int4 v = s_win[(b * CH + c) * pitch + inst];
+                        m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
+                    }
+                    s_suf[b * pitch + inst] = m;
+                }
+            }
+            asm volatile("" ::: "memory");
+        } else if (n_blocks > 0) {
+            for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(std::false_type{}, i, 0, 0);
+        }
     };
 
     const long long kNone = 0x7fffffffffffffffll;
     const int ic = mine ? inst : 0;
     const int row4 = pitch * 4, row16 = pitch * 16;              // bytes from a row of the tables to the next
-    int nP = 0, nD = 0;                                          // lane l: request l of the next 64
-    if (lane < n_req) { nP = prompt_tokens[lane]; nD = pred_tokens[lane]; }
     // The requests of one group of 64.  FAR: their tokens could take a sum, or one of the tables' w[t] + t, to 2^31, so
     // they are scored slot by slot in 64 bits.
     auto walk = [&](auto far, int base, int cnt, int vP, int vD) {
+        if (SOLO && !owner) {                                    // (along for the barriers)
+            const int n = nw > 1 ? __popcll(__ballot(lane < cnt && vP >= 0 && vD >= 0)) : 0;
+            for (int q = 0; q < n; ++q) {
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                par ^= 16;
+            }
+            return;
+        }
         // blocks below b lie under the request's ramp whole, block b is looked at slot by slot (where the ramp ends on
         // a block boundary that only repeats what the tables say), blocks from the next one on keep their values
         const int vDc = min(max(vD, 0), window), vb = n_blocks > 0 ? vDc / block : 0;
@@ -321,6 +657,14 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     // request's ramp adds to the block it ends in is worked out for 64 requests at once; what it adds to a lane's slots of
     // the chosen window, while the exchange is under way.
     auto walk_narrow = [&](auto many, int base, int cnt, int vP, int vD) {
+        if (SOLO && !owner) {
+            if (many.value)
+                for (int n = __popcll(__ballot(lane < cnt && vP >= 0 && vD >= 0)); n > 0; --n) {
+                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    par ^= 16;
+                }
+            return;
+        }
         constexpr int B = CH ? 4 * CH : 4;                       // slots of a block
         const int vDc = min(max(vD, 0), window), vb = vDc / B, vw = min(vb, n_blocks - 1);
         const int v_pre = vb * row4, v_suf = (vDc + B - 1) / B * row4, v_win = vw * (B / 4) * row16;
@@ -421,13 +765,81 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     };
     // bound: no window value is above it, load_bound: no instance's queue, a hundredfold, is (a request raises them by its
     // tokens and the window; taken afresh when that has added up).  A queue or limit below 0 counts as one without bound.
-    long long bound = largest(mine ? s_suf[ic] : kMin);
     auto load100 = [&]() { return mine ? (s100 < 0 || thr < 0 || s100 >= 1 << 30 ? 1 << 30 : (int)s100) : 0; };
-    bool narrow = NARROW;
-    long long load_bound = narrow ? largest(load100()) : 0;
-    for (int base = 0; base < n_req; base += 64) {
-        const int cnt = min(64, n_req - base), vP = nP, vD = nD;
-        if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
+    long long bound = 0, load_bound = 0;
+    bool narrow = NARROW, tables = false;
+    // groups of 64 requests to walk with the tables before the next solo_walk; twice as many each time that one stops for
+    // too many windows read
+    int wait = 0, spell = 1;
+    int ahead = -1, nP = 0, nD = 0;                              // lane l: request ahead + l
+    for (int base = 0; base < n_req;) {
+        if (SOLO && narrow && wait == 0) {
+            int most = 0;
+            if (mine) {
+                int f = -1, t_f = window;                        // where no sum reaches 0, no ramp reaches beyond t*
+                for (int t = 0; t < window; t += 4) {
+                    const int4 v = s_win[(t >> 2) * pitch + inst];
+                    const int x[4] = {v.x, v.y, v.z, v.w};       // (slots behind the window hold the minimum)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int at = (int)((unsigned)x[e] + (t + e < window ? (unsigned)(t + e) : 0u));
+                        most = max(most, x[e]);
+                        if (at > f) { f = at; t_f = t + e; }
+                    }
+                }
+                const int lim = (int)min(thr, 0x7fffffffll);
+                s_state[(inst & ((1 << lanes_log2) - 1)) * 64 + (inst >> lanes_log2)] =
+                    solo_numbers(max(f, 0), t_f, most, lim, beta);
+                s_added[inst] = (int)s100;
+            }
+            bound = largest(most);
+            load_bound = largest(load100());
+            const SoloWalk a = {prompt_tokens, pred_tokens, n_req, n_inst, window, pitch, beta, (int*)s_win, lanes_log2, s_state, s_added,
+                                s_lists, assigned, score100, st};
+            if (!peaks_fit(bound, beta) || load_bound >= 1 << 29) {
+                narrow = false;                                  // (neither ever falls)
+                continue;
+            }
+            if (wave == 0) {
+                bool heavy;
+                const int to = nw == 2   ? solo_walk<2>(a, base, bound, load_bound, heavy)
+                               : nw <= 4 ? solo_walk<4>(a, base, bound, load_bound, heavy)
+                                         : solo_walk<8>(a, base, bound, load_bound, heavy);
+                if (lane == 0) { s_exit[0] = to; s_exit[1] = heavy; }
+            } else {
+                solo_follow(a, wave);
+            }
+            __syncthreads();
+            if (mine) {
+                const int rise = s_state[(inst & ((1 << lanes_log2) - 1)) * 64 + (inst >> lanes_log2)].x - (int)s100, dP = s_added[inst];
+                s100 += rise;
+                qp += dP;
+                cd += rise / 100 - dP;
+            }
+            const int to = __builtin_amdgcn_readfirstlane(s_exit[0]);
+            const bool heavy = __builtin_amdgcn_readfirstlane(s_exit[1]);
+            if (heavy) {
+                wait = spell;
+                spell = min(2 * spell, 64);
+            } else {
+                spell = 1;
+                if (to == base) wait = 1;                        // (the bounds of this group do not do)
+            }
+            base = to;
+            tables = false;
+            continue;
+        }
+        if (!tables) {
+            make_tables();
+            tables = true;
+            bound = largest(mine ? s_suf[ic] : kMin);
+            if (narrow) load_bound = largest(load100());
+        }
+        const int cnt = min(64, n_req - base);
+        if (ahead != base && lane < cnt) { nP = prompt_tokens[base + lane]; nD = pred_tokens[base + lane]; }
+        const int vP = nP, vD = nD;
+        ahead = base + 64;
+        if (ahead + lane < n_req) { nP = prompt_tokens[ahead + lane]; nD = pred_tokens[ahead + lane]; }
         // largest prompt and prediction of the group
         int most = lane < cnt ? max(vP, 0) : 0, most_d = lane < cnt ? max(vD, 0) : 0;
         for (int o = 32; o > 0; o >>= 1) {
@@ -437,14 +849,12 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         most = __builtin_amdgcn_readfirstlane(most);
         const long long rise = 64ll * ((long long)most + window);
         const long long load_rise = 6400ll * ((long long)most + __builtin_amdgcn_readfirstlane(most_d));
-        // what walk_narrow asks for: peaks below 2^24, penalties and the rest of a score below 2^29
-        auto peaks_fit = [&](long long peak) { return peak < 1 << 24 && peak * 100 * max(beta, 1) < 1 << 29; };
-        auto fits = [&]() { return peaks_fit(bound + rise) && load_bound + load_rise < 1 << 29; };
+        auto fits = [&]() { return peaks_fit(bound + rise, beta) && load_bound + load_rise < 1 << 29; };
         if ((narrow && !fits()) || bound + rise >= 2147483647ll) {
             bound = largest(mine ? s_suf[ic] : kMin);
             if (narrow) {
                 load_bound = largest(load100());
-                narrow = peaks_fit(bound) && load_bound < 1 << 29;     // (neither ever falls)
+                narrow = peaks_fit(bound, beta) && load_bound < 1 << 29;     // (neither ever falls)
             }
         }
         if (NARROW && narrow && fits()) {
@@ -454,6 +864,10 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
         else walk(std::false_type{}, base, cnt, vP, vD);
         bound += rise;
         load_bound += load_rise;
+        base += 64;
+        if (wait > 0) --wait;
+        // (solo_walk's wavefront goes on with windows that others have written)
+        if (SOLO && wait == 0) __syncthreads();
     }
     if (range_fault) report_fault(st, PS_ST_RANGE, -1);
     if (mine) { queued_p[inst] = qp; current_d[inst] = cd; }
@@ -720,7 +1134,7 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     // last one, a single block per window, takes less)
     const size_t map_bytes = (size_t)n_inst * 20 + (size_t)n_inst * window * 4 + 20928;
     if (map_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
-    const RoutePlan p = plan_route(n_inst, window);
+    RoutePlan p = plan_route(n_inst, window, kRouteLdsBytes);
     if (p.lds_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
@@ -730,38 +1144,59 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
                                 kRouteLdsBytes) != hipSuccess ||
             hipFuncSetAttribute((const void*)route_reg_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<0, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<0, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<1, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<1, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<1, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<2, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<4, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<2, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute((const void*)route_kernel<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void*)route_kernel<2, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<4, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<4, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kRouteLdsBytes) != hipSuccess ||
+            hipFuncSetAttribute((const void*)route_kernel<4, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRouteLdsBytes) != hipSuccess)
             return PS_EHIP;
         lds_attr_set = true;
     }
-#define PS_ROUTE(...)                                                                                                    \
-    hipLaunchKernelGGL((route_kernel<__VA_ARGS__>), dim3(1), dim3(kRouteThreads), p.lds_bytes, s, prompt_tokens, pred_tokens, \
-                       n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens, capacity, queued_p,           \
-                       current_d, t_mem_pct, beta, assigned, score100, status)
+#define PS_ROUTE(CH, NARROW, SOLO)                                                                                       \
+    hipLaunchKernelGGL((route_kernel<CH, NARROW, SOLO>), dim3(1), dim3(SOLO ? 64 * kSoloWaves : kRouteThreads), p.lds_bytes, s,    \
+                       prompt_tokens, pred_tokens, n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens,   \
+                       capacity, queued_p, current_d, t_mem_pct, beta, assigned, score100, status, solo_at)
+#define PS_ROUTE_CH(CH)                                \
+    do {                                               \
+        if (solo_at) PS_ROUTE(CH, true, true);         \
+        else if (narrow) PS_ROUTE(CH, true, false);    \
+        else PS_ROUTE(CH, false, false);               \
+    } while (0)
+    int solo_at = 0;
     if (tables_pay(n_req, window, p)) {
         const bool narrow = n_req >= 12;
-        if (!by_piece(p)) PS_ROUTE(0, false);
-        else if (p.block == 4 && narrow) PS_ROUTE(1, true);
-        else if (p.block == 4) PS_ROUTE(1, false);
-        else if (p.block == 8 && narrow) PS_ROUTE(2, true);
-        else if (p.block == 8) PS_ROUTE(2, false);
-        else if (narrow) PS_ROUTE(4, true);
-        else PS_ROUTE(4, false);
+        if (narrow && by_piece(p) && n_inst > 64 && n_inst <= kSoloInstances) {
+            // room for one wavefront's walk, if need be with the next larger blocks
+            const size_t more = solo_lds_bytes(n_inst);
+            const RoutePlan smaller = plan_route(n_inst, window, kRouteLdsBytes - more);
+            if (by_piece(smaller) && (smaller.lds_bytes + 15) / 16 * 16 + more <= (size_t)kRouteLdsBytes) {
+                p = smaller;
+                solo_at = (int)((p.lds_bytes + 15) / 16 * 16);
+                p.lds_bytes = solo_at + more;
+            }
+        }
+        if (!by_piece(p)) PS_ROUTE(0, false, false);
+        else if (p.block == 4) PS_ROUTE_CH(1);
+        else if (p.block == 8) PS_ROUTE_CH(2);
+        else PS_ROUTE_CH(4);
         return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
     }
+#undef PS_ROUTE_CH
 #undef PS_ROUTE
     int tpi = 64;                                               // threads per instance: a power of two, <= 64
     while (tpi > 1 && (int64_t)tpi * n_inst > kRouteThreads) tpi >>= 1;

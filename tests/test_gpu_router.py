@@ -156,6 +156,42 @@ def test_values_that_pass_the_bounds_of_the_short_form(K, l, beta, peak, queued)
     assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
 
 
+@pytest.mark.parametrize("K,l,n", [(1, 16, 70), (5, 100, 300), (64, 128, 200), (65, 33, 130), (130, 100, 400),
+                                   (256, 100, 1000), (256, 128, 150), (300, 60, 200), (700, 40, 300), (1000, 30, 300)])
+@pytest.mark.parametrize("load", ["free", "mixed", "filling", "ties", "all over", "one by one"])
+def test_walk_in_order_of_scores(K, l, n, load):
+    """Requests that go to the smallest queue while every window is below its limit (the sorted walk), with instances over
+    and near their limits among them, limits reached on the way, equal scores, requests that add nothing, faulty ones and
+    lists that end inside a group of 64.  Integers: everything must match."""
+    print(f"route sorted K={K} l={l} n={n} {load}", flush=True)
+    rng = np.random.default_rng(K * 131 + l + n)
+    P, D, win, cap, qp, cd = random_case(rng, K, l, n, False)
+    level = {"free": 0.1, "mixed": 1.0, "filling": 0.0, "ties": 0.0, "all over": 1.0, "one by one": 0.0}[load]
+    win = np.rint(rng.random((K, 1)) * level * cap[:, None] * (1.0 - 0.5 * np.arange(l) / l)).astype(np.int64)
+    if load == "all over":
+        win += cap[:, None]
+    if load == "filling":                                       # some requests each before the limit
+        cap = 600 + 40 * np.arange(K) % 3000
+    if load == "ties":
+        qp[:], cd[:] = 7, 11
+        P[rng.random(n) < 0.3] = 40
+        D[P == 40] = 60
+    if load == "one by one":                                    # one instance takes all, until it is at its limit
+        qp = qp + 30_000
+        qp[K // 2] = 0
+        cap[K // 2] = 4000
+    P[rng.random(n) < 0.1] = 0
+    D[rng.random(n) < 0.1] = 0
+    bad = rng.random(n) < 0.03
+    P[bad] = -1
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ok = ~bad
+    ra, rs, rw, rq, rc = orr.route(P[ok], D[ok], win, cap, qp, cd)
+    assert flags == (ps.PS_ST_BAD_RECORD if bad.any() else 0)
+    assert np.array_equal(a[ok], ra) and np.array_equal(s[ok], rs) and (a[bad] == -1).all() and (s[bad] == 0).all()
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
 def test_state_of_an_instance_with_huge_queues():
     """The state is carried exactly in int64 also where a hundredfold no longer fits (10^17 tokens as a mark of an
     instance that is out of use)."""
