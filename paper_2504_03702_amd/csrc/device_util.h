@@ -185,3 +185,31 @@ __device__ __forceinline__ void gather_runs(uint32_t (&u)[2][2][R]) {
             u[1][b][r] = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
         }
 }
+
+// ---- LayerNorm of narrow fp32 rows (hidden a multiple of 32, at most PS_NARROW_WIDTH) ----------------------------------
+// In eight parts: part 2 w + h has the upper (h) or lower four of every eight elements in the w-th quarter of the row, adds
+// them up four at a time, and the parts' sums are paired neighbour by neighbour.
+__device__ __forceinline__ float narrow_quad(float a, float b, float c, float d) { return (a + b) + (c + d); }
+__device__ __forceinline__ float narrow_squares(float a, float b, float c, float d) {
+    return fmaf(a, a, b * b) + fmaf(c, c, d * d);
+}
+// (mean, 1 / std) of row x by eight neighbouring lanes, lane `part` of them; all get it.
+__device__ __forceinline__ float2 narrow_moments(const float* x, int H, float eps, int part) {
+    const int groups = H / 8, g0 = groups * (part >> 1) / 4, g1 = groups * ((part >> 1) + 1) / 4, at = 4 * (part & 1);
+    auto all = [](float v) {
+        v += __shfl_xor(v, 1, 64);
+        v += __shfl_xor(v, 2, 64);
+        return v + __shfl_xor(v, 4, 64);
+    };
+    float sum = 0.f, sq = 0.f;
+    for (int g = g0; g < g1; ++g) {
+        const float4 v = *(const float4*)(x + 8 * g + at);
+        sum += narrow_quad(v.x, v.y, v.z, v.w);
+    }
+    const float mean = all(sum) / (float)H;      // (a product would be contracted with what follows, here or there)
+    for (int g = g0; g < g1; ++g) {
+        const float4 v = *(const float4*)(x + 8 * g + at);
+        sq += narrow_squares(v.x - mean, v.y - mean, v.z - mean, v.w - mean);
+    }
+    return make_float2(mean, 1.0f / sqrtf(all(sq) / (float)H + eps));
+}

@@ -109,6 +109,9 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
 void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* pred_f, int32_t* pred_tokens,
                  ps_status* st, hipStream_t s);
 void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipStream_t s);
+#define PS_NARROW_WIDTH 256  // fp32 models up to this hidden size (a multiple of 32): LayerNorms in one order of sums everywhere
+// Whether that leaves the last layer's sums, not their LayerNorm, in ws.x (calls of few rows through a narrow model).
+bool f32_maps_take_norms(const ps_model_info& info, int64_t max_rows);
 void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hipStream_t s);
 
 // bf16 kernels

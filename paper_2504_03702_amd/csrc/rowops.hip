@@ -197,12 +197,22 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int total = meta->total_rows;
+    // calls of at most 64 requests: what a lane's request has is one trip to memory, and a count of the starts up to the row
+    // finds the row's own (by bisection and one after the other it was a trip each: 768 rows of 16 requests, hidden 128, 5.0 ->
+    // 4.4 us)
+    const int few = n_req <= 64 ? min(lane, n_req - 1) : -1;
+    const int q_start = few >= 0 ? row_start[few] : 0, q_len = few >= 0 ? seq_len[few] : 0, q_first = few >= 0 ? offsets[few] : 0;
     const int64_t live = ((int64_t)total + PS_KEY_SLACK + PS_ROW_TILE - 1) / PS_ROW_TILE * PS_ROW_TILE;
     if (row >= live) return;
     T* out = x + row * H;
     bf16_t* yrow = lo_out ? lo_out + row * H : nullptr;  // bf16 path: lo parts of the sums, and row statistics
-    int r = -1, p = 0;
-    if (row < total) {
+    int r = -1, p = 0, S = 0, first = 0;
+    if (row < total && few >= 0) {
+        r = __popcll(__ballot(lane < n_req && q_start <= row)) - 1;
+        p = (int)(row - __builtin_amdgcn_readlane(q_start, r));
+        S = __builtin_amdgcn_readlane(q_len, r);
+        first = __builtin_amdgcn_readlane(q_first, r);
+    } else if (row < total) {
         int lo = 0, hi = n_req - 1;          // largest r with row_start[r] <= row
         while (lo < hi) {
             int mid = (lo + hi + 1) >> 1;
@@ -210,8 +220,9 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
         }
         r = lo;
         p = (int)(row - row_start[r]);
+        S = seq_len[r];
+        first = offsets[r];
     }
-    const int S = r >= 0 ? seq_len[r] : 0;
     if (r < 0 || p >= S) {
         for (int i = lane; i < H; i += 64) {
             store_elem<T>(out, i, 0.f);
@@ -225,7 +236,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
     const int n_text = S - n_soft;
     const T* src;
     if (p < n_text) {
-        const int id = token_ids[offsets[r] + p];
+        const int id = token_ids[first + p];
         if (id < 0 || id >= vocab) {
             // faulty request: flagged here, its row zeroed; the head reports NaN / -1 for it
             if (lane == 0) {
@@ -342,6 +353,7 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
     extern __shared__ float s_c[];           // [H], kHeadWaves partial sums, [kHeadWaves][kHeadSlots] the rounds' sums
     const int r = blockIdx.x / parts, part = blockIdx.x - r * parts;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t crow = row_start[r];       // (with the two others: one trip)
     if (seq_len[r] <= 0 || bad_req[r]) {
         if (threadIdx.x == 0 && part == 0) {
             pred_f[r] = __builtin_nanf("");
@@ -370,7 +382,6 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
     };
     if (wide) load_w(u0 + wave, 0);
     asm volatile("" ::: "memory");
-    const int64_t crow = row_start[r];
     if (y_lo) {
         // bf16 models (H at most 2048: two elements a thread): x holds the hi parts of the last sums
         const bf16_t* hi = (const bf16_t*)x + crow * H;
@@ -383,6 +394,12 @@ __global__ __launch_bounds__(kHeadWaves * 64) void head_kernel(const T* __restri
         const float rstd = 1.0f / sqrtf(head_block_sum(fmaf(d0, d0, d1 * d1), s_c + H) / (float)H + eps);
         if (i0 < H) s_c[i0] = fmaf(d0 * rstd, ln_g[i0], ln_b[i0]);
         if (i1 < H) s_c[i1] = fmaf(d1 * rstd, ln_g[i1], ln_b[i1]);
+    } else if (ln_g) {
+        // fp32 models whose maps take the LayerNorms (hidden at most PS_NARROW_WIDTH): x holds the last sums
+        const float* c = (const float*)x + crow * H;
+        const int i = threadIdx.x;
+        const float2 st = narrow_moments(c, H, eps, i & 7);      // (by every eight lanes)
+        if (i < H) s_c[i] = fmaf((c[i] - st.x) * st.y, ln_g[i], ln_b[i]);
     } else {
         const T* c = x + crow * H;
         for (int i = threadIdx.x; i < H; i += kHeadWaves * 64) s_c[i] = load_elem<T>(c, i);
@@ -515,6 +532,7 @@ void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* p
     int parts = 256 / n_req < rounds ? 256 / n_req : rounds;
     if (parts < 1 || rounds > kHeadSlots) parts = 1;
     const dim3 grid((unsigned)n_req * (unsigned)parts);
+    const bool sums = f.dtype != 1 && f32_maps_take_norms(f, ws.max_rows);
     if (f.dtype == 1)
         hipLaunchKernelGGL(head_kernel<bf16_t>, grid, dim3(kHeadWaves * 64), lds, s, (const bf16_t*)ws.x, ws.seq_len, ws.row_start,
                            ws.bad_req, (const bf16_t*)ws.la, (const float*)m->layers.back().ln2_g,
@@ -522,7 +540,8 @@ void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* p
                            m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f, pred_tokens, st);
     else
         hipLaunchKernelGGL(head_kernel<float>, grid, dim3(kHeadWaves * 64), lds, s, (const float*)ws.x, ws.seq_len, ws.row_start,
-                           ws.bad_req, (const bf16_t*)nullptr, (const float*)nullptr, (const float*)nullptr, 0.f, f.hidden,
+                           ws.bad_req, (const bf16_t*)nullptr, sums ? (const float*)m->layers.back().ln2_g : nullptr,
+                           sums ? (const float*)m->layers.back().ln2_b : nullptr, m->ln_eps, f.hidden,
                            f.head_hidden, m->w_h1t, m->b_h1, m->w_h2, m->b_h2, f.d_max, parts, ws.head_sum, ws.head_done, pred_f,
                            pred_tokens, st);
 }

@@ -277,3 +277,24 @@ def test_more_feed_forward_units_than_a_grid_has_tiles(tmp_models):
     assert flags == 0
     assert rel_err(got_f, ref_f).max() < TOL_FP32
     check_tokens(got_f, got_t, ref_t, cfg.d_max)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn", [(32, 1, 32), (96, 3, 160), (128, 2, 512), (224, 7, 96), (256, 4, 1024),
+                                              (256, 4, 100), (288, 4, 64)])
+def test_maps_that_take_the_layer_norms(tmp_models, hidden, heads, ffn):
+    """Narrow models in calls of few rows, where the maps make the LayerNorms of their operands and residuals themselves, on
+    both sides of that rule (rows, widths): against the oracle, and the same requests in calls of other sizes to the bit."""
+    cfg = wl.ModelConfig(layers=2, hidden=hidden, heads=heads, ffn=ffn, vocab=500, max_pos=80, n_soft=0, head_hidden=48,
+                         dtype=wl.DTYPE_FP32)
+    model, ref = make(tmp_models, f"norms{hidden}_{ffn}.bin", cfg=cfg, ln_jitter=0.1, bias_std=0.05)
+    rng = np.random.default_rng(hidden + ffn)
+    lengths = rng.integers(1, 81, 150).astype(np.int32)
+    batch = wl.pack_prompts(lengths, rng.integers(0, cfg.vocab, int(lengths.sum())).astype(np.int32))
+    got_f, got_t, flags, _ = run_predict(model, batch)
+    ref_f, ref_t = op.predict_load(ref, batch.token_ids, batch.offsets)
+    assert flags == 0 and rel_err(got_f, ref_f).max() < TOL_FP32
+    check_tokens(got_f, got_t, ref_t, cfg.d_max)
+    for n in (1, 3, 30):
+        part = wl.pack_prompts(lengths[:n], batch.token_ids[: int(batch.offsets[n])])
+        f, _, flags, _ = run_predict(model, part)
+        assert flags == 0 and np.array_equal(f, got_f[:n]), n
