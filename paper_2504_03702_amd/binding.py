@@ -2,7 +2,9 @@
 
 Argument marshalling only: tensors supply device pointers, ``torch.cuda.current_stream()`` the
 stream; every step of the path runs in the library's HIP kernels.  There is no fallback: if the
-library is missing or there is no GPU the calls raise."""
+library is missing or there is no GPU the calls raise.  The calls with nothing to object to are
+marshalled by an extension module (``csrc/marshal.cpp``); what it hands back is marshalled here,
+with the checks that say what is wrong."""
 from __future__ import annotations
 
 import ctypes
@@ -42,11 +44,12 @@ class ps_status(ctypes.Structure):
 
 
 _lib = None
+_native = None          # the extension module, bound to the loaded library
 
 
 def load_library() -> ctypes.CDLL:
     """Load ``libpreserve.so`` (built in-tree by ``build.py``) and declare its entry points."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -91,6 +94,10 @@ def load_library() -> ctypes.CDLL:
     lib.ps_profile_stream_read.argtypes = [vp, ctypes.c_int64, vp, vp]
     lib.ps_strerror.restype = ctypes.c_char_p
     lib.ps_strerror.argtypes = [ctypes.c_int]
+    from . import _marshal
+    _marshal.bind(*[ctypes.cast(getattr(lib, "ps_" + name), vp).value for name in (
+        "predict_load", "anticipate", "anticipate_static", "lookahead_update", "scaler_scan", "route", "forecast")])
+    _native = _marshal
     _lib = lib
     return lib
 
@@ -105,6 +112,19 @@ def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, name: str) -> Optional[i
 
 def _stream() -> int:
     return torch.cuda.current_stream().cuda_stream
+
+
+def _made(name: str, *args) -> bool:
+    """Whether the extension module has made the call; False before the library is loaded and for arguments with
+    anything to object to."""
+    if _native is None:
+        return False
+    code = getattr(_native, name)(*args)
+    if code is NotImplemented:
+        return False
+    if code != PS_OK:
+        raise PsError(code, "ps_" + name)
+    return True
 
 
 def _check(code: int, where: str) -> None:
@@ -188,6 +208,8 @@ def ps_status_read(status: torch.Tensor) -> Tuple[int, int]:
 def ps_predict_load(model: Model, token_ids: torch.Tensor, offsets: torch.Tensor,
                     lengths: Optional[torch.Tensor], pred_f: torch.Tensor, pred_tokens: torch.Tensor,
                     workspace: torch.Tensor, status: Optional[torch.Tensor] = None) -> None:
+    if _made("predict_load", model.handle, token_ids, offsets, lengths, pred_f, pred_tokens, workspace, status):
+        return
     n_req = offsets.numel() - 1
     _check(load_library().ps_predict_load(
         model.handle, _ptr(token_ids, torch.int32, "token_ids"), _ptr(offsets, torch.int32, "offsets"),
@@ -205,6 +227,8 @@ def ps_anticipate(pred_tokens: torch.Tensor, instance_id: torch.Tensor, arrival_
                   rate: Optional[torch.Tensor], n_inst: int, horizon: int, load: torch.Tensor,
                   overflow: Optional[torch.Tensor], workspace: torch.Tensor,
                   status: Optional[torch.Tensor] = None) -> None:
+    if _made("anticipate", pred_tokens, instance_id, arrival_bucket, rate, n_inst, horizon, load, overflow, workspace, status):
+        return
     if load.numel() != n_inst * horizon or (overflow is not None and overflow.numel() != n_inst) or \
             (rate is not None and rate.numel() != n_inst) or \
             instance_id.numel() != pred_tokens.numel() or arrival_bucket.numel() != pred_tokens.numel():
@@ -224,6 +248,8 @@ def ps_anticipate_static(pred_tokens: torch.Tensor, instance_id: torch.Tensor, a
                          rate: Optional[torch.Tensor], n_inst: int, horizon: int, load: torch.Tensor,
                          overflow: Optional[torch.Tensor], status: Optional[torch.Tensor] = None) -> None:
     """ps_anticipate without a workspace argument: the library's own fixed device array holds the partial curves."""
+    if _made("anticipate_static", pred_tokens, instance_id, arrival_bucket, rate, n_inst, horizon, load, overflow, status):
+        return
     if load.numel() != n_inst * horizon or (overflow is not None and overflow.numel() != n_inst) or \
             (rate is not None and rate.numel() != n_inst) or \
             instance_id.numel() != pred_tokens.numel() or arrival_bucket.numel() != pred_tokens.numel():
@@ -245,6 +271,9 @@ def ps_lookahead_update(instance_id: torch.Tensor, start_iter: torch.Tensor, pro
                         kv_tokens: torch.Tensor, overflow: Optional[torch.Tensor], workspace: torch.Tensor,
                         capacity: Optional[torch.Tensor] = None, fraction: Optional[torch.Tensor] = None,
                         status: Optional[torch.Tensor] = None) -> None:
+    if _made("lookahead_update", instance_id, start_iter, prompt_tokens, i_begin, i_end, sign, n_inst, map_len, kv_tokens,
+             overflow, workspace, capacity, fraction, status):
+        return
     cols = (instance_id, start_iter, prompt_tokens, i_begin, i_end, sign)
     n = instance_id.numel()
     if any(c.numel() != n for c in cols) or kv_tokens.numel() != n_inst * map_len or \
@@ -265,6 +294,9 @@ def ps_scaler_scan(kv_tokens: torch.Tensor, capacity: torch.Tensor, n_inst: int,
                    over_count: torch.Tensor, peak_tokens: torch.Tensor, overloaded: torch.Tensor,
                    summary: torch.Tensor, scale_down: torch.Tensor, over_pct: int = 95, share_pct: int = 10,
                    idle_pct: int = 30) -> None:
+    if _made("scaler_scan", kv_tokens, capacity, n_inst, map_len, window, over_count, peak_tokens, overloaded, summary,
+             scale_down, over_pct, share_pct, idle_pct):
+        return
     if kv_tokens.numel() != n_inst * map_len or capacity.numel() != n_inst or summary.numel() != 2 or \
             scale_down.numel() != 1 or any(t.numel() != n_inst for t in (over_count, peak_tokens, overloaded)):
         raise ValueError("ps_scaler_scan: array sizes do not match n_inst / map_len")
@@ -280,6 +312,9 @@ def ps_route(prompt_tokens: torch.Tensor, pred_tokens: torch.Tensor, n_inst: int
              window_tokens: Optional[torch.Tensor], capacity: torch.Tensor, queued_p: torch.Tensor,
              current_d: torch.Tensor, assigned: torch.Tensor, score100: torch.Tensor, t_mem_pct: int = 80,
              beta: int = 1, status: Optional[torch.Tensor] = None) -> None:
+    if _made("route", prompt_tokens, pred_tokens, n_inst, window, window_tokens, capacity, queued_p, current_d, assigned, score100,
+             t_mem_pct, beta, status):
+        return
     n = prompt_tokens.numel()
     if pred_tokens.numel() != n or assigned.numel() != n or score100.numel() != n or capacity.numel() != n_inst or \
             queued_p.numel() != n_inst or current_d.numel() != n_inst or \
@@ -295,6 +330,8 @@ def ps_route(prompt_tokens: torch.Tensor, pred_tokens: torch.Tensor, n_inst: int
 
 def ps_forecast(weights: torch.Tensor, hidden: int, hist_p: torch.Tensor, hist_d: torch.Tensor, n_services: int,
                 k: int, mu: torch.Tensor, out: torch.Tensor) -> None:
+    if _made("forecast", weights, hidden, hist_p, hist_d, n_services, k, mu, out):
+        return
     if weights.numel() != n_services * 2 * (5 * hidden * hidden + 10 * hidden + 1) or hist_p.numel() != n_services * k or \
             hist_d.numel() != n_services * k or mu.numel() != 3 * n_services or out.numel() != 5 * n_services:
         raise ValueError("ps_forecast: array sizes do not match n_services / hidden / k")
