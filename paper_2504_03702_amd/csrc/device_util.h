@@ -58,6 +58,34 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Inclusive prefix sums over the wavefront (rows of 16 lanes with ROWS_ONLY), by the vector unit's own lane moves: a shuffle is a
+// trip through LDS a step and half.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_add64(long long v) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xf, false);
+    return v + (((long long)hi << 32) | lo);
+}
+template <bool ROWS_ONLY = false>
+__device__ __forceinline__ long long prefix_sum64(long long v) {
+    v = dpp_add64<0x111, 0xf>(v);        // row_shr 1, 2, 4, 8
+    v = dpp_add64<0x112, 0xf>(v);
+    v = dpp_add64<0x114, 0xf>(v);
+    v = dpp_add64<0x118, 0xf>(v);
+    if (ROWS_ONLY) return v;
+    v = dpp_add64<0x142, 0xa>(v);        // row_bcast 15 into rows 1 and 3
+    return dpp_add64<0x143, 0xc>(v);     // row_bcast 31 into rows 2 and 3
+}
+__device__ __forceinline__ long long readlane64(long long v, int l) {
+    return ((long long)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) | (unsigned)__builtin_amdgcn_readlane((int)v, l);
+}
+// Of sixteen wavefronts' values (in LDS): the sum of those in front of wavefront `wave`, and of all.
+__device__ __forceinline__ long long sum_in_front(const long long* s_wave, int wave, long long& all) {
+    const long long incl = prefix_sum64<true>(s_wave[threadIdx.x & 15]);
+    all = readlane64(incl, 15);
+    return wave > 0 ? readlane64(incl, wave - 1) : 0;
+}
+
 // erf-GELU x * Phi(x) with Phi(x) - 1/2 = x * Q(x^2) on |x| <= 4.5 (Q: degree-8 least-squares fit on Chebyshev
 // nodes, coefficients taken to the variable x^2) and Phi clamped beyond; absolute error of the result below
 // 6e-5, under the bf16 rounding of the stored value wherever the value is not itself tiny.  Eleven full-rate

@@ -256,8 +256,9 @@ __global__ __launch_bounds__(kBinThreads) void lookahead_bin_kernel(
 template <bool VEC, bool PACKED, bool SHARED>
 __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* s_slp, long long* s_w0, long long* s_w1, int k,
                                              int map_len, int32_t* __restrict__ kv_tokens, const int32_t* __restrict__ capacity,
-                                             float* __restrict__ fraction, long long* __restrict__ prow, ps_status* st) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                             float* __restrict__ fraction, long long* __restrict__ prow, ps_status* st,
+                                             const int4* ahead = nullptr) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int32_t* out = kv_tokens + (int64_t)k * map_len;
     float* frow = fraction ? fraction + (int64_t)k * map_len : nullptr;
     const int cap = fraction ? capacity[k] : 1;
@@ -269,7 +270,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
         int was[4] = {0, 0, 0, 0};                              // the map's row, requested ahead of the scan
         if (VEC) {
             if (t < map_len) {
-                const int4 v = *(const int4*)(out + t);
+                const int4 v = ahead && t0 == 0 ? *ahead : *(const int4*)(out + t);
                 was[0] = v.x; was[1] = v.y; was[2] = v.z; was[3] = v.w;
             }
         } else {
@@ -289,21 +290,12 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
         }
 #pragma unroll
         for (int c = 1; c < 4; ++c) { a0[c] += a0[c - 1]; a1[c] += a1[c - 1]; }
-        long long i0 = a0[3], i1 = a1[3];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const long long u0 = __shfl_up(i0, o, 64), u1 = __shfl_up(i1, o, 64);
-            if (lane >= o) { i0 += u0; i1 += u1; }
-        }
+        const long long i0 = prefix_sum64(a0[3]), i1 = prefix_sum64(a1[3]);
         if (lane == 63) { s_w0[wave] = i0; s_w1[wave] = i1; }
         __syncthreads();
-        long long before0 = carry0 + i0 - a0[3], before1 = carry1 + i1 - a1[3];
-        long long tot0 = 0, tot1 = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wave) { before0 += s_w0[w]; before1 += s_w1[w]; }
-            tot0 += s_w0[w];
-            tot1 += s_w1[w];
-        }
+        long long tot0, tot1;
+        const long long before0 = carry0 + i0 - a0[3] + sum_in_front(s_w0, wave, tot0);
+        const long long before1 = carry1 + i1 - a1[3] + sum_in_front(s_w1, wave, tot1);
         int now[4];
         float part[4];
 #pragma unroll
@@ -315,7 +307,7 @@ __device__ __forceinline__ void scan_lds_row(const long long* s_off, const int* 
             }
             if (t + c < map_len && (nv > 2147483647ll || nv < -2147483648ll)) report_fault(st, PS_ST_RANGE, -1);
             now[c] = (int32_t)(uint32_t)(unsigned long long)nv;
-            part[c] = frow ? (float)nv / cap_f : 0.f;
+            part[c] = frow ? (nv == now[c] ? (float)now[c] : (float)nv) / cap_f : 0.f;
         }
         if (VEC) {
             if (t < map_len) {
@@ -446,7 +438,8 @@ __global__ __launch_bounds__(256) void lookahead_combine_kernel(const long long*
 // One launch and no scratch: a workgroup per instance looks through the whole list's instances (from its XCD's L2; eight
 // ids a thread requested together), applies its own records to an LDS row as above and scans the row into the map.  The
 // atomic route clears, updates and reads back a map-sized difference array: 4096 records over 256 instances of 4096 slots
-// took it 20 us in three launches, 11.5 here.
+// took it 20 us in three launches, 9.4 here with shuffles in the scan and the map's row requested by it, 8.2 with the sums by lane
+// moves and the row and the first ids requested ahead of all else.
 //
 // Where it pays (microseconds, atomic route / this one).  Every instance is a workgroup of 1024 threads that looks through
 // the list, so its time grows with instances beyond two a compute unit and with records times instances; the atomic
@@ -480,14 +473,22 @@ __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     __shared__ long long s_w0[16], s_w1[16];
     __shared__ unsigned long long s_ovf;
     const int k = blockIdx.x, tid = threadIdx.x;
+    // the first ids, and the map's row that the scan will want, ahead of all else
+    constexpr int U = 8;
+    int kk[U];
+    auto look = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) kk[u] = instance_id[min(r0 + 1024 * u, n - 1)];
+    };
+    if (n > 0) look(tid);                // (of no records there is not even a first)
+    int4 was = make_int4(0, 0, 0, 0);
+    if (VEC && 4 * tid < map_len) was = *(const int4*)(kv_tokens + (int64_t)k * map_len + 4 * tid);
+    asm volatile("" ::: "memory");
     for (int i = tid; i < map_len; i += 1024) s_row[i] = 0;
     if (tid == 0) s_ovf = 0;
     __syncthreads();
-    constexpr int U = 8;
     for (int r0 = tid; r0 < n; r0 += 1024 * U) {
-        int kk[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) kk[u] = instance_id[min(r0 + 1024 * u, n - 1)];
+        if (r0 != tid) look(r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int r = r0 + 1024 * u;
@@ -516,7 +517,8 @@ __global__ __launch_bounds__(1024) void lookahead_direct_kernel(
     }
     __syncthreads();
     if (tid == 0 && overflow && s_ovf) overflow[k] += (int64_t)s_ovf;
-    scan_lds_row<VEC, true, false>((const long long*)s_row, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st);
+    scan_lds_row<VEC, true, false>((const long long*)s_row, nullptr, s_w0, s_w1, k, map_len, kv_tokens, capacity, fraction, nullptr, st,
+                                   VEC ? &was : nullptr);
 }
 
 // Layout of the workspace.  Atomic route: the difference array.  Binned route: entries, table, and from there to the end

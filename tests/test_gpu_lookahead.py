@@ -255,6 +255,30 @@ def test_scaler_sizes_around_the_single_launch(K, L, window):
     assert abs(got[5] - ref[5]) <= 4e-16 * (K + abs(ref[5]))
 
 
+@pytest.mark.parametrize("K,L,window,skip", [(1, 4, 1, 0), (3, 128, 63, 0), (65, 132, 65, 0), (70, 512, 129, 0), (257, 200, 190, 0),
+                                             (5, 128, 100, 1), (66, 130, 130, 0), (512, 128, 128, 0)])
+def test_scaler_rows_in_whole_groups_and_not(K, L, window, skip):
+    """Four slots a load where rows are whole 16-byte groups, and maps whose rows or start are not; windows that end inside a
+    group and at the edges of a lane's batch."""
+    from oracle import scaler as osc
+    print(f"scaler groups K={K} L={L} window={window} skip={skip}", flush=True)
+    rng = np.random.default_rng(K * L + window)
+    cap = rng.integers(1, 2000, K).astype(np.int32)
+    kv = (rng.uniform(-0.1, 1.2, (K, L)) * cap[:, None]).astype(np.int32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    z = lambda m, dt=torch.int32: torch.full((m,), -9, dtype=dt, device="cuda:0")
+    held = torch.zeros(K * L + skip, dtype=torch.int32, device="cuda:0")
+    held[skip:] = t(kv).reshape(-1)
+    oc, pk, ov, summ, sd = z(K), z(K), z(K), z(2), z(1, torch.float64)
+    ps.ps_scaler_scan(held[skip:], t(cap), K, L, window, oc, pk, ov, summ, sd)
+    ref = osc.scaler_scan(kv, cap, window)
+    for g, r in zip((oc, pk, ov), ref[:3]):
+        assert np.array_equal(g.cpu().numpy(), r)
+    assert summ.tolist() == [ref[3], ref[4]]
+    # the same fp64 operations in the same order, but for a fused multiply-add in the last one
+    assert abs(sd.item() - ref[5]) <= 4e-16 * (K + abs(ref[5]))
+
+
 @pytest.mark.parametrize("n,K,L", [(1, 1, 1), (7, 3, 5), (1024, 2, 4096), (8193, 5, 1023), (16384, 512, 64), (16385, 3, 300),
                                    (16384, 513, 64), (5000, 4, 12800), (5000, 4, 12801), (5000, 4, 19200), (5000, 4, 19201),
                                    (16384, 256, 64), (16384, 257, 64), (8192, 512, 64), (300, 513, 70), (300, 768, 4096),
