@@ -44,6 +44,7 @@ Workspace plan_workspace(const ps_model_info& info, int64_t n_tokens, int32_t n_
         ws.sa = (float2*)take(8 * rows);
         ws.sb = (float2*)take(8 * rows);
         ws.ps = (float2*)take(8 * rows * (H / 64));
+        ws.first_row = (uint8_t*)take(rows);
         ws.cls_rows = (int64_t)align_up((size_t)(n_req > 0 ? n_req : 1), PS_ROW_TILE);
         ws.cls_a = take(2 * ws.cls_rows * 2 * H);
         ws.cls_g = take(2 * ws.cls_rows * 2 * F);

@@ -118,12 +118,15 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     };
 #define PS_TIMED(FAM, CALL) do { ProfScope p_(m, FAM, s); CALL; } while (0)
     // the per-request side maps of calls of more than 16 requests
+    auto side_args = [&](const void* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K) {
+        SmallGemm p = {};
+        p.A = (const bf16_t*)A; p.W = (const bf16_t*)W; p.bias = bias; p.res = r; p.C = C;
+        p.max_rows = ws.cls_rows; p.N = N; p.K = K; p.hidden = H; p.rows = n_req_dev;
+        return p;
+    };
     auto side_gemm = [&](GemmEpilogue epi, const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C,
                          int N, int K) {
-        SmallGemm p = {};
-        p.A = A; p.W = (const bf16_t*)W; p.bias = bias; p.res = r; p.C = C;
-        p.max_rows = ws.cls_rows; p.N = N; p.K = K; p.hidden = H; p.rows = n_req_dev;
-        launch_small_gemm_bf16(epi, p, nullptr, s);
+        launch_small_gemm_bf16(epi, side_args(A, W, bias, r, C, N, K), nullptr, s);
     };
     const bool skinny = n_req <= PS_SKINNY_ROWS;
     auto skinny_args = [&](const void* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K,
@@ -134,6 +137,8 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     // Calls of a few requests over few rows: a layer is five launches, each map's launch doing the per-request map
     // beside it and making the row statistics it needs from the previous launch's pieces.
     const bool fused = skinny && ws.max_rows <= PS_FUSED_ROWS;
+    // With more requests, up to PS_CARRIED_REQUESTS, the launches of the maps of all rows carry the per-request ones.
+    const bool carried = !skinny && n_req <= PS_CARRIED_REQUESTS;
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
         // After the last layer only the first row of every request goes on (to the head), and within
@@ -217,6 +222,18 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
                 PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
             }
+        } else if (carried && !last) {
+            SmallGemm so = side_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H);
+            SmallGemm s1 = side_args(ws.cls_a, w.w_1d, w.b_1, none, ws.cls_g, F, H);
+            SmallGemm s2 = side_args(ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F);
+            so.max_rows = s1.max_rows = s2.max_rows = (int64_t)align_up((size_t)n_req, 64);
+            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb, nullptr, ws.max_rows,
+                                                   H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, &so, ws.first_row));
+            PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, &ffn_cls));
+            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr, ws.max_rows,
+                                                   F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, &s1, nullptr));
+            PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la, nullptr, ws.max_rows,
+                                                   H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, &s2, ws.first_row));
         } else {
             if (!last)
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,

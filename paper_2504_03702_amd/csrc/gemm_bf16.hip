@@ -32,16 +32,12 @@
 
 #include "device_util.h"
 #include "internal.h"
+#include "small_gemm.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-#define GLOBAL_AS __attribute__((address_space(1)))
-#define LDS_AS __attribute__((address_space(3)))
 
 template <int BM, int BN, int WM, int WN>
 struct Tile {
@@ -82,6 +78,8 @@ struct GemmArgs {
     bf16_t* Vt;
     int64_t max_rows;            // rows of every activation buffer; also the row stride of Vt
     int N, K, hidden;
+    int wgs;                     // workgroups of the map itself
+    const uint8_t* first_row;    // rows that a side map writes (1), for the kernels that carry one
 };
 
 // One region of the output: the rows from row_begin on, in tiles of bm rows (32 for each of the 2 x TM blocks of the two
@@ -109,12 +107,12 @@ struct Region {
 // first feed-forward map of hidden 1024, 1024 of those tiles: 90 us with bands, 101 without.
 template <bool BANDS>
 struct Walk {
-    int n_tiles, m_tiles, slots, xcd, slot, full, rest, n_my;
-    __device__ __forceinline__ Walk(int m, int n) : n_tiles(n), m_tiles(m) {
-        xcd = blockIdx.x & 7; slot = blockIdx.x >> 3; slots = gridDim.x >> 3;
+    int n_tiles, m_tiles, wgs, slots, xcd, slot, full, rest, n_my;
+    __device__ __forceinline__ Walk(int m, int n, int wgs_) : n_tiles(n), m_tiles(m), wgs(wgs_) {
+        xcd = blockIdx.x & 7; slot = blockIdx.x >> 3; slots = wgs >> 3;
         const int tiles = m * n;
-        full = tiles / (int)gridDim.x;
-        rest = tiles - full * (int)gridDim.x;
+        full = tiles / wgs;
+        rest = tiles - full * wgs;
         const int per = (rest + 7) >> 3;
         n_my = full + (slot < per && xcd * per + slot < rest ? 1 : 0);
     }
@@ -125,7 +123,7 @@ struct Walk {
             const int P = n_tiles >> 2, done = 8 % P == 0 ? 0 : full / P * P;
             run = round < done ? (round / P * 8 + xcd) * P + round % P : round * 8 + xcd;
         }
-        const int id = round < full ? run * slots + slot : full * (int)gridDim.x + xcd * ((rest + 7) >> 3) + slot;
+        const int id = round < full ? run * slots + slot : full * wgs + xcd * ((rest + 7) >> 3) + slot;
         if constexpr (BANDS) {
             const int high = n_tiles < 4 ? 1 : 8;
             const int band = id / (high * n_tiles), in = id - band * high * n_tiles, rb = min(high, m_tiles - high * band);
@@ -139,7 +137,7 @@ struct Walk {
 };
 
 // All tiles of a region that belong to this workgroup, by one of its wavefronts; TM: the wavefront's 32-row blocks.
-template <typename T, int WN, int TM, int EPI, bool PLANNED>
+template <typename T, int WN, int TM, int EPI, bool PLANNED, bool SKIP>
 __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                              const float* __restrict__ bias, void* __restrict__ Cv, bf16_t* __restrict__ Vt,
                                              const Region& rg_, unsigned char* smem) {
@@ -158,7 +156,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
 
     // (EPI_GELU_SPLIT: small tiles, but many of them for many requests)
     constexpr bool BANDS = PLANNED || EPI == EPI_GELU_SPLIT;
-    const Walk<BANDS> walk(rg_.m_tiles, N / BN);
+    const Walk<BANDS> walk(rg_.m_tiles, N / BN, g.wgs);
     const int n_my = walk.n_my;
     if (n_my == 0) return;
     // first row of a tile; the last tile is moved up where it would pass the end of the buffers (rows of two tiles are
@@ -338,6 +336,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
         auto row_in = [](int s) { return 16 * (s >> 1) + 4 * (s & 1); };
         auto lane_row = [](int l) { return ((l >> 3) & 3) + 8 * (l >> 5); };
         u32x4 ph[D + 1], pl[D + 1];
+        int first_a = 0, first_b = 0;                             // SKIP: whether rows lane, 64 + lane are a side map's
         auto fetch_sums = [&](int s, int in_tile) {               // in_tile: of the lane's first element in the wavefront's tile
             const int64_t at = (int64_t)(m_base + row_in(s)) * N + n_base;
             ph[s % (D + 1)] = *(const u32x4*)(res.y_hi + at + in_tile);
@@ -364,6 +363,10 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
             };
             for (int kt = 0; kt < slices - (RESIDUAL ? 1 : 0); ++kt) slice(kt);
             if constexpr (RESIDUAL) {
+                if constexpr (SKIP) {
+                    first_a = g.first_row[m_base + lane];         // (the buffers' last rows at most: tiles are inside)
+                    if (TM > 2) first_b = g.first_row[min(m_base + 64 + lane, (int)g.max_rows - 1)];
+                }
                 const int off = lane_row(lane) * N + 8 * (lane & 7);
 #pragma unroll
                 for (int s = 0; s < D; ++s) fetch_sums(s, off);
@@ -491,6 +494,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
             const auto ps_out = range(res.pstats + (int64_t)m_base * pieces + (n_base >> 6), 8 * pieces, 8);
             const int ps_off = cg == 0 ? lane_row(el) * pieces * 8 : INT_MIN;          // one lane a row, the others out of range
             float* strip = (float*)(smem + T::STRIPS) + wave * 8 * T::STRIP_LD;
+            const unsigned long long skip_a = SKIP ? __ballot(first_a != 0) : 0, skip_b = SKIP ? __ballot(first_b != 0) : 0;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 // The next slice's DMAs, while nothing is behind them: with one on its way the compiler takes every wait for
@@ -523,9 +527,19 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
                                           (fmaf(o[4], o[4], o[5] * o[5]) + fmaf(o[6], o[6], o[7] * o[7])));
                 const u32x2 ps = {__float_as_uint(sm), __float_as_uint(sq)};
                 // (offsets in the vector operand: the scalar one takes no part in the range check)
-                __builtin_amdgcn_raw_buffer_store_b128(ho, hi_out, 2 * (in_tile + row_in(s) * N), 0, 0);
-                __builtin_amdgcn_raw_buffer_store_b128(lo, lo_out, 2 * (in_tile + row_in(s) * N), 0, 0);
-                __builtin_amdgcn_raw_buffer_store_b64(ps, ps_out, ps_off + 8 * row_in(s) * pieces, 0, 0);
+                int at = 2 * (in_tile + row_in(s) * N), ps_at = ps_off + 8 * row_in(s) * pieces;
+                if constexpr (SKIP) {
+                    // (bits 0-3 and 8-11: the strip's rows; most strips have none, and only stores that are dropped differ)
+                    const unsigned mine = (unsigned)((s < 8 ? skip_a : skip_b) >> (row_in(s) & 63)) & 0xf0fu;
+                    if (__builtin_expect(mine != 0, 0)) {
+                        const bool drop = mine >> lane_row(el) & 1;
+                        at = drop ? INT_MIN : at;
+                        ps_at = drop ? INT_MIN : ps_at;
+                    }
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(ho, hi_out, at, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(lo, lo_out, at, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(ps, ps_out, ps_at, 0, 0);
             }
             continue;
         }
@@ -595,13 +609,36 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// The per-request map that a launch can carry (see launch_gemm_bf16): 64 x 64 tiles for the maps back to the hidden width, 128 x 64
+// for the first feed-forward map, with as many slices on their way as the launch's LDS has room for.
+constexpr int kNoSide = -1;
+template <int EPI>
+constexpr int side_of = EPI == EPI_BIAS_RESIDUAL ? (int)EPI_RESIDUAL_MAPPED : (int)EPI_GELU_SPLIT;
+template <int SIDE, int BM>
+struct SideTile {
+    static constexpr int TM = SIDE == EPI_GELU_SPLIT ? 2 : 1;
+    static constexpr int STAGES = SIDE == EPI_GELU_SPLIT ? (BM == 256 ? 6 : 3) : (BM == 256 ? 8 : 4);
+    static constexpr int BYTES = SIDE == kNoSide ? 0 : STAGES * 64 * (TM + 1) * 128;
+};
+
 // Rows in two regions: plan->m_tiles tiles of BM rows, then the others in tiles of 32 (tm0 + tm1) rows, as prep chose them
-// (PLANNED); without a plan all in tiles of BM rows.
-template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED>
+// (PLANNED); without a plan all in tiles of BM rows.  SIDE: workgroups from g.wgs on do a per-request map; a unit that has no tile
+// in the launch's last round takes them.
+template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED, int SIDE>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
-                                                                 const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk) {
+                                                                 const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk,
+                                                                 SmallGemm side) {
     using T = Tile<BM, BN, WM, WN>;
-    __shared__ __align__(1024) unsigned char smem[EPI == EPI_BIAS_RESIDUAL ? T::LDS : T::STRIPS];
+    using S = SideTile<SIDE, BM>;
+    constexpr int kBytes = EPI == EPI_BIAS_RESIDUAL ? T::LDS : T::STRIPS;
+    constexpr bool SKIP = SIDE == EPI_RESIDUAL_MAPPED;
+    __shared__ __align__(1024) unsigned char smem[kBytes > S::BYTES ? kBytes : S::BYTES];
+    if constexpr (SIDE != kNoSide) {
+        if ((int)blockIdx.x >= g.wgs) {
+            if (threadIdx.x < 256) small_tile<SIDE, S::TM, 1, S::STAGES>(side, blockIdx.x - g.wgs, smem, nullptr);
+            return;
+        }
+    }
     // clock probe (profiling only): core cycles and constant-rate ticks over this workgroup's life
     const int64_t clk_c0 = clk ? (int64_t)clock64() : 0, clk_w0 = clk ? (int64_t)wall_clock64() : 0;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -610,7 +647,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
     if constexpr (!PLANNED) {
         rg.row_begin = 0; rg.bm = BM; rg.tm0 = T::TM;
         rg.m_tiles = (rg.rows + BM - 1) / BM;
-        region_tiles<T, WN, T::TM, EPI, false>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+        region_tiles<T, WN, T::TM, EPI, false, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
     } else {
         static_assert(T::TM == 4, "regions of 2 to 4 blocks a wavefront");
         const GemmPlan pl = *plan;
@@ -622,9 +659,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
             if (rg.m_tiles <= 0) break;
             if (r == 1 && pl.m_tiles > 0) dma_barrier();     // every wavefront's parked DMAs have landed
             const int tm = wave / WN == 0 ? tm0 : tm1;       // both paths meet the same barriers
-            if (tm == 4) region_tiles<T, WN, 4, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else if (tm == 3) region_tiles<T, WN, 3, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else region_tiles<T, WN, 2, EPI, true>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            if (tm == 4) region_tiles<T, WN, 4, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else if (tm == 3) region_tiles<T, WN, 3, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else region_tiles<T, WN, 2, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
         }
     }
     if (clk && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -634,17 +671,32 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
 }
 
 template <int BM, int BN, int WM, int WN, bool PLANNED>
-void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk,
-                hipStream_t s) {
+void launch_cfg(GemmEpilogue epi, GemmArgs g, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk,
+                const SmallGemm* side, hipStream_t s) {
     // persistent: one workgroup per compute unit; the small tiles leave room for two (LDS and registers), which then hide
     // each other's waits, and take fewer workgroups if there cannot be that many tiles
     const int64_t tiles = (g.max_rows + BM - 1) / BM * (g.N / BN);
-    const int64_t wgs = PLANNED ? 256 : tiles < 512 ? (tiles + 7) / 8 * 8 : 512;
-    const dim3 grid((unsigned)wgs), block(WM * WN * 64);
-#define PS_LAUNCH(E) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED>), grid, block, 0, s, g, total_rows, plan, clk)
+    g.wgs = (int)(PLANNED ? 256 : tiles < 512 ? (tiles + 7) / 8 * 8 : 512);
+    const dim3 block(WM * WN * 64);
+    // a side map's tiles, hi and lo part of a request in one
+    auto side_wgs = [&](int tm) {
+        const int64_t n = (side->max_rows * 2 + 64 * tm - 1) / (64 * tm) * (side->N / 64);
+        return (unsigned)((n + 7) / 8 * 8);
+    };
+#define PS_LAUNCH(E)                                                                                                     \
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kNoSide>), dim3((unsigned)g.wgs), block, 0, s, g, total_rows, plan, clk, SmallGemm{})
+#define PS_LAUNCH_SIDE(E)                                                                                                \
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, side_of<E>>), dim3((unsigned)g.wgs + side_wgs(SideTile<side_of<E>, BM>::TM)), \
+                       block, 0, s, g, total_rows, plan, clk, *side)
     switch (epi) {
-        case EPI_BIAS_GELU: PS_LAUNCH(EPI_BIAS_GELU); break;
-        case EPI_BIAS_RESIDUAL: PS_LAUNCH(EPI_BIAS_RESIDUAL); break;
+        case EPI_BIAS_GELU:
+            if (side) PS_LAUNCH_SIDE(EPI_BIAS_GELU);
+            else PS_LAUNCH(EPI_BIAS_GELU);
+            break;
+        case EPI_BIAS_RESIDUAL:
+            if (side) PS_LAUNCH_SIDE(EPI_BIAS_RESIDUAL);
+            else PS_LAUNCH(EPI_BIAS_RESIDUAL);
+            break;
         case EPI_QKV: PS_LAUNCH(EPI_QKV); break;
         case EPI_KV: PS_LAUNCH(EPI_KV); break;
         case EPI_GELU_SPLIT:
@@ -653,6 +705,7 @@ void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, 
         default: break;                                  // the mapped forms are small_gemm.hip's and skinny_gemm.hip's
     }
 #undef PS_LAUNCH
+#undef PS_LAUNCH_SIDE
 }
 
 }  // namespace
@@ -664,14 +717,15 @@ void launch_cfg(GemmEpilogue epi, const GemmArgs& g, const int32_t* total_rows, 
 // and are moved up (row_of).
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc residual, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
-                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s) {
+                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s,
+                      const SmallGemm* side, const uint8_t* first_row) {
     // Problems with few 256 x 256 tiles (whole calls on a micro-batch of a few requests) would leave most compute
     // units idle: 128 x 128 tiles give four times as many workgroups to spread them over.  EPI_GELU_SPLIT has only these
     // (its second set of accumulators): 4096 requests of hidden 768 in 57 us, 20000 in 234.
     const int64_t big_tiles = (max_rows + 255) / 256 * (N / 256);
-    const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden};
+    const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden, 0, first_row};
     if (epi == EPI_GELU_SPLIT || big_tiles < 128)
-        launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, s);
+        launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, side, s);
     else
-        launch_cfg<256, 256, 2, 4, true>(epi, g, total_rows, plan, clk, s);
+        launch_cfg<256, 256, 2, 4, true>(epi, g, total_rows, plan, clk, side, s);
 }

@@ -92,6 +92,7 @@ struct Workspace {
     bf16_t *la, *lb;             // lo parts belonging to x and x1
     float2 *sa, *sb;
     float2 *ps;                  // [rows][hidden / 64] per-row partial (sum, sum of squares) of the newest sums
+    uint8_t* first_row;          // [rows] bf16 path: 1 for the first row of a request
     void *cls_a, *cls_g;         // per-request rows of the [CLS] refinement: [cls_rows][2H], [cls_rows][2F] bf16
     int64_t cls_rows;
     int64_t max_rows;            // rows every activation buffer holds (multiple of PS_ROW_TILE)
@@ -140,12 +141,6 @@ struct ResidualSrc {
     // `stats` are the statistics of the operand's rows, colsum is c above and the bias argument is d
     const float* colsum;
 };
-// C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
-// The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,
-// may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
-void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
-                      ResidualSrc res, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
-                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s);
 // The per-request forms (EPI_GELU_SPLIT, EPI_RESIDUAL_MAPPED, EPI_Q_MAPPED) for calls of at most PS_SKINNY_ROWS
 // requests: a stream over W with the contraction split among a workgroup's wavefronts.
 #define PS_SKINNY_ROWS 16
@@ -153,6 +148,13 @@ void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const 
 // Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
 // 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
 #define PS_FUSED_ROWS 3584
+// Calls of more than PS_SKINNY_ROWS and up to this many requests: the launches of the maps of all rows carry the per-request ones
+// in further workgroups, which take the units that the launch's last round leaves idle (64 padded prompts of hidden 768: of 256
+// units the maps back to it use 200 to 230), instead of three launches of 7 to 15 us that use a few units each.  Milliseconds,
+// apart / carried: six-layer encoder 17 requests 0.839 / 0.732, 40 1.213 / 1.046, 128 2.99 / 2.87, 256 5.25 / 5.13, 512 9.77 / 9.66;
+// padded twelve-layer 33 2.80 / 2.33, 64 4.37 / 4.11, 200 10.96 / 10.75; packed 17 2.07 / 1.71, 400 20.06 / 19.82, 1024 49.8 / 49.6,
+// 2048 even; production 24 6.82 / 6.49, 100 22.6 / 22.1, 400 78.7 / 78.4.
+#define PS_CARRIED_REQUESTS 1024
 enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
 struct SkinnyArgs {
     const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)
@@ -189,6 +191,15 @@ struct SmallGemm {
     const int32_t *row_start, *seq_len;
 };
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
+// C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
+// The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,
+// may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
+// side: EPI_BIAS_RESIDUAL and EPI_BIAS_GELU can carry the per-request map of the same sublayer (EPI_RESIDUAL_MAPPED, EPI_GELU_SPLIT;
+// more than PS_SKINNY_ROWS requests) in further workgroups; rows that first_row marks are then left to it.
+void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
+                      ResidualSrc res, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
+                      int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s,
+                      const SmallGemm* side = nullptr, const uint8_t* first_row = nullptr);
 // out[r][0:hidden] = x[first row of request r] for every request (zeros for faulty ones and padding rows).
 void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* x, bf16_t* out, hipStream_t s);
 // first_rows_only: compute (at least) the first query row of every request and nothing beyond its

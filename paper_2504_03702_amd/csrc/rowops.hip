@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
                                                     int32_t* bad_req, T* __restrict__ x,
                                                     bf16_t* __restrict__ lo_out, float2* __restrict__ stats_out,
                                                     const int32_t* __restrict__ qtile_start, int4* __restrict__ qtiles,
-                                                    ps_status* st) {
+                                                    uint8_t* __restrict__ first_row, ps_status* st) {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int total = meta->total_rows;
@@ -223,6 +223,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
         S = seq_len[r];
         first = offsets[r];
     }
+    if (first_row && lane == 0) first_row[row] = r >= 0 && S > 0 && p == 0;
     if (r < 0 || p >= S) {
         for (int i = lane; i < H; i += 64) {
             store_elem<T>(out, i, 0.f);
@@ -514,13 +515,14 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
         hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const bf16_t*)m->e_tok, (const bf16_t*)m->e_pos, (const bf16_t*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
-                           ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, ws.qtile_start, ws.qtiles, st);
+                           ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, ws.qtile_start, ws.qtiles,
+                           n_req > PS_SKINNY_ROWS && n_req <= PS_CARRIED_REQUESTS ? ws.first_row : nullptr, st);
     else
         hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const float*)m->e_tok, (const float*)m->e_pos, (const float*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
                            ws.row_start, ws.bad_req, (float*)ws.x, (bf16_t*)nullptr, (float2*)nullptr, (const int32_t*)nullptr,
-                           (int4*)nullptr, st);
+                           (int4*)nullptr, (uint8_t*)nullptr, st);
 }
 
 void launch_head(const ps_model* m, int32_t n_req, const Workspace& ws, float* pred_f, int32_t* pred_tokens,
