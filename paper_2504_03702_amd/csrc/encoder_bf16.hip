@@ -137,8 +137,8 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     // Calls of a few requests over few rows: a layer is five launches, each map's launch doing the per-request map
     // beside it and making the row statistics it needs from the previous launch's pieces.
     const bool fused = skinny && ws.max_rows <= PS_FUSED_ROWS;
-    // With more requests, up to PS_CARRIED_REQUESTS, the launches of the maps of all rows carry the per-request ones.
-    const bool carried = !skinny && n_req <= PS_CARRIED_REQUESTS;
+    // With more of either, up to PS_CARRIED_REQUESTS, the launches of the maps of all rows carry the per-request ones.
+    const bool carried = carries_side_maps(n_req, ws.max_rows);
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
         // After the last layer only the first row of every request goes on (to the head), and within
@@ -208,19 +208,22 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_GELU, small(x1, w.w_1, w.d_1, fold_1, g, F, H, rows, ws.ps, ws.sb), &s1, s));
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(g, w.w_2, w.b_2, mid, ws.la, H, F, rows, nullptr, nullptr), &s2, s));
             } else {
+                // (a side map that its launch cannot carry comes behind it)
+                const bool o_too = !last && carries_few(ws, H), f_too = !last && carries_few(ws, F);
                 if (!last)
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,
-                                                           nullptr, ws.max_rows, H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
-                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb, nullptr, ws.max_rows,
+                                                           H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, o_too ? &so : nullptr));
+                if (!o_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
                 if (!last) {
                     PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, nullptr));
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr,
-                                                           ws.max_rows, F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s));
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la,
-                                                           nullptr, ws.max_rows, H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s));
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr, ws.max_rows,
+                                                           F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, nullptr, nullptr, f_too ? &s1 : nullptr));
                 }
-                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
-                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
+                if (!f_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
+                if (!last)
+                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la, nullptr, ws.max_rows,
+                                                           H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, o_too ? &s2 : nullptr));
+                if (!o_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
             }
         } else if (carried && !last) {
             SmallGemm so = side_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H);
@@ -228,12 +231,12 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
             SmallGemm s2 = side_args(ws.cls_g, w.w_2d, w.b_2, mid_cls, ws.la, H, F);
             so.max_rows = s1.max_rows = s2.max_rows = (int64_t)align_up((size_t)n_req, 64);
             PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb, nullptr, ws.max_rows,
-                                                   H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, &so, ws.first_row));
+                                                   H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, &so));
             PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, &ffn_cls));
             PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr, ws.max_rows,
-                                                   F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, &s1, nullptr));
+                                                   F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, nullptr, &s1));
             PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la, nullptr, ws.max_rows,
-                                                   H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, &s2, ws.first_row));
+                                                   H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, &s2));
         } else {
             if (!last)
                 PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb,

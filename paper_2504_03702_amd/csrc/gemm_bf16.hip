@@ -32,6 +32,7 @@
 
 #include "device_util.h"
 #include "internal.h"
+#include "skinny_gemm.h"
 #include "small_gemm.h"
 
 namespace {
@@ -609,33 +610,40 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The per-request map that a launch can carry (see launch_gemm_bf16): 64 x 64 tiles for the maps back to the hidden width, 128 x 64
-// for the first feed-forward map, with as many slices on their way as the launch's LDS has room for.
+// The per-request map that a launch can carry (see launch_gemm_bf16): blocks of the skinny form up to PS_SKINNY_ROWS requests
+// (FEW), else 64 x 64 tiles for the maps back to the hidden width, 128 x 64 for the first feed-forward map, with as many slices on
+// their way as the launch's LDS has room for.
 constexpr int kNoSide = -1;
 template <int EPI>
 constexpr int side_of = EPI == EPI_BIAS_RESIDUAL ? (int)EPI_RESIDUAL_MAPPED : (int)EPI_GELU_SPLIT;
-template <int SIDE, int BM>
+template <int SIDE, int BM, bool FEW>
 struct SideTile {
+    using Args = std::conditional_t<FEW, SkinnyArgs, SmallGemm>;
     static constexpr int TM = SIDE == EPI_GELU_SPLIT ? 2 : 1;
     static constexpr int STAGES = SIDE == EPI_GELU_SPLIT ? (BM == 256 ? 6 : 3) : (BM == 256 ? 8 : 4);
-    static constexpr int BYTES = SIDE == kNoSide ? 0 : STAGES * 64 * (TM + 1) * 128;
+    static constexpr int BYTES = SIDE == kNoSide ? 0 : FEW ? kSkinnyLds : STAGES * 64 * (TM + 1) * 128;
 };
 
 // Rows in two regions: plan->m_tiles tiles of BM rows, then the others in tiles of 32 (tm0 + tm1) rows, as prep chose them
 // (PLANNED); without a plan all in tiles of BM rows.  SIDE: workgroups from g.wgs on do a per-request map; a unit that has no tile
 // in the launch's last round takes them.
-template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED, int SIDE>
+template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED, int SIDE, bool FEW>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
                                                                  const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk,
-                                                                 SmallGemm side) {
+                                                                 typename SideTile<SIDE, BM, FEW>::Args side) {
     using T = Tile<BM, BN, WM, WN>;
-    using S = SideTile<SIDE, BM>;
+    using S = SideTile<SIDE, BM, FEW>;
     constexpr int kBytes = EPI == EPI_BIAS_RESIDUAL ? T::LDS : T::STRIPS;
     constexpr bool SKIP = SIDE == EPI_RESIDUAL_MAPPED;
     __shared__ __align__(1024) unsigned char smem[kBytes > S::BYTES ? kBytes : S::BYTES];
     if constexpr (SIDE != kNoSide) {
         if ((int)blockIdx.x >= g.wgs) {
-            if (threadIdx.x < 256) small_tile<SIDE, S::TM, 1, S::STAGES>(side, blockIdx.x - g.wgs, smem, nullptr);
+            if constexpr (FEW) {
+                if ((int)(blockIdx.x - g.wgs) * kSkinnyCols < side.N)
+                    skinny_block<SIDE, WM * WN, SIDE != EPI_RESIDUAL_MAPPED>(side, blockIdx.x - g.wgs, smem);
+            } else {
+                if (threadIdx.x < 256) small_tile<SIDE, S::TM, 1, S::STAGES>(side, blockIdx.x - g.wgs, smem, nullptr);
+            }
             return;
         }
     }
@@ -672,7 +680,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
 
 template <int BM, int BN, int WM, int WN, bool PLANNED>
 void launch_cfg(GemmEpilogue epi, GemmArgs g, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk,
-                const SmallGemm* side, hipStream_t s) {
+                const SmallGemm* side, const SkinnyArgs* few, hipStream_t s) {
     // persistent: one workgroup per compute unit; the small tiles leave room for two (LDS and registers), which then hide
     // each other's waits, and take fewer workgroups if there cannot be that many tiles
     const int64_t tiles = (g.max_rows + BM - 1) / BM * (g.N / BN);
@@ -684,19 +692,23 @@ void launch_cfg(GemmEpilogue epi, GemmArgs g, const int32_t* total_rows, const G
         return (unsigned)((n + 7) / 8 * 8);
     };
 #define PS_LAUNCH(E)                                                                                                     \
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kNoSide>), dim3((unsigned)g.wgs), block, 0, s, g, total_rows, plan, clk, SmallGemm{})
+    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kNoSide, false>), dim3((unsigned)g.wgs), block, 0, s, g, total_rows, plan, clk, SmallGemm{})
 #define PS_LAUNCH_SIDE(E)                                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, side_of<E>>), dim3((unsigned)g.wgs + side_wgs(SideTile<side_of<E>, BM>::TM)), \
-                       block, 0, s, g, total_rows, plan, clk, *side)
+    do {                                                                                                                 \
+        constexpr int kSide = side_of<E>;                                                                                \
+        if (few)                                                                                                         \
+            hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kSide, true>),                              \
+                               dim3((unsigned)(g.wgs + few->N / kSkinnyCols)), block, 0, s, g, total_rows, plan, clk, *few);    \
+        else if (side)                                                                                                   \
+            hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kSide, false>),                             \
+                               dim3((unsigned)g.wgs + side_wgs(SideTile<kSide, BM, false>::TM)), block, 0, s, g, total_rows, plan, \
+                               clk, *side);                                                                              \
+        else                                                                                                             \
+            PS_LAUNCH(E);                                                                                                \
+    } while (0)
     switch (epi) {
-        case EPI_BIAS_GELU:
-            if (side) PS_LAUNCH_SIDE(EPI_BIAS_GELU);
-            else PS_LAUNCH(EPI_BIAS_GELU);
-            break;
-        case EPI_BIAS_RESIDUAL:
-            if (side) PS_LAUNCH_SIDE(EPI_BIAS_RESIDUAL);
-            else PS_LAUNCH(EPI_BIAS_RESIDUAL);
-            break;
+        case EPI_BIAS_GELU: PS_LAUNCH_SIDE(EPI_BIAS_GELU); break;
+        case EPI_BIAS_RESIDUAL: PS_LAUNCH_SIDE(EPI_BIAS_RESIDUAL); break;
         case EPI_QKV: PS_LAUNCH(EPI_QKV); break;
         case EPI_KV: PS_LAUNCH(EPI_KV); break;
         case EPI_GELU_SPLIT:
@@ -718,14 +730,13 @@ void launch_cfg(GemmEpilogue epi, GemmArgs g, const int32_t* total_rows, const G
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc residual, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
                       int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s,
-                      const SmallGemm* side, const uint8_t* first_row) {
+                      const uint8_t* first_row, const SmallGemm* side, const SkinnyArgs* few) {
     // Problems with few 256 x 256 tiles (whole calls on a micro-batch of a few requests) would leave most compute
     // units idle: 128 x 128 tiles give four times as many workgroups to spread them over.  EPI_GELU_SPLIT has only these
     // (its second set of accumulators): 4096 requests of hidden 768 in 57 us, 20000 in 234.
-    const int64_t big_tiles = (max_rows + 255) / 256 * (N / 256);
     const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden, 0, first_row};
-    if (epi == EPI_GELU_SPLIT || big_tiles < 128)
-        launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, side, s);
+    if (epi == EPI_GELU_SPLIT || !large_tiles(max_rows, N))
+        launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, side, few, s);
     else
-        launch_cfg<256, 256, 2, 4, true>(epi, g, total_rows, plan, clk, side, s);
+        launch_cfg<256, 256, 2, 4, true>(epi, g, total_rows, plan, clk, side, few, s);
 }

@@ -96,6 +96,7 @@ struct Workspace {
     void *cls_a, *cls_g;         // per-request rows of the [CLS] refinement: [cls_rows][2H], [cls_rows][2F] bf16
     int64_t cls_rows;
     int64_t max_rows;            // rows every activation buffer holds (multiple of PS_ROW_TILE)
+    int64_t likely_rows;         // rows in use, as far as the host can tell (for choices that change no result)
     int64_t max_qtiles;
     size_t bytes;
 };
@@ -155,6 +156,10 @@ struct ResidualSrc {
 // padded twelve-layer 33 2.80 / 2.33, 64 4.37 / 4.11, 200 10.96 / 10.75; packed 17 2.07 / 1.71, 400 20.06 / 19.82, 1024 49.8 / 49.6,
 // 2048 even; production 24 6.82 / 6.49, 100 22.6 / 22.1, 400 78.7 / 78.4.
 #define PS_CARRIED_REQUESTS 1024
+// Whether the large maps of a call carry its per-request ones (the others have launches of their own, or take the small tiles).
+inline bool carries_side_maps(int32_t n_req, int64_t max_rows) {
+    return n_req <= PS_CARRIED_REQUESTS && (n_req > PS_SKINNY_ROWS || max_rows > PS_FUSED_ROWS);
+}
 enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
 struct SkinnyArgs {
     const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)
@@ -191,15 +196,24 @@ struct SmallGemm {
     const int32_t *row_start, *seq_len;
 };
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
+// Whether a map of `max_rows` rows takes 256 x 256 tiles.
+inline bool large_tiles(int64_t max_rows, int N) { return (max_rows + 255) / 256 * (N / 256) >= 128; }
+// Whether it can carry the side map of a few requests.  That map's blocks stream W at one unit's rate: beside a tile of 128 x 128
+// on the same unit they are what the launch waits for (12 production prompts, 352 tiles: output projection 24 us and 9 apart, 35
+// together; second feed-forward map 73 and 30, 112), on a unit of their own they are hidden.  Padded calls are taken to hold half
+// of their slots (12 padded prompts of hidden 768 1.90 -> 1.49 ms carried, 16 2.05 -> 1.67).
+inline bool carries_few(const Workspace& ws, int N) {
+    return large_tiles(ws.max_rows, N) || (ws.likely_rows + 127) / 128 * (N / 128) + N / 64 <= 256;
+}
 // C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
 // The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,
 // may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
-// side: EPI_BIAS_RESIDUAL and EPI_BIAS_GELU can carry the per-request map of the same sublayer (EPI_RESIDUAL_MAPPED, EPI_GELU_SPLIT;
-// more than PS_SKINNY_ROWS requests) in further workgroups; rows that first_row marks are then left to it.
+// side, few: EPI_BIAS_RESIDUAL and EPI_BIAS_GELU can carry the per-request map of the same sublayer (EPI_RESIDUAL_MAPPED,
+// EPI_GELU_SPLIT) in further workgroups, few for at most PS_SKINNY_ROWS requests; rows that first_row marks are then left to it.
 void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const float* bias,
                       ResidualSrc res, void* C, bf16_t* vt, int64_t max_rows, int N, int K,
                       int hidden, const int32_t* total_rows, const GemmPlan* plan, int64_t* clk, hipStream_t s,
-                      const SmallGemm* side = nullptr, const uint8_t* first_row = nullptr);
+                      const uint8_t* first_row = nullptr, const SmallGemm* side = nullptr, const SkinnyArgs* few = nullptr);
 // out[r][0:hidden] = x[first row of request r] for every request (zeros for faulty ones and padding rows).
 void launch_cls_rows(const ps_model* m, int32_t n_req, const Workspace& ws, const bf16_t* x, bf16_t* out, hipStream_t s);
 // first_rows_only: compute (at least) the first query row of every request and nothing beyond its

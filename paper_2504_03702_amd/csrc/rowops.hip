@@ -516,7 +516,7 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
                            (const bf16_t*)m->e_tok, (const bf16_t*)m->e_pos, (const bf16_t*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
                            ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, ws.qtile_start, ws.qtiles,
-                           n_req > PS_SKINNY_ROWS && n_req <= PS_CARRIED_REQUESTS ? ws.first_row : nullptr, st);
+                           carries_side_maps(n_req, ws.max_rows) ? ws.first_row : nullptr, st);
     else
         hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const float*)m->e_tok, (const float*)m->e_pos, (const float*)m->e_soft,
