@@ -17,7 +17,7 @@ Workspace plan_workspace(const ps_model_info& info, int64_t n_tokens, int32_t n_
     const int64_t H = info.hidden, F = info.ffn;
     int64_t rows = n_tokens + (int64_t)n_req * (info.n_soft + PS_ROW_ALIGN - 1) + PS_KEY_SLACK;
     rows = (int64_t)align_up((size_t)(rows > 0 ? rows : 1), PS_ROW_TILE);
-    ws.max_rows = ws.likely_rows = rows;
+    ws.max_rows = rows;
     ws.max_qtiles = rows / PS_ATT_BQ + n_req;
     size_t off = 0;
     uint8_t* b = (uint8_t*)base;
@@ -222,7 +222,7 @@ extern "C" int ps_predict_load(ps_model* m, const int32_t* token_ids, const int3
     if (((uintptr_t)workspace & 255) != 0) return PS_EWORKSPACE;
     Workspace ws = plan_workspace(m->info, n_tokens, n_req, workspace);
     if (ws.bytes > workspace_bytes) return PS_EWORKSPACE;
-    if (lengths) ws.likely_rows = ws.max_rows / 2;
+    ws.padded = lengths != nullptr;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
     {

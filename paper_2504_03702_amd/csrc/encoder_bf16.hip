@@ -136,9 +136,9 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
     };
     // Calls of a few requests over few rows: a layer is five launches, each map's launch doing the per-request map
     // beside it and making the row statistics it needs from the previous launch's pieces.
-    const bool fused = skinny && ws.max_rows <= PS_FUSED_ROWS;
+    const bool fused = small_maps(ws, n_req, H);
     // With more of either, up to PS_CARRIED_REQUESTS, the launches of the maps of all rows carry the per-request ones.
-    const bool carried = carries_side_maps(n_req, ws.max_rows);
+    const bool carried = carries_side_maps(ws, n_req, H);
     for (int l = 0; l < f.layers; ++l) {
         const LayerWeights& w = m->layers[(size_t)l];
         // After the last layer only the first row of every request goes on (to the head), and within

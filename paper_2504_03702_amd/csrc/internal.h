@@ -96,7 +96,7 @@ struct Workspace {
     void *cls_a, *cls_g;         // per-request rows of the [CLS] refinement: [cls_rows][2H], [cls_rows][2F] bf16
     int64_t cls_rows;
     int64_t max_rows;            // rows every activation buffer holds (multiple of PS_ROW_TILE)
-    int64_t likely_rows;         // rows in use, as far as the host can tell (for choices that change no result)
+    bool padded;                 // the caller's layout: how many of the rows are in use is for the device to know
     int64_t max_qtiles;
     size_t bytes;
 };
@@ -145,10 +145,6 @@ struct ResidualSrc {
 // The per-request forms (EPI_GELU_SPLIT, EPI_RESIDUAL_MAPPED, EPI_Q_MAPPED) for calls of at most PS_SKINNY_ROWS
 // requests: a stream over W with the contraction split among a workgroup's wavefronts.
 #define PS_SKINNY_ROWS 16
-// Activation rows (of the workspace) up to which a call of a few requests takes the launches that carry both maps.
-// Against the large tiles with launches of their own for the rest: six-layer encoder, hidden 768: 253 rows 805 -> 350 us,
-// 1536 rows 890 -> 520, 3170 rows 938 -> 890; hidden 1024: 3700 rows even, 4700 rows 4.3 -> 5.0 ms.
-#define PS_FUSED_ROWS 3584
 // Calls of more than PS_SKINNY_ROWS and up to this many requests: the launches of the maps of all rows carry the per-request ones
 // in further workgroups, which take the units that the launch's last round leaves idle (64 padded prompts of hidden 768: of 256
 // units the maps back to it use 200 to 230), instead of three launches of 7 to 15 us that use a few units each.  Milliseconds,
@@ -156,10 +152,6 @@ struct ResidualSrc {
 // padded twelve-layer 33 2.80 / 2.33, 64 4.37 / 4.11, 200 10.96 / 10.75; packed 17 2.07 / 1.71, 400 20.06 / 19.82, 1024 49.8 / 49.6,
 // 2048 even; production 24 6.82 / 6.49, 100 22.6 / 22.1, 400 78.7 / 78.4.
 #define PS_CARRIED_REQUESTS 1024
-// Whether the large maps of a call carry its per-request ones (the others have launches of their own, or take the small tiles).
-inline bool carries_side_maps(int32_t n_req, int64_t max_rows) {
-    return n_req <= PS_CARRIED_REQUESTS && (n_req > PS_SKINNY_ROWS || max_rows > PS_FUSED_ROWS);
-}
 enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
 struct SkinnyArgs {
     const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)
@@ -196,6 +188,19 @@ struct SmallGemm {
     const int32_t *row_start, *seq_len;
 };
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
+// Whether a call of a few requests takes the small tiles, whose launches carry both maps: up to 3584 rows (of the workspace), of
+// wide models fewer.  Padded calls, which hold half of their slots or so, up to 4608.  Against the large tiles with the side maps
+// carried, small / large, us: packed, hidden 768, twelve layers, 12 requests (2500 rows) 1465 / 1472, 13 1542 / 1495, 14 1588 /
+// 1455; hidden 1024, 8 requests (2400 rows) 2708 / 2428, 10 3182 / 2770, 7 (2200) 2567 / 2553; padded to 512, 8 requests, slots
+// filled to 0.4 1195 / 1277, 0.6 1382 / 1423, 0.8 1567 / 1495.
+inline bool small_maps(const Workspace& ws, int32_t n_req, int hidden) {
+    const int64_t most = ws.padded ? 4608 : 2300000 / hidden < 3584 ? 2300000 / hidden : 3584;
+    return n_req <= PS_SKINNY_ROWS && ws.max_rows <= most;
+}
+// Whether the large maps of a call carry its per-request ones (the others have launches of their own, or take the small tiles).
+inline bool carries_side_maps(const Workspace& ws, int32_t n_req, int hidden) {
+    return n_req <= PS_CARRIED_REQUESTS && !small_maps(ws, n_req, hidden);
+}
 // Whether a map of `max_rows` rows takes 256 x 256 tiles.
 inline bool large_tiles(int64_t max_rows, int N) { return (max_rows + 255) / 256 * (N / 256) >= 128; }
 // Whether it can carry the side map of a few requests.  That map's blocks stream W at one unit's rate: beside a tile of 128 x 128
@@ -203,7 +208,7 @@ inline bool large_tiles(int64_t max_rows, int N) { return (max_rows + 255) / 256
 // together; second feed-forward map 73 and 30, 112), on a unit of their own they are hidden.  Padded calls are taken to hold half
 // of their slots (12 padded prompts of hidden 768 1.90 -> 1.49 ms carried, 16 2.05 -> 1.67).
 inline bool carries_few(const Workspace& ws, int N) {
-    return large_tiles(ws.max_rows, N) || (ws.likely_rows + 127) / 128 * (N / 128) + N / 64 <= 256;
+    return large_tiles(ws.max_rows, N) || (ws.max_rows / (ws.padded ? 2 : 1) + 127) / 128 * (N / 128) + N / 64 <= 256;
 }
 // C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
 // The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,

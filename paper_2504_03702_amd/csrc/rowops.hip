@@ -500,7 +500,7 @@ void launch_prep(const ps_model* m, const int32_t* offsets, const int32_t* lengt
                  const Workspace& ws, ps_status* st, hipStream_t s) {
     const int h = m->info.hidden / 256, f = m->info.ffn / 256;
     // (calls that take the small tiles only, run_encoder_bf16, need none; nor do fp32 models)
-    const bool planned = m->info.dtype == 1 && (n_req > PS_SKINNY_ROWS || ws.max_rows > PS_FUSED_ROWS);
+    const bool planned = m->info.dtype == 1 && !small_maps(ws, n_req, m->info.hidden);
     const int4 plan_cols = planned ? make_int4(3 * h, 2 * h, h, f) : make_int4(0, 0, 0, 0);
     hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, offsets, lengths, n_req, m->info.n_soft, m->info.max_pos,
                        (long long)n_tokens, (long long)(ws.max_rows - PS_KEY_SLACK), plan_cols, planned ? 1 : 0, ws.meta, ws.seq_len,
@@ -516,7 +516,7 @@ void launch_embed(const ps_model* m, const int32_t* token_ids, const int32_t* of
                            (const bf16_t*)m->e_tok, (const bf16_t*)m->e_pos, (const bf16_t*)m->e_soft,
                            m->lne_g, m->lne_b, m->ln_eps, f.hidden, f.vocab, f.n_soft, ws.meta, ws.seq_len,
                            ws.row_start, ws.bad_req, (bf16_t*)ws.x, ws.la, ws.sa, ws.qtile_start, ws.qtiles,
-                           carries_side_maps(n_req, ws.max_rows) ? ws.first_row : nullptr, st);
+                           carries_side_maps(ws, n_req, f.hidden) ? ws.first_row : nullptr, st);
     else
         hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks), dim3(256), 0, s, token_ids, offsets, n_req,
                            (const float*)m->e_tok, (const float*)m->e_pos, (const float*)m->e_soft,
