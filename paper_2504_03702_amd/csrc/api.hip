@@ -16,6 +16,7 @@ Workspace plan_workspace(const ps_model_info& info, int64_t n_tokens, int32_t n_
     const size_t es = info.dtype == 1 ? 2 : 4;
     const int64_t H = info.hidden, F = info.ffn;
     int64_t rows = n_tokens + (int64_t)n_req * (info.n_soft + PS_ROW_ALIGN - 1) + PS_KEY_SLACK;
+    ws.likely_rows = rows;
     rows = (int64_t)align_up((size_t)(rows > 0 ? rows : 1), PS_ROW_TILE);
     ws.max_rows = rows;
     ws.max_qtiles = rows / PS_ATT_BQ + n_req;

@@ -96,6 +96,7 @@ struct Workspace {
     void *cls_a, *cls_g;         // per-request rows of the [CLS] refinement: [cls_rows][2H], [cls_rows][2F] bf16
     int64_t cls_rows;
     int64_t max_rows;            // rows every activation buffer holds (multiple of PS_ROW_TILE)
+    int64_t likely_rows;         // rows in use if the caller's offsets do not overlap (for choices that change no result)
     bool padded;                 // the caller's layout: how many of the rows are in use is for the device to know
     int64_t max_qtiles;
     size_t bytes;
@@ -178,6 +179,7 @@ struct SmallGemm {
     void* C;
     bf16_t* vt;
     int64_t max_rows;            // rows the buffers hold; also the row stride of vt
+    int64_t likely_rows;         // rows by which the tiles are chosen (0: max_rows)
     int N, K, hidden;
     const int32_t* rows;         // rows to compute
     const int32_t* live_rows;    // rows that belong to requests (the others take statistics of zero)

@@ -41,8 +41,9 @@ void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     const int side_blocks = SIDE != kNoSide ? (int)align_up((size_t)(side->N / kSkinnyCols), 8) : 0;
     const SkinnyArgs sd = SIDE != kNoSide ? *side : SkinnyArgs{};
     constexpr int kParts = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED ? 2 : 1;   // rows of the tile per row of the result
-    auto tiles = [&](int bm, int bn) { return (p.max_rows * kParts + bm - 1) / bm * (p.N / bn); };
-    auto grid = [&](int bm, int bn) { return dim3((unsigned)(side_blocks + (tiles(bm, bn) + 7) / 8 * 8)); };
+    auto tiles_of = [&](int64_t rows, int bm, int bn) { return (rows * kParts + bm - 1) / bm * (p.N / bn); };
+    auto tiles = [&](int bm, int bn) { return tiles_of(p.likely_rows ? p.likely_rows : p.max_rows, bm, bn); };
+    auto grid = [&](int bm, int bn) { return dim3((unsigned)(side_blocks + (tiles_of(p.max_rows, bm, bn) + 7) / 8 * 8)); };
 #define PS_SMALL(TM, TN, STAGES) \
     hipLaunchKernelGGL((small_gemm_kernel<EPI, TM, TN, STAGES, SIDE>), grid(64 * TM, 64 * TN), dim3(256), 0, s, p, sd, side_blocks)
     // At most one 64 x 64 tile per compute unit: a unit to itself, seven slices on their way.  Beyond that what the unit
