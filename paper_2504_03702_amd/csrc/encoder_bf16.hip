@@ -158,8 +158,8 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
         const float2* stats_in = l > 0 ? ws.ps : nullptr;   // (fused) pieces of the sums entering the layer; the embedding leaves statistics
         auto small = [&](const bf16_t* A, const void* W, const float* bias, const ResidualSrc& r, void* C, int N, int K,
                          const int32_t* n_rows, const float2* pieces, float2* stats_out) {
-            return SmallGemm{A, (const bf16_t*)W, bias, r, C, vt, ws.max_rows, ws.likely_rows, N, K, H, n_rows, rows, pieces, stats_out,
-                             1.0f / (float)H, m->ln_eps, n_req, ws.row_start, ws.seq_len};
+            return SmallGemm{A, (const bf16_t*)W, bias, r, C, vt, ws.max_rows, ws.likely_rows,
+                             ws.likely_rows / (ws.padded ? 2 : 1), N, K, H, n_rows, rows, pieces, stats_out, 1.0f / (float)H, m->ln_eps, n_req, ws.row_start, ws.seq_len};
         };
         if (!last) {
             if (fused)

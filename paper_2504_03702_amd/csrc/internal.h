@@ -180,6 +180,7 @@ struct SmallGemm {
     bf16_t* vt;
     int64_t max_rows;            // rows the buffers hold; also the row stride of vt
     int64_t likely_rows;         // rows by which the tiles are chosen (0: max_rows)
+    int64_t usual_rows;          // of padded calls half of them (0: max_rows)
     int N, K, hidden;
     const int32_t* rows;         // rows to compute
     const int32_t* live_rows;    // rows that belong to requests (the others take statistics of zero)

@@ -5,7 +5,7 @@
 //
 // With so few rows the map is a stream over W: a tiled kernel would put one tile on a handful of compute units and
 // walk the whole contraction there, slice after slice, each waiting out a trip to memory.  Here a workgroup owns 64
-// output columns and the contraction is split in 8 shares, dealt to its wavefronts: each issues
+// output columns (or 32) and the contraction is split in 8 shares, dealt to its wavefronts: each issues
 // v_mfma_f32_16x16x32_bf16 on fragments loaded straight from global memory (A: request r = lane % 16, sixteen
 // consecutive k per lane and 64-deep round; W the same with its row = output column), several rounds' loads
 // requested before the first is used.  Where A carries each value as hi + lo, a W fragment serves both parts.  The
@@ -58,14 +58,17 @@ struct SkinnyPieces {
     }
 };
 
-// One block of 64 output columns by NW wavefronts; smem: kSkinnyLds bytes.  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED
-// take hi | lo rows (each W fragment serves two MFMAs).  GATHER: the rows of A are taken from the stream itself, at each request's first row: for EPI_Q_MAPPED the hi
-// parts, for EPI_GELU_SPLIT the LayerNorm of the sums (both parts joined), as hi | lo.
-template <int EPI, int NW, bool GATHER>
+// One block of 16 G output columns by NW wavefronts; smem: kSkinnyLds bytes.  EPI_GELU_SPLIT and EPI_RESIDUAL_MAPPED
+// take hi | lo rows (each W fragment serves two MFMAs).  GATHER: the rows of A are taken from the stream itself, at
+// each request's first row: for EPI_Q_MAPPED the hi parts, for EPI_GELU_SPLIT the LayerNorm of the sums (both parts
+// joined), as hi | lo.
+// G: groups of 16 columns of a block; 4, or 2 for EPI_GELU_SPLIT, which leaves no pieces of 64 columns.
+template <int EPI, int NW, bool GATHER, int G = kSkinnyCols / 16>
 __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem) {
     constexpr bool DUAL = EPI != EPI_Q_MAPPED;
     constexpr bool NORM = GATHER && EPI == EPI_GELU_SPLIT;
     constexpr int SH = kSkinnyShares / NW;
+    static_assert(G == kSkinnyCols / 16 || EPI == EPI_GELU_SPLIT, "pieces of 64 columns");
     const ResidualSrc& res = p.res;
     const int N = p.N, K = p.K;
     sk_f32x4(*s_part)[4][64] = (sk_f32x4(*)[4][64])smem;    // [share][column group][lane]: 16 rows x 16 columns each
@@ -73,7 +76,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     float2* s_st = (float2*)(smem + (kSkinnyShares + 1) * 4 * 64 * 16);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int frow = lane & 15, fq = lane >> 4;
-    const int n0 = block * kSkinnyCols;
+    const int n0 = block * 16 * G;
     const int n_req = p.n_req;
     // The stream row of request frow.  (Absent requests take the last one's, faulty ones have a row start inside the
     // buffers too; the results of both are not stored.)
@@ -116,7 +119,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     }
     auto epilogue_loads = [&]() {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < G; ++g) {
             const int c = n0 + 16 * g + frow;
             bv[g] = p.bias[c];
             if (EPI == EPI_Q_MAPPED) cs[g] = res.colsum[c];
@@ -127,7 +130,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
             for (int e = 0; e < 4; ++e) {
                 st[e] = res.stats[srow[e]];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                for (int g = 0; g < G; ++g) {
                     const int64_t at = srow[e] * N + n0 + 16 * g + frow;
                     yprev[e][g] = stream_join(res.y_hi[at], res.y_lo[at]);
                 }
@@ -151,16 +154,16 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     constexpr int U = 2;                                // rounds whose loads are in flight together
     const int first = wave * SH;
     const int r0 = first * total_rounds / kSkinnyShares, r1 = (first + SH) * total_rounds / kSkinnyShares;
-    sk_f32x4 acc[4];
+    sk_f32x4 acc[G];
     int share = first, share_end = (first + 1) * total_rounds / kSkinnyShares;
     auto clear = [&]() {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < G; ++g) acc[g] = sk_f32x4{0.f, 0.f, 0.f, 0.f};
     };
     auto close_shares = [&](int t) {                    // round t belongs to a later share
         while (share < first + SH && t >= share_end) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) s_part[share][g][lane] = acc[g];
+            for (int g = 0; g < G; ++g) s_part[share][g][lane] = acc[g];
             clear();
             ++share;
             share_end = (share + 1) * total_rounds / kSkinnyShares;
@@ -173,7 +176,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     const float *gp = NORM ? res.gamma + 16 * fq : nullptr, *bp = NORM ? res.beta + 16 * fq : nullptr;
 #pragma unroll 1
     for (int t0 = r0; t0 == r0 || t0 < r1; t0 += U) {
-        sk_bf16x8 fa[U][2] = {}, fl[DUAL ? U : 1][2] = {}, fw[U][4][2];
+        sk_bf16x8 fa[U][2] = {}, fl[DUAL ? U : 1][2] = {}, fw[U][G][2];
         float4 gv[NORM ? U : 1][4], bb[NORM ? U : 1][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -186,7 +189,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
                     if (DUAL) fl[u][h] = *(const sk_bf16x8*)(lp + 64 * t + 8 * h);
                 }
 #pragma unroll
-                for (int g = 0; g < 4; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg + 64 * t + 8 * h);
+                for (int g = 0; g < G; ++g) fw[u][g][h] = *(const sk_bf16x8*)(wp + g * wg + 64 * t + 8 * h);
             }
             if (NORM) {
 #pragma unroll
@@ -225,7 +228,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
                     fl[u][h] = yl.v;
                 }
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                for (int g = 0; g < G; ++g) {
                     acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][h], fw[u][g][h], acc[g], 0, 0, 0);
                     if (DUAL) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl[u][h], fw[u][g][h], acc[g], 0, 0, 0);
                 }
@@ -234,7 +237,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
     }
     close_shares(total_rounds);
     __syncthreads();
-    if (wave < 4) {                                     // column group `wave`: the eight partial results in order
+    if (wave < G) {                                     // column group `wave`: the eight partial results in order
         sk_f32x4 t = s_part[0][wave][lane];
 #pragma unroll
         for (int w = 1; w < kSkinnyShares; ++w) {
@@ -251,14 +254,14 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
         for (int e = 0; e < 4; ++e) st[e] = make_float2(__shfl(ast.x, 4 * fq + e, 64), __shfl(ast.y, 4 * fq + e, 64));
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = s_sum[g][lane];
+    for (int g = 0; g < G; ++g) acc[g] = s_sum[g][lane];
     if (EPI == EPI_GELU_SPLIT) {
         bf16_t* C = (bf16_t*)p.C;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int64_t r = 4 * fq + e;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < G; ++g) {
                 const int c = n0 + 16 * g + frow;
                 const float v = gelu_erf(acc[g][e] + bv[g]);
                 const bf16_t hi = f32_to_bf16(v);
@@ -275,7 +278,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
             bf16_t* C = (bf16_t*)p.C;
             const float nm = -st[e].x * st[e].y;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < G; ++g) {
                 const float v = fmaf(acc[g][e], st[e].y, fmaf(nm, cs[g], bv[g]));
                 if (live[e]) C[row * 2 * p.hidden + n0 + 16 * g + frow] = f32_to_bf16(v);
             }
@@ -283,7 +286,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
             bf16_t* Cl = (bf16_t*)p.C;
             float sm = 0.f, sq = 0.f;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < G; ++g) {
                 const int c = n0 + 16 * g + frow;
                 const float o = residual_sum(acc[g][e], yprev[e][g], st[e], gm[g], bt[g] + bv[g]);
                 sm += o;

@@ -5,10 +5,10 @@ namespace {
 
 const int kSkinnyWaves = 8;
 
-template <int EPI, bool GATHER>
+template <int EPI, bool GATHER, int G>
 __global__ __launch_bounds__(kSkinnyWaves * 64) void skinny_gemm_kernel(SkinnyArgs p) {
     __shared__ __align__(16) unsigned char smem[kSkinnyLds];
-    skinny_block<EPI, kSkinnyWaves, GATHER>(p, blockIdx.x, smem);
+    skinny_block<EPI, kSkinnyWaves, GATHER, G>(p, blockIdx.x, smem);
 }
 
 }  // namespace
@@ -20,9 +20,9 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void skinny_gemm_kernel(SkinnyAr
 void launch_skinny_gemm_bf16(GemmEpilogue epi, const SkinnyArgs& p, hipStream_t s) {
     const dim3 grid((unsigned)(p.N / kSkinnyCols)), block(kSkinnyWaves * 64);
     switch (epi) {
-        case EPI_GELU_SPLIT: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_GELU_SPLIT, true>), grid, block, 0, s, p); break;
-        case EPI_RESIDUAL_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_RESIDUAL_MAPPED, false>), grid, block, 0, s, p); break;
-        case EPI_Q_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_Q_MAPPED, true>), grid, block, 0, s, p); break;
+        case EPI_GELU_SPLIT: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_GELU_SPLIT, true, 2>), dim3((unsigned)(p.N / 32)), block, 0, s, p); break;
+        case EPI_RESIDUAL_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_RESIDUAL_MAPPED, false, 4>), grid, block, 0, s, p); break;
+        case EPI_Q_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_Q_MAPPED, true, 4>), grid, block, 0, s, p); break;
         default: break;                                  // the other epilogues have no per-request form
     }
 }

@@ -20,8 +20,10 @@
 namespace {
 
 constexpr int kNoSide = -1;
+constexpr int kSideGroups = kSkinnyCols / 16;
 
-template <int EPI, int TM, int TN, int STAGES, int SIDE>
+// G: groups of 16 columns of a block of the side map
+template <int EPI, int TM, int TN, int STAGES, int SIDE, int G>
 __global__ __launch_bounds__(256, TM == 2 && TN == 1 ? 2 : 1) void small_gemm_kernel(SmallGemm p, SkinnyArgs side, int side_blocks) {
     constexpr int kBytes = STAGES * 64 * (TM + TN) * 128;
     static_assert(SIDE == kNoSide || kBytes >= kSkinnyLds, "LDS regions");
@@ -29,7 +31,8 @@ __global__ __launch_bounds__(256, TM == 2 && TN == 1 ? 2 : 1) void small_gemm_ke
     __shared__ float2 s_st[64 * TM];
     if (SIDE != kNoSide) {
         if ((int)blockIdx.x < side_blocks) {
-            if ((int)blockIdx.x * kSkinnyCols < side.N) skinny_block<SIDE, 4, SIDE != EPI_RESIDUAL_MAPPED>(side, blockIdx.x, smem);
+            if ((int)blockIdx.x * 16 * G < side.N)
+                skinny_block<SIDE, 4, SIDE != EPI_RESIDUAL_MAPPED, G>(side, blockIdx.x, smem);
             return;
         }
     }
@@ -38,14 +41,21 @@ __global__ __launch_bounds__(256, TM == 2 && TN == 1 ? 2 : 1) void small_gemm_ke
 
 template <int EPI, int SIDE>
 void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
-    const int side_blocks = SIDE != kNoSide ? (int)align_up((size_t)(side->N / kSkinnyCols), 8) : 0;
     const SkinnyArgs sd = SIDE != kNoSide ? *side : SkinnyArgs{};
     constexpr int kParts = EPI == EPI_GELU_SPLIT || EPI == EPI_RESIDUAL_MAPPED ? 2 : 1;   // rows of the tile per row of the result
     auto tiles_of = [&](int64_t rows, int bm, int bn) { return (rows * kParts + bm - 1) / bm * (p.N / bn); };
     auto tiles = [&](int bm, int bn) { return tiles_of(p.likely_rows ? p.likely_rows : p.max_rows, bm, bn); };
-    auto grid = [&](int bm, int bn) { return dim3((unsigned)(side_blocks + (tiles_of(p.max_rows, bm, bn) + 7) / 8 * 8)); };
-#define PS_SMALL(TM, TN, STAGES) \
-    hipLaunchKernelGGL((small_gemm_kernel<EPI, TM, TN, STAGES, SIDE>), grid(64 * TM, 64 * TN), dim3(256), 0, s, p, sd, side_blocks)
+    const int64_t usual = p.usual_rows ? p.usual_rows : p.max_rows;
+    auto blocks = [&](int groups) { return SIDE != kNoSide ? (int)align_up((size_t)(sd.N / (16 * groups)), 8) : 0; };
+    auto grid = [&](int bm, int bn, int groups) {
+        return dim3((unsigned)(blocks(groups) + (tiles_of(p.max_rows, bm, bn) + 7) / 8 * 8));
+    };
+#define PS_SMALL(TM, TN, STAGES, G) \
+    hipLaunchKernelGGL((small_gemm_kernel<EPI, TM, TN, STAGES, SIDE, G>), grid(64 * TM, 64 * TN, G), dim3(256), 0, s, p, sd, blocks(G))
+    // Blocks of 32 columns for the first feed-forward map's side map: half the loads a block, where the launch waits for
+    // those blocks, that is while they and the tiles have places at the same time (one prompt of hidden 768, 192 + 48
+    // places of 512, 342 -> 326 us a call, 5 of 432 + 48 410 -> 396; 6 of 480 + 48 take 421, with 32 columns 435; 3 padded to 512, half of 528 + 48, 765 -> 744).
+    constexpr int kFine = SIDE == EPI_GELU_SPLIT ? 2 : kSideGroups;
     // At most one 64 x 64 tile per compute unit: a unit to itself, seven slices on their way.  Beyond that what the unit
     // reads from LDS and L2 per product counts: 128 x 64 tiles, two to a unit (1536 rows of hidden 768, the query-key-value
     // map, 468 tiles for 512 places, 18.5 -> 16.0 us, the second feed-forward map 31.7 -> 26.0; where the tiles just pass the
@@ -54,16 +64,22 @@ void launch(const SmallGemm& p, const SkinnyArgs* side, hipStream_t s) {
     // (1922 rows of hidden 1024: 54.5 -> 44.5 us).
     constexpr bool kResid = EPI == EPI_BIAS_RESIDUAL || EPI == EPI_RESIDUAL_MAPPED;
     if (tiles(64, 64) <= 256) {
-        PS_SMALL(1, 1, 8);
+        PS_SMALL(1, 1, 8, kFine);
         return;
     }
     if constexpr (kResid) {
         if (tiles(128, 128) >= 128) {
-            PS_SMALL(2, 2, 4);
+            PS_SMALL(2, 2, 4, kSideGroups);
             return;
         }
     }
-    PS_SMALL(2, 1, 3);
+    if constexpr (kFine != kSideGroups) {
+        if (tiles_of(usual, 128, 64) + blocks(kSideGroups) <= 512) {
+            PS_SMALL(2, 1, 3, kFine);
+            return;
+        }
+    }
+    PS_SMALL(2, 1, 3, kSideGroups);
 #undef PS_SMALL
 }
 
