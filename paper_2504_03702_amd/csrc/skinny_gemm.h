@@ -62,13 +62,12 @@ struct SkinnyPieces {
 // take hi | lo rows (each W fragment serves two MFMAs).  GATHER: the rows of A are taken from the stream itself, at
 // each request's first row: for EPI_Q_MAPPED the hi parts, for EPI_GELU_SPLIT the LayerNorm of the sums (both parts
 // joined), as hi | lo.
-// G: groups of 16 columns of a block; 4, or 2 for EPI_GELU_SPLIT, which leaves no pieces of 64 columns.
+// G: groups of 16 columns of a block; 4 where it leaves pieces of 64 columns.
 template <int EPI, int NW, bool GATHER, int G = kSkinnyCols / 16>
 __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem) {
     constexpr bool DUAL = EPI != EPI_Q_MAPPED;
     constexpr bool NORM = GATHER && EPI == EPI_GELU_SPLIT;
     constexpr int SH = kSkinnyShares / NW;
-    static_assert(G == kSkinnyCols / 16 || EPI == EPI_GELU_SPLIT, "pieces of 64 columns");
     const ResidualSrc& res = p.res;
     const int N = p.N, K = p.K;
     sk_f32x4(*s_part)[4][64] = (sk_f32x4(*)[4][64])smem;    // [share][column group][lane]: 16 rows x 16 columns each
@@ -297,7 +296,7 @@ __device__ void skinny_block(const SkinnyArgs& p, int block, unsigned char* smem
                     Cl[row * N + c] = (bf16_t)w;
                 }
             }
-            if (res.pstats) {
+            if (G == kSkinnyCols / 16 && res.pstats) {
                 sm = sum16(sm);
                 sq = sum16(sq);
                 if (live[e] && frow == 0) res.pstats[row * (N >> 6) + (n0 >> 6)] = make_float2(sm, sq);

@@ -21,7 +21,13 @@ void launch_skinny_gemm_bf16(GemmEpilogue epi, const SkinnyArgs& p, hipStream_t 
     const dim3 grid((unsigned)(p.N / kSkinnyCols)), block(kSkinnyWaves * 64);
     switch (epi) {
         case EPI_GELU_SPLIT: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_GELU_SPLIT, true, 2>), dim3((unsigned)(p.N / 32)), block, 0, s, p); break;
-        case EPI_RESIDUAL_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_RESIDUAL_MAPPED, false, 4>), grid, block, 0, s, p); break;
+        case EPI_RESIDUAL_MAPPED:
+            // Without pieces of 64 columns to leave (the last layer) 16 columns a block: what a unit can have on its way from
+            // memory bounds this, and 48 units ask for more than 12 (one prompt, hidden 768: second feed-forward map 14.8 ->
+            // 6.5 us, output projection 6.4 -> 4.2; the first feed-forward map, 96 blocks of 32, is no faster with 192).
+            if (p.res.pstats) hipLaunchKernelGGL((skinny_gemm_kernel<EPI_RESIDUAL_MAPPED, false, 4>), grid, block, 0, s, p);
+            else hipLaunchKernelGGL((skinny_gemm_kernel<EPI_RESIDUAL_MAPPED, false, 1>), dim3((unsigned)(p.N / 16)), block, 0, s, p);
+            break;
         case EPI_Q_MAPPED: hipLaunchKernelGGL((skinny_gemm_kernel<EPI_Q_MAPPED, true, 4>), grid, block, 0, s, p); break;
         default: break;                                  // the other epilogues have no per-request form
     }
