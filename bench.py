@@ -29,8 +29,8 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak
 # step), from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; profiles/production_gemm_traffic.txt)
 # scaled by what the same counters read for a 1 GiB elementwise copy (x2.0 and x1.0).  Valid only for
 # the kernel source it was measured on: reported as null once that file has changed.
-GEMM_TRAFFIC = {"source_sha256_16": "3fba2fa1ecc01798", "workload": "production",
-                "fetch_bytes": 23.049e9, "write_bytes": 10.075e9}
+GEMM_TRAFFIC = {"source_sha256_16": "82767097dfbd03e4", "workload": "production",
+                "fetch_bytes": 21.771e9, "write_bytes": 10.075e9}
 
 
 def measured_gemm_traffic(workload: str):
