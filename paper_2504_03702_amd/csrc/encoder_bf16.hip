@@ -207,23 +207,18 @@ void run_encoder_bf16(const ps_model* m, int32_t n_req, const Workspace& ws, hip
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(att, w.w_o, w.b_o, in, ws.lb, H, H, rows, nullptr, nullptr), &so, s));
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_GELU, small(x1, w.w_1, w.d_1, fold_1, g, F, H, rows, ws.ps, ws.sb), &s1, s));
                 PS_TIMED(PS_FAM_GEMM, launch_small_gemm_bf16(EPI_BIAS_RESIDUAL, small(g, w.w_2, w.b_2, mid, ws.la, H, F, rows, nullptr, nullptr), &s2, s));
+            } else if (!last) {
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb, nullptr, ws.max_rows,
+                                                       H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, &so));
+                PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, nullptr));
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr, ws.max_rows,
+                                                       F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, nullptr, nullptr, &s1));
+                PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la, nullptr, ws.max_rows,
+                                                       H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, &s2));
             } else {
-                // (a side map that its launch cannot carry comes behind it)
-                const bool o_too = !last && carries_few(ws, H), f_too = !last && carries_few(ws, F);
-                if (!last)
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, att, (const bf16_t*)w.w_o, w.b_o, in, ws.lb, nullptr, ws.max_rows,
-                                                           H, H, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, o_too ? &so : nullptr));
-                if (!o_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
-                if (!last) {
-                    PS_TIMED(PS_FAM_LAYERNORM, ln_stats(ws.sb, true, nullptr));
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_GELU, x1, (const bf16_t*)w.w_1, w.d_1, fold_1, g, nullptr, ws.max_rows,
-                                                           F, H, H, rows, &ws.meta->plan[PS_PLAN_F], clk, s, nullptr, nullptr, f_too ? &s1 : nullptr));
-                }
-                if (!f_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
-                if (!last)
-                    PS_TIMED(PS_FAM_GEMM, launch_gemm_bf16(EPI_BIAS_RESIDUAL, g, (const bf16_t*)w.w_2, w.b_2, mid, ws.la, nullptr, ws.max_rows,
-                                                           H, F, H, rows, &ws.meta->plan[PS_PLAN_H], clk, s, ws.first_row, nullptr, o_too ? &s2 : nullptr));
-                if (!o_too) PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, so, s));
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_GELU_SPLIT, s1, s));
+                PS_TIMED(PS_FAM_REFINE, launch_skinny_gemm_bf16(EPI_RESIDUAL_MAPPED, s2, s));
             }
         } else if (carried && !last) {
             SmallGemm so = side_args(ws.cls_a, w.w_od, w.b_o, in_cls, ws.lb, H, H);

@@ -80,6 +80,7 @@ struct GemmArgs {
     int64_t max_rows;            // rows of every activation buffer; also the row stride of Vt
     int N, K, hidden;
     int wgs;                     // workgroups of the map itself
+    int ahead;                   // workgroups of a side map in front of them in the grid, a multiple of 8
     const uint8_t* first_row;    // rows that a side map writes (1), for the kernels that carry one
 };
 
@@ -109,8 +110,8 @@ struct Region {
 template <bool BANDS>
 struct Walk {
     int n_tiles, m_tiles, wgs, slots, xcd, slot, full, rest, n_my;
-    __device__ __forceinline__ Walk(int m, int n, int wgs_) : n_tiles(n), m_tiles(m), wgs(wgs_) {
-        xcd = blockIdx.x & 7; slot = blockIdx.x >> 3; slots = wgs >> 3;
+    __device__ __forceinline__ Walk(int m, int n, int wgs_, int wg) : n_tiles(n), m_tiles(m), wgs(wgs_) {
+        xcd = wg & 7; slot = wg >> 3; slots = wgs >> 3;
         const int tiles = m * n;
         full = tiles / wgs;
         rest = tiles - full * wgs;
@@ -138,7 +139,7 @@ struct Walk {
 };
 
 // All tiles of a region that belong to this workgroup, by one of its wavefronts; TM: the wavefront's 32-row blocks.
-template <typename T, int WN, int TM, int EPI, bool PLANNED, bool SKIP>
+template <typename T, int WN, int TM, int EPI, bool PLANNED, bool SKIP, bool AHEAD>
 __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                              const float* __restrict__ bias, void* __restrict__ Cv, bf16_t* __restrict__ Vt,
                                              const Region& rg_, unsigned char* smem) {
@@ -157,7 +158,7 @@ __device__ __forceinline__ void region_tiles(const GemmArgs& g, const bf16_t* __
 
     // (EPI_GELU_SPLIT: small tiles, but many of them for many requests)
     constexpr bool BANDS = PLANNED || EPI == EPI_GELU_SPLIT;
-    const Walk<BANDS> walk(rg_.m_tiles, N / BN, g.wgs);
+    const Walk<BANDS> walk(rg_.m_tiles, N / BN, g.wgs, blockIdx.x - (AHEAD ? g.ahead : 0));
     const int n_my = walk.n_my;
     if (n_my == 0) return;
     // first row of a tile; the last tile is moved up where it would pass the end of the buffers (rows of two tiles are
@@ -625,24 +626,29 @@ struct SideTile {
 };
 
 // Rows in two regions: plan->m_tiles tiles of BM rows, then the others in tiles of 32 (tm0 + tm1) rows, as prep chose them
-// (PLANNED); without a plan all in tiles of BM rows.  SIDE: workgroups from g.wgs on do a per-request map; a unit that has no tile
-// in the launch's last round takes them.
+// (PLANNED); without a plan all in tiles of BM rows.  SIDE: further workgroups do a per-request map.  Behind the map's own a unit
+// that has no tile in the launch's last round takes them.  Blocks of a few requests' map beside 128 x 128 tiles (AHEAD), which take
+// as long as a tile, come first: the tiles are then dealt to the other units as long as there are any, and share one beyond.
+// Two wavefronts a SIMD: for 128 x 128 tiles two workgroups a unit, which the compiler misses by itself with a few requests' map
+// (202 + 64 registers; 216 so).  Padded calls of hidden 768, twelve layers, slots all filled, one workgroup a unit / two: 12 requests
+// 2482 / 2110 us, 16 2648 / 2314; filled to a half, where all tiles have a unit each, 1524 / 1512 and 1641 / 1621, but 5 % more
+// than the first with the side blocks behind the tiles.  12 prompts of the production encoder 3578 -> 3154 us, 8 3428 -> 2797.
 template <int BM, int BN, int WM, int WN, int EPI, bool PLANNED, int SIDE, bool FEW>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmArgs g, const int32_t* __restrict__ total_rows,
                                                                  const GemmPlan* __restrict__ plan, int64_t* __restrict__ clk,
                                                                  typename SideTile<SIDE, BM, FEW>::Args side) {
     using T = Tile<BM, BN, WM, WN>;
     using S = SideTile<SIDE, BM, FEW>;
     constexpr int kBytes = EPI == EPI_BIAS_RESIDUAL ? T::LDS : T::STRIPS;
-    constexpr bool SKIP = SIDE == EPI_RESIDUAL_MAPPED;
+    constexpr bool SKIP = SIDE == EPI_RESIDUAL_MAPPED, AHEAD = FEW && !PLANNED;
     __shared__ __align__(1024) unsigned char smem[kBytes > S::BYTES ? kBytes : S::BYTES];
     if constexpr (SIDE != kNoSide) {
-        if ((int)blockIdx.x >= g.wgs) {
+        const int b = AHEAD ? (int)blockIdx.x : (int)blockIdx.x - g.wgs;
+        if (AHEAD ? b < g.ahead : b >= 0) {
             if constexpr (FEW) {
-                if ((int)(blockIdx.x - g.wgs) * kSkinnyCols < side.N)
-                    skinny_block<SIDE, WM * WN, SIDE != EPI_RESIDUAL_MAPPED>(side, blockIdx.x - g.wgs, smem);
+                if (b * kSkinnyCols < side.N) skinny_block<SIDE, WM * WN, SIDE != EPI_RESIDUAL_MAPPED>(side, b, smem);
             } else {
-                if (threadIdx.x < 256) small_tile<SIDE, S::TM, 1, S::STAGES>(side, blockIdx.x - g.wgs, smem, nullptr);
+                if (threadIdx.x < 256) small_tile<SIDE, S::TM, 1, S::STAGES>(side, b, smem, nullptr);
             }
             return;
         }
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
     if constexpr (!PLANNED) {
         rg.row_begin = 0; rg.bm = BM; rg.tm0 = T::TM;
         rg.m_tiles = (rg.rows + BM - 1) / BM;
-        region_tiles<T, WN, T::TM, EPI, false, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+        region_tiles<T, WN, T::TM, EPI, false, SKIP, AHEAD>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
     } else {
         static_assert(T::TM == 4, "regions of 2 to 4 blocks a wavefront");
         const GemmPlan pl = *plan;
@@ -667,12 +673,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, con
             if (rg.m_tiles <= 0) break;
             if (r == 1 && pl.m_tiles > 0) dma_barrier();     // every wavefront's parked DMAs have landed
             const int tm = wave / WN == 0 ? tm0 : tm1;       // both paths meet the same barriers
-            if (tm == 4) region_tiles<T, WN, 4, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else if (tm == 3) region_tiles<T, WN, 3, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
-            else region_tiles<T, WN, 2, EPI, true, SKIP>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            if (tm == 4) region_tiles<T, WN, 4, EPI, true, SKIP, AHEAD>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else if (tm == 3) region_tiles<T, WN, 3, EPI, true, SKIP, AHEAD>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
+            else region_tiles<T, WN, 2, EPI, true, SKIP, AHEAD>(g, g.A, g.W, g.bias, g.C, g.Vt, rg, smem);
         }
     }
-    if (clk && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (clk && blockIdx.x == (AHEAD ? g.ahead : 0) && threadIdx.x == 0) {
         clk[0] = (int64_t)clock64() - clk_c0;
         clk[1] = (int64_t)wall_clock64() - clk_w0;
     }
@@ -696,10 +702,11 @@ void launch_cfg(GemmEpilogue epi, GemmArgs g, const int32_t* total_rows, const G
 #define PS_LAUNCH_SIDE(E)                                                                                                \
     do {                                                                                                                 \
         constexpr int kSide = side_of<E>;                                                                                \
-        if (few)                                                                                                         \
+        if (few) {                                                                                                       \
+            g.ahead = (int)align_up((size_t)(few->N / kSkinnyCols), 8);                                                  \
             hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kSide, true>),                              \
-                               dim3((unsigned)(g.wgs + few->N / kSkinnyCols)), block, 0, s, g, total_rows, plan, clk, *few);    \
-        else if (side)                                                                                                   \
+                               dim3((unsigned)(g.wgs + g.ahead)), block, 0, s, g, total_rows, plan, clk, *few);          \
+        } else if (side)                                                                                                   \
             hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, PLANNED, kSide, false>),                             \
                                dim3((unsigned)g.wgs + side_wgs(SideTile<kSide, BM, false>::TM)), block, 0, s, g, total_rows, plan, \
                                clk, *side);                                                                              \
@@ -734,7 +741,7 @@ void launch_gemm_bf16(GemmEpilogue epi, const bf16_t* A, const bf16_t* W, const 
     // Problems with few 256 x 256 tiles (whole calls on a micro-batch of a few requests) would leave most compute
     // units idle: 128 x 128 tiles give four times as many workgroups to spread them over.  EPI_GELU_SPLIT has only these
     // (its second set of accumulators): 4096 requests of hidden 768 in 57 us, 20000 in 234.
-    const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden, 0, first_row};
+    const GemmArgs g = {A, W, bias, residual, C, vt, max_rows, N, K, hidden, 0, 0, first_row};
     if (epi == EPI_GELU_SPLIT || !large_tiles(max_rows, N))
         launch_cfg<128, 128, 2, 2, false>(epi, g, total_rows, nullptr, clk, side, few, s);
     else

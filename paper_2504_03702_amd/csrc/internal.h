@@ -206,13 +206,6 @@ inline bool carries_side_maps(const Workspace& ws, int32_t n_req, int hidden) {
 }
 // Whether a map of `max_rows` rows takes 256 x 256 tiles.
 inline bool large_tiles(int64_t max_rows, int N) { return (max_rows + 255) / 256 * (N / 256) >= 128; }
-// Whether it can carry the side map of a few requests.  That map's blocks stream W at one unit's rate: beside a tile of 128 x 128
-// on the same unit they are what the launch waits for (12 production prompts, 352 tiles: output projection 24 us and 9 apart, 35
-// together; second feed-forward map 73 and 30, 112), on a unit of their own they are hidden.  Padded calls are taken to hold half
-// of their slots (12 padded prompts of hidden 768 1.90 -> 1.49 ms carried, 16 2.05 -> 1.67).
-inline bool carries_few(const Workspace& ws, int N) {
-    return large_tiles(ws.max_rows, N) || (ws.max_rows / (ws.padded ? 2 : 1) + 127) / 128 * (N / 128) + N / 64 <= 256;
-}
 // C[rows, N] = A[rows, K] * W^T (+ epilogue); W is [N][K] (EPI_GELU_SPLIT: [N][K / 2], A is hi | lo); rows = *total_rows (device).
 // The residual epilogues write the new sums as hi (residual.x_out) + lo (C) bf16 pairs; all epilogues write bf16.  clk (device,
 // may be null): workgroup 0 leaves {core clock cycles, constant-rate timer ticks} of its run there.
