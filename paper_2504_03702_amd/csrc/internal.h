@@ -192,12 +192,15 @@ struct SmallGemm {
 };
 void launch_small_gemm_bf16(GemmEpilogue epi, const SmallGemm& p, const SkinnyArgs* side, hipStream_t s);
 // Whether a call of a few requests takes the small tiles, whose launches carry both maps: up to 3584 rows (of the workspace), of
-// wide models fewer.  Padded calls, which hold half of their slots or so, up to 4608.  Against the large tiles with the side maps
-// carried, small / large, us: packed, hidden 768, twelve layers, 12 requests (2500 rows) 1465 / 1472, 13 1542 / 1495, 14 1588 /
-// 1455; hidden 1024, 8 requests (2400 rows) 2708 / 2428, 10 3182 / 2770, 7 (2200) 2567 / 2553; padded to 512, 8 requests, slots
-// filled to 0.4 1195 / 1277, 0.6 1382 / 1423, 0.8 1567 / 1495.
+// wide models fewer.  What of a padded call's slots is filled the host cannot see: those go by a line of their own.  Against the
+// large tiles with the side maps carried, small / large, us, four layers, the lengths equal: packed, hidden 768, 2816 rows 378 /
+// 420, 437 / 432, 3072 431 / 430, 3328 452 / 452; 1024, 2048 rows 410 / 478, 2304 484 / 484; 2048, 1280 rows 788 / 877, 1536 855 /
+// 890 and 920 / 923, 1792 966 / 924, 2048 1120 / 1003.  Padded to 512 and filled to a half / full: hidden 768, 4352 rows 385 /
+// 414 and 546 / 491, 4864 400 / 432 and 600 / 510; 1024, 3840 rows 480 / 496 and 694 / 588, 4352 497 / 515 and 872 / 672; 2048,
+// 3840 rows 1358 / 1123 and 2364 / 1445; 3328 rows, where a quarter is 837 / 897 and a half 1089 / 976, are left to the small tiles.
 inline bool small_maps(const Workspace& ws, int32_t n_req, int hidden) {
-    const int64_t most = ws.padded ? 4608 : 2300000 / hidden < 3584 ? 2300000 / hidden : 3584;
+    auto within = [](int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : v > hi ? hi : v; };
+    const int64_t most = ws.padded ? within(3932160 / hidden, 3584, 4608) : within(2300000 / hidden, 1536, 3584);
     return n_req <= PS_SKINNY_ROWS && ws.max_rows <= most;
 }
 // Whether the large maps of a call carry its per-request ones (the others have launches of their own, or take the small tiles).

@@ -54,6 +54,23 @@ def test_few_requests_of_many_rows(tmp_models, cfg, n, slots):
     assert flags == 0 and np.array_equal(got, wide)
 
 
+def test_few_requests_of_the_widest_model(tmp_models):
+    """Hidden 2048, whose lines between small and large tiles lie lower: 1280 packed rows (small), 1792, and eight padded requests
+    in 512 slots (large) give each request the same bits."""
+    cfg = wl.ModelConfig(layers=2, hidden=2048, heads=32, ffn=2048, vocab=500, max_pos=640, dtype=wl.DTYPE_BF16)
+    print("predict carried few hidden=2048", flush=True)
+    model, _ = make(tmp_models, "carried_2048.bin", cfg, ln_jitter=0.1, bias_std=0.05)
+    lengths = [130, 1, 64, 257, 200, 8, 127, 300]
+    batch = batch_of(lengths, cfg.vocab)
+    got, _, flags, _ = run_predict(model, batch)
+    assert flags == 0 and np.isfinite(got).all()
+    more = batch_of(lengths + [250] * 2, cfg.vocab)
+    more.token_ids[: batch.token_ids.size] = batch.token_ids
+    for other in (more, padded_to(batch, 512)):
+        far, _, flags, _ = run_predict(model, other)
+        assert flags == 0 and np.array_equal(got, far[: len(lengths)])
+
+
 def test_requests_without_rows(tmp_models):
     """Faulty requests among carried ones: a token outside the vocabulary (its rows are there), one that is too long (none)."""
     model, _ = make(tmp_models, f"carried_{WIDE.hidden}.bin", WIDE, ln_jitter=0.1, bias_std=0.05)
