@@ -23,8 +23,9 @@
 // A decision is some 150 instructions of one wavefront after the other (no more than one to a SIMD is at work), so their
 // number counts as well: where a bound on queues and windows allows, scores are made in one register (walk_narrow).
 // 4096 requests over 256 instances with windows of 100: 13.0 ms when four threads per instance scanned the
-// window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.06 in one register; 64
-// instances 2.06 and 1.43; by one wavefront 1.32 (solo_walk).  Scoring a request ahead and putting the last chosen instance's score right afterwards: 3.67.
+// window in registers for every request, 3.09 ms from the tables with scores in 64 bits, 2.05 in one register (1.27 by one
+// wavefront over windows that fall towards their end, solo_walk); 64 instances 2.06 and 1.46.  Scoring a request ahead and putting
+// the last chosen instance's score right afterwards: 3.67.
 #include <type_traits>
 
 #include "device_util.h"
@@ -45,7 +46,7 @@ struct RoutePlan {
     size_t lds_bytes;
 };
 
-RoutePlan plan_route(int n_inst, int window, size_t room) {
+RoutePlan plan_route(int n_inst, int window) {
     RoutePlan p;
     const int whole = (window + 3) / 4 * 4;
     for (int block = 4 * ((window + 4 * kRouteMaxBlocks - 1) / (4 * kRouteMaxBlocks));; block *= 2) {
@@ -57,7 +58,7 @@ RoutePlan plan_route(int n_inst, int window, size_t room) {
         for (int odd = 1; odd >= 0; --odd) {
             p.pitch = odd ? n_inst | 1 : n_inst;
             p.lds_bytes = 512 + (size_t)p.pitch * 4 * ((size_t)p.n_blocks * block + 2 * (size_t)(p.n_blocks + 1));
-            if (p.lds_bytes <= room) return p;
+            if (p.lds_bytes <= (size_t)kRouteLdsBytes) return p;
         }
         if (block == whole) return p;
     }
@@ -146,15 +147,35 @@ __device__ __forceinline__ bool peaks_fit(long long peak, int beta) { return pea
 // the numbers afresh while the next batch is walked; until then an instance's old numbers are a lower bound (windows only grow),
 // and F is less than P + D' above the old one, which keeps most instances below their limit: only where it does not, and the
 // instance is the choice again already, the walk waits for them.  A decision is some 110 instructions of one wavefront and no
-// exchange: 4096 requests over 256 instances of 100 slots 2052 -> 1320 us, 1450 to 2020 as calls fill the windows to their limits;
-// 100 instances 2026 -> 1260 (1690 full), 2048 requests over 128 of 64 slots 1017 -> 612, over 256 of 128 1267 -> 670, over 500
-// of 60 1445 -> 870.  Up to 64 instances a walk with the tables has no exchange either, and waits would be frequent (20 instances
-// 739 -> 820, 64 1470 -> 1280 to 1440): left to it.
+// exchange.
+//
+// What it gains is for the windows to say.  Microseconds, the tables alone / with this walk in front of them, 4096 requests over
+// instances x slots, windows that fall by half towards their end (as requests finish) | all slots near the limit | slots each on
+// their own, around the limits | windows that rise to their limits:
+//   65 x 100    2035 / 1146 | 2050 / 2050 | 2036 / 2036 | 2006 / 1864        256 x 100  2048 / 1272 | 2050 / 2050 | 2047 / 2054 | 2049 / 2055
+//   128 x 64    2031 /  977 | 2035 / 2034 | 2028 / 1893 | 2032 / 1499        256 x 128  2513 / 1307 | 2517 / 2498 | 2512 / 2498 | 2512 / 2496
+//   300 x 60    2202 / 1806 | 2239 / 2238 | 2198 / 2207 | 2237 / 2244        500 x 60   2890 / 1750 | 2892 / 2864 | 2886 / 2853 | 2886 / 2859
+// Windows whose largest w[t] + t lies at t* anywhere are the bad ones: most ramps end before, and each such request looks at windows
+// one after the other (256 x 100: 2800 us near the limit, 2680 on their own, as long as nothing stopped it).  So where most instances
+// are at their limits behind their first slot the walk does not begin, and it keeps account of its costs (solo_saves).  Short calls:
+// 32 requests over 256 x 100 34.8 / 29.5 falling, 35.0 near the limit, 36.1 on their own; 64 50.2 / 38.8, 50.5, 51.0; 256 x 100 of
+// 12, where nothing is gained, 25.1 / 25.2 to 26.5.  257 to 384 instances, whose tables cost less: 64 requests over 300 48.2 / 42.1
+// falling, but 57.3 on their own, 256 151 / 122 and 160.  Up to 64 instances a walk with the tables has no exchange either, and waits
+// would be frequent (20 instances 739 -> 820, 64 1470 -> 1280 to 1440): left to it.
 const int kSoloInstances = 512;              // eight a lane
+inline int solo_least_requests(int n_inst) { return n_inst > 256 && n_inst <= 384 ? 256 : 32; }
 const int kSoloTokens = 1 << 20;             // prompts and predictions from here on are not walked
 const int kSoloWaves = 8;
 const int kSoloBatch = 16;
-const int kSoloEffort = 96;                  // windows read and, five times each, waits for 64 requests beyond which the tables are the cheaper way
+// Which requests leave the short way is for the windows and the requests to say, so the walk keeps account of what it saves
+// against the tables and of what it pays, and leaves the rest of the call to them where the costs pass the savings.  Cycles by
+// regression over groups of 64 requests, two / four / eight instances a lane: a request 570 / 700 / 970, by the tables 1190 / 1200 /
+// 1290 to 1690; one off the short way 705 / 850 / 1220 more, a window read 690 / 870 / 1110, a wait 2400 / 2700 / 3400.  In eighths
+// of a window read: what a request saves, what a read or a request off the short way costs and a wait, how far costs may run ahead
+// of savings, and savings count on.
+template <int R>
+__device__ __forceinline__ int solo_saves(int n_inst) { return R == 2 ? 6 : R == 4 ? 4 : n_inst <= 384 ? 2 : 3; }
+const int kSoloUnit = 8, kSoloWait = 26, kSoloSlack = 32, kSoloMost = 128;
 struct SoloWalk {
     const int32_t* prompt_tokens;
     const int32_t* pred_tokens;
@@ -222,10 +243,10 @@ __device__ __forceinline__ void solo_apply(const SoloWalk& a, const SoloSlots& s
     }
 }
 
-// Wavefront 0's part; the others are in solo_follow.  Returns the first request not walked; heavy: it stopped for its effort.
+// Wavefront 0's part; the others are in solo_follow.  Returns the first request not walked.
 template <int R>
-__device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long bound, long long load_bound, bool& heavy_out) {
-    const int lane = threadIdx.x, window = a.window, beta = a.beta, beta100 = 100 * beta;
+__device__ __forceinline__ int solo_walk(const SoloWalk& a, long long bound, long long load_bound) {
+    const int lane = threadIdx.x, window = a.window, beta = a.beta, beta100 = 100 * beta, saves = solo_saves<R>(a.n_inst);
     const SoloSlots sl(a, lane);
     // score; its penalty at P = 0; an upper bound of that, above it where the penalty is an old one; t*; as its name
     int s[R], p[R], u[R], top[R], low[R], id[R];
@@ -242,10 +263,10 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
             a.added[i] = 0;
         }
     }
-    int nP = 0, nD = 0;
-    if (base + lane < a.n_req) { nP = a.prompt_tokens[base + lane]; nD = a.pred_tokens[base + lane]; }
-    bool heavy = false, drain = false, last = false;
-    int vP = 0, vDc = 0, v_add = 0, cnt = 0, most = 0, effort = 0, out_i = -1, out_s = 0, buffer = 0;
+    int base = 0, nP = 0, nD = 0;
+    if (lane < a.n_req) { nP = a.prompt_tokens[lane]; nD = a.pred_tokens[lane]; }
+    bool quit = false, drain = false, last = false;
+    int vP = 0, vDc = 0, v_add = 0, cnt = 0, most = 0, credit = 0, out_i = -1, out_s = 0, buffer = 0;
     unsigned long long todo = 0, part = 0;   // of the group: requests to walk; the batch at hand
     bool open = false;                       // a group is being walked
     for (;;) {
@@ -262,7 +283,7 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
         }
         cur = 0;
         // ---- the next group ----
-        if (!open && base < a.n_req && !heavy) {
+        if (!open && base < a.n_req && !quit) {
             cnt = min(64, a.n_req - base);
             vP = nP;
             int vD = nD;
@@ -279,7 +300,7 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
                     v_add = 100 * (vP + vD);
                     most = (int)wave_umax(good ? (unsigned)vP : 0);
                     out_i = -1;
-                    out_s = effort = 0;
+                    out_s = 0;
                     todo = __ballot(good);
                     part = (1ull << kSoloBatch) - 1;
                     open = true;
@@ -296,6 +317,7 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
             reach = (int)wave_umax((unsigned)reach);
             while (!(todo & part)) part <<= kSoloBatch;
             unsigned long long now = todo & part;
+            const unsigned long long all = now;
             int L[R], best, src, at, sure;                       // smallest score, its lane (the lowest), its place there
             auto smallest = [&](int pb) {
                 int own = L[0];
@@ -355,6 +377,7 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
                 // a ramp that ends before some t*, or an instance whose numbers are not made yet
                 const int P = __builtin_amdgcn_readlane(vP, q), Dc = __builtin_amdgcn_readlane(vDc, q);
                 const int add = __builtin_amdgcn_readlane(v_add, q), pb = beta100 * P;
+                credit -= kSoloUnit;
 #pragma unroll
                 for (int j = 0; j < R; ++j) L[j] = s[j] + max(top[j] < Dc ? p[j] + pb : low[j], 0);
                 unsigned seen = 0;                               // the lane's instances whose window has been read
@@ -376,16 +399,19 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
                         L[j] = id[j] == i ? s[j] + over : L[j];
                         seen |= id[j] == i ? 1u << j : 0u;
                     }
-                    ++effort;
+                    credit -= kSoloUnit;
                 }
                 if (!sure) {
                     drain = true;
-                    effort += 5;
+                    credit -= kSoloWait;
                     break;
                 }
                 commit(q, add, pb + beta100 * Dc);
                 now &= now - 1;
-            } while (now);
+                quit = credit + saves * (int)__popcll(all ^ now) < -kSoloSlack;
+            } while (now && !quit);
+            credit = min(credit + saves * (int)__popcll(all ^ now), kSoloMost);
+            quit |= credit < -kSoloSlack;
             todo = (todo & ~part) | now;
         } else {
             drain = false;
@@ -396,15 +422,16 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
         ((int2*)list)[lane] = make_int2(done && vDc > 0 ? out_i | vDc << 16 : -1, vP);
         if (lane == 0) *(int*)(list + 64 * 8) = last;
         buffer ^= 1;
-        if (open && !todo) {
+        if (open && (!todo || quit)) {                           // (a group left half walked goes on with the tables)
+            if (todo) cnt = __builtin_ctzll(todo);
             if (out_i >= 0) atomicAdd(a.added + out_i, vP);
             if (lane < cnt) {
                 a.assigned[base + lane] = out_i;
                 a.score100[base + lane] = out_s;
             }
-            base += 64;
+            base += cnt;
+            todo = 0;
             open = false;
-            heavy = effort > kSoloEffort;
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (last) break;
@@ -413,7 +440,6 @@ __device__ __forceinline__ int solo_walk(const SoloWalk& a, int base, long long 
 #pragma unroll
     for (int j = 0; j < R; ++j)
         if (lane * R + j < a.n_inst) a.state[64 * j + lane].x = s[j];
-    heavy_out = heavy;
     return base;
 }
 __device__ __forceinline__ void solo_follow(const SoloWalk& a, int wave) {
@@ -431,15 +457,14 @@ __device__ __forceinline__ void solo_follow(const SoloWalk& a, int wave) {
 // plan, a lane takes a block).  NARROW: with walk_narrow, for calls of 12 requests and more, where it saves over a
 // microsecond of a call by itself; its bounds cost a call of few (256 instances of 100 slots, 3 requests 27.5 us without,
 // 27.6 with, 8 30.9 and 29.8, 12 34.1 and 31.8; 64 instances 23.7 and 24.2, 26.3 and 25.9, 28.2 and 27.5).
-// SOLO: with one wavefront's walk, NARROW too; 512 threads, all of which stay (the walk's registers do not fit sixteen wavefronts).
+// SOLO: with one wavefront's walk in front of the tables' one (NARROW too); eight wavefronts stay for it.
 template <int CH, bool NARROW, bool SOLO>
-__global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_kernel(
+__global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int32_t* __restrict__ prompt_tokens, const int32_t* __restrict__ pred_tokens, int n_req, int n_inst,
     int window, int block, int n_blocks, int pitch, int32_t* __restrict__ window_tokens,
     const int32_t* __restrict__ capacity, int64_t* __restrict__ queued_p, int64_t* __restrict__ current_d, int t_mem_pct,
     int beta, int32_t* __restrict__ assigned, int64_t* __restrict__ score100, ps_status* st, int solo_at) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    constexpr int kWaves = SOLO ? kSoloWaves : 16;
     int4* s_best = (int4*)lds_raw;                               // [2][16] a wavefront's minimum: score, instance
     int4* s_win = (int4*)(lds_raw + 512);                        // [pieces][pitch]
     const int pieces = n_blocks * (block >> 2);
@@ -454,16 +479,16 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
     // nothing is ever added
     for (int t0 = 0; t0 < 4 * pieces; t0 += 64) {
         const int t = t0 + lane;
-        for (int i0 = wave; i0 < n_inst; i0 += kWaves * 8) {
+        for (int i0 = wave; i0 < n_inst; i0 += 16 * 8) {
             int v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + kWaves * u;
+                const int i = i0 + 16 * u;
                 v[u] = i < n_inst && t < window ? window_tokens[(int64_t)i * window + t] : kMin;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + kWaves * u;
+                const int i = i0 + 16 * u;
                 if (i < n_inst && t < 4 * pieces) ((int*)(s_win + (t >> 2) * pitch + i))[t & 3] = v[u];
             }
         }
@@ -480,15 +505,10 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
         s_suf[n_blocks * pitch + inst] = kMin;
     }
     if (tid < 32) s_best[tid] = make_int4(0x7fffffff, 0, 0, 0);
-    // the one wavefront's walk: its share of LDS (there with SOLO)
-    int4* const s_state = (int4*)(lds_raw + solo_at);
-    const int lanes_log2 = nw == 1 ? 0 : 32 - __builtin_clz(nw - 1);
-    int* const s_exit = (int*)(s_state + (64 << lanes_log2));
-    unsigned char* const s_lists = (unsigned char*)(s_exit + 4);
-    int* const s_added = (int*)(s_lists + 2 * kSoloList);
+    if (SOLO && tid == 0) *(int*)(lds_raw + solo_at) = 0;
     __syncthreads();
-    if (!SOLO && wave >= nw) return;
-    const bool owner = wave < nw;
+    // (all eight wavefronts of the one wavefront's walk meet the barriers up to its end)
+    if (wave >= (SOLO ? kSoloWaves : nw)) return;
 
     // One instance's window with a request's ramp added on its first Dc slots, and its two rows of block maxima:
     // all lanes of its wavefront, lane j and lane 32 + n_parts - 1 - j for part j (a piece or a block) of the window.
@@ -529,28 +549,15 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
         // keep that order
         asm volatile("" ::: "memory");
     };
-    // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
-    int par = 0;
-    // The largest of the lanes' values (0 at the least), uniform over the workgroup.
-    auto largest = [&](int top) {
-        for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
-        if (SOLO || nw > 1) {                                    // (all wavefronts of SOLO)
-            if (lane == 0) s_best[par + wave].x = top;           // (the slots that are written next)
-            __syncthreads();
-            for (int w = 0; w < (SOLO ? kWaves : nw); ++w) top = max(top, s_best[par + w].x);
-            __syncthreads();
-            if (SOLO && lane == 0) s_best[par + wave].x = 0x7fffffff;
-        }
-        return __builtin_amdgcn_readfirstlane(max(top, 0));
-    };
-
+    int last = 0;                                                // SOLO: the block that has the first largest w[t] + t
     auto make_tables = [&]() {
         if (CH > 0) {
             // every thread its own instance's rows
             if (mine) {
                 int m = kMin;
                 for (int b = 0; b < n_blocks; ++b) {
-    #pragma unroll
+                    const int was = m;
+#pragma unroll
                     for (int c = 0; c < CH; ++c) {
                         const int4 v = s_win[(b * CH + c) * pitch + inst];
                         const int t = 4 * (b * CH + c);
@@ -562,10 +569,11 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
                         if (t + 3 < window) m = max(m, (int)((unsigned)v.w + (unsigned)(t + 3)));
                     }
                     s_pre[(b + 1) * pitch + inst] = m;
+                    if (SOLO && m > was) last = b;
                 }
                 m = kMin;
                 for (int b = n_blocks - 1; b >= 0; --b) {
-    #pragma unroll
+#pragma unroll
                     for (int c = 0; c < CH; ++c) {
                         const int4 v = s_win[(b * CH + c) * pitch + inst];
                         m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
@@ -578,21 +586,29 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
             for (int i = 64 * wave; i < min(64 * wave + 64, n_inst); ++i) update(std::false_type{}, i, 0, 0);
         }
     };
+    make_tables();
+    // exchange slots alternate: one is rewritten two requests later, after the barrier of the one in between
+    int par = 0;
+    // The largest of the lanes' values (0 at the least), uniform over the workgroup.
+    auto largest = [&](int top) {
+        for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
+        if (nw > 1) {
+            if (lane == 0 && (!SOLO || wave < nw)) s_best[par + wave].x = top;   // (the slots that are written next)
+            __syncthreads();
+            for (int w = 0; w < nw; ++w) top = max(top, s_best[par + w].x);
+            __syncthreads();
+        }
+        return __builtin_amdgcn_readfirstlane(max(top, 0));
+    };
 
     const long long kNone = 0x7fffffffffffffffll;
     const int ic = mine ? inst : 0;
     const int row4 = pitch * 4, row16 = pitch * 16;              // bytes from a row of the tables to the next
+    int nP = 0, nD = 0;                                          // lane l: request l of the next 64
+    if (lane < n_req) { nP = prompt_tokens[lane]; nD = pred_tokens[lane]; }
     // The requests of one group of 64.  FAR: their tokens could take a sum, or one of the tables' w[t] + t, to 2^31, so
     // they are scored slot by slot in 64 bits.
     auto walk = [&](auto far, int base, int cnt, int vP, int vD) {
-        if (SOLO && !owner) {                                    // (along for the barriers)
-            const int n = nw > 1 ? __popcll(__ballot(lane < cnt && vP >= 0 && vD >= 0)) : 0;
-            for (int q = 0; q < n; ++q) {
-                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                par ^= 16;
-            }
-            return;
-        }
         // blocks below b lie under the request's ramp whole, block b is looked at slot by slot (where the ramp ends on
         // a block boundary that only repeats what the tables say), blocks from the next one on keep their values
         const int vDc = min(max(vD, 0), window), vb = n_blocks > 0 ? vDc / block : 0;
@@ -657,14 +673,6 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
     // request's ramp adds to the block it ends in is worked out for 64 requests at once; what it adds to a lane's slots of
     // the chosen window, while the exchange is under way.
     auto walk_narrow = [&](auto many, int base, int cnt, int vP, int vD) {
-        if (SOLO && !owner) {
-            if (many.value)
-                for (int n = __popcll(__ballot(lane < cnt && vP >= 0 && vD >= 0)); n > 0; --n) {
-                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                    par ^= 16;
-                }
-            return;
-        }
         constexpr int B = CH ? 4 * CH : 4;                       // slots of a block
         const int vDc = min(max(vD, 0), window), vb = vDc / B, vw = min(vb, n_blocks - 1);
         const int v_pre = vb * row4, v_suf = (vDc + B - 1) / B * row4, v_win = vw * (B / 4) * row16;
@@ -678,6 +686,11 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
         // lanes without an instance stay above every score
         const int lim = mine ? (int)min(thr, 0x7fffffffll) : 0x7fffffff, s0 = mine ? (int)s100 : 1 << 30;
         int s32 = s0;
+        // Where the loop starts within 32 bytes of instructions is worth up to 5 % of it.  In the kernels with one wavefront's walk
+        // it would start in a poor place; all eight measured, 4096 requests that go to the tables at once: 256 instances of 100 slots
+        // 2052 us here, 2060 to 2153 elsewhere; of 112 (CH 2) 2196, 2187 to 2284; of 128 (CH 4) 2500, 2508 to 2600.  (What stands
+        // in front of the loop moves it: to be measured again with it.)
+        if constexpr (SOLO) asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(CH == 1 ? 6 : 4));
         for (unsigned long long todo = __ballot(good); todo; todo &= todo - 1) {
             const int q = __builtin_ctzll(todo);
             const int at = __builtin_amdgcn_readlane(v_win, q);
@@ -765,81 +778,72 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
     };
     // bound: no window value is above it, load_bound: no instance's queue, a hundredfold, is (a request raises them by its
     // tokens and the window; taken afresh when that has added up).  A queue or limit below 0 counts as one without bound.
+    long long bound = largest(mine ? s_suf[ic] : kMin);
     auto load100 = [&]() { return mine ? (s100 < 0 || thr < 0 || s100 >= 1 << 30 ? 1 << 30 : (int)s100) : 0; };
-    long long bound = 0, load_bound = 0;
-    bool narrow = NARROW, tables = false;
-    // groups of 64 requests to walk with the tables before the next solo_walk; twice as many each time that one stops for
-    // too many windows read
-    int wait = 0, spell = 1;
-    int ahead = -1, nP = 0, nD = 0;                              // lane l: request ahead + l
-    for (int base = 0; base < n_req;) {
-        if (SOLO && narrow && wait == 0) {
-            int most = 0;
-            if (mine) {
-                int f = -1, t_f = window;                        // where no sum reaches 0, no ramp reaches beyond t*
-                for (int t = 0; t < window; t += 4) {
-                    const int4 v = s_win[(t >> 2) * pitch + inst];
-                    const int x[4] = {v.x, v.y, v.z, v.w};       // (slots behind the window hold the minimum)
+    bool narrow = NARROW;
+    long long load_bound = narrow ? largest(load100()) : 0;
+    int walked = 0;                                              // requests that one wavefront's walk has done
+    if constexpr (SOLO) {
+        const int lanes_log2 = 32 - __builtin_clz(nw - 1);
+        int* const words = (int*)(lds_raw + solo_at);            // [4] instances at their limits, requests walked
+        int4* const state = (int4*)(words + 4);
+        unsigned char* const lists = (unsigned char*)(state + (64 << lanes_log2));
+        const SoloWalk a = {prompt_tokens, pred_tokens, n_req, n_inst, window, pitch, beta, (int*)s_win, lanes_log2, state,
+                            (int*)(lists + 2 * kSoloList), lists, assigned, score100, st};
+        int4* const own = state + solo_at_state(a, ic);
+        bool late = false;                                       // at its limit, but not from the first slot on
+        if (mine) {
+            // (where no sum reaches 0, no ramp reaches beyond t*)
+            const int f = s_pre[n_blocks * pitch + inst], most = max(s_suf[inst], 0), lim = (int)min(thr, 0x7fffffffll);
+            int t_f = window;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int at = (int)((unsigned)x[e] + (t + e < window ? (unsigned)(t + e) : 0u));
-                        most = max(most, x[e]);
-                        if (at > f) { f = at; t_f = t + e; }
-                    }
-                }
-                const int lim = (int)min(thr, 0x7fffffffll);
-                s_state[(inst & ((1 << lanes_log2) - 1)) * 64 + (inst >> lanes_log2)] =
-                    solo_numbers(max(f, 0), t_f, most, lim, beta);
-                s_added[inst] = (int)s100;
+            for (int c = CH - 1; c >= 0; --c) {
+                const int t = 4 * (last * CH + c);
+                const int4 v = s_win[(last * CH + c) * pitch + inst];
+                if (t + 3 < window && (int)((unsigned)v.w + (unsigned)(t + 3)) == f) t_f = t + 3;
+                if (t + 2 < window && (int)((unsigned)v.z + (unsigned)(t + 2)) == f) t_f = t + 2;
+                if (t + 1 < window && (int)((unsigned)v.y + (unsigned)(t + 1)) == f) t_f = t + 1;
+                if (t < window && (int)((unsigned)v.x + (unsigned)t) == f) t_f = t;
             }
-            bound = largest(most);
-            load_bound = largest(load100());
-            const SoloWalk a = {prompt_tokens, pred_tokens, n_req, n_inst, window, pitch, beta, (int*)s_win, lanes_log2, s_state, s_added,
-                                s_lists, assigned, score100, st};
-            if (!peaks_fit(bound, beta) || load_bound >= 1 << 29) {
-                narrow = false;                                  // (neither ever falls)
-                continue;
-            }
+            if (f < 0) t_f = window;
+            late = t_f > 0 && 100ll * f > lim;
+            *own = solo_numbers(max(f, 0), t_f, most, lim, beta);
+            a.added[inst] = (int)s100;
+        }
+        const int n_late = __popcll(__ballot(late));
+        if (lane == 0 && wave < nw) atomicAdd(words, n_late);
+        __syncthreads();
+        if (peaks_fit(bound, beta) && load_bound < 1 << 29 && 2 * words[0] <= n_inst) {
             if (wave == 0) {
-                bool heavy;
-                const int to = nw == 2   ? solo_walk<2>(a, base, bound, load_bound, heavy)
-                               : nw <= 4 ? solo_walk<4>(a, base, bound, load_bound, heavy)
-                                         : solo_walk<8>(a, base, bound, load_bound, heavy);
-                if (lane == 0) { s_exit[0] = to; s_exit[1] = heavy; }
+                const int to = nw == 2   ? solo_walk<2>(a, bound, load_bound)
+                               : nw <= 4 ? solo_walk<4>(a, bound, load_bound)
+                                         : solo_walk<8>(a, bound, load_bound);
+                if (lane == 0) words[1] = to;
             } else {
                 solo_follow(a, wave);
             }
             __syncthreads();
+            walked = __builtin_amdgcn_readfirstlane(words[1]);
+        }
+        if (wave >= nw) return;
+        if (walked > 0) {
             if (mine) {
-                const int rise = s_state[(inst & ((1 << lanes_log2) - 1)) * 64 + (inst >> lanes_log2)].x - (int)s100, dP = s_added[inst];
+                const int rise = own->x - (int)s100, dP = a.added[inst];
                 s100 += rise;
                 qp += dP;
                 cd += rise / 100 - dP;
             }
-            const int to = __builtin_amdgcn_readfirstlane(s_exit[0]);
-            const bool heavy = __builtin_amdgcn_readfirstlane(s_exit[1]);
-            if (heavy) {
-                wait = spell;
-                spell = min(2 * spell, 64);
-            } else {
-                spell = 1;
-                if (to == base) wait = 1;                        // (the bounds of this group do not do)
+            if (walked < n_req) {
+                make_tables();
+                bound = largest(mine ? s_suf[ic] : kMin);
+                load_bound = largest(load100());
+                if (walked + lane < n_req) { nP = prompt_tokens[walked + lane]; nD = pred_tokens[walked + lane]; }
             }
-            base = to;
-            tables = false;
-            continue;
         }
-        if (!tables) {
-            make_tables();
-            tables = true;
-            bound = largest(mine ? s_suf[ic] : kMin);
-            if (narrow) load_bound = largest(load100());
-        }
-        const int cnt = min(64, n_req - base);
-        if (ahead != base && lane < cnt) { nP = prompt_tokens[base + lane]; nD = pred_tokens[base + lane]; }
-        const int vP = nP, vD = nD;
-        ahead = base + 64;
-        if (ahead + lane < n_req) { nP = prompt_tokens[ahead + lane]; nD = pred_tokens[ahead + lane]; }
+    }
+    for (int base = walked; base < n_req; base += 64) {
+        const int cnt = min(64, n_req - base), vP = nP, vD = nD;
+        if (base + 64 + lane < n_req) { nP = prompt_tokens[base + 64 + lane]; nD = pred_tokens[base + 64 + lane]; }
         // largest prompt and prediction of the group
         int most = lane < cnt ? max(vP, 0) : 0, most_d = lane < cnt ? max(vD, 0) : 0;
         for (int o = 32; o > 0; o >>= 1) {
@@ -858,16 +862,12 @@ __global__ __launch_bounds__(SOLO ? 64 * kSoloWaves : kRouteThreads) void route_
             }
         }
         if (NARROW && narrow && fits()) {
-            if (nw > 1) walk_narrow(std::true_type{}, base, cnt, vP, vD);
+            if (SOLO || nw > 1) walk_narrow(std::true_type{}, base, cnt, vP, vD);
             else walk_narrow(std::false_type{}, base, cnt, vP, vD);
         } else if (bound + rise >= 2147483647ll) walk(std::true_type{}, base, cnt, vP, vD);
         else walk(std::false_type{}, base, cnt, vP, vD);
         bound += rise;
         load_bound += load_rise;
-        base += 64;
-        if (wait > 0) --wait;
-        // (solo_walk's wavefront goes on with windows that others have written)
-        if (SOLO && wait == 0) __syncthreads();
     }
     if (range_fault) report_fault(st, PS_ST_RANGE, -1);
     if (mine) { queued_p[inst] = qp; current_d[inst] = cd; }
@@ -1134,7 +1134,7 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     // last one, a single block per window, takes less)
     const size_t map_bytes = (size_t)n_inst * 20 + (size_t)n_inst * window * 4 + 20928;
     if (map_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
-    RoutePlan p = plan_route(n_inst, window, kRouteLdsBytes);
+    RoutePlan p = plan_route(n_inst, window);
     if (p.lds_bytes > (size_t)kRouteLdsBytes) return PS_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
@@ -1168,7 +1168,7 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
         lds_attr_set = true;
     }
 #define PS_ROUTE(CH, NARROW, SOLO)                                                                                       \
-    hipLaunchKernelGGL((route_kernel<CH, NARROW, SOLO>), dim3(1), dim3(SOLO ? 64 * kSoloWaves : kRouteThreads), p.lds_bytes, s,    \
+    hipLaunchKernelGGL((route_kernel<CH, NARROW, SOLO>), dim3(1), dim3(kRouteThreads), p.lds_bytes, s,    \
                        prompt_tokens, pred_tokens, n_req, n_inst, window, p.block, p.n_blocks, p.pitch, window_tokens,   \
                        capacity, queued_p, current_d, t_mem_pct, beta, assigned, score100, status, solo_at)
 #define PS_ROUTE_CH(CH)                                \
@@ -1180,15 +1180,11 @@ extern "C" int ps_route(const int32_t* prompt_tokens, const int32_t* pred_tokens
     int solo_at = 0;
     if (tables_pay(n_req, window, p)) {
         const bool narrow = n_req >= 12;
-        if (narrow && by_piece(p) && n_inst > 64 && n_inst <= kSoloInstances) {
-            // room for one wavefront's walk, if need be with the next larger blocks
-            const size_t more = solo_lds_bytes(n_inst);
-            const RoutePlan smaller = plan_route(n_inst, window, kRouteLdsBytes - more);
-            if (by_piece(smaller) && (smaller.lds_bytes + 15) / 16 * 16 + more <= (size_t)kRouteLdsBytes) {
-                p = smaller;
-                solo_at = (int)((p.lds_bytes + 15) / 16 * 16);
-                p.lds_bytes = solo_at + more;
-            }
+        // one wavefront's walk, where there is room for it beside the tables
+        const size_t at = (p.lds_bytes + 15) / 16 * 16, more = solo_lds_bytes(n_inst);
+        if (n_req >= solo_least_requests(n_inst) && by_piece(p) && n_inst > 64 && n_inst <= kSoloInstances && at + more <= (size_t)kRouteLdsBytes) {
+            solo_at = (int)at;
+            p.lds_bytes = at + more;
         }
         if (!by_piece(p)) PS_ROUTE(0, false, false);
         else if (p.block == 4) PS_ROUTE_CH(1);

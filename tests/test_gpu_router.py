@@ -157,19 +157,26 @@ def test_values_that_pass_the_bounds_of_the_short_form(K, l, beta, peak, queued)
 
 
 @pytest.mark.parametrize("K,l,n", [(1, 16, 70), (5, 100, 300), (64, 128, 200), (65, 33, 130), (130, 100, 400),
-                                   (256, 100, 1000), (256, 128, 150), (300, 60, 200), (700, 40, 300), (1000, 30, 300)])
-@pytest.mark.parametrize("load", ["free", "mixed", "filling", "ties", "all over", "one by one"])
-def test_walk_in_order_of_scores(K, l, n, load):
-    """Requests that go to the smallest queue while every window is below its limit (the sorted walk), with instances over
-    and near their limits among them, limits reached on the way, equal scores, requests that add nothing, faulty ones and
-    lists that end inside a group of 64.  Integers: everything must match."""
-    print(f"route sorted K={K} l={l} n={n} {load}", flush=True)
+                                   (256, 100, 1000), (256, 128, 150), (300, 60, 200), (700, 40, 300), (1000, 30, 300),
+                                   # one wavefront's walk: beside larger blocks, without room for it, and at its most instances
+                                   (250, 125, 300), (260, 100, 300), (512, 56, 200), (500, 60, 300), (513, 56, 200), (70, 50, 31),
+                                   (70, 50, 32)])
+@pytest.mark.parametrize("load", ["free", "mixed", "filling", "ties", "all over", "one by one", "uneven", "rising"])
+def test_walks_over_free_and_full_windows(K, l, n, load):
+    """Windows below their limits, over and near them, limits reached on the way, equal scores, requests that add nothing,
+    faulty ones and lists that end inside a group of 64: what one wavefront walks to the end, does not begin or leaves on the
+    way to the tables.  Integers: everything must match."""
+    print(f"route walks K={K} l={l} n={n} {load}", flush=True)
     rng = np.random.default_rng(K * 131 + l + n)
     P, D, win, cap, qp, cd = random_case(rng, K, l, n, False)
-    level = {"free": 0.1, "mixed": 1.0, "filling": 0.0, "ties": 0.0, "all over": 1.0, "one by one": 0.0}[load]
+    level = {"free": 0.1, "mixed": 1.0, "filling": 0.0, "ties": 0.0, "all over": 1.0, "one by one": 0.0}.get(load, 0.0)
     win = np.rint(rng.random((K, 1)) * level * cap[:, None] * (1.0 - 0.5 * np.arange(l) / l)).astype(np.int64)
     if load == "all over":
         win += cap[:, None]
+    if load == "uneven":                                        # most requests' windows have to be read, after a while
+        win = rng.integers(0, 200_000, (K, l))
+    if load == "rising":
+        win = np.rint(rng.random((K, 1)) * cap[:, None] * (0.5 + 0.5 * np.arange(l) / l)).astype(np.int64)
     if load == "filling":                                       # some requests each before the limit
         cap = 600 + 40 * np.arange(K) % 3000
     if load == "ties":
@@ -190,6 +197,46 @@ def test_walk_in_order_of_scores(K, l, n, load):
     assert flags == (ps.PS_ST_BAD_RECORD if bad.any() else 0)
     assert np.array_equal(a[ok], ra) and np.array_equal(s[ok], rs) and (a[bad] == -1).all() and (s[bad] == 0).all()
     assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
+@pytest.mark.parametrize("what", ["prompt", "prediction"])
+@pytest.mark.parametrize("at", [0, 63, 64, 150, 259])
+def test_a_huge_request_between_ordinary_ones(what, at):
+    """A request of 2^20 tokens ends one wavefront's walk at the group it is in; those after it go on from its state."""
+    print(f"route huge {what} at {at}", flush=True)
+    rng = np.random.default_rng(at)
+    P, D, win, cap, qp, cd = random_case(rng, 130, 40, 260, False)
+    win = np.rint(rng.random((130, 1)) * 0.5 * cap[:, None] * (1.0 - 0.5 * np.arange(40) / 40)).astype(np.int64)
+    (P if what == "prompt" else D)[at] = 1 << 20
+    a, s, w, q2, c2, flags, _ = run_route(P, D, win, cap, qp, cd)
+    ra, rs, rw, rq, rc = orr.route(P, D, win, cap, qp, cd)
+    assert flags == 0
+    assert np.array_equal(a, ra) and np.array_equal(s, rs)
+    assert np.array_equal(w, rw) and np.array_equal(q2, rq) and np.array_equal(c2, rc)
+
+
+def test_windows_at_their_limits_go_by_the_tables():
+    """4096 requests over full windows of 256 instances take no longer than the tables do (1.4 times as long as over 64
+    instances, where there is no other walk; 1.9 when one wavefront read every window over and over)."""
+    def fastest(K):
+        rng = np.random.default_rng(K)
+        P, D, _, cap, qp, cd = random_case(rng, K, 100, 4096, False)
+        win = np.rint(cap[:, None] * (0.78 + 0.06 * rng.random((K, 100)))).astype(np.int64)
+        t32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(DEV)
+        t64 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int64)).to(DEV)
+        P, D, win, cap, qp, cd = t32(P), t32(D), t32(win).reshape(-1), t32(cap), t64(qp), t64(cd)
+        a, s, took = t32(np.zeros(4096)), t64(np.zeros(4096)), []
+        for _ in range(8):
+            state = win.clone(), qp.clone(), cd.clone()
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            ps.ps_route(P, D, K, 100, state[0], cap, state[1], state[2], a, s)
+            e[1].record()
+            torch.cuda.synchronize()
+            took.append(e[0].elapsed_time(e[1]))
+        return min(took)
+    one, several = fastest(64), fastest(256)
+    assert several < 1.6 * one, (one, several)
 
 
 def test_state_of_an_instance_with_huge_queues():

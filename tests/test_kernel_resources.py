@@ -58,3 +58,10 @@ def test_maps_in_tiles_of_128_rows_leave_room_for_two(kernels):
     assert any("true>" in n for n in small)                      # those that carry the maps of a few requests among them
     assert {n: workgroups_a_unit(k) for n, k in small.items() if workgroups_a_unit(k) < 2} == {}
     assert {n: k for n, k in small.items() if k["vgpr_spill_count"]} == {}
+
+
+def test_short_router_calls_keep_their_scalars(kernels):
+    """A decision is a chain of some 150 instructions, so scalars that do not fit their registers are paid for by every request of
+    a call of few (19 of them: 2 to 3 % of 3 to 11 requests)."""
+    few = {n: k for n, k in kernels.items() if re.match(r"route_kernel<[124], false", n)}
+    assert few and {n: k for n, k in few.items() if k["sgpr_spill_count"] > 10 or k["vgpr_spill_count"]} == {}
