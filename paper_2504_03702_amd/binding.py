@@ -4,11 +4,13 @@ Argument marshalling only: tensors supply device pointers, ``torch.cuda.current_
 stream; every step of the path runs in the library's HIP kernels.  There is no fallback: if the
 library is missing or there is no GPU the calls raise.  The calls with nothing to object to are
 marshalled by an extension module (``csrc/marshal.cpp``); what it hands back is marshalled here,
-with the checks that say what is wrong."""
+with the checks that say what is wrong, and so is every call where the module is not built."""
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -44,7 +46,7 @@ class ps_status(ctypes.Structure):
 
 
 _lib = None
-_native = None          # the extension module, bound to the loaded library
+_native = None          # the extension module, bound to the loaded library; None where there is none
 
 
 def load_library() -> ctypes.CDLL:
@@ -94,12 +96,24 @@ def load_library() -> ctypes.CDLL:
     lib.ps_profile_stream_read.argtypes = [vp, ctypes.c_int64, vp, vp]
     lib.ps_strerror.restype = ctypes.c_char_p
     lib.ps_strerror.argtypes = [ctypes.c_int]
-    from . import _marshal
-    _marshal.bind(*[ctypes.cast(getattr(lib, "ps_" + name), vp).value for name in (
-        "predict_load", "anticipate", "anticipate_static", "lookahead_update", "scaler_scan", "route", "forecast")])
-    _native = _marshal
+    _native = _extension()
+    if _native is not None:
+        _native.bind(*[ctypes.cast(getattr(lib, "ps_" + name), vp).value for name in (
+            "predict_load", "anticipate", "anticipate_static", "lookahead_update", "scaler_scan", "route", "forecast")])
     _lib = lib
     return lib
+
+
+def _extension():
+    """The extension module, None if it is not there or does not load (built for another torch): calls then take some
+    microseconds more."""
+    try:
+        return importlib.import_module("._marshal", __package__)
+    except ModuleNotFoundError:
+        return None
+    except ImportError as e:
+        warnings.warn(f"calls go by ctypes: {e}")
+        return None
 
 
 def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, name: str) -> Optional[int]:

@@ -3,6 +3,8 @@ No compute calls: this runs without a GPU."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -59,3 +61,28 @@ def test_bad_model_files_are_rejected(lib, tmp_path):
     trunc = tmp_path / "trunc.bin"
     trunc.write_bytes(raw[:-4])
     assert lib.ps_model_load(os.fsencode(str(trunc)), 0, ctypes.byref(out)) == -3
+
+
+@pytest.mark.parametrize("module", ["missing", "broken", "there"])
+def test_library_loads_without_the_marshalling_module(lib, tmp_path, module):
+    """The library alone is enough: calls are marshalled by the binding itself where the extension module is missing or does
+    not load."""
+    from paper_2504_03702_amd import build
+    package = tmp_path / "paper_2504_03702_amd"
+    package.mkdir()
+    for name in os.listdir(build.HERE):
+        if name.endswith(".py") or name == "libpreserve.so":
+            os.symlink(os.path.join(build.HERE, name), package / name)
+    ext = package / os.path.basename(build.MARSHAL)
+    if module == "broken":
+        ext.write_bytes(b"no shared object")
+    elif module == "there":
+        if not os.path.exists(build.MARSHAL):
+            build.build_library(verbose=False)
+        os.symlink(build.MARSHAL, ext)
+    code = ("import warnings; warnings.simplefilter('ignore')\n"
+            "from paper_2504_03702_amd import binding as b\n"
+            "print(b.__file__, b.load_library().ps_anticipate_workspace_bytes(4096, 256, 600) > 0, b._native is not None)")
+    out = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.split() == [str(package / "binding.py"), "True", str(module == "there")]
