@@ -28,17 +28,25 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak
 # Bytes that left the L2 caches per large-GEMM launch (average over the 61 launches of a production
 # step), from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; profiles/production_gemm_traffic.txt)
 # scaled by what the same counters read for a 1 GiB elementwise copy (x2.0 and x1.0).  Valid only for
-# the kernel source it was measured on: reported as null once that file has changed.
-GEMM_TRAFFIC = {"source_sha256_16": "82767097dfbd03e4", "workload": "production",
-                "fetch_bytes": 21.771e9, "write_bytes": 10.075e9}
+# the sources it was measured on, the kernel's and those it takes its tiles, parts and launch from:
+# reported as null once one of them has changed.
+GEMM_SOURCES = ("gemm_bf16.hip", "internal.h", "device_util.h", "small_gemm.h", "skinny_gemm.h", "rowops.hip")
+GEMM_TRAFFIC = {"source_sha256_16": "4cc68f70599a4cb5", "workload": "production",
+                "fetch_bytes": 21.707e9, "write_bytes": 10.075e9}
+
+
+def gemm_sources_digest():
+    import hashlib
+    digest = hashlib.sha256()
+    for name in GEMM_SOURCES:
+        with open(os.path.join(ROOT, "paper_2504_03702_amd", "csrc", name), "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()[:16]
 
 
 def measured_gemm_traffic(workload: str):
-    import hashlib
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2504_03702_amd", "csrc", "gemm_bf16.hip")
     try:
-        with open(src, "rb") as f:
-            digest = hashlib.sha256(f.read()).hexdigest()[:16]
+        digest = gemm_sources_digest()
     except OSError:
         return None
     if digest != GEMM_TRAFFIC["source_sha256_16"] or workload != GEMM_TRAFFIC["workload"]:

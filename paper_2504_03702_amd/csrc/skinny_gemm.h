@@ -4,12 +4,12 @@
 //   C[r, n] = sum_k A[r, k] * W[n, k]  for r < 16, then the same epilogues as the tiled GEMM's per-request forms.
 //
 // With so few rows the map is a stream over W: a tiled kernel would put one tile on a handful of compute units and
-// walk the whole contraction there, slice after slice, each waiting out a trip to memory.  Here a workgroup owns 64
-// output columns (or 32) and the contraction is split in 8 shares, dealt to its wavefronts: each issues
+// walk the whole contraction there, slice after slice, each waiting out a trip to memory.  Here a workgroup owns 64, 32
+// or 16 output columns (16 G) and the contraction is split in 8 shares, dealt to its wavefronts: each issues
 // v_mfma_f32_16x16x32_bf16 on fragments loaded straight from global memory (A: request r = lane % 16, sixteen
 // consecutive k per lane and 64-deep round; W the same with its row = output column), several rounds' loads
 // requested before the first is used.  Where A carries each value as hi + lo, a W fragment serves both parts.  The
-// shares' partial 16 x 64 results are added through LDS in a fixed order; one wavefront applies the epilogue.  The
+// shares' partial 16 x 16 G results are added through LDS in a fixed order; one wavefront applies the epilogue.  The
 // result does not depend on the number of wavefronts (8 in the kernel of its own, 4 where the block shares a launch
 // with the map of all rows), but it differs from the tiled kernels' in the last bits (another order of additions),
 // so a request's prediction in a call of at most 16 requests need not be bit-equal to the same request's in a larger
@@ -25,7 +25,7 @@ typedef __bf16 sk_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sk_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSkinnyShares = 8;     // parts of the contraction, added in this order
-constexpr int kSkinnyCols = 64;      // output columns per workgroup: one piece of the rows' partial statistics
+constexpr int kSkinnyCols = 64;      // most output columns per workgroup: one piece of the rows' partial statistics
 constexpr int kSkinnyLds = kSkinnyShares * 4 * 64 * 16 + 4 * 64 * 16 + 16 * 8;
 
 // sum over the 16 lanes that share lane / 16, every one of them gets it; fixed order

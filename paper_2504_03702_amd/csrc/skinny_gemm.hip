@@ -15,8 +15,8 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void skinny_gemm_kernel(SkinnyAr
 
 // Requirements: at most 16 rows in use (A holds at least 16 rows, the unused ones finite), N % 64 == 0,
 // K % 64 == 0 (both hold for every per-request map of a bf16 model: K is its hidden or feed-forward width).
-// EPI_RESIDUAL_MAPPED takes A as [16][2K] (hi | lo) and leaves no pieces (res.pstats is null); EPI_GELU_SPLIT and EPI_Q_MAPPED read the stream rows of
-// the requests' first tokens.
+// EPI_RESIDUAL_MAPPED takes A as [16][2K] (hi | lo) and leaves no pieces (res.pstats is null); EPI_GELU_SPLIT and
+// EPI_Q_MAPPED read the stream rows of the requests' first tokens.
 void launch_skinny_gemm_bf16(GemmEpilogue epi, const SkinnyArgs& p, hipStream_t s) {
     const dim3 grid((unsigned)(p.N / kSkinnyCols)), block(kSkinnyWaves * 64);
     switch (epi) {
