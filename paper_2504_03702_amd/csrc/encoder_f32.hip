@@ -474,21 +474,51 @@ __global__ __launch_bounds__(256) void layernorm_f32_kernel(const float* __restr
     for (int i = lane; i < H; i += 64) out[row * H + i] = (x[i] - mean) * rstd * gamma[i] + beta[i];
 }
 
-// LayerNorm of the rows that the maps above could take themselves, in calls of many rows: eight lanes a row, the same sums in
-// the same order.
-__global__ __launch_bounds__(256) void layernorm_f32_narrow_kernel(const float* __restrict__ in, float* __restrict__ out,
-                                                                   const float* __restrict__ gamma,
-                                                                   const float* __restrict__ beta, float eps, int H,
-                                                                   const BatchMeta* meta) {
-    const int64_t row = (int64_t)blockIdx.x * 32 + (threadIdx.x >> 3);
-    if (row >= meta->total_rows) return;          // eight lanes together
-    const float* x = in + row * H;
-    const float2 st = narrow_moments(x, H, eps, threadIdx.x & 7);
-    for (int i = 4 * (threadIdx.x & 7); i < H; i += 32) {
-        const float4 v = *(const float4*)(x + i), g = *(const float4*)(gamma + i), b = *(const float4*)(beta + i);
-        *(float4*)(out + row * H + i) = make_float4(fmaf((v.x - st.x) * st.y, g.x, b.x), fmaf((v.y - st.x) * st.y, g.y, b.y),
-                                                    fmaf((v.z - st.x) * st.y, g.z, b.z), fmaf((v.w - st.x) * st.y, g.w, b.w));
+// LayerNorm of the rows that the maps above could take themselves, in calls of many rows: eight lanes a row (narrow_moments' parts),
+// the same sums in the same order.  A lane has its part of the row, of Q = H / 32 groups (at most QM), in registers: one trip to
+// memory, and eight rows make a workgroup (THREADS 64), so that a call of some hundred rows has many units at it.  Two layers of
+// hidden 256, 1540 rows: 192 us a call with a wavefront a row, 198 with 32 rows a workgroup and a trip for each pass, 187; 192 wide
+// 166, 167, 162; 128 113, 113, 110; 12000 rows of 256 790, 787, 784.  Rows of 64 and less keep 32 a workgroup (1 % of a call).
+template <int QM, int THREADS>
+__global__ __launch_bounds__(THREADS) void layernorm_f32_narrow_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                                  const float* __restrict__ gamma,
+                                                                  const float* __restrict__ beta, float eps, int H,
+                                                                  const BatchMeta* meta) {
+    const int64_t row = (int64_t)blockIdx.x * (THREADS / 8) + (threadIdx.x >> 3);
+    const int total = meta->total_rows;           // looked at when the loads are on their way (all rows lie in the buffers)
+    const int part = threadIdx.x & 7, Q = H / 32, at = 8 * Q * (part >> 1) + 4 * (part & 1);
+    const float* x = in + row * H + at;
+    float4 v[QM], g[QM], b[QM];
+#pragma unroll
+    for (int u = 0; u < QM; ++u) v[u] = *(const float4*)(x + 8 * min(u, Q - 1));
+#pragma unroll
+    for (int u = 0; u < QM; ++u) {
+        g[u] = *(const float4*)(gamma + at + 8 * min(u, Q - 1));
+        b[u] = *(const float4*)(beta + at + 8 * min(u, Q - 1));
     }
+    asm volatile("" ::: "memory");
+    if (row >= total) return;                     // eight lanes together
+    auto all = [](float t) {
+        t += __shfl_xor(t, 1, 64);
+        t += __shfl_xor(t, 2, 64);
+        return t + __shfl_xor(t, 4, 64);
+    };
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int u = 0; u < QM; ++u)
+        if (u < Q) sum += narrow_quad(v[u].x, v[u].y, v[u].z, v[u].w);
+    const float mean = all(sum) / (float)H;
+#pragma unroll
+    for (int u = 0; u < QM; ++u) {
+        v[u].x -= mean; v[u].y -= mean; v[u].z -= mean; v[u].w -= mean;
+        if (u < Q) sq += narrow_squares(v[u].x, v[u].y, v[u].z, v[u].w);
+    }
+    const float rstd = 1.0f / sqrtf(all(sq) / (float)H + eps);
+#pragma unroll
+    for (int u = 0; u < QM; ++u)
+        if (u < Q)
+            *(float4*)(out + row * H + at + 8 * u) = make_float4(fmaf(v[u].x * rstd, g[u].x, b[u].x), fmaf(v[u].y * rstd, g[u].y, b[u].y),
+                                                                 fmaf(v[u].z * rstd, g[u].z, b[u].z), fmaf(v[u].w * rstd, g[u].w, b[u].w));
 }
 
 template <int EPI, int TM>
@@ -594,9 +624,15 @@ void run_encoder_f32(const ps_model* m, int32_t n_req, const Workspace& ws, hipS
         return;                                                  // (the head takes the last LayerNorm)
     }
     auto layer_norm = [&](float* out, const float* gamma, const float* beta) {
-        if (narrow_norms(f))
-            hipLaunchKernelGGL(layernorm_f32_narrow_kernel, dim3(row_blocks / 8), dim3(256), 0, s, y, out, gamma, beta, m->ln_eps, H, ws.meta);
-        else
+        auto narrow = [&](auto kernel, unsigned threads) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(ws.max_rows / (threads / 8))), dim3(threads), 0, s, y, out, gamma, beta, m->ln_eps, H,
+                               ws.meta);
+        };
+        if (narrow_norms(f)) {
+            if (H <= 64) narrow(layernorm_f32_narrow_kernel<2, 256>, 256);
+            else if (H <= 128) narrow(layernorm_f32_narrow_kernel<4, 64>, 64);
+            else narrow(layernorm_f32_narrow_kernel<8, 64>, 64);
+        } else
             hipLaunchKernelGGL(layernorm_f32_kernel, dim3(row_blocks), dim3(256), 0, s, y, out, gamma, beta, m->ln_eps, H, ws.meta);
     };
     for (int l = 0; l < f.layers; ++l) {

@@ -65,3 +65,11 @@ def test_short_router_calls_keep_their_scalars(kernels):
     a call of few (19 of them: 2 to 3 % of 3 to 11 requests)."""
     few = {n: k for n, k in kernels.items() if re.match(r"route_kernel<[124], false", n)}
     assert few and {n: k for n, k in few.items() if k["sgpr_spill_count"] > 10 or k["vgpr_spill_count"]} == {}
+
+
+def test_layer_norms_of_narrow_rows_spread_over_the_units(kernels):
+    """Rows of 128 to 256 floats: eight to a workgroup, all of a row in registers (32 to a workgroup and a trip to memory for each
+    pass made calls of some 1500 rows 3 % slower than a wavefront a row)."""
+    narrow = {n: k for n, k in kernels.items() if re.match(r"layernorm_f32_narrow_kernel<[48]", n)}
+    assert len(narrow) == 2
+    assert {n: k for n, k in narrow.items() if k["max_flat_workgroup_size"] != 64 or k["vgpr_spill_count"] or k["sgpr_spill_count"]} == {}
