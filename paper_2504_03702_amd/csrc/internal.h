@@ -152,7 +152,15 @@ struct ResidualSrc {
 // apart / carried: six-layer encoder 17 requests 0.839 / 0.732, 40 1.213 / 1.046, 128 2.99 / 2.87, 256 5.25 / 5.13, 512 9.77 / 9.66;
 // padded twelve-layer 33 2.80 / 2.33, 64 4.37 / 4.11, 200 10.96 / 10.75; packed 17 2.07 / 1.71, 400 20.06 / 19.82, 1024 49.8 / 49.6,
 // 2048 even; production 24 6.82 / 6.49, 100 22.6 / 22.1, 400 78.7 / 78.4.
+// In models wider than 768 the per-request tiles outgrow the idle units sooner, most of all beside short prompts, whose maps of all
+// rows are short (three layers, prompts of 4 to 12 tokens, apart / carried: hidden 1024 600 requests 0.954 / 0.919, 700 1.061 / 1.086;
+// 1280 400 1.012 / 0.972, 500 1.132 / 1.151; 1536 400 1.278 / 1.227, 700 1.875 / 1.943; 2048 300 1.701 / 1.612, 400 1.897 / 1.922,
+// 1000 3.97 / 4.25; of 10 to 60 tokens 1024 700 2.214 / 2.173, 1280 500 2.300 / 2.246, 1536 500 3.013 / 3.003, 1000 5.94 / 6.08, 2048
+// 400 4.069 / 4.010, 700 6.92 / 7.00, 1000 9.51 / 9.77): there requests times hidden size have a line, with fewer rows a request a
+// lower one.
 #define PS_CARRIED_REQUESTS 1024
+#define PS_CARRIED_WIDTHS (800 * 1024)
+#define PS_CARRIED_WIDTHS_SHORT (600 * 1024)
 enum SkinnyStats { SKINNY_STATS_GIVEN = 0, SKINNY_STATS_PIECES = 1, SKINNY_STATS_ROWS = 2 };
 struct SkinnyArgs {
     const bf16_t *A, *W;         // A: EPI_RESIDUAL_MAPPED only (the other two read the stream rows of the first tokens)
@@ -205,7 +213,9 @@ inline bool small_maps(const Workspace& ws, int32_t n_req, int hidden) {
 }
 // Whether the large maps of a call carry its per-request ones (the others have launches of their own, or take the small tiles).
 inline bool carries_side_maps(const Workspace& ws, int32_t n_req, int hidden) {
-    return n_req <= PS_CARRIED_REQUESTS && !small_maps(ws, n_req, hidden);
+    const int64_t most = ws.max_rows < 32 * (int64_t)n_req ? PS_CARRIED_WIDTHS_SHORT : PS_CARRIED_WIDTHS;
+    const bool fits = n_req <= PS_CARRIED_REQUESTS && (hidden <= 768 || (int64_t)n_req * hidden <= most);
+    return fits && !small_maps(ws, n_req, hidden);
 }
 // Whether a map of `max_rows` rows takes 256 x 256 tiles.
 inline bool large_tiles(int64_t max_rows, int N) { return (max_rows + 255) / 256 * (N / 256) >= 128; }

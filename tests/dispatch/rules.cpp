@@ -13,6 +13,7 @@ int main() {
         ws.max_rows = rows;
         ws.padded = padded != 0;
         if (!strcmp(rule, "small_maps")) printf("%d\n", (int)small_maps(ws, (int32_t)n_req, (int)hidden));
+        else if (!strcmp(rule, "carries_side_maps")) printf("%d\n", (int)carries_side_maps(ws, (int32_t)n_req, (int)hidden));
         else return 1;
     }
     return 0;

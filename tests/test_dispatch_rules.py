@@ -39,3 +39,14 @@ def rows_of(tokens, n_req):
 ])
 def test_small_tiles_where_they_are_faster(ask, hidden, n, length, padded, small):
     assert ask("small_maps", rows_of(n * length, n), int(padded), n, hidden) == small
+
+
+@pytest.mark.parametrize("hidden,n,length,carried", [
+    # where the launches of all rows' maps have idle units for the per-request tiles (prompts of 8 tokens, three layers, carried /
+    # apart: hidden 1024 600 requests 919 / 954 us, 700 1086 / 1061, of 35 2173 / 2214; 2048 300 1612 / 1701, 400 1922 / 1897, 1000 4252 / 3973)
+    (1024, 600, 8, True), (1024, 700, 8, False), (1024, 700, 35, True), (1280, 500, 8, False), (1280, 500, 35, True), (2048, 300, 8, True), (2048, 400, 8, False), (2048, 1000, 35, False),
+    (1536, 400, 8, True), (1536, 700, 8, False), (768, 1024, 100, True), (256, 1024, 30, True), (512, 1025, 30, False),
+    (768, 17, 30, True), (768, 16, 206, True), (768, 8, 20, False),
+])
+def test_side_maps_are_carried_where_that_is_faster(ask, hidden, n, length, carried):
+    assert ask("carries_side_maps", rows_of(n * length, n), 0, n, hidden) == carried
